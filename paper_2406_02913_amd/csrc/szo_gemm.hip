@@ -1245,14 +1245,14 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
     rc = small_m_launch_one(desc, seed, step, (float)sign * eps, 1, true, partial_area(workspace),
                             partial_area(workspace) + nb, (hipStream_t)stream);
     if (rc != SZO_OK) return rc;
-    return reduce_partials(partial_area(workspace), nb, loss_acc, (hipStream_t)stream);
+    return reduce_partials(partial_area(workspace), nb, 1.0, loss_acc, (hipStream_t)stream);
   }
   int blocks;
   plan_tiles((int)desc->M, (int)desc->N, desc->format, &blocks);
   if (blocks < 0 || blocks > kMaxLossPartials) return SZO_EUNSUPPORTED;
   rc = run_forward(desc, seed, step, sign, eps, partial_area(workspace), scale, (hipStream_t)stream);
   if (rc != SZO_OK) return rc;
-  return reduce_partials(partial_area(workspace), blocks, loss_acc, (hipStream_t)stream);
+  return reduce_partials(partial_area(workspace), blocks, 1.0, loss_acc, (hipStream_t)stream);
 }
 
 int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,

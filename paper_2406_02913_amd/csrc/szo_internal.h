@@ -31,9 +31,8 @@ inline int set_lds_limit_once(std::atomic<uint64_t>& done, const void* fn, size_
   return SZO_OK;
 }
 
-// Loss workspace: a ticket counter (first 64 bytes) followed by one fp64 partial per
-// workgroup.  The last workgroup to finish adds the partials in index order, which makes
-// the sum independent of scheduling.
+// Loss workspace: 64 reserved bytes followed by one fp64 partial per workgroup.  A kernel launched behind the one
+// that wrote them adds the partials in index order, which makes the sum independent of scheduling.
 constexpr int kMaxLossPartials = 1 << 21;       // 16 MiB: a 32-block 7B stack at 4096 tokens has 2 x 340 000 dual-sign tiles
 constexpr size_t kWorkspaceHeader = 64;
 constexpr int kMaxStepMatrices = 4096;            // descriptor table of the few-token step
@@ -41,19 +40,8 @@ constexpr size_t kTableBytesPerMatrix = 144;
 constexpr size_t kWorkspaceTableOffset = kWorkspaceHeader + sizeof(double) * (size_t)kMaxLossPartials;
 constexpr size_t kWorkspaceBytes = kWorkspaceTableOffset + kTableBytesPerMatrix * (size_t)kMaxStepMatrices;
 
-struct LossSink {
-  unsigned int* ticket;   // device; zero between calls
-  double* partials;       // device; [kMaxLossPartials]
-  double* loss_acc;       // device; += scale * total
-  double scale;
-};
-
-inline LossSink make_sink(void* workspace, double* loss_acc, double scale) {
-  return LossSink{(unsigned int*)workspace, (double*)((char*)workspace + kWorkspaceHeader), loss_acc, scale};
-}
-
-// loss_acc[0] += sum of partials[0..count) in a fixed order (one workgroup).
-int reduce_partials(const double* partials, int count, double* loss_acc, hipStream_t stream);
+// loss_acc[0] += scale * sum of partials[0..count) in a fixed order (one workgroup).
+int reduce_partials(const double* partials, int count, double scale, double* loss_acc, hipStream_t stream);
 // scalars[0] = sum partials[0..count), scalars[1] = sum partials[count..2*count), scalars[2] = SPSA g.
 int reduce_step(const double* partials, int count, float eps, double* scalars, hipStream_t stream);
 
@@ -97,38 +85,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
-}
-
-// Called by every thread of every workgroup exactly once, with the thread's partial sum.
-// `scratch` is LDS for one double per wave.  Grid is 1-D or flattened to `block_linear` of
-// `nblocks`.
-__device__ __forceinline__ void block_loss_commit(double local, double* scratch, const LossSink& sink,
-                                                  unsigned int block_linear, unsigned int nblocks) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = (blockDim.x + 63) >> 6;
-  const double w = wave_sum(local);
-  if (lane == 0) scratch[wave] = w;
-  __syncthreads();
-  __shared__ unsigned int s_last;
-  if (threadIdx.x == 0) {
-    double b = 0.0;
-    for (int i = 0; i < nwaves; ++i) b += scratch[i];
-    __hip_atomic_store(&sink.partials[block_linear], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
-    const unsigned int t = __hip_atomic_fetch_add(sink.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (t == nblocks - 1u);
-  }
-  __syncthreads();
-  if (s_last && wave == 0) {
-    __threadfence();
-    double acc = 0.0;
-    for (unsigned int i = lane; i < nblocks; i += 64)
-      acc += __hip_atomic_load(&sink.partials[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    acc = wave_sum(acc);
-    if (lane == 0) {
-      *sink.loss_acc += sink.scale * acc;
-      __hip_atomic_store(sink.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
 }
 
 }  // namespace szo
