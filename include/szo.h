@@ -189,7 +189,7 @@ int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, u
  * allocating routine (no hipMalloc / hipHostMalloc, no event creation unless szo_kernel_timing is
  * on) and can be captured into a HIP graph.
  * Limit: at most 65 536 workgroups per sign over the whole step (one per 256 x 256 output tile, or
- * per 128 x 128 tile for small layers, or per 256-column strip and slice of token rows of a few-token
+ * per 128 x 128 tile for small layers, or per 64- or 256-column strip and slice of token rows of a few-token
  * layer): beyond that SZO_EUNSUPPORTED, with nothing enqueued.  A Llama-2-7B decoder block at 4096
  * tokens has 3 088 per sign.
  * All calls on one GPU share that array: calls that overlap in time on one GPU (different streams
@@ -298,7 +298,8 @@ int szo_debug_zbar(uint64_t nnz_base, int64_t nnz, uint64_t seed, uint64_t step,
  * both forwards of 256 x 128 outputs and dequantises the weights once -- unless a layer has x_minus,
  * 7 = as 0 and the few-token path loads its codes as a non-temporal stream in every launch with one slice
  * of token rows per strip (by default only when the launch streams more codes than the last-level cache
- * holds).
+ * holds), 8 / 9 = as 0 and the few-token path takes its kernel for small launches (K split over the waves of
+ * a workgroup) always / never, 10 = 9 and 7.
  * Process-wide, not thread-safe; results do not depend on it beyond fp32 summation order. */
 int szo_set_tile_config(int config);
 

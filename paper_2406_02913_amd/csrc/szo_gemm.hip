@@ -907,7 +907,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kerne
 
 static int g_tile_config = 0;      // 0 = choose by shape, 1 = 128x128 (4 waves), 2 = 256x256 (8 waves), 3 = 2 + always group the step,
                                    // 4, 5 = as 0 with the few-token path's 32- / 48-row passes forced (see small_m_force_rblocks),
-                                   // 6 = as 0 + always group the step, 7 = as 0 + non-temporal code stream in every one-slice launch
+                                   // 6 = as 0 + always group the step, 7 = as 0 + non-temporal code stream in every one-slice launch,
+                                   // 8, 9 = as 0 with the few-token path's split kernel always / never chosen, 10 = 9 and 7
 static bool few_token_enabled() { return g_tile_config == 0 || g_tile_config >= 4; }
 
 static int ilog2_exact(int v) {
@@ -1164,24 +1165,26 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
   // Kernel choice as in szo_zo_step: the few-token kernel (one launch per layer, both signs) when every
   // layer qualifies for it -- here also: no layer with a second activation set, which needs the grouped
   // launch's dual kernel -- else the tiled kernel, one launch per layer and sign.
-  bool few_all = few_token_enabled() && n > 0;
-  for (int i = 0; few_all && i < n; ++i) {
-    if (descs[i].M <= 0 || descs[i].N <= 0) continue;
-    few_all = !descs[i].x_minus && small_m_step_eligible(&descs[i]);
-  }
-  auto few_one = [few_all](const szo_linear_desc*) { return few_all; };
+  // `compact`: when the partials of the layers' preferred launches exceed the array, the ones with fewer of them.
+  bool few_all = false, compact = false;
   int64_t T = 0;
-  for (int i = 0; i < n; ++i) {     // reject everything before anything is enqueued
-    const szo_linear_desc* d = &descs[i];
-    const int rc = validate_desc(d, 1, false, true);
-    if (rc != SZO_OK) return rc;
-    if (d->nnz > 0 && (!d->sp_val || ((uintptr_t)d->sp_val & 15))) return SZO_EINVAL;
-    if (d->M == 0 || d->N == 0) continue;
-    int blocks;
-    if (few_one(d)) blocks = small_m_blocks(d) * small_m_slices(d);
-    else plan_tiles((int)d->M, (int)d->N, d->format, &blocks);
-    if (blocks < 0) return SZO_EUNSUPPORTED;
-    T += blocks;
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    compact = attempt == 1;
+    few_all = few_token_enabled() && small_m_eligible(descs, n, false, true) && (!compact || small_m_eligible(descs, n, true, true));
+    T = 0;
+    for (int i = 0; i < n; ++i) {     // reject everything before anything is enqueued
+      const szo_linear_desc* d = &descs[i];
+      const int rc = validate_desc(d, 1, false, true);
+      if (rc != SZO_OK) return rc;
+      if (d->nnz > 0 && (!d->sp_val || ((uintptr_t)d->sp_val & 15))) return SZO_EINVAL;
+      if (d->M == 0 || d->N == 0) continue;
+      if (few_all) { T += small_m_partials(d, compact); continue; }
+      int blocks;
+      plan_tiles((int)d->M, (int)d->N, d->format, &blocks);
+      if (blocks < 0) return SZO_EUNSUPPORTED;
+      T += blocks;
+    }
+    if (2 * T <= kNoAllocMaxPartials || !few_all) break;
   }
   if (2 * T > kNoAllocMaxPartials) return SZO_EUNSUPPORTED;
   double* part = nullptr;
@@ -1191,9 +1194,9 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
-    if (few_one(d)) {
-      rc = small_m_launch_one(d, seed, step, eps, 1, true, part + off, part + T + off, s);
-      off += small_m_blocks(d) * small_m_slices(d);
+    if (few_all) {
+      rc = small_m_launch_one(d, seed, step, eps, 1, true, part + off, part + T + off, compact, s);
+      off += small_m_partials(d, compact);
     } else {
       const double scale = 1.0 / ((double)d->M * (double)d->N);
       int blocks;
@@ -1215,10 +1218,11 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
 }
 
 int szo_set_tile_config(int config) {
-  if (config < 0 || config > 7) return SZO_EINVAL;
+  if (config < 0 || config > 10) return SZO_EINVAL;
   g_tile_config = config;
   small_m_force_rblocks(config == 4 ? 2 : config == 5 ? 3 : 0);
-  small_m_force_stream_once(config == 7);
+  small_m_force_stream_once(config == 7 || config == 10);
+  small_m_force_split(config == 8 ? 1 : config >= 9 ? -1 : 0);
   return SZO_OK;
 }
 
@@ -1226,9 +1230,9 @@ int szo_linear_fwd(const szo_linear_desc* desc, uint64_t seed, uint64_t step, in
   const int rc = validate_desc(desc, sign, true, false);
   if (rc != SZO_OK) return rc;
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
-  if (few_token_enabled() && small_m_step_eligible(desc))
+  if (few_token_enabled() && small_m_eligible(desc, 1, false, false))
     return small_m_launch_one(desc, seed, step, sign == 0 ? 0.0f : eps, sign == 0 ? 1 : sign, false, nullptr, nullptr,
-                              (hipStream_t)stream);
+                              false, (hipStream_t)stream);
   return run_forward(desc, seed, step, sign, eps, nullptr, 0.0, (hipStream_t)stream);
 }
 
@@ -1238,14 +1242,14 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   if (rc != SZO_OK) return rc;
   if (!loss_acc || !workspace || ((uintptr_t)workspace & 7)) return SZO_EINVAL;
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
-  if (few_token_enabled() && small_m_step_eligible(desc) && scale == 1.0 / ((double)desc->M * (double)desc->N)) {
+  if (few_token_enabled() && small_m_eligible(desc, 1, false, false) && scale == 1.0 / ((double)desc->M * (double)desc->N)) {
     // the few-token kernel computes both signs at once: make the requested one its "+" forward
-    const int nb = small_m_blocks(desc) * small_m_slices(desc);           // partials of all slices
+    const int64_t nb = small_m_partials(desc);
     if (2 * nb > kMaxLossPartials) return SZO_EUNSUPPORTED;
     rc = small_m_launch_one(desc, seed, step, (float)sign * eps, 1, true, partial_area(workspace),
-                            partial_area(workspace) + nb, (hipStream_t)stream);
+                            partial_area(workspace) + nb, false, (hipStream_t)stream);
     if (rc != SZO_OK) return rc;
-    return reduce_partials(partial_area(workspace), nb, 1.0, loss_acc, (hipStream_t)stream);
+    return reduce_partials(partial_area(workspace), (int)nb, 1.0, loss_acc, (hipStream_t)stream);
   }
   int blocks;
   plan_tiles((int)desc->M, (int)desc->N, desc->format, &blocks);
@@ -1277,12 +1281,9 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   }
   int rc;
   // Few-token stacks: one pass over the weights serves both forwards of the step.
-  bool few = fuse && few_token_enabled() && n > 0 && n <= kMaxStepMatrices;
-  const bool one_pass = flags & SZO_STEP_ONE_DENSE_PASS;     // the caller asks for the slicing path at any token count
-  for (int i = 0; few && i < n; ++i) {
-    if (descs[i].M == 0 || descs[i].N == 0) continue;        // an empty layer contributes nothing on either path
-    few = one_pass ? small_m_shape_eligible(&descs[i]) : small_m_step_eligible(&descs[i]);
-  }
+  // SZO_STEP_ONE_DENSE_PASS: the caller asks for that path at any token count.
+  const bool few = fuse && few_token_enabled() && n <= kMaxStepMatrices &&
+                   small_m_eligible(descs, n, (flags & SZO_STEP_ONE_DENSE_PASS) != 0, false);
   if (few) {
     rc = small_m_step(descs, n, seed, step, eps, lr, (char*)workspace + kWorkspaceTableOffset,
                       partial_area(workspace), scalars, true, true, s);

@@ -45,17 +45,18 @@ int reduce_partials(const double* partials, int count, double scale, double* los
 // scalars[0] = sum partials[0..count), scalars[1] = sum partials[count..2*count), scalars[2] = SPSA g.
 int reduce_step(const double* partials, int count, float eps, double* scalars, hipStream_t stream);
 
-// Few-token path (szo_smallm.hip): M <= 16, K % 128 == 0, fp16 tile.
-bool small_m_eligible(const szo_linear_desc* d);
-bool small_m_step_eligible(const szo_linear_desc* d);      // few enough tokens: sliced into passes of 16 or 32 token rows
-int small_m_blocks(const szo_linear_desc* d);
-int small_m_slices(const szo_linear_desc* d);              // passes over the weights: 16 or 32 token rows each
-bool small_m_shape_eligible(const szo_linear_desc* d);     // the same without looking at the token count
+// Few-token path (szo_smallm.hip, szo_split.hip).
+// Whether every layer of a launch is taken: few enough tokens to run as slices of 16 or more token rows, or, with
+// any_token_count, a shape that the stream kernel takes whatever its number of tokens.
+bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool one_set_only);
+int64_t small_m_partials(const szo_linear_desc* d, bool compact = false);   // loss partials per sign of a single-matrix launch;
+                                                            // compact: of the stream kernel, which makes fewer of them
+void small_m_force_split(int how);                          // testing hook: 1 = the split kernel always, -1 = only where nothing else can, 0 = choose
 void small_m_force_rblocks(int r);                         // testing hook: 0 = choose; 2, 3 = 32 / 48 token rows per pass wherever M > 16
 void small_m_force_stream_once(bool on);                    // testing hook: non-temporal code stream in every one-slice launch
 size_t small_m_table_bytes(int n);
 int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int sign, bool loss_mode,
-                       double* partial_plus, double* partial_minus, hipStream_t stream);
+                       double* partial_plus, double* partial_minus, bool compact, hipStream_t stream);
 int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,
                  void* table_dev, double* partial_plus, double* scalars, bool do_forward, bool do_update,
                  hipStream_t stream);

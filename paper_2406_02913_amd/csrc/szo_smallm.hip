@@ -30,21 +30,12 @@
 // Everything is accumulated in a fixed order: results are bit-reproducible.
 #include <algorithm>
 #include <cstddef>
+#include <utility>
 #include <vector>
-#include "szo_internal.h"
-#include "szo_rng.h"
+#include "szo_few.h"
 
 namespace szo {
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
-constexpr int SM_ROWS = 16;             // token rows of the MFMA (M padded up to this)
 constexpr int SM_BN = 256;              // output columns per workgroup = 4 bands of 64
 constexpr int SM_KC = 256;              // columns of x staged per chunk (double buffered) = 2 blocks of 128
 constexpr int SM_XSTRIDE = SM_KC + 8;   // LDS row stride of x in fp16 elements (+16 B against bank conflicts)
@@ -55,115 +46,11 @@ constexpr int SM_CAP = 512;             // entries held per band (ring)
                                         // the table format keeps its tables in 32 more registers: three workgroups)
 #endif
 
-struct SmallMat {
-  const uint16_t* x;        // bf16 [M,K]
-  const uint16_t* x2;       // bf16 [M,K] or null: the -eps forward's activations where they differ (DUAL kernels)
-  const uint8_t* qweight;   // [N,K/2]
-  const uint16_t* scales;   // fp16 [N,K/group]
-  const uint32_t* tile_ptr;
-  const uint32_t* sp_idx;
-  float* sp_val;
-  const uint16_t* target;   // bf16 [M,N]   (loss mode)
-  float* y;                 // fp32 [M,N]   (store mode)
-  uint64_t nnz_base;
-  double loss_scale;
-  int N, K;
-  int M;                    // token rows of this entry (<= 16 or <= 32, by instantiation): longer matrices are split into slices
-  uint32_t nnz;
-  int group_shift;
-  uint32_t div_mul;
-  int div_shift;
-  int first_block;          // workgroups of earlier matrices in this launch
-  int partial_base;         // index of this matrix's first loss partial
-  int64_t first_quad;       // threads of earlier matrices in the grouped update (one per Philox counter = 4 entries,
-                            // rounded up to whole waves of 64 per matrix)
-};
-
-static_assert(sizeof(SmallMat) <= kTableBytesPerMatrix, "table entries must fit the workspace's table area");
-
-struct SmallArgs {
-  const SmallMat* table;    // device table of n_mats matrices, or null: use `one`
-  SmallMat one;
-  int n_mats;
-  int slices;               // slices of token rows per strip in this launch (the longest matrix's count)
-  int stream_once;          // host's choice: load the codes as a non-temporal stream (see small_m_kernel, ONCE)
-  int store_sign;           // store mode: which forward to write (-1, 0, +1); loss mode: unused
-  int loss_mode;            // 1: write loss partials for both signs, 0: store y
-  uint64_t seed, step;
-  float eps;                // perturbation scale of the "+" forward (the "-" forward uses -eps)
-  double* partial_plus;     // [total workgroups]
-  double* partial_minus;
-};
-
-__device__ __forceinline__ uint32_t sm_fast_div(uint32_t v, uint32_t mul, int shift) {
-  const uint32_t t = __umulhi(mul, v);
-  return (t + ((v - t) >> 1)) >> shift;
-}
-
 // Position of column kk inside its 8-element chunk in LDS: chunks keep the order 0,4,1,5,2,6,3,7
 // in which the dequantised nibbles come out, so that x and the weights pair up element by element.
 __device__ __forceinline__ int sm_xpos(int kk) {
   const int w = kk & 7;
   return (kk & ~7) | ((w & 3) << 1) | (w >> 2);
-}
-
-// (a & mask) | bits: one v_and_or_b32 when `bits` is in a register.  Plain C on purpose.  As inline assembly
-// the instruction is opaque to the compiler's hazard handling, which keeps two wait states between a vector
-// instruction that writes a register and a matrix instruction that reads it: here the result IS a matrix
-// operand, and with the assembly form sequences with a single wait state were generated (harmless while
-// other waves share the SIMD and issue in between, wrong products for a wave that has the SIMD to itself).
-__device__ __forceinline__ uint32_t sm_and_or(uint32_t a, uint32_t mask, uint32_t bits_vgpr) {
-  return (a & mask) | bits_vgpr;
-}
-
-// 8 codes -> 8 fp16 values in the order (0,4)(1,5)(2,6)(3,7).
-// RAW: 1024+c for even positions and 64+c for odd ones (the caller removes the constants);
-// otherwise (c - 8) times the group scale.
-template <bool RAW>
-__device__ __forceinline__ half8_t sm_dequant_word(uint32_t q, uint32_t magic_lo, uint32_t magic_hi, half2_t s2) {
-  const uint32_t q8 = q >> 8;
-  half2_t h0 = __builtin_bit_cast(half2_t, sm_and_or(q, 0x000F000Fu, magic_lo));
-  half2_t h1 = __builtin_bit_cast(half2_t, sm_and_or(q, 0x00F000F0u, magic_hi));
-  half2_t h2 = __builtin_bit_cast(half2_t, sm_and_or(q8, 0x000F000Fu, magic_lo));
-  half2_t h3 = __builtin_bit_cast(half2_t, sm_and_or(q8, 0x00F000F0u, magic_hi));
-  if (!RAW) {
-    const half2_t off_lo = {(_Float16)1032.0f, (_Float16)1032.0f}, off_hi = {(_Float16)72.0f, (_Float16)72.0f};
-    h0 = (h0 - off_lo) * s2; h1 = (h1 - off_hi) * s2; h2 = (h2 - off_lo) * s2; h3 = (h3 - off_hi) * s2;
-  }
-  half8_t r;
-  r[0] = h0[0]; r[1] = h0[1]; r[2] = h1[0]; r[3] = h1[1];
-  r[4] = h2[0]; r[5] = h2[1]; r[6] = h3[0]; r[7] = h3[1];
-  return r;
-}
-
-// word w of the staged form of 8 bf16 values: (x[w], x[w+4]) as fp16
-__device__ __forceinline__ uint32_t sm_stage_x_word(u32x4 u, int w) {
-  const uint32_t first = (w < 2) ? u[0] : u[1], second = (w < 2) ? u[2] : u[3];
-  float a, b;
-  if ((w & 1) == 0) { a = __uint_as_float(first << 16); b = __uint_as_float(second << 16); }
-  else              { a = __uint_as_float(first & 0xFFFF0000u); b = __uint_as_float(second & 0xFFFF0000u); }
-  auto h = __builtin_amdgcn_cvt_pkrtz(a, b);
-  return __builtin_bit_cast(uint32_t, h);
-}
-
-// Eight codes of one row -> eight fp16 table values in the order (0,4)(1,5)(2,6)(3,7).  The row's table of 16
-// entries is held as four byte planes T = {low bytes of entries 0-7, high bytes of 0-7, low bytes of 8-15,
-// high bytes of 8-15}, two registers each: the byte permute looks up four codes at a time by their low
-// three bits, and bit 3 picks the plane through a byte mask.
-__device__ __forceinline__ half8_t sm_lut_word(uint32_t q, const uint32_t (&T)[8]) {
-  const uint32_t sel_e = q & 0x07070707u, sel_o = (q >> 4) & 0x07070707u;         // even codes 0,2,4,6 | odd codes 1,3,5,7
-  const uint32_t m_e = __builtin_amdgcn_perm(0u, 0x0000FF00u, (q >> 3) & 0x01010101u);   // 0xFF where the code is >= 8
-  const uint32_t m_o = __builtin_amdgcn_perm(0u, 0x0000FF00u, (q >> 7) & 0x01010101u);
-  auto pick = [](uint32_t m, uint32_t b, uint32_t a) { return (m & b) | (~m & a); };
-  const uint32_t lo_e = pick(m_e, __builtin_amdgcn_perm(T[5], T[4], sel_e), __builtin_amdgcn_perm(T[1], T[0], sel_e));
-  const uint32_t hi_e = pick(m_e, __builtin_amdgcn_perm(T[7], T[6], sel_e), __builtin_amdgcn_perm(T[3], T[2], sel_e));
-  const uint32_t lo_o = pick(m_o, __builtin_amdgcn_perm(T[5], T[4], sel_o), __builtin_amdgcn_perm(T[1], T[0], sel_o));
-  const uint32_t hi_o = pick(m_o, __builtin_amdgcn_perm(T[7], T[6], sel_o), __builtin_amdgcn_perm(T[3], T[2], sel_o));
-  const u32x4 w = {__builtin_amdgcn_perm(hi_e, lo_e, 0x06020400u),      // codes 0, 4
-                   __builtin_amdgcn_perm(hi_o, lo_o, 0x06020400u),      // codes 1, 5
-                   __builtin_amdgcn_perm(hi_e, lo_e, 0x07030501u),      // codes 2, 6
-                   __builtin_amdgcn_perm(hi_o, lo_o, 0x07030501u)};     // codes 3, 7
-  return __builtin_bit_cast(half8_t, w);
 }
 
 // MODE 1 (uniform format, quantisation group of 128): the scales of a block's four subtiles are
@@ -177,7 +64,6 @@ __device__ __forceinline__ half8_t sm_lut_word(uint32_t q, const uint32_t (&T)[8
 // with R blocks of token rows, so that matrices with more than 16 tokens stream their weights less
 // often; each block costs 48 more registers (accumulators and activation operands): 196 and 253
 // registers, i.e. two workgroups per CU instead of three.
-constexpr int SM_PLAIN = 0, SM_FAST = 1, SM_LUT = 2;
 // DUAL (R = 2 only): the two forwards read different activations (x for +eps, x2 for -eps).  Block 0 then
 // holds 16 token rows of x and block 1 the same rows of x2: still one pass over the weights for both
 // signs, but nothing else is shared, and y(+) = acc[0] + eps accz[0], y(-) = acc[1] - eps accz[1].
@@ -205,37 +91,13 @@ __global__ void __launch_bounds__(256, R == 1 ? (MODE == SM_LUT ? 3 : SM_MIN_BLO
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Workgroup ids go round-robin over the 8 XCDs, each with its own L2.  Remap them so that eight
-  // consecutive strips (normally of one matrix, which all read the same x) run on one XCD and
-  // consecutive groups of eight rotate over the XCDs; the ragged tail (< 64 ids) keeps its order.
-  int bid = (int)blockIdx.x;
-  if (bid < (int)(gridDim.x & ~63u)) {
-    const int xcd = bid & 7, i = bid >> 3;
-    bid = (((i >> 3) << 3) + xcd) * 8 + (i & 7);
-  }
+  int bid = xcd_unit((int)blockIdx.x, (int)gridDim.x);
   // ---- which slice of token rows, which matrix, which 256-column strip ----
   // Consecutive (remapped) ids are the slices of one strip: they read the same weights, so they should
   // run at the same time on the same XCD and share them through its L2.
   const int slice = bid % a.slices;
   bid /= a.slices;
-  // The table entry is read through the constant address space (scalar loads: the table is written
-  // before the launch and never during it), so that its fields live in scalar registers like the
-  // kernel arguments do; read through a generic pointer they would occupy ~30 vector registers.
-  SmallMat mt = a.one;
-  if (a.table) {
-    constexpr int W = (int)(sizeof(SmallMat) / 4), FB = (int)(offsetof(SmallMat, first_block) / 4);
-    static_assert(sizeof(SmallMat) % 4 == 0 && offsetof(SmallMat, first_block) % 4 == 0, "table entry is read as words");
-    const auto* tab = (const uint32_t __attribute__((address_space(4)))*)a.table;
-    int lo = 0, hi = a.n_mats - 1;                          // last matrix whose first_block <= bid
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if ((int)tab[mid * W + FB] <= bid) lo = mid; else hi = mid - 1;
-    }
-    struct Words { uint32_t w[W]; } raw;
-#pragma unroll
-    for (int i = 0; i < W; ++i) raw.w[i] = tab[lo * W + i];
-    mt = __builtin_bit_cast(SmallMat, raw);
-  }
+  SmallMat mt = find_matrix(a, bid);
   // a launch has as many slices of TOK token rows per strip as its longest matrix needs
   if (slice * TOK >= mt.M) return;
   mt.x += (size_t)slice * TOK * (size_t)mt.K;
@@ -244,9 +106,6 @@ __global__ void __launch_bounds__(256, R == 1 ? (MODE == SM_LUT ? 3 : SM_MIN_BLO
   if (mt.y) mt.y += (size_t)slice * TOK * (size_t)mt.N;
   mt.M = min(TOK, mt.M - slice * TOK);
   mt.partial_base += slice * ((mt.N + SM_BN - 1) / SM_BN);      // slice i of a matrix: partials [i * strips ..)
-  // Pointers read out of a table are generic to the compiler; say that they are global memory, or
-  // every access becomes a flat load with conservative waits on both memory counters.
-#define SZO_GLOBAL(T, p) ((const T __attribute__((address_space(1)))*)(p))
   const auto g_x = SZO_GLOBAL(uint16_t, mt.x);
   const auto g_x2 = SZO_GLOBAL(uint16_t, DUAL ? mt.x2 : mt.x);
   const auto g_q = SZO_GLOBAL(uint8_t, mt.qweight);
@@ -302,12 +161,7 @@ __global__ void __launch_bounds__(256, R == 1 ? (MODE == SM_LUT ? 3 : SM_MIN_BLO
 #pragma unroll
     for (int s = 0; s < (LUT ? 4 : 1); ++s) {
       const int n = min((int)bsafe * 64 + 16 * s + nn, N - 1);
-      const auto* lp = reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>(g_scales + (size_t)n * 16);
-      const u32x4 lo = lp[0], hi = lp[1];                   // entries 0-7 and 8-15, two per word
-      tb[s][0] = __builtin_amdgcn_perm(lo[1], lo[0], 0x06040200u); tb[s][1] = __builtin_amdgcn_perm(lo[3], lo[2], 0x06040200u);
-      tb[s][2] = __builtin_amdgcn_perm(lo[1], lo[0], 0x07050301u); tb[s][3] = __builtin_amdgcn_perm(lo[3], lo[2], 0x07050301u);
-      tb[s][4] = __builtin_amdgcn_perm(hi[1], hi[0], 0x06040200u); tb[s][5] = __builtin_amdgcn_perm(hi[3], hi[2], 0x06040200u);
-      tb[s][6] = __builtin_amdgcn_perm(hi[1], hi[0], 0x07050301u); tb[s][7] = __builtin_amdgcn_perm(hi[3], hi[2], 0x07050301u);
+      load_lut_planes(g_scales + (size_t)n * 16, tb[s]);
     }
   }
   // ---- x staging: piece = 8 columns (16 bytes of bf16) of one row; thread handles pieces
@@ -635,13 +489,36 @@ __global__ void __launch_bounds__(256) sparse_update_table_kernel(const SmallMat
 static size_t small_lds_bytes(int r) {
   return (size_t)2 * SM_ROWS * r * SM_XSTRIDE * 2 + (size_t)3 * 4 * SM_CAP * 2;
 }
-// Blocks of 16 token rows per pass for a matrix of a launch.  Two (half as many passes over the weights)
-// only pay when the launch is large: two-block workgroups run two to a CU instead of three, and a launch
-// that fits the chip in one go (measured: a single decoder block) is faster as more, smaller passes side
-// by side.  `launch_wgs16` = workgroups the whole launch would have with 16 rows per pass.
+
+static int64_t bands_of(const szo_linear_desc* d) { return (d->N + 63) / 64; }
+static int64_t strips_of(const szo_linear_desc* d) { return (d->N + SM_BN - 1) / SM_BN; }
+
+// What one launch consists of: how many workgroups it would have with 16 token rows per pass, as 256-column strips
+// and as 64-row bands.
+struct LaunchShape {
+  int64_t strips16 = 0, bands16 = 0;
+  void add(const szo_linear_desc* d) {
+    if (d->M <= 0 || d->N <= 0) return;
+    const int64_t slices = (d->M + SM_ROWS - 1) / SM_ROWS;
+    strips16 += strips_of(d) * slices;
+    bands16 += bands_of(d) * slices;
+  }
+};
+
+// The stream kernel (small_m_kernel) needs whole 128-column blocks, the fp16 tile and 32-bit code offsets; the split
+// kernel also takes the other uniform layers.
+static bool stream_ok(const szo_linear_desc* d) {
+  return d->K % 128 == 0 && d->tile_dtype == SZO_TILE_F16 && (uint64_t)(bands_of(d) * 64) * (uint64_t)d->K / 2 < (1ull << 32);
+}
+
+// Blocks of 16 token rows per pass of the stream kernel for a matrix of a launch.  Two (half as many passes over
+// the weights) only pay when the launch is large: two-block workgroups run two to a CU instead of three, and a
+// launch that fits the chip in one go is faster as more, smaller passes side by side.
 constexpr int64_t kSmallWideWorkgroups = 1536;              // two rounds of the 768 workgroups the chip holds
 static int g_force_rblocks = 0;                             // testing hook: 2 or 3 = that many wherever M > 16
 void small_m_force_rblocks(int r) { g_force_rblocks = r; }
+static int g_force_split = 0;                               // testing hook: 1 = always the split kernel, -1 = only where nothing else can
+void small_m_force_split(int how) { g_force_split = how; }
 static int small_m_rblocks(const szo_linear_desc* d, int64_t launch_wgs16) {
   if (d->M <= SM_ROWS) return 1;
   if (g_force_rblocks) return g_force_rblocks;
@@ -653,31 +530,59 @@ static int small_m_rblocks(const szo_linear_desc* d, int64_t launch_wgs16) {
   return best + 1;
 }
 
-bool small_m_eligible(const szo_linear_desc* d) {
-  return d->M >= 1 && d->M <= SM_ROWS && d->N >= 1 && (d->K % 128) == 0 &&
-         (d->format == SZO_FORMAT_LUT || d->group >= 32) && d->tile_dtype == SZO_TILE_F16 &&
-         (uint64_t)((d->N + 63) / 64 * 64) * (uint64_t)d->K / 2 < (1ull << 32);   // 32-bit code offsets
+// Which kernel and instantiation a matrix of a launch runs with: a variant (stream kernel with 1, 2 or 3 blocks of
+// token rows or with two activation sets; split kernel with one or two sets) and a dequantisation (uniform format
+// with a group of 128; table format; other uniform groups; uniform layers whose other kernel is the tiled one, with
+// either tile type).  Their number orders the step's table and launches.
+enum { V_STREAM1, V_STREAM2, V_STREAM3, V_STREAM_DUAL, V_SPLIT, V_SPLIT_DUAL, kVariants };
+enum { D_FAST, D_LUT, D_PLAIN, D_TILE_F16, D_TILE_BF16, kDequants };
+constexpr int kClasses = kVariants * kDequants;
+struct FewPlan {
+  int variant, dequant;
+  int cls() const { return variant * kDequants + dequant; }
+  static FewPlan of_class(int cls) { return FewPlan{cls / kDequants, cls % kDequants}; }
+  bool split() const { return variant >= V_SPLIT; }
+  bool dual() const { return variant == V_STREAM_DUAL || variant == V_SPLIT_DUAL; }
+  int rblocks() const { return variant <= V_STREAM3 ? variant + 1 : variant == V_STREAM_DUAL ? 2 : 1; }
+  int mode() const { return dequant == D_FAST ? SM_FAST : dequant == D_LUT ? SM_LUT : SM_PLAIN; }
+  int rows() const { return dual() || split() ? SM_ROWS : SM_ROWS * rblocks(); }       // token rows of one slice
+  int64_t units(const szo_linear_desc* d) const { return split() ? bands_of(d) : strips_of(d); }   // workgroups per slice
+  int slices(const szo_linear_desc* d) const { return (int)((d->M + rows() - 1) / rows()); }
+};
+
+// Launches of at most this many bands x slices take the split kernel.  Measured against the stream kernel, us per
+// step: OPT blocks at 16 tokens, 576 / 1152 / 2304 / 3456 units: 47 / 66 / 125 / 183 against 130 / 134 / 158 / 179;
+// one Llama block at 32 / 64 / 128 tokens, 1400 / 2800 / 5600 units: 62 / 92 / 173 against 95 / 100 / 135.  The table
+// format (look-ups: 700 / 1400 / 2100 units 61 / 108 / 164 against 143 / 145 / 147) and two activation sets (65 / 115
+// against 113 / 118 at 700 / 1400) do more work per unit.
+constexpr int64_t kSplitUnits = 2800, kSplitUnitsHeavy = 1500;
+static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, bool dual, bool compact = false) {
+  FewPlan p;
+  if (d->format == SZO_FORMAT_LUT) p.dequant = D_LUT;
+  else if (d->tile_dtype == SZO_TILE_BF16) p.dequant = D_TILE_BF16;
+  else if (!stream_ok(d)) p.dequant = D_TILE_F16;
+  else p.dequant = d->group == 128 ? D_FAST : D_PLAIN;
+  bool split = launch.bands16 <= (dual || p.dequant == D_LUT ? kSplitUnitsHeavy : kSplitUnits);
+  if (g_force_split) split = g_force_split > 0;
+  if (g_force_rblocks || compact) split = false;
+  if (!stream_ok(d)) split = true;
+  if (split) p.variant = dual ? V_SPLIT_DUAL : V_SPLIT;
+  else p.variant = dual ? V_STREAM_DUAL : V_STREAM1 + small_m_rblocks(d, launch.strips16) - 1;
+  return p;
 }
 
-// Which instantiation a matrix runs with: uniform format with a group of 128 (one scale per
-// 128-column block) takes the fast one, the table format its own, everything else the plain one.
-static int small_m_mode(const szo_linear_desc* d) {
-  if (d->format == SZO_FORMAT_LUT) return SM_LUT;
-  return d->group == 128 ? SM_FAST : SM_PLAIN;
+// Waves of a split workgroup: 16 (which fill a CU) while every workgroup has a CU to itself, then 8, two workgroups
+// to a CU, then 4: with more workgroups than the chip holds at once the depth of the split matters less than what a
+// workgroup costs; no more than K has blocks of 128 columns.  Measured, us per call with 4 / 8 / 16 waves: a
+// 4096 x 4096 layer at 100 tokens (448 workgroups) - / 16.9 / 21.8; an OPT block at 16 tokens (576) 57 / 47 / 54, four
+// of them (2304) 131 / 125 / 178; with the bf16 tile a Llama block at 64 tokens (2800) 134 / 194 / -.
+static int split_waves(int64_t workgroups, int64_t longest_k) {
+  const int64_t blocks = (longest_k + 127) / 128;
+  const int most = workgroups <= 256 ? 16 : workgroups <= 2304 ? 8 : 4;
+  int w = 2;
+  while (w < most && w < blocks) w *= 2;
+  return w;
 }
-// position of an instantiation (mode, row blocks) in a step's table and launch order
-// (classes 9..11: two activation sets, always two blocks of rows)
-constexpr int kSmallClasses = 12;
-static int small_m_class(const szo_linear_desc* d, int rblocks, bool dual) {
-  const int m = small_m_mode(d), mi = m == SM_FAST ? 0 : m == SM_LUT ? 1 : 2;
-  return dual ? 9 + mi : 3 * mi + (rblocks - 1);
-}
-static bool class_dual(int cls) { return cls >= 9; }
-static int class_mode(int cls) {
-  const int mi = class_dual(cls) ? cls - 9 : cls / 3;
-  return mi == 0 ? SM_FAST : mi == 1 ? SM_LUT : SM_PLAIN;
-}
-static int class_rblocks(int cls) { return class_dual(cls) ? 2 : cls % 3 + 1; }
 
 template <int MODE, int R, bool DUAL>
 static void launch_variant(dim3 blocks, const SmallArgs& a, hipStream_t stream) {
@@ -701,11 +606,27 @@ static int stream_once_rule(int slices, int64_t launch_code_bytes) {
   return slices == 1 && (g_force_stream_once || launch_code_bytes > kLastLevelCacheBytes);
 }
 
-static void small_m_launch(int mode, int r, bool dual, dim3 blocks, const SmallArgs& a, hipStream_t stream) {
-  if (dual) launch_mode<2, true>(mode, blocks, a, stream);
-  else if (r == 1) launch_mode<1, false>(mode, blocks, a, stream);
-  else if (r == 2) launch_mode<2, false>(mode, blocks, a, stream);
-  else launch_mode<3, false>(mode, blocks, a, stream);
+// One launch of the matrices described by `a` (their table or the single one), `units` workgroups per slice.
+static int launch_plan(const FewPlan& p, int64_t units, int slices, int64_t longest_k, int64_t launch_code_bytes,
+                       SmallArgs& a, hipStream_t stream) {
+  if (units * slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+  a.slices = slices;
+  a.stream_once = stream_once_rule(slices, launch_code_bytes);
+  const int wgs = (int)(units * slices);
+  int rc = timing_begin(stream);
+  if (rc != SZO_OK) return rc;
+  if (p.split()) {
+    rc = split_launch(p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, split_waves(wgs, longest_k), wgs, a, stream);
+    if (rc != SZO_OK) return rc;
+  } else {
+    const dim3 blocks((unsigned)wgs);
+    if (p.dual()) launch_mode<2, true>(p.mode(), blocks, a, stream);
+    else if (p.rblocks() == 1) launch_mode<1, false>(p.mode(), blocks, a, stream);
+    else if (p.rblocks() == 2) launch_mode<2, false>(p.mode(), blocks, a, stream);
+    else launch_mode<3, false>(p.mode(), blocks, a, stream);
+    SZO_LAUNCH_CHECK();
+  }
+  return timing_end(stream);
 }
 
 // The step also takes matrices with more tokens: they run as slices of 16 or 32 token rows, each a pass
@@ -714,30 +635,40 @@ static void small_m_launch(int mode, int r, bool dual, dim3 blocks, const SmallA
 // ceil(M/32) stays below 7.5 ceil(M/256), e.g. up to 224 tokens and from 257 to 448; beyond 15 such
 // slices the tiled kernel is the default (SZO_STEP_ONE_DENSE_PASS overrides that).
 constexpr int kSmallMaxSlices = 15;
-bool small_m_shape_eligible(const szo_linear_desc* d) {
-  if (d->M < 1) return false;
-  szo_linear_desc one = *d;
-  one.M = 1;
-  return small_m_eligible(&one);
-}
-bool small_m_step_eligible(const szo_linear_desc* d) {
+// Uniform layers that only the split kernel takes (bf16 tile, K an odd multiple of 64), against 128x128 tiles in one
+// grouped launch.  Measured with the bf16 tile, us per step: one Llama block at 16 / 64 / 128 tokens 62 / 134 / 302
+// against 371 / 375 / 379, sixteen blocks 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where
+// the tiles would leave the chip idle.
+constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTokensSmallLaunch = 128;
+static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch) {
+  if (!stream_ok(d))
+    return d->format == SZO_FORMAT_UNIFORM &&
+           d->M <= (launch.bands16 <= 2304 ? kSplitOnlyTokensSmallLaunch : kSplitOnlyTokens);
   // two activation sets: a pass holds 16 token rows of each, so it is worth less
   const int64_t slices = (d->M + (d->x_minus ? 15 : 31)) / (d->x_minus ? 16 : 32), tile_rows = (d->M + 255) / 256;
-  if (slices > kSmallMaxSlices || 2 * slices >= 15 * tile_rows) return false;
-  return small_m_shape_eligible(d);
+  return slices <= kSmallMaxSlices && 2 * slices < 15 * tile_rows;
+}
+bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool one_set_only) {
+  LaunchShape shape;
+  for (int i = 0; i < n; ++i) shape.add(&descs[i]);
+  for (int i = 0; i < n; ++i) {
+    const szo_linear_desc* d = &descs[i];
+    if (d->M <= 0 || d->N <= 0) continue;                   // an empty layer contributes nothing on either path
+    if (one_set_only && d->x_minus) return false;
+    if (!(any_token_count ? stream_ok(d) : layer_eligible(d, shape))) return false;
+  }
+  return n > 0;
 }
 
-int small_m_blocks(const szo_linear_desc* d) { return (int)((d->N + SM_BN - 1) / SM_BN); }
-
-static int64_t small_m_wgs16(const szo_linear_desc* d) {
-  return (int64_t)small_m_blocks(d) * ((d->M + SM_ROWS - 1) / SM_ROWS);
+static FewPlan plan_of_one(const szo_linear_desc* d, bool compact) {
+  LaunchShape shape;
+  shape.add(d);
+  return few_plan(d, shape, false, compact);
 }
-static int slices_of(const szo_linear_desc* d, int rblocks, bool dual = false) {
-  const int rows = dual ? SM_ROWS : SM_ROWS * rblocks;
-  return (int)((d->M + rows - 1) / rows);
+int64_t small_m_partials(const szo_linear_desc* d, bool compact) {
+  const FewPlan p = plan_of_one(d, compact);
+  return p.units(d) * p.slices(d);
 }
-// passes of a single-matrix call
-int small_m_slices(const szo_linear_desc* d) { return slices_of(d, small_m_rblocks(d, small_m_wgs16(d))); }
 
 size_t small_m_table_bytes(int n) { return sizeof(SmallMat) * (size_t)n; }
 
@@ -782,17 +713,14 @@ static int set_small_attrs() {
   return rc;
 }
 
-// One matrix, descriptor passed in the kernel arguments (no device table needed).
-// One launch of strips x slices workgroups.  In loss mode slice i writes its partials at
-// partial_*[i * small_m_blocks(d) ..], scaled by 1 / (M N) of the whole matrix, so that their sum over
-// all slices is the matrix's loss.
+// One matrix, descriptor passed in the kernel arguments (no device table needed), as one launch.  In loss mode
+// slice i writes its partials behind those of slice i - 1, small_m_partials(d, compact) in all, scaled by 1 / (M N) of the
+// whole matrix, so that their sum is the matrix's loss.
 int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int sign, bool loss_mode,
-                       double* partial_plus, double* partial_minus, hipStream_t stream) {
+                       double* partial_plus, double* partial_minus, bool compact, hipStream_t stream) {
   const int rc = set_small_attrs();
   if (rc != SZO_OK) return rc;
-  const int blocks = small_m_blocks(d);
-  const int rblocks = small_m_rblocks(d, small_m_wgs16(d));
-  const int slices = slices_of(d, rblocks);
+  const FewPlan p = plan_of_one(d, compact);
   SmallArgs a{};
   fill_mat(a.one, d);                                       // whole matrix: the kernel offsets rows by slice
   a.table = nullptr; a.n_mats = 1;
@@ -800,15 +728,7 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   a.seed = seed; a.step = step; a.eps = eps;
   a.partial_plus = partial_plus;
   a.partial_minus = partial_minus;
-  const int trc = timing_begin(stream);
-  if (trc != SZO_OK) return trc;
-  a.slices = slices;
-  a.stream_once = stream_once_rule(slices, code_bytes(d));
-  small_m_launch(small_m_mode(d), rblocks, false, dim3((unsigned)(blocks * slices)), a, stream);
-  SZO_LAUNCH_CHECK();
-  const int erc = timing_end(stream);
-  if (erc != SZO_OK) return erc;
-  return SZO_OK;
+  return launch_plan(p, p.units(d), p.slices(d), d->K, code_bytes(d), a, stream);
 }
 
 // A whole stack in one launch per instantiation.  The table is assembled on the host, longest K
@@ -822,58 +742,48 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   int rc = set_small_attrs();
   if (rc != SZO_OK) return rc;
   if (n > kMaxStepMatrices) return SZO_EUNSUPPORTED;
-  int64_t wgs16 = 0;
-  for (int i = 0; i < n; ++i) wgs16 += small_m_wgs16(&descs[i]);
+  LaunchShape shape;
+  for (int i = 0; i < n; ++i) shape.add(&descs[i]);
   // two activation sets (forward launches only): one block of rows for each, whatever the token count
-  auto dual_of = [&](const szo_linear_desc* d) { return do_forward && d->x_minus != nullptr; };
-  auto rblocks_of = [&](const szo_linear_desc* d) { return dual_of(d) ? 2 : small_m_rblocks(d, wgs16); };
+  auto plan_for = [&](const szo_linear_desc* d) { return few_plan(d, shape, do_forward && d->x_minus != nullptr); };
   if (small_m_table_bytes(n) > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;
   static thread_local std::vector<SmallMat> host_table;
   host_table.resize((size_t)std::max(n, 1));
   SmallMat* const host = host_table.data();
-  // order: by instantiation (fast, table format, plain; fewer rows per pass first), inside each by K descending
-  int order[kMaxStepMatrices];
-  for (int i = 0; i < n; ++i) order[i] = i;
-  auto sort_key = [&](int o) {
-    return ((int64_t)(kSmallClasses - 1 - small_m_class(&descs[o], rblocks_of(&descs[o]), dual_of(&descs[o]))) << 40) + descs[o].K;
-  };
-  for (int i = 1; i < n; ++i) {                       // insertion sort: n is a few hundred
-    const int o = order[i];
-    const int64_t key = sort_key(o);
-    int j = i - 1;
-    while (j >= 0) {
-      if (sort_key(order[j]) >= key) break;
-      order[j + 1] = order[j];
-      --j;
-    }
-    order[j + 1] = o;
-  }
-  // One table entry per matrix; a launch has (strips of its matrices) x (slices of its longest matrix)
+  // order: by instantiation, inside each by K descending
+  static thread_local std::vector<std::pair<int64_t, int>> order;
+  order.resize((size_t)n);
+  for (int i = 0; i < n; ++i)
+    order[(size_t)i] = {((int64_t)plan_for(&descs[i]).cls() << 40) - descs[i].K, i};
+  std::sort(order.begin(), order.end());
+  // One table entry per matrix; a launch has (units of its matrices) x (slices of its longest matrix)
   // workgroups (those past a matrix's last slice return at once), and slice i of a matrix writes its
   // loss partials behind those of slice i - 1.
-  int class_entries[kSmallClasses] = {}, class_blocks[kSmallClasses] = {}, class_slices[kSmallClasses] = {}, entries = 0;
-  int64_t class_code_bytes[kSmallClasses] = {};
+  struct ClassTotals { int entries = 0, slices = 0; int64_t units = 0, k = 0, code_bytes = 0; } classes[kClasses];
+  int entries = 0;
   int64_t quads = 0, partials = 0;
-  for (int r = 0; r < n; ++r) {
-    const szo_linear_desc* d = &descs[order[r]];
-    const int rblocks = rblocks_of(d);
-    const int cls = small_m_class(d, rblocks, dual_of(d));
+  for (const auto& o : order) {
+    const szo_linear_desc* d = &descs[o.second];
+    const FewPlan p = plan_for(d);
+    ClassTotals& c = classes[p.cls()];
     // a layer without tokens or outputs has no workgroups; it keeps its table entry for the update
     const bool live = d->M > 0 && d->N > 0;
-    const int slices = live ? slices_of(d, rblocks, dual_of(d)) : 0, b = live ? small_m_blocks(d) : 0;
+    const int slices = live ? p.slices(d) : 0;
+    const int64_t units = live ? p.units(d) : 0;
     SmallMat& m = host[entries++];
     fill_mat(m, d);
-    m.first_block = class_blocks[cls];
+    m.first_block = (int)c.units;
     m.partial_base = (int)partials;
     m.first_quad = quads;
-    class_blocks[cls] += b;
-    class_slices[cls] = std::max(class_slices[cls], slices);
-    if (live) class_code_bytes[cls] += code_bytes(d);
-    ++class_entries[cls];
-    partials += (int64_t)b * slices;
+    c.units += units;
+    c.slices = std::max(c.slices, slices);
+    c.k = std::max(c.k, d->K);
+    if (live) c.code_bytes += code_bytes(d);
+    ++c.entries;
+    partials += units * slices;
     quads += (((int64_t)d->nnz + 3) / 4 + 63) & ~(int64_t)63;      // a wave of the update serves one matrix
     if (do_forward && 2 * partials > kMaxLossPartials) return SZO_EUNSUPPORTED;
-    if ((int64_t)class_blocks[cls] * class_slices[cls] > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+    if (c.units * c.slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
   }
   rc = stage_table(host, sizeof(SmallMat) * (size_t)entries, table_dev, stream);
   if (rc != SZO_OK) return rc;
@@ -883,17 +793,14 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   a.partial_plus = partial_plus; a.partial_minus = do_forward ? partial_plus + partials : nullptr;
   const SmallMat* tdev = (const SmallMat*)table_dev;
   int first_entry = 0;
-  for (int cls = 0; cls < kSmallClasses; ++cls) {
-    if (do_forward && class_blocks[cls] > 0 && class_slices[cls] > 0) {
-      a.table = tdev + first_entry; a.n_mats = class_entries[cls];
-      a.slices = class_slices[cls];
-      a.stream_once = stream_once_rule(a.slices, class_code_bytes[cls]);
-      if ((rc = timing_begin(stream)) != SZO_OK) return rc;
-      small_m_launch(class_mode(cls), class_rblocks(cls), class_dual(cls), dim3((unsigned)(class_blocks[cls] * class_slices[cls])), a, stream);
-      SZO_LAUNCH_CHECK();
-      if ((rc = timing_end(stream)) != SZO_OK) return rc;
+  for (int cls = 0; cls < kClasses; ++cls) {
+    const ClassTotals& c = classes[cls];
+    if (do_forward && c.units > 0 && c.slices > 0) {
+      a.table = tdev + first_entry; a.n_mats = c.entries;
+      rc = launch_plan(FewPlan::of_class(cls), c.units, c.slices, c.k, c.code_bytes, a, stream);
+      if (rc != SZO_OK) return rc;
     }
-    first_entry += class_entries[cls];
+    first_entry += c.entries;
   }
   if (do_forward) {
     rc = reduce_step(partial_plus, (int)partials, eps, scalars, stream);

@@ -1,0 +1,423 @@
+// Few-token kernel for launches that do not fill the chip: K split over the waves of a workgroup.
+//
+// A launch over one layer or one decoder block has too few 256-column strips to occupy 256 CUs, and what it then
+// waits for is not bandwidth but the serial walk of a wave along K: one 4096 x 4096 layer at one token has 64 bands
+// of 64 rows, i.e. 64 waves on a chip that holds 4096, each of which takes 31 us for its 32 blocks of 128 columns
+// (120 us at K = 16384).  Here a workgroup is ONE band and one slice of 16 token rows, and its 2..16 waves take
+// consecutive parts of K.  Nothing is shared inside the loop -- a wave reads its own columns of x straight into
+// registers, there is no staging and no barrier -- and the waves' accumulators are added through LDS, in wave order,
+// before the epilogue.  More splits mean shorter chains; the whole sum stays inside one workgroup, so no second
+// kernel and no partial outputs in memory are needed.
+//
+// The arithmetic is that of small_m_kernel: y(+-) = x dq^T + x v^T +- eps x z^T, un-centred codes with the block's
+// scale applied in fp32 for groups of 128, the sensitive entries as one-hot matrix products of 16 entries.
+// With several slices each of them reads the band's codes (neighbouring workgroups of one XCD, through its L2).
+//
+// Measured (us per call, stream kernel -> this one): a 4096 x 4096 forward at 1 / 16 / 100 / 224 tokens 30 / 31 / 32 /
+// 32 -> 9.9 / 11.6 / 16.9 / 29; a step over one OPT block at 1 / 16 tokens 128 / 130 -> 40 / 47; a step over a Llama
+// block with the bf16 tile at 16 tokens, which the tiled kernel ran before, 371 -> 62.  What is left at one layer is a
+// chain of a few memory round trips and the launch itself; from ~3000 workgroups on the x and the sums of every band
+// cost more than the stream kernel's idle waves.
+#include <atomic>
+#include <type_traits>
+#include "szo_few.h"
+
+namespace szo {
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+
+constexpr int SP_WIN = 256;             // sensitive entries computed per refill of a wave's window
+constexpr int SP_MAX_WAVES = 16;
+constexpr int SP_XROW = 128 + 8;        // LDS row stride of a staged block of x, in 16-bit elements
+
+// Operand types and the two matrix products per 16-bit tile type.  fp16: operands in the element order
+// (0,4)(1,5)(2,6)(3,7), see sm_dequant_word; bf16: in natural order, activations unchanged.
+template <bool BF16> struct SplitOps;
+template <> struct SplitOps<false> {
+  typedef half8_t frag;
+  static __device__ __forceinline__ frag activations(u32x4 u) {
+    const u32x4 w = {sm_stage_x_word(u, 0), sm_stage_x_word(u, 1), sm_stage_x_word(u, 2), sm_stage_x_word(u, 3)};
+    return __builtin_bit_cast(half8_t, w);
+  }
+  static __device__ __forceinline__ uint16_t narrow(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
+  static __device__ __forceinline__ uint16_t activation(uint16_t bits) {      // same truncation as the staged form
+    auto h = __builtin_amdgcn_cvt_pkrtz(__uint_as_float((uint32_t)bits << 16), 0.0f);
+    return (uint16_t)(__builtin_bit_cast(uint32_t, h) & 0xFFFFu);
+  }
+  static __device__ __forceinline__ float4_t dense(frag x, frag w, float4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(x, w, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ float4_t sparse(u32x2 x, u32x2 w, float4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(half4_t, x), __builtin_bit_cast(half4_t, w), c, 0, 0, 0);
+  }
+};
+template <> struct SplitOps<true> {
+  typedef bf16x8_t frag;
+  static __device__ __forceinline__ frag activations(u32x4 u) { return __builtin_bit_cast(bf16x8_t, u); }
+  static __device__ __forceinline__ uint16_t narrow(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+  static __device__ __forceinline__ uint16_t activation(uint16_t bits) { return bits; }
+  static __device__ __forceinline__ float4_t dense(frag x, frag w, float4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ float4_t sparse(u32x2 x, u32x2 w, float4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, x), __builtin_bit_cast(short4_t, w), c, 0, 0, 0);
+  }
+};
+
+// Eight codes -> eight bf16 weights (c - 8) s in natural order, each rounded once.
+__device__ __forceinline__ bf16x8_t dequant_word_bf16(uint32_t q, float s) {
+  const float m8s = -8.0f * s;
+  u32x4 o;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float2_t f = {fmaf((float)((q >> (8 * w)) & 15u), s, m8s), fmaf((float)((q >> (8 * w + 4)) & 15u), s, m8s)};
+    o[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+  }
+  return __builtin_bit_cast(bf16x8_t, o);
+}
+
+// MODE as in small_m_kernel; BF16 (bf16 tile type) exists for SM_PLAIN only, which serves every group size.
+// DUAL: the -eps forward reads activations of its own (x2): one pass over the codes, two dense products.
+// TILE_ROUND: the sensitive weights enter as v +- eps z rounded to the tile type, as they stand in the tiled
+// kernel's weight tile (the dense code under them is the zero code), instead of v and z rounded one by one: for the
+// layers whose other kernel is the tiled one, so that both give the same results up to fp32 summation order.
+// Accumulator sets:            one set of x                       two sets (DUAL)
+//   v and z apart              0: dense + x v^T  1: x z^T         0, 1: the same of x   2, 3: of x2
+//   TILE_ROUND                 0: dense  1: x w+^T  2: x w-^T     0: dense + x w+^T     1: dense + x w-^T of x2
+template <bool DUAL, bool TILE_ROUND> constexpr int split_sets() { return TILE_ROUND ? (DUAL ? 2 : 3) : (DUAL ? 4 : 2); }
+template <int MODE, bool DUAL, bool TILE_ROUND> constexpr int split_max_waves() {
+  return MODE == SM_LUT || DUAL || TILE_ROUND ? 8 : SP_MAX_WAVES;
+}
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>
+__global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>())) band_split_kernel(SmallArgs a) {
+  static_assert(!BF16 || (MODE == SM_PLAIN && TILE_ROUND), "bf16 tile: plain dequantisation, rounded as in the tile");
+  constexpr bool FAST = MODE == SM_FAST, LUT = MODE == SM_LUT;
+  constexpr int SETS = DUAL ? 2 : 1;
+  constexpr int NACC = split_sets<DUAL, TILE_ROUND>();
+  constexpr int RED = NACC * 1024;                          // floats a wave leaves for the sum over the waves
+  constexpr int DENSE1 = TILE_ROUND ? 1 : 2;                // accumulator set of x2's dense product
+  typedef SplitOps<BF16> Ops;
+  typedef typename Ops::frag frag_t;
+  extern __shared__ __attribute__((aligned(16))) float red[];                     // [waves][NACC][1024]
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
+  int bid = xcd_unit((int)blockIdx.x, (int)gridDim.x);
+  const int slice = bid % a.slices;
+  bid /= a.slices;
+  SmallMat mt = find_matrix(a, bid);
+  if (slice * SM_ROWS >= mt.M) return;
+  const int N = mt.N, K = mt.K, M = min(SM_ROWS, mt.M - slice * SM_ROWS);
+  const int band = bid - mt.first_block, ktiles = K >> 6;
+  const size_t row0 = (size_t)slice * SM_ROWS;
+  const auto g_x = SZO_GLOBAL(uint16_t, mt.x) + row0 * (size_t)K;
+  const auto g_x2 = SZO_GLOBAL(uint16_t, DUAL ? mt.x2 : mt.x) + row0 * (size_t)K;
+  const auto g_q = SZO_GLOBAL(uint8_t, mt.qweight) + (size_t)band * (size_t)ktiles * 2048;
+  const auto g_scales = SZO_GLOBAL(uint16_t, mt.scales);
+  const auto g_tile_ptr = SZO_GLOBAL(uint32_t, mt.tile_ptr) + (size_t)band * (size_t)ktiles;
+  const auto g_sp_idx = SZO_GLOBAL(uint32_t, mt.sp_idx);
+  const auto g_sp_val = SZO_GLOBAL(float, mt.sp_val);
+  const auto g_target = SZO_GLOBAL(uint16_t, mt.target) + row0 * (size_t)N;
+  float __attribute__((address_space(1)))* const g_y = (float __attribute__((address_space(1)))*)mt.y + row0 * (size_t)N;
+  const int nn = lane & 15, jj = lane >> 4;
+  const bool with_z = a.eps != 0.0f;
+
+  // this wave's part of K, in blocks of 128 columns (the last block of a K that is an odd multiple of 64 is half
+  // empty: its codes are read from the last tile and multiplied with zeros)
+  const int nkb = (K + 127) >> 7;
+  const int b0 = wave * nkb / waves, b1 = (wave + 1) * nkb / waves;
+
+  // x of a block, 16 rows of 256 bytes, is loaded row by row (16 lanes per row: one load instruction touches 8 lines,
+  // against 64 if every lane fetched the pieces of its own operand row) and turned into operands through 4 KB of
+  // LDS of the wave's own; rows past M repeat the last one and only reach output rows past M.
+  const int xr_row = lane >> 4, xr_piece = lane & 15;       // load i: row 4 i + xr_row, columns 8 xr_piece ..
+  const uint32_t xrow = (uint32_t)min(nn, M - 1) * (uint32_t)K * 2u; // operand row of this lane (sensitive entries), in bytes
+  u32x4 q[4], xr[SETS][4] = {};
+  // Loads are a uniform base plus a 32-bit byte offset per lane (64-bit addresses per lane cost twice the registers).
+  const auto b_x = (const uint8_t __attribute__((address_space(1)))*)g_x;
+  const auto b_x2 = (const uint8_t __attribute__((address_space(1)))*)g_x2;
+  const uint32_t q_lane = (uint32_t)nn * 32u + (uint32_t)(jj & 1) * 16u;
+  auto load_q = [&](int b, int s) {
+    const uint32_t off = (uint32_t)min(2 * b + (jj >> 1), ktiles - 1) * 2048u + q_lane;
+    q[s] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>(g_q + (size_t)off + 512 * s);
+  };
+  uint32_t x_lane[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x_lane[i] = (uint32_t)min(4 * i + xr_row, M - 1) * (uint32_t)K * 2u;
+  auto load_x = [&](int b) {
+    const uint32_t col = (uint32_t)min(128 * b + 8 * xr_piece, K - 8) * 2u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int set = 0; set < SETS; ++set)
+        xr[set][i] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>((set ? b_x2 : b_x) + (size_t)(x_lane[i] + col));
+  };
+  const int gshift = mt.group_shift, groups = FAST ? K >> 7 : LUT ? 0 : K >> gshift;
+  const auto g_sc = (const uint8_t __attribute__((address_space(1)))*)(g_scales + (size_t)band * (size_t)groups * 64);
+  u32x2 sc = {0u, 0u};                                      // the lane's four scales of a group
+  auto load_scales = [&](int b) {
+    if (LUT) return;
+    const int g = FAST ? b : min((128 * b + 32 * jj) >> gshift, groups - 1);
+    sc = *reinterpret_cast<const u32x2 __attribute__((address_space(1)))*>(g_sc + (size_t)((uint32_t)g * 128u + 8u * (uint32_t)nn));
+  };
+  uint32_t e_lo = 0, e_hi = 0;                              // this wave's sensitive entries
+  if (b0 < b1) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) load_q(b0, s);
+    load_x(b0);
+    load_scales(b0);
+    if (mt.nnz > 0) {
+      e_lo = __builtin_amdgcn_readfirstlane(g_tile_ptr[2 * b0]);
+      e_hi = __builtin_amdgcn_readfirstlane(g_tile_ptr[min(2 * b1, ktiles)]);
+    }
+  }
+  uint32_t tb[LUT ? 4 : 1][8];
+  if (LUT) {
+#pragma unroll
+    for (int s = 0; s < (LUT ? 4 : 1); ++s) load_lut_planes(g_scales + (size_t)min(band * 64 + 16 * s + nn, N - 1) * 16, tb[s]);
+  }
+
+  float4_t acc[NACC][4];
+#pragma unroll
+  for (int i = 0; i < NACC; ++i)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc[i][s] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // ---- sensitive entries, while the first codes are on their way: 256 at a time into the wave's own part of LDS
+  //      (its later accumulator area), then 16 per matrix product ----
+  {
+    uint32_t* const wk = reinterpret_cast<uint32_t*>(red + wave * RED);            // column
+    uint16_t* const wr = reinterpret_cast<uint16_t*>(wk + SP_WIN);                  // row of the band
+    uint16_t* const wv = wr + SP_WIN;                                                // 16-bit v | v + eps z
+    uint16_t* const wz = wv + SP_WIN;                                                // 16-bit z | v - eps z
+    for (uint32_t w0 = e_lo & ~3u; w0 < e_hi; w0 += SP_WIN) {
+      const uint32_t j = w0 + 4u * lane, last = mt.nnz - 1u;
+      uint32_t idx[4];
+      float val[4], z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t je = min(j + e, last);               // clamped; entries past the end are never consumed
+        idx[e] = g_sp_idx[je];
+        val[e] = g_sp_val[je];
+      }
+      if (with_z) zbar_quad((mt.nnz_base + j) >> 2, a.seed, a.step, z);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t n = sm_fast_div(idx[e], mt.div_mul, mt.div_shift);
+        wk[4 * lane + e] = idx[e] - n * (uint32_t)K;
+        wr[4 * lane + e] = (uint16_t)(n - (uint32_t)(band * 64));
+        wv[4 * lane + e] = Ops::narrow(TILE_ROUND ? fmaf(a.eps, z[e], val[e]) : val[e]);
+        wz[4 * lane + e] = Ops::narrow(TILE_ROUND ? fmaf(-a.eps, z[e], val[e]) : z[e]);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // window visible to the other lanes of the wave
+      const uint32_t hi = min(e_hi, w0 + (uint32_t)SP_WIN);
+      for (uint32_t g0 = w0; g0 < hi; g0 += 16u) {
+        const uint32_t at = g0 - w0 + 4u * (uint32_t)jj;
+        const u32x4 kw = *reinterpret_cast<const u32x4*>(wk + at);
+        const u32x2 rw = *reinterpret_cast<const u32x2*>(wr + at);
+        const u32x2 vw = *reinterpret_cast<const u32x2*>(wv + at);
+        const u32x2 zw = *reinterpret_cast<const u32x2*>(wz + at);
+        uint32_t mlo[4], mhi[4];
+        uint16_t ax[SETS][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                       // every gather requested before the first is used
+          const uint32_t e = w0 + at + (uint32_t)i;
+          const uint32_t col = e >= e_lo && e < hi ? kw[i] : 0u;   // entries of other waves: a valid address, masked below
+#pragma unroll
+          for (int set = 0; set < SETS; ++set)
+            ax[set][i] = *reinterpret_cast<const uint16_t __attribute__((address_space(1)))*>((set ? b_x2 : b_x) + (size_t)(xrow + 2u * col));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t e = w0 + at + (uint32_t)i;
+          one_hot_entry((rw[i >> 1] >> (16 * (i & 1))) & 63u, nn, e >= e_lo && e < hi, mlo[i], mhi[i]);
+#pragma unroll
+          for (int set = 0; set < SETS; ++set) ax[set][i] = Ops::activation(ax[set][i]);
+        }
+        u32x2 xw[SETS];
+#pragma unroll
+        for (int set = 0; set < SETS; ++set)
+          xw[set] = u32x2{(uint32_t)ax[set][0] | ((uint32_t)ax[set][1] << 16), (uint32_t)ax[set][2] | ((uint32_t)ax[set][3] << 16)};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          u32x2 bv, bz;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t ma = (s < 2) ? mlo[2 * h] : mhi[2 * h], mb = (s < 2) ? mlo[2 * h + 1] : mhi[2 * h + 1];
+            const uint32_t mask = __builtin_amdgcn_perm(mb, ma, (s & 1) ? 0x07060302u : 0x05040100u);
+            bv[h] = vw[h] & mask;
+            bz[h] = zw[h] & mask;
+          }
+          if constexpr (TILE_ROUND) {
+            constexpr int PLUS = DUAL ? 0 : 1;
+            acc[PLUS][s] = Ops::sparse(xw[0], bv, acc[PLUS][s]);
+            acc[PLUS + 1][s] = Ops::sparse(xw[SETS - 1], bz, acc[PLUS + 1][s]);
+          } else {
+#pragma unroll
+            for (int set = 0; set < SETS; ++set) {
+              acc[2 * set][s] = Ops::sparse(xw[set], bv, acc[2 * set][s]);
+              if (with_z) acc[2 * set + 1][s] = Ops::sparse(xw[set], bz, acc[2 * set + 1][s]);
+            }
+          }
+        }
+      }
+      asm volatile("" ::: "memory");                        // the next refill overwrites the window
+    }
+  }
+
+  // ---- dense: this wave's blocks of 128 columns, codes and x one block ahead ----
+  uint16_t* const xs = reinterpret_cast<uint16_t*>(red + wave * RED);              // [16][SP_XROW], in place of the window
+  uint32_t magic_lo = 0x64006400u, magic_hi = 0x54005400u;
+  asm volatile("" : "+v"(magic_lo), "+v"(magic_hi));
+  const half8_t minus_offsets = {(_Float16)-1032.0f, (_Float16)-1032.0f, (_Float16)-72.0f, (_Float16)-72.0f,
+                                 (_Float16)-1032.0f, (_Float16)-1032.0f, (_Float16)-72.0f, (_Float16)-72.0f};
+  // MORE at compile time: as a run-time condition around the loads it made the compiler drain them in every iteration
+  auto dense_block = [&](int b, auto more_tag) {
+    constexpr bool MORE = decltype(more_tag)::value;
+    const bool empty = 128 * b + 8 * xr_piece >= K;         // the columns this lane has loaded lie past the end of K
+    frag_t af[SETS][4];
+#pragma unroll
+    for (int set = 0; set < SETS; ++set) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<frag_t*>(xs + (4 * i + xr_row) * SP_XROW + 8 * xr_piece) =
+            Ops::activations(empty ? u32x4{0u, 0u, 0u, 0u} : xr[set][i]);
+      asm volatile("" ::: "memory");                        // written by the wave's other lanes; LDS keeps a wave's order
+#pragma unroll
+      for (int t = 0; t < 4; ++t) af[set][t] = *reinterpret_cast<const frag_t*>(xs + nn * SP_XROW + 32 * jj + 8 * t);
+      asm volatile("" ::: "memory");
+    }
+    if (MORE) load_x(b + 1);
+    const half4_t sh4 = __builtin_bit_cast(half4_t, sc);
+    if (MORE) load_scales(b + 1);
+    float4_t init[SETS];
+#pragma unroll
+    for (int set = 0; set < SETS; ++set) {
+      init[set] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (FAST) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) init[set] = Ops::dense(af[set][t], minus_offsets, init[set]);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const u32x4 qs = q[s];
+      if (MORE) load_q(b + 1, s);
+      float4_t tmp[SETS];
+#pragma unroll
+      for (int set = 0; set < SETS; ++set) tmp[set] = FAST ? init[set] : acc[set * DENSE1][s];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        frag_t w;
+        if constexpr (BF16) w = dequant_word_bf16(qs[t], (float)sh4[s]);
+        else if constexpr (LUT) w = sm_lut_word(qs[t], tb[s]);
+        else w = sm_dequant_word<FAST>(qs[t], magic_lo, magic_hi, half2_t{sh4[s], sh4[s]});
+#pragma unroll
+        for (int set = 0; set < SETS; ++set) tmp[set] = Ops::dense(af[set][t], w, tmp[set]);
+      }
+#pragma unroll
+      for (int set = 0; set < SETS; ++set) {
+        if (FAST) {
+          const float sf = (float)sh4[s];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[set * DENSE1][s][r] = fmaf(tmp[set][r], sf, acc[set * DENSE1][s][r]);
+        } else {
+          acc[set * DENSE1][s] = tmp[set];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);                    // subtiles in program order: fewer registers in flight
+    }
+  };
+  for (int b = b0; b + 1 < b1; ++b) dense_block(b, std::true_type{});
+  if (b0 < b1) dense_block(b1 - 1, std::false_type{});
+
+  // ---- sum over the waves, in wave order ----
+  {
+    float4_t* const mine = reinterpret_cast<float4_t*>(red + wave * RED);
+#pragma unroll
+    for (int i = 0; i < NACC; ++i)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) mine[i * 256 + s * 64 + lane] = acc[i][s];
+  }
+  __syncthreads();
+  // Output o of 1024: column o & 15 of subtile o >> 8, token row (o >> 4) & 15; its accumulator sits in register
+  // m & 3 of lane 16 (m >> 2) + column.  Wave-wide LDS reads touch every bank once, y is stored 64 bytes at a time.
+  double lp = 0.0, lm = 0.0;
+  for (int o = tid; o < 1024; o += (int)blockDim.x) {
+    const int m = (o >> 4) & 15, n = band * 64 + 16 * (o >> 8) + (o & 15);
+    if (m >= M || n >= N) continue;
+    const float* p = red + (o >> 8) * 256 + ((m >> 2) * 16 + (o & 15)) * 4 + (m & 3);
+    float t = 0.0f;
+    if (a.loss_mode) t = __uint_as_float((uint32_t)g_target[(size_t)m * N + n] << 16);
+    float d[NACC];
+#pragma unroll
+    for (int i = 0; i < NACC; ++i) d[i] = 0.0f;
+    for (int w = 0; w < waves; ++w, p += RED) {
+#pragma unroll
+      for (int i = 0; i < NACC; ++i) d[i] += p[i * 1024];
+    }
+    float yp, ym;
+    if (TILE_ROUND) {
+      yp = DUAL ? d[0] : d[0] + d[1];
+      ym = DUAL ? d[1] : d[0] + d[NACC - 1];
+    } else {
+      yp = d[0] + a.eps * d[1];
+      ym = d[NACC - 2] - a.eps * d[NACC - 1];
+    }
+    if (a.loss_mode) {
+      const float dp = yp - t, dm = ym - t;
+      lp += (double)(dp * dp);
+      lm += (double)(dm * dm);
+    } else {
+      g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : a.store_sign < 0 ? ym : yp;
+    }
+  }
+  if (a.loss_mode) {
+    __shared__ double part[2][SP_MAX_WAVES];
+    lp = wave_sum(lp);
+    lm = wave_sum(lm);
+    if (lane == 0) { part[0][wave] = lp; part[1][wave] = lm; }
+    __syncthreads();
+    if (tid == 0) {
+      double bp = 0.0, bm = 0.0;
+      for (int w = 0; w < waves; ++w) { bp += part[0][w]; bm += part[1][w]; }
+      const int pi = mt.partial_base + slice * ((N + 63) >> 6) + band;
+      ((double __attribute__((address_space(1)))*)a.partial_plus)[pi] = bp * mt.loss_scale;
+      ((double __attribute__((address_space(1)))*)a.partial_minus)[pi] = bm * mt.loss_scale;
+    }
+  }
+}
+
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>
+static int launch(int waves, int workgroups, const SmallArgs& a, hipStream_t stream) {
+  constexpr size_t per_wave = split_sets<DUAL, TILE_ROUND>() * 1024 * sizeof(float);
+  constexpr int most = split_max_waves<MODE, DUAL, TILE_ROUND>();
+  if (waves > most) waves = most;
+  static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
+  const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND>;
+  const int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, per_wave * most);
+  if (rc != SZO_OK) return rc;
+  kern<<<(unsigned)workgroups, 64 * waves, per_wave * waves, stream>>>(a);
+  SZO_LAUNCH_CHECK();
+  return SZO_OK;
+}
+
+template <bool DUAL>
+static int launch_mode(int mode, bool bf16, bool tile_round, int waves, int workgroups, const SmallArgs& a, hipStream_t stream) {
+  if (bf16) return launch<SM_PLAIN, true, DUAL, true>(waves, workgroups, a, stream);
+  if (tile_round) return launch<SM_PLAIN, false, DUAL, true>(waves, workgroups, a, stream);
+  if (mode == SM_FAST) return launch<SM_FAST, false, DUAL, false>(waves, workgroups, a, stream);
+  if (mode == SM_LUT) return launch<SM_LUT, false, DUAL, false>(waves, workgroups, a, stream);
+  return launch<SM_PLAIN, false, DUAL, false>(waves, workgroups, a, stream);
+}
+
+int split_launch(int mode, bool dual, bool bf16, bool tile_round, int waves, int workgroups, const SmallArgs& a, hipStream_t stream) {
+  return dual ? launch_mode<true>(mode, bf16, tile_round, waves, workgroups, a, stream)
+              : launch_mode<false>(mode, bf16, tile_round, waves, workgroups, a, stream);
+}
+
+}  // namespace szo
