@@ -26,6 +26,7 @@
 #include <vector>
 #include "szo_internal.h"
 #include "szo_rng.h"
+#include "szo_tile.h"
 #include <mutex>
 #include <type_traits>
 
@@ -38,154 +39,6 @@ static __device__ __align__(256) double scratch[kNoAllocMaxPartials];
 
 namespace szo {
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
-typedef float float16_t __attribute__((ext_vector_type(16)));
-
-constexpr int BK = 64;                 // K extent of one staged tile = SZO_TILE_COLS
-constexpr int kWindow = 256;           // sensitive entries computed per refill of a wave's window
-
-struct FwdParams {
-  const uint16_t* x;        // bf16 [M,K]
-  const uint8_t* qweight;   // [N,K/2]
-  const uint16_t* scales;   // fp16 [N,K/group]
-  const uint32_t* tile_ptr;
-  const uint32_t* sp_idx;
-  const float* sp_val;
-  float* y;                 // may be null when the loss is fused
-  const uint16_t* target;   // bf16 [M,N] (fused loss only)
-  int M, N, K;
-  int group_shift;          // log2(group)
-  int ktiles;               // K / 64
-  int bands;                // ceil(N / 64)
-  int grid_m, grid_n;
-  uint32_t nnz;
-  uint32_t div_mul;         // exact division of a flat index by K: see fast_div
-  int div_shift;
-  uint64_t nnz_base, seed, step;
-  float signed_eps;         // sign * eps; 0 = no perturbation
-  double* partials;         // fused loss: one scaled partial per workgroup, [grid_m*grid_n]
-  double loss_scale;
-  int first_block;          // grouped launch: id of this entry's first workgroup (a multiple of 8)
-  int pad_;
-  const uint16_t* lut;      // fp16 [N,16], table format only
-  // grouped launch: one entry runs BOTH forwards of its matrix; the fields above describe the +eps one
-  const uint16_t* x_minus;  // activations of the -eps forward (= x unless the layer has a second set)
-  double* partials_minus;   // loss partials of the -eps forward
-};
-
-// floor(v / d) for 32-bit v with a precomputed multiplier (Granlund-Montgomery, round-up form).
-__device__ __forceinline__ uint32_t fast_div(uint32_t v, uint32_t mul, int shift) {
-  const uint32_t t = __umulhi(mul, v);
-  return (t + ((v - t) >> 1)) >> shift;
-}
-
-// Position of column kk (0..63) of tile row r inside the LDS tile, in 16-bit elements.
-// Rows are 64 elements (128 bytes), so two rows span the 64 four-byte banks; the eight
-// 16-byte chunks of a row are XOR-swizzled with row_swizzle(row), chosen for both ways the tile is
-// accessed with 16 bytes per lane.  Reads are served 16 lanes (256 bytes) per cycle: 16 lanes reading the
-// same chunk of 16 consecutive rows must touch every bank exactly once, which (row / 2) mod 8 gives.
-// Writes are served 8 lanes (128 bytes) per cycle and conflict when two of them fall into the same 16 bytes
-// modulo 128, whatever the row's parity (measured: a weight wave writing one chunk of 64 consecutive rows
-// took 16 cycles instead of 8 with the (row / 2) swizzle alone, 15 % of all LDS cycles of the kernel);
-// the extra (row & 1) * 4 makes 8 consecutive rows distinct as well, and keeps the read property.
-// In f16 mode the eight elements of a chunk are stored in the order
-// 0,4,1,5,2,6,3,7 -- the order in which two nibbles per 16-bit lane fall out of a packed
-// word -- and the activations are stored in the same order, which leaves the dot product
-// unchanged.
-__device__ __forceinline__ int row_swizzle(int r) { return ((r >> 1) & 7) ^ ((r & 1) << 2); }
-
-template <int DT>
-__device__ __forceinline__ int lds_pos(int r, int kk) {
-  const int chunk = kk >> 3, w = kk & 7;
-  const int p = (DT == SZO_TILE_F16) ? (((w & 3) << 1) | (w >> 2)) : w;
-  return r * BK + (((chunk ^ row_swizzle(r)) << 3) | p);
-}
-
-__device__ __forceinline__ int chunk_off(int r, int chunk) {   // in 16-bit elements
-  return r * BK + ((chunk ^ row_swizzle(r)) << 3);
-}
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// ---- activations: word w (0..3) of the staged form of one 16-byte chunk of 8 bf16 --------------
-// f16 mode pairs elements (0,4) (1,5) (2,6) (3,7); bf16 -> fp32 is a shift and fp32 -> fp16 is
-// exact for |x| in [2^-14, 65504] (8-bit significand).
-template <int DT>
-__device__ __forceinline__ uint32_t stage_x_word(u32x4 u, int w) {
-  if (DT == SZO_TILE_BF16) return u[w];
-  const uint32_t first = (w < 2) ? u[0] : u[1], second = (w < 2) ? u[2] : u[3];
-  float a, b;
-  if ((w & 1) == 0) { a = __uint_as_float(first << 16); b = __uint_as_float(second << 16); }
-  else              { a = __uint_as_float(first & 0xFFFF0000u); b = __uint_as_float(second & 0xFFFF0000u); }
-  auto h = __builtin_amdgcn_cvt_pkrtz(a, b);
-  return __builtin_bit_cast(uint32_t, h);
-}
-
-// ---- weights: word w (0..3) of the 8 dequantised elements of one 32-bit word of codes ----------
-// dq = (code - 8) * scale, one rounding to the tile type.  f16 mode: a nibble in mantissa bits
-// 0..3 under exponent pattern 0x6400 reads 1024 + code, one in bits 4..7 under 0x5400 reads
-// 64 + code; removing the offset is exact and the product with the fp16 scale is rounded once,
-// which is the rounding of the exact (code-8)*scale.  Output pairs are codes (0,4) (1,5) (2,6) (3,7).
-// (a & mask) | bits in one VALU instruction, `bits` in a VGPR.  Inline assembly keeps the instruction in
-// the slot it is written in (as plain C the tiled step measured 1 % slower).  The compiler's hazard
-// handling cannot see into it, which is safe here and only here: the result feeds packed-half arithmetic
-// and an LDS store, never a matrix instruction, whose operands all come from LDS reads
-// (tests/test_isa_hazards.py checks the generated code for exactly that).
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t bits_vgpr) {
-  uint32_t r;
-  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(mask), "v"(bits_vgpr));
-  return r;
-}
-
-struct DequantConsts { uint32_t magic_lo, magic_hi; };   // 0x64006400 and 0x54005400 held in VGPRs
-
-template <int DT>
-__device__ __forceinline__ uint32_t dequant_out(uint32_t q, int w, float scale_f32, half2_t scale_h2,
-                                                const DequantConsts& k) {
-  if (DT == SZO_TILE_F16) {
-    const uint32_t src = (w < 2) ? q : (q >> 8);
-    half2_t h;
-    if ((w & 1) == 0) {
-      h = __builtin_bit_cast(half2_t, and_or(src, 0x000F000Fu, k.magic_lo));
-      const half2_t off = {(_Float16)1032.0f, (_Float16)1032.0f};
-      h = (h - off) * scale_h2;
-    } else {
-      h = __builtin_bit_cast(half2_t, and_or(src, 0x00F000F0u, k.magic_hi));
-      const half2_t off = {(_Float16)72.0f, (_Float16)72.0f};
-      h = (h - off) * scale_h2;
-    }
-    return __builtin_bit_cast(uint32_t, h);
-  } else {
-    const float m8s = -8.0f * scale_f32;
-    float2_t f = {fmaf((float)((q >> (8 * w)) & 15u), scale_f32, m8s),          // exact in fp32
-                  fmaf((float)((q >> (8 * w + 4)) & 15u), scale_f32, m8s)};
-    bf16x2_t b = __builtin_convertvector(f, bf16x2_t);                            // round to nearest even
-    return __builtin_bit_cast(uint32_t, b);
-  }
-}
-
-template <int DT> struct Frag;
-template <> struct Frag<SZO_TILE_F16> {
-  typedef half8_t type;
-  static __device__ __forceinline__ float16_t mfma(type a, type b, float16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ float load(const uint16_t* p) { return (float)*reinterpret_cast<const _Float16*>(p); }
-  static __device__ __forceinline__ void store(uint16_t* p, float v) { *reinterpret_cast<_Float16*>(p) = (_Float16)v; }
-};
-template <> struct Frag<SZO_TILE_BF16> {
-  typedef bf16x8_t type;
-  static __device__ __forceinline__ float16_t mfma(type a, type b, float16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ float load(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
-  static __device__ __forceinline__ void store(uint16_t* p, float v) { *reinterpret_cast<__bf16*>(p) = (__bf16)v; }
-};
-
 // Workgroup = WAVES_M x WAVES_N waves; each wave computes (32*WMB) x (32*WNB) outputs.
 //
 // Schedule of one K step of one wave.  The wave issues SLOTS = 4*WMB*WNB MFMAs.  Its staging
@@ -197,25 +50,6 @@ template <> struct Frag<SZO_TILE_BF16> {
 // the compiler from regrouping the slots.  Global loads are in place: as soon as a unit's
 // registers have been consumed they are reloaded with the same unit of the tile after next,
 // which gives every load one full K step (about a microsecond) to arrive.
-// Workgroup id -> output tile.  Workgroup ids go round-robin over the 8 XCDs, each with its own L2, so
-// ids with equal (id % 8) are first made consecutive ("logical" id): the workgroups resident on one XCD
-// at a time (32 with the 256x256 tile) are then a run of consecutive logical ids, and logical ids walk
-// the tile grid in strips of `strip` row blocks, so that run covers strip x (32 / strip) tiles which
-// share `strip` activation strips and 32 / strip weight strips through that L2.  `count` ids in all;
-// `bid`'s residue mod 8 is its XCD both in a launch of its own and in a grouped launch (entries start
-// at multiples of 8).
-__device__ __forceinline__ int logical_block(int bid, int count) {
-  const int q = count >> 3, r = count & 7;
-  const int xcd = bid & 7, idx = bid >> 3;
-  return xcd * q + min(xcd, r) + idx;
-}
-__device__ __forceinline__ void tile_of_logical(int L, int grid_m, int grid_n, int strip, int& bm, int& bn) {
-  const int width = strip * grid_n, g = L / width, first_m = strip * g;
-  const int gsize = min(grid_m - first_m, strip), rem = L - g * width;
-  bm = first_m + rem % gsize;
-  bn = rem / gsize;
-}
-
 // DUAL (grouped launch of a step, loss fused, both forwards read the same activations): the workgroup
 // computes BOTH forwards of a tile of BM x BN/2 outputs.  Rows [0, BN/2) of the weight tile in LDS hold
 // W + eps z, rows [BN/2, BN) the same rows of W with W - eps z: the codes are loaded and dequantised once
@@ -353,8 +187,8 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     // load instructions of the wave (64 rows x 16 bytes each) cover it without gaps.  Bands past N re-read the
     // last band (their outputs are never stored) and column tiles past the end re-read the last
     // tile (never consumed): the loads stay unconditional and in order.
-    const uint8_t* qrow[2];
-    const uint16_t* srow[2];
+    global_u8 qrow[2];
+    global_u16 srow[2];
     {
       const size_t bsafe = (size_t)min(band, p.bands - 1);
 #pragma unroll
@@ -370,7 +204,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     dqk.magic_lo = 0x64006400u; dqk.magic_hi = 0x54005400u;
     asm volatile("" : "+v"(dqk.magic_lo), "+v"(dqk.magic_hi));   // keep them in registers, not as literals
     auto load_q = [&](int kt, int i) {
-      qreg[i] = *reinterpret_cast<const u32x4*>(qrow[i] + (size_t)min(kt, nk - 1) * (64 * BK / 2));
+      qreg[i] = *reinterpret_cast<global_u32x4>(qrow[i] + (size_t)min(kt, nk - 1) * (64 * BK / 2));
     };
     auto load_s = [&](int kt, int i) {
       sreg[i] = srow[i][(size_t)((min(kt, nk - 1) * BK + 32 * i) >> p.group_shift) * 64];
@@ -388,10 +222,10 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
         uint32_t idx[4];
         float val[4];
         if (j + 3 < pr.nnz) {
-          const uint4 iv = *reinterpret_cast<const uint4*>(pr.sp_idx + j);
-          const float4 vv = *reinterpret_cast<const float4*>(pr.sp_val + j);
-          idx[0] = iv.x; idx[1] = iv.y; idx[2] = iv.z; idx[3] = iv.w;
-          val[0] = vv.x; val[1] = vv.y; val[2] = vv.z; val[3] = vv.w;
+          const u32x4 iv = *reinterpret_cast<global_u32x4>(pr.sp_idx + j);
+          const u32x4 vv = *reinterpret_cast<global_u32x4>(pr.sp_val + j);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) { idx[c] = iv[c]; val[c] = __uint_as_float(vv[c]); }
         } else {
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
@@ -478,15 +312,15 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       // lane l stages row l of the band, all 64 columns of a tile (32 bytes of codes, two 16-byte loads).
       static_assert(DT == SZO_TILE_F16 && SCATTER_IN_SLOTS, "table format: fp16 tile, 32-slot schedule");
       const int lrow = wave * 64 + lane;                           // row of the weight tile
-      const uint8_t* const qr = p.qweight + ((size_t)min(band, p.bands - 1) * (size_t)nk * 64 + (size_t)lane) * 32;
+      const global_u8 qr = p.qweight + ((size_t)min(band, p.bands - 1) * (size_t)nk * 64 + (size_t)lane) * 32;
       u32x4 qv[2];
       auto load_qv = [&](int kt, int h) {
-        qv[h] = *reinterpret_cast<const u32x4*>(qr + (size_t)min(kt, nk - 1) * (64 * BK / 2) + 16 * h);
+        qv[h] = *reinterpret_cast<global_u32x4>(qr + (size_t)min(kt, nk - 1) * (64 * BK / 2) + 16 * h);
       };
       uint32_t lo_a0, lo_a1, lo_b0, lo_b1, hi_a0, hi_a1, hi_b0, hi_b1;
       {
         // rows past N re-read the last row's table: their outputs are never used
-        const u32x4* const lp = reinterpret_cast<const u32x4*>(p.lut + (size_t)min(n0 + lrow, p.N - 1) * 16);
+        const global_u32x4 lp = reinterpret_cast<global_u32x4>(p.lut + (size_t)min(n0 + lrow, p.N - 1) * 16);
         const u32x4 a = lp[0], b = lp[1];                          // entries 0-7 and 8-15, two per word
         lo_a0 = __builtin_amdgcn_perm(a[1], a[0], 0x06040200u); lo_a1 = __builtin_amdgcn_perm(a[3], a[2], 0x06040200u);
         hi_a0 = __builtin_amdgcn_perm(a[1], a[0], 0x07050301u); hi_a1 = __builtin_amdgcn_perm(a[3], a[2], 0x07050301u);
@@ -702,13 +536,13 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     // =============================== activation wave ===========================================
     const int xt = tid - 64 * W_WAVES;
     const int xc = xt & 7, xr = xt >> 3;                       // chunk, row (plus X_ROWS_PER_PASS*u)
-    const uint16_t* xrow[8];
+    global_u16 xrow[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       xrow[u] = p.x + (size_t)min(m0 + xr + X_ROWS_PER_PASS * u, p.M - 1) * p.K + xc * 8;
     u32x4 xreg[8];
     auto load_x = [&](int kt, int u) {
-      xreg[u] = *reinterpret_cast<const u32x4*>(xrow[u] + min(kt, nk - 1) * BK);
+      xreg[u] = *reinterpret_cast<global_u32x4>(xrow[u] + min(kt, nk - 1) * BK);
     };
     u32x4 outw;
     auto make_slice = [&](int dst, int load_kt) {
@@ -771,15 +605,15 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       const int ncl = min(n0 + 8 * c, pe.N - 8);
 #pragma unroll
       for (int b = 0; b < PASSES; b += BATCH) {
-        uint4 t[BATCH];
+        u32x4 t[BATCH];
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
           const int m = min(m0 + r0 + ROWS_PER_PASS * (b + i), pe.M - 1);
-          t[i] = *reinterpret_cast<const uint4*>(pe.target + (size_t)m * pe.N + ncl);
+          t[i] = *reinterpret_cast<global_u32x4>(pe.target + (size_t)m * pe.N + ncl);
         }
 #pragma unroll
         for (int i = 0; i < BATCH; ++i)
-          *reinterpret_cast<uint4*>(T + (r0 + ROWS_PER_PASS * (b + i)) * TROW + 16 * c) = t[i];
+          *reinterpret_cast<u32x4*>(T + (r0 + ROWS_PER_PASS * (b + i)) * TROW + 16 * c) = t[i];
       }
       __syncthreads();
     }
@@ -990,18 +824,18 @@ static int dispatch_tile(FwdParams& p, hipStream_t stream) {
 
 // Enqueues one forward.  With `partials` set the loss is fused: workgroup b stores
 // scale * sum (y - target)^2 of its tile to partials[b].
-static int fill_params(FwdParams& p, const szo_linear_desc* d, uint64_t seed, uint64_t step, int sign, float eps,
-                       double* partials, double scale) {
+int fill_params(FwdParams& p, const szo_linear_desc* d, uint64_t seed, uint64_t step, int sign, float eps,
+                double* partials, double scale) {
   p = FwdParams{};
-  p.x = (const uint16_t*)d->x;
-  p.qweight = d->qweight;
-  p.scales = (const uint16_t*)d->scales;
-  p.lut = (const uint16_t*)d->lut;
-  p.tile_ptr = d->tile_ptr;
-  p.sp_idx = d->sp_idx;
-  p.sp_val = d->sp_val;
-  p.y = d->y;
-  p.target = (const uint16_t*)d->target;
+  p.x = (global_u16)d->x;
+  p.qweight = (global_u8)d->qweight;
+  p.scales = (global_u16)d->scales;
+  p.lut = (global_u16)d->lut;
+  p.tile_ptr = (global_u32)d->tile_ptr;
+  p.sp_idx = (global_u32)d->sp_idx;
+  p.sp_val = (global_f32)d->sp_val;
+  p.y = (global_f32_out)d->y;
+  p.target = (global_u16)d->target;
   p.M = (int)d->M; p.N = (int)d->N; p.K = (int)d->K;
   p.nnz = (uint32_t)d->nnz;
   p.group_shift = d->format == SZO_FORMAT_LUT ? 0 : ilog2_exact(d->group);
@@ -1017,7 +851,7 @@ static int fill_params(FwdParams& p, const szo_linear_desc* d, uint64_t seed, ui
   }
   p.nnz_base = d->nnz_base; p.seed = seed; p.step = step;
   p.signed_eps = (float)sign * eps;
-  p.partials = partials;
+  p.partials = (global_f64_out)partials;
   p.loss_scale = scale;
   return SZO_OK;
 }
@@ -1030,7 +864,7 @@ static int run_forward(const szo_linear_desc* d, uint64_t seed, uint64_t step, i
   FwdParams p;
   const int frc = fill_params(p, d, seed, step, sign, eps, partials, scale);
   if (frc != SZO_OK) return frc;
-  if (step_minus && d->x_minus) p.x = (const uint16_t*)d->x_minus;
+  if (step_minus && d->x_minus) p.x = (global_u16)d->x_minus;
   if (d->format == SZO_FORMAT_LUT)
     return fuse ? launch<2, 4, 4, 2, SZO_TILE_F16, true, SZO_FORMAT_LUT>(p, stream)
                 : launch<2, 4, 4, 2, SZO_TILE_F16, false, SZO_FORMAT_LUT>(p, stream);
@@ -1103,8 +937,8 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
     FwdParams p;
     const int rc = fill_params(p, d, seed, step, +1, eps, partials + offset, scale);
     if (rc != SZO_OK) return rc;
-    p.x_minus = d->x_minus ? (const uint16_t*)d->x_minus : p.x;
-    p.partials_minus = partials + T + offset;
+    p.x_minus = d->x_minus ? (global_u16)d->x_minus : p.x;
+    p.partials_minus = (global_f64_out)(partials + T + offset);
     p.grid_m = gm; p.grid_n = gn;
     p.y = nullptr;                                          // the step's fused path never writes y
     p.first_block = (int)first_block;
