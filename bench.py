@@ -47,11 +47,12 @@ def algorithmic_bytes_fwd(m, M, fused=True):
 
 
 def few_token_path(M, two_sets=False):
-    """The library's rule for the few-token path (slices of 16 / 32 token rows instead of 256-row tiles):
-    at most 15 slices of 32 rows (16 with two activation sets), and fewer than 7.5 of them per row of
-    tiles.  Only used to label the kernel and to pick default step counts."""
-    rows = 16 if two_sets else 32
-    slices, tile_rows = (M + rows - 1) // rows, (M + 255) // 256
+    """Whether a step over a large stack computes its dense product once for both signs: up to 512 tokens with one set of
+    activations, at most 15 slices of 16 rows that beat 7.5 of them per row of 256-row tiles with two.  Only used to label
+    the kernel and to pick default step counts."""
+    if not two_sets:
+        return M <= 512
+    slices, tile_rows = (M + 15) // 16, (M + 255) // 256
     return slices <= 15 and 2 * slices < 15 * tile_rows
 
 
@@ -88,13 +89,13 @@ def rooflines(mats, M, t, few, fused, traffic=None):
     launches = t["fwd_launches"]
     k_ms = t["fwd_ms"] / launches
     one_pass = float(sum(algorithmic_bytes_fwd(m, M, fused) for m in mats))
-    if few:       # one launch streams every matrix once and serves both signs
-        kernel = "small_m_kernel"
+    if few:       # one launch computes the dense product once and serves both signs
+        kernel = "small_m_kernel" if M <= 32 else "onepass_table_kernel"
         launch_bytes = one_pass * steps / launches
     else:         # large fused steps run every forward of the step in one table-driven launch
         kernel = "linear_fwd_table_kernel" if launches == steps else "linear_fwd_kernel"
         launch_bytes = one_pass * 2 * steps / launches
-    launch_flops = 2 * fwd_flops * steps / launches
+    launch_flops = (1 if few else 2) * fwd_flops * steps / launches      # dense products that are executed
     tflops = launch_flops / (k_ms * 1e-3) / 1e12
     gbs = launch_bytes / (k_ms * 1e-3) / 1e9
     mfma_bound = (launch_flops / launch_bytes) > (PEAK_MFMA_16BIT_TFLOPS * 1e12) / (PEAK_HBM_GBS * 1e9)
@@ -269,7 +270,7 @@ def main():
                     help="give every layer a second, different set of activations for its -eps forward (desc.x_minus), "
                          "as inside a model; the few-token path then still reads the weights once for both signs")
     ap.add_argument("--one-dense-pass", action="store_true",
-                    help="SZO_STEP_ONE_DENSE_PASS: the slicing path of the few-token case at any token count (the dense "
+                    help="SZO_STEP_ONE_DENSE_PASS at any token count (the dense "
                          "product of a slice is computed once and serves both signs; valid because both forwards of a "
                          "layer see the same x in this benchmark).  Not the default: see include/szo.h")
     ap.add_argument("--tile-config", type=int, default=0, choices=[0, 1, 2, 3, 4, 5, 6, 7],
@@ -421,7 +422,7 @@ def main():
                                f"mask {cfg['density']:g} {cfg['mask']}, eps={eps}, lr={lr}",
                    "loss": "fused into the forward epilogue" if flags else "separate kernel",
                    "dense_product": ("once per sign" if (not few or args.two_activation_sets)
-                                     else "once per slice of token rows, shared by both signs"),
+                                     else "once, shared by both signs"),
                    "activations": "x for +eps, x_minus for -eps" if args.two_activation_sets else "one x for both signs",
                    "tile": args.tile, "format": args.format, "accumulate": "f32", "loss_accumulate": "f64"},
         "step_tflops": round(step_flops / (ms_per_step * 1e-3) / 1e12, 2),

@@ -155,9 +155,12 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * scalars: device double[3], overwritten with (L+, L-, g).  flags: bit 0 set = use the
  * loss-fusing forward and never write y (desc->y may then be NULL); large steps then run all
  * forwards (every layer, both signs) as one launch driven by a descriptor table that is staged in
- * the workspace, and steps with few tokens per layer (up to 224, and 257 to 448: wherever slices of
- * 32 token rows beat rows of 256-row tiles) stream the weights once per 16 or 32 token rows, each
- * pass serving both signs.
+ * the workspace.  Steps of up to 512 tokens whose layers have one set of activations compute the dense
+ * product once for both signs, in whichever kernel is fastest for their size: few tokens stream the
+ * weights once per 16 to 48 token rows, more of them run on the matrix cores in tiles of 64 token rows.
+ * With bit 0 clear y holds the -eps forward's outputs afterwards, and the loss is summed in fp64 from the
+ * fp32 outputs; layers with one set of activations and no output buffer in common with another layer run as
+ * one launch there too.
  * descs: host array, read before the call returns.  Everything is enqueued on `stream`.  The
  * descriptor tables of the grouped launches (forwards of a fused step; the update of every step)
  * travel through a ring of eight pinned host buffers per host thread (allocated on first use,
@@ -168,11 +171,10 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * be captured.  The workspace must not be shared with a call running concurrently on another
  * stream. */
 #define SZO_STEP_FUSED_LOSS 1
-/* Bit 1 (with bit 0): take the slicing path of the few-token case at ANY token count.  Both forwards of
- * a layer see the same x in this call, so y(+-) = x (dq + v)^T +- eps x z^T: the dense product is
- * computed once per slice of up to 48 token rows and serves both signs, the sparse products are added.
- * Same results as two forwards; half the dense work; the weights are streamed once per slice.  Not the
- * default for many tokens because it does not carry over to a caller whose two forwards see different
+/* Bit 1 (with bit 0): one dense product per layer at ANY token count.  Both forwards of a layer see the
+ * same x in this call, so y(+-) = x (dq + v)^T +- eps x z^T: the dense product is computed once and serves
+ * both signs, the sparse products are added.  Same results as two forwards; half the dense work.  Not the
+ * default beyond 512 tokens because it does not carry over to a caller whose two forwards see different
  * activations (every layer of a real model but the first), who calls szo_linear_fwd per sign instead. */
 #define SZO_STEP_ONE_DENSE_PASS 2
 int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
@@ -183,14 +185,14 @@ int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, u
  * SZO_STEP_FUSED_LOSS (scalars = (L+, L-, g); every layer's sp_val updated; desc->y is not written),
  * up to the order in which the fp64 loss partials are added.  It takes no workspace: the loss partials
  * live in a fixed array inside the library (1 MiB per GPU, kept until the process ends), and it
- * stages no descriptor table: every layer is one plain launch of the few-token kernel (when every
- * layer of the step qualifies for it and none has x_minus), else one tiled launch per sign; then one
+ * stages no descriptor table: every layer is one plain launch that serves both signs (when every
+ * layer of the step qualifies for one and none has x_minus), else one tiled launch per sign; then one
  * reduction, and one update launch per layer.  It calls no
  * allocating routine (no hipMalloc / hipHostMalloc, no event creation unless szo_kernel_timing is
  * on) and can be captured into a HIP graph.
  * Limit: at most 65 536 workgroups per sign over the whole step (one per 256 x 256 output tile, or
- * per 128 x 128 tile for small layers, or per 64- or 256-column strip and slice of token rows of a few-token
- * layer): beyond that SZO_EUNSUPPORTED, with nothing enqueued.  A Llama-2-7B decoder block at 4096
+ * per 128 x 128 tile for small layers, or per 64- or 256-column strip and slice of token rows where one
+ * launch serves both signs): beyond that SZO_EUNSUPPORTED, with nothing enqueued.  A Llama-2-7B decoder block at 4096
  * tokens has 3 088 per sign.
  * All calls on one GPU share that array: calls that overlap in time on one GPU (different streams
  * or host threads) race on it.  Nothing in it needs clearing between calls (every partial that is
@@ -299,7 +301,8 @@ int szo_debug_zbar(uint64_t nnz_base, int64_t nnz, uint64_t seed, uint64_t step,
  * 7 = as 0 and the few-token path loads its codes as a non-temporal stream in every launch with one slice
  * of token rows per strip (by default only when the launch streams more codes than the last-level cache
  * holds), 8 / 9 = as 0 and the few-token path takes its kernel for small launches (K split over the waves of
- * a workgroup) always / never, 10 = 9 and 7.
+ * a workgroup) always / never, 10 = 9 and 7, 11 = szo_zo_step takes the kernel that computes one dense
+ * product per layer in tiles of 64 token rows wherever it can (chosen by size with 0, never with 1 to 10).
  * Process-wide, not thread-safe; results do not depend on it beyond fp32 summation order. */
 int szo_set_tile_config(int config);
 

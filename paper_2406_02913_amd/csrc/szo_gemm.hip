@@ -742,7 +742,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kerne
 static int g_tile_config = 0;      // 0 = choose by shape, 1 = 128x128 (4 waves), 2 = 256x256 (8 waves), 3 = 2 + always group the step,
                                    // 4, 5 = as 0 with the few-token path's 32- / 48-row passes forced (see small_m_force_rblocks),
                                    // 6 = as 0 + always group the step, 7 = as 0 + non-temporal code stream in every one-slice launch,
-                                   // 8, 9 = as 0 with the few-token path's split kernel always / never chosen, 10 = 9 and 7
+                                   // 8, 9 = as 0 with the few-token path's split kernel always / never chosen, 10 = 9 and 7,
+                                   // 11 = the one-dense-pass kernel wherever it can run (chosen by shape with 0, never with the others)
 static bool few_token_enabled() { return g_tile_config == 0 || g_tile_config >= 4; }
 
 static int ilog2_exact(int v) {
@@ -871,6 +872,20 @@ static int run_forward(const szo_linear_desc* d, uint64_t seed, uint64_t step, i
   if (d->tile_dtype == SZO_TILE_F16)
     return fuse ? dispatch_tile<SZO_TILE_F16, true>(p, stream) : dispatch_tile<SZO_TILE_F16, false>(p, stream);
   return fuse ? dispatch_tile<SZO_TILE_BF16, true>(p, stream) : dispatch_tile<SZO_TILE_BF16, false>(p, stream);
+}
+
+// The sparse update of a step: one grouped launch for the whole stack (per-matrix launches when the table does not fit).
+static int update_all(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float lr, double* scalars,
+                      void* workspace, hipStream_t s) {
+  if (n <= kMaxStepMatrices && small_m_table_bytes(n) <= kTableBytesPerMatrix * (size_t)kMaxStepMatrices)
+    return small_m_step(descs, n, seed, step, 0.0f, lr, (char*)workspace + kWorkspaceTableOffset, nullptr, scalars,
+                        false, true, s);
+  for (int i = 0; i < n; ++i) {
+    const int rc = szo_sparse_update(descs[i].sp_val, descs[i].sp_idx, descs[i].nnz, descs[i].nnz_base, seed, step,
+                                     scalars + 2, lr, s);
+    if (rc != SZO_OK) return rc;
+  }
+  return SZO_OK;
 }
 
 static double* partial_area(void* workspace) { return (double*)((char*)workspace + kWorkspaceHeader); }
@@ -1020,6 +1035,10 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
     }
     if (2 * T <= kNoAllocMaxPartials || !few_all) break;
   }
+  // ... or, where szo_zo_step would take it, the one-dense-pass kernel, if its partials fit.
+  int64_t one_T = onepass_partials(descs, n, few_token_enabled() && small_m_eligible(descs, n, false, false), false, false);
+  if (2 * one_T > kNoAllocMaxPartials) one_T = 0;
+  if (one_T) T = one_T;
   if (2 * T > kNoAllocMaxPartials) return SZO_EUNSUPPORTED;
   double* part = nullptr;
   int rc = noalloc_partials(&part);
@@ -1028,7 +1047,10 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
-    if (few_all) {
+    if (one_T) {
+      rc = onepass_one(d, seed, step, eps, part + off, part + T + off, s);
+      off += onepass_tiles(d);
+    } else if (few_all) {
       rc = small_m_launch_one(d, seed, step, eps, 1, true, part + off, part + T + off, compact, s);
       off += small_m_partials(d, compact);
     } else {
@@ -1052,11 +1074,12 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
 }
 
 int szo_set_tile_config(int config) {
-  if (config < 0 || config > 10) return SZO_EINVAL;
+  if (config < 0 || config > 11) return SZO_EINVAL;
   g_tile_config = config;
   small_m_force_rblocks(config == 4 ? 2 : config == 5 ? 3 : 0);
   small_m_force_stream_once(config == 7 || config == 10);
-  small_m_force_split(config == 8 ? 1 : config >= 9 ? -1 : 0);
+  small_m_force_split(config == 8 ? 1 : config == 9 || config == 10 ? -1 : 0);
+  onepass_force(config == 11 ? 1 : config == 0 ? 0 : -1);
   return SZO_OK;
 }
 
@@ -1118,6 +1141,16 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   // SZO_STEP_ONE_DENSE_PASS: the caller asks for that path at any token count.
   const bool few = fuse && few_token_enabled() && n <= kMaxStepMatrices &&
                    small_m_eligible(descs, n, (flags & SZO_STEP_ONE_DENSE_PASS) != 0, false);
+  // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip).
+  {
+    int64_t T = 0;
+    rc = onepass_forwards(descs, n, seed, step, eps, few && small_m_eligible(descs, n, false, false),
+                          (flags & SZO_STEP_ONE_DENSE_PASS) != 0, !fuse, (char*)workspace + kWorkspaceTableOffset,
+                          partial_area(workspace), &T, s);
+    if (rc == SZO_OK) rc = reduce_step(partial_area(workspace), (int)T, eps, scalars, s);
+    if (rc == SZO_OK) return update_all(descs, n, seed, step, lr, scalars, workspace, s);
+    if (rc != SZO_EUNSUPPORTED) return rc;      // otherwise nothing was enqueued
+  }
   if (few) {
     rc = small_m_step(descs, n, seed, step, eps, lr, (char*)workspace + kWorkspaceTableOffset,
                       partial_area(workspace), scalars, true, true, s);
@@ -1165,16 +1198,7 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
               : szo_spsa_g(scalars, scalars + 1, eps, scalars + 2, s);
     if (rc != SZO_OK) return rc;
   }
-  // one grouped update launch for the whole stack (per-matrix launches when the table does not fit)
-  if (n <= kMaxStepMatrices && small_m_table_bytes(n) <= kTableBytesPerMatrix * (size_t)kMaxStepMatrices)
-    return small_m_step(descs, n, seed, step, eps, lr, (char*)workspace + kWorkspaceTableOffset, nullptr, scalars,
-                        false, true, s);
-  for (int i = 0; i < n; ++i) {
-    rc = szo_sparse_update(descs[i].sp_val, descs[i].sp_idx, descs[i].nnz, descs[i].nnz_base, seed, step,
-                           scalars + 2, lr, s);
-    if (rc != SZO_OK) return rc;
-  }
-  return SZO_OK;
+  return update_all(descs, n, seed, step, lr, scalars, workspace, s);
 }
 
 }  // extern "C"

@@ -61,6 +61,17 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
                  void* table_dev, double* partial_plus, double* scalars, bool do_forward, bool do_update,
                  hipStream_t stream);
 
+// Many tokens, one dense product per layer (szo_onepass.hip): both forwards of every layer as one launch, the loss fused
+// and, with store_y, the -eps outputs written.  SZO_EUNSUPPORTED, with nothing enqueued, when the stack does not qualify.
+int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
+                     bool store_y, void* table_dev, double* partials, int64_t* partials_per_sign, hipStream_t stream);
+// The same for callers without a table: how many loss partials per sign the step has if it takes this kernel (0: it does
+// not), and one layer's launch.
+int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y);
+int64_t onepass_tiles(const szo_linear_desc* d);            // loss partials per sign of one layer
+int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, double* plus, double* minus, hipStream_t stream);
+void onepass_force(int how);                                // testing hook: 1 = wherever the kernel can, -1 = never, 0 = choose
+
 // Optional kernel timing (szo_kernel_timing): when switched on, every launch of a forward kernel
 // (kind 0) or of a sparse update kernel (kind 1) is bracketed by a pair of events on its own stream.
 // Both calls are no-ops when timing is off.  Defined in szo_kernels.hip.

@@ -1,0 +1,590 @@
+// A whole step's forwards with ONE dense product per layer, on the matrix cores.
+//
+// Both forwards of a layer of szo_zo_step read the same activations, and the sensitive weights of the two are
+// v + eps z and v - eps z (Section 3.4), so
+//     D = x (Dequantize(Q(w_dense)) + v)^T        Z = x z^T        y(+-) = D +- eps Z:
+// the dense product is the same in both and is computed once; the sensitive entries add products with a matrix that has
+// a few entries per 64 rows and 128 columns.
+//
+// Workgroup = 64 token rows x 256 rows of W, four waves, each one band of 64 rows of W by itself: a wave streams its
+// codes into registers and dequantises them there into operands of v_mfma_f32_32x32x16 (every operand serves two
+// blocks of 32 token rows), so the weights never pass through LDS and only the activations, converted once per
+// workgroup and shared by its waves, need a barrier (one per chunk of 128 columns, double buffered).  Two workgroups
+// share a CU and cover each other's barriers.
+//
+// Sensitive entries.  A wave keeps a ring of its band's entries in LDS, 256 computed at a time.  Sixteen of them at a
+// time are written as two one-hot 64 x 16 operands (v and z at [row][slot]) to LDS of the wave's own; the wave gathers
+// their columns of the staged x and multiplies both: D += x_g V^T, Z += x_g Z^T.  The first sixteen of a chunk (at a
+// density of 0.1 % it has eight on average) run inside the dense schedule, more of them in a loop behind it.
+//
+// Precision.  The dense weights are rounded to the tile type as in the tiled kernel; v and z are rounded to it one by
+// one (2^-11 relative in fp16) instead of as part of w +- eps z, and eps is applied in fp32.
+#include <algorithm>
+#include <cstddef>
+#include <type_traits>
+#include <vector>
+#include "szo_internal.h"
+#include "szo_rng.h"
+#include "szo_tile.h"
+
+namespace szo {
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int OP_BM = 64, OP_BN = 256, OP_WAVES = 4;        // token rows, rows of W, waves of a workgroup
+constexpr int OP_KC = 128;                                  // columns per chunk
+constexpr int OP_XROW = 2 * OP_KC + 16;                     // LDS row of staged activations in bytes (+16 against bank conflicts)
+constexpr int OP_RING = 512, OP_REFILL = 256;               // sensitive entries held / computed at a time per wave
+constexpr int OP_TROW = 2 * OP_BN + 32;                     // LDS row of the target tile in the epilogue
+
+struct OnePassLds {                                         // byte offsets
+  static constexpr int X = 0, RING = X + 2 * OP_BM * OP_XROW, HOT = RING + OP_WAVES * OP_RING * 8,   // [wave] 2 x 64 rows x 16 slots
+                       POS = HOT + OP_WAVES * 4096, SINK = POS + OP_WAVES * 64, BYTES = SINK + OP_WAVES * 256;
+};
+static_assert(OnePassLds::BYTES <= 80 * 1024 && OP_BM * OP_TROW <= OnePassLds::RING, "two workgroups per CU; the target tile replaces x");
+
+typedef const uint32_t __attribute__((address_space(4)))* table_words;
+__device__ __forceinline__ FwdParams read_entry(table_words e) {
+  struct Words { uint32_t w[sizeof(FwdParams) / 4]; } raw;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(FwdParams) / 4); ++i) raw.w[i] = e[i];
+  return __builtin_bit_cast(FwdParams, raw);
+}
+
+// `entry`: where p came from in a descriptor table, or null if it came with the launch.
+template <int DT, bool STORE_Y>
+__device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, table_words entry) {
+  typedef typename Frag<DT>::type frag_t;
+  // Fields that are rarely needed are read again where they are used (the laundered pointer keeps the loads there).
+  auto cold = [&]() -> FwdParams {
+    if (entry == nullptr) return p;
+    table_words e = entry;
+    asm volatile("" : "+s"(e));
+    return read_entry(e);
+  };
+  int bm, bn;
+  tile_of_logical(logical_block(bid, p.grid_m * p.grid_n), p.grid_m, p.grid_n, 8, bm, bn);
+
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = bm * OP_BM, n0 = bn * OP_BN, K = p.K;
+  const int ktiles = p.ktiles, nchunks = (K + OP_KC - 1) / OP_KC;
+  const int band = n0 / 64 + wave;
+  const int half = lane >> 5, l31 = lane & 31;
+
+  // Scalar base plus 32 bits per lane, both pinned where they are used: left alone the compiler precomputes 64-bit lane
+  // addresses for every load of the loop, which does not fit the register file.
+  auto lane_address = [](global_u8 base, uint32_t lane_bytes) -> global_u8 {
+    asm volatile("" : "+s"(base));
+    asm volatile("" : "+v"(lane_bytes));
+    return base + (size_t)lane_bytes;
+  };
+
+  // ---- codes and scales.  Lane (n, half) reads 16 bytes = 32 columns of row n (block j: row 32 j + n) of a 64-column
+  //      tile; word w of them is the operand of columns 32 half + 8 w .. of the tile.  Tiles past the end re-read the last
+  //      one and meet zeros in x; bands past N re-read the last band, their outputs are never used. ----
+  const size_t bsafe = (size_t)min(band, p.bands - 1);
+  const int gshift = p.group_shift;
+  const global_u8 q_base = p.qweight + bsafe * (size_t)ktiles * 2048;
+  const global_u8 s_base = (global_u8)(p.scales + bsafe * (size_t)(K >> gshift) * 64);
+  const uint32_t q_lane = (uint32_t)l31 * 32u + (uint32_t)half * 16u;
+  const uint32_t s_lane = (uint32_t)((l31 & 15) * 8 + (l31 >> 4) * 2);
+  u32x4 q[2][2];                                            // [tile of the chunk][block of 32 rows of W]
+  uint32_t sc[2][2];                                        // 32 bits each: packed in pairs, a load would be waited for where it is issued
+  auto load_q = [&](int c, int t, int j) {
+    const int k = min(2 * c + t, ktiles - 1);
+    q[t][j] = *reinterpret_cast<global_u32x4>(lane_address(q_base + (size_t)k * 2048 + 1024 * j, q_lane));
+    // group of columns 64 k + 32 half ..: with groups of 32 the two half waves read neighbouring groups
+    const uint32_t h_off = gshift == 5 ? (uint32_t)half * 128u : 0u;
+    sc[t][j] = *reinterpret_cast<global_u16>(lane_address(s_base + (size_t)((k * 64) >> gshift) * 128 + 4 * j, s_lane + h_off));
+  };
+
+  // ---- activations: thread tid stages 16 bytes of rows (tid / 16) + 16 i ----
+  const global_u8 x_base = (global_u8)(p.x + (size_t)m0 * K);
+  uint32_t x_lane[4];                                       // in bytes; 64 rows of K < 2^23 columns (checked on the host)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x_lane[i] = (uint32_t)min((tid >> 4) + 16 * i, p.M - 1 - m0) * (uint32_t)K * 2u;
+  u32x4 xr[4];
+  const int x_col = 8 * (tid & 15);
+  auto load_x = [&](int c, int i) {
+    const uint32_t col = (uint32_t)min(OP_KC * c + x_col, K - 8) * 2u;
+    xr[i] = *reinterpret_cast<global_u32x4>(lane_address(x_base, x_lane[i] + col));
+  };
+  u32x4 xo;
+  auto clip_x = [&](int c) {                                // K an odd multiple of 64: the last chunk's second half is zero
+    if (OP_KC * (c + 1) <= K) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (OP_KC * c + x_col >= K) xr[i] = u32x4{0u, 0u, 0u, 0u};
+  };
+  auto store_x_word = [&](int c, int i, int w) {            // word w of piece i; the fourth one writes the piece
+    xo[w] = stage_x_word<DT>(xr[i], w);
+    if (w == 3)
+      *reinterpret_cast<u32x4*>(smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + ((tid >> 4) + 16 * i) * OP_XROW + 16 * (tid & 15)) = xo;
+  };
+
+  float16_t acc[2][2], accz[2][2];                          // [block of 32 token rows][block of 32 rows of W]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.0f; accz[i][j][r] = 0.0f; }
+
+  // ---- sensitive entries ----
+  const bool band_ok = band < p.bands && p.nnz > 0;
+  u32x2* const ring = reinterpret_cast<u32x2*>(smem + OnePassLds::RING) + wave * OP_RING;    // v | z << 16 ; row << 8 | byte of the column
+  uint8_t* const hot = smem + OnePassLds::HOT + wave * 4096;                                  // [v, z][64 rows][16 slots]
+  uint32_t* const pos = reinterpret_cast<uint32_t*>(smem + OnePassLds::POS) + wave * 16;      // byte of the column of each slot
+  uint8_t* const sink = smem + OnePassLds::SINK + wave * 256 + 4 * lane;
+  auto tp_at = [&](int c) -> uint32_t {
+    return band_ok ? p.tile_ptr[(uint32_t)band * (uint32_t)ktiles + (uint32_t)min(2 * c, ktiles)] : 0u;
+  };
+  uint32_t tp0 = tp_at(0), tp1 = tp_at(1);
+  uint32_t w_hi = 0;                                        // entries below w_hi have been computed
+  auto refill = [&]() {                                     // only reached when an entry of the band is wanted: nnz > 0
+    const FwdParams pr = cold();
+    const uint32_t j = w_hi + 4u * lane, lastj = pr.nnz - 1u;
+    uint32_t idx[4];
+    float val[4], z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t je = min(j + e, lastj);                // clamped; entries past the end are never consumed
+      idx[e] = pr.sp_idx[je];
+      val[e] = pr.sp_val[je];
+    }
+    if (pr.signed_eps != 0.0f) zbar_quad((pr.nnz_base + j) >> 2, pr.seed, pr.step, z);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t n = fast_div(idx[e], pr.div_mul, pr.div_shift);
+      const uint32_t k = idx[e] - n * (uint32_t)pr.K, r = (n - (uint32_t)(band * 64)) & 63u;
+      const uint32_t kb = 2u * ((k & (uint32_t)(OP_KC - 8)) + (uint32_t)lds_pos<DT>(0, (int)(k & 7u)));
+      uint16_t vb, zb;
+      Frag<DT>::store(&vb, val[e]);
+      Frag<DT>::store(&zb, z[e]);
+      ring[(j + e) & (uint32_t)(OP_RING - 1)] = u32x2{(uint32_t)vb | ((uint32_t)zb << 16), (r << 8) | kb};
+    }
+    w_hi += OP_REFILL;
+  };
+  // Group of up to 16 entries from entry g0: slot `lane` of the one-hot operands.
+  u32x2 ent = {0u, 0u};
+  uint8_t* hot_at = sink;                                   // where this lane's last entry stands
+  auto group_read = [&](uint32_t g0) { ent = ring[(g0 + (uint32_t)(lane & 15)) & (uint32_t)(OP_RING - 1)]; };
+  auto group_put = [&](uint32_t g0, uint32_t g_end) {
+    const bool mine = lane < 16 && g0 + (uint32_t)lane < g_end;
+    *reinterpret_cast<uint16_t*>(hot_at) = 0;
+    *reinterpret_cast<uint16_t*>(hot_at + (hot_at == sink ? 0 : 2048)) = 0;
+    hot_at = mine ? hot + (ent[1] >> 8) * 32u + 2u * (uint32_t)lane : sink;
+    *reinterpret_cast<uint16_t*>(hot_at) = (uint16_t)(ent[0] & 0xFFFFu);
+    *reinterpret_cast<uint16_t*>(mine ? hot_at + 2048 : sink) = (uint16_t)(ent[0] >> 16);
+    // slots without an entry: a valid column, multiplied with zero
+    *reinterpret_cast<uint32_t*>(lane < 16 ? (uint8_t*)(pos + lane) : sink) = mine ? (ent[1] & 0xFFu) : 0u;
+  };
+  u32x4 gp[2], za[2], zb[2];
+  const uint32_t gather_base = (uint32_t)l31 * OP_XROW;
+  auto group_pos = [&]() {
+    gp[0] = *reinterpret_cast<const u32x4*>(pos + 8 * half);
+    gp[1] = *reinterpret_cast<const u32x4*>(pos + 8 * half + 4);
+  };
+  uint16_t graw[8];
+  auto group_gather = [&](int c, int i) {
+    const uint8_t* const x = smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + 32 * i * OP_XROW;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[e >> 2][e & 3] + gather_base));
+  };
+  auto group_pack = [&](int i) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) za[i][h] = (uint32_t)graw[2 * h] | ((uint32_t)graw[2 * h + 1] << 16);
+  };
+  auto group_hot = [&](int which) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) zb[j] = *reinterpret_cast<const u32x4*>(hot + which * 2048 + (32 * j + l31) * 32 + 16 * half);
+  };
+  auto group_multiply = [&](int which, int i, int j) {
+    float16_t& a = which ? accz[i][j] : acc[i][j];
+    a = Frag<DT>::mfma(__builtin_bit_cast(frag_t, za[i]), __builtin_bit_cast(frag_t, zb[j]), a);
+  };
+  auto group_all = [&](int c, uint32_t g0, uint32_t g_end) {
+    while (w_hi < min(g0 + 16u, g_end)) refill();
+    group_read(g0);
+    group_put(g0, g_end);
+    group_pos();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { group_gather(c, i); group_pack(i); }
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+      group_hot(which);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) group_multiply(which, i, j);
+    }
+  };
+
+  // ---- dense operands ----
+  DequantConsts dqk;
+  dqk.magic_lo = 0x64006400u; dqk.magic_hi = 0x54005400u;
+  asm volatile("" : "+v"(dqk.magic_lo), "+v"(dqk.magic_hi));
+  u32x4 b[2][2];                                            // [parity of the step][block]
+  auto dequant = [&](int step, int j, int part) {           // words 2 part, 2 part + 1 of the operand of step 0..7
+    const int t = (step >> 2) & 1, c = step & 3;
+    const _Float16 sh = __builtin_bit_cast(_Float16, (uint16_t)sc[t][j]);
+    if constexpr (DT == SZO_TILE_F16) {
+      // as dequant_out, in plain C: the two words go side by side through the three instructions, so that none waits
+      // for the one before it
+      const uint32_t src = part ? q[t][j][c] >> 8 : q[t][j][c];
+      half2_t lo = __builtin_bit_cast(half2_t, (src & 0x000F000Fu) | dqk.magic_lo);
+      half2_t hi = __builtin_bit_cast(half2_t, (src & 0x00F000F0u) | dqk.magic_hi);
+      lo = lo - half2_t{(_Float16)1032.0f, (_Float16)1032.0f};
+      hi = hi - half2_t{(_Float16)72.0f, (_Float16)72.0f};
+      lo = lo * half2_t{sh, sh};
+      hi = hi * half2_t{sh, sh};
+      b[step & 1][j][2 * part] = __builtin_bit_cast(uint32_t, lo);
+      b[step & 1][j][2 * part + 1] = __builtin_bit_cast(uint32_t, hi);
+    } else {
+#pragma unroll
+      for (int w = 2 * part; w < 2 * part + 2; ++w)
+        b[step & 1][j][w] = dequant_out<DT>(q[t][j][c], w, (float)sh, half2_t{sh, sh}, dqk);
+    }
+  };
+  frag_t a[2][2];
+  const uint32_t a_lane = (uint32_t)(OnePassLds::X + l31 * OP_XROW + 64 * half);
+  auto read_a = [&](int c, int step, int i) {
+    a[step & 1][i] = *reinterpret_cast<const frag_t*>(smem + a_lane + (c & 1) * OP_BM * OP_XROW + 32 * i * OP_XROW + 128 * ((step >> 2) & 1) + 16 * (step & 3));
+  };
+
+  // ---- prologue ----
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_x(0, i);
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) load_q(0, t, j);
+  *reinterpret_cast<u32x4*>(hot + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
+  *reinterpret_cast<u32x4*>(hot + 1024 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
+  *reinterpret_cast<u32x4*>(hot + 2048 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
+  *reinterpret_cast<u32x4*>(hot + 3072 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
+  w_hi = __builtin_amdgcn_readfirstlane(tp0) & ~3u;
+  clip_x(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) store_x_word(0, i, w);
+    load_x(min(1, nchunks - 1), i);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int part = 0; part < 2; ++part) dequant(0, j, part);
+  __syncthreads();
+
+  // ---- chunks of 128 columns: 8 steps of 16 columns x 4 matrix instructions.  Behind every instruction stands a share of
+  //      the work for later: the next step's operands, the next chunk's activations, the entries' operands ----
+  for (int c = 0; c < nchunks; ++c) {
+    const uint32_t tp2 = tp_at(c + 2);
+    const uint32_t j_lo = __builtin_amdgcn_readfirstlane(tp0), j_hi = __builtin_amdgcn_readfirstlane(tp1);
+    while (w_hi < min(j_lo + 16u, j_hi)) refill();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) read_a(c, 0, i);
+    group_read(j_lo);
+#pragma unroll
+    for (int step = 0; step < 8; ++step) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = u & 1, j = u >> 1, s = 4 * step + u;
+        acc[i][j] = Frag<DT>::mfma(a[step & 1][i], __builtin_bit_cast(frag_t, b[step & 1][j]), acc[i][j]);
+        if (step < 7 && u < 2) read_a(c, step + 1, u);
+        // next step's weights: block 0 behind the first two instructions, block 1 behind the others
+        dequant(step + 1, u >> 1, u & 1);
+        if ((step & 3) == 2 && (u & 1)) load_q(c + 1, step >> 2, u >> 1);        // the tile's last word has been taken
+        if (s == 4) group_put(j_lo, j_hi);
+        if (s == 8) group_pos();
+        if (s == 12) group_gather(c, 0);
+        if (s == 15) group_pack(0);
+        if (s == 16) group_gather(c, 1);
+        if (s == 17) group_hot(0);
+        if (s == 19) group_pack(1);
+        if (s >= 20 && s < 24) group_multiply(0, s & 1, (s >> 1) & 1);
+        if (s == 24) group_hot(1);
+        if (s >= 28) group_multiply(1, s & 1, (s >> 1) & 1);
+        if (s == 16) clip_x(c + 1);
+        if (s >= 16) {
+          store_x_word(c + 1, (s - 16) >> 2, s & 3);
+          if ((s & 3) == 3) load_x(min(c + 2, nchunks - 1), (s - 16) >> 2);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    for (uint32_t g0 = j_lo + 16u; g0 < j_hi; g0 += 16u) group_all(c, g0, j_hi);
+    tp0 = tp1; tp1 = tp2;
+    __syncthreads();                                        // next chunk's x complete, this one's no longer read
+  }
+
+  // ---- epilogue: register r of block (i, j) holds token row 32 i + 8 (r/4) + 4 (lane/32) + r%4, column 32 j + lane%32 of
+  //      the wave.  The bf16 target tile is copied to the place of x with coalesced loads first ----
+  const FwdParams pe = cold();
+  const bool staged = ((pe.N & 7) == 0) && ((reinterpret_cast<uintptr_t>(pe.target) & 15) == 0);
+  if (staged) {
+    constexpr int CPR = OP_BN / 8, ROWS_PER_PASS = 64 * OP_WAVES / CPR, PASSES = OP_BM / ROWS_PER_PASS, BATCH = 4;
+    static_assert(PASSES % BATCH == 0, "whole batches");
+    const int cc = tid % CPR, r0 = tid / CPR;
+    const int ncl = min(n0 + 8 * cc, pe.N - 8);
+#pragma unroll
+    for (int bt = 0; bt < PASSES; bt += BATCH) {
+      u32x4 t[BATCH];
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {
+        const int m = min(m0 + r0 + ROWS_PER_PASS * (bt + i), pe.M - 1);
+        t[i] = *reinterpret_cast<global_u32x4>(pe.target + (size_t)m * pe.N + ncl);
+      }
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i)
+        *reinterpret_cast<u32x4*>(smem + (r0 + ROWS_PER_PASS * (bt + i)) * OP_TROW + 16 * cc) = t[i];
+    }
+    __syncthreads();
+  }
+  const float eps = pe.signed_eps;
+  const int ml0 = 4 * half, nl0 = wave * 64 + l31;
+  const uint8_t* const trow = smem + ml0 * OP_TROW + nl0 * 2;
+  // Without y: with d = D - t the losses are sum d^2 +- 2 eps sum d Z + eps^2 sum Z^2, and their difference, which g
+  // is made of, is summed as such instead of being left over from two nearly equal sums.
+  double loss_plus = 0.0, loss_minus = 0.0, sum_dd = 0.0, sum_dz = 0.0, sum_zz = 0.0;
+  auto finish = [&](auto full_tag, auto staged_tag) {
+    constexpr bool FULL = decltype(full_tag)::value, STAGED = decltype(staged_tag)::value;
+    const uint32_t base = (uint32_t)(m0 + ml0) * (uint32_t)pe.N + (uint32_t)(n0 + nl0);   // M * N < 2^32 checked on the host
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        float dd = 0.0f, dz = 0.0f, zz = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int dm = 32 * i + 8 * (r >> 2) + (r & 3), dn = 32 * j;
+          if (FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) {
+            const uint32_t off = base + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn;
+            uint32_t tb;
+            if (STAGED) tb = *reinterpret_cast<const uint16_t*>(trow + dm * OP_TROW + dn * 2);
+            else tb = pe.target[off];
+            const float t = __uint_as_float(tb << 16);
+            if (STORE_Y) {                                  // as mse_kernel: differences and squares in fp64
+              const float ez = eps * accz[i][j][r], yp = acc[i][j][r] + ez, ym = acc[i][j][r] - ez;
+              pe.y[off] = ym;
+              const double dp = (double)yp - (double)t, dmn = (double)ym - (double)t;
+              loss_plus = fma(dp, dp, loss_plus);
+              loss_minus = fma(dmn, dmn, loss_minus);
+            } else {
+              const float d = acc[i][j][r] - t, z = accz[i][j][r];
+              dd = fmaf(d, d, dd);
+              dz = fmaf(d, z, dz);
+              zz = fmaf(z, z, zz);
+            }
+          }
+        }
+        if (!STORE_Y) { sum_dd += (double)dd; sum_dz += (double)dz; sum_zz += (double)zz; }
+      }
+  };
+  {
+    using T = std::true_type;
+    using F = std::false_type;
+    const bool full = m0 + OP_BM <= pe.M && n0 + OP_BN <= pe.N;
+    if (full && staged) finish(T{}, T{});
+    else if (staged) finish(F{}, T{});
+    else finish(F{}, F{});
+  }
+  if (!STORE_Y) {
+    const double even = fma((double)eps * (double)eps, sum_zz, sum_dd), odd = 2.0 * (double)eps * sum_dz;
+    loss_plus = even + odd;
+    loss_minus = even - odd;
+  }
+  __shared__ double wave_part[2][OP_WAVES];
+  loss_plus = wave_sum(loss_plus);
+  loss_minus = wave_sum(loss_minus);
+  if (lane == 0) { wave_part[0][wave] = loss_plus; wave_part[1][wave] = loss_minus; }
+  __syncthreads();
+  if (tid < 2) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < OP_WAVES; ++i) t += wave_part[tid][i];
+    (tid == 0 ? pe.partials : pe.partials_minus)[bm * pe.grid_n + bn] = t * pe.loss_scale;
+  }
+}
+
+// Every layer of a step in one grid: `table` holds one entry per layer, ordered by first_block (a multiple of 8).
+template <int DT, bool STORE_Y>
+__global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const FwdParams* table, int n_entries) {
+  constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
+  const table_words tab = (table_words)table;
+  int first = 0, last = n_entries - 1;                      // last entry whose first_block <= blockIdx.x
+  while (first < last) {
+    const int mid = (first + last + 1) >> 1;
+    if ((int)tab[mid * W + FB] <= (int)blockIdx.x) first = mid; else last = mid - 1;
+  }
+  const FwdParams p = read_entry(tab + first * W);
+  const int bid = (int)blockIdx.x - p.first_block;
+  if (bid >= p.grid_m * p.grid_n) return;
+  onepass_body<DT, STORE_Y>(p, bid, tab + first * W);
+}
+
+// One layer, its descriptor in the kernel arguments.
+template <int DT>
+__global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_kernel(FwdParams p) {
+  onepass_body<DT, false>(p, (int)blockIdx.x, nullptr);
+}
+
+// ---- host side -----------------------------------------------------------------------------
+
+template <typename Kernel, typename... Args>
+static int launch(Kernel kern, std::atomic<uint64_t>& lds_limit_set, int64_t blocks, hipStream_t stream, Args... args) {
+  int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, OnePassLds::BYTES);
+  if (rc != SZO_OK) return rc;
+  rc = timing_begin(stream);
+  if (rc != SZO_OK) return rc;
+  kern<<<(unsigned)blocks, 64 * OP_WAVES, OnePassLds::BYTES, stream>>>(args...);
+  SZO_LAUNCH_CHECK();
+  return timing_end(stream);
+}
+template <int DT, bool STORE_Y>
+static int launch_table(const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
+  static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
+  return launch(onepass_table_kernel<DT, STORE_Y>, lds_limit_set, blocks, stream, table_dev, entries);
+}
+template <int DT>
+static int launch_one(const FwdParams& p, hipStream_t stream) {
+  static std::atomic<uint64_t> lds_limit_set{0};
+  return launch(onepass_kernel<DT>, lds_limit_set, (int64_t)p.grid_m * p.grid_n, stream, p);
+}
+
+static int g_force_onepass = 0;                             // testing hook: 1 = wherever the kernel can, -1 = never
+void onepass_force(int how) { g_force_onepass = how; }
+
+// Whether a step takes this kernel.  `few`: the few-token path would take the step otherwise; `asked_for`: the caller
+// wants one dense pass (SZO_STEP_ONE_DENSE_PASS).  Measured at a density of 0.1 % unless said otherwise, us per step,
+// other path -> this one:
+//  * against the few-token path: more than 32 tokens and 512 workgroups, two per CU.  Four Llama blocks at 32 / 48 / 64 /
+//    128 tokens (700 .. 1400 workgroups) 159 / 232 / 241 / 517 -> 189 / 192 / 193 / 346; one Mistral block at 128 / 192
+//    tokens (416 / 624) 153 / 256 -> 204 / 214; 32 OPT blocks at 64 / 224 tokens 1531 / 5697 -> 1241 / 4334.  Where the
+//    few-token path has only its split kernel (bf16 tile, K an odd multiple of 64): four Llama blocks with the bf16 tile
+//    at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393.
+//  * against the tiled kernel, up to kOnePassTokens tokens unless the caller asks for it: beyond that a step is two full
+//    forwards per layer by default, the products of the single-layer calls.  The two differ by what a row of tiles
+//    costs: a unit of 64 token rows here takes 1 + 108 rho
+//    (rho = share of sensitive weights; one Llama block at 2048 tokens, rho = 0.0001 / 0.001 / 0.002 / 0.004 / 0.006:
+//    1459 / 1450 / 1448 / 1464 / 1479 -> 1070 / 1079 / 1216 / 1419 / 1662), one of a 256-row tile 1.42 / 4, padding
+//    included.  Single layers: 4096 x 4096 at 256 / 1024 / 4096 tokens 128 / 135 / 249 -> 71 / 76 / 196, 1024 x 1024
+//    50 / 50 / 53 -> 36 / 37 / 39.  Steps of a handful of workgroups gain nothing: they keep the tiled kernel.
+//  * with the outputs written (flags = 0) the other path is two tiled launches and two passes over y per layer: one Llama
+//    block at 1 / 256 / 1024 tokens 1044 / 1063 / 1508 -> 150 / 189 / 621; rho = 0.01, 1024 tokens: 1836 -> 1128.
+constexpr int64_t kOnePassTokens = 512;
+static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y) {
+  int64_t wgs = 0, most_tokens = 0;
+  double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0;
+  bool stream = true;
+  for (int i = 0; i < n; ++i) {
+    const szo_linear_desc* d = &descs[i];
+    if (d->M == 0 || d->N == 0) continue;
+    const double size = (double)d->N * (double)d->K;
+    wgs += ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
+    most_tokens = std::max<int64_t>(most_tokens, d->M);
+    weights += size;
+    entries += (double)d->nnz;
+    here += size * (double)((d->M + 63) / 64);
+    tiled += size * (double)((d->M + 255) / 256) * 4.0;
+    stream = stream && d->K % 128 == 0 && d->tile_dtype == SZO_TILE_F16;
+  }
+  const double rho = entries / weights;
+  if (store_y) return wgs >= 4 && rho <= 0.015;
+  if (few) return wgs >= 512 ? most_tokens > (stream ? 32 : 16) : !stream && most_tokens > 64 && wgs >= 256;
+  if (wgs < (most_tokens <= 128 ? 256 : 32)) return false;
+  return asked_for || (most_tokens <= kOnePassTokens && (1.0 + 108.0 * rho) * here < 1.42 * tiled);
+}
+
+// The outputs are written by concurrent workgroups: layers must not share them (a caller that only wants the losses may
+// hand out one buffer for the whole stack).
+static bool outputs_overlap(const szo_linear_desc* descs, int n) {
+  static thread_local std::vector<std::pair<uintptr_t, uintptr_t>> spans;
+  spans.clear();
+  for (int i = 0; i < n; ++i) {
+    const szo_linear_desc* d = &descs[i];
+    if (d->M == 0 || d->N == 0) continue;
+    spans.push_back({(uintptr_t)d->y, (uintptr_t)d->y + sizeof(float) * (size_t)d->M * (size_t)d->N});
+  }
+  std::sort(spans.begin(), spans.end());
+  for (size_t i = 1; i < spans.size(); ++i)
+    if (spans[i].first < spans[i - 1].second) return true;
+  return false;
+}
+
+int64_t onepass_tiles(const szo_linear_desc* d) {
+  return ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
+}
+
+// Loss partials per sign of the step if it takes this kernel, 0 if not.
+int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y) {
+  if (g_force_onepass < 0) return 0;
+  int64_t T = 0;
+  const szo_linear_desc* any = nullptr;
+  for (int i = 0; i < n; ++i) {
+    const szo_linear_desc* d = &descs[i];
+    if (d->M == 0 || d->N == 0) continue;
+    if (d->format != SZO_FORMAT_UNIFORM || d->x_minus || d->K >= (1 << 23)) return 0;
+    if (any && d->tile_dtype != any->tile_dtype) return 0;
+    any = d;
+    T += onepass_tiles(d);
+  }
+  if (T == 0 || (g_force_onepass == 0 && !worth_it(descs, n, few, asked_for, store_y))) return 0;
+  return store_y && outputs_overlap(descs, n) ? 0 : T;
+}
+
+static int fill_tiled(FwdParams& p, const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, double* plus, double* minus) {
+  const int rc = fill_params(p, d, seed, step, +1, eps, plus, 1.0 / ((double)d->M * (double)d->N));
+  p.partials_minus = (global_f64_out)minus;
+  p.grid_m = (int)((d->M + OP_BM - 1) / OP_BM);
+  p.grid_n = (int)((d->N + OP_BN - 1) / OP_BN);
+  return rc;
+}
+
+int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, double* plus, double* minus, hipStream_t stream) {
+  FwdParams p;
+  const int rc = fill_tiled(p, d, seed, step, eps, plus, minus);
+  if (rc != SZO_OK) return rc;
+  if (onepass_tiles(d) > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+  return d->tile_dtype == SZO_TILE_F16 ? launch_one<SZO_TILE_F16>(p, stream) : launch_one<SZO_TILE_BF16>(p, stream);
+}
+
+int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
+                     bool store_y, void* table_dev, double* partials, int64_t* partials_per_sign, hipStream_t stream) {
+  const int64_t T = onepass_partials(descs, n, few, asked_for, store_y);
+  if (T == 0 || 2 * T > kMaxLossPartials) return SZO_EUNSUPPORTED;
+  static thread_local std::vector<int> order;
+  order.clear();
+  for (int i = 0; i < n; ++i)
+    if (descs[i].M > 0 && descs[i].N > 0) order.push_back(i);
+  if (sizeof(FwdParams) * order.size() > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;
+  // longest K first: the last workgroups to start are the shortest
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return descs[a].K > descs[b].K; });
+  static thread_local std::vector<FwdParams> table;
+  table.clear();
+  int64_t first_block = 0, offset = 0;
+  for (int i : order) {
+    const szo_linear_desc* d = &descs[i];
+    FwdParams p;
+    const int rc = fill_tiled(p, d, seed, step, eps, partials + offset, partials + T + offset);
+    if (rc != SZO_OK) return rc;
+    p.first_block = (int)first_block;
+    table.push_back(p);
+    first_block += (onepass_tiles(d) + 7) & ~(int64_t)7;
+    if (first_block > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+    offset += onepass_tiles(d);
+  }
+  const int rc = stage_table(table.data(), sizeof(FwdParams) * table.size(), table_dev, stream);
+  if (rc != SZO_OK) return rc;
+  *partials_per_sign = T;
+  const FwdParams* t = (const FwdParams*)table_dev;
+  const int e = (int)table.size();
+  if (descs[order[0]].tile_dtype == SZO_TILE_F16)
+    return store_y ? launch_table<SZO_TILE_F16, true>(t, e, first_block, stream) : launch_table<SZO_TILE_F16, false>(t, e, first_block, stream);
+  return store_y ? launch_table<SZO_TILE_BF16, true>(t, e, first_block, stream) : launch_table<SZO_TILE_BF16, false>(t, e, first_block, stream);
+}
+
+}  // namespace szo

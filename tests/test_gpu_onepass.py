@@ -1,0 +1,122 @@
+"""GPU parity of the step with one dense product per layer (forced by tile configuration 11, or chosen), at the edges of
+its tiles: ragged token rows, bands and columns, K with half a chunk at the end, more sensitive entries per chunk than one
+group of sixteen and per ring than one refill, no entries, every group size, both tile types, and the outputs."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import layer as olayer, zo as ozo
+from paper_2406_02913_amd import szo
+from helpers import UpdateBound, clone, make_pair, rel_fro, sigma_g
+
+pytestmark = pytest.mark.gpu
+
+LAYERS = {            # (seed, M, N, K, group, density, mask)
+    "one_token_one_row": [(401, 1, 1, 64, 32, 5e-2, "uniform")],
+    "half_chunk": [(402, 63, 65, 192, 64, 2e-2, "uniform")],
+    "tile_exactly": [(403, 64, 256, 128, 128, 1e-2, "uniform")],
+    "one_more_each": [(404, 65, 257, 1088, 32, 1e-3, "uniform")],
+    "dense_mask": [(405, 70, 100, 2048, 128, 0.3, "uniform")],        # 2400 entries per chunk: ring and refills
+    "hot_rows": [(406, 129, 300, 1024, 128, 1e-2, "heavy_tail")],
+    "several": [(407, 200, 320, 512, 128, 2e-3, "uniform"), (408, 5, 64, 320, 64, 0.0, "uniform"),
+                (409, 130, 513, 384, 128, 2e-2, "uniform")],
+}
+
+
+@pytest.fixture(autouse=True)
+def _auto_tile_config():
+    yield
+    szo.szo_set_tile_config(0)
+
+
+def _pairs(name):
+    os_, ds_, base = [], [], 0
+    for sd, M, N, K, G, dens, kind in LAYERS[name]:
+        o, d = make_pair(sd, M, N, K, G, dens, kind=kind, nnz_base=base)
+        base += (o.sp_idx.size + 3) // 4 * 4
+        os_.append(o)
+        ds_.append(d)
+    return os_, ds_
+
+
+@pytest.mark.parametrize("tile", ["f16", "bf16"])
+@pytest.mark.parametrize("with_y", [False, True])
+@pytest.mark.parametrize("name", sorted(LAYERS))
+def test_step_matches_oracle(name, with_y, tile):
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    os_, ds_ = _pairs(name)
+    ref = [clone(o) for o in os_]
+    sg, seed, eps, lr = sigma_g(os_), 19, 1e-3, 1e-3
+    ws = szo.new_workspace()
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    for d in ds_:
+        d.y.fill_(float("nan"))
+    szo.szo_set_tile_config(11)
+    szo.szo_kernel_timing(True)
+    bound = UpdateBound(sg, lr)
+    for step in range(2):
+        z = []
+        before = [clone(o) for o in ref]
+        szo.szo_zo_step([d.desc(dt, with_y=with_y) for d in ds_], seed, step, eps, lr, scal, ws,
+                        0 if with_y else szo.STEP_FUSED_LOSS)
+        r = ozo.zo_step(ref, seed, step, eps, lr)
+        z = r["z"]
+        lp, lm, g = scal.cpu().numpy()
+        cells = sum(o.x_bits.shape[0] * o.codes.shape[0] for o in os_)
+        # as for the dual-sign tiles: an independent rounding error of ~1e-4 per output, averaged over the outputs
+        ltol, gtol = (max(1e-5, 2e-3 / np.sqrt(cells)), 1e-2) if tile == "f16" else (5e-3, 1e-1)
+        size = max(r["loss_plus"], 1.0)
+        assert abs(lp - r["loss_plus"]) <= ltol * size and abs(lm - r["loss_minus"]) <= ltol * size, (lp, lm, r)
+        assert abs(g - r["g"]) <= gtol * max(abs(r["g"]), sg), (g, r["g"], sg)
+        bound.add(r, extra_dg=(gtol - 1e-2) * max(abs(r["g"]), sg))
+        if with_y and step == 0:        # the outputs are those of the -eps forward; 16-bit operands: 2^-11 / 2^-8 relative
+            for o, d, zi in zip(before, ds_, z):
+                want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, o.group, o.sp_idx, o.sp_val, zi, -1, eps, "E")
+                got = d.y.cpu().numpy()
+                assert np.isfinite(got).all() and rel_fro(got, want) <= (5e-4 if tile == "f16" else 4e-3)
+    _, launches = szo.szo_kernel_timing_read()
+    szo.szo_kernel_timing(False)
+    assert launches == 2                                     # one launch per step for all layers and both signs
+    for i, (o, d, om) in enumerate(zip(os_, ds_, ref)):
+        if o.sp_idx.size:
+            bound.check(i, d.sp_val.cpu().numpy(), om.sp_val, o.sp_val)
+
+
+def test_layers_that_share_their_output_buffer_run_one_after_the_other():
+    """One buffer for the outputs of a stack holds the last layer's afterwards: concurrent workgroups would mix them."""
+    (oa, ob), (da, db) = [list(t) for t in zip(*[make_pair(411 + i, 300, 320, 256, 128, 5e-3, nnz_base=8192 * i) for i in range(2)])]
+    results = []
+    for shared in (False, True):
+        ws = szo.new_workspace()
+        scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+        descs = [da.desc(), db.desc()]
+        if shared:
+            descs[0].y = descs[1].y
+        szo.szo_zo_step(descs, 3, 0, 1e-3, 0.0, scal, ws, 0)
+        results.append((scal.cpu().numpy().copy(), db.y.cpu().numpy().copy()))
+    (s0, y0), (s1, y1) = results
+    sg = sigma_g([oa, ob])
+    assert abs(s0[0] - s1[0]) <= 1e-5 * s0[0] and abs(s0[2] - s1[2]) <= 1e-2 * max(abs(s0[2]), sg)
+    assert rel_fro(y1, y0) <= 5e-4
+
+
+def test_chosen_for_a_step_of_some_hundred_tokens_and_bit_reproducible():
+    """... and the entry point without a workspace takes the same kernel: only the grouping of the partials differs."""
+    outs = []
+    for _ in range(2):
+        o, d = make_pair(421, 500, 2048, 512, 128, 1e-3)
+        ws = szo.new_workspace()
+        scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+        szo.szo_kernel_timing(True)
+        szo.szo_zo_step([d.desc(with_y=False)], 9, 0, 1e-3, 1e-3, scal, ws, szo.STEP_FUSED_LOSS)
+        _, launches = szo.szo_kernel_timing_read()
+        szo.szo_kernel_timing(False)
+        assert launches == 1
+        outs.append((scal.cpu().numpy().copy(), d.sp_val.cpu().numpy().copy()))
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+    r = ozo.zo_step([clone(o)], 9, 0, 1e-3, 1e-3)
+    lp, lm, g = outs[0][0]
+    assert abs(lp - r["loss_plus"]) <= 1e-5 * r["loss_plus"] and abs(g - r["g"]) <= 1e-2 * max(abs(r["g"]), sigma_g([o]))
+    o, d = make_pair(421, 500, 2048, 512, 128, 1e-3)
+    szo.szo_zo_step_noalloc([d.desc(with_y=False)], 9, 0, 1e-3, 1e-3, scal)
+    assert np.allclose(scal.cpu().numpy()[:2], outs[0][0][:2], rtol=1e-12, atol=0.0)
