@@ -46,9 +46,13 @@ struct SmallMat {
 
 static_assert(sizeof(SmallMat) <= kTableBytesPerMatrix, "table entries must fit the workspace's table area");
 
+// Launches over a handful of matrices carry their table in the kernel arguments (read by scalar loads like the rest of
+// them) instead of staging it in device memory: one launch and one event record less per step.
+static_assert(kInlineMats * sizeof(SmallMat) <= 2048, "kernel arguments are limited to 4 KB");
+
 struct SmallArgs {
-  const SmallMat* table;    // device table of n_mats matrices, or null: use `one`
-  SmallMat one;
+  const SmallMat* table;    // device table of n_mats matrices, or null: they are in `inl`
+  SmallMat inl[kInlineMats];
   int n_mats;
   int slices;               // slices of token rows per strip in this launch (the longest matrix's count)
   int stream_once;          // host's choice: load the codes as a non-temporal stream (see small_m_kernel, ONCE)
@@ -139,27 +143,30 @@ __device__ __forceinline__ int xcd_unit(int bid, int grid) {
   return bid;
 }
 
+// The table of a kernel whose first argument is an Args with the members `table` and `inl`.
+template <typename Args>
+__device__ __forceinline__ const uint32_t __attribute__((address_space(4)))* mat_table(const Args& a) {
+  typedef const uint32_t __attribute__((address_space(4)))* words;
+  return a.table ? (words)a.table : (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Args, inl) / 4;
+}
+
 // Table entry of workgroup `unit`: the last matrix whose first_block <= unit.  Read through the constant address
 // space (scalar loads: the table is written before the launch and never during it), so that its fields live in
 // scalar registers like the kernel arguments do; read through a generic pointer they would occupy ~30 vector
 // registers.
 __device__ __forceinline__ SmallMat find_matrix(const SmallArgs& a, int unit) {
-  SmallMat mt = a.one;
-  if (a.table) {
-    constexpr int W = (int)(sizeof(SmallMat) / 4), FB = (int)(offsetof(SmallMat, first_block) / 4);
-    static_assert(sizeof(SmallMat) % 4 == 0 && offsetof(SmallMat, first_block) % 4 == 0, "table entry is read as words");
-    const auto* tab = (const uint32_t __attribute__((address_space(4)))*)a.table;
-    int lo = 0, hi = a.n_mats - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if ((int)tab[mid * W + FB] <= unit) lo = mid; else hi = mid - 1;
-    }
-    struct Words { uint32_t w[W]; } raw;
-#pragma unroll
-    for (int i = 0; i < W; ++i) raw.w[i] = tab[lo * W + i];
-    mt = __builtin_bit_cast(SmallMat, raw);
+  constexpr int W = (int)(sizeof(SmallMat) / 4), FB = (int)(offsetof(SmallMat, first_block) / 4);
+  static_assert(sizeof(SmallMat) % 4 == 0 && offsetof(SmallMat, first_block) % 4 == 0, "table entry is read as words");
+  const auto* tab = mat_table(a);
+  int lo = 0, hi = a.n_mats - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if ((int)tab[mid * W + FB] <= unit) lo = mid; else hi = mid - 1;
   }
-  return mt;
+  struct Words { uint32_t w[W]; } raw;
+#pragma unroll
+  for (int i = 0; i < W; ++i) raw.w[i] = tab[lo * W + i];
+  return __builtin_bit_cast(SmallMat, raw);
 }
 
 // The tables of one row, 16 fp16 entries at p, as the four byte planes that sm_lut_word() reads.

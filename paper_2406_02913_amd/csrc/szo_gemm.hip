@@ -875,11 +875,15 @@ static int run_forward(const szo_linear_desc* d, uint64_t seed, uint64_t step, i
 }
 
 // The sparse update of a step: one grouped launch for the whole stack (per-matrix launches when the table does not fit).
-static int update_all(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float lr, double* scalars,
-                      void* workspace, hipStream_t s) {
-  if (n <= kMaxStepMatrices && small_m_table_bytes(n) <= kTableBytesPerMatrix * (size_t)kMaxStepMatrices)
-    return small_m_step(descs, n, seed, step, 0.0f, lr, (char*)workspace + kWorkspaceTableOffset, nullptr, scalars,
-                        false, true, s);
+// With partials_per_sign > 0 g is formed from that many loss partials first; otherwise scalars[2] holds it.
+static int update_all(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr, double* scalars,
+                      double* partials, int64_t partials_per_sign, void* table_dev, hipStream_t s) {
+  if (n <= (table_dev ? kMaxStepMatrices : kInlineMats) && small_m_table_bytes(n) <= kTableBytesPerMatrix * (size_t)kMaxStepMatrices)
+    return small_m_step(descs, n, seed, step, eps, lr, table_dev, partials, partials_per_sign, scalars, false, s);
+  if (partials_per_sign > 0) {
+    const int rc = reduce_step(partials, (int)partials_per_sign, eps, scalars, s);
+    if (rc != SZO_OK) return rc;
+  }
   for (int i = 0; i < n; ++i) {
     const int rc = szo_sparse_update(descs[i].sp_val, descs[i].sp_idx, descs[i].nnz, descs[i].nnz_base, seed, step,
                                      scalars + 2, lr, s);
@@ -1063,14 +1067,11 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
     }
     if (rc != SZO_OK) return rc;
   }
-  rc = reduce_step(part, (int)T, eps, scalars, s);
-  if (rc != SZO_OK) return rc;
-  for (int i = 0; i < n; ++i) {
-    rc = szo_sparse_update(descs[i].sp_val, descs[i].sp_idx, descs[i].nnz, descs[i].nnz_base, seed, step,
-                           scalars + 2, lr, s);
+  if (T == 0) {                     // no layer with tokens: zero losses, g = 0
+    rc = reduce_step(part, 0, eps, scalars, s);
     if (rc != SZO_OK) return rc;
   }
-  return SZO_OK;
+  return update_all(descs, n, seed, step, eps, lr, scalars, part, T, nullptr, s);
 }
 
 int szo_set_tile_config(int config) {
@@ -1137,6 +1138,7 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
     total += blocks;
   }
   int rc;
+  void* const table_dev = (char*)workspace + kWorkspaceTableOffset;
   // Few-token stacks: one pass over the weights serves both forwards of the step.
   // SZO_STEP_ONE_DENSE_PASS: the caller asks for that path at any token count.
   const bool few = fuse && few_token_enabled() && n <= kMaxStepMatrices &&
@@ -1147,58 +1149,50 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
     rc = onepass_forwards(descs, n, seed, step, eps, few && small_m_eligible(descs, n, false, false),
                           (flags & SZO_STEP_ONE_DENSE_PASS) != 0, !fuse, (char*)workspace + kWorkspaceTableOffset,
                           partial_area(workspace), &T, s);
-    if (rc == SZO_OK) rc = reduce_step(partial_area(workspace), (int)T, eps, scalars, s);
-    if (rc == SZO_OK) return update_all(descs, n, seed, step, lr, scalars, workspace, s);
+    if (rc == SZO_OK) return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
     if (rc != SZO_EUNSUPPORTED) return rc;      // otherwise nothing was enqueued
   }
   if (few) {
-    rc = small_m_step(descs, n, seed, step, eps, lr, (char*)workspace + kWorkspaceTableOffset,
-                      partial_area(workspace), scalars, true, true, s);
+    rc = small_m_step(descs, n, seed, step, eps, lr, table_dev, partial_area(workspace), 0, scalars, true, s);
     if (rc != SZO_EUNSUPPORTED) return rc;      // too many slices for the table: nothing was enqueued, take the tiled path
   }
-  bool grouped = false;
   if (fuse) {
     int64_t T = 0;
     rc = grouped_forwards(descs, n, seed, step, eps, (char*)workspace + kWorkspaceTableOffset, partial_area(workspace),
                           &T, s);
-    if (rc == SZO_OK) {
-      grouped = true;
-      rc = reduce_step(partial_area(workspace), (int)T, eps, scalars, s);
-      if (rc != SZO_OK) return rc;
-    } else if (rc != SZO_EUNSUPPORTED) {
-      return rc;
-    }
+    if (rc == SZO_OK)
+      return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
+    if (rc != SZO_EUNSUPPORTED) return rc;
   }
-  if (!grouped) {
-    if (fuse && 2 * total > kMaxLossPartials) return SZO_EUNSUPPORTED;
-    if (!fuse) {
-      rc = zero_words(scalars, 6, s);
-      if (rc != SZO_OK) return rc;
-    }
-    for (int pass = 0; pass < 2; ++pass) {
-      const int sign = pass == 0 ? +1 : -1;
-      double* part = partial_area(workspace) + (size_t)pass * (size_t)total;
-      for (int i = 0; i < n; ++i) {
-        const szo_linear_desc* d = &descs[i];
-        if (d->M == 0 || d->N == 0) continue;
-        const double scale = 1.0 / ((double)d->M * (double)d->N);
-        if (fuse) {
-          int blocks;
-          plan_tiles((int)d->M, (int)d->N, d->format, &blocks);
-          rc = run_forward(d, seed, step, sign, eps, part, scale, s, pass == 1);
-          part += blocks;
-        } else {
-          rc = run_forward(d, seed, step, sign, eps, nullptr, 0.0, s, pass == 1);
-          if (rc == SZO_OK) rc = szo_mse_loss(d->y, d->target, d->M * d->N, scale, scalars + pass, workspace, s);
-        }
-        if (rc != SZO_OK) return rc;
-      }
-    }
-    rc = fuse ? reduce_step(partial_area(workspace), (int)total, eps, scalars, s)
-              : szo_spsa_g(scalars, scalars + 1, eps, scalars + 2, s);
+  if (fuse && 2 * total > kMaxLossPartials) return SZO_EUNSUPPORTED;
+  if (!fuse) {
+    rc = zero_words(scalars, 6, s);
     if (rc != SZO_OK) return rc;
   }
-  return update_all(descs, n, seed, step, lr, scalars, workspace, s);
+  for (int pass = 0; pass < 2; ++pass) {
+    const int sign = pass == 0 ? +1 : -1;
+    double* part = partial_area(workspace) + (size_t)pass * (size_t)total;
+    for (int i = 0; i < n; ++i) {
+      const szo_linear_desc* d = &descs[i];
+      if (d->M == 0 || d->N == 0) continue;
+      const double scale = 1.0 / ((double)d->M * (double)d->N);
+      if (fuse) {
+        int blocks;
+        plan_tiles((int)d->M, (int)d->N, d->format, &blocks);
+        rc = run_forward(d, seed, step, sign, eps, part, scale, s, pass == 1);
+        part += blocks;
+      } else {
+        rc = run_forward(d, seed, step, sign, eps, nullptr, 0.0, s, pass == 1);
+        if (rc == SZO_OK) rc = szo_mse_loss(d->y, d->target, d->M * d->N, scale, scalars + pass, workspace, s);
+      }
+      if (rc != SZO_OK) return rc;
+    }
+  }
+  if (!fuse || total == 0) {        // no layer with tokens: zero losses, g = 0
+    rc = fuse ? reduce_step(partial_area(workspace), 0, eps, scalars, s) : szo_spsa_g(scalars, scalars + 1, eps, scalars + 2, s);
+    if (rc != SZO_OK) return rc;
+  }
+  return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), fuse ? total : 0, table_dev, s);
 }
 
 }  // extern "C"

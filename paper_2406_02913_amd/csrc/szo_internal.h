@@ -58,8 +58,9 @@ size_t small_m_table_bytes(int n);
 int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int sign, bool loss_mode,
                        double* partial_plus, double* partial_minus, bool compact, hipStream_t stream);
 int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,
-                 void* table_dev, double* partial_plus, double* scalars, bool do_forward, bool do_update,
+                 void* table_dev, double* partial_plus, int64_t partials_per_sign, double* scalars, bool do_forward,
                  hipStream_t stream);
+constexpr int kInlineMats = 8;                              // matrices whose table travels in the kernel arguments
 
 // Many tokens, one dense product per layer (szo_onepass.hip): both forwards of every layer as one launch, the loss fused
 // and, with store_y, the -eps outputs written.  SZO_EUNSUPPORTED, with nothing enqueued, when the stack does not qualify.

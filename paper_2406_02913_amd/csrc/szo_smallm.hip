@@ -449,16 +449,56 @@ __global__ void __launch_bounds__(256, R == 1 ? (MODE == SM_LUT ? 3 : SM_MIN_BLO
 // a binary search on scalar loads (through the constant address space) and keeps the entry's fields in
 // scalar registers.  (Searching per lane with vector loads made every wave wait for eight dependent
 // memory round trips before it could touch its entries; the launch then took 27 us for 52 MB.)
-__global__ void __launch_bounds__(256) sparse_update_table_kernel(const SmallMat* __restrict__ table, int n_mats,
-                                                                  int64_t total_quads, uint64_t seed, uint64_t step,
-                                                                  const double* __restrict__ g, float lr) {
+struct UpdateArgs {
+  const SmallMat* table;    // as in SmallArgs
+  SmallMat inl[kInlineMats];
+  int n_mats;
+  int partials_per_sign;    // > 0: the losses are still partials, and this launch forms g from them
+  const double* partials;   // "+" partials, then "-" partials
+  double* scalars;          // (L+, L-, g): written if partials_per_sign > 0, else g is read
+  int64_t total_quads;
+  uint64_t seed, step;
+  float lr, eps;
+};
+
+// What reduce_step_kernel adds up, in its order: 256 threads stand for its 1024.
+__device__ __forceinline__ double block_sum_as_1024(const double* __restrict__ v, int count, double (&scratch)[16]) {
+  for (int k = 0; k < 4; ++k) {
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    int i = 256 * k + (int)threadIdx.x;
+    for (; i + 3 * 1024 < count; i += 4 * 1024) { a0 += v[i]; a1 += v[i + 1024]; a2 += v[i + 2 * 1024]; a3 += v[i + 3 * 1024]; }
+    for (; i < count; i += 1024) a0 += v[i];
+    const double a = wave_sum((a0 + a1) + (a2 + a3));
+    if ((threadIdx.x & 63) == 0) scratch[4 * k + (threadIdx.x >> 6)] = a;
+  }
+  __syncthreads();
+  double t = 0.0;
+  for (int i = 0; i < 16; ++i) t += scratch[i];
+  __syncthreads();
+  return t;
+}
+
+// With few partials every workgroup adds them up by itself (same order, same g everywhere) instead of waiting for a
+// launch that does: a step over one 256 x 256 layer at 64 tokens has 16 of them per sign.
+__global__ void __launch_bounds__(256) sparse_update_table_kernel(UpdateArgs a) {
   constexpr int W = (int)(sizeof(SmallMat) / 4), FQ = (int)(offsetof(SmallMat, first_quad) / 4);
   static_assert(offsetof(SmallMat, first_quad) % 8 == 0, "first_quad is read as two words");
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int64_t tw = (int64_t)blockIdx.x * 256 + 64 * wave;           // the wave's first thread
-  if (tw >= total_quads) return;
-  const auto* tab = (const uint32_t __attribute__((address_space(4)))*)table;
-  int lo = 0, hi = n_mats - 1;                                        // last matrix whose first_quad <= tw
+  double g;
+  if (a.partials_per_sign > 0) {
+    __shared__ double scratch[16];
+    const double lp = block_sum_as_1024(a.partials, a.partials_per_sign, scratch);
+    const double lm = block_sum_as_1024(a.partials + a.partials_per_sign, a.partials_per_sign, scratch);
+    g = (a.eps == 0.0f) ? 0.0 : (lp - lm) / (2.0 * (double)a.eps);
+    if (blockIdx.x == 0 && threadIdx.x == 0) { a.scalars[0] = lp; a.scalars[1] = lm; a.scalars[2] = g; }
+  } else {
+    g = a.scalars[2];
+  }
+  if (tw >= a.total_quads) return;
+  const uint64_t seed = a.seed, step = a.step;
+  const auto* tab = mat_table(a);
+  int lo = 0, hi = a.n_mats - 1;                                      // last matrix whose first_quad <= tw
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     const int64_t fq = (int64_t)(((uint64_t)tab[mid * W + FQ + 1] << 32) | tab[mid * W + FQ]);
@@ -470,7 +510,7 @@ __global__ void __launch_bounds__(256) sparse_update_table_kernel(const SmallMat
   const SmallMat mt = __builtin_bit_cast(SmallMat, raw);
   const int64_t tq = tw + (int64_t)(threadIdx.x & 63) - mt.first_quad, j0 = 4 * tq;
   if (j0 >= (int64_t)mt.nnz) return;
-  const float c = (float)((double)lr * *g);
+  const float c = (float)((double)a.lr * g);                          // lr * g, rounded once
   float z[4];
   zbar_quad((mt.nnz_base >> 2) + (uint64_t)tq, seed, step, z);
   float __attribute__((address_space(1)))* const v = (float __attribute__((address_space(1)))*)mt.sp_val + j0;
@@ -722,7 +762,7 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   if (rc != SZO_OK) return rc;
   const FewPlan p = plan_of_one(d, compact);
   SmallArgs a{};
-  fill_mat(a.one, d);                                       // whole matrix: the kernel offsets rows by slice
+  fill_mat(a.inl[0], d);                                       // whole matrix: the kernel offsets rows by slice
   a.table = nullptr; a.n_mats = 1;
   a.store_sign = sign; a.loss_mode = loss_mode ? 1 : 0;
   a.seed = seed; a.step = step; a.eps = eps;
@@ -731,17 +771,24 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   return launch_plan(p, p.units(d), p.slices(d), d->K, code_bytes(d), a, stream);
 }
 
+// Partials that every workgroup of the update adds up by itself: as many as cost less than a launch of their own.  With
+// the table in the kernel arguments a small step is two launches instead of four, us per step: one 256 x 256 layer at 64
+// tokens (16 partials per sign, 1 workgroup) 18.9 -> 13.4, one OPT block at 16 tokens (576 per sign, 202 workgroups: just
+// below the line) 56 -> 52, a 4096 x 4096 layer at 16 tokens (64 per sign, 17 workgroups) 27 -> 19.8.
+constexpr int64_t kFusedReduceReads = 1 << 17;              // partials per sign x workgroups
+
 // A whole stack in one launch per instantiation.  The table is assembled on the host, longest K
-// first (their workgroups run longest, so they should start first), copied into `table_dev`
-// (device, small_m_table_bytes(n)) with an asynchronous copy on the stream, and also drives one
-// grouped sparse update when `do_update` is set.  With `do_forward` false only the table is staged
-// and the update runs (used by the many-token step, whose forwards are launched per matrix).
+// first (their workgroups run longest, so they should start first), and travels in the kernel arguments
+// (up to kInlineMats matrices) or is copied into `table_dev` (device, small_m_table_bytes(n)) with an
+// asynchronous copy on the stream; it also drives one grouped sparse update.  With `do_forward` false only the
+// update runs (used by the other paths): `partials_per_sign` > 0 says that g has still to be formed from
+// that many loss partials per sign.
 int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,
-                 void* table_dev, double* partial_plus, double* scalars, bool do_forward, bool do_update,
+                 void* table_dev, double* partial_plus, int64_t partials_per_sign, double* scalars, bool do_forward,
                  hipStream_t stream) {
-  int rc = set_small_attrs();
+  int rc = do_forward ? set_small_attrs() : SZO_OK;
   if (rc != SZO_OK) return rc;
-  if (n > kMaxStepMatrices) return SZO_EUNSUPPORTED;
+  if (n > kMaxStepMatrices || (n > kInlineMats && !table_dev)) return SZO_EUNSUPPORTED;
   LaunchShape shape;
   for (int i = 0; i < n; ++i) shape.add(&descs[i]);
   // two activation sets (forward launches only): one block of rows for each, whatever the token count
@@ -785,32 +832,49 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
     if (do_forward && 2 * partials > kMaxLossPartials) return SZO_EUNSUPPORTED;
     if (c.units * c.slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
   }
-  rc = stage_table(host, sizeof(SmallMat) * (size_t)entries, table_dev, stream);
-  if (rc != SZO_OK) return rc;
-  SmallArgs a{};
-  a.store_sign = 1; a.loss_mode = 1;
-  a.seed = seed; a.step = step; a.eps = eps;
-  a.partial_plus = partial_plus; a.partial_minus = do_forward ? partial_plus + partials : nullptr;
-  const SmallMat* tdev = (const SmallMat*)table_dev;
-  int first_entry = 0;
-  for (int cls = 0; cls < kClasses; ++cls) {
-    const ClassTotals& c = classes[cls];
-    if (do_forward && c.units > 0 && c.slices > 0) {
-      a.table = tdev + first_entry; a.n_mats = c.entries;
-      rc = launch_plan(FewPlan::of_class(cls), c.units, c.slices, c.k, c.code_bytes, a, stream);
-      if (rc != SZO_OK) return rc;
-    }
-    first_entry += c.entries;
-  }
-  if (do_forward) {
-    rc = reduce_step(partial_plus, (int)partials, eps, scalars, stream);
+  const bool inl = entries <= kInlineMats;
+  if (!inl) {
+    rc = stage_table(host, sizeof(SmallMat) * (size_t)entries, table_dev, stream);
     if (rc != SZO_OK) return rc;
   }
-  if (do_update && quads > 0) {
-    const int64_t ub = (quads + 255) / 256;
-    if (ub > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+  const SmallMat* tdev = inl ? nullptr : (const SmallMat*)table_dev;
+  if (do_forward) {
+    SmallArgs a{};
+    a.store_sign = 1; a.loss_mode = 1;
+    a.seed = seed; a.step = step; a.eps = eps;
+    a.partial_plus = partial_plus; a.partial_minus = partial_plus + partials;
+    int first_entry = 0;
+    for (int cls = 0; cls < kClasses; ++cls) {
+      const ClassTotals& c = classes[cls];
+      if (c.units > 0 && c.slices > 0) {
+        a.table = inl ? nullptr : tdev + first_entry;
+        if (inl) std::copy(host + first_entry, host + first_entry + c.entries, a.inl);
+        a.n_mats = c.entries;
+        rc = launch_plan(FewPlan::of_class(cls), c.units, c.slices, c.k, c.code_bytes, a, stream);
+        if (rc != SZO_OK) return rc;
+      }
+      first_entry += c.entries;
+    }
+    partials_per_sign = partials;
+  }
+  const int64_t ub = (quads + 255) / 256;
+  if (ub > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+  const bool reduce_here = ub > 0 && partials_per_sign > 0 && partials_per_sign * ub <= kFusedReduceReads;
+  // (a step without a single live layer has no partials: its losses are the sums over none)
+  if (!reduce_here && (do_forward || partials_per_sign > 0)) {
+    rc = reduce_step(partial_plus, (int)partials_per_sign, eps, scalars, stream);
+    if (rc != SZO_OK) return rc;
+  }
+  if (ub > 0) {
+    UpdateArgs u{};
+    u.table = tdev;
+    if (inl) std::copy(host, host + entries, u.inl);
+    u.n_mats = entries; u.total_quads = quads;
+    u.partials_per_sign = reduce_here ? (int)partials_per_sign : 0;
+    u.partials = partial_plus; u.scalars = scalars;
+    u.seed = seed; u.step = step; u.lr = lr; u.eps = eps;
     if ((rc = timing_begin(stream, 1)) != SZO_OK) return rc;
-    sparse_update_table_kernel<<<(unsigned)ub, 256, 0, stream>>>(tdev, entries, quads, seed, step, scalars + 2, lr);
+    sparse_update_table_kernel<<<(unsigned)ub, 256, 0, stream>>>(u);
     SZO_LAUNCH_CHECK();
     if ((rc = timing_end(stream)) != SZO_OK) return rc;
   }
