@@ -463,9 +463,10 @@ void onepass_force(int how) { g_force_onepass = how; }
 // other path -> this one:
 //  * against the few-token path: more than 32 tokens and 512 workgroups, two per CU.  Four Llama blocks at 32 / 48 / 64 /
 //    128 tokens (700 .. 1400 workgroups) 159 / 232 / 241 / 517 -> 189 / 192 / 193 / 346; one Mistral block at 128 / 192
-//    tokens (416 / 624) 153 / 256 -> 204 / 214; 32 OPT blocks at 64 / 224 tokens 1531 / 5697 -> 1241 / 4334.  Where the
-//    few-token path has only its split kernel (bf16 tile, K an odd multiple of 64): four Llama blocks with the bf16 tile
-//    at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393.
+//    tokens (416 / 624) 153 / 256 -> 204 / 214; 32 OPT blocks at 64 / 224 tokens 1531 / 5697 -> 1241 / 4334.
+//    Not up to 64 tokens where the longest K (12 us per 1024 columns here, 7 there) outlasts everything else: four OPT
+//    blocks at 64 tokens 214 -> 241.  Where the few-token path has only its split kernel (bf16 tile, K an odd multiple of
+//    64): four Llama blocks with the bf16 tile at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393.
 //  * against the tiled kernel, up to kOnePassTokens tokens unless the caller asks for it: beyond that a step is two full
 //    forwards per layer by default, the products of the single-layer calls.  The two differ by what a row of tiles
 //    costs: a unit of 64 token rows here takes 1 + 108 rho
@@ -478,13 +479,16 @@ void onepass_force(int how) { g_force_onepass = how; }
 constexpr int64_t kOnePassTokens = 512;
 static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y) {
   int64_t wgs = 0, most_tokens = 0;
-  double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0;
+  double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0, wg_k = 0.0, longest_k = 0.0;
   bool stream = true;
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
     const double size = (double)d->N * (double)d->K;
-    wgs += ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
+    const int64_t tiles = ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
+    wgs += tiles;
+    wg_k += (double)tiles * (double)d->K;
+    longest_k = std::max(longest_k, (double)d->K);
     most_tokens = std::max<int64_t>(most_tokens, d->M);
     weights += size;
     entries += (double)d->nnz;
@@ -494,7 +498,8 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
   }
   const double rho = entries / weights;
   if (store_y) return wgs >= 4 && rho <= 0.015;
-  if (few) return wgs >= 512 ? most_tokens > (stream ? 32 : 16) : !stream && most_tokens > 64 && wgs >= 256;
+  if (few && wgs < 512) return !stream && most_tokens > 64 && wgs >= 256;
+  if (few) return most_tokens > (stream ? 32 : 16) && (!stream || most_tokens > 64 || 205.0 * longest_k <= wg_k);
   if (wgs < (most_tokens <= 128 ? 256 : 32)) return false;
   return asked_for || (most_tokens <= kOnePassTokens && (1.0 + 108.0 * rho) * here < 1.42 * tiled);
 }

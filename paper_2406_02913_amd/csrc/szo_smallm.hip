@@ -537,11 +537,14 @@ static int64_t strips_of(const szo_linear_desc* d) { return (d->N + SM_BN - 1) /
 // and as 64-row bands.
 struct LaunchShape {
   int64_t strips16 = 0, bands16 = 0;
+  double band_k = 0.0, longest_k = 0.0;                     // K summed over those bands, longest K, in units of 1024
   void add(const szo_linear_desc* d) {
     if (d->M <= 0 || d->N <= 0) return;
     const int64_t slices = (d->M + SM_ROWS - 1) / SM_ROWS;
     strips16 += strips_of(d) * slices;
     bands16 += bands_of(d) * slices;
+    band_k += (double)(bands_of(d) * slices) * (double)d->K / 1024.0;
+    longest_k = std::max(longest_k, (double)d->K / 1024.0);
   }
 };
 
@@ -590,19 +593,27 @@ struct FewPlan {
   int slices(const szo_linear_desc* d) const { return (int)((d->M + rows() - 1) / rows()); }
 };
 
-// Launches of at most this many bands x slices take the split kernel.  Measured against the stream kernel, us per
-// step: OPT blocks at 16 tokens, 576 / 1152 / 2304 / 3456 units: 47 / 66 / 125 / 183 against 130 / 134 / 158 / 179;
-// one Llama block at 32 / 64 / 128 tokens, 1400 / 2800 / 5600 units: 62 / 92 / 173 against 95 / 100 / 135.  The table
-// format (look-ups: 700 / 1400 / 2100 units 61 / 108 / 164 against 143 / 145 / 147) and two activation sets (65 / 115
-// against 113 / 118 at 700 / 1400) do more work per unit.
-constexpr int64_t kSplitUnits = 2800, kSplitUnitsHeavy = 1500;
+// Whether a launch takes the split kernel.  The stream kernel's time is the chain of its longest K, which the split
+// shortens, plus its share of the work; the split kernel pays for the sums of every band instead.  The two lines below
+// are fitted to single layers of 2048..16384 rows x 512..16384 columns at 16..200 tokens and to whole blocks, and were
+// right to 10 % in all of them.  us per step, split / stream: 16384 x 2048 at 16 / 64 / 128 tokens 18 / 34 / 52 against 26 / 27 /
+// 34, 16384 x 16384 at 16 / 64 / 128 tokens 39 / 109 / 199 against 125 / 130 / 179, 4096 x 512 at 64 / 200 tokens 14 / 20
+// against 16 / 17; one / two / four OPT blocks at 16 tokens 47 / 66 / 125 against 130 / 134 / 158, one Llama block at 64
+// tokens 92 against 100.  Look-ups (table format) and two activation sets cost more per unit in the split kernel: one Llama
+// block at 16 / 32 / 48 tokens with tables 61 / 108 / 164 against 143 / 145 / 147, with two sets at 16 / 32 65 / 115
+// against 113 / 118.
+static bool split_pays(const LaunchShape& launch, bool dual, bool lut) {
+  const double split = 0.012 * (double)launch.bands16 + 0.0058 * launch.band_k;
+  const double stream = 6.9 * launch.longest_k + 0.0026 * launch.band_k;
+  return split * (dual ? 1.65 : lut ? 1.25 : 1.0) <= stream;
+}
 static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, bool dual, bool compact = false) {
   FewPlan p;
   if (d->format == SZO_FORMAT_LUT) p.dequant = D_LUT;
   else if (d->tile_dtype == SZO_TILE_BF16) p.dequant = D_TILE_BF16;
   else if (!stream_ok(d)) p.dequant = D_TILE_F16;
   else p.dequant = d->group == 128 ? D_FAST : D_PLAIN;
-  bool split = launch.bands16 <= (dual || p.dequant == D_LUT ? kSplitUnitsHeavy : kSplitUnits);
+  bool split = split_pays(launch, dual, p.dequant == D_LUT);
   if (g_force_split) split = g_force_split > 0;
   if (g_force_rblocks || compact) split = false;
   if (!stream_ok(d)) split = true;
