@@ -29,7 +29,7 @@ struct SmallMat {
   const uint32_t* sp_idx;
   float* sp_val;
   const uint16_t* target;   // bf16 [M,N]   (loss mode)
-  float* y;                 // fp32 [M,N]   (store mode)
+  float* y;                 // fp32 [M,N]   (store_sign != 0)
   uint64_t nnz_base;
   double loss_scale;
   int N, K;
@@ -56,8 +56,8 @@ struct SmallArgs {
   int n_mats;
   int slices;               // slices of token rows per strip in this launch (the longest matrix's count)
   int stream_once;          // host's choice: load the codes as a non-temporal stream (see small_m_kernel, ONCE)
-  int store_sign;           // store mode: which forward to write (-1, 0, +1); loss mode: unused
-  int loss_mode;            // 1: write loss partials for both signs, 0: store y
+  int store_sign;           // which forward's outputs are written to y (+1, -1), 0: neither
+  int loss_mode;            // 1: write loss partials for both signs
   uint64_t seed, step;
   float eps;                // perturbation scale of the "+" forward (the "-" forward uses -eps)
   double* partial_plus;     // [total workgroups]

@@ -1057,7 +1057,7 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
       rc = onepass_one(d, seed, step, eps, part + off, part + T + off, s);
       off += onepass_tiles(d);
     } else if (few_all) {
-      rc = small_m_launch_one(d, seed, step, eps, 1, true, part + off, part + T + off, compact, s);
+      rc = small_m_launch_one(d, seed, step, eps, 0, true, part + off, part + T + off, compact, s);
       off += small_m_partials(d, compact);
     } else {
       const double scale = 1.0 / ((double)d->M * (double)d->N);
@@ -1106,7 +1106,7 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
     // the few-token kernel computes both signs at once: make the requested one its "+" forward
     const int64_t nb = small_m_partials(desc);
     if (2 * nb > kMaxLossPartials) return SZO_EUNSUPPORTED;
-    rc = small_m_launch_one(desc, seed, step, (float)sign * eps, 1, true, partial_area(workspace),
+    rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, partial_area(workspace),
                             partial_area(workspace) + nb, false, (hipStream_t)stream);
     if (rc != SZO_OK) return rc;
     return reduce_partials(partial_area(workspace), (int)nb, 1.0, loss_acc, (hipStream_t)stream);

@@ -25,8 +25,8 @@
 //     entries per refill so that all lanes work), and multiplies them in groups of 16 entries as a
 //     second, tiny MFMA: A = the entries' columns of x (gathered from LDS), B = a one-hot matrix
 //     that routes entry e to its row (value v or z).  No atomics, no read-modify-write chains.
-// The epilogue forms y(+-) and either stores y for the requested sign or folds the squared error
-// against the target into two fp64 partials per workgroup (one per sign).
+// The epilogue forms y(+-), stores y for the requested sign and folds the squared error against the
+// target into two fp64 partials per workgroup (one per sign); a launch asks for either or both.
 // Everything is accumulated in a fixed order: results are bit-reproducible.
 #include <algorithm>
 #include <cstddef>
@@ -423,9 +423,8 @@ __global__ void __launch_bounds__(256, R == 1 ? (MODE == SM_LUT ? 3 : SM_MIN_BLO
           const float dp = yp - t, dm = ym - t;
           if (!DUAL || rb == 0) lp += (double)(dp * dp);    // DUAL: block 0 is the +eps forward, block 1 the -eps one
           if (!DUAL || rb == 1) lm += (double)(dm * dm);
-        } else {
-          g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : a.store_sign < 0 ? ym : acc[rb][s][r];
         }
+        if (!DUAL && a.store_sign) g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : ym;
       }
     }
   }
@@ -766,8 +765,8 @@ static int set_small_attrs() {
 
 // One matrix, descriptor passed in the kernel arguments (no device table needed), as one launch.  In loss mode
 // slice i writes its partials behind those of slice i - 1, small_m_partials(d, compact) in all, scaled by 1 / (M N) of the
-// whole matrix, so that their sum is the matrix's loss.
-int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int sign, bool loss_mode,
+// whole matrix, so that their sum is the matrix's loss.  store_sign: the forward whose outputs are written to d->y, 0 = none.
+int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int store_sign, bool loss_mode,
                        double* partial_plus, double* partial_minus, bool compact, hipStream_t stream) {
   const int rc = set_small_attrs();
   if (rc != SZO_OK) return rc;
@@ -775,7 +774,7 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   SmallArgs a{};
   fill_mat(a.inl[0], d);                                       // whole matrix: the kernel offsets rows by slice
   a.table = nullptr; a.n_mats = 1;
-  a.store_sign = sign; a.loss_mode = loss_mode ? 1 : 0;
+  a.store_sign = store_sign; a.loss_mode = loss_mode ? 1 : 0;
   a.seed = seed; a.step = step; a.eps = eps;
   a.partial_plus = partial_plus;
   a.partial_minus = partial_minus;
@@ -851,7 +850,7 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   const SmallMat* tdev = inl ? nullptr : (const SmallMat*)table_dev;
   if (do_forward) {
     SmallArgs a{};
-    a.store_sign = 1; a.loss_mode = 1;
+    a.store_sign = 0; a.loss_mode = 1;
     a.seed = seed; a.step = step; a.eps = eps;
     a.partial_plus = partial_plus; a.partial_minus = partial_plus + partials;
     int first_entry = 0;

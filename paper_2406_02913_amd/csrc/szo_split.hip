@@ -372,9 +372,8 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
       const float dp = yp - t, dm = ym - t;
       lp += (double)(dp * dp);
       lm += (double)(dm * dm);
-    } else {
-      g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : a.store_sign < 0 ? ym : yp;
     }
+    if (!DUAL && a.store_sign) g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : ym;
   }
   if (a.loss_mode) {
     __shared__ double part[2][SP_MAX_WAVES];
