@@ -690,9 +690,12 @@ constexpr int kSmallMaxSlices = 15;
 // against 371 / 375 / 379, sixteen blocks 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where
 // the tiles would leave the chip idle.
 constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTokensSmallLaunch = 128;
+// The split kernel's byte offsets inside a band's codes (32 per column) and inside its sixteen rows of x (32 per column)
+// have 32 bits; stream_ok's bound on the codes keeps the other layers below that.
+constexpr int64_t kSplitOnlyColumns = 1 << 23;
 static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch) {
   if (!stream_ok(d))
-    return d->format == SZO_FORMAT_UNIFORM &&
+    return d->format == SZO_FORMAT_UNIFORM && d->K < kSplitOnlyColumns &&
            d->M <= (launch.bands16 <= 2304 ? kSplitOnlyTokensSmallLaunch : kSplitOnlyTokens);
   // two activation sets: a pass holds 16 token rows of each, so it is worth less
   const int64_t slices = (d->M + (d->x_minus ? 15 : 31)) / (d->x_minus ? 16 : 32), tile_rows = (d->M + 255) / 256;

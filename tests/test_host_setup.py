@@ -212,3 +212,15 @@ def test_kernel_timing_calls_are_safe_without_any_launch():
     assert szo.szo_kernel_timing_read() == (0.0, 0)
     szo.szo_kernel_timing(False)
     assert szo.lib.szo_kernel_timing_read(None, None) == szo.EINVAL
+
+
+def test_layers_beyond_the_split_kernels_offsets_are_left_to_the_tiled_kernel():
+    """Host rule only: the few-token kernels address a band's codes and its rows of x with 32-bit byte offsets."""
+    eligible = szo.lib._ZN3szo16small_m_eligibleEPK15szo_linear_descibb
+    eligible.restype, eligible.argtypes = ctypes.c_bool, [ctypes.POINTER(szo.LinearDesc), ctypes.c_int, ctypes.c_bool, ctypes.c_bool]
+    for K, tile, want in ((4160, szo.TILE_BF16, True), (4160, szo.TILE_F16, True), ((1 << 23) - 64, szo.TILE_BF16, True),
+                          (1 << 23, szo.TILE_BF16, False), ((1 << 27) + 64, szo.TILE_BF16, False),
+                          ((1 << 27) + 64, szo.TILE_F16, False), ((1 << 28) + 64, szo.TILE_F16, False),
+                          ((1 << 27) - 128, szo.TILE_F16, True), (1 << 27, szo.TILE_F16, False)):
+        d = szo.LinearDesc(M=8, N=15, K=K, group=64, tile_dtype=tile)
+        assert eligible(ctypes.byref(d), 1, False, False) is want, (K, tile)
