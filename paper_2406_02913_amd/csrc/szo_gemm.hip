@@ -1102,10 +1102,11 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   if (rc != SZO_OK) return rc;
   if (!loss_acc || !workspace || ((uintptr_t)workspace & 7)) return SZO_EINVAL;
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
-  if (few_token_enabled() && small_m_eligible(desc, 1, false, false) && scale == 1.0 / ((double)desc->M * (double)desc->N)) {
-    // the few-token kernel computes both signs at once: make the requested one its "+" forward
-    const int64_t nb = small_m_partials(desc);
-    if (2 * nb > kMaxLossPartials) return SZO_EUNSUPPORTED;
+  // the few-token kernels compute both signs at once: make the requested one the "+" forward.  Their scale is that of a
+  // step's loss, and both signs' partials have to fit.
+  const bool few = few_token_enabled() && small_m_eligible(desc, 1, false, false) && scale == 1.0 / ((double)desc->M * (double)desc->N);
+  const int64_t nb = few ? small_m_partials(desc) : 0;
+  if (few && 2 * nb <= kMaxLossPartials) {
     rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, partial_area(workspace),
                             partial_area(workspace) + nb, false, (hipStream_t)stream);
     if (rc != SZO_OK) return rc;

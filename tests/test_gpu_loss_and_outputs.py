@@ -62,3 +62,25 @@ def test_steps_with_the_loss_fused_leave_the_outputs_alone(M, K, G, tile, cfg):
     szo.szo_zo_step([desc], 5, 0, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
     szo.szo_zo_step_noalloc([desc], 5, 0, 1e-3, 0.0, scal)
     assert bool((d.y == 7.0).all())
+
+
+def test_a_layer_with_more_partials_than_the_workspace_holds_takes_the_tiled_kernel():
+    """64 tokens, one 64-column tile and 2^24 + 64 rows: one band more than the split kernel has room for partials."""
+    M, N, K = 64, (1 << 24) + 64, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randint(256, (N // 64, 64, 32), generator=gen, device="cuda", dtype=torch.uint8)      # [band][row][byte]
+    scales = torch.full((N,), 0.01, device="cuda", dtype=torch.float16)
+    x = torch.randn((M, K), generator=gen, device="cuda", dtype=torch.bfloat16)
+    target = torch.randn((M, N), generator=gen, device="cuda", dtype=torch.bfloat16)
+    tile_ptr = torch.zeros(N // 64 + 1, device="cuda", dtype=torch.int32)
+    desc = szo.make_desc(M, N, K, 64, 0, 0, x, q.view(-1), scales, tile_ptr, None, None, None, target, szo.TILE_BF16)
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    szo.szo_linear_fwd_mse(desc, 1, 0, 0, 0.0, 1.0 / (M * N), loss, szo.new_workspace())
+    want = 0.0
+    for lo in range(0, N, 1 << 20):
+        rows = q.view(N, 32)[lo:lo + (1 << 20)]
+        codes = torch.stack([rows & 15, rows >> 4], dim=2).view(-1, K).float() - 8.0
+        w = (codes * scales[0].float()).bfloat16().float()
+        want += ((x.float() @ w.t()).double() - target[:, lo:lo + (1 << 20)].double()).square_().sum().item() / (M * N)
+    # the same bf16 operands, fp32 sums of 64 products
+    assert abs(loss.item() - want) <= 1e-6 * want
