@@ -58,7 +58,8 @@ extern "C" {
  *   SZO_TILE_F16 (default) keeps w_sparse +- eps*z within the estimator's error budget (11-bit
  *   significand), but NARROWS THE ACTIVATION DOMAIN: the bf16 activations are converted to fp16 with
  *   truncation, which is exact only for 2^-14 <= |x| <= 65504.  Larger magnitudes saturate at
- *   +-65504 (infinities stay infinite), smaller ones lose low bits and vanish below 2^-24; no error
+ *   +-65504 (infinities stay infinite, except that the few-token kernel for large launches may turn all
+ *   outputs of such a token row into NaN), smaller ones lose low bits and vanish below 2^-24; no error
  *   is raised.  A caller whose activations may leave that range (outlier channels of a real model)
  *   measures them with szo_activation_absmax() and takes what szo_choose_tile_dtype() returns.
  *   SZO_TILE_BF16 stages the activations unchanged (full bf16 range); the sensitive values are then

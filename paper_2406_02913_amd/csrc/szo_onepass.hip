@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <vector>
 #include "szo_internal.h"
+#include "szo_nonfinite.h"
 #include "szo_rng.h"
 #include "szo_tile.h"
 
@@ -350,8 +351,9 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   // Without y: with d = D - t the losses are sum d^2 +- 2 eps sum d Z + eps^2 sum Z^2, and their difference, which g
   // is made of, is summed as such instead of being left over from two nearly equal sums.
   double loss_plus = 0.0, loss_minus = 0.0, sum_dd = 0.0, sum_dz = 0.0, sum_zz = 0.0;
-  auto finish = [&](auto full_tag, auto staged_tag) {
-    constexpr bool FULL = decltype(full_tag)::value, STAGED = decltype(staged_tag)::value;
+  uint8_t* const special = smem + OnePassLds::RING;         // AGAIN: token rows that are left out
+  auto finish = [&](auto full_tag, auto staged_tag, auto again_tag) {
+    constexpr bool FULL = decltype(full_tag)::value, STAGED = decltype(staged_tag)::value, AGAIN = decltype(again_tag)::value;
     const uint32_t base = (uint32_t)(m0 + ml0) * (uint32_t)pe.N + (uint32_t)(n0 + nl0);   // M * N < 2^32 checked on the host
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -361,15 +363,15 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int dm = 32 * i + 8 * (r >> 2) + (r & 3), dn = 32 * j;
-          if (FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) {
+          if ((FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) && !(AGAIN && special[ml0 + dm])) {
             const uint32_t off = base + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn;
             uint32_t tb;
             if (STAGED) tb = *reinterpret_cast<const uint16_t*>(trow + dm * OP_TROW + dn * 2);
             else tb = pe.target[off];
             const float t = __uint_as_float(tb << 16);
-            if (STORE_Y) {                                  // as mse_kernel: differences and squares in fp64
+            if (STORE_Y || AGAIN) {                         // as mse_kernel: differences and squares in fp64
               const float ez = eps * accz[i][j][r], yp = acc[i][j][r] + ez, ym = acc[i][j][r] - ez;
-              pe.y[off] = ym;
+              if (!AGAIN) pe.y[off] = ym;
               const double dp = (double)yp - (double)t, dmn = (double)ym - (double)t;
               loss_plus = fma(dp, dp, loss_plus);
               loss_minus = fma(dmn, dmn, loss_minus);
@@ -381,16 +383,16 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
             }
           }
         }
-        if (!STORE_Y) { sum_dd += (double)dd; sum_dz += (double)dz; sum_zz += (double)zz; }
+        if (!STORE_Y && !AGAIN) { sum_dd += (double)dd; sum_dz += (double)dz; sum_zz += (double)zz; }
       }
   };
+  using T = std::true_type;
+  using F = std::false_type;
   {
-    using T = std::true_type;
-    using F = std::false_type;
     const bool full = m0 + OP_BM <= pe.M && n0 + OP_BN <= pe.N;
-    if (full && staged) finish(T{}, T{});
-    else if (staged) finish(F{}, T{});
-    else finish(F{}, F{});
+    if (full && staged) finish(T{}, T{}, F{});
+    else if (staged) finish(F{}, T{}, F{});
+    else finish(F{}, F{}, F{});
   }
   if (!STORE_Y) {
     const double even = fma((double)eps * (double)eps, sum_zz, sum_dd), odd = 2.0 * (double)eps * sum_dz;
@@ -398,15 +400,52 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     loss_minus = even - odd;
   }
   __shared__ double wave_part[2][OP_WAVES];
-  loss_plus = wave_sum(loss_plus);
-  loss_minus = wave_sum(loss_minus);
-  if (lane == 0) { wave_part[0][wave] = loss_plus; wave_part[1][wave] = loss_minus; }
-  __syncthreads();
-  if (tid < 2) {
-    double t = 0.0;
+  double tile_plus, tile_minus;                             // of the whole workgroup, in every thread
+  auto sum_waves = [&]() {
+    loss_plus = wave_sum(loss_plus);
+    loss_minus = wave_sum(loss_minus);
+    if (lane == 0) { wave_part[0][wave] = loss_plus; wave_part[1][wave] = loss_minus; }
+    __syncthreads();
+    tile_plus = 0.0; tile_minus = 0.0;
 #pragma unroll
-    for (int i = 0; i < OP_WAVES; ++i) t += wave_part[tid][i];
-    (tid == 0 ? pe.partials : pe.partials_minus)[bm * pe.grid_n + bn] = t * pe.loss_scale;
+    for (int i = 0; i < OP_WAVES; ++i) { tile_plus += wave_part[0][i]; tile_minus += wave_part[1][i]; }
+  };
+  sum_waves();
+  if (!(__builtin_isfinite(tile_plus) && __builtin_isfinite(tile_minus))) {
+    // Outputs that are not finite.  The squares are added one by one this time (D = inf and Z = 0 have no product); token
+    // rows with an infinite or NaN activation are left out and evaluated by their definition, thread = column.
+    __syncthreads();
+    for (int i = 0; i < OP_BM / OP_WAVES; ++i) {
+      const int row = OP_BM / OP_WAVES * wave + i;
+      bool bad = false;
+      for (int k = 8 * lane; m0 + row < pe.M && k < K; k += 8 * 64) {
+        const u32x4 u = *reinterpret_cast<global_u32x4>(pe.x + (size_t)(m0 + row) * K + k);
+        for (int w = 0; w < 4; ++w) bad = bad || (u[w] & 0x7F80u) == 0x7F80u || (u[w] & 0x7F800000u) == 0x7F800000u;
+      }
+      const bool any = __any(bad);
+      if (lane == 0) special[row] = any ? 1 : 0;
+    }
+    __syncthreads();
+    loss_plus = 0.0; loss_minus = 0.0;
+    finish(F{}, F{}, T{});
+    const WeightSource source = {pe.qweight, pe.scales, nullptr, pe.tile_ptr, pe.sp_idx, pe.sp_val, K, gshift, pe.nnz, pe.nnz_base, pe.seed, pe.step};
+    for (int row = 0; row < OP_BM; ++row) {
+      if (!special[row] || n0 + tid >= pe.N) continue;
+      const uint32_t n = (uint32_t)(n0 + tid), off = (uint32_t)(m0 + row) * (uint32_t)pe.N + n;
+      const global_u16 x = pe.x + (size_t)(m0 + row) * K;
+      float yp = 0.0f, ym = 0.0f;
+      nonfinite_output<DT>(source, x, n, eps, yp);
+      nonfinite_output<DT>(source, x, n, -eps, ym);
+      if (STORE_Y) pe.y[off] = ym;
+      const double t = (double)__uint_as_float((uint32_t)pe.target[off] << 16), dp = (double)yp - t, dmn = (double)ym - t;
+      loss_plus = fma(dp, dp, loss_plus);
+      loss_minus = fma(dmn, dmn, loss_minus);
+    }
+    sum_waves();
+  }
+  if (tid == 0) {
+    pe.partials[bm * pe.grid_n + bn] = tile_plus * pe.loss_scale;
+    pe.partials_minus[bm * pe.grid_n + bn] = tile_minus * pe.loss_scale;
   }
 }
 

@@ -21,6 +21,7 @@
 #include <atomic>
 #include <type_traits>
 #include "szo_few.h"
+#include "szo_nonfinite.h"
 
 namespace szo {
 
@@ -347,34 +348,61 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
   // Output o of 1024: column o & 15 of subtile o >> 8, token row (o >> 4) & 15; its accumulator sits in register
   // m & 3 of lane 16 (m >> 2) + column.  Wave-wide LDS reads touch every bank once, y is stored 64 bytes at a time.
   double lp = 0.0, lm = 0.0;
-  for (int o = tid; o < 1024; o += (int)blockDim.x) {
-    const int m = (o >> 4) & 15, n = band * 64 + 16 * (o >> 8) + (o & 15);
-    if (m >= M || n >= N) continue;
-    const float* p = red + (o >> 8) * 256 + ((m >> 2) * 16 + (o & 15)) * 4 + (m & 3);
-    float t = 0.0f;
-    if (a.loss_mode) t = __uint_as_float((uint32_t)g_target[(size_t)m * N + n] << 16);
-    float d[NACC];
+  bool all_finite = true;
+  // AGAIN: a second time, with the outputs of token rows that hold an infinite or NaN activation by their definition
+  auto finish = [&](auto again_tag) {
+    constexpr bool AGAIN = decltype(again_tag)::value;
+    WeightSource source;
+    global_u16 x_plus, x_minus;
+    if constexpr (AGAIN) {
+      int unit = bid;                                       // the entry is read again (laundered: not kept for this)
+      asm volatile("" : "+s"(unit));
+      const SmallMat ms = find_matrix(a, unit);
+      source = WeightSource{(global_u8)ms.qweight, LUT ? nullptr : (global_u16)ms.scales, LUT ? (global_u16)ms.scales : nullptr,
+                            (global_u32)ms.tile_ptr, (global_u32)ms.sp_idx, (global_f32)ms.sp_val, ms.K, ms.group_shift,
+                            ms.nnz, ms.nnz_base, a.seed, a.step};
+      x_plus = (global_u16)ms.x + (size_t)slice * SM_ROWS * (size_t)ms.K;
+      x_minus = (global_u16)(DUAL ? ms.x2 : ms.x) + (size_t)slice * SM_ROWS * (size_t)ms.K;
+    }
+    lp = 0.0; lm = 0.0;
+    for (int o = tid; o < 1024; o += (int)blockDim.x) {
+      const int m = (o >> 4) & 15, n = band * 64 + 16 * (o >> 8) + (o & 15);
+      if (m >= M || n >= N) continue;
+      const float* p = red + (o >> 8) * 256 + ((m >> 2) * 16 + (o & 15)) * 4 + (m & 3);
+      float t = 0.0f;
+      if (a.loss_mode) t = __uint_as_float((uint32_t)g_target[(size_t)m * N + n] << 16);
+      float d[NACC];
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) d[i] = 0.0f;
-    for (int w = 0; w < waves; ++w, p += RED) {
+      for (int i = 0; i < NACC; ++i) d[i] = 0.0f;
+      for (int w = 0; w < waves; ++w, p += RED) {
 #pragma unroll
-      for (int i = 0; i < NACC; ++i) d[i] += p[i * 1024];
+        for (int i = 0; i < NACC; ++i) d[i] += p[i * 1024];
+      }
+      float yp, ym;
+      if (TILE_ROUND) {
+        yp = DUAL ? d[0] : d[0] + d[1];
+        ym = DUAL ? d[1] : d[0] + d[NACC - 1];
+      } else {
+        yp = d[0] + a.eps * d[1];
+        ym = d[NACC - 2] - a.eps * d[NACC - 1];
+      }
+      if constexpr (AGAIN) {
+        constexpr int DT = BF16 ? SZO_TILE_BF16 : SZO_TILE_F16;
+        nonfinite_output<DT>(source, x_plus + (size_t)m * source.K, (uint32_t)n, a.eps, yp);
+        nonfinite_output<DT>(source, x_minus + (size_t)m * source.K, (uint32_t)n, -a.eps, ym);
+      } else {
+        all_finite = all_finite && __builtin_isfinite(yp) && __builtin_isfinite(ym);
+      }
+      if (a.loss_mode) {
+        const float dp = yp - t, dm = ym - t;
+        lp += (double)(dp * dp);
+        lm += (double)(dm * dm);
+      }
+      if (!DUAL && a.store_sign) g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : ym;
     }
-    float yp, ym;
-    if (TILE_ROUND) {
-      yp = DUAL ? d[0] : d[0] + d[1];
-      ym = DUAL ? d[1] : d[0] + d[NACC - 1];
-    } else {
-      yp = d[0] + a.eps * d[1];
-      ym = d[NACC - 2] - a.eps * d[NACC - 1];
-    }
-    if (a.loss_mode) {
-      const float dp = yp - t, dm = ym - t;
-      lp += (double)(dp * dp);
-      lm += (double)(dm * dm);
-    }
-    if (!DUAL && a.store_sign) g_y[(size_t)m * N + n] = a.store_sign > 0 ? yp : ym;
-  }
+  };
+  finish(std::false_type{});
+  if (__builtin_expect(!__all(all_finite), 0)) finish(std::true_type{});
   if (a.loss_mode) {
     __shared__ double part[2][SP_MAX_WAVES];
     lp = wave_sum(lp);
