@@ -143,13 +143,6 @@ __device__ __forceinline__ int xcd_unit(int bid, int grid) {
   return bid;
 }
 
-// The table of a kernel whose first argument is an Args with the members `table` and `inl`.
-template <typename Args>
-__device__ __forceinline__ const uint32_t __attribute__((address_space(4)))* mat_table(const Args& a) {
-  typedef const uint32_t __attribute__((address_space(4)))* words;
-  return a.table ? (words)a.table : (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Args, inl) / 4;
-}
-
 // Table entry of workgroup `unit`: the last matrix whose first_block <= unit.  Read through the constant address
 // space (scalar loads: the table is written before the launch and never during it), so that its fields live in
 // scalar registers like the kernel arguments do; read through a generic pointer they would occupy ~30 vector
@@ -157,7 +150,8 @@ __device__ __forceinline__ const uint32_t __attribute__((address_space(4)))* mat
 __device__ __forceinline__ SmallMat find_matrix(const SmallArgs& a, int unit) {
   constexpr int W = (int)(sizeof(SmallMat) / 4), FB = (int)(offsetof(SmallMat, first_block) / 4);
   static_assert(sizeof(SmallMat) % 4 == 0 && offsetof(SmallMat, first_block) % 4 == 0, "table entry is read as words");
-  const auto* tab = mat_table(a);
+  typedef const uint32_t __attribute__((address_space(4)))* words;
+  const words tab = a.table ? (words)a.table : (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SmallArgs, inl) / 4;
   int lo = 0, hi = a.n_mats - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;

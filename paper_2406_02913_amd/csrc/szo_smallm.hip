@@ -30,6 +30,7 @@
 // Everything is accumulated in a fixed order: results are bit-reproducible.
 #include <algorithm>
 #include <cstddef>
+#include <type_traits>
 #include <utility>
 #include <vector>
 #include "szo_few.h"
@@ -450,7 +451,6 @@ __global__ void __launch_bounds__(256, R == 1 ? (MODE == SM_LUT ? 3 : SM_MIN_BLO
 // memory round trips before it could touch its entries; the launch then took 27 us for 52 MB.)
 struct UpdateArgs {
   const SmallMat* table;    // as in SmallArgs
-  SmallMat inl[kInlineMats];
   int n_mats;
   int partials_per_sign;    // > 0: the losses are still partials, and this launch forms g from them
   const double* partials;   // "+" partials, then "-" partials
@@ -459,6 +459,7 @@ struct UpdateArgs {
   uint64_t seed, step;
   float lr, eps;
 };
+struct InlineUpdateArgs { UpdateArgs staged; SmallMat inl[kInlineMats]; };         // the table in the kernel arguments
 
 // What reduce_step_kernel adds up, in its order: 256 threads stand for its 1024.
 __device__ __forceinline__ double block_sum_as_1024(const double* __restrict__ v, int count, double (&scratch)[16]) {
@@ -479,13 +480,22 @@ __device__ __forceinline__ double block_sum_as_1024(const double* __restrict__ v
 
 // With few partials every workgroup adds them up by itself (same order, same g everywhere) instead of waiting for a
 // launch that does: a step over one 256 x 256 layer at 64 tokens has 16 of them per sign.
-__global__ void __launch_bounds__(256) sparse_update_table_kernel(UpdateArgs a) {
+// REDUCE and the inline table are compile-time: the update of a stack is bound by how many waves are resident while their
+// table search, Philox rounds and value loads follow each other, and keeps the small form (21 registers, no LDS, 8 waves per
+// SIMD).  As one kernel for everything (74 registers, 6 waves) it took 22.8 / 24.6 / 25.3 us on 32 OPT blocks at 1 / 16 / 64
+// tokens instead of 20.7 / 22.3 / 22.5.
+template <bool REDUCE, typename Args>
+__global__ void __launch_bounds__(256) sparse_update_table_kernel(Args args) {
+  constexpr bool INLINE = std::is_same_v<Args, InlineUpdateArgs>;
+  const UpdateArgs& a = reinterpret_cast<const UpdateArgs&>(args);
+  static_assert(offsetof(InlineUpdateArgs, staged) == 0, "both forms begin alike");
   constexpr int W = (int)(sizeof(SmallMat) / 4), FQ = (int)(offsetof(SmallMat, first_quad) / 4);
   static_assert(offsetof(SmallMat, first_quad) % 8 == 0, "first_quad is read as two words");
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int64_t tw = (int64_t)blockIdx.x * 256 + 64 * wave;           // the wave's first thread
+  if (!REDUCE && tw >= a.total_quads) return;
   double g;
-  if (a.partials_per_sign > 0) {
+  if constexpr (REDUCE) {
     __shared__ double scratch[16];
     const double lp = block_sum_as_1024(a.partials, a.partials_per_sign, scratch);
     const double lm = block_sum_as_1024(a.partials + a.partials_per_sign, a.partials_per_sign, scratch);
@@ -496,7 +506,8 @@ __global__ void __launch_bounds__(256) sparse_update_table_kernel(UpdateArgs a) 
   }
   if (tw >= a.total_quads) return;
   const uint64_t seed = a.seed, step = a.step;
-  const auto* tab = mat_table(a);
+  typedef const uint32_t __attribute__((address_space(4)))* words;
+  const words tab = INLINE ? (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(InlineUpdateArgs, inl) / 4 : (words)a.table;
   int lo = 0, hi = a.n_mats - 1;                                      // last matrix whose first_quad <= tw
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -784,11 +795,12 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   return launch_plan(p, p.units(d), p.slices(d), d->K, code_bytes(d), a, stream);
 }
 
-// Partials that every workgroup of the update adds up by itself: as many as cost less than a launch of their own.  With
-// the table in the kernel arguments a small step is two launches instead of four, us per step: one 256 x 256 layer at 64
-// tokens (16 partials per sign, 1 workgroup) 18.9 -> 13.4, one OPT block at 16 tokens (576 per sign, 202 workgroups: just
-// below the line) 56 -> 52, a 4096 x 4096 layer at 16 tokens (64 per sign, 17 workgroups) 27 -> 19.8.
-constexpr int64_t kFusedReduceReads = 1 << 17;              // partials per sign x workgroups
+// When every workgroup of the update adds up the partials by itself instead of waiting for a launch that does: few partials,
+// because their sum stands at the beginning of each workgroup's chain, and few workgroups, because each of them reads all.
+// Single layers, us per step with a launch of its own -> here: 16 partials per sign and 1 workgroup 14.1 -> 13.8, 64 and 17
+// 20.3 -> 20.1, 256 and 17 13.8 -> 13.6, 128 and 328 25.8 -> 25.4; beyond the line 400 and 2 16.9 -> 17.4, 1216 and 17
+// 51.7 -> 52.2, 256 and 656 27.4 -> 28.1, one OPT block at 16 tokens (576 and 202) 41.7 -> 42.4.
+constexpr int64_t kFusedReducePartials = 256, kFusedReduceWorkgroups = 256;
 
 // A whole stack in one launch per instantiation.  The table is assembled on the host, longest K
 // first (their workgroups run longest, so they should start first), and travels in the kernel arguments
@@ -872,22 +884,26 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   }
   const int64_t ub = (quads + 255) / 256;
   if (ub > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
-  const bool reduce_here = ub > 0 && partials_per_sign > 0 && partials_per_sign * ub <= kFusedReduceReads;
+  const bool reduce_here = ub > 0 && ub <= kFusedReduceWorkgroups && partials_per_sign > 0 && partials_per_sign <= kFusedReducePartials;
   // (a step without a single live layer has no partials: its losses are the sums over none)
   if (!reduce_here && (do_forward || partials_per_sign > 0)) {
     rc = reduce_step(partial_plus, (int)partials_per_sign, eps, scalars, stream);
     if (rc != SZO_OK) return rc;
   }
   if (ub > 0) {
-    UpdateArgs u{};
+    InlineUpdateArgs with_table{};
+    UpdateArgs& u = with_table.staged;
     u.table = tdev;
-    if (inl) std::copy(host, host + entries, u.inl);
+    if (inl) std::copy(host, host + entries, with_table.inl);
     u.n_mats = entries; u.total_quads = quads;
     u.partials_per_sign = reduce_here ? (int)partials_per_sign : 0;
     u.partials = partial_plus; u.scalars = scalars;
     u.seed = seed; u.step = step; u.lr = lr; u.eps = eps;
     if ((rc = timing_begin(stream, 1)) != SZO_OK) return rc;
-    sparse_update_table_kernel<<<(unsigned)ub, 256, 0, stream>>>(u);
+    if (inl && reduce_here) sparse_update_table_kernel<true><<<(unsigned)ub, 256, 0, stream>>>(with_table);
+    else if (inl) sparse_update_table_kernel<false><<<(unsigned)ub, 256, 0, stream>>>(with_table);
+    else if (reduce_here) sparse_update_table_kernel<true><<<(unsigned)ub, 256, 0, stream>>>(u);
+    else sparse_update_table_kernel<false><<<(unsigned)ub, 256, 0, stream>>>(u);
     SZO_LAUNCH_CHECK();
     if ((rc = timing_end(stream)) != SZO_OK) return rc;
   }
