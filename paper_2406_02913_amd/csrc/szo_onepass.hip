@@ -17,8 +17,17 @@
 // their columns of the staged x and multiplies both: D += x_g V^T, Z += x_g Z^T.  The first sixteen of a chunk (at a
 // density of 0.1 % it has eight on average) run inside the dense schedule, more of them in a loop behind it.
 //
-// Precision.  The dense weights are rounded to the tile type as in the tiled kernel; v and z are rounded to it one by
-// one (2^-11 relative in fp16) instead of as part of w +- eps z, and eps is applied in fp32.
+// Precision.  fp16 tile, groups of 128 (GROUP_SCALE, one group per chunk): the integer codes are multiplied exactly and
+// the sum of a chunk takes the group's scale in fp32, as in the few-token kernels; other groups, and the bf16 tile: the
+// dense weights are rounded to the tile type as in the tiled kernel.  v and z are rounded to it one by one (2^-11 relative
+// in fp16) instead of as part of w +- eps z, and eps is applied in fp32.
+// Relative error of a loss against fp64, two Llama blocks at 128 tokens: 4e-9 with GROUP_SCALE (few-token kernel 8e-9,
+// weights rounded after scaling 7e-8); of g, 6e-4 in all three.
+// GROUP_SCALE needs a third set of sums: it takes one block of 32 rows of W after the other (the operands of x are
+// read twice, the scales cost 64 instructions per chunk instead of 64 in the dequantisation) and holds half as much of x
+// in registers.  us per step, weights rounded after scaling -> scale in fp32: one Llama block with SZO_STEP_ONE_DENSE_PASS at 4096 tokens
+// 2182 -> 2126, four Llama blocks at 128 tokens 322 -> 316, eight OPT blocks at 64 325 -> 327, a 1024 x 4096 layer with
+// outputs at 300 tokens (20 workgroups: nothing stands behind the scaling of a chunk) 65.2 -> 66.9.
 #include <algorithm>
 #include <cstddef>
 #include <type_traits>
@@ -53,8 +62,9 @@ __device__ __forceinline__ FwdParams read_entry(table_words e) {
 }
 
 // `entry`: where p came from in a descriptor table, or null if it came with the launch.
-template <int DT, bool STORE_Y>
+template <int DT, bool STORE_Y, bool GROUP_SCALE>
 __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, table_words entry) {
+  static_assert(!GROUP_SCALE || DT == SZO_TILE_F16, "integer codes are fp16 operands");
   typedef typename Frag<DT>::type frag_t;
   // Fields that are rarely needed are read again where they are used (the laundered pointer keeps the loads there).
   auto cold = [&]() -> FwdParams {
@@ -98,31 +108,36 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     q[t][j] = *reinterpret_cast<global_u32x4>(lane_address(q_base + (size_t)k * 2048 + 1024 * j, q_lane));
     // group of columns 64 k + 32 half ..: with groups of 32 the two half waves read neighbouring groups
     const uint32_t h_off = gshift == 5 ? (uint32_t)half * 128u : 0u;
-    sc[t][j] = *reinterpret_cast<global_u16>(lane_address(s_base + (size_t)((k * 64) >> gshift) * 128 + 4 * j, s_lane + h_off));
+    if (!GROUP_SCALE) sc[t][j] = *reinterpret_cast<global_u16>(lane_address(s_base + (size_t)((k * 64) >> gshift) * 128 + 4 * j, s_lane + h_off));
+  };
+  auto load_group_scale = [&](int c, int j) {               // one per chunk: groups of 128
+    sc[0][j] = *reinterpret_cast<global_u16>(lane_address(s_base + (size_t)min(c, (ktiles >> 1) - 1) * 128 + 4 * j, s_lane));
   };
 
   // ---- activations: thread tid stages 16 bytes of rows (tid / 16) + 16 i ----
   const global_u8 x_base = (global_u8)(p.x + (size_t)m0 * K);
-  uint32_t x_lane[4];                                       // in bytes; 64 rows of K < 2^23 columns (checked on the host)
-#pragma unroll
-  for (int i = 0; i < 4; ++i) x_lane[i] = (uint32_t)min((tid >> 4) + 16 * i, p.M - 1 - m0) * (uint32_t)K * 2u;
-  u32x4 xr[4];
+  const uint32_t x_row = (uint32_t)(tid >> 4) * (uint32_t)K * 2u;      // in bytes; 64 rows of K < 2^23 columns (checked on the host)
+  const uint32_t x_last = (uint32_t)min(p.M - 1 - m0, OP_BM - 1) * (uint32_t)K * 2u;
+  constexpr int XP = GROUP_SCALE ? 2 : 4;                   // pieces of x in registers: half a chunk ahead, or a whole one
+  u32x4 xr[XP];
   const int x_col = 8 * (tid & 15);
   auto load_x = [&](int c, int i) {
     const uint32_t col = (uint32_t)min(OP_KC * c + x_col, K - 8) * 2u;
-    xr[i] = *reinterpret_cast<global_u32x4>(lane_address(x_base, x_lane[i] + col));
+    uint32_t row = x_row;                                   // (pinned: one register instead of one per piece)
+    if (GROUP_SCALE) asm volatile("" : "+v"(row));
+    xr[i % XP] = *reinterpret_cast<global_u32x4>(lane_address(x_base, min(row + (uint32_t)i * (uint32_t)K * 32u, x_last) + col));
   };
-  u32x4 xo;
+  u32x2 xo;
   auto clip_x = [&](int c) {                                // K an odd multiple of 64: the last chunk's second half is zero
     if (OP_KC * (c + 1) <= K) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < XP; ++i)
       if (OP_KC * c + x_col >= K) xr[i] = u32x4{0u, 0u, 0u, 0u};
   };
-  auto store_x_word = [&](int c, int i, int w) {            // word w of piece i; the fourth one writes the piece
-    xo[w] = stage_x_word<DT>(xr[i], w);
-    if (w == 3)
-      *reinterpret_cast<u32x4*>(smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + ((tid >> 4) + 16 * i) * OP_XROW + 16 * (tid & 15)) = xo;
+  auto store_x_word = [&](int c, int i, int w) {            // word w of piece i; every second one writes half the piece
+    xo[w & 1] = stage_x_word<DT>(xr[i % XP], w);
+    if (w & 1)
+      *reinterpret_cast<u32x2*>(smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + ((tid >> 4) + 16 * i) * OP_XROW + 16 * (tid & 15) + 8 * (w >> 1)) = xo;
   };
 
   float16_t acc[2][2], accz[2][2];                          // [block of 32 token rows][block of 32 rows of W]
@@ -139,10 +154,9 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   uint8_t* const hot = smem + OnePassLds::HOT + wave * 4096;                                  // [v, z][64 rows][16 slots]
   uint32_t* const pos = reinterpret_cast<uint32_t*>(smem + OnePassLds::POS) + wave * 16;      // byte of the column of each slot
   uint8_t* const sink = smem + OnePassLds::SINK + wave * 256 + 4 * lane;
-  auto tp_at = [&](int c) -> uint32_t {
-    return band_ok ? p.tile_ptr[(uint32_t)band * (uint32_t)ktiles + (uint32_t)min(2 * c, ktiles)] : 0u;
-  };
-  uint32_t tp0 = tp_at(0), tp1 = tp_at(1);
+  const table_words bounds = (table_words)(uintptr_t)(p.tile_ptr + (band_ok ? (size_t)band * (size_t)ktiles : 0));       // scalar loads
+  auto tp_at = [&](int c) -> uint32_t { return band_ok ? bounds[min(2 * c, ktiles)] : 0u; };
+  uint32_t j_lo = tp_at(0), j_hi = tp_at(1);                // entries of the chunk
   uint32_t w_hi = 0;                                        // entries below w_hi have been computed
   auto refill = [&]() {                                     // only reached when an entry of the band is wanted: nnz > 0
     const FwdParams pr = cold();
@@ -182,7 +196,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     // slots without an entry: a valid column, multiplied with zero
     *reinterpret_cast<uint32_t*>(lane < 16 ? (uint8_t*)(pos + lane) : sink) = mine ? (ent[1] & 0xFFu) : 0u;
   };
-  u32x4 gp[2], za[2], zb[2];
+  u32x4 gp[2], za[GROUP_SCALE ? 1 : 2], zb[2];              // (GROUP_SCALE: one block of token rows after the other)
   const uint32_t gather_base = (uint32_t)l31 * OP_XROW;
   auto group_pos = [&]() {
     gp[0] = *reinterpret_cast<const u32x4*>(pos + 8 * half);
@@ -196,7 +210,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   };
   auto group_pack = [&](int i) {
 #pragma unroll
-    for (int h = 0; h < 4; ++h) za[i][h] = (uint32_t)graw[2 * h] | ((uint32_t)graw[2 * h + 1] << 16);
+    for (int h = 0; h < 4; ++h) za[GROUP_SCALE ? 0 : i][h] = (uint32_t)graw[2 * h] | ((uint32_t)graw[2 * h + 1] << 16);
   };
   auto group_hot = [&](int which) {
 #pragma unroll
@@ -204,7 +218,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   };
   auto group_multiply = [&](int which, int i, int j) {
     float16_t& a = which ? accz[i][j] : acc[i][j];
-    a = Frag<DT>::mfma(__builtin_bit_cast(frag_t, za[i]), __builtin_bit_cast(frag_t, zb[j]), a);
+    a = Frag<DT>::mfma(__builtin_bit_cast(frag_t, za[GROUP_SCALE ? 0 : i]), __builtin_bit_cast(frag_t, zb[j]), a);
   };
   auto group_all = [&](int c, uint32_t g0, uint32_t g_end) {
     while (w_hi < min(g0 + 16u, g_end)) refill();
@@ -212,14 +226,15 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     group_put(g0, g_end);
     group_pos();
 #pragma unroll
-    for (int i = 0; i < 2; ++i) { group_gather(c, i); group_pack(i); }
+    for (int i = 0; i < 2; ++i) {
+      group_gather(c, i);
+      group_pack(i);
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      group_hot(which);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int which = 0; which < 2; ++which) {
+        group_hot(which);
 #pragma unroll
         for (int j = 0; j < 2; ++j) group_multiply(which, i, j);
+      }
     }
   };
 
@@ -227,7 +242,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   DequantConsts dqk;
   dqk.magic_lo = 0x64006400u; dqk.magic_hi = 0x54005400u;
   asm volatile("" : "+v"(dqk.magic_lo), "+v"(dqk.magic_hi));
-  u32x4 b[2][2];                                            // [parity of the step][block]
+  u32x4 b[2][2];                                            // [parity of the step][block]; GROUP_SCALE: one block at a time, in [.][0]
   auto dequant = [&](int step, int j, int part) {           // words 2 part, 2 part + 1 of the operand of step 0..7
     const int t = (step >> 2) & 1, c = step & 3;
     const _Float16 sh = __builtin_bit_cast(_Float16, (uint16_t)sc[t][j]);
@@ -239,10 +254,12 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
       half2_t hi = __builtin_bit_cast(half2_t, (src & 0x00F000F0u) | dqk.magic_hi);
       lo = lo - half2_t{(_Float16)1032.0f, (_Float16)1032.0f};
       hi = hi - half2_t{(_Float16)72.0f, (_Float16)72.0f};
-      lo = lo * half2_t{sh, sh};
-      hi = hi * half2_t{sh, sh};
-      b[step & 1][j][2 * part] = __builtin_bit_cast(uint32_t, lo);
-      b[step & 1][j][2 * part + 1] = __builtin_bit_cast(uint32_t, hi);
+      if (!GROUP_SCALE) {
+        lo = lo * half2_t{sh, sh};
+        hi = hi * half2_t{sh, sh};
+      }
+      b[step & 1][GROUP_SCALE ? 0 : j][2 * part] = __builtin_bit_cast(uint32_t, lo);
+      b[step & 1][GROUP_SCALE ? 0 : j][2 * part + 1] = __builtin_bit_cast(uint32_t, hi);
     } else {
 #pragma unroll
       for (int w = 2 * part; w < 2 * part + 2; ++w)
@@ -257,7 +274,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
 
   // ---- prologue ----
 #pragma unroll
-  for (int i = 0; i < 4; ++i) load_x(0, i);
+  for (int i = 0; i < XP; ++i) load_x(0, i);
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -266,41 +283,50 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   *reinterpret_cast<u32x4*>(hot + 1024 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
   *reinterpret_cast<u32x4*>(hot + 2048 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
   *reinterpret_cast<u32x4*>(hot + 3072 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
-  w_hi = __builtin_amdgcn_readfirstlane(tp0) & ~3u;
-  clip_x(0);
+  w_hi = j_lo & ~3u;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if (!GROUP_SCALE && i == 0) clip_x(0);
 #pragma unroll
     for (int w = 0; w < 4; ++w) store_x_word(0, i, w);
-    load_x(min(1, nchunks - 1), i);
+    load_x(i + XP < 4 ? 0 : min(1, nchunks - 1), (i + XP) & 3);
   }
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < 2; ++j) {
+    if (GROUP_SCALE) load_group_scale(0, j);
 #pragma unroll
-    for (int part = 0; part < 2; ++part) dequant(0, j, part);
+    for (int part = 0; part < 2; ++part) if (!GROUP_SCALE || j == 0) dequant(0, j, part);
+  }
   __syncthreads();
 
   // ---- chunks of 128 columns: 8 steps of 16 columns x 4 matrix instructions.  Behind every instruction stands a share of
   //      the work for later: the next step's operands, the next chunk's activations, the entries' operands ----
   for (int c = 0; c < nchunks; ++c) {
-    const uint32_t tp2 = tp_at(c + 2);
-    const uint32_t j_lo = __builtin_amdgcn_readfirstlane(tp0), j_hi = __builtin_amdgcn_readfirstlane(tp1);
+    const uint32_t j_next = tp_at(c + 2);
     while (w_hi < min(j_lo + 16u, j_hi)) refill();
 #pragma unroll
     for (int i = 0; i < 2; ++i) read_a(c, 0, i);
     group_read(j_lo);
-#pragma unroll
-    for (int step = 0; step < 8; ++step) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = u & 1, j = u >> 1, s = 4 * step + u;
-        acc[i][j] = Frag<DT>::mfma(a[step & 1][i], __builtin_bit_cast(frag_t, b[step & 1][j]), acc[i][j]);
-        if (step < 7 && u < 2) read_a(c, step + 1, u);
-        // next step's weights: block 0 behind the first two instructions, block 1 behind the others
-        dequant(step + 1, u >> 1, u & 1);
-        if ((step & 3) == 2 && (u & 1)) load_q(c + 1, step >> 2, u >> 1);        // the tile's last word has been taken
-        if (s == 4) group_put(j_lo, j_hi);
-        if (s == 8) group_pos();
+    auto behind = [&](int s) {                              // what stands behind matrix instruction s of 32
+      if (s == 4) group_put(j_lo, j_hi);
+      if (s == 8) group_pos();
+      if (GROUP_SCALE) {
+        if (s == 11) group_gather(c, 0);
+        if (s == 13) group_hot(0);
+        if (s == 14) group_pack(0);
+        if (s == 15 || s == 16) group_multiply(0, 0, s - 15);
+        if (s == 17) { group_hot(1); group_gather(c, 1); }
+        if (s == 20 || s == 21) group_multiply(1, 0, s - 20);
+        if (s == 22) { group_hot(0); group_pack(1); }
+        if (s == 25 || s == 26) group_multiply(0, 1, s - 25);
+        if (s == 27) group_hot(1);
+        if (s == 30 || s == 31) group_multiply(1, 1, s - 30);
+        if (s & 8) {                                        // next chunk's x: pieces 0, 1 behind 8..15, pieces 2, 3 behind 24..31
+          const int i = (s >> 4) * 2 + ((s >> 2) & 1);
+          store_x_word(c + 1, i, s & 3);
+          if ((s & 3) == 3) load_x(min(s < 16 ? c + 1 : c + 2, nchunks - 1), i ^ 2);
+        }
+      } else {
         if (s == 12) group_gather(c, 0);
         if (s == 15) group_pack(0);
         if (s == 16) group_gather(c, 1);
@@ -314,11 +340,57 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
           store_x_word(c + 1, (s - 16) >> 2, s & 3);
           if ((s & 3) == 3) load_x(min(c + 2, nchunks - 1), (s - 16) >> 2);
         }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (GROUP_SCALE) {
+      // Groups of 128 = one chunk: the products with the integer codes are summed for one block of rows of W at a time,
+      // and the sums take the group's scale in fp32.
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        float16_t part[2];
+#pragma unroll
+        for (int step = 0; step < 8; ++step) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            float16_t zero;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+            part[i] = Frag<DT>::mfma(a[step & 1][i], __builtin_bit_cast(frag_t, b[step & 1][0]), step == 0 ? zero : part[i]);
+            if (j == 0 || step < 7) read_a(c, (step + 1) & 7, i);
+            if (step < 7) dequant(step + 1, j, i); else dequant(8, j ^ 1, i);
+            if ((step & 3) == 2 && i == 1) load_q(c + 1, step >> 2, j);
+            behind(16 * j + 2 * step + i);
+          }
+        }
+        const float scale = (float)__builtin_bit_cast(_Float16, (uint16_t)sc[0][j]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = fmaf(part[i][r], scale, acc[i][j][r]);
+        // the sums are done before the next ones begin: there are no registers for a third set
+        asm volatile("" : "+v"(acc[0][j]), "+v"(acc[1][j]), "+v"(b[0][0]));
+        load_group_scale(c + 1, j);
         __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int step = 0; step < 8; ++step) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = u & 1, j = u >> 1;
+          acc[i][j] = Frag<DT>::mfma(a[step & 1][i], __builtin_bit_cast(frag_t, b[step & 1][j]), acc[i][j]);
+          if (step < 7 && u < 2) read_a(c, step + 1, u);
+          // next step's weights: block 0 behind the first two instructions, block 1 behind the others
+          dequant(step + 1, u >> 1, u & 1);
+          if ((step & 3) == 2 && (u & 1)) load_q(c + 1, step >> 2, u >> 1);        // the tile's last word has been taken
+          behind(4 * step + u);
+        }
       }
     }
     for (uint32_t g0 = j_lo + 16u; g0 < j_hi; g0 += 16u) group_all(c, g0, j_hi);
-    tp0 = tp1; tp1 = tp2;
+    j_lo = j_hi;
+    j_hi = j_next;
     __syncthreads();                                        // next chunk's x complete, this one's no longer read
   }
 
@@ -449,8 +521,12 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   }
 }
 
+// Which forms of the body a kernel holds: the launches over layers of one kind, i.e. almost all of them, take a kernel with
+// that one alone.
+constexpr int kNoGroups128 = 0, kAllGroups128 = 1, kSomeGroups128 = 2;
+
 // Every layer of a step in one grid: `table` holds one entry per layer, ordered by first_block (a multiple of 8).
-template <int DT, bool STORE_Y>
+template <int DT, bool STORE_Y, int GROUPS>
 __global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const FwdParams* table, int n_entries) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
   const table_words tab = (table_words)table;
@@ -462,13 +538,16 @@ __global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const F
   const FwdParams p = read_entry(tab + first * W);
   const int bid = (int)blockIdx.x - p.first_block;
   if (bid >= p.grid_m * p.grid_n) return;
-  onepass_body<DT, STORE_Y>(p, bid, tab + first * W);
+  if constexpr (GROUPS == kAllGroups128) onepass_body<DT, STORE_Y, true>(p, bid, tab + first * W);
+  else if constexpr (GROUPS == kNoGroups128) onepass_body<DT, STORE_Y, false>(p, bid, tab + first * W);
+  else if (p.group_shift == 7) onepass_body<DT, STORE_Y, true>(p, bid, tab + first * W);
+  else onepass_body<DT, STORE_Y, false>(p, bid, tab + first * W);
 }
 
 // One layer, its descriptor in the kernel arguments.
-template <int DT>
+template <int DT, int GROUPS>
 __global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_kernel(FwdParams p) {
-  onepass_body<DT, false>(p, (int)blockIdx.x, nullptr);
+  onepass_body<DT, false, GROUPS == kAllGroups128>(p, (int)blockIdx.x, nullptr);
 }
 
 // ---- host side -----------------------------------------------------------------------------
@@ -483,15 +562,22 @@ static int launch(Kernel kern, std::atomic<uint64_t>& lds_limit_set, int64_t blo
   SZO_LAUNCH_CHECK();
   return timing_end(stream);
 }
-template <int DT, bool STORE_Y>
+template <int DT, bool STORE_Y, int GROUPS>
 static int launch_table(const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
   static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
-  return launch(onepass_table_kernel<DT, STORE_Y>, lds_limit_set, blocks, stream, table_dev, entries);
+  return launch(onepass_table_kernel<DT, STORE_Y, GROUPS>, lds_limit_set, blocks, stream, table_dev, entries);
 }
-template <int DT>
+template <bool STORE_Y>
+static int launch_table(bool bf16, int groups, const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
+  if (bf16) return launch_table<SZO_TILE_BF16, STORE_Y, kNoGroups128>(table_dev, entries, blocks, stream);
+  if (groups == kNoGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kNoGroups128>(table_dev, entries, blocks, stream);
+  if (groups == kAllGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kAllGroups128>(table_dev, entries, blocks, stream);
+  return launch_table<SZO_TILE_F16, STORE_Y, kSomeGroups128>(table_dev, entries, blocks, stream);
+}
+template <int DT, int GROUPS>
 static int launch_one(const FwdParams& p, hipStream_t stream) {
   static std::atomic<uint64_t> lds_limit_set{0};
-  return launch(onepass_kernel<DT>, lds_limit_set, (int64_t)p.grid_m * p.grid_n, stream, p);
+  return launch(onepass_kernel<DT, GROUPS>, lds_limit_set, (int64_t)p.grid_m * p.grid_n, stream, p);
 }
 
 static int g_force_onepass = 0;                             // testing hook: 1 = wherever the kernel can, -1 = never
@@ -593,7 +679,8 @@ int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float ep
   const int rc = fill_tiled(p, d, seed, step, eps, plus, minus);
   if (rc != SZO_OK) return rc;
   if (onepass_tiles(d) > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
-  return d->tile_dtype == SZO_TILE_F16 ? launch_one<SZO_TILE_F16>(p, stream) : launch_one<SZO_TILE_BF16>(p, stream);
+  if (d->tile_dtype == SZO_TILE_BF16) return launch_one<SZO_TILE_BF16, kNoGroups128>(p, stream);
+  return d->group == 128 ? launch_one<SZO_TILE_F16, kAllGroups128>(p, stream) : launch_one<SZO_TILE_F16, kNoGroups128>(p, stream);
 }
 
 int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
@@ -625,10 +712,10 @@ int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;
   const FwdParams* t = (const FwdParams*)table_dev;
-  const int e = (int)table.size();
-  if (descs[order[0]].tile_dtype == SZO_TILE_F16)
-    return store_y ? launch_table<SZO_TILE_F16, true>(t, e, first_block, stream) : launch_table<SZO_TILE_F16, false>(t, e, first_block, stream);
-  return store_y ? launch_table<SZO_TILE_BF16, true>(t, e, first_block, stream) : launch_table<SZO_TILE_BF16, false>(t, e, first_block, stream);
+  const int e = (int)table.size(), with = (int)std::count_if(table.begin(), table.end(), [](const FwdParams& p) { return p.group_shift == 7; });
+  const int groups = with == e ? kAllGroups128 : with == 0 ? kNoGroups128 : kSomeGroups128;
+  const bool bf16 = descs[order[0]].tile_dtype == SZO_TILE_BF16;
+  return store_y ? launch_table<true>(bf16, groups, t, e, first_block, stream) : launch_table<false>(bf16, groups, t, e, first_block, stream);
 }
 
 }  // namespace szo

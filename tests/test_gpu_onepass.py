@@ -120,3 +120,19 @@ def test_chosen_for_a_step_of_some_hundred_tokens_and_bit_reproducible():
     o, d = make_pair(421, 500, 2048, 512, 128, 1e-3)
     szo.szo_zo_step_noalloc([d.desc(with_y=False)], 9, 0, 1e-3, 1e-3, scal)
     assert np.allclose(scal.cpu().numpy()[:2], outs[0][0][:2], rtol=1e-12, atol=0.0)
+
+
+@pytest.mark.parametrize("flags", [0, szo.STEP_FUSED_LOSS, szo.STEP_FUSED_LOSS | szo.STEP_ONE_DENSE_PASS])
+@pytest.mark.parametrize("M,N,K", [(64, 256, 4096), (65, 200, 384), (129, 70, 128)])
+def test_groups_of_128_take_their_scale_in_fp32(M, N, K, flags):
+    """No rounding of the dense weights: what is left are fp32 sums of K products, 2^-24 sqrt(K) relative at most for the
+    outputs (weights rounded to fp16 after scaling: 1.7e-4) and, averaged over the outputs, far less for the losses."""
+    o, d = make_pair(431, M, N, K, 128, 0.0)
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_set_tile_config(11)
+    szo.szo_zo_step([d.desc(with_y=flags == 0)], 9, 0, 1e-3, 0.0, scal, szo.new_workspace(), flags)
+    want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, 128, o.sp_idx, o.sp_val)
+    if flags == 0:
+        assert rel_fro(d.y.cpu().numpy(), want) <= 2.0 ** -24 * np.sqrt(K)
+    loss = olayer.mse_loss(want, o.target_bits)
+    assert np.all(np.abs(scal.cpu().numpy()[:2] - loss) <= 1e-7 * loss)
