@@ -421,7 +421,9 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   const int ml0 = 4 * half, nl0 = wave * 64 + l31;
   const uint8_t* const trow = smem + ml0 * OP_TROW + nl0 * 2;
   // Without y: with d = D - t the losses are sum d^2 +- 2 eps sum d Z + eps^2 sum Z^2, and their difference, which g
-  // is made of, is summed as such instead of being left over from two nearly equal sums.
+  // is made of, is summed as such instead of being left over from two nearly equal sums.  Squares and products are exact and
+  // are added one by one in fp64 (as in the few-token kernels; sixteen at a time in fp32
+  // first is no faster: four Llama blocks at 128 tokens 305 against 306 us per step, one block at 4096 on request 2037 against 2041).
   double loss_plus = 0.0, loss_minus = 0.0, sum_dd = 0.0, sum_dz = 0.0, sum_zz = 0.0;
   uint8_t* const special = smem + OnePassLds::RING;         // AGAIN: token rows that are left out
   auto finish = [&](auto full_tag, auto staged_tag, auto again_tag) {
@@ -431,7 +433,6 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        float dd = 0.0f, dz = 0.0f, zz = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int dm = 32 * i + 8 * (r >> 2) + (r & 3), dn = 32 * j;
@@ -448,14 +449,13 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
               loss_plus = fma(dp, dp, loss_plus);
               loss_minus = fma(dmn, dmn, loss_minus);
             } else {
-              const float d = acc[i][j][r] - t, z = accz[i][j][r];
-              dd = fmaf(d, d, dd);
-              dz = fmaf(d, z, dz);
-              zz = fmaf(z, z, zz);
+              const double d = (double)(acc[i][j][r] - t), z = (double)accz[i][j][r];
+              sum_dd = fma(d, d, sum_dd);
+              sum_dz = fma(d, z, sum_dz);
+              sum_zz = fma(z, z, sum_zz);
             }
           }
         }
-        if (!STORE_Y && !AGAIN) { sum_dd += (double)dd; sum_dz += (double)dz; sum_zz += (double)zz; }
       }
   };
   using T = std::true_type;

@@ -136,3 +136,15 @@ def test_groups_of_128_take_their_scale_in_fp32(M, N, K, flags):
         assert rel_fro(d.y.cpu().numpy(), want) <= 2.0 ** -24 * np.sqrt(K)
     loss = olayer.mse_loss(want, o.target_bits)
     assert np.all(np.abs(scal.cpu().numpy()[:2] - loss) <= 1e-7 * loss)
+
+
+@pytest.mark.parametrize("G", [128, 64])
+def test_squares_are_added_in_fp64(G):
+    """Zero weights: the differences are the bf16 targets, their squares exact, and the loss is their mean to fp64."""
+    o, d = make_pair(441, 70, 300, 256, G, 0.0)
+    d.qweight.fill_(0x88)
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_set_tile_config(11)
+    szo.szo_zo_step([d.desc(with_y=False)], 9, 0, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+    want = float((d.target.double() ** 2).mean().item())
+    assert np.all(np.abs(scal.cpu().numpy()[:2] - want) <= 1e-13 * want)      # 21 000 terms, fp64: 2^-53 sqrt(21 000) = 2e-14
