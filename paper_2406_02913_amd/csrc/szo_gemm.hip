@@ -1023,7 +1023,7 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
   int64_t T = 0;
   for (int attempt = 0; attempt < 2; ++attempt) {
     compact = attempt == 1;
-    few_all = few_token_enabled() && small_m_eligible(descs, n, false, true) && (!compact || small_m_eligible(descs, n, true, true));
+    few_all = few_token_enabled() && small_m_eligible(descs, n, false, true, 2) && (!compact || small_m_eligible(descs, n, true, true, 2));
     T = 0;
     for (int i = 0; i < n; ++i) {     // reject everything before anything is enqueued
       const szo_linear_desc* d = &descs[i];
@@ -1042,7 +1042,7 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
   // ... or, where the tiled kernel would run, the one-dense-pass kernel under szo_zo_step's conditions, if its partials fit.
   // (Not in place of the few-token path: launched layer by layer it does not fill the chip; one OPT block at 405 tokens
   // 465 us with the few-token kernels, 479 with this one.)
-  int64_t one_T = few_token_enabled() && small_m_eligible(descs, n, false, true) ? 0 : onepass_partials(descs, n, false, false, false);
+  int64_t one_T = few_token_enabled() && small_m_eligible(descs, n, false, true, 2) ? 0 : onepass_partials(descs, n, false, false, false, true);
   if (2 * one_T > kNoAllocMaxPartials) one_T = 0;
   if (one_T) T = one_T;
   if (2 * T > kNoAllocMaxPartials) return SZO_EUNSUPPORTED;
@@ -1090,7 +1090,7 @@ int szo_linear_fwd(const szo_linear_desc* desc, uint64_t seed, uint64_t step, in
   const int rc = validate_desc(desc, sign, true, false);
   if (rc != SZO_OK) return rc;
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
-  if (few_token_enabled() && small_m_eligible(desc, 1, false, false))
+  if (few_token_enabled() && small_m_eligible(desc, 1, false, false, 1))
     return small_m_launch_one(desc, seed, step, sign == 0 ? 0.0f : eps, sign == 0 ? 1 : sign, false, nullptr, nullptr,
                               false, (hipStream_t)stream);
   return run_forward(desc, seed, step, sign, eps, nullptr, 0.0, (hipStream_t)stream);
@@ -1104,7 +1104,7 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
   // the few-token kernels compute both signs at once: make the requested one the "+" forward.  Their scale is that of a
   // step's loss, and both signs' partials have to fit.
-  const bool few = few_token_enabled() && small_m_eligible(desc, 1, false, false) && scale == 1.0 / ((double)desc->M * (double)desc->N);
+  const bool few = few_token_enabled() && small_m_eligible(desc, 1, false, false, 1) && scale == 1.0 / ((double)desc->M * (double)desc->N);
   const int64_t nb = few ? small_m_partials(desc) : 0;
   if (few && 2 * nb <= kMaxLossPartials) {
     rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, partial_area(workspace),
@@ -1145,11 +1145,11 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   // Few-token stacks: one pass over the weights serves both forwards of the step.
   // SZO_STEP_ONE_DENSE_PASS: the caller asks for that path at any token count.
   const bool few = fuse && few_token_enabled() && n <= kMaxStepMatrices &&
-                   small_m_eligible(descs, n, (flags & SZO_STEP_ONE_DENSE_PASS) != 0, false);
+                   small_m_eligible(descs, n, (flags & SZO_STEP_ONE_DENSE_PASS) != 0, false, 2);
   // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip).
   {
     int64_t T = 0;
-    rc = onepass_forwards(descs, n, seed, step, eps, few && small_m_eligible(descs, n, false, false),
+    rc = onepass_forwards(descs, n, seed, step, eps, few && small_m_eligible(descs, n, false, false, 2),
                           (flags & SZO_STEP_ONE_DENSE_PASS) != 0, !fuse, (char*)workspace + kWorkspaceTableOffset,
                           partial_area(workspace), &T, s);
     if (rc == SZO_OK) return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);

@@ -47,8 +47,13 @@ int reduce_step(const double* partials, int count, float eps, double* scalars, h
 
 // Few-token path (szo_smallm.hip, szo_split.hip).
 // Whether every layer of a launch is taken: few enough tokens to run as slices of 16 or more token rows, or, with
-// any_token_count, a shape that the stream kernel takes whatever its number of tokens.
-bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool one_set_only);
+// any_token_count, a shape that the stream kernel takes whatever its number of tokens.  `forwards`: 2 for a step, 1 for the
+// single-forward calls (what the tiled kernel would have to do instead).  `separate`: one launch per layer; a step of such
+// launches takes no second activation set.
+bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool separate, int forwards);
+// Estimated us of a step's forwards, up to 128 tokens, where the stream kernel does not take every layer: on the few-token path
+// (`few`) or in the tiled kernel.
+double small_m_rounded_us(const szo_linear_desc* descs, int n, bool few, bool separate);
 int64_t small_m_partials(const szo_linear_desc* d, bool compact = false);   // loss partials per sign of a single-matrix launch;
                                                             // compact: of the stream kernel, which makes fewer of them
 void small_m_force_split(int how);                          // testing hook: 1 = the split kernel always, -1 = only where nothing else can, 0 = choose
@@ -67,8 +72,8 @@ constexpr int kInlineMats = 8;                              // matrices whose ta
 int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
                      bool store_y, void* table_dev, double* partials, int64_t* partials_per_sign, hipStream_t stream);
 // The same for callers without a table: how many loss partials per sign the step has if it takes this kernel (0: it does
-// not), and one layer's launch.
-int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y);
+// not), and one layer's launch.  `separate`: every layer is a launch of its own.
+int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y, bool separate);
 int64_t onepass_tiles(const szo_linear_desc* d);            // loss partials per sign of one layer
 int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, double* plus, double* minus, hipStream_t stream);
 void onepass_force(int how);                                // testing hook: 1 = wherever the kernel can, -1 = never, 0 = choose

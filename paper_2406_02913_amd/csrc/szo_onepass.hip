@@ -580,6 +580,10 @@ static int launch_one(const FwdParams& p, hipStream_t stream) {
   return launch(onepass_kernel<DT, GROUPS>, lds_limit_set, (int64_t)p.grid_m * p.grid_n, stream, p);
 }
 
+int64_t onepass_tiles(const szo_linear_desc* d) {
+  return ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
+}
+
 static int g_force_onepass = 0;                             // testing hook: 1 = wherever the kernel can, -1 = never
 void onepass_force(int how) { g_force_onepass = how; }
 
@@ -591,7 +595,9 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    tokens (416 / 624) 153 / 256 -> 204 / 214; 32 OPT blocks at 64 / 224 tokens 1531 / 5697 -> 1241 / 4334.
 //    Not up to 64 tokens where the longest K (12 us per 1024 columns here, 7 there) outlasts everything else: four OPT
 //    blocks at 64 tokens 214 -> 241.  Where the few-token path has only its split kernel (bf16 tile, K an odd multiple of
-//    64): four Llama blocks with the bf16 tile at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393.
+//    64): four Llama blocks with the bf16 tile at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393; there, and against
+//    the 128-row tiles that such layers run on otherwise, both paths are estimated from sizes and density (fitted with
+//    split_rounded_us): one OPT block at 128 tokens and 0.1 / 0.7 / 1 %, tiles -> this one 379 / 437 / 463 -> 253 / 473 / 568.
 //  * against the tiled kernel, up to kOnePassTokens tokens unless the caller asks for it: beyond that a step is two full
 //    forwards per layer by default, the products of the single-layer calls.  The two differ by what a row of tiles
 //    costs: a unit of 64 token rows here takes 1 + 108 rho
@@ -602,7 +608,7 @@ void onepass_force(int how) { g_force_onepass = how; }
 //  * with the outputs written (flags = 0) the other path is two tiled launches and two passes over y per layer: one Llama
 //    block at 1 / 256 / 1024 tokens 1044 / 1063 / 1508 -> 150 / 189 / 621; rho = 0.01, 1024 tokens: 1836 -> 1128.
 constexpr int64_t kOnePassTokens = 512;
-static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y) {
+static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y, bool separate) {
   int64_t wgs = 0, most_tokens = 0;
   double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0, wg_k = 0.0, longest_k = 0.0;
   bool stream = true;
@@ -610,9 +616,8 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
     const double size = (double)d->N * (double)d->K;
-    const int64_t tiles = ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
-    wgs += tiles;
-    wg_k += (double)tiles * (double)d->K;
+    wgs += onepass_tiles(d);
+    wg_k += (double)onepass_tiles(d) * (double)d->K;
     longest_k = std::max(longest_k, (double)d->K);
     most_tokens = std::max<int64_t>(most_tokens, d->M);
     weights += size;
@@ -623,9 +628,15 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
   }
   const double rho = entries / weights;
   if (store_y) return wgs >= 4 && rho <= 0.015;
-  if (few && wgs < 512) return !stream && most_tokens > 64 && wgs >= 256;
-  if (few) return most_tokens > (stream ? 32 : 16) && (!stream || most_tokens > 64 || 205.0 * longest_k <= wg_k);
-  if (wgs < (most_tokens <= 128 ? 256 : 32)) return false;
+  if (few && (wgs < 512 ? stream || most_tokens <= 64 || wgs < 256 : most_tokens <= (stream ? 32 : 16))) return false;
+  if (few && stream) return most_tokens > 64 || 205.0 * longest_k <= wg_k;
+  if (!few && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
+  if (!stream && most_tokens <= 128) {
+    const double k = longest_k / 1024.0;
+    const double us = 26.6 + 3.5 * k + std::max(9.3 * k * (1.0 + 176.0 * rho), 0.0221 * wg_k / 1024.0 * (1.0 + 42.0 * rho));
+    if (us >= small_m_rounded_us(descs, n, few, separate)) return false;
+    if (few) return true;
+  }
   return asked_for || (most_tokens <= kOnePassTokens && (1.0 + 108.0 * rho) * here < 1.42 * tiled);
 }
 
@@ -645,12 +656,8 @@ static bool outputs_overlap(const szo_linear_desc* descs, int n) {
   return false;
 }
 
-int64_t onepass_tiles(const szo_linear_desc* d) {
-  return ((d->M + OP_BM - 1) / OP_BM) * ((d->N + OP_BN - 1) / OP_BN);
-}
-
 // Loss partials per sign of the step if it takes this kernel, 0 if not.
-int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y) {
+int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y, bool separate) {
   if (g_force_onepass < 0) return 0;
   int64_t T = 0;
   const szo_linear_desc* any = nullptr;
@@ -662,7 +669,7 @@ int64_t onepass_partials(const szo_linear_desc* descs, int n, bool few, bool ask
     any = d;
     T += onepass_tiles(d);
   }
-  if (T == 0 || (g_force_onepass == 0 && !worth_it(descs, n, few, asked_for, store_y))) return 0;
+  if (T == 0 || (g_force_onepass == 0 && !worth_it(descs, n, few, asked_for, store_y, separate))) return 0;
   return store_y && outputs_overlap(descs, n) ? 0 : T;
 }
 
@@ -685,7 +692,7 @@ int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float ep
 
 int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
                      bool store_y, void* table_dev, double* partials, int64_t* partials_per_sign, hipStream_t stream) {
-  const int64_t T = onepass_partials(descs, n, few, asked_for, store_y);
+  const int64_t T = onepass_partials(descs, n, few, asked_for, store_y, false);
   if (T == 0 || 2 * T > kMaxLossPartials) return SZO_EUNSUPPORTED;
   static thread_local std::vector<int> order;
   order.clear();

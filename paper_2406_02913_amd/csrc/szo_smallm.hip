@@ -543,19 +543,33 @@ static size_t small_lds_bytes(int r) {
 static int64_t bands_of(const szo_linear_desc* d) { return (d->N + 63) / 64; }
 static int64_t strips_of(const szo_linear_desc* d) { return (d->N + SM_BN - 1) / SM_BN; }
 
-// What one launch consists of: how many workgroups it would have with 16 token rows per pass, as 256-column strips
-// and as 64-row bands.
+// What one launch consists of, as the rules below need it: sums over its matrices, K in units of 1024, entries in
+// thousands.  A slice is 16 token rows.
 struct LaunchShape {
-  int64_t strips16 = 0, bands16 = 0;
-  double band_k = 0.0, longest_k = 0.0;                     // K summed over those bands, longest K, in units of 1024
+  int64_t strips16 = 0, bands16 = 0;                        // 256-column strips and 64-row bands, times slices
+  double band_k = 0.0, longest_k = 0.0;                     // K summed over those bands, longest K
+  double slice_entries = 0.0, row_entries = 0.0;            // sensitive entries times slices, times token rows / 16
+  double entries = 0.0, weights = 0.0, sum_k = 0.0;
+  int64_t matrices = 0, tiles128 = 0;                       // 128 x 128 output tiles
+  double tile_k = 0.0;                                      // K summed over those tiles
   void add(const szo_linear_desc* d) {
     if (d->M <= 0 || d->N <= 0) return;
-    const int64_t slices = (d->M + SM_ROWS - 1) / SM_ROWS;
+    const int64_t slices = (d->M + SM_ROWS - 1) / SM_ROWS, tiles = ((d->M + 127) / 128) * ((d->N + 127) / 128);
+    const double k = (double)d->K / 1024.0, nnz = (double)d->nnz * 1e-3;
     strips16 += strips_of(d) * slices;
     bands16 += bands_of(d) * slices;
-    band_k += (double)(bands_of(d) * slices) * (double)d->K / 1024.0;
-    longest_k = std::max(longest_k, (double)d->K / 1024.0);
+    band_k += (double)(bands_of(d) * slices) * k;
+    longest_k = std::max(longest_k, k);
+    slice_entries += nnz * (double)slices;
+    row_entries += nnz * (double)d->M / SM_ROWS;
+    entries += nnz;
+    weights += (double)d->N * (double)d->K;
+    sum_k += k;
+    ++matrices;
+    tiles128 += tiles;
+    tile_k += (double)tiles * k;
   }
+  double percent() const { return weights > 0.0 ? 1e5 * entries / weights : 0.0; }      // sensitive weights, in percent
 };
 
 // The stream kernel (small_m_kernel) needs whole 128-column blocks, the fp16 tile and 32-bit code offsets; the split
@@ -604,18 +618,25 @@ struct FewPlan {
 };
 
 // Whether a launch takes the split kernel.  The stream kernel's time is the chain of its longest K, which the split
-// shortens, plus its share of the work; the split kernel pays for the sums of every band instead.  The two lines below
-// are fitted to single layers of 2048..16384 rows x 512..16384 columns at 16..200 tokens and to whole blocks, and were
-// right to 10 % in all of them.  us per step, split / stream: 16384 x 2048 at 16 / 64 / 128 tokens 18 / 34 / 52 against 26 / 27 /
-// 34, 16384 x 16384 at 16 / 64 / 128 tokens 39 / 109 / 199 against 125 / 130 / 179, 4096 x 512 at 64 / 200 tokens 14 / 20
-// against 16 / 17; one / two / four OPT blocks at 16 tokens 47 / 66 / 125 against 130 / 134 / 158, one Llama block at 64
-// tokens 92 against 100.  Look-ups (table format) and two activation sets cost more per unit in the split kernel: one Llama
-// block at 16 / 32 / 48 tokens with tables 61 / 108 / 164 against 143 / 145 / 147, with two sets at 16 / 32 65 / 115
-// against 113 / 118.
-static bool split_pays(const LaunchShape& launch, bool dual, bool lut) {
-  const double split = 0.012 * (double)launch.bands16 + 0.0058 * launch.band_k;
-  const double stream = 6.9 * launch.longest_k + 0.0026 * launch.band_k;
-  return split * (dual ? 1.65 : lut ? 1.25 : 1.0) <= stream;
+// shortens, plus its share of the work; the split kernel pays for the sums of every band.  A mask of more than 0.1 % adds to
+// both: the split kernel fetches the columns of x of every sensitive entry from memory, for every token row, where the
+// stream kernel reads them from the staged x, one after the other along its chain.  Fitted to steps over single layers of
+// 512..16384 rows x 512..16384 columns and one to four blocks, 1..448 tokens, 0.01..1 %, spread evenly and half in 1 % of the
+// rows: the choice costs 0.2..0.7 % on average, and is up to 20 % slower than the stream kernel in 9 of 1948 cases (16384 x 4096
+// at 40 tokens and 1 %: its last slice is half empty), where the rule without the mask was up to 33 % slower in 48.
+// us per step, split against stream: 16384 x 2048 at 16 / 64 / 128 tokens 18 / 34 / 52 against 26 / 27 / 34; one / two / four
+// OPT blocks at 16 tokens 47 / 66 / 125 against 130 / 134 / 158; one Llama block at 64 tokens and 0.01 / 0.1 / 0.4 / 1 %
+// 76 / 89 / 155 / 297 against 90 / 98 / 142 / 223; four Mistral blocks at 1 % at 1 / 16 tokens 222 / 393 against 308 / 326.
+// With groups of 32 and 64 the stream kernel loads its scales where it needs them; look-ups (table format) and two activation
+// sets cost more per unit in the split kernel: three Llama blocks at 16 tokens with tables 165 against 145, one Mistral block
+// with two sets at 16 / 32 tokens 70 / 116 against 134 / 139.
+static bool split_pays(const LaunchShape& launch, bool dual, bool lut, bool plain) {
+  const double percent = launch.percent(), over = std::max(percent - 0.1, 0.0), share = percent > 0.0 ? over / percent : 0.0;
+  const double split = (lut ? 0.018 : 0.012) * (dual ? 1.65 : 1.0) * (double)launch.bands16 +
+                       (lut ? 0.0068 : 0.0058) * (dual ? 1.65 : 1.0) * launch.band_k +
+                       (0.012 * launch.row_entries + 0.008 * launch.slice_entries) * share * (dual ? 2.0 : 1.0);
+  const double stream = ((plain ? 12.9 : 6.9) + 8.0 * over) * launch.longest_k + 0.0026 * launch.band_k;
+  return split <= stream;
 }
 static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, bool dual, bool compact = false) {
   FewPlan p;
@@ -623,7 +644,7 @@ static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, boo
   else if (d->tile_dtype == SZO_TILE_BF16) p.dequant = D_TILE_BF16;
   else if (!stream_ok(d)) p.dequant = D_TILE_F16;
   else p.dequant = d->group == 128 ? D_FAST : D_PLAIN;
-  bool split = split_pays(launch, dual, p.dequant == D_LUT);
+  bool split = split_pays(launch, dual, p.dequant == D_LUT, p.dequant == D_PLAIN);
   if (g_force_split) split = g_force_split > 0;
   if (g_force_rblocks || compact) split = false;
   if (!stream_ok(d)) split = true;
@@ -696,11 +717,24 @@ static int launch_plan(const FewPlan& p, int64_t units, int slices, int64_t long
 // ceil(M/32) stays below 7.5 ceil(M/256), e.g. up to 224 tokens and from 257 to 448; beyond 15 such
 // slices the tiled kernel is the default (SZO_STEP_ONE_DENSE_PASS overrides that).
 constexpr int kSmallMaxSlices = 15;
-// Uniform layers that only the split kernel takes (bf16 tile, K an odd multiple of 64), against 128x128 tiles in one
-// grouped launch.  Measured with the bf16 tile, us per step: one Llama block at 16 / 64 / 128 tokens 62 / 134 / 302
-// against 371 / 375 / 379, sixteen blocks 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where
-// the tiles would leave the chip idle.
+// Uniform layers that only the split kernel takes (bf16 tile, K an odd multiple of 64), against 128x128 tiles.  Measured with
+// the bf16 tile, us per step: one Llama block at 16 / 64 / 128 tokens 62 / 134 / 302 against 371 / 375 / 379, sixteen blocks
+// 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where the tiles would leave the chip idle.
 constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTokensSmallLaunch = 128;
+// Inside these limits both are estimated: the split kernel by its bands and their entries or the chain of the longest K, the
+// tiles by the chain of the longest K or their share of the work, one launch after the other where they are too few for a
+// grouped one.  Fitted, in about us, to steps and single-layer losses with the bf16 tile over the same shapes, masks spread
+// evenly and half in 1 % of the rows: 20 of 3028 cases are more than 3 % slower than the tiles (20 % at most: a 300 x 320 layer at
+// one token), where token counts alone left 74 (65 %).  us per step at 1 %, split against tiles: a 16384 x 4096 layer at 64 / 128
+// tokens 140 / 266 against 191 / 186, three Llama blocks at 64 tokens 869 against 689, one OPT block at 128 tokens 437 against 463.
+static double split_rounded_us(const LaunchShape& l) {
+  return 13.5 + std::max(0.016 * (double)l.bands16 + 0.0036 * l.band_k + 0.02 * l.slice_entries, l.longest_k * (1.9 + 5.3 * l.percent()));
+}
+static double tiled_us(const LaunchShape& l, int forwards) {
+  const double chain = 9.1 * (1.0 + 0.05 * l.percent()), share = 0.0123 * forwards * l.tile_k * (1.0 + 0.73 * l.percent());
+  const bool one_launch = l.matrices == 1 ? forwards == 1 : forwards * l.tiles128 >= 384;
+  return 7.0 + 11.3 * (double)(forwards * l.matrices) + std::max(chain * (one_launch ? l.longest_k : forwards * l.sum_k), share);
+}
 // The split kernel's byte offsets inside a band's codes (32 per column) and inside its sixteen rows of x (32 per column)
 // have 32 bits; stream_ok's bound on the codes keeps the other layers below that.
 constexpr int64_t kSplitOnlyColumns = 1 << 23;
@@ -712,18 +746,31 @@ static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch) 
   const int64_t slices = (d->M + (d->x_minus ? 15 : 31)) / (d->x_minus ? 16 : 32), tile_rows = (d->M + 255) / 256;
   return slices <= kSmallMaxSlices && 2 * slices < 15 * tile_rows;
 }
-bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool one_set_only) {
+// `separate`: every matrix is a launch of its own (then the sums of their times are compared).
+static double rounded_us(const szo_linear_desc* descs, int n, bool split, int forwards, bool separate) {
+  if (!separate) {
+    LaunchShape shape;
+    for (int i = 0; i < n; ++i) shape.add(&descs[i]);
+    return split ? split_rounded_us(shape) : tiled_us(shape, forwards);
+  }
+  double us = 0.0;
+  for (int i = 0; i < n; ++i) us += rounded_us(&descs[i], 1, split, forwards, false);
+  return us;
+}
+double small_m_rounded_us(const szo_linear_desc* descs, int n, bool few, bool separate) { return rounded_us(descs, n, few, 2, separate); }
+bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool separate, int forwards) {
   LaunchShape shape;
   for (int i = 0; i < n; ++i) shape.add(&descs[i]);
+  bool all_stream = true;
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc* d = &descs[i];
     if (d->M <= 0 || d->N <= 0) continue;                   // an empty layer contributes nothing on either path
-    if (one_set_only && d->x_minus) return false;
+    if (separate && forwards == 2 && d->x_minus) return false;
     if (!(any_token_count ? stream_ok(d) : layer_eligible(d, shape))) return false;
+    all_stream = all_stream && stream_ok(d);
   }
-  return n > 0;
+  return n > 0 && (all_stream || rounded_us(descs, n, true, forwards, separate) <= rounded_us(descs, n, false, forwards, separate));
 }
-
 static FewPlan plan_of_one(const szo_linear_desc* d, bool compact) {
   LaunchShape shape;
   shape.add(d);
@@ -770,10 +817,15 @@ static int set_attrs_of_modes() {
   return rc;
 }
 static int set_small_attrs() {
+  static std::atomic<uint64_t> all_done{0};                   // one look instead of one per instantiation
+  int dev = 0;
+  SZO_HIP(hipGetDevice(&dev));
+  if (all_done.load(std::memory_order_acquire) & (1ull << (dev & 63))) return SZO_OK;
   int rc = set_attrs_of_modes<1, false>();
   if (rc == SZO_OK) rc = set_attrs_of_modes<2, false>();
   if (rc == SZO_OK) rc = set_attrs_of_modes<3, false>();
   if (rc == SZO_OK) rc = set_attrs_of_modes<2, true>();
+  if (rc == SZO_OK) all_done.fetch_or(1ull << (dev & 63), std::memory_order_release);
   return rc;
 }
 

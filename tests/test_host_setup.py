@@ -216,11 +216,40 @@ def test_kernel_timing_calls_are_safe_without_any_launch():
 
 def test_layers_beyond_the_split_kernels_offsets_are_left_to_the_tiled_kernel():
     """Host rule only: the few-token kernels address a band's codes and its rows of x with 32-bit byte offsets."""
-    eligible = szo.lib._ZN3szo16small_m_eligibleEPK15szo_linear_descibb
-    eligible.restype, eligible.argtypes = ctypes.c_bool, [ctypes.POINTER(szo.LinearDesc), ctypes.c_int, ctypes.c_bool, ctypes.c_bool]
+    eligible = szo.lib._ZN3szo16small_m_eligibleEPK15szo_linear_descibbi
+    eligible.restype, eligible.argtypes = ctypes.c_bool, [ctypes.POINTER(szo.LinearDesc), ctypes.c_int, ctypes.c_bool, ctypes.c_bool, ctypes.c_int]
     for K, tile, want in ((4160, szo.TILE_BF16, True), (4160, szo.TILE_F16, True), ((1 << 23) - 64, szo.TILE_BF16, True),
                           (1 << 23, szo.TILE_BF16, False), ((1 << 27) + 64, szo.TILE_BF16, False),
                           ((1 << 27) + 64, szo.TILE_F16, False), ((1 << 28) + 64, szo.TILE_F16, False),
                           ((1 << 27) - 128, szo.TILE_F16, True), (1 << 27, szo.TILE_F16, False)):
         d = szo.LinearDesc(M=8, N=15, K=K, group=64, tile_dtype=tile)
-        assert eligible(ctypes.byref(d), 1, False, False) is want, (K, tile)
+        assert eligible(ctypes.byref(d), 1, False, False, 1) is want, (K, tile)
+
+
+def _rule(name, result, *args):
+    f = getattr(szo.lib, name)
+    f.restype, f.argtypes = result, [ctypes.POINTER(szo.LinearDesc)] + list(args)
+    return f
+
+
+def _layers(shapes, M, density, tile=szo.TILE_F16, group=128):
+    return szo.desc_array([szo.LinearDesc(M=M, N=n, K=k, group=group, tile_dtype=tile, nnz=int(density * n * k)) for n, k in shapes])
+
+
+def test_kernel_choice_follows_the_density_of_the_mask():
+    """Host rules only, at sizes where both sides were measured: the split kernel (one partial per 64-row band and slice)
+    against the stream kernel (one per 256-column strip), the split kernel against tiles, the one-dense-pass kernel against both."""
+    partials = _rule("_ZN3szo16small_m_partialsEPK15szo_linear_descb", ctypes.c_int64, ctypes.c_bool)
+    for (n, k, m), density, split in (((16384, 16384, 96), 1e-4, True), ((16384, 16384, 96), 1e-2, False), ((16384, 4096, 64), 1e-3, True),
+                                      ((16384, 4096, 64), 1e-2, False), ((4096, 4096, 16), 1e-2, True), ((4096, 16384, 224), 1e-2, False)):
+        d = _layers([(n, k)], m, density)
+        slices = (m + 15) // 16
+        assert (partials(d, False) == n // 64 * slices) is split, (n, k, m, density)
+    eligible = _rule("_ZN3szo16small_m_eligibleEPK15szo_linear_descibbi", ctypes.c_bool, ctypes.c_int, ctypes.c_bool, ctypes.c_bool, ctypes.c_int)
+    for m, density, want in ((64, 1e-2, True), (128, 1e-3, True), (128, 1e-2, False)):
+        assert eligible(_layers([(16384, 4096)], m, density, szo.TILE_BF16, 64), 1, False, False, 2) is want, (m, density)
+    tiles = _rule("_ZN3szo16onepass_partialsEPK15szo_linear_descibbbb", ctypes.c_int64, ctypes.c_int, *[ctypes.c_bool] * 4)
+    block = [(n, k) for _, n, k in synth.OPT_6_7B_BLOCK]
+    for density, taken in ((1e-3, True), (1e-2, False)):
+        d = _layers(block, 128, density, szo.TILE_BF16, 64)
+        assert (tiles(d, len(block), False, False, False, False) > 0) is taken, density
