@@ -172,11 +172,14 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * be captured.  The workspace must not be shared with a call running concurrently on another
  * stream. */
 #define SZO_STEP_FUSED_LOSS 1
-/* Bit 1 (with bit 0): one dense product per layer at ANY token count.  Both forwards of a layer see the
+/* Bit 1 (with bit 0): one dense product per layer beyond 512 tokens too.  Both forwards of a layer see the
  * same x in this call, so y(+-) = x (dq + v)^T +- eps x z^T: the dense product is computed once and serves
- * both signs, the sparse products are added.  Same results as two forwards; half the dense work.  Not the
- * default beyond 512 tokens because it does not carry over to a caller whose two forwards see different
- * activations (every layer of a real model but the first), who calls szo_linear_fwd per sign instead. */
+ * both signs, the sparse products are added.  Same results as two forwards up to rounding; half the dense
+ * work.  A step keeps two products all the same where its layers have a second set of activations
+ * or where it loses by it (bf16 tile or K an odd multiple of 64 with masks of about 1 % and more, where the sparse products
+ * cost what the second dense product does).  Not the default beyond 512 tokens because it does not carry over to a
+ * caller whose two forwards see different activations (every layer of a real model but the first), who calls
+ * szo_linear_fwd per sign instead. */
 #define SZO_STEP_ONE_DENSE_PASS 2
 int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
                 float eps, float lr, double* scalars, void* workspace, int flags, void* stream);

@@ -1142,16 +1142,15 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   }
   int rc;
   void* const table_dev = (char*)workspace + kWorkspaceTableOffset;
-  // Few-token stacks: one pass over the weights serves both forwards of the step.
-  // SZO_STEP_ONE_DENSE_PASS: the caller asks for that path at any token count.
-  const bool few = fuse && few_token_enabled() && n <= kMaxStepMatrices &&
-                   small_m_eligible(descs, n, (flags & SZO_STEP_ONE_DENSE_PASS) != 0, false, 2);
+  // Few-token stacks: one pass over the weights serves both forwards of the step.  SZO_STEP_ONE_DENSE_PASS: also at token counts
+  // that the rule leaves to the tiled kernel.
+  const bool can_few = fuse && few_token_enabled() && n <= kMaxStepMatrices, asked_for = (flags & SZO_STEP_ONE_DENSE_PASS) != 0;
+  const bool few_rule = can_few && small_m_eligible(descs, n, false, false, 2);
+  const bool few = few_rule || (can_few && asked_for && small_m_eligible(descs, n, true, false, 2));
   // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip).
   {
     int64_t T = 0;
-    rc = onepass_forwards(descs, n, seed, step, eps, few && small_m_eligible(descs, n, false, false, 2),
-                          (flags & SZO_STEP_ONE_DENSE_PASS) != 0, !fuse, (char*)workspace + kWorkspaceTableOffset,
-                          partial_area(workspace), &T, s);
+    rc = onepass_forwards(descs, n, seed, step, eps, few_rule, asked_for, !fuse, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK) return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
     if (rc != SZO_EUNSUPPORTED) return rc;      // otherwise nothing was enqueued
   }

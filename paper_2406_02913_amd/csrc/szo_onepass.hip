@@ -598,6 +598,12 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    64): four Llama blocks with the bf16 tile at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393; there, and against
 //    the 128-row tiles that such layers run on otherwise, both paths are estimated from sizes and density (fitted with
 //    split_rounded_us): one OPT block at 128 tokens and 0.1 / 0.7 / 1 %, tiles -> this one 379 / 437 / 463 -> 253 / 473 / 568.
+//  * asked for at more tokens than the few-token path takes by itself, against its slices: from 160 workgroups on (110
+//    with smaller groups, whose slices are slower).  A 2048 x 12288 layer at 512 tokens (64 of them) 91 -> 154, a 4096 x 16384
+//    layer at 512 / 700 (128 / 176) 187 / 240 -> 210 / 214.
+//    Without slices (bf16 tile, K an odd multiple of 64): wherever it has 32 workgroups and the tiles would run layer by layer,
+//    and against a grouped launch, which is slower with that tile, up to 1.75 / 4: two OPT blocks at 224 tokens and 0.4 %
+//    636 -> 400, four at 512 tokens and 1 % 1654 -> 2179.
 //  * against the tiled kernel, up to kOnePassTokens tokens unless the caller asks for it: beyond that a step is two full
 //    forwards per layer by default, the products of the single-layer calls.  The two differ by what a row of tiles
 //    costs: a unit of 64 token rows here takes 1 + 108 rho
@@ -609,14 +615,15 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    block at 1 / 256 / 1024 tokens 1044 / 1063 / 1508 -> 150 / 189 / 621; rho = 0.01, 1024 tokens: 1836 -> 1128.
 constexpr int64_t kOnePassTokens = 512;
 static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y, bool separate) {
-  int64_t wgs = 0, most_tokens = 0;
+  int64_t wgs = 0, tiles = 0, most_tokens = 0;
   double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0, wg_k = 0.0, longest_k = 0.0;
-  bool stream = true;
+  bool stream = true, groups_of_128 = true;
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
     const double size = (double)d->N * (double)d->K;
     wgs += onepass_tiles(d);
+    tiles += ((d->M + 255) / 256) * ((d->N + 127) / 128);
     wg_k += (double)onepass_tiles(d) * (double)d->K;
     longest_k = std::max(longest_k, (double)d->K);
     most_tokens = std::max<int64_t>(most_tokens, d->M);
@@ -625,19 +632,25 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
     here += size * (double)((d->M + 63) / 64);
     tiled += size * (double)((d->M + 255) / 256) * 4.0;
     stream = stream && d->K % 128 == 0 && d->tile_dtype == SZO_TILE_F16;
+    groups_of_128 = groups_of_128 && d->group == 128;
   }
   const double rho = entries / weights;
   if (store_y) return wgs >= 4 && rho <= 0.015;
-  if (few && (wgs < 512 ? stream || most_tokens <= 64 || wgs < 256 : most_tokens <= (stream ? 32 : 16))) return false;
-  if (few && stream) return most_tokens > 64 || 205.0 * longest_k <= wg_k;
-  if (!few && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
+  if (asked_for && stream && !few) return wgs >= (groups_of_128 ? 160 : 110);
+  if (!(asked_for && !stream)) {
+    if (few && (wgs < 512 ? stream || most_tokens <= 64 || wgs < 256 : most_tokens <= (stream ? 32 : 16))) return false;
+    if (few && stream) return most_tokens > 64 || 205.0 * longest_k <= wg_k;
+    if (!few && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
+  }
   if (!stream && most_tokens <= 128) {
     const double k = longest_k / 1024.0;
     const double us = 26.6 + 3.5 * k + std::max(9.3 * k * (1.0 + 176.0 * rho), 0.0221 * wg_k / 1024.0 * (1.0 + 42.0 * rho));
     if (us >= small_m_rounded_us(descs, n, few, separate)) return false;
     if (few) return true;
   }
-  return asked_for || (most_tokens <= kOnePassTokens && (1.0 + 108.0 * rho) * here < 1.42 * tiled);
+  // asked for in a step too small for a grouped tiled launch (384 tiles of 256 x 128): the tiles would run layer by layer and sign
+  if (asked_for && tiles < 384) return wgs >= 32;
+  return (asked_for || most_tokens <= kOnePassTokens) && (1.0 + 108.0 * rho) * here < (asked_for ? 1.75 : 1.42) * tiled;
 }
 
 // The outputs are written by concurrent workgroups: layers must not share them (a caller that only wants the losses may

@@ -148,3 +148,19 @@ def test_squares_are_added_in_fp64(G):
     szo.szo_zo_step([d.desc(with_y=False)], 9, 0, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
     want = float((d.target.double() ** 2).mean().item())
     assert np.all(np.abs(scal.cpu().numpy()[:2] - want) <= 1e-13 * want)      # 21 000 terms, fp64: 2^-53 sqrt(21 000) = 2e-14
+
+
+@pytest.mark.parametrize("M,N,K,G,tile", [(16, 700, 512, 64, "bf16"), (16, 700, 192, 64, "f16"), (100, 300, 320, 32, "bf16")])
+def test_one_dense_pass_on_request_does_not_lose_the_few_token_path(M, N, K, G, tile):
+    """Layers that the stream kernel does not take: the flag changes neither the number of launches nor the result."""
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    o, d = make_pair(451, M, N, K, G, 1e-2)
+    ws, out = szo.new_workspace(), []
+    for flags in (szo.STEP_FUSED_LOSS, szo.STEP_FUSED_LOSS | szo.STEP_ONE_DENSE_PASS):
+        scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+        szo.szo_kernel_timing(True)
+        szo.szo_zo_step([d.desc(dt, with_y=False)], 9, 0, 1e-3, 0.0, scal, ws, flags)
+        _, launches = szo.szo_kernel_timing_read()
+        szo.szo_kernel_timing(False)
+        out.append((launches, scal.cpu().numpy().tolist()))
+    assert out[0] == out[1] and out[0][0] == 1

@@ -253,3 +253,9 @@ def test_kernel_choice_follows_the_density_of_the_mask():
     for density, taken in ((1e-3, True), (1e-2, False)):
         d = _layers(block, 128, density, szo.TILE_BF16, 64)
         assert (tiles(d, len(block), False, False, False, False) > 0) is taken, density
+
+
+def test_one_dense_pass_on_request_falls_back_to_the_slices_of_the_few_token_path():
+    tiles = _rule("_ZN3szo16onepass_partialsEPK15szo_linear_descibbbb", ctypes.c_int64, ctypes.c_int, *[ctypes.c_bool] * 4)
+    for (n, k, m), taken in (((2048, 12288, 512), False), ((4096, 4096, 512), False), ((4096, 4096, 1000), True), ((16384, 4096, 512), True)):
+        assert (tiles(_layers([(n, k)], m, 1e-3), 1, False, True, False, False) > 0) is taken, (n, k, m)
