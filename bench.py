@@ -47,13 +47,32 @@ def algorithmic_bytes_fwd(m, M, fused=True):
 
 
 def few_token_path(M, two_sets=False):
-    """Whether a step over a large stack computes its dense product once for both signs: up to 512 tokens with one set of
-    activations, at most 15 slices of 16 rows that beat 7.5 of them per row of 256-row tiles with two.  Only used to label
-    the kernel and to pick default step counts."""
-    if not two_sets:
-        return M <= 512
-    slices, tile_rows = (M + 15) // 16, (M + 255) // 256
+    """Token counts that the library's few-token path takes by itself: at most 15 slices of 32 token rows (16 with two
+    activation sets), fewer than 7.5 of them per row of 256-row tiles."""
+    slices, tile_rows = (M + (15 if two_sets else 31)) // (16 if two_sets else 32), (M + 255) // 256
     return slices <= 15 and 2 * slices < 15 * tile_rows
+
+
+def one_product_kernel(mats, M, two_sets=False, asked_for=False):
+    """Which kernel computes a fused step's dense product once for both signs, or None where two forwards run: the
+    library's rules for fp16-tile layers with K a multiple of 128, restated to label the measurement."""
+    few, uniform = few_token_path(M, two_sets), all(m.lut is None for m in mats)
+    wgs = sum(-(-m.N // 256) * -(-M // 64) for m in mats)
+    wg_k = sum(-(-m.N // 256) * -(-M // 64) * m.K for m in mats)
+    rho = sum(m.nnz for m in mats) / sum(m.N * m.K for m in mats)
+    if uniform and not two_sets:
+        if few:
+            taken = wgs >= 512 and M > 32 and (M > 64 or 205 * max(m.K for m in mats) <= wg_k)
+        elif asked_for:
+            taken = wgs >= 160
+        else:
+            taken = wgs >= 32 and M <= 512 and (1 + 108 * rho) * -(-M // 64) < 1.42 * 4 * -(-M // 256)
+        if taken:
+            return "onepass_table_kernel"
+    if few or asked_for:
+        # a few blocks: K split over the waves of a workgroup
+        return "band_split_kernel" if M <= 64 and wgs * -(-M // 16) <= 600 else "small_m_kernel"
+    return None
 
 
 def time_steps(szo, torch, descs, seed, eps, lr, flags, steps, warmup, first_step=0):
@@ -82,20 +101,20 @@ def time_steps(szo, torch, descs, seed, eps, lr, flags, steps, warmup, first_ste
             "steps": steps, "warmup": warmup, "last": (lp, lm, g)}
 
 
-def rooflines(mats, M, t, few, fused, traffic=None):
+def rooflines(mats, M, t, one_product, fused, traffic=None):
     """Roofline entry of the dominant (forward) kernel and the figures of the sparse update, per launch."""
     steps = t["steps"]
     fwd_flops = sum(2.0 * M * m.N * m.K for m in mats)
     launches = t["fwd_launches"]
     k_ms = t["fwd_ms"] / launches
     one_pass = float(sum(algorithmic_bytes_fwd(m, M, fused) for m in mats))
-    if few:       # one launch computes the dense product once and serves both signs
-        kernel = "small_m_kernel" if M <= 32 else "onepass_table_kernel"
+    if one_product:       # this kernel computes the dense product once and serves both signs
+        kernel = one_product
         launch_bytes = one_pass * steps / launches
     else:         # large fused steps run every forward of the step in one table-driven launch
         kernel = "linear_fwd_table_kernel" if launches == steps else "linear_fwd_kernel"
         launch_bytes = one_pass * 2 * steps / launches
-    launch_flops = (1 if few else 2) * fwd_flops * steps / launches      # dense products that are executed
+    launch_flops = (1 if one_product else 2) * fwd_flops * steps / launches      # dense products that are executed
     tflops = launch_flops / (k_ms * 1e-3) / 1e12
     gbs = launch_bytes / (k_ms * 1e-3) / 1e9
     mfma_bound = (launch_flops / launch_bytes) > (PEAK_MFMA_16BIT_TFLOPS * 1e12) / (PEAK_HBM_GBS * 1e9)
@@ -145,7 +164,7 @@ def extra_workload(szo, torch, stack, name, seed, data_seed, dt, variants, steps
         t = time_steps(szo, torch, descs, seed, cfg["eps"], cfg["lr"], szo.STEP_FUSED_LOSS,
                        steps or (200 if few else 20), warmup if warmup is not None else (30 if few else 5))
         traffic = MEASURED_TRAFFIC_BYTES.get(f"{name}:{v['density']:g}" if "density" in v else f"{name}:{M}") if dt == szo.TILE_F16 else None
-        roof, upd, step_flops = rooflines(mats, M, t, few, True, traffic)
+        roof, upd, step_flops = rooflines(mats, M, t, one_product_kernel(mats, M), True, traffic)
         row = {"M": M, "density": v.get("density", cfg["density"]), "matrices": len(mats),
                "ms_per_step": round(t["ms_per_step"], 4), "steps": t["steps"], "warmup": t["warmup"],
                "step_tflops": round(step_flops / (t["ms_per_step"] * 1e-3) / 1e12, 2),
@@ -273,10 +292,11 @@ def main():
                     help="SZO_STEP_ONE_DENSE_PASS at any token count (the dense "
                          "product of a slice is computed once and serves both signs; valid because both forwards of a "
                          "layer see the same x in this benchmark).  Not the default: see include/szo.h")
-    ap.add_argument("--tile-config", type=int, default=0, choices=[0, 1, 2, 3, 4, 5, 6, 7],
+    ap.add_argument("--tile-config", type=int, default=0, choices=range(12),
                     help="0: the library chooses (few-token path for small token counts); 1 / 2: force the tiled kernel with "
                          "128x128 / 256x256 workgroup tiles; 3: as 2, and always one grouped launch per step; 4: as 0 "
-                         "with 32 token rows per pass of the few-token path wherever there are more than 16 (for comparisons)")
+                         "with 32 token rows per pass of the few-token path wherever there are more than 16; 8 / 9 / 11: the few-token "
+                         "path's split / stream kernel, the one-dense-pass kernel (all of them in include/szo.h; for comparisons)")
     ap.add_argument("--seed", type=int, default=2024)
     ap.add_argument("--data-seed", type=int, default=0)
     ap.add_argument("--cpu-seconds", type=float, default=12.0, help="budget of the oracle baseline leg (0 = skip)")
@@ -356,13 +376,19 @@ def main():
     lp, lm, g = t["last"]
     log(f"[bench] {ms_per_step:.3f} ms/step (events), {t['wall_ms_per_step']:.3f} ms/step (wall); "
         f"last step L+={lp:.6f} L-={lm:.6f} g={g:.4e}")
-    few = (all((few_token_path(m.M, args.two_activation_sets) or args.one_dense_pass) and m.K % 128 == 0 for m in mats)
-           and dt == szo.TILE_F16 and args.tile_config in (0, 4, 5) and bool(flags))        # the library's few-token path
+    one_product = None                   # with another tile type, K or configuration the label stays with the tiled kernel
+    if all(m.K % 128 == 0 for m in mats) and dt == szo.TILE_F16 and flags:
+        if args.tile_config == 0:
+            one_product = one_product_kernel(mats, M, args.two_activation_sets, args.one_dense_pass)
+        elif args.tile_config in (4, 5, 7, 8, 9, 10) and (few_token_path(M, args.two_activation_sets) or args.one_dense_pass):
+            one_product = "band_split_kernel" if args.tile_config == 8 else "small_m_kernel"
+        elif args.tile_config == 11:
+            one_product = "onepass_table_kernel"
     traffic = MEASURED_TRAFFIC_BYTES.get(args.workload) if (
         args.layers is None and args.m is None and args.density is None and flags and dt == szo.TILE_F16
         and args.tile_config == 0 and args.format == "uniform" and not args.two_activation_sets
         and not args.one_dense_pass) else None
-    roof, upd, step_flops = rooflines(mats, M, t, few, bool(flags), traffic)
+    roof, upd, step_flops = rooflines(mats, M, t, one_product, bool(flags), traffic)
     log(f"[bench] {roof['kernel']}: {roof['avg_launch_us']:.1f} us/launch avg over {roof['launches_timed']} launches of the "
         f"timed steps, {roof['achieved']} {roof['unit']}")
 
@@ -373,11 +399,11 @@ def main():
         try:
             d16 = descs_for(szo, mats, 16, dt, with_y=False)
             t16 = time_steps(szo, torch, d16, args.seed, eps, lr, flags, 200, 30, first_step=1000)
-            r16, u16, _ = rooflines(mats, 16, t16, True, True, MEASURED_TRAFFIC_BYTES.get("c3m16"))
+            r16, u16, _ = rooflines(mats, 16, t16, one_product_kernel(mats, 16), True, MEASURED_TRAFFIC_BYTES.get("c3m16"))
             extras["few_token"] = {"workload": f"the same {len(mats)} matrices at M=16 tokens (the first 16 rows of every x and target)",
                                    "ms_per_step": round(t16["ms_per_step"], 4), "value": round(1e3 / t16["ms_per_step"], 2),
                                    "unit": "ZO steps/s", "steps": 200, "warmup": 30, "roofline": r16, "sparse_update": u16}
-            log(f"[bench] few_token: {t16['ms_per_step']:.4f} ms/step, small_m_kernel {r16['achieved']} GB/s "
+            log(f"[bench] few_token: {t16['ms_per_step']:.4f} ms/step, {r16['kernel']} {r16['achieved']} GB/s "
                 f"({100 * r16['frac']:.1f} % of the HBM peak)")
         except Exception as e:      # noqa: BLE001 -- reported in the line instead of losing the headline
             extras["few_token"] = {"error": f"{type(e).__name__}: {e}"}
@@ -421,7 +447,7 @@ def main():
                                + (f"int4 group {cfg['group']}, " if args.format == "uniform" else "4-bit table format, ") +
                                f"mask {cfg['density']:g} {cfg['mask']}, eps={eps}, lr={lr}",
                    "loss": "fused into the forward epilogue" if flags else "separate kernel",
-                   "dense_product": ("once per sign" if (not few or args.two_activation_sets)
+                   "dense_product": ("once per sign" if (not one_product or args.two_activation_sets)
                                      else "once, shared by both signs"),
                    "activations": "x for +eps, x_minus for -eps" if args.two_activation_sets else "one x for both signs",
                    "tile": args.tile, "format": args.format, "accumulate": "f32", "loss_accumulate": "f64"},
