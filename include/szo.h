@@ -63,7 +63,15 @@ extern "C" {
  *   is raised.  A caller whose activations may leave that range (outlier channels of a real model)
  *   measures them with szo_activation_absmax() and takes what szo_choose_tile_dtype() returns.
  *   SZO_TILE_BF16 stages the activations unchanged (full bf16 range); the sensitive values are then
- *   rounded to 8 significant bits, which costs about 1-2 % of sigma_g on the SPSA scalar. */
+ *   rounded to 8 significant bits, which costs about 1-2 % of sigma_g on the SPSA scalar.
+ * The kernels round to this type in two ways, and which of them runs a call depends on its sizes, the format, the
+ * density of the mask and the entry point:
+ *   - as ONE weight tile: dq is rounded, then dq + (v + eps z) and dq + (v - eps z) are (tiled kernel; the
+ *     few-token kernels for layers with the bf16 tile or K an odd multiple of 64);
+ *   - v and z one by one, eps applied in fp32 (the other few-token launches, the one-dense-pass kernel), which
+ *     leaves less error in g; dq itself is not rounded there with the fp16 tile and groups of 128.
+ * Results of the same layer on two kernels therefore agree to these roundings, not to fp32 summation order: outputs
+ * to about 2^-11 (fp16 tile) or 2^-8 (bf16) relative, g to 1-2 % of sigma_g with the bf16 tile. */
 #define SZO_TILE_F16   0
 #define SZO_TILE_BF16  1
 
@@ -157,14 +165,15 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * loss-fusing forward and never write y (desc->y may then be NULL); large steps then run all
  * forwards (every layer, both signs) as one launch driven by a descriptor table that is staged in
  * the workspace.  Steps of up to 512 tokens whose layers have one set of activations compute the dense
- * product once for both signs, in whichever kernel is fastest for their size: few tokens stream the
- * weights once per 16 to 48 token rows, more of them run on the matrix cores in tiles of 64 token rows.
+ * product once for both signs where that is the faster way: few tokens stream the weights once per 16 to 48
+ * token rows; more of them run on the matrix cores in tiles of 64 token rows, if the layers are of the uniform
+ * format with one tile type, fill the chip, and their masks are sparse (up to about 0.4 % against the tiled kernel).
  * With bit 0 clear y holds the -eps forward's outputs afterwards, and the loss is summed in fp64 from the
- * fp32 outputs; layers with one set of activations and no output buffer in common with another layer run as
- * one launch there too.
+ * fp32 outputs; layers of the uniform format with one tile type, one set of activations, masks of up to 1.5 % and no
+ * output buffer in common with another layer run as one launch there too.
  * descs: host array, read before the call returns.  Everything is enqueued on `stream`.  The
- * descriptor tables of the grouped launches (forwards of a fused step; the update of every step)
- * travel through a ring of eight pinned host buffers per host thread (allocated on first use,
+ * descriptor tables of the grouped launches (forwards of a step; the update), except those of up to eight layers
+ * on the few-token path and in the update, which are kernel arguments, travel through a ring of eight pinned host buffers per host thread (allocated on first use,
  * released when the thread ends); a call waits on the host only if a copy issued eight tables
  * earlier on this thread (four tiled steps) has not executed yet.  Because of those buffers NO
  * variant of this call can be captured into a HIP graph: it returns SZO_EUNSUPPORTED, with nothing
@@ -174,7 +183,7 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
 #define SZO_STEP_FUSED_LOSS 1
 /* Bit 1 (with bit 0): one dense product per layer beyond 512 tokens too.  Both forwards of a layer see the
  * same x in this call, so y(+-) = x (dq + v)^T +- eps x z^T: the dense product is computed once and serves
- * both signs, the sparse products are added.  Same results as two forwards up to rounding; half the dense
+ * both signs, the sparse products are added.  Same results as two forwards up to the roundings above; half the dense
  * work.  A step keeps two products all the same where its layers have a second set of activations
  * or where it loses by it (bf16 tile or K an odd multiple of 64 with masks of about 1 % and more, where the sparse products
  * cost what the second dense product does).  Not the default beyond 512 tokens because it does not carry over to a
@@ -187,11 +196,14 @@ int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, u
 /* The same step for callers that cannot allocate: code running under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same inputs, same outputs as szo_zo_step with
  * SZO_STEP_FUSED_LOSS (scalars = (L+, L-, g); every layer's sp_val updated; desc->y is not written),
- * up to the order in which the fp64 loss partials are added.  It takes no workspace: the loss partials
+ * up to the order in which the fp64 loss partials are added where both run the same kernels, and up to the roundings
+ * described at SZO_TILE_F16 where they do not (launched layer by layer, other kernels pay: a step over several layers
+ * may take the one-dense-pass kernel there and the few-token or tiled kernels here).  It takes no workspace: the loss partials
  * live in a fixed array inside the library (1 MiB per GPU, kept until the process ends), and it
  * stages no descriptor table: every layer is one plain launch that serves both signs (when every
- * layer of the step qualifies for one and none has x_minus), else one tiled launch per sign; then one
- * reduction, and one update launch per layer.  It calls no
+ * layer of the step qualifies for one and none has x_minus), else one tiled launch per sign; then the
+ * reduction and the update: one launch each for up to eight layers (a single one for the smallest), else one
+ * reduction and one update launch per layer.  It calls no
  * allocating routine (no hipMalloc / hipHostMalloc, no event creation unless szo_kernel_timing is
  * on) and can be captured into a HIP graph.
  * Limit: at most 65 536 workgroups per sign over the whole step (one per 256 x 256 output tile, or
@@ -271,7 +283,7 @@ int szo_activation_absmax(const void* x /* device bf16 */, int64_t count, float*
  * (x_absmax <= 65504), else SZO_TILE_BF16; SZO_EINVAL for a negative or NaN argument. */
 int szo_choose_tile_dtype(float x_absmax);
 
-/* Timing of the forward kernels (the tiled kernel and the few-token kernel) for benchmarks.
+/* Timing of the forward kernels (tiled, few-token and one-dense-pass) for benchmarks.
  * szo_kernel_timing(1) makes every later forward-kernel launch record a pair of events around
  * itself on the stream it is launched on; szo_kernel_timing(0) stops that.  Either call drops
  * what was recorded.  szo_kernel_timing_read() waits for the recorded launches, returns the sum
@@ -307,7 +319,8 @@ int szo_debug_zbar(uint64_t nnz_base, int64_t nnz, uint64_t seed, uint64_t step,
  * holds), 8 / 9 = as 0 and the few-token path takes its kernel for small launches (K split over the waves of
  * a workgroup) always / never, 10 = 9 and 7, 11 = szo_zo_step takes the kernel that computes one dense
  * product per layer in tiles of 64 token rows wherever it can (chosen by size with 0, never with 1 to 10).
- * Process-wide, not thread-safe; results do not depend on it beyond fp32 summation order. */
+ * Process-wide, not thread-safe.  Results depend on it by the roundings described at SZO_TILE_F16 and by fp32
+ * summation order. */
 int szo_set_tile_config(int config);
 
 /* HIP error code of the most recent SZO_ELAUNCH on this thread (0 if none). */

@@ -164,3 +164,54 @@ def test_one_dense_pass_on_request_does_not_lose_the_few_token_path(M, N, K, G, 
         szo.szo_kernel_timing(False)
         out.append((launches, scal.cpu().numpy().tolist()))
     assert out[0] == out[1] and out[0][0] == 1
+
+
+def test_noalloc_step_on_this_kernel_gives_the_same_g_and_values():
+    results = []
+    for entry in ("workspace", "noalloc"):
+        o, d = make_pair(461, 300, 2048, 512, 128, 2e-3)
+        scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+        szo.szo_kernel_timing(True)
+        if entry == "workspace":
+            szo.szo_zo_step([d.desc(with_y=False)], 9, 0, 1e-3, 1e-3, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+        else:
+            szo.szo_zo_step_noalloc([d.desc(with_y=False)], 9, 0, 1e-3, 1e-3, scal)
+        _, launches = szo.szo_kernel_timing_read()
+        szo.szo_kernel_timing(False)
+        assert launches == 1
+        results.append((scal.cpu().numpy().copy(), d.sp_val.cpu().numpy().copy(), o))
+    (s0, v0, o), (s1, v1, _) = results
+    assert np.allclose(s0[:2], s1[:2], rtol=1e-12, atol=0.0)                 # the order of the partials
+    assert abs(s0[2] - s1[2]) <= 1e-12 * s0[0] / 1e-3                        # ... over 2 eps
+    r = ozo.zo_step([clone(o)], 9, 0, 1e-3, 1e-3)
+    assert abs(s1[2] - r["g"]) <= 1e-2 * max(abs(r["g"]), sigma_g([o]))
+    assert np.max(np.abs(v0 - v1)) <= np.max(np.spacing(np.abs(v0)))
+
+
+def test_a_bf16_stack_differs_between_the_entry_points_by_the_rounding_of_the_sensitive_weights():
+    """Eight layers that one grouped launch computes with v and z rounded one by one, and eight launches of the split kernel
+    with v +- eps z rounded: the losses agree to the averaged rounding, g to a few percent of sigma_g, both near the oracle."""
+    os_, ds_, base = [], [], 0
+    for i in range(8):
+        o, d = make_pair(471 + i, 64, 16384, 128, 64, 1e-3, nnz_base=base)
+        base += (o.sp_idx.size + 3) // 4 * 4
+        os_.append(o)
+        ds_.append(d)
+    descs = [d.desc(szo.TILE_BF16, with_y=False) for d in ds_]
+    out = []
+    for entry, want in (("workspace", 1), ("noalloc", 8)):
+        scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+        szo.szo_kernel_timing(True)
+        if entry == "workspace":
+            szo.szo_zo_step(descs, 9, 0, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+        else:
+            szo.szo_zo_step_noalloc(descs, 9, 0, 1e-3, 0.0, scal)
+        _, launches = szo.szo_kernel_timing_read()
+        szo.szo_kernel_timing(False)
+        assert launches == want
+        out.append(scal.cpu().numpy().copy())
+    r, sg = ozo.zo_step([clone(o) for o in os_], 9, 0, 1e-3, 0.0), sigma_g(os_)
+    for s in out:                # 2^-9 per weight, averaged over 8 x 10^6 outputs; the bar on g with this tile type is 1e-1
+        assert abs(s[0] - r["loss_plus"]) <= 1e-4 * r["loss_plus"] and abs(s[1] - r["loss_minus"]) <= 1e-4 * r["loss_minus"]
+        assert abs(s[2] - r["g"]) <= 1e-1 * max(abs(r["g"]), sg)
+    assert abs(out[0][2] - out[1][2]) <= 1e-1 * max(abs(r["g"]), sg)
