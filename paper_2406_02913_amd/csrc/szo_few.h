@@ -54,6 +54,8 @@ struct SmallArgs {
   const SmallMat* table;    // device table of n_mats matrices, or null: they are in `inl`
   SmallMat inl[kInlineMats];
   int n_mats;
+  uint32_t part_shifts;     // split kernel, 4 bits per matrix of `inl`: its bands are cut into 1 << these workgroups (staged tables: 0)
+  int few_rows;             // split kernel: no matrix of the launch has more than four token rows
   int slices;               // slices of token rows per strip in this launch (the longest matrix's count)
   int stream_once;          // host's choice: load the codes as a non-temporal stream (see small_m_kernel, ONCE)
   int store_sign;           // which forward's outputs are written to y (+1, -1), 0: neither
@@ -147,21 +149,30 @@ __device__ __forceinline__ int xcd_unit(int bid, int grid) {
 // space (scalar loads: the table is written before the launch and never during it), so that its fields live in
 // scalar registers like the kernel arguments do; read through a generic pointer they would occupy ~30 vector
 // registers.
-__device__ __forceinline__ SmallMat find_matrix(const SmallArgs& a, int unit) {
+typedef const uint32_t __attribute__((address_space(4)))* small_words;
+__device__ __forceinline__ small_words small_table(const SmallArgs& a) {
+  return a.table ? (small_words)a.table : (small_words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SmallArgs, inl) / 4;
+}
+__device__ __forceinline__ int find_index(const SmallArgs& a, int unit) {
   constexpr int W = (int)(sizeof(SmallMat) / 4), FB = (int)(offsetof(SmallMat, first_block) / 4);
   static_assert(sizeof(SmallMat) % 4 == 0 && offsetof(SmallMat, first_block) % 4 == 0, "table entry is read as words");
-  typedef const uint32_t __attribute__((address_space(4)))* words;
-  const words tab = a.table ? (words)a.table : (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SmallArgs, inl) / 4;
+  const small_words tab = small_table(a);
   int lo = 0, hi = a.n_mats - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if ((int)tab[mid * W + FB] <= unit) lo = mid; else hi = mid - 1;
   }
+  return lo;
+}
+__device__ __forceinline__ SmallMat read_matrix(const SmallArgs& a, int index) {
+  constexpr int W = (int)(sizeof(SmallMat) / 4);
   struct Words { uint32_t w[W]; } raw;
+  const small_words tab = small_table(a);
 #pragma unroll
-  for (int i = 0; i < W; ++i) raw.w[i] = tab[lo * W + i];
+  for (int i = 0; i < W; ++i) raw.w[i] = tab[index * W + i];
   return __builtin_bit_cast(SmallMat, raw);
 }
+__device__ __forceinline__ SmallMat find_matrix(const SmallArgs& a, int unit) { return read_matrix(a, find_index(a, unit)); }
 
 // The tables of one row, 16 fp16 entries at p, as the four byte planes that sm_lut_word() reads.
 __device__ __forceinline__ void load_lut_planes(const uint16_t __attribute__((address_space(1)))* p, uint32_t (&T)[8]) {

@@ -1018,12 +1018,13 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
   // Kernel choice as in szo_zo_step: the few-token kernel (one launch per layer, both signs) when every
   // layer qualifies for it -- here also: no layer with a second activation set, which needs the grouped
   // launch's dual kernel -- else the tiled kernel, one launch per layer and sign.
-  // `compact`: when the partials of the layers' preferred launches exceed the array, the ones with fewer of them.
-  bool few_all = false, compact = false;
+  // `less`: when the partials of the layers' preferred launches exceed the array, the ones with fewer of them.
+  bool few_all = false;
+  Partials less = kBandsInParts;
   int64_t T = 0;
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    compact = attempt == 1;
-    few_all = few_token_enabled() && small_m_eligible(descs, n, false, true, 2) && (!compact || small_m_eligible(descs, n, true, true, 2));
+  for (Partials attempt : {kBandsInParts, kWholeBands, kStreamKernel}) {
+    less = attempt;
+    few_all = few_token_enabled() && small_m_eligible(descs, n, false, true, 2) && (less != kStreamKernel || small_m_eligible(descs, n, true, true, 2));
     T = 0;
     for (int i = 0; i < n; ++i) {     // reject everything before anything is enqueued
       const szo_linear_desc* d = &descs[i];
@@ -1031,7 +1032,7 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
       if (rc != SZO_OK) return rc;
       if (d->nnz > 0 && (!d->sp_val || ((uintptr_t)d->sp_val & 15))) return SZO_EINVAL;
       if (d->M == 0 || d->N == 0) continue;
-      if (few_all) { T += small_m_partials(d, compact); continue; }
+      if (few_all) { T += small_m_launch_partials(d, less); continue; }
       int blocks;
       plan_tiles((int)d->M, (int)d->N, d->format, &blocks);
       if (blocks < 0) return SZO_EUNSUPPORTED;
@@ -1057,8 +1058,8 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
       rc = onepass_one(d, seed, step, eps, part + off, part + T + off, s);
       off += onepass_tiles(d);
     } else if (few_all) {
-      rc = small_m_launch_one(d, seed, step, eps, 0, true, part + off, part + T + off, compact, s);
-      off += small_m_partials(d, compact);
+      rc = small_m_launch_one(d, seed, step, eps, 0, true, part + off, part + T + off, less, s);
+      off += small_m_launch_partials(d, less);
     } else {
       const double scale = 1.0 / ((double)d->M * (double)d->N);
       int blocks;
@@ -1092,7 +1093,7 @@ int szo_linear_fwd(const szo_linear_desc* desc, uint64_t seed, uint64_t step, in
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
   if (few_token_enabled() && small_m_eligible(desc, 1, false, false, 1))
     return small_m_launch_one(desc, seed, step, sign == 0 ? 0.0f : eps, sign == 0 ? 1 : sign, false, nullptr, nullptr,
-                              false, (hipStream_t)stream);
+                              kBandsInParts, (hipStream_t)stream);
   return run_forward(desc, seed, step, sign, eps, nullptr, 0.0, (hipStream_t)stream);
 }
 
@@ -1105,10 +1106,10 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   // the few-token kernels compute both signs at once: make the requested one the "+" forward.  Their scale is that of a
   // step's loss, and both signs' partials have to fit.
   const bool few = few_token_enabled() && small_m_eligible(desc, 1, false, false, 1) && scale == 1.0 / ((double)desc->M * (double)desc->N);
-  const int64_t nb = few ? small_m_partials(desc) : 0;
+  const int64_t nb = few ? small_m_launch_partials(desc, kBandsInParts) : 0;
   if (few && 2 * nb <= kMaxLossPartials) {
     rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, partial_area(workspace),
-                            partial_area(workspace) + nb, false, (hipStream_t)stream);
+                            partial_area(workspace) + nb, kBandsInParts, (hipStream_t)stream);
     if (rc != SZO_OK) return rc;
     return reduce_partials(partial_area(workspace), (int)nb, 1.0, loss_acc, (hipStream_t)stream);
   }

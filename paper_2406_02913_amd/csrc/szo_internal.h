@@ -54,14 +54,17 @@ bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count,
 // Estimated us of a step's forwards, up to 128 tokens, where the stream kernel does not take every layer: on the few-token path
 // (`few`) or in the tiled kernel.
 double small_m_rounded_us(const szo_linear_desc* descs, int n, bool few, bool separate);
-int64_t small_m_partials(const szo_linear_desc* d, bool compact = false);   // loss partials per sign of a single-matrix launch;
-                                                            // compact: of the stream kernel, which makes fewer of them
+int64_t small_m_partials(const szo_linear_desc* d, bool compact = false);   // loss partials per sign of a single-matrix launch, one per
+                                                            // band (split kernel) or strip (stream kernel; compact: always) and slice
+// ... and of the launch as it runs by itself, which may cut bands into parts; callers with little room ask for fewer.
+enum Partials { kBandsInParts, kWholeBands, kStreamKernel };
+int64_t small_m_launch_partials(const szo_linear_desc* d, Partials less);
 void small_m_force_split(int how);                          // testing hook: 1 = the split kernel always, -1 = only where nothing else can, 0 = choose
 void small_m_force_rblocks(int r);                         // testing hook: 0 = choose; 2, 3 = 32 / 48 token rows per pass wherever M > 16
 void small_m_force_stream_once(bool on);                    // testing hook: non-temporal code stream in every one-slice launch
 size_t small_m_table_bytes(int n);
 int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int store_sign, bool loss_mode,
-                       double* partial_plus, double* partial_minus, bool compact, hipStream_t stream);
+                       double* partial_plus, double* partial_minus, Partials less, hipStream_t stream);
 int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,
                  void* table_dev, double* partial_plus, int64_t partials_per_sign, double* scalars, bool do_forward,
                  hipStream_t stream);

@@ -50,5 +50,10 @@ __device__ __forceinline__ void zbar_quad(uint64_t quad, uint64_t seed, uint64_t
   box_muller(w.w0, w.w1, z[0], z[1]);
   box_muller(w.w2, w.w3, z[2], z[3]);
 }
+// Two of them: entries 4*quad + {0,1}, or {2,3} with `second`.
+__device__ __forceinline__ void zbar_pair(uint64_t quad, bool second, uint64_t seed, uint64_t step, float z[2]) {
+  const Words4 w = zbar_words(quad, seed, step);
+  box_muller(second ? w.w2 : w.w0, second ? w.w3 : w.w1, z[0], z[1]);
+}
 
 }  // namespace szo

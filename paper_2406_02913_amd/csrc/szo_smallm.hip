@@ -606,14 +606,15 @@ enum { D_FAST, D_LUT, D_PLAIN, D_TILE_F16, D_TILE_BF16, kDequants };
 constexpr int kClasses = kVariants * kDequants;
 struct FewPlan {
   int variant, dequant;
+  int part_shift = 0;                                       // split kernel: workgroups per band, see split_part_shift
   int cls() const { return variant * kDequants + dequant; }
-  static FewPlan of_class(int cls) { return FewPlan{cls / kDequants, cls % kDequants}; }
+  static FewPlan of_class(int cls) { return FewPlan{cls / kDequants, cls % kDequants, 0}; }
   bool split() const { return variant >= V_SPLIT; }
   bool dual() const { return variant == V_STREAM_DUAL || variant == V_SPLIT_DUAL; }
   int rblocks() const { return variant <= V_STREAM3 ? variant + 1 : variant == V_STREAM_DUAL ? 2 : 1; }
   int mode() const { return dequant == D_FAST ? SM_FAST : dequant == D_LUT ? SM_LUT : SM_PLAIN; }
   int rows() const { return dual() || split() ? SM_ROWS : SM_ROWS * rblocks(); }       // token rows of one slice
-  int64_t units(const szo_linear_desc* d) const { return split() ? bands_of(d) : strips_of(d); }   // workgroups per slice
+  int64_t units(const szo_linear_desc* d) const { return split() ? bands_of(d) << part_shift : strips_of(d); }   // workgroups per slice
   int slices(const szo_linear_desc* d) const { return (int)((d->M + rows() - 1) / rows()); }
 };
 
@@ -638,7 +639,20 @@ static bool split_pays(const LaunchShape& launch, bool dual, bool lut, bool plai
   const double stream = ((plain ? 12.9 : 6.9) + 8.0 * over) * launch.longest_k + 0.0026 * launch.band_k;
   return split <= stream;
 }
-static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, bool dual, bool compact = false) {
+// Workgroups per band of a split launch, 1 << the result.  A band's wave dequantises four 16-row subtiles for each 128 columns, one
+// after the other, which is most of a small launch's time: cut into two or four workgroups the band takes more CUs.  Each of them
+// stages x and looks through the band's entries again, so only while all workgroups still have a CU to themselves (one
+// forward at 16 tokens, us with 1 / 2 / 4 workgroups per band: 4096 x 4096 (64 bands) 10.4 / 7.7 / 6.6, 8192 x 4096 10.5 / 8.0 / 9.5,
+// 11008 x 4096 10.8 / 11.3 / 12.7, 4096 x 16384 26.8 / 19.6 / 16.5); and in two where the chain of a long K outlasts the
+// whole launch's work, both estimated as in split_pays (a step over one OPT block at 1 / 16 tokens, fc2's bands cut in two:
+// 33.8 / 42.4 -> 31.1 / 35.5; where the chain is shorter it loses: one Mistral block 31.9 / 39.9 -> 36.2 / 41.8).
+static int split_part_shift(const szo_linear_desc* d, const LaunchShape& launch) {
+  if (launch.bands16 <= 64) return 2;
+  if (launch.bands16 <= 128) return 1;
+  const double k = (double)d->K / 1024.0, chain = 3.2 + 1.55 * k, work = 0.012 * (double)launch.bands16 + 0.0058 * launch.band_k;
+  return k >= 8.0 && chain > 1.1 * work ? 1 : 0;
+}
+static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, bool dual, Partials less = kBandsInParts) {
   FewPlan p;
   if (d->format == SZO_FORMAT_LUT) p.dequant = D_LUT;
   else if (d->tile_dtype == SZO_TILE_BF16) p.dequant = D_TILE_BF16;
@@ -646,24 +660,27 @@ static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, boo
   else p.dequant = d->group == 128 ? D_FAST : D_PLAIN;
   bool split = split_pays(launch, dual, p.dequant == D_LUT, p.dequant == D_PLAIN);
   if (g_force_split) split = g_force_split > 0;
-  if (g_force_rblocks || compact) split = false;
+  if (g_force_rblocks || less == kStreamKernel) split = false;
   if (!stream_ok(d)) split = true;
-  if (split) p.variant = dual ? V_SPLIT_DUAL : V_SPLIT;
+  if (split) {
+    p.variant = dual ? V_SPLIT_DUAL : V_SPLIT;
+    p.part_shift = less == kBandsInParts ? split_part_shift(d, launch) : 0;
+  }
   else p.variant = dual ? V_STREAM_DUAL : V_STREAM1 + small_m_rblocks(d, launch.strips16) - 1;
   return p;
 }
 
-// Waves of a split workgroup: 16 (which fill a CU) while every workgroup has a CU to itself, then 8, two workgroups
-// to a CU, then 4: with more workgroups than the chip holds at once the depth of the split matters less than what a
-// workgroup costs; no more than K has blocks of 128 columns.  Measured, us per call with 4 / 8 / 16 waves: a
-// 4096 x 4096 layer at 100 tokens (448 workgroups) - / 16.9 / 21.8; an OPT block at 16 tokens (576) 57 / 47 / 54, four
-// of them (2304) 131 / 125 / 178; with the bf16 tile a Llama block at 64 tokens (2800) 134 / 194 / -.
-static int split_waves(int64_t workgroups, int64_t longest_k) {
+// Waves of a split workgroup.  Four, because the sum over the waves and the loss are spread over them; eight where
+// each of them still has two subtiles of a 128-column block to itself; 16 for the longest K while every workgroup has a CU to itself.
+// One forward at 16 tokens, us with 4 / 8 / 16 waves: 512 x 512 4.2 / 4.5 / 5.6 (bands in four parts, as all of these but the last two), 2048 x 1024
+// 4.7 / 4.9 / 6.0, 4096 x 2048 5.7 / 5.5 / 7.1, 4096 x 4096 7.6 / 6.6 / 7.8, 4096 x 11008 16.2 / 12.2 / 11.9, 4096 x 16384
+// 26.1 / 18.8 / 16.5, 8192 x 8192 17.8 / 12.9 / 13.1, 16384 x 4096 13.6 / 11.8 / 12.1.  With more workgroups than the chip holds at
+// once the depth of the split matters less than what a workgroup costs: us per step, one Llama block with the bf16 tile at 64 tokens (2800)
+// 134 / 194 / -.  `part_rows`: rows of W of a workgroup.
+static int split_waves(int64_t workgroups, int64_t longest_k, int part_rows) {
   const int64_t blocks = (longest_k + 127) / 128;
-  const int most = workgroups <= 256 ? 16 : workgroups <= 2304 ? 8 : 4;
-  int w = 2;
-  while (w < most && w < blocks) w *= 2;
-  return w;
+  if (workgroups > 2304 || blocks * (part_rows / 16) < 16) return 4;
+  return workgroups <= 256 && blocks > 96 ? 16 : 8;
 }
 
 template <int MODE, int R, bool DUAL>
@@ -689,16 +706,17 @@ static int stream_once_rule(int slices, int64_t launch_code_bytes) {
 }
 
 // One launch of the matrices described by `a` (their table or the single one), `units` workgroups per slice.
-static int launch_plan(const FewPlan& p, int64_t units, int slices, int64_t longest_k, int64_t launch_code_bytes,
+static int launch_plan(const FewPlan& p, int64_t units, int slices, int64_t longest_k, int64_t most_rows, int64_t launch_code_bytes, int part_rows,
                        SmallArgs& a, hipStream_t stream) {
   if (units * slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
   a.slices = slices;
+  a.few_rows = most_rows <= 4;
   a.stream_once = stream_once_rule(slices, launch_code_bytes);
   const int wgs = (int)(units * slices);
   int rc = timing_begin(stream);
   if (rc != SZO_OK) return rc;
   if (p.split()) {
-    rc = split_launch(p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, split_waves(wgs, longest_k), wgs, a, stream);
+    rc = split_launch(p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, split_waves(wgs, longest_k, part_rows), wgs, a, stream);
     if (rc != SZO_OK) return rc;
   } else {
     const dim3 blocks((unsigned)wgs);
@@ -771,13 +789,14 @@ bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count,
   }
   return n > 0 && (all_stream || rounded_us(descs, n, true, forwards, separate) <= rounded_us(descs, n, false, forwards, separate));
 }
-static FewPlan plan_of_one(const szo_linear_desc* d, bool compact) {
+static FewPlan plan_of_one(const szo_linear_desc* d, Partials less) {
   LaunchShape shape;
   shape.add(d);
-  return few_plan(d, shape, false, compact);
+  return few_plan(d, shape, false, less);
 }
-int64_t small_m_partials(const szo_linear_desc* d, bool compact) {
-  const FewPlan p = plan_of_one(d, compact);
+int64_t small_m_partials(const szo_linear_desc* d, bool compact) { return small_m_launch_partials(d, compact ? kStreamKernel : kWholeBands); }
+int64_t small_m_launch_partials(const szo_linear_desc* d, Partials less) {
+  const FewPlan p = plan_of_one(d, less);
   return p.units(d) * p.slices(d);
 }
 
@@ -830,21 +849,22 @@ static int set_small_attrs() {
 }
 
 // One matrix, descriptor passed in the kernel arguments (no device table needed), as one launch.  In loss mode
-// slice i writes its partials behind those of slice i - 1, small_m_partials(d, compact) in all, scaled by 1 / (M N) of the
+// slice i writes its partials behind those of slice i - 1, small_m_launch_partials(d, less) in all, scaled by 1 / (M N) of the
 // whole matrix, so that their sum is the matrix's loss.  store_sign: the forward whose outputs are written to d->y, 0 = none.
 int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int store_sign, bool loss_mode,
-                       double* partial_plus, double* partial_minus, bool compact, hipStream_t stream) {
+                       double* partial_plus, double* partial_minus, Partials less, hipStream_t stream) {
   const int rc = set_small_attrs();
   if (rc != SZO_OK) return rc;
-  const FewPlan p = plan_of_one(d, compact);
+  const FewPlan p = plan_of_one(d, less);
   SmallArgs a{};
-  fill_mat(a.inl[0], d);                                       // whole matrix: the kernel offsets rows by slice
+  fill_mat(a.inl[0], d);
+  a.part_shifts = (uint32_t)p.part_shift;                                       // whole matrix: the kernel offsets rows by slice
   a.table = nullptr; a.n_mats = 1;
   a.store_sign = store_sign; a.loss_mode = loss_mode ? 1 : 0;
   a.seed = seed; a.step = step; a.eps = eps;
   a.partial_plus = partial_plus;
   a.partial_minus = partial_minus;
-  return launch_plan(p, p.units(d), p.slices(d), d->K, code_bytes(d), a, stream);
+  return launch_plan(p, p.units(d), p.slices(d), d->K, d->M, code_bytes(d), 64 >> p.part_shift, a, stream);
 }
 
 // When every workgroup of the update adds up the partials by itself instead of waiting for a launch that does: few partials,
@@ -869,7 +889,11 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   LaunchShape shape;
   for (int i = 0; i < n; ++i) shape.add(&descs[i]);
   // two activation sets (forward launches only): one block of rows for each, whatever the token count
-  auto plan_for = [&](const szo_linear_desc* d) { return few_plan(d, shape, do_forward && d->x_minus != nullptr); };
+  auto plan_for = [&](const szo_linear_desc* d) {
+    FewPlan p = few_plan(d, shape, do_forward && d->x_minus != nullptr);
+    if (n > kInlineMats) p.part_shift = 0;                  // (part_shifts belongs to the table in the arguments)
+    return p;
+  };
   if (small_m_table_bytes(n) > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;
   static thread_local std::vector<SmallMat> host_table;
   host_table.resize((size_t)std::max(n, 1));
@@ -883,7 +907,7 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   // One table entry per matrix; a launch has (units of its matrices) x (slices of its longest matrix)
   // workgroups (those past a matrix's last slice return at once), and slice i of a matrix writes its
   // loss partials behind those of slice i - 1.
-  struct ClassTotals { int entries = 0, slices = 0; int64_t units = 0, k = 0, code_bytes = 0; } classes[kClasses];
+  struct ClassTotals { int entries = 0, slices = 0; int64_t units = 0, k = 0, rows = 0, code_bytes = 0; int part_rows = 0; } classes[kClasses];
   int entries = 0;
   int64_t quads = 0, partials = 0;
   for (const auto& o : order) {
@@ -902,6 +926,8 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
     c.units += units;
     c.slices = std::max(c.slices, slices);
     c.k = std::max(c.k, d->K);
+    c.rows = std::max(c.rows, d->M);
+    c.part_rows = std::max(c.part_rows, 64 >> p.part_shift);
     if (live) c.code_bytes += code_bytes(d);
     ++c.entries;
     partials += units * slices;
@@ -925,9 +951,11 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
       const ClassTotals& c = classes[cls];
       if (c.units > 0 && c.slices > 0) {
         a.table = inl ? nullptr : tdev + first_entry;
+        a.part_shifts = 0;
         if (inl) std::copy(host + first_entry, host + first_entry + c.entries, a.inl);
+        for (int e = 0; inl && e < c.entries; ++e) a.part_shifts |= (uint32_t)plan_for(&descs[order[(size_t)(first_entry + e)].second]).part_shift << (4 * e);
         a.n_mats = c.entries;
-        rc = launch_plan(FewPlan::of_class(cls), c.units, c.slices, c.k, c.code_bytes, a, stream);
+        rc = launch_plan(FewPlan::of_class(cls), c.units, c.slices, c.k, c.rows, c.code_bytes, c.part_rows, a, stream);
         if (rc != SZO_OK) return rc;
       }
       first_entry += c.entries;

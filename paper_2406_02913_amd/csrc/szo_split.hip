@@ -9,15 +9,20 @@
 // before the epilogue.  More splits mean shorter chains; the whole sum stays inside one workgroup, so no second
 // kernel and no partial outputs in memory are needed.
 //
+// Where that leaves CUs idle, a band is cut further, into two or four workgroups of 32 or 16 rows (part_shifts, chosen by
+// split_part_shift): each stages x again and looks through the band's entries again, but dequantises only its own rows.
+//
 // The arithmetic is that of small_m_kernel: y(+-) = x dq^T + x v^T +- eps x z^T, un-centred codes with the block's
 // scale applied in fp32 for groups of 128, the sensitive entries as one-hot matrix products of 16 entries.
 // With several slices each of them reads the band's codes (neighbouring workgroups of one XCD, through its L2).
 //
-// Measured (us per call, stream kernel -> this one): a 4096 x 4096 forward at 1 / 16 / 100 / 224 tokens 30 / 31 / 32 /
-// 32 -> 9.9 / 11.6 / 16.9 / 29; a step over one OPT block at 1 / 16 tokens 128 / 130 -> 40 / 47; a step over a Llama
-// block with the bf16 tile at 16 tokens, which the tiled kernel ran before, 371 -> 62.  What is left at one layer is a
-// chain of a few memory round trips and the launch itself; from ~3000 workgroups on the x and the sums of every band
-// cost more than the stream kernel's idle waves.
+// Measured, us of GPU time per call in a graph, with whole bands and 16 waves -> cut bands, x staged for the token rows that
+// exist and two entries per lane: a 4096 x 4096 forward at 1 / 16 tokens 9.8 / 11.6 -> 5.3 / 6.6, 4096 x 16384 21.8 / 27.5 ->
+// 11.2 / 16.8, 16384 x 4096 (bands whole) 11.0 / 13.1 -> 9.5 / 11.8.  An empty launch takes 3.4 there; the rest is a chain of a few
+// memory round trips (table, tile bounds, entries, their columns of x) beside the dequantisation.  Against the stream
+// kernel: a step over one OPT block at 1 / 16 tokens 128 / 130 -> 31 / 36, a Llama block with the bf16 tile at 16 tokens,
+// which the tiled kernel ran before, 371 -> 62; from ~3000 workgroups on the x and the sums of every band cost more than
+// the stream kernel's idle waves.
 #include <atomic>
 #include <type_traits>
 #include "szo_few.h"
@@ -30,7 +35,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
-constexpr int SP_WIN = 256;             // sensitive entries computed per refill of a wave's window
+constexpr int SP_WIN = 128;             // sensitive entries computed per refill of a wave's window, two per lane
 constexpr int SP_MAX_WAVES = 16;
 constexpr int SP_XROW = 128 + 8;        // LDS row stride of a staged block of x, in 16-bit elements
 
@@ -92,31 +97,33 @@ template <bool DUAL, bool TILE_ROUND> constexpr int split_sets() { return TILE_R
 template <int MODE, bool DUAL, bool TILE_ROUND> constexpr int split_max_waves() {
   return MODE == SM_LUT || DUAL || TILE_ROUND ? 8 : SP_MAX_WAVES;
 }
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>
-__global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>())) band_split_kernel(SmallArgs a) {
+// SUBS: the workgroup's 16-row subtiles of the band.  XP: load instructions for 16 token rows of x, four rows each; with
+// XP = 1 rows 4..15 of the operands are whatever LDS held: they only reach output rows that do not exist.
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, int SUBS, int XP>
+__device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, const int bid, const int slice) {
   static_assert(!BF16 || (MODE == SM_PLAIN && TILE_ROUND), "bf16 tile: plain dequantisation, rounded as in the tile");
   constexpr bool FAST = MODE == SM_FAST, LUT = MODE == SM_LUT;
   constexpr int SETS = DUAL ? 2 : 1;
   constexpr int NACC = split_sets<DUAL, TILE_ROUND>();
-  constexpr int RED = NACC * 1024;                          // floats a wave leaves for the sum over the waves
+  constexpr int RED = NACC * 1024;                          // floats of LDS per wave: its window, its x, its accumulators
   constexpr int DENSE1 = TILE_ROUND ? 1 : 2;                // accumulator set of x2's dense product
   typedef SplitOps<BF16> Ops;
   typedef typename Ops::frag frag_t;
   extern __shared__ __attribute__((aligned(16))) float red[];                     // [waves][NACC][1024]
 
+  asm volatile("" : "+s"(index));                           // (the bodies read the entry one by one: read before the choice, it overflows the scalar registers)
+  const SmallMat mt = read_matrix(a, index);
+  if (slice * SM_ROWS >= mt.M) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
-  int bid = xcd_unit((int)blockIdx.x, (int)gridDim.x);
-  const int slice = bid % a.slices;
-  bid /= a.slices;
-  SmallMat mt = find_matrix(a, bid);
-  if (slice * SM_ROWS >= mt.M) return;
   const int N = mt.N, K = mt.K, M = min(SM_ROWS, mt.M - slice * SM_ROWS);
-  const int band = bid - mt.first_block, ktiles = K >> 6;
+  // this workgroup's rows: SUBS of the four 16-row subtiles of a band, from subtile sub0 on
+  constexpr int PIECES = 4 / SUBS;
+  const int band = (bid - mt.first_block) / PIECES, piece = (bid - mt.first_block) % PIECES, sub0 = piece * SUBS, ktiles = K >> 6;
   const size_t row0 = (size_t)slice * SM_ROWS;
   const auto g_x = SZO_GLOBAL(uint16_t, mt.x) + row0 * (size_t)K;
   const auto g_x2 = SZO_GLOBAL(uint16_t, DUAL ? mt.x2 : mt.x) + row0 * (size_t)K;
-  const auto g_q = SZO_GLOBAL(uint8_t, mt.qweight) + (size_t)band * (size_t)ktiles * 2048;
+  const auto g_q = SZO_GLOBAL(uint8_t, mt.qweight) + (size_t)band * (size_t)ktiles * 2048 + 512 * sub0;
   const auto g_scales = SZO_GLOBAL(uint16_t, mt.scales);
   const auto g_tile_ptr = SZO_GLOBAL(uint32_t, mt.tile_ptr) + (size_t)band * (size_t)ktiles;
   const auto g_sp_idx = SZO_GLOBAL(uint32_t, mt.sp_idx);
@@ -136,7 +143,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
   // LDS of the wave's own; rows past M repeat the last one and only reach output rows past M.
   const int xr_row = lane >> 4, xr_piece = lane & 15;       // load i: row 4 i + xr_row, columns 8 xr_piece ..
   const uint32_t xrow = (uint32_t)min(nn, M - 1) * (uint32_t)K * 2u; // operand row of this lane (sensitive entries), in bytes
-  u32x4 q[4], xr[SETS][4] = {};
+  u32x4 q[SUBS], xr[SETS][XP] = {};
   // Loads are a uniform base plus a 32-bit byte offset per lane (64-bit addresses per lane cost twice the registers).
   const auto b_x = (const uint8_t __attribute__((address_space(1)))*)g_x;
   const auto b_x2 = (const uint8_t __attribute__((address_space(1)))*)g_x2;
@@ -145,29 +152,29 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
     const uint32_t off = (uint32_t)min(2 * b + (jj >> 1), ktiles - 1) * 2048u + q_lane;
     q[s] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>(g_q + (size_t)off + 512 * s);
   };
-  uint32_t x_lane[4];
+  uint32_t x_lane[XP];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) x_lane[i] = (uint32_t)min(4 * i + xr_row, M - 1) * (uint32_t)K * 2u;
+  for (int i = 0; i < XP; ++i) x_lane[i] = (uint32_t)min(4 * i + xr_row, M - 1) * (uint32_t)K * 2u;
   auto load_x = [&](int b) {
     const uint32_t col = (uint32_t)min(128 * b + 8 * xr_piece, K - 8) * 2u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < XP; ++i)
 #pragma unroll
       for (int set = 0; set < SETS; ++set)
         xr[set][i] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>((set ? b_x2 : b_x) + (size_t)(x_lane[i] + col));
   };
   const int gshift = mt.group_shift, groups = FAST ? K >> 7 : LUT ? 0 : K >> gshift;
   const auto g_sc = (const uint8_t __attribute__((address_space(1)))*)(g_scales + (size_t)band * (size_t)groups * 64);
-  u32x2 sc = {0u, 0u};                                      // the lane's four scales of a group
+  uint64_t sc = 0u;                                         // the lane's scales of a group, subtile sub0's first
   auto load_scales = [&](int b) {
     if (LUT) return;
     const int g = FAST ? b : min((128 * b + 32 * jj) >> gshift, groups - 1);
-    sc = *reinterpret_cast<const u32x2 __attribute__((address_space(1)))*>(g_sc + (size_t)((uint32_t)g * 128u + 8u * (uint32_t)nn));
+    sc = *reinterpret_cast<const uint64_t __attribute__((address_space(1)))*>(g_sc + (size_t)((uint32_t)g * 128u + 8u * (uint32_t)nn));
   };
   uint32_t e_lo = 0, e_hi = 0;                              // this wave's sensitive entries
   if (b0 < b1) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) load_q(b0, s);
+    for (int s = 0; s < SUBS; ++s) load_q(b0, s);
     load_x(b0);
     load_scales(b0);
     if (mt.nnz > 0) {
@@ -175,17 +182,17 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
       e_hi = __builtin_amdgcn_readfirstlane(g_tile_ptr[min(2 * b1, ktiles)]);
     }
   }
-  uint32_t tb[LUT ? 4 : 1][8];
+  uint32_t tb[LUT ? SUBS : 1][8];
   if (LUT) {
 #pragma unroll
-    for (int s = 0; s < (LUT ? 4 : 1); ++s) load_lut_planes(g_scales + (size_t)min(band * 64 + 16 * s + nn, N - 1) * 16, tb[s]);
+    for (int s = 0; s < (LUT ? SUBS : 1); ++s) load_lut_planes(g_scales + (size_t)min(band * 64 + 16 * (sub0 + s) + nn, N - 1) * 16, tb[s]);
   }
 
-  float4_t acc[NACC][4];
+  float4_t acc[NACC][SUBS];
 #pragma unroll
   for (int i = 0; i < NACC; ++i)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) acc[i][s] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s = 0; s < SUBS; ++s) acc[i][s] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
   // ---- sensitive entries, while the first codes are on their way: 256 at a time into the wave's own part of LDS
   //      (its later accumulator area), then 16 per matrix product ----
@@ -195,28 +202,46 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
     uint16_t* const wv = wr + SP_WIN;                                                // 16-bit v | v + eps z
     uint16_t* const wz = wv + SP_WIN;                                                // 16-bit z | v - eps z
     for (uint32_t w0 = e_lo & ~3u; w0 < e_hi; w0 += SP_WIN) {
-      const uint32_t j = w0 + 4u * lane, last = mt.nnz - 1u;
-      uint32_t idx[4];
-      float val[4], z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      const uint32_t j = w0 + 2u * lane, last = mt.nnz - 1u;
+      uint32_t idx[2];
+      float val[2], z[2] = {0.0f, 0.0f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t je = min(j + e, last);               // clamped; entries past the end are never consumed
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t je = min(j + e, last);               // clamped; entries past the end are left out
         idx[e] = g_sp_idx[je];
         val[e] = g_sp_val[je];
       }
-      if (with_z) zbar_quad((mt.nnz_base + j) >> 2, a.seed, a.step, z);
+      if (with_z) zbar_pair((mt.nnz_base + j) >> 2, (j & 2u) != 0u, a.seed, a.step, z);
+      // A part of a band keeps those of its own rows, one after the other, in order; a whole band keeps all of them where they
+      // stand and counts those of this wave's columns, lo .. hi of the window.
+      uint32_t row[2], at = SUBS == 4 ? 2u * lane : 0u;
+      uint32_t lo = SUBS == 4 ? max(e_lo, w0) - w0 : 0u, hi = SUBS == 4 ? min(e_hi - w0, (uint32_t)SP_WIN) : 0u;
+      bool in[2];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < 2; ++e) {
         const uint32_t n = sm_fast_div(idx[e], mt.div_mul, mt.div_shift);
-        wk[4 * lane + e] = idx[e] - n * (uint32_t)K;
-        wr[4 * lane + e] = (uint16_t)(n - (uint32_t)(band * 64));
-        wv[4 * lane + e] = Ops::narrow(TILE_ROUND ? fmaf(a.eps, z[e], val[e]) : val[e]);
-        wz[4 * lane + e] = Ops::narrow(TILE_ROUND ? fmaf(-a.eps, z[e], val[e]) : z[e]);
+        row[e] = n - (uint32_t)(band * 64 + 16 * sub0);
+        idx[e] -= n * (uint32_t)K;
+        in[e] = SUBS == 4 || (j + e >= e_lo && j + e < e_hi && row[e] < (uint32_t)(16 * SUBS));
+        if (SUBS < 4) {
+          const uint64_t m = __ballot(in[e]);
+          at += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+          hi += (uint32_t)__popcll(m);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        if (in[e]) {
+          wk[at] = idx[e];
+          wr[at] = (uint16_t)row[e];
+          wv[at] = Ops::narrow(TILE_ROUND ? fmaf(a.eps, z[e], val[e]) : val[e]);
+          wz[at] = Ops::narrow(TILE_ROUND ? fmaf(-a.eps, z[e], val[e]) : z[e]);
+          ++at;
+        }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // window visible to the other lanes of the wave
-      const uint32_t hi = min(e_hi, w0 + (uint32_t)SP_WIN);
-      for (uint32_t g0 = w0; g0 < hi; g0 += 16u) {
-        const uint32_t at = g0 - w0 + 4u * (uint32_t)jj;
+      for (uint32_t g0 = 0; g0 < hi; g0 += 16u) {
+        const uint32_t at = g0 + 4u * (uint32_t)jj;
         const u32x4 kw = *reinterpret_cast<const u32x4*>(wk + at);
         const u32x2 rw = *reinterpret_cast<const u32x2*>(wr + at);
         const u32x2 vw = *reinterpret_cast<const u32x2*>(wv + at);
@@ -225,8 +250,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
         uint16_t ax[SETS][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {                       // every gather requested before the first is used
-          const uint32_t e = w0 + at + (uint32_t)i;
-          const uint32_t col = e >= e_lo && e < hi ? kw[i] : 0u;   // entries of other waves: a valid address, masked below
+          const uint32_t e = at + (uint32_t)i, col = e >= lo && e < hi ? kw[i] : 0u;   // not an entry of this wave: a valid address, masked below
 #pragma unroll
           for (int set = 0; set < SETS; ++set)
             ax[set][i] = *reinterpret_cast<const uint16_t __attribute__((address_space(1)))*>((set ? b_x2 : b_x) + (size_t)(xrow + 2u * col));
@@ -234,8 +258,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const uint32_t e = w0 + at + (uint32_t)i;
-          one_hot_entry((rw[i >> 1] >> (16 * (i & 1))) & 63u, nn, e >= e_lo && e < hi, mlo[i], mhi[i]);
+          one_hot_entry((rw[i >> 1] >> (16 * (i & 1))) & 63u, nn, at + (uint32_t)i >= lo && at + (uint32_t)i < hi, mlo[i], mhi[i]);
 #pragma unroll
           for (int set = 0; set < SETS; ++set) ax[set][i] = Ops::activation(ax[set][i]);
         }
@@ -244,7 +267,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
         for (int set = 0; set < SETS; ++set)
           xw[set] = u32x2{(uint32_t)ax[set][0] | ((uint32_t)ax[set][1] << 16), (uint32_t)ax[set][2] | ((uint32_t)ax[set][3] << 16)};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < SUBS; ++s) {
           u32x2 bv, bz;
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
@@ -284,7 +307,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
 #pragma unroll
     for (int set = 0; set < SETS; ++set) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < XP; ++i)
         *reinterpret_cast<frag_t*>(xs + (4 * i + xr_row) * SP_XROW + 8 * xr_piece) =
             Ops::activations(empty ? u32x4{0u, 0u, 0u, 0u} : xr[set][i]);
       asm volatile("" ::: "memory");                        // written by the wave's other lanes; LDS keeps a wave's order
@@ -293,7 +316,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
       asm volatile("" ::: "memory");
     }
     if (MORE) load_x(b + 1);
-    const half4_t sh4 = __builtin_bit_cast(half4_t, sc);
+    const half4_t sh4 = __builtin_bit_cast(half4_t, SUBS == 4 ? sc : sc >> (16 * sub0));
     if (MORE) load_scales(b + 1);
     float4_t init[SETS];
 #pragma unroll
@@ -305,7 +328,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
       }
     }
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < SUBS; ++s) {
       const u32x4 qs = q[s];
       if (MORE) load_q(b + 1, s);
       float4_t tmp[SETS];
@@ -342,7 +365,7 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
 #pragma unroll
     for (int i = 0; i < NACC; ++i)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) mine[i * 256 + s * 64 + lane] = acc[i][s];
+      for (int s = 0; s < SUBS; ++s) mine[i * 256 + s * 64 + lane] = acc[i][s];
   }
   __syncthreads();
   // Output o of 1024: column o & 15 of subtile o >> 8, token row (o >> 4) & 15; its accumulator sits in register
@@ -355,9 +378,9 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
     WeightSource source;
     global_u16 x_plus, x_minus;
     if constexpr (AGAIN) {
-      int unit = bid;                                       // the entry is read again (laundered: not kept for this)
-      asm volatile("" : "+s"(unit));
-      const SmallMat ms = find_matrix(a, unit);
+      int again = index;                                    // the entry is read again (laundered: not kept for this)
+      asm volatile("" : "+s"(again));
+      const SmallMat ms = read_matrix(a, again);
       source = WeightSource{(global_u8)ms.qweight, LUT ? nullptr : (global_u16)ms.scales, LUT ? (global_u16)ms.scales : nullptr,
                             (global_u32)ms.tile_ptr, (global_u32)ms.sp_idx, (global_f32)ms.sp_val, ms.K, ms.group_shift,
                             ms.nnz, ms.nnz_base, a.seed, a.step};
@@ -365,8 +388,8 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
       x_minus = (global_u16)(DUAL ? ms.x2 : ms.x) + (size_t)slice * SM_ROWS * (size_t)ms.K;
     }
     lp = 0.0; lm = 0.0;
-    for (int o = tid; o < 1024; o += (int)blockDim.x) {
-      const int m = (o >> 4) & 15, n = band * 64 + 16 * (o >> 8) + (o & 15);
+    for (int o = tid; o < 256 * SUBS; o += (int)blockDim.x) {
+      const int m = (o >> 4) & 15, n = band * 64 + 16 * (sub0 + (o >> 8)) + (o & 15);
       if (m >= M || n >= N) continue;
       const float* p = red + (o >> 8) * 256 + ((m >> 2) * 16 + (o & 15)) * 4 + (m & 3);
       float t = 0.0f;
@@ -412,11 +435,28 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
     if (tid == 0) {
       double bp = 0.0, bm = 0.0;
       for (int w = 0; w < waves; ++w) { bp += part[0][w]; bm += part[1][w]; }
-      const int pi = mt.partial_base + slice * ((N + 63) >> 6) + band;
+      const int pi = mt.partial_base + (slice * ((N + 63) >> 6) + band) * PIECES + piece;
       ((double __attribute__((address_space(1)))*)a.partial_plus)[pi] = bp * mt.loss_scale;
       ((double __attribute__((address_space(1)))*)a.partial_minus)[pi] = bm * mt.loss_scale;
     }
   }
+}
+
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>
+__global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>())) band_split_kernel(SmallArgs a) {
+  int bid = xcd_unit((int)blockIdx.x, (int)gridDim.x);
+  const int slice = bid % a.slices;
+  bid /= a.slices;
+  const int index = find_index(a, bid);
+  const uint32_t part_shift = (a.part_shifts >> (4 * (index & 7))) & 15u;
+  auto run = [&](auto rows_tag) {
+    constexpr int XP = decltype(rows_tag)::value;
+    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, 4, XP>(a, index, bid, slice);
+    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, 2, XP>(a, index, bid, slice);
+    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, 1, XP>(a, index, bid, slice);
+  };
+  if (MODE == SM_FAST && !DUAL && a.few_rows) run(std::integral_constant<int, 1>{});
+  else run(std::integral_constant<int, 4>{});
 }
 
 template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>

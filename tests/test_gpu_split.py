@@ -109,6 +109,40 @@ def test_stream_kernel_still_matches_oracle_and_the_split_kernel():
     assert rel_fro(ys[9], want) <= 5e-4 and rel_fro(ys[8], ys[9]) <= 2e-6      # same products, other summation order
 
 
+# (seed, M, N, K, group, density, format, tile): bands x slices of up to 64 / 128 / more are cut into four / two / one workgroups each
+@pytest.mark.parametrize("shape", [
+    (251, 4, 64 * 64, 128, 128, 5e-3, "uniform", "f16"),      # 64 bands: the last with four parts, x staged for up to four rows
+    (252, 5, 64 * 64 + 1, 128, 128, 5e-3, "uniform", "f16"),  # 65: two parts, the last band of one row
+    (253, 3, 64 * 129 - 63, 256, 128, 2e-3, "uniform", "f16"),   # 129: whole bands, three rows
+    (254, 33, 64 * 43, 256, 128, 2e-3, "uniform", "f16"),     # three slices, the last of one row: 129
+    (255, 17, 64 * 40, 384, 64, 3e-3, "uniform", "bf16"),     # two parts, sensitive weights rounded in the tile
+    (256, 130, 500, 8192, 128, 1e-3, "uniform", "f16"),       # 72 and a K of 64 blocks
+    (257, 144, 1000, 8192, 128, 1e-3, "uniform", "f16"),      # 144, cut in two for the length of K's chain alone
+    (258, 16, 100, 640, 128, 8e-2, "lut", "f16"),             # four parts, several windows of entries per wave
+], ids=lambda s: str(s[0]))
+def test_bands_cut_into_parts_match_oracle(shape):
+    s, M, N, K, G, dens, fmt, tile = shape
+    szo.szo_set_tile_config(8)
+    o, d = make_pair(s, M, N, K, G, dens, nnz_base=8, fmt=fmt)
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    z = ophilox.zbar(5, 2, 8, o.sp_idx.size)
+    rounded = tile == "bf16"                             # the bounds are those of test_forward_matches_oracle
+    want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, G, o.sp_idx, o.sp_val, z, +1, 1e-3, "D" if rounded else "E",
+                             *((tile,) if rounded else ()), **({} if rounded else {"lut": o.lut}))
+    d.y.fill_(float("nan"))
+    szo.szo_linear_fwd(d.desc(tile_dtype=dt), 5, 2, +1, 1e-3)
+    y = d.y.cpu().numpy()
+    assert np.isfinite(y).all() and rel_fro(y, want) <= (2e-5 if rounded else 5e-4 if fmt == "uniform" else 1e-3)
+    # one loss partial per workgroup: none of them lost or added twice
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    szo.szo_linear_fwd_mse(d.desc(tile_dtype=dt), 5, 2, +1, 1e-3, 1.0 / (M * N), loss, szo.new_workspace())
+    mine = float(((d.y.double() - d.target.double()) ** 2).mean().item())
+    assert abs(loss.item() - mine) <= 1e-6 * mine
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_zo_step([d.desc(tile_dtype=dt, with_y=False)], 5, 2, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+    assert abs(scal[0].item() - mine) <= 1e-6 * mine
+
+
 def test_noalloc_falls_back_to_fewer_partials():
     """A step whose split launches would write more loss partials than the fixed array holds keeps working."""
     szo.szo_set_tile_config(0)
