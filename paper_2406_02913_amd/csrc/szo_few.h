@@ -194,7 +194,14 @@ __device__ __forceinline__ void one_hot_entry(uint32_t row, int nn, bool counts,
   mhi = mine ? (uint32_t)(m >> 32) : 0u;
 }
 
-// Launches of the split kernel (szo_split.hip).  `waves` waves per workgroup, one workgroup per band and slice.
-int split_launch(int mode, bool dual, bool bf16, bool tile_round, int waves, int workgroups, const SmallArgs& a, hipStream_t stream);
+// One launch of the split kernel (szo_split.hip): a workgroup per band or part of one and slice of 16 token rows.
+struct SplitLaunch {
+  int mode;                 // SM_*
+  bool dual, bf16, tile_round;
+  bool one;                 // only the "+" forward is wanted (used by tile_round)
+  int subs;                 // most subtiles of a workgroup: 4 >> the smallest part shift of the launch
+  int waves, workgroups;
+};
+int split_launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream);
 
 }  // namespace szo

@@ -1058,7 +1058,7 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
       rc = onepass_one(d, seed, step, eps, part + off, part + T + off, s);
       off += onepass_tiles(d);
     } else if (few_all) {
-      rc = small_m_launch_one(d, seed, step, eps, 0, true, part + off, part + T + off, less, s);
+      rc = small_m_launch_one(d, seed, step, eps, 0, true, true, part + off, part + T + off, less, s);
       off += small_m_launch_partials(d, less);
     } else {
       const double scale = 1.0 / ((double)d->M * (double)d->N);
@@ -1092,7 +1092,7 @@ int szo_linear_fwd(const szo_linear_desc* desc, uint64_t seed, uint64_t step, in
   if (rc != SZO_OK) return rc;
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
   if (few_token_enabled() && small_m_eligible(desc, 1, false, false, 1))
-    return small_m_launch_one(desc, seed, step, sign == 0 ? 0.0f : eps, sign == 0 ? 1 : sign, false, nullptr, nullptr,
+    return small_m_launch_one(desc, seed, step, sign == 0 ? 0.0f : eps, sign == 0 ? 1 : sign, false, false, nullptr, nullptr,
                               kBandsInParts, (hipStream_t)stream);
   return run_forward(desc, seed, step, sign, eps, nullptr, 0.0, (hipStream_t)stream);
 }
@@ -1108,7 +1108,7 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   const bool few = few_token_enabled() && small_m_eligible(desc, 1, false, false, 1) && scale == 1.0 / ((double)desc->M * (double)desc->N);
   const int64_t nb = few ? small_m_launch_partials(desc, kBandsInParts) : 0;
   if (few && 2 * nb <= kMaxLossPartials) {
-    rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, partial_area(workspace),
+    rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, false, partial_area(workspace),
                             partial_area(workspace) + nb, kBandsInParts, (hipStream_t)stream);
     if (rc != SZO_OK) return rc;
     return reduce_partials(partial_area(workspace), (int)nb, 1.0, loss_acc, (hipStream_t)stream);

@@ -63,7 +63,7 @@ void small_m_force_split(int how);                          // testing hook: 1 =
 void small_m_force_rblocks(int r);                         // testing hook: 0 = choose; 2, 3 = 32 / 48 token rows per pass wherever M > 16
 void small_m_force_stream_once(bool on);                    // testing hook: non-temporal code stream in every one-slice launch
 size_t small_m_table_bytes(int n);
-int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int store_sign, bool loss_mode,
+int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int store_sign, bool loss_mode, bool both_signs,
                        double* partial_plus, double* partial_minus, Partials less, hipStream_t stream);
 int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,
                  void* table_dev, double* partial_plus, int64_t partials_per_sign, double* scalars, bool do_forward,

@@ -675,11 +675,14 @@ static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, boo
 // One forward at 16 tokens, us with 4 / 8 / 16 waves: 512 x 512 4.2 / 4.5 / 5.6 (bands in four parts, as all of these but the last two), 2048 x 1024
 // 4.7 / 4.9 / 6.0, 4096 x 2048 5.7 / 5.5 / 7.1, 4096 x 4096 7.6 / 6.6 / 7.8, 4096 x 11008 16.2 / 12.2 / 11.9, 4096 x 16384
 // 26.1 / 18.8 / 16.5, 8192 x 8192 17.8 / 12.9 / 13.1, 16384 x 4096 13.6 / 11.8 / 12.1.  With more workgroups than the chip holds at
-// once the depth of the split matters less than what a workgroup costs: us per step, one Llama block with the bf16 tile at 64 tokens (2800)
-// 134 / 194 / -.  `part_rows`: rows of W of a workgroup.
-static int split_waves(int64_t workgroups, int64_t longest_k, int part_rows) {
-  const int64_t blocks = (longest_k + 127) / 128;
-  if (workgroups > 2304 || blocks * (part_rows / 16) < 16) return 4;
+// once the depth of the split matters less than what a workgroup costs.  us per step with 4 / 8 waves: one Llama block at 16 / 24 /
+// 48 tokens (664 / 1328 / 1992 workgroups) 43.5 / 36.3, 55.1 / 57.1, 70.5 / 77.3, one OPT block at 64 tokens (2304) 83 / 93; with the
+// sensitive weights rounded as in the tile for both signs, where the registers of eight waves leave no room for a second
+// workgroup on a CU, a 5000 x 4160 layer at 48 / 77 tokens (237 / 395) 23.5 / 22.1, 30.8 / 35.3, a Llama block at 48 tokens 89 / 130.
+// `subs`: 16-row subtiles of a workgroup.
+static int split_waves(const FewPlan& p, bool one_sign, int64_t workgroups, int64_t longest_k, int subs) {
+  const int64_t blocks = (longest_k + 127) / 128, wide = p.dual() ? 2304 : p.dequant >= D_TILE_F16 && !one_sign ? 256 : 1024;
+  if (workgroups > wide || blocks * subs < 16) return 4;
   return workgroups <= 256 && blocks > 96 ? 16 : 8;
 }
 
@@ -705,18 +708,30 @@ static int stream_once_rule(int slices, int64_t launch_code_bytes) {
   return slices == 1 && (g_force_stream_once || launch_code_bytes > kLastLevelCacheBytes);
 }
 
-// One launch of the matrices described by `a` (their table or the single one), `units` workgroups per slice.
-static int launch_plan(const FewPlan& p, int64_t units, int slices, int64_t longest_k, int64_t most_rows, int64_t launch_code_bytes, int part_rows,
-                       SmallArgs& a, hipStream_t stream) {
-  if (units * slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
-  a.slices = slices;
-  a.few_rows = most_rows <= 4;
-  a.stream_once = stream_once_rule(slices, launch_code_bytes);
-  const int wgs = (int)(units * slices);
+struct LaunchTotals {                                       // over a launch's matrices
+  int slices = 0, subs = 1;                                 // most slices; most 16-row subtiles of a split workgroup
+  int64_t units = 0, k = 0, rows = 0, code_bytes = 0;       // workgroups per slice, longest K, most token rows, codes
+  void add(const FewPlan& p, const szo_linear_desc* d) {
+    slices = std::max(slices, p.slices(d));
+    subs = std::max(subs, 4 >> p.part_shift);
+    units += p.units(d);
+    k = std::max(k, d->K);
+    rows = std::max(rows, d->M);
+    code_bytes += ::szo::code_bytes(d);
+  }
+};
+// One launch of the matrices described by `a` (their table or the single one).
+static int launch_plan(const FewPlan& p, const LaunchTotals& t, bool one_sign, SmallArgs& a, hipStream_t stream) {
+  if (t.units * t.slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
+  a.slices = t.slices;
+  a.few_rows = t.rows <= 4;
+  a.stream_once = stream_once_rule(t.slices, t.code_bytes);
+  const int wgs = (int)(t.units * t.slices);
   int rc = timing_begin(stream);
   if (rc != SZO_OK) return rc;
   if (p.split()) {
-    rc = split_launch(p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, split_waves(wgs, longest_k, part_rows), wgs, a, stream);
+    rc = split_launch(SplitLaunch{p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, one_sign, t.subs,
+                                  split_waves(p, one_sign, wgs, t.k, t.subs), wgs}, a, stream);
     if (rc != SZO_OK) return rc;
   } else {
     const dim3 blocks((unsigned)wgs);
@@ -852,7 +867,7 @@ static int set_small_attrs() {
 // slice i writes its partials behind those of slice i - 1, small_m_launch_partials(d, less) in all, scaled by 1 / (M N) of the
 // whole matrix, so that their sum is the matrix's loss.  store_sign: the forward whose outputs are written to d->y, 0 = none.
 int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float eps, int store_sign, bool loss_mode,
-                       double* partial_plus, double* partial_minus, Partials less, hipStream_t stream) {
+                       bool both_signs, double* partial_plus, double* partial_minus, Partials less, hipStream_t stream) {
   const int rc = set_small_attrs();
   if (rc != SZO_OK) return rc;
   const FewPlan p = plan_of_one(d, less);
@@ -862,9 +877,12 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   a.table = nullptr; a.n_mats = 1;
   a.store_sign = store_sign; a.loss_mode = loss_mode ? 1 : 0;
   a.seed = seed; a.step = step; a.eps = eps;
+  if (!both_signs && store_sign < 0) { a.eps = -eps; a.store_sign = 1; }     // the wanted forward is the "+" one
   a.partial_plus = partial_plus;
   a.partial_minus = partial_minus;
-  return launch_plan(p, p.units(d), p.slices(d), d->K, d->M, code_bytes(d), 64 >> p.part_shift, a, stream);
+  LaunchTotals t;
+  t.add(p, d);
+  return launch_plan(p, t, !both_signs, a, stream);
 }
 
 // When every workgroup of the update adds up the partials by itself instead of waiting for a launch that does: few partials,
@@ -907,7 +925,7 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
   // One table entry per matrix; a launch has (units of its matrices) x (slices of its longest matrix)
   // workgroups (those past a matrix's last slice return at once), and slice i of a matrix writes its
   // loss partials behind those of slice i - 1.
-  struct ClassTotals { int entries = 0, slices = 0; int64_t units = 0, k = 0, rows = 0, code_bytes = 0; int part_rows = 0; } classes[kClasses];
+  struct ClassTotals : LaunchTotals { int entries = 0; } classes[kClasses];
   int entries = 0;
   int64_t quads = 0, partials = 0;
   for (const auto& o : order) {
@@ -923,12 +941,7 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
     m.first_block = (int)c.units;
     m.partial_base = (int)partials;
     m.first_quad = quads;
-    c.units += units;
-    c.slices = std::max(c.slices, slices);
-    c.k = std::max(c.k, d->K);
-    c.rows = std::max(c.rows, d->M);
-    c.part_rows = std::max(c.part_rows, 64 >> p.part_shift);
-    if (live) c.code_bytes += code_bytes(d);
+    if (live) c.add(p, d);
     ++c.entries;
     partials += units * slices;
     quads += (((int64_t)d->nnz + 3) / 4 + 63) & ~(int64_t)63;      // a wave of the update serves one matrix
@@ -955,7 +968,7 @@ int small_m_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t st
         if (inl) std::copy(host + first_entry, host + first_entry + c.entries, a.inl);
         for (int e = 0; inl && e < c.entries; ++e) a.part_shifts |= (uint32_t)plan_for(&descs[order[(size_t)(first_entry + e)].second]).part_shift << (4 * e);
         a.n_mats = c.entries;
-        rc = launch_plan(FewPlan::of_class(cls), c.units, c.slices, c.k, c.rows, c.code_bytes, c.part_rows, a, stream);
+        rc = launch_plan(FewPlan::of_class(cls), c, false, a, stream);
         if (rc != SZO_OK) return rc;
       }
       first_entry += c.entries;

@@ -73,13 +73,23 @@ template <> struct SplitOps<true> {
   }
 };
 
-// Eight codes -> eight bf16 weights (c - 8) s in natural order, each rounded once.
-__device__ __forceinline__ bf16x8_t dequant_word_bf16(uint32_t q, float s) {
-  const float m8s = -8.0f * s;
+// Eight codes -> eight bf16 weights (c - 8) s in natural order, each rounded once.  Two nibbles at a time become 1024 + c and
+// 64 + c in fp16 (as in sm_dequant_word); a mixed-precision fma takes them to (c - 8) s, exact in fp32: 17 instructions, where
+// extracting and converting every code by itself took 28.
+__device__ __forceinline__ bf16x8_t dequant_word_bf16(uint32_t q, _Float16 s) {
+  const float sf = (float)s, off_lo = -1032.0f * sf, off_hi = -72.0f * sf;       // exact: 11 bits times 11 and 4
+  half2_t h[4];                                             // codes (0,4) (1,5) (2,6) (3,7)
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const uint32_t src = p ? q >> 8 : q;
+    h[2 * p] = __builtin_bit_cast(half2_t, (src & 0x000F000Fu) | 0x64006400u);
+    h[2 * p + 1] = __builtin_bit_cast(half2_t, (src & 0x00F000F0u) | 0x54005400u);
+  }
+  auto weight = [&](int e) { return fmaf((float)h[e & 3][e >> 2], sf, e & 1 ? off_hi : off_lo); };
   u32x4 o;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const float2_t f = {fmaf((float)((q >> (8 * w)) & 15u), s, m8s), fmaf((float)((q >> (8 * w + 4)) & 15u), s, m8s)};
+    const float2_t f = {weight(2 * w), weight(2 * w + 1)};
     o[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
   }
   return __builtin_bit_cast(bf16x8_t, o);
@@ -93,23 +103,30 @@ __device__ __forceinline__ bf16x8_t dequant_word_bf16(uint32_t q, float s) {
 // Accumulator sets:            one set of x                       two sets (DUAL)
 //   v and z apart              0: dense + x v^T  1: x z^T         0, 1: the same of x   2, 3: of x2
 //   TILE_ROUND                 0: dense  1: x w+^T  2: x w-^T     0: dense + x w+^T     1: dense + x w-^T of x2
-template <bool DUAL, bool TILE_ROUND> constexpr int split_sets() { return TILE_ROUND ? (DUAL ? 2 : 3) : (DUAL ? 4 : 2); }
+//   TILE_ROUND, ONE sign       0: dense + x w+^T
+template <bool DUAL, bool TILE_ROUND, bool ONE> constexpr int split_sets() { return TILE_ROUND ? (ONE ? 1 : DUAL ? 2 : 3) : (DUAL ? 4 : 2); }
 template <int MODE, bool DUAL, bool TILE_ROUND> constexpr int split_max_waves() {
   return MODE == SM_LUT || DUAL || TILE_ROUND ? 8 : SP_MAX_WAVES;
 }
-// SUBS: the workgroup's 16-row subtiles of the band.  XP: load instructions for 16 token rows of x, four rows each; with
+// Floats of LDS per wave: its window of entries, then its x, then its accumulators of `subs` subtiles.
+constexpr int split_wave_floats(int nacc, int subs) {
+  const int acc = nacc * subs * 256, x = (16 * SP_XROW * 2 + 15) / 16 * 4;
+  return acc > x ? acc : x;
+}
+// SUBS: the workgroup's 16-row subtiles of the band.   XP: load instructions for 16 token rows of x, four rows each; with
 // XP = 1 rows 4..15 of the operands are whatever LDS held: they only reach output rows that do not exist.
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, int SUBS, int XP>
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE, int SUBS, int XP>
 __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, const int bid, const int slice) {
   static_assert(!BF16 || (MODE == SM_PLAIN && TILE_ROUND), "bf16 tile: plain dequantisation, rounded as in the tile");
   constexpr bool FAST = MODE == SM_FAST, LUT = MODE == SM_LUT;
+  static_assert(!ONE || (TILE_ROUND && !DUAL), "instantiations");
   constexpr int SETS = DUAL ? 2 : 1;
-  constexpr int NACC = split_sets<DUAL, TILE_ROUND>();
-  constexpr int RED = NACC * 1024;                          // floats of LDS per wave: its window, its x, its accumulators
+  constexpr int NACC = split_sets<DUAL, TILE_ROUND, ONE>();
+  constexpr int RED = split_wave_floats(NACC, SUBS);
   constexpr int DENSE1 = TILE_ROUND ? 1 : 2;                // accumulator set of x2's dense product
   typedef SplitOps<BF16> Ops;
   typedef typename Ops::frag frag_t;
-  extern __shared__ __attribute__((aligned(16))) float red[];                     // [waves][NACC][1024]
+  extern __shared__ __attribute__((aligned(16))) float red[];                     // [waves][RED]
 
   asm volatile("" : "+s"(index));                           // (the bodies read the entry one by one: read before the choice, it overflows the scalar registers)
   const SmallMat mt = read_matrix(a, index);
@@ -142,7 +159,8 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
   // against 64 if every lane fetched the pieces of its own operand row) and turned into operands through 4 KB of
   // LDS of the wave's own; rows past M repeat the last one and only reach output rows past M.
   const int xr_row = lane >> 4, xr_piece = lane & 15;       // load i: row 4 i + xr_row, columns 8 xr_piece ..
-  const uint32_t xrow = (uint32_t)min(nn, M - 1) * (uint32_t)K * 2u; // operand row of this lane (sensitive entries), in bytes
+  const uint32_t row_bytes = (uint32_t)K * 2u, last_row = (uint32_t)(M - 1) * row_bytes;
+  const uint32_t xrow = min((uint32_t)nn * row_bytes, last_row);   // operand row of this lane (sensitive entries), in bytes
   u32x4 q[SUBS], xr[SETS][XP] = {};
   // Loads are a uniform base plus a 32-bit byte offset per lane (64-bit addresses per lane cost twice the registers).
   const auto b_x = (const uint8_t __attribute__((address_space(1)))*)g_x;
@@ -152,16 +170,15 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
     const uint32_t off = (uint32_t)min(2 * b + (jj >> 1), ktiles - 1) * 2048u + q_lane;
     q[s] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>(g_q + (size_t)off + 512 * s);
   };
-  uint32_t x_lane[XP];
-#pragma unroll
-  for (int i = 0; i < XP; ++i) x_lane[i] = (uint32_t)min(4 * i + xr_row, M - 1) * (uint32_t)K * 2u;
+  const uint32_t x_lane = (uint32_t)xr_row * row_bytes;
   auto load_x = [&](int b) {
     const uint32_t col = (uint32_t)min(128 * b + 8 * xr_piece, K - 8) * 2u;
 #pragma unroll
     for (int i = 0; i < XP; ++i)
 #pragma unroll
       for (int set = 0; set < SETS; ++set)
-        xr[set][i] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>((set ? b_x2 : b_x) + (size_t)(x_lane[i] + col));
+        xr[set][i] = *reinterpret_cast<const u32x4 __attribute__((address_space(1)))*>(
+            (set ? b_x2 : b_x) + (size_t)(min(x_lane + (uint32_t)(4 * i) * row_bytes, last_row) + col));
   };
   const int gshift = mt.group_shift, groups = FAST ? K >> 7 : LUT ? 0 : K >> gshift;
   const auto g_sc = (const uint8_t __attribute__((address_space(1)))*)(g_scales + (size_t)band * (size_t)groups * 64);
@@ -253,7 +270,8 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
           const uint32_t e = at + (uint32_t)i, col = e >= lo && e < hi ? kw[i] : 0u;   // not an entry of this wave: a valid address, masked below
 #pragma unroll
           for (int set = 0; set < SETS; ++set)
-            ax[set][i] = *reinterpret_cast<const uint16_t __attribute__((address_space(1)))*>((set ? b_x2 : b_x) + (size_t)(xrow + 2u * col));
+            ax[set][i] = *reinterpret_cast<const uint16_t __attribute__((address_space(1)))*>(
+                (set ? b_x2 : b_x) + (size_t)(xrow + 2u * col));
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -277,9 +295,9 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
             bz[h] = zw[h] & mask;
           }
           if constexpr (TILE_ROUND) {
-            constexpr int PLUS = DUAL ? 0 : 1;
+            constexpr int PLUS = DUAL || ONE ? 0 : 1;
             acc[PLUS][s] = Ops::sparse(xw[0], bv, acc[PLUS][s]);
-            acc[PLUS + 1][s] = Ops::sparse(xw[SETS - 1], bz, acc[PLUS + 1][s]);
+            if constexpr (!ONE) acc[PLUS + 1][s] = Ops::sparse(xw[SETS - 1], bz, acc[PLUS + 1][s]);
           } else {
 #pragma unroll
             for (int set = 0; set < SETS; ++set) {
@@ -337,7 +355,7 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         frag_t w;
-        if constexpr (BF16) w = dequant_word_bf16(qs[t], (float)sh4[s]);
+        if constexpr (BF16) w = dequant_word_bf16(qs[t], sh4[s]);
         else if constexpr (LUT) w = sm_lut_word(qs[t], tb[s]);
         else w = sm_dequant_word<FAST>(qs[t], magic_lo, magic_hi, half2_t{sh4[s], sh4[s]});
 #pragma unroll
@@ -365,11 +383,11 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
 #pragma unroll
     for (int i = 0; i < NACC; ++i)
 #pragma unroll
-      for (int s = 0; s < SUBS; ++s) mine[i * 256 + s * 64 + lane] = acc[i][s];
+      for (int s = 0; s < SUBS; ++s) mine[i * 64 * SUBS + s * 64 + lane] = acc[i][s];
   }
   __syncthreads();
-  // Output o of 1024: column o & 15 of subtile o >> 8, token row (o >> 4) & 15; its accumulator sits in register
-  // m & 3 of lane 16 (m >> 2) + column.  Wave-wide LDS reads touch every bank once, y is stored 64 bytes at a time.
+  // Output o: column o & 15 of subtile o >> 8, token row (o >> 4) & 15; its accumulator sits in register m & 3 of lane
+  // 16 (m >> 2) + column.  Wave-wide LDS reads touch every bank once, y is stored 64 bytes at a time.
   double lp = 0.0, lm = 0.0;
   bool all_finite = true;
   // AGAIN: a second time, with the outputs of token rows that hold an infinite or NaN activation by their definition
@@ -399,15 +417,15 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
       for (int i = 0; i < NACC; ++i) d[i] = 0.0f;
       for (int w = 0; w < waves; ++w, p += RED) {
 #pragma unroll
-        for (int i = 0; i < NACC; ++i) d[i] += p[i * 1024];
+        for (int i = 0; i < NACC; ++i) d[i] += p[i * SUBS * 256];
       }
       float yp, ym;
       if (TILE_ROUND) {
-        yp = DUAL ? d[0] : d[0] + d[1];
-        ym = DUAL ? d[1] : d[0] + d[NACC - 1];
+        yp = DUAL || ONE ? d[0] : d[0] + d[1 % NACC];
+        ym = DUAL ? d[NACC - 1] : ONE ? yp : d[0] + d[NACC - 1];
       } else {
-        yp = d[0] + a.eps * d[1];
-        ym = d[NACC - 2] - a.eps * d[NACC - 1];
+        yp = d[0] + a.eps * d[NACC > 1 ? 1 : 0];
+        ym = d[NACC > 1 ? NACC - 2 : 0] - a.eps * d[NACC - 1];
       }
       if constexpr (AGAIN) {
         constexpr int DT = BF16 ? SZO_TILE_BF16 : SZO_TILE_F16;
@@ -442,7 +460,8 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
   }
 }
 
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>
+// ONE: the "+" forward alone is wanted (single forwards of TILE_ROUND layers); the partials and outputs of the other are not valid then.
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE>
 __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>())) band_split_kernel(SmallArgs a) {
   int bid = xcd_unit((int)blockIdx.x, (int)gridDim.x);
   const int slice = bid % a.slices;
@@ -451,40 +470,43 @@ __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>(
   const uint32_t part_shift = (a.part_shifts >> (4 * (index & 7))) & 15u;
   auto run = [&](auto rows_tag) {
     constexpr int XP = decltype(rows_tag)::value;
-    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, 4, XP>(a, index, bid, slice);
-    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, 2, XP>(a, index, bid, slice);
-    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, 1, XP>(a, index, bid, slice);
+    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 4, XP>(a, index, bid, slice);
+    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 2, XP>(a, index, bid, slice);
+    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 1, XP>(a, index, bid, slice);
   };
   if (MODE == SM_FAST && !DUAL && a.few_rows) run(std::integral_constant<int, 1>{});
   else run(std::integral_constant<int, 4>{});
 }
 
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND>
-static int launch(int waves, int workgroups, const SmallArgs& a, hipStream_t stream) {
-  constexpr size_t per_wave = split_sets<DUAL, TILE_ROUND>() * 1024 * sizeof(float);
-  constexpr int most = split_max_waves<MODE, DUAL, TILE_ROUND>();
-  if (waves > most) waves = most;
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE = false>
+static int launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) {
+  constexpr int nacc = split_sets<DUAL, TILE_ROUND, ONE>(), most = split_max_waves<MODE, DUAL, TILE_ROUND>();
+  constexpr size_t most_bytes = split_wave_floats(nacc, 4) * sizeof(float) * most;
+  const int waves = l.waves < most ? l.waves : most;
   static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
-  const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND>;
-  const int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, per_wave * most);
+  const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND, ONE>;
+  const int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, most_bytes);
   if (rc != SZO_OK) return rc;
-  kern<<<(unsigned)workgroups, 64 * waves, per_wave * waves, stream>>>(a);
+  kern<<<(unsigned)l.workgroups, 64 * waves, split_wave_floats(nacc, l.subs) * sizeof(float) * (size_t)waves, stream>>>(a);
   SZO_LAUNCH_CHECK();
   return SZO_OK;
 }
 
 template <bool DUAL>
-static int launch_mode(int mode, bool bf16, bool tile_round, int waves, int workgroups, const SmallArgs& a, hipStream_t stream) {
-  if (bf16) return launch<SM_PLAIN, true, DUAL, true>(waves, workgroups, a, stream);
-  if (tile_round) return launch<SM_PLAIN, false, DUAL, true>(waves, workgroups, a, stream);
-  if (mode == SM_FAST) return launch<SM_FAST, false, DUAL, false>(waves, workgroups, a, stream);
-  if (mode == SM_LUT) return launch<SM_LUT, false, DUAL, false>(waves, workgroups, a, stream);
-  return launch<SM_PLAIN, false, DUAL, false>(waves, workgroups, a, stream);
+static int launch_mode(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) {
+  if constexpr (!DUAL) {
+    if (l.bf16 && l.one) return launch<SM_PLAIN, true, false, true, true>(l, a, stream);
+    if (l.tile_round && l.one) return launch<SM_PLAIN, false, false, true, true>(l, a, stream);
+  }
+  if (l.bf16) return launch<SM_PLAIN, true, DUAL, true>(l, a, stream);
+  if (l.tile_round) return launch<SM_PLAIN, false, DUAL, true>(l, a, stream);
+  if (l.mode == SM_FAST) return launch<SM_FAST, false, DUAL, false>(l, a, stream);
+  if (l.mode == SM_LUT) return launch<SM_LUT, false, DUAL, false>(l, a, stream);
+  return launch<SM_PLAIN, false, DUAL, false>(l, a, stream);
 }
 
-int split_launch(int mode, bool dual, bool bf16, bool tile_round, int waves, int workgroups, const SmallArgs& a, hipStream_t stream) {
-  return dual ? launch_mode<true>(mode, bf16, tile_round, waves, workgroups, a, stream)
-              : launch_mode<false>(mode, bf16, tile_round, waves, workgroups, a, stream);
+int split_launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) {
+  return l.dual ? launch_mode<true>(l, a, stream) : launch_mode<false>(l, a, stream);
 }
 
 }  // namespace szo
