@@ -66,7 +66,8 @@ def one_product_kernel(mats, M, two_sets=False, asked_for=False):
         elif asked_for:
             taken = wgs >= 160
         else:
-            taken = wgs >= 32 and M <= 512 and (1 + 108 * rho) * -(-M // 64) < 1.42 * 4 * -(-M // 256)
+            tiles = sum(-(-m.N // 128) * -(-M // 256) for m in mats)
+            taken = wgs >= 32 and (M <= 2048 or tiles <= 2048) and (1 + 108 * rho) * -(-M // 64) < (1.42 if M <= 512 else 1.34) * 4 * -(-M // 256)
         if taken:
             return "onepass_table_kernel"
     if few or asked_for:

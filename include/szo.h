@@ -164,10 +164,13 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * scalars: device double[3], overwritten with (L+, L-, g).  flags: bit 0 set = use the
  * loss-fusing forward and never write y (desc->y may then be NULL); large steps then run all
  * forwards (every layer, both signs) as one launch driven by a descriptor table that is staged in
- * the workspace.  Steps of up to 512 tokens whose layers have one set of activations compute the dense
- * product once for both signs where that is the faster way: few tokens stream the weights once per 16 to 48
- * token rows; more of them run on the matrix cores in tiles of 64 token rows, if the layers are of the uniform
- * format with one tile type, fill the chip, and their masks are sparse (up to about 0.4 % against the tiled kernel).
+ * the workspace.  Both forwards of a layer with one set of activations see the same x, so y(+-) = x (dq + v)^T +- eps x z^T: such
+ * steps compute the dense product once for both signs where that is the faster way, and add the sparse products.  Few
+ * tokens stream the weights once per 16 to 48 token rows; more of them run on the matrix cores in tiles of 64 token rows, if
+ * the layers are of the uniform format with one tile type, fill the chip, and their masks are sparse (against the tiled kernel up to
+ * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Otherwise, and beyond 2048
+ * tokens in steps of more than 2048 output tiles of 256 x 128, each layer runs as two full products, as the single-layer
+ * calls compute them; the results are the same up to the roundings described at SZO_TILE_F16.
  * With bit 0 clear y holds the -eps forward's outputs afterwards, and the loss is summed in fp64 from the
  * fp32 outputs; layers of the uniform format with one tile type, one set of activations, masks of up to 1.5 % and no
  * output buffer in common with another layer run as one launch there too.
@@ -181,14 +184,12 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * be captured.  The workspace must not be shared with a call running concurrently on another
  * stream. */
 #define SZO_STEP_FUSED_LOSS 1
-/* Bit 1 (with bit 0): one dense product per layer beyond 512 tokens too.  Both forwards of a layer see the
- * same x in this call, so y(+-) = x (dq + v)^T +- eps x z^T: the dense product is computed once and serves
- * both signs, the sparse products are added.  Same results as two forwards up to the roundings above; half the dense
- * work.  A step keeps two products all the same where its layers have a second set of activations
- * or where it loses by it (bf16 tile or K an odd multiple of 64 with masks of about 1 % and more, where the sparse products
- * cost what the second dense product does).  Not the default beyond 512 tokens because it does not carry over to a
- * caller whose two forwards see different activations (every layer of a real model but the first), who calls
- * szo_linear_fwd per sign instead. */
+/* Bit 1 (with bit 0): one dense product per layer in larger steps, with denser masks and in steps of few workgroups too: half the
+ * dense work, same results up to the roundings above.  A step keeps two products all the same where its layers have a
+ * second set of activations or where it loses by it (bf16 tile or K an odd multiple of 64 with masks of about 1 % and
+ * more, where the sparse products cost what the second dense product does).  Not the default for large steps because
+ * it does not carry over to a caller whose two forwards see different activations (every layer of a real model but the
+ * first), who calls szo_linear_fwd per sign instead. */
 #define SZO_STEP_ONE_DENSE_PASS 2
 int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
                 float eps, float lr, double* scalars, void* workspace, int flags, void* stream);

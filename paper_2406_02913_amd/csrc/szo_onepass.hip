@@ -604,16 +604,23 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    Without slices (bf16 tile, K an odd multiple of 64): wherever it has 32 workgroups and the tiles would run layer by layer,
 //    and against a grouped launch, which is slower with that tile, up to 1.75 / 4: two OPT blocks at 224 tokens and 0.4 %
 //    636 -> 400, four at 512 tokens and 1 % 1654 -> 2179.
-//  * against the tiled kernel, up to kOnePassTokens tokens unless the caller asks for it: beyond that a step is two full
-//    forwards per layer by default, the products of the single-layer calls.  The two differ by what a row of tiles
+//  * against the tiled kernel, which computes both forwards: the two differ by what a row of tiles
 //    costs: a unit of 64 token rows here takes 1 + 108 rho
 //    (rho = share of sensitive weights; one Llama block at 2048 tokens, rho = 0.0001 / 0.001 / 0.002 / 0.004 / 0.006:
 //    1459 / 1450 / 1448 / 1464 / 1479 -> 1070 / 1079 / 1216 / 1419 / 1662), one of a 256-row tile 1.42 / 4, padding
-//    included.  Single layers: 4096 x 4096 at 256 / 1024 / 4096 tokens 128 / 135 / 249 -> 71 / 76 / 196, 1024 x 1024
-//    50 / 50 / 53 -> 36 / 37 / 39.  Steps of a handful of workgroups gain nothing: they keep the tiled kernel.
+//    included.  Steps of a handful of workgroups gain nothing: they keep the tiled kernel.
+//    Beyond 512 tokens the chip is at its power limit, where masks with rows full of entries and the bf16 tile cost more: one
+//    Llama block at 4096 tokens on request, rho = 0.0001 / 0.001 / 0.002 / 0.004: 2759 / 2762 / 2780 / 2832 -> 2058 / 2114 / 2386 / 2864,
+//    half the entries in 1 % of the rows at 0.001 / 0.002: 2760 / 2797 -> 2195 / 2489, bf16 tile 2830 -> 2386 at 0.001, 2894 -> 3076
+//    at 0.004.
+//    Without being asked up to 2048 tokens, or while the tiled launch has eight rounds of workgroups at most: there the last
+//    rows of tiles, the last round and the launches per layer weigh as much as the second product.  One Llama block at 520 /
+//    1000 / 2048 tokens 582 / 809 / 1416 -> 326 / 548 / 1064; single layers at 600 / 2048 / 8192 tokens: 4096 x 4096 122 / 175 / 462 -> 67 / 101 /
+//    352, 1024 x 1024 45 / 41 / 58 -> 19 / 24 / 40, 1024 x 16384 433 / 427 / 672 -> 98 / 180 / 359.  Larger steps keep the products of the
+//    single-layer calls unless asked (a Mistral block at 8192 tokens 5865 -> 4568): their losses are those calls' up to the order of
+//    the partial sums, which callers that split a step rely on.
 //  * with the outputs written (flags = 0) the other path is two tiled launches and two passes over y per layer: one Llama
 //    block at 1 / 256 / 1024 tokens 1044 / 1063 / 1508 -> 150 / 189 / 621; rho = 0.01, 1024 tokens: 1836 -> 1128.
-constexpr int64_t kOnePassTokens = 512;
 static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y, bool separate) {
   int64_t wgs = 0, tiles = 0, most_tokens = 0;
   double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0, wg_k = 0.0, longest_k = 0.0;
@@ -650,7 +657,9 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
   }
   // asked for in a step too small for a grouped tiled launch (384 tiles of 256 x 128): the tiles would run layer by layer and sign
   if (asked_for && tiles < 384) return wgs >= 32;
-  return (asked_for || most_tokens <= kOnePassTokens) && (1.0 + 108.0 * rho) * here < (asked_for ? 1.75 : 1.42) * tiled;
+  if (!asked_for && most_tokens > 2048 && tiles > 2048) return false;
+  const double line = asked_for ? 1.75 : most_tokens <= 512 ? 1.42 : stream ? 1.34 : 1.22;
+  return (1.0 + 108.0 * rho) * here < line * tiled;
 }
 
 // The outputs are written by concurrent workgroups: layers must not share them (a caller that only wants the losses may

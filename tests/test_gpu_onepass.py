@@ -215,3 +215,35 @@ def test_a_bf16_stack_differs_between_the_entry_points_by_the_rounding_of_the_se
         assert abs(s[0] - r["loss_plus"]) <= 1e-4 * r["loss_plus"] and abs(s[1] - r["loss_minus"]) <= 1e-4 * r["loss_minus"]
         assert abs(s[2] - r["g"]) <= 1e-1 * max(abs(r["g"]), sg)
     assert abs(out[0][2] - out[1][2]) <= 1e-1 * max(abs(r["g"]), sg)
+
+
+@pytest.mark.parametrize("M,N,K,G,density,tile", [
+    (513, 2048, 1024, 128, 1e-3, "f16"),        # the first size beyond 512 tokens: nine rows of tiles, the last of one token row
+    (2048, 300, 512, 128, 2e-3, "f16"), (2049, 256, 256, 128, 3e-3, "f16"),      # either side of the limit on tokens (few tiles)
+    (700, 700, 320, 64, 1e-3, "bf16"),          # the other line: tile type, half a chunk at the end
+])
+def test_chosen_beyond_512_tokens_and_equal_to_two_forwards(M, N, K, G, density, tile):
+    """Losses, g and the updated values of the step against two perturbed forwards of the same layer on the tiled kernel:
+    they differ by the rounding of the weights after scaling (2^-11, 2^-8 with the bf16 tile) averaged over the outputs."""
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    o, d = make_pair(481, M, N, K, G, density)
+    v0 = d.sp_val.cpu().numpy().copy()
+    ws, scal, lr = szo.new_workspace(), torch.zeros(3, dtype=torch.float64, device="cuda"), 1e-2
+    two = torch.zeros(2, dtype=torch.float64, device="cuda")
+    szo.szo_set_tile_config(2)
+    for sign in (1, -1):
+        szo.szo_linear_fwd_mse(d.desc(dt, with_y=False), 9, 3, sign, 1e-3, 1.0 / (M * N), two[(1 - sign) // 2:(1 - sign) // 2 + 1], ws)
+    szo.szo_set_tile_config(0)
+    szo.szo_kernel_timing(True)
+    szo.szo_zo_step([d.desc(dt, with_y=False)], 9, 3, 1e-3, lr, scal, ws, szo.STEP_FUSED_LOSS)
+    _, launches = szo.szo_kernel_timing_read()
+    szo.szo_kernel_timing(False)
+    assert launches == 1
+    (lp, lm, g), want, sg = scal.cpu().numpy(), two.cpu().numpy(), sigma_g([o])
+    ltol, gtol = (1e-5, 1e-2) if tile == "f16" else (1e-3, 1e-1)          # the bars of the tiled kernel against the oracle
+    assert abs(lp - want[0]) <= ltol * want[0] and abs(lm - want[1]) <= ltol * want[1]
+    want_g = (want[0] - want[1]) / (2.0 * float(np.float32(1e-3)))
+    assert abs(g - want_g) <= 2 * gtol * max(abs(want_g), sg)
+    z = ozo.zo_step([clone(o)], 9, 3, 1e-3, lr)["z"][0]
+    moved = d.sp_val.cpu().numpy().astype(np.float64) - v0
+    assert np.max(np.abs(moved + float(np.float32(lr)) * g * z)) <= 1e-5 * abs(lr * g) * 6 + np.spacing(np.float32(0.2))
