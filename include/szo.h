@@ -166,7 +166,8 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * forwards (every layer, both signs) as one launch driven by a descriptor table that is staged in
  * the workspace.  Both forwards of a layer with one set of activations see the same x, so y(+-) = x (dq + v)^T +- eps x z^T: such
  * steps compute the dense product once for both signs where that is the faster way, and add the sparse products.  Few
- * tokens stream the weights once per 16 to 48 token rows; more of them run on the matrix cores in tiles of 64 token rows, if
+ * tokens, or launches of so few workgroups that any tile would outlast them, stream the weights once per 16 to 48 token rows; the
+ * others run on the matrix cores in tiles of 64 token rows, if
  * the layers are of the uniform format with one tile type, fill the chip, and their masks are sparse (against the tiled kernel up to
  * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Otherwise, and beyond 2048
  * tokens in steps of more than 2048 output tiles of 256 x 128, each layer runs as two full products, as the single-layer

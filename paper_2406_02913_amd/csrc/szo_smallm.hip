@@ -631,26 +631,32 @@ struct FewPlan {
 // With groups of 32 and 64 the stream kernel loads its scales where it needs them; look-ups (table format) and two activation
 // sets cost more per unit in the split kernel: three Llama blocks at 16 tokens with tables 165 against 145, one Mistral block
 // with two sets at 16 / 32 tokens 70 / 116 against 134 / 139.
-static bool split_pays(const LaunchShape& launch, bool dual, bool lut, bool plain) {
+struct FewEstimate { double split, stream; };
+static FewEstimate few_estimate(const LaunchShape& launch, bool dual, bool lut, bool plain) {
   const double percent = launch.percent(), over = std::max(percent - 0.1, 0.0), share = percent > 0.0 ? over / percent : 0.0;
   const double split = (lut ? 0.018 : 0.012) * (dual ? 1.65 : 1.0) * (double)launch.bands16 +
                        (lut ? 0.0068 : 0.0058) * (dual ? 1.65 : 1.0) * launch.band_k +
                        (0.012 * launch.row_entries + 0.008 * launch.slice_entries) * share * (dual ? 2.0 : 1.0);
   const double stream = ((plain ? 12.9 : 6.9) + 8.0 * over) * launch.longest_k + 0.0026 * launch.band_k;
-  return split <= stream;
+  return FewEstimate{split, stream};
+}
+static bool split_pays(const LaunchShape& launch, bool dual, bool lut, bool plain) {
+  const FewEstimate e = few_estimate(launch, dual, lut, plain);
+  return e.split <= e.stream;
 }
 // Workgroups per band of a split launch, 1 << the result.  A band's wave dequantises four 16-row subtiles for each 128 columns, one
 // after the other, which is most of a small launch's time: cut into two or four workgroups the band takes more CUs.  Each of them
 // stages x and looks through the band's entries again, so only while all workgroups still have a CU to themselves (one
 // forward at 16 tokens, us with 1 / 2 / 4 workgroups per band: 4096 x 4096 (64 bands) 10.4 / 7.7 / 6.6, 8192 x 4096 10.5 / 8.0 / 9.5,
 // 11008 x 4096 10.8 / 11.3 / 12.7, 4096 x 16384 26.8 / 19.6 / 16.5); and in two where the chain of a long K outlasts the
-// whole launch's work, both estimated as in split_pays (a step over one OPT block at 1 / 16 tokens, fc2's bands cut in two:
-// 33.8 / 42.4 -> 31.1 / 35.5; where the chain is shorter it loses: one Mistral block 31.9 / 39.9 -> 36.2 / 41.8).
+// whole launch's work, both estimated as in split_pays, and its bands are a quarter of it at most (a step over one OPT block at
+// 1 / 16 tokens, fc2's bands cut in two: 33.8 / 42.4 -> 31.1 / 35.5; where the chain is shorter it loses: one Mistral block 31.9 / 39.9 ->
+// 36.2 / 41.8; so does a layer by itself: 1024 x 16384 at 200 tokens with groups of 32 32.3 -> 41.8).
 static int split_part_shift(const szo_linear_desc* d, const LaunchShape& launch) {
   if (launch.bands16 <= 64) return 2;
   if (launch.bands16 <= 128) return 1;
   const double k = (double)d->K / 1024.0, chain = 3.2 + 1.55 * k, work = 0.012 * (double)launch.bands16 + 0.0058 * launch.band_k;
-  return k >= 8.0 && chain > 1.1 * work ? 1 : 0;
+  return k >= 8.0 && 4 * bands_of(d) * ((d->M + SM_ROWS - 1) / SM_ROWS) <= launch.bands16 && chain > 1.1 * work ? 1 : 0;
 }
 static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, bool dual, Partials less = kBandsInParts) {
   FewPlan p;
@@ -752,8 +758,8 @@ static int launch_plan(const FewPlan& p, const LaunchTotals& t, bool one_sign, S
 constexpr int kSmallMaxSlices = 15;
 // Uniform layers that only the split kernel takes (bf16 tile, K an odd multiple of 64), against 128x128 tiles.  Measured with
 // the bf16 tile, us per step: one Llama block at 16 / 64 / 128 tokens 62 / 134 / 302 against 371 / 375 / 379, sixteen blocks
-// 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where the tiles would leave the chip idle.
-constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTokensSmallLaunch = 128;
+// 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where the tiles would leave the chip idle (2304 workgroups here).
+constexpr int64_t kSplitOnlyTokens = 64;
 // Inside these limits both are estimated: the split kernel by its bands and their entries or the chain of the longest K, the
 // tiles by the chain of the longest K or their share of the work, one launch after the other where they are too few for a
 // grouped one.  Fitted, in about us, to steps and single-layer losses with the bf16 tile over the same shapes, masks spread
@@ -771,10 +777,27 @@ static double tiled_us(const LaunchShape& l, int forwards) {
 // The split kernel's byte offsets inside a band's codes (32 per column) and inside its sixteen rows of x (32 per column)
 // have 32 bits; stream_ok's bound on the codes keeps the other layers below that.
 constexpr int64_t kSplitOnlyColumns = 1 << 23;
-static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch) {
+// Whatever the number of tokens: launches that end before the other kernels have walked the longest K, which take at least the
+// time below for it however little work there is (their tiles are then few, and each has all of K to itself).  Measured, us,
+// other kernels -> this path: a forward of a 300 x 4096 layer at 450 / 1000 / 4000 tokens 55 / 56 / 56 -> 11 / 17 / 46, 64 x 16384 at
+// 600 / 8000 tokens 203 / 208 -> 21 / 80, 1024 x 4096 at 600 / 2000 tokens 56 / 57 -> 26 / 48, 4096 x 1024 at 450 tokens 18.9 -> 15.4;
+// steps of the same 132 / 69 / 78 -> 18 / 25 / 50, 422 / 208 -> 28 / 88, 65 / 66 -> 35 / 57, 29.7 -> 23.8; beyond the line a step over 4096 x
+// 4096 at 600 tokens 67 -> 68, a forward 57 -> 59.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
+// forward of a 1024 x 1024 / 4096 x 4096 layer at 300 tokens 21 / 70 -> 9 / 45.
+// (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.)
+static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
+  if (d->K < 1024) return false;
+  const FewEstimate e = few_estimate(launch, d->x_minus && forwards == 2, d->format == SZO_FORMAT_LUT, d->group != 128);
+  // (the estimates are of steps up to 448 tokens: with groups below 128 and dense masks a forward over more of them takes up to that much longer)
+  const double few = std::min(e.split * (d->group != 128 ? 1.35 : 1.0), e.stream + 3.0 + 0.0015 * (double)launch.bands16) *
+                     (1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0));
+  return few < (forwards == 2 ? 10.0 + 11.8 * launch.longest_k : 5.0 + 12.7 * launch.longest_k);
+}
+static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (!stream_ok(d))
     return d->format == SZO_FORMAT_UNIFORM && d->K < kSplitOnlyColumns &&
-           d->M <= (launch.bands16 <= 2304 ? kSplitOnlyTokensSmallLaunch : kSplitOnlyTokens);
+           (launch.bands16 <= 2304 || d->M <= kSplitOnlyTokens);
+  if (outruns_the_chain(d, launch, forwards)) return true;
   // two activation sets: a pass holds 16 token rows of each, so it is worth less
   const int64_t slices = (d->M + (d->x_minus ? 15 : 31)) / (d->x_minus ? 16 : 32), tile_rows = (d->M + 255) / 256;
   return slices <= kSmallMaxSlices && 2 * slices < 15 * tile_rows;
@@ -799,7 +822,7 @@ bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count,
     const szo_linear_desc* d = &descs[i];
     if (d->M <= 0 || d->N <= 0) continue;                   // an empty layer contributes nothing on either path
     if (separate && forwards == 2 && d->x_minus) return false;
-    if (!(any_token_count ? stream_ok(d) : layer_eligible(d, shape))) return false;
+    if (!(any_token_count ? stream_ok(d) : layer_eligible(d, shape, forwards))) return false;
     all_stream = all_stream && stream_ok(d);
   }
   return n > 0 && (all_stream || rounded_us(descs, n, true, forwards, separate) <= rounded_us(descs, n, false, forwards, separate));

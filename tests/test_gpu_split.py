@@ -117,7 +117,7 @@ def test_stream_kernel_still_matches_oracle_and_the_split_kernel():
     (254, 33, 64 * 43, 256, 128, 2e-3, "uniform", "f16"),     # three slices, the last of one row: 129
     (255, 17, 64 * 40, 384, 64, 3e-3, "uniform", "bf16"),     # two parts, sensitive weights rounded in the tile
     (256, 130, 500, 8192, 128, 1e-3, "uniform", "f16"),       # 72 and a K of 64 blocks
-    (257, 144, 1000, 8192, 128, 1e-3, "uniform", "f16"),      # 144, cut in two for the length of K's chain alone
+    (257, 144, 1000, 8192, 128, 1e-3, "uniform", "f16"),      # 144: whole bands again
     (258, 16, 100, 640, 128, 8e-2, "lut", "f16"),             # four parts, several windows of entries per wave
 ], ids=lambda s: str(s[0]))
 def test_bands_cut_into_parts_match_oracle(shape):
@@ -141,6 +141,43 @@ def test_bands_cut_into_parts_match_oracle(shape):
     scal = torch.zeros(3, dtype=torch.float64, device="cuda")
     szo.szo_zo_step([d.desc(tile_dtype=dt, with_y=False)], 5, 2, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
     assert abs(scal[0].item() - mine) <= 1e-6 * mine
+
+
+def test_long_k_beside_many_short_bands_is_cut_in_two():
+    """132 bands of K = 128 and 4 of K = 16384 in one step: the latter are cut for the length of their chain alone."""
+    os_, ds_, base = [], [], 0
+    for sd, M, N, K, dens in ((261, 64, 2100, 128, 5e-3), (262, 64, 64, 16384, 1e-3)):
+        o, d = make_pair(sd, M, N, K, 128, dens, nnz_base=base)
+        base += (o.sp_idx.size + 3) // 4 * 4
+        os_.append(o)
+        ds_.append(d)
+    szo.szo_set_tile_config(8)
+    _check_step(os_, ds_, szo.STEP_FUSED_LOSS, ltol=1e-4)
+
+
+@pytest.mark.parametrize("M,N,K,G,fmt,tile", [
+    (449, 64, 1024, 128, "uniform", "f16"),       # the first size beyond the limit on tokens, K at its lower limit
+    (1500, 130, 4096, 128, "uniform", "f16"),     # 94 slices; the split or the stream kernel by their estimates
+    (700, 300, 2048, 64, "uniform", "f16"), (500, 100, 1152, 128, "lut", "f16"), (300, 200, 1088, 64, "uniform", "bf16"),
+])
+def test_many_tokens_of_a_layer_that_the_tiles_would_walk_for_longer(M, N, K, G, fmt, tile):
+    """Few workgroups and a long K: any number of tokens runs as slices, one launch for both signs of a step; outputs,
+    losses and g to the bounds of the few-token path against the oracle."""
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    o, d = make_pair(271, M, N, K, G, 2e-3, nnz_base=4, fmt=fmt)
+    z = ophilox.zbar(7, 1, 4, o.sp_idx.size)
+    args, kw = (("D", tile), {}) if tile == "bf16" else (("E",), {"lut": o.lut})
+    want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, G, o.sp_idx, o.sp_val, z, -1, 1e-3, *args, **kw)
+    szo.szo_linear_fwd(d.desc(tile_dtype=dt), 7, 1, -1, 1e-3)
+    assert rel_fro(d.y.cpu().numpy(), want) <= (2e-5 if tile == "bf16" else 5e-4 if G == 128 and fmt == "uniform" else 1e-3)
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_kernel_timing(True)
+    szo.szo_zo_step([d.desc(tile_dtype=dt, with_y=False)], 7, 1, 1e-3, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+    _, launches = szo.szo_kernel_timing_read()
+    szo.szo_kernel_timing(False)
+    assert launches == 1
+    loss = olayer.mse_loss(want, o.target_bits)
+    assert abs(scal[1].item() - loss) <= 1e-4 * loss
 
 
 def test_noalloc_falls_back_to_fewer_partials():
