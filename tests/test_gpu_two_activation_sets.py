@@ -82,6 +82,21 @@ def test_tiled_kernel_with_two_activation_sets(cfg):
     _check_step([o1, o2], [d1, d2], 0, ltol=1e-5)                          # separate loss kernel
 
 
+@pytest.mark.parametrize("K", [(192, 512, 320), (512, 192, 192), (64, 128, 576)])
+def test_grouped_launch_over_layers_in_any_order_of_k(K):
+    # the launch takes the longest K first; losses and updates are the layers' own whatever their order
+    szo.szo_set_tile_config(3)
+    os_, ds_, base = [], [], 0
+    for i, k in enumerate(K):
+        o, d = make_pair(110 + i, 270 - 20 * i, 320, k, 64, 5e-3, nnz_base=base)
+        if i != 1:
+            o, d = _with_x_minus(o, d, seed=610 + i)
+        base += (o.sp_idx.size + 3) // 4 * 4
+        os_.append(o)
+        ds_.append(d)
+    _check_step(os_, ds_, szo.STEP_FUSED_LOSS, ltol=1e-5)
+
+
 def test_mixed_step_and_equal_sets_reduce_to_the_plain_step():
     # a step over a layer with two sets and a layer with one; and x_minus == x must give what no x_minus gives
     o1, d1 = _with_x_minus(*make_pair(98, 16, 256, 512, 128, 5e-3, nnz_base=0), seed=602)
