@@ -97,6 +97,15 @@ def test_grouped_launch_over_layers_in_any_order_of_k(K):
     _check_step(os_, ds_, szo.STEP_FUSED_LOSS, ltol=1e-5)
 
 
+# Rows in the last row of tiles: fewer than half, exactly half, one more (256-row tiles grouped and per layer, 128-row tiles)
+@pytest.mark.parametrize("cfg,M", [(3, 257), (3, 384), (3, 385), (2, 128), (2, 300), (1, 192), (1, 193)])
+@pytest.mark.parametrize("fmt", ["uniform", "lut"])
+def test_tiled_kernel_with_half_empty_last_tiles(cfg, M, fmt):
+    szo.szo_set_tile_config(cfg)
+    o, d = _with_x_minus(*make_pair(120, M, 320, 448, 64, 5e-3, fmt=fmt), seed=620)
+    _check_step([o], [d], szo.STEP_FUSED_LOSS, ltol=1e-5)
+
+
 def test_mixed_step_and_equal_sets_reduce_to_the_plain_step():
     # a step over a layer with two sets and a layer with one; and x_minus == x must give what no x_minus gives
     o1, d1 = _with_x_minus(*make_pair(98, 16, 256, 512, 128, 5e-3, nnz_base=0), seed=602)
