@@ -151,7 +151,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   // ---- sensitive entries ----
   const bool band_ok = band < p.bands && p.nnz > 0;
   u32x2* const ring = reinterpret_cast<u32x2*>(smem + OnePassLds::RING) + wave * OP_RING;    // v | z << 16 ; row << 8 | byte of the column
-  uint8_t* const hot = smem + OnePassLds::HOT + wave * 4096;                                  // [v, z][64 rows][16 slots]
+  uint8_t* const hot = smem + OnePassLds::HOT + wave * 4096;                                  // [v, z][half][64 rows][8 slots]
   uint32_t* const pos = reinterpret_cast<uint32_t*>(smem + OnePassLds::POS) + wave * 16;      // byte of the column of each slot
   uint8_t* const sink = smem + OnePassLds::SINK + wave * 256 + 4 * lane;
   const table_words bounds = (table_words)(uintptr_t)(p.tile_ptr + (band_ok ? (size_t)band * (size_t)ktiles : 0));       // scalar loads
@@ -182,7 +182,14 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     }
     w_hi += OP_REFILL;
   };
-  // Group of up to 16 entries from entry g0: slot `lane` of the one-hot operands.
+  // Group of up to 16 entries from entry g0.  Entry e of the group stands in slot e / 2 of half e & 1, so that eight or fewer
+  // fill the first four slots of both halves and the columns of the others need not be gathered (a chunk of 64 rows has eight
+  // on average at 0.1 %; two-byte gathers of 32 rows meet on a quarter of the LDS banks).  us per step, all sixteen
+  // gathered -> this: one Llama block at 4096 tokens on request, rho = 0.0001 / 0.001 / 0.004, 2082 / 2123 / 2828 -> 2014 / 2101 / 2827;
+  // four at 128 tokens, 0.0003, 312 -> 303; 32 OPT blocks at 64 tokens 1270 -> 1258.  Skipping a quarter at a time, or all of an
+  // empty group, spills registers in the schedule (2.5 and 1.6 times as long).
+  const uint32_t slot_byte = ((uint32_t)lane & 1u) * 1024u + ((uint32_t)lane >> 1) * 2u;     // lanes 0..15
+  uint32_t* const slot_pos = pos + 8 * (lane & 1) + ((lane & 15) >> 1);
   u32x2 ent = {0u, 0u};
   uint8_t* hot_at = sink;                                   // where this lane's last entry stands
   auto group_read = [&](uint32_t g0) { ent = ring[(g0 + (uint32_t)(lane & 15)) & (uint32_t)(OP_RING - 1)]; };
@@ -190,11 +197,11 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     const bool mine = lane < 16 && g0 + (uint32_t)lane < g_end;
     *reinterpret_cast<uint16_t*>(hot_at) = 0;
     *reinterpret_cast<uint16_t*>(hot_at + (hot_at == sink ? 0 : 2048)) = 0;
-    hot_at = mine ? hot + (ent[1] >> 8) * 32u + 2u * (uint32_t)lane : sink;
+    hot_at = mine ? hot + (ent[1] >> 8) * 16u + slot_byte : sink;
     *reinterpret_cast<uint16_t*>(hot_at) = (uint16_t)(ent[0] & 0xFFFFu);
     *reinterpret_cast<uint16_t*>(mine ? hot_at + 2048 : sink) = (uint16_t)(ent[0] >> 16);
     // slots without an entry: a valid column, multiplied with zero
-    *reinterpret_cast<uint32_t*>(lane < 16 ? (uint8_t*)(pos + lane) : sink) = mine ? (ent[1] & 0xFFu) : 0u;
+    *reinterpret_cast<uint32_t*>(lane < 16 ? (uint8_t*)slot_pos : sink) = mine ? (ent[1] & 0xFFu) : 0u;
   };
   u32x4 gp[2], za[GROUP_SCALE ? 1 : 2], zb[2];              // (GROUP_SCALE: one block of token rows after the other)
   const uint32_t gather_base = (uint32_t)l31 * OP_XROW;
@@ -203,10 +210,18 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     gp[1] = *reinterpret_cast<const u32x4*>(pos + 8 * half + 4);
   };
   uint16_t graw[8];
+  bool many = false;                                        // more than eight entries in the group
   auto group_gather = [&](int c, int i) {
     const uint8_t* const x = smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + 32 * i * OP_XROW;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[e >> 2][e & 3] + gather_base));
+    for (int e = 0; e < 4; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[0][e] + gather_base));
+    if (many) {
+#pragma unroll
+      for (int e = 4; e < 8; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[1][e - 4] + gather_base));
+    } else {
+#pragma unroll
+      for (int e = 4; e < 8; ++e) graw[e] = 0;
+    }
   };
   auto group_pack = [&](int i) {
 #pragma unroll
@@ -214,7 +229,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   };
   auto group_hot = [&](int which) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) zb[j] = *reinterpret_cast<const u32x4*>(hot + which * 2048 + (32 * j + l31) * 32 + 16 * half);
+    for (int j = 0; j < 2; ++j) zb[j] = *reinterpret_cast<const u32x4*>(hot + which * 2048 + 1024 * half + (32 * j + l31) * 16);
   };
   auto group_multiply = [&](int which, int i, int j) {
     float16_t& a = which ? accz[i][j] : acc[i][j];
@@ -223,6 +238,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   auto group_all = [&](int c, uint32_t g0, uint32_t g_end) {
     while (w_hi < min(g0 + 16u, g_end)) refill();
     group_read(g0);
+    many = g_end - g0 > 8u;
     group_put(g0, g_end);
     group_pos();
 #pragma unroll
@@ -307,6 +323,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
 #pragma unroll
     for (int i = 0; i < 2; ++i) read_a(c, 0, i);
     group_read(j_lo);
+    many = j_hi - j_lo > 8u;
     auto behind = [&](int s) {                              // what stands behind matrix instruction s of 32
       if (s == 4) group_put(j_lo, j_hi);
       if (s == 8) group_pos();

@@ -82,6 +82,24 @@ def test_step_matches_oracle(name, with_y, tile):
             bound.check(i, d.sp_val.cpu().numpy(), om.sp_val, o.sp_val)
 
 
+# One chunk of one band with as many entries as fill half a group, a group, and one more; and none
+@pytest.mark.parametrize("group", [128, 64])
+@pytest.mark.parametrize("nnz", [0, 1, 7, 8, 9, 15, 16, 17, 24, 25, 33])
+def test_groups_of_sensitive_entries(nnz, group):
+    o, d = make_pair(440 + nnz, 70, 64, 128, group, nnz=nnz)
+    ref = clone(o)
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_set_tile_config(11)
+    eps = 0.1                                                # z weighs as much as the values: one entry is 1 % of the outputs
+    szo.szo_zo_step([d.desc()], 7, 0, eps, 0.0, scal, szo.new_workspace(), 0)
+    r = ozo.zo_step([ref], 7, 0, eps, 0.0)
+    lp, lm, _ = scal.cpu().numpy()
+    ltol = 2e-3 / np.sqrt(70 * 64)                           # as above
+    assert abs(lp - r["loss_plus"]) <= ltol * r["loss_plus"] and abs(lm - r["loss_minus"]) <= ltol * r["loss_minus"]
+    want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, o.group, o.sp_idx, o.sp_val, r["z"][0], -1, eps, "E")
+    assert rel_fro(d.y.cpu().numpy(), want) <= 5e-4
+
+
 def test_layers_that_share_their_output_buffer_run_one_after_the_other():
     """One buffer for the outputs of a stack holds the last layer's afterwards: concurrent workgroups would mix them."""
     (oa, ob), (da, db) = [list(t) for t in zip(*[make_pair(411 + i, 300, 320, 256, 128, 5e-3, nnz_base=8192 * i) for i in range(2)])]
