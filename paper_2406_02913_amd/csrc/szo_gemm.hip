@@ -70,14 +70,14 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   static_assert(BM == 8 * X_ROWS_PER_PASS, "every activation lane stages 8 chunks per tile");
   constexpr int MPK = WMB * WNB;                   // MFMAs per k-step
   constexpr int SLOTS = 4 * MPK;                   // MFMAs per K step
-  static_assert(SLOTS % 8 == 0 && SLOTS <= 32, "8 staging units must spread evenly over the slots");
   constexpr int SPU = SLOTS / 8;                   // slots per activation staging unit: 1, 2 or 4
   constexpr int WPS = 4 / SPU;                     // output words produced per slot
-  // Weight waves of the 32-slot schedule finish their dense staging in the first 24 slots (3 per
-  // unit) and spend the last 8 on the sensitive entries of the tile, so that the dependent LDS
-  // round trips of the scatter also run in the shadow of MFMAs instead of after them.
-  constexpr bool SCATTER_IN_SLOTS = (SLOTS == 32);
-  constexpr int DSPU = SCATTER_IN_SLOTS ? 3 : SPU; // slots per weight staging unit
+  // Weight waves finish their dense staging in the first three quarters of the slots (32 slots: 3 per unit; 16 slots: 3 per
+  // two units) and spend the rest on the sensitive entries of the tile, so that the dependent LDS
+  // round trips of the scatter also run in the shadow of MFMAs instead of after them (16 slots: forwards of a Llama block's linears
+  // at 600 tokens 513 -> 486 us, a 3000 x 4096 layer at 560 tokens and 1 % 68 -> 63, a 4096 x 4096 composed step at 1000 128 -> 121).
+  static_assert(SLOTS == 32 || SLOTS == 16, "two schedules exist");
+  constexpr int SC_WINDOW = SLOTS == 32 ? 24 : 6, SC_READ = SLOTS == 32 ? 27 : 12, SC_STORE = SLOTS == 32 ? 30 : 15;
   static_assert(WMB + WNB <= MPK, "operand reads of the next k-step must fit behind this one's MFMAs");
   typedef typename Frag<DT>::type frag_t;
 
@@ -294,7 +294,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       const uint32_t hi = __builtin_amdgcn_readlane(tp_reg, kt & 63), lo = tile_lo;
       tile_lo = hi;
       if (hi <= lo) return;
-      if (SCATTER_IN_SLOTS && hi - lo <= 64u) {
+      if (hi - lo <= 64u) {
         if (lo < win_lo || hi > win_hi) refill(lo & ~3u);
         sc_cnt = hi - lo;
         sc_e0 = lo - win_lo;
@@ -310,7 +310,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       // byte-permute instruction, four codes at a time: low 3 bits of the codes select inside a plane,
       // bit 3 picks the plane.  That only pays if a lane keeps ONE row's table for the whole K loop:
       // lane l stages row l of the band, all 64 columns of a tile (32 bytes of codes, two 16-byte loads).
-      static_assert(DT == SZO_TILE_F16 && SCATTER_IN_SLOTS, "table format: fp16 tile, 32-slot schedule");
+      static_assert(DT == SZO_TILE_F16 && SLOTS == 32, "table format: fp16 tile, 32-slot schedule");
       const int lrow = wave * 64 + lane;                           // row of the weight tile
       const global_u8 qr = p.qweight + ((size_t)min(band, p.bands - 1) * (size_t)nk * 64 + (size_t)lane) * 32;
       u32x4 qv[2];
@@ -405,13 +405,13 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       }
     } else {
     // ---- slices ---------------------------------------------------------------------------------
-    // Dense part: unit u = code word u%4 of row half u/4; DSPU slots per unit; the unit's four
-    // output words are spread 4 | 2,2 | 2,1,1 | 1,1,1,1 over them.  In the 32-slot schedule the
+    // Dense part: unit u = code word u%4 of row half u/4; the unit's four output words are spread 2,1,1 over three slots, with
+    // 16 slots the eight words of two units 3,3,2.  In the 32-slot schedule the
     // three instructions of an output word (and_or, subtract offset, multiply by scale) run in
     // three consecutive slots, so no slot holds two dependent VALU instructions.
-    // Scatter part (32-slot schedule only): window read, tile read, add + write, three slots
-    // apart; lanes without an entry go through a per-lane sink in LDS, which keeps it branch-free.
-    constexpr int PIPE = SCATTER_IN_SLOTS ? 1 : 0;      // slot distance between the stages of a word
+    // Scatter part: window read, tile read (behind the last dense write), add + write, three slots
+    // or more apart; lanes without an entry go through a per-lane sink in LDS, which keeps it branch-free.
+    constexpr int PIPE = SLOTS == 32 ? 1 : 0;      // slot distance between the stages of a word
     u32x4 outw;
     uint32_t st_a[3][2], st_b[3][2];
     uint32_t sc_pos = 0xFFFFu;
@@ -422,15 +422,15 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       return [&, dst, load_kt](int s) {
         // the k-th (0 or 1) output word staged from slot `slot`: unit u, word w; false if none
         auto item = [](int slot, int k, int& u, int& w) -> bool {
-          if (slot < 0 || slot >= 8 * DSPU) return false;
-          u = slot / DSPU;
-          const int ph = slot % DSPU;
-          const int w0 = (DSPU == 3) ? (ph == 0 ? 0 : ph + 1) : ph * (4 / DSPU);
-          const int nw = (DSPU == 3) ? (ph == 0 ? 2 : 1) : (4 / DSPU);
-          w = w0 + k;
+          if (slot < 0 || slot >= SLOTS / 4 * 3) return false;
+          const int ph = slot % 3;
+          const int w0 = SLOTS == 32 ? (ph == 0 ? 0 : ph + 1) : 3 * ph;
+          const int nw = SLOTS == 32 ? (ph == 0 ? 2 : 1) : (ph < 2 ? 3 : 2);
+          u = SLOTS == 32 ? slot / 3 : 2 * (slot / 3) + ((w0 + k) >> 2);
+          w = (w0 + k) & 3;
           return k < nw;
         };
-        constexpr int KMAX = (DSPU == 1) ? 4 : 2;
+        constexpr int KMAX = SLOTS == 32 ? 2 : 3;
         static_assert(KMAX <= 2 || PIPE == 0, "stage registers hold two words per slot");
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
@@ -480,14 +480,14 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
             }
           }
         }
-        if (SCATTER_IN_SLOTS) {
+        {
           const bool active = (uint32_t)lane < sc_cnt;
-          if (s == 24) {
+          if (s == SC_WINDOW) {
             const uint32_t e = active ? sc_e0 + lane : 0u;
             sc_pos = wp[e];
             sc_val = wv[e];
             if (DUAL) sc_val_minus = wv_minus[e];
-          } else if (s == 27) {                         // every dense word of the tile is written by slot 25
+          } else if (s == SC_READ) {                         // every dense word of the tile has been written
             const bool ok = active && sc_pos != 0xFFFFu;
             sc_addr = ok ? ldsB + dst * BN * BK + sc_pos : sink16 + wave * 64 + lane;
             sc_val = ok ? sc_val : 0.0f;
@@ -497,7 +497,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
               sc_val_minus = ok ? sc_val_minus : 0.0f;
               sc_old_minus = Frag<DT>::load(sc_addr_minus);
             }
-          } else if (s == 30) {
+          } else if (s == SC_STORE) {
             Frag<DT>::store(sc_addr, sc_old + sc_val);
             if (DUAL) Frag<DT>::store(sc_addr_minus, sc_old_minus + sc_val_minus);
           }

@@ -784,7 +784,8 @@ constexpr int64_t kSplitOnlyColumns = 1 << 23;
 // steps of the same 132 / 69 / 78 -> 18 / 25 / 50, 422 / 208 -> 28 / 88, 65 / 66 -> 35 / 57, 29.7 -> 23.8; beyond the line a step over 4096 x
 // 4096 at 600 tokens 67 -> 68, a forward 57 -> 59.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
 // forward of a 1024 x 1024 / 4096 x 4096 layer at 300 tokens 21 / 70 -> 9 / 45.
-// (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.)
+// (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.  The tiles' times are those of the
+// 128 x 128 schedule that scattered behind its last matrix instruction; it takes 5 % less by now, and the line stays where both were measured.)
 static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (d->K < 1024) return false;
   const FewEstimate e = few_estimate(launch, d->x_minus && forwards == 2, d->format == SZO_FORMAT_LUT, d->group != 128);

@@ -56,6 +56,22 @@ def test_forward_matches_oracle(shape, dt, dtname, tol_d, tile_cfg):
         assert np.max(np.abs(y - yD)) <= 1e-4 * scale + 1e-6
 
 
+# One 64 x 64 tile with none, one, as many entries as the schedule scatters by itself, and one more; then all of them
+@pytest.mark.parametrize("tile_cfg", [1, 2])
+@pytest.mark.parametrize("nnz", [0, 1, 64, 65, 4096])
+def test_entries_of_a_tile(nnz, tile_cfg):
+    szo.szo_set_tile_config(tile_cfg)
+    for dt, dtname, tol in DTYPES:
+        o, d = make_pair(60, 70, 64, 64, 32, nnz=nnz)
+        # v - eps z is formed in fp32: where its error crosses a rounding boundary of the tile type the weight is an ulp off.  With
+        # eps = 1e-3 that error is the last rounding's, 2^-25 of the weight: a share of at most 2^-16 / 2^-13 of the weights by 2^-8 /
+        # 2^-11 (bf16 / fp16), 1.5e-5 / 6e-6 of the result if all are sensitive (with eps = 0.1 the error of z does so more often)
+        z = ophilox.zbar(9, 2, 0, o.sp_idx.size)
+        y = _run(d, -1, 1e-3, 9, 2, dt)
+        want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, 32, o.sp_idx, o.sp_val, z, -1, 1e-3, "D", dtname)
+        assert rel_fro(y, want) <= tol
+
+
 def test_perturbation_difference_is_linear_in_z():
     # y(+) - y(-) = 2 eps x Z^T: checks the sign convention and that only masked entries move
     o, d = make_pair(7, 96, 256, 256, 32, 5e-3)
