@@ -966,6 +966,10 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
   static thread_local std::vector<FwdParams> table;
   table.clear();
   int64_t first_block = 0, offset = 0;
+  // Half-empty last rows of tiles, which take about half as long, get entries of their own: a layer that begins there.
+  const bool ordered = wgs <= 8192;
+  const bool split = ordered && !dual && descs[0].format == SZO_FORMAT_UNIFORM &&
+                     2 * sizeof(FwdParams) * (size_t)live <= kTableBytesPerMatrix * (size_t)kMaxStepMatrices;
   for (int i = 0; i < n; ++i) {                             // partials in the layers' order, whatever order the launch takes
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
@@ -978,6 +982,21 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
     p.partials_minus = (global_f64_out)(partials + T + offset);
     p.grid_m = gm; p.grid_n = gn;
     p.y = nullptr;                                          // the step's fused path never writes y
+    const bool half = split && gm * tile - (int)d->M >= tile / 2;
+    if (half && gm > 1) {
+      FwdParams last = p;
+      const size_t rows = (size_t)(gm - 1) * (size_t)tile;
+      last.x += rows * (size_t)d->K;
+      last.x_minus += rows * (size_t)d->K;
+      last.target += rows * (size_t)d->N;
+      last.M -= (int)rows;
+      last.partials += (size_t)(gm - 1) * (size_t)gn;
+      last.partials_minus += (size_t)(gm - 1) * (size_t)gn;
+      last.grid_m = 1;
+      table.push_back(last);
+      p.M = (int)rows;
+      p.grid_m = gm - 1;
+    }
     table.push_back(p);
     offset += (int64_t)gm * gn;
   }
@@ -985,7 +1004,12 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
   // time.  In the caller's order it ended with the last block's longest layer: two Mistral blocks with two sets of activations at
   // 333 tokens (1344 tiles, the last 64 of them 3.4 times as long as the others) 889 -> 812 us per step.  From 32 rounds of
   // workgroups on there is nothing to gain (a Mistral block at 8192 tokens, 42 rounds, 6251 -> 6295): the caller's order.
-  if (wgs <= 8192) std::stable_sort(table.begin(), table.end(), [](const FwdParams& a, const FwdParams& b) { return a.K > b.K; });
+  // Half-empty tiles are ordered by half their K: those blocks 733 -> 688 on another box, one OPT / Mistral block at 600 tokens
+  // 575 / 619 -> 517 / 541, two Llama blocks at 850 1479 -> 1448.
+  if (ordered) {
+    auto walk = [&](const FwdParams& p) { return (int64_t)p.K * (split && p.grid_m * tile - p.M >= tile / 2 ? 1 : 2); };
+    std::stable_sort(table.begin(), table.end(), [&](const FwdParams& a, const FwdParams& b) { return walk(a) > walk(b); });
+  }
   for (FwdParams& p : table) {
     p.first_block = (int)first_block;
     first_block += ((dual ? 1 : 2) * (int64_t)p.grid_m * p.grid_n + 7) & ~(int64_t)7;
