@@ -62,7 +62,8 @@ __device__ __forceinline__ FwdParams read_entry(table_words e) {
 }
 
 // `entry`: where p came from in a descriptor table, or null if it came with the launch.
-template <int DT, bool STORE_Y, bool GROUP_SCALE>
+// SPARSE: most chunks of a band hold eight sensitive entries at most, whose gathers take half the slots of a group (see below).
+template <int DT, bool STORE_Y, bool GROUP_SCALE, bool SPARSE>
 __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, table_words entry) {
   static_assert(!GROUP_SCALE || DT == SZO_TILE_F16, "integer codes are fp16 operands");
   typedef typename Frag<DT>::type frag_t;
@@ -151,7 +152,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   // ---- sensitive entries ----
   const bool band_ok = band < p.bands && p.nnz > 0;
   u32x2* const ring = reinterpret_cast<u32x2*>(smem + OnePassLds::RING) + wave * OP_RING;    // v | z << 16 ; row << 8 | byte of the column
-  uint8_t* const hot = smem + OnePassLds::HOT + wave * 4096;                                  // [v, z][half][64 rows][8 slots]
+  uint8_t* const hot = smem + OnePassLds::HOT + wave * 4096;                                  // [v, z][64 rows][16 slots]; SPARSE: [v, z][half][64 rows][8 slots]
   uint32_t* const pos = reinterpret_cast<uint32_t*>(smem + OnePassLds::POS) + wave * 16;      // byte of the column of each slot
   uint8_t* const sink = smem + OnePassLds::SINK + wave * 256 + 4 * lane;
   const table_words bounds = (table_words)(uintptr_t)(p.tile_ptr + (band_ok ? (size_t)band * (size_t)ktiles : 0));       // scalar loads
@@ -182,14 +183,12 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     }
     w_hi += OP_REFILL;
   };
-  // Group of up to 16 entries from entry g0.  Entry e of the group stands in slot e / 2 of half e & 1, so that eight or fewer
-  // fill the first four slots of both halves and the columns of the others need not be gathered (a chunk of 64 rows has eight
-  // on average at 0.1 %; two-byte gathers of 32 rows meet on a quarter of the LDS banks).  us per step, all sixteen
-  // gathered -> this: one Llama block at 4096 tokens on request, rho = 0.0001 / 0.001 / 0.004, 2082 / 2123 / 2828 -> 2014 / 2101 / 2827;
-  // four at 128 tokens, 0.0003, 312 -> 303; 32 OPT blocks at 64 tokens 1270 -> 1258.  Skipping a quarter at a time, or all of an
-  // empty group, spills registers in the schedule (2.5 and 1.6 times as long).
-  const uint32_t slot_byte = ((uint32_t)lane & 1u) * 1024u + ((uint32_t)lane >> 1) * 2u;     // lanes 0..15
-  uint32_t* const slot_pos = pos + 8 * (lane & 1) + ((lane & 15) >> 1);
+  // Group of up to 16 entries from entry g0.  Entry e of it stands in slot e, or, SPARSE, in slot e / 2 of half e & 1, so that
+  // eight or fewer fill the first four slots of both halves and the columns of the others need not be gathered (two-byte
+  // gathers of 32 rows meet on a quarter of the LDS banks).  Only the schedule's group looks whether it has eight: further
+  // groups of a chunk are full but for the last, and a branch among their gathers keeps those of the second block of token rows from
+  // running beside the products of the first.  Skipping a quarter at a time, or all of an empty group, spills registers in the
+  // schedule (2.5 and 1.6 times as long).  What it gives, and where: kSparseEntries below.
   u32x2 ent = {0u, 0u};
   uint8_t* hot_at = sink;                                   // where this lane's last entry stands
   auto group_read = [&](uint32_t g0) { ent = ring[(g0 + (uint32_t)(lane & 15)) & (uint32_t)(OP_RING - 1)]; };
@@ -197,11 +196,12 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     const bool mine = lane < 16 && g0 + (uint32_t)lane < g_end;
     *reinterpret_cast<uint16_t*>(hot_at) = 0;
     *reinterpret_cast<uint16_t*>(hot_at + (hot_at == sink ? 0 : 2048)) = 0;
-    hot_at = mine ? hot + (ent[1] >> 8) * 16u + slot_byte : sink;
+    if constexpr (SPARSE) hot_at = mine ? hot + (ent[1] >> 8) * 16u + ((uint32_t)lane & 1u) * 1024u + ((uint32_t)lane >> 1) * 2u : sink;
+    else hot_at = mine ? hot + (ent[1] >> 8) * 32u + 2u * (uint32_t)lane : sink;
     *reinterpret_cast<uint16_t*>(hot_at) = (uint16_t)(ent[0] & 0xFFFFu);
     *reinterpret_cast<uint16_t*>(mine ? hot_at + 2048 : sink) = (uint16_t)(ent[0] >> 16);
     // slots without an entry: a valid column, multiplied with zero
-    *reinterpret_cast<uint32_t*>(lane < 16 ? (uint8_t*)slot_pos : sink) = mine ? (ent[1] & 0xFFu) : 0u;
+    *reinterpret_cast<uint32_t*>(lane < 16 ? (uint8_t*)(SPARSE ? pos + 8 * (lane & 1) + (lane >> 1) : pos + lane) : sink) = mine ? (ent[1] & 0xFFu) : 0u;
   };
   u32x4 gp[2], za[GROUP_SCALE ? 1 : 2], zb[2];              // (GROUP_SCALE: one block of token rows after the other)
   const uint32_t gather_base = (uint32_t)l31 * OP_XROW;
@@ -210,17 +210,26 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
     gp[1] = *reinterpret_cast<const u32x4*>(pos + 8 * half + 4);
   };
   uint16_t graw[8];
-  bool many = false;                                        // more than eight entries in the group
-  auto group_gather = [&](int c, int i) {
+  bool many = false;                                        // SPARSE: more than eight entries in the schedule's group
+  auto gather_all = [&](int c, int i) {
     const uint8_t* const x = smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + 32 * i * OP_XROW;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[0][e] + gather_base));
-    if (many) {
+    for (int e = 0; e < 8; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[e >> 2][e & 3] + gather_base));
+  };
+  auto group_gather = [&](int c, int i) {                   // of the schedule
+    if constexpr (SPARSE) {
+      const uint8_t* const x = smem + OnePassLds::X + (c & 1) * OP_BM * OP_XROW + 32 * i * OP_XROW;
 #pragma unroll
-      for (int e = 4; e < 8; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[1][e - 4] + gather_base));
+      for (int e = 0; e < 4; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[0][e] + gather_base));
+      if (many) {
+#pragma unroll
+        for (int e = 4; e < 8; ++e) graw[e] = *reinterpret_cast<const uint16_t*>(x + (gp[1][e - 4] + gather_base));
+      } else {
+#pragma unroll
+        for (int e = 4; e < 8; ++e) graw[e] = 0;
+      }
     } else {
-#pragma unroll
-      for (int e = 4; e < 8; ++e) graw[e] = 0;
+      gather_all(c, i);
     }
   };
   auto group_pack = [&](int i) {
@@ -229,7 +238,8 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   };
   auto group_hot = [&](int which) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) zb[j] = *reinterpret_cast<const u32x4*>(hot + which * 2048 + 1024 * half + (32 * j + l31) * 16);
+    for (int j = 0; j < 2; ++j)
+      zb[j] = *reinterpret_cast<const u32x4*>(SPARSE ? hot + which * 2048 + 1024 * half + (32 * j + l31) * 16 : hot + which * 2048 + (32 * j + l31) * 32 + 16 * half);
   };
   auto group_multiply = [&](int which, int i, int j) {
     float16_t& a = which ? accz[i][j] : acc[i][j];
@@ -238,12 +248,11 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
   auto group_all = [&](int c, uint32_t g0, uint32_t g_end) {
     while (w_hi < min(g0 + 16u, g_end)) refill();
     group_read(g0);
-    many = g_end - g0 > 8u;
     group_put(g0, g_end);
     group_pos();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      group_gather(c, i);
+      gather_all(c, i);
       group_pack(i);
 #pragma unroll
       for (int which = 0; which < 2; ++which) {
@@ -323,7 +332,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
 #pragma unroll
     for (int i = 0; i < 2; ++i) read_a(c, 0, i);
     group_read(j_lo);
-    many = j_hi - j_lo > 8u;
+    if (SPARSE) many = j_hi - j_lo > 8u;
     auto behind = [&](int s) {                              // what stands behind matrix instruction s of 32
       if (s == 4) group_put(j_lo, j_hi);
       if (s == 8) group_pos();
@@ -543,7 +552,7 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
 constexpr int kNoGroups128 = 0, kAllGroups128 = 1, kSomeGroups128 = 2;
 
 // Every layer of a step in one grid: `table` holds one entry per layer, ordered by first_block (a multiple of 8).
-template <int DT, bool STORE_Y, int GROUPS>
+template <int DT, bool STORE_Y, int GROUPS, bool SPARSE>
 __global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const FwdParams* table, int n_entries) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
   const table_words tab = (table_words)table;
@@ -555,16 +564,16 @@ __global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const F
   const FwdParams p = read_entry(tab + first * W);
   const int bid = (int)blockIdx.x - p.first_block;
   if (bid >= p.grid_m * p.grid_n) return;
-  if constexpr (GROUPS == kAllGroups128) onepass_body<DT, STORE_Y, true>(p, bid, tab + first * W);
-  else if constexpr (GROUPS == kNoGroups128) onepass_body<DT, STORE_Y, false>(p, bid, tab + first * W);
-  else if (p.group_shift == 7) onepass_body<DT, STORE_Y, true>(p, bid, tab + first * W);
-  else onepass_body<DT, STORE_Y, false>(p, bid, tab + first * W);
+  if constexpr (GROUPS == kAllGroups128) onepass_body<DT, STORE_Y, true, SPARSE>(p, bid, tab + first * W);
+  else if constexpr (GROUPS == kNoGroups128) onepass_body<DT, STORE_Y, false, SPARSE>(p, bid, tab + first * W);
+  else if (p.group_shift == 7) onepass_body<DT, STORE_Y, true, SPARSE>(p, bid, tab + first * W);
+  else onepass_body<DT, STORE_Y, false, SPARSE>(p, bid, tab + first * W);
 }
 
 // One layer, its descriptor in the kernel arguments.
-template <int DT, int GROUPS>
+template <int DT, int GROUPS, bool SPARSE>
 __global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_kernel(FwdParams p) {
-  onepass_body<DT, false, GROUPS == kAllGroups128>(p, (int)blockIdx.x, nullptr);
+  onepass_body<DT, false, GROUPS == kAllGroups128, SPARSE>(p, (int)blockIdx.x, nullptr);
 }
 
 // ---- host side -----------------------------------------------------------------------------
@@ -579,22 +588,39 @@ static int launch(Kernel kern, std::atomic<uint64_t>& lds_limit_set, int64_t blo
   SZO_LAUNCH_CHECK();
   return timing_end(stream);
 }
-template <int DT, bool STORE_Y, int GROUPS>
+template <int DT, bool STORE_Y, int GROUPS, bool SPARSE>
 static int launch_table(const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
   static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
-  return launch(onepass_table_kernel<DT, STORE_Y, GROUPS>, lds_limit_set, blocks, stream, table_dev, entries);
+  return launch(onepass_table_kernel<DT, STORE_Y, GROUPS, SPARSE>, lds_limit_set, blocks, stream, table_dev, entries);
 }
-template <bool STORE_Y>
+template <bool STORE_Y, bool SPARSE>
 static int launch_table(bool bf16, int groups, const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
-  if (bf16) return launch_table<SZO_TILE_BF16, STORE_Y, kNoGroups128>(table_dev, entries, blocks, stream);
-  if (groups == kNoGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kNoGroups128>(table_dev, entries, blocks, stream);
-  if (groups == kAllGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kAllGroups128>(table_dev, entries, blocks, stream);
-  return launch_table<SZO_TILE_F16, STORE_Y, kSomeGroups128>(table_dev, entries, blocks, stream);
+  if (bf16) return launch_table<SZO_TILE_BF16, STORE_Y, kNoGroups128, SPARSE>(table_dev, entries, blocks, stream);
+  if (groups == kNoGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kNoGroups128, SPARSE>(table_dev, entries, blocks, stream);
+  if (groups == kAllGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kAllGroups128, SPARSE>(table_dev, entries, blocks, stream);
+  return launch_table<SZO_TILE_F16, STORE_Y, kSomeGroups128, false>(table_dev, entries, blocks, stream);
 }
-template <int DT, int GROUPS>
+template <int DT, int GROUPS, bool SPARSE>
 static int launch_one(const FwdParams& p, hipStream_t stream) {
   static std::atomic<uint64_t> lds_limit_set{0};
-  return launch(onepass_kernel<DT, GROUPS>, lds_limit_set, (int64_t)p.grid_m * p.grid_n, stream, p);
+  return launch(onepass_kernel<DT, GROUPS, SPARSE>, lds_limit_set, (int64_t)p.grid_m * p.grid_n, stream, p);
+}
+template <bool SPARSE>
+static int launch_one(const szo_linear_desc* d, const FwdParams& p, hipStream_t stream) {
+  if (d->tile_dtype == SZO_TILE_BF16) return launch_one<SZO_TILE_BF16, kNoGroups128, SPARSE>(p, stream);
+  return d->group == 128 ? launch_one<SZO_TILE_F16, kAllGroups128, SPARSE>(p, stream) : launch_one<SZO_TILE_F16, kNoGroups128, SPARSE>(p, stream);
+}
+
+// Whether a launch of `wgs` workgroups takes the SPARSE form: the gathers that it saves against the branch in its schedule, which
+// costs more where no second workgroup shares the CU (two do from 512 on).  us per call, all sixteen slots gathered -> SPARSE, at
+// a density of 0.01 / 0.05 / 0.1 / 0.2 / 0.3 %: one Llama block at 4096 tokens on request 2012 / 2037 / 2068 / 2316 / 2505 -> 1954 / 1996 /
+// 2033 / 2327 / 2535, at 300 tokens 182 / 181 / 186 / 204 / 226 -> 176 / 175 / 182 / 206 / 229, sixteen OPT blocks at 64 tokens 602 / 610 / 617 /
+// 690 / 760 -> 587 / 590 / 612 / 704 / 770; one 4096 x 4096 layer at 600 tokens (160 workgroups) 65.1 / 65.2 / 67.1 / 80.2 / 88.6 -> 64.6 /
+// 64.9 / 68.9 / 84.0 / 92.4, with groups of 64 63.5 / 62.8 / 65.1 / 77.2 / 84.4 -> 62.2 / 61.3 / 66.4 / 80.7 / 88.2; one Llama block with outputs
+// at one token (172) at 0.05 / 0.07 / 0.13 / 0.3 % 146 / 146 / 155 / 199 -> 147 / 149 / 163 / 210.
+constexpr double kSparseEntries = 0.0012, kSparseEntriesAlone = 0.00075;
+static bool sparse_launch(double entries, double weights, int64_t wgs) {
+  return entries <= (wgs >= 512 ? kSparseEntries : kSparseEntriesAlone) * weights;
 }
 
 int64_t onepass_tiles(const szo_linear_desc* d) {
@@ -725,8 +751,7 @@ int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float ep
   const int rc = fill_tiled(p, d, seed, step, eps, plus, minus);
   if (rc != SZO_OK) return rc;
   if (onepass_tiles(d) > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
-  if (d->tile_dtype == SZO_TILE_BF16) return launch_one<SZO_TILE_BF16, kNoGroups128>(p, stream);
-  return d->group == 128 ? launch_one<SZO_TILE_F16, kAllGroups128>(p, stream) : launch_one<SZO_TILE_F16, kNoGroups128>(p, stream);
+  return sparse_launch((double)d->nnz, (double)d->N * (double)d->K, onepass_tiles(d)) ? launch_one<true>(d, p, stream) : launch_one<false>(d, p, stream);
 }
 
 int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
@@ -743,8 +768,11 @@ int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_
   static thread_local std::vector<FwdParams> table;
   table.clear();
   int64_t first_block = 0, offset = 0;
+  double entries = 0.0, weights = 0.0;
   for (int i : order) {
     const szo_linear_desc* d = &descs[i];
+    entries += (double)d->nnz;
+    weights += (double)d->N * (double)d->K;
     FwdParams p;
     const int rc = fill_tiled(p, d, seed, step, eps, partials + offset, partials + T + offset);
     if (rc != SZO_OK) return rc;
@@ -761,7 +789,9 @@ int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_
   const int e = (int)table.size(), with = (int)std::count_if(table.begin(), table.end(), [](const FwdParams& p) { return p.group_shift == 7; });
   const int groups = with == e ? kAllGroups128 : with == 0 ? kNoGroups128 : kSomeGroups128;
   const bool bf16 = descs[order[0]].tile_dtype == SZO_TILE_BF16;
-  return store_y ? launch_table<true>(bf16, groups, t, e, first_block, stream) : launch_table<false>(bf16, groups, t, e, first_block, stream);
+  if (sparse_launch(entries, weights, T))
+    return store_y ? launch_table<true, true>(bf16, groups, t, e, first_block, stream) : launch_table<false, true>(bf16, groups, t, e, first_block, stream);
+  return store_y ? launch_table<true, false>(bf16, groups, t, e, first_block, stream) : launch_table<false, false>(bf16, groups, t, e, first_block, stream);
 }
 
 }  // namespace szo

@@ -100,6 +100,25 @@ def test_groups_of_sensitive_entries(nnz, group):
     assert rel_fro(d.y.cpu().numpy(), want) <= 5e-4
 
 
+@pytest.mark.parametrize("group,tile", [(128, "f16"), (64, "f16"), (64, "bf16")])
+@pytest.mark.parametrize("nnz", [1, 8, 9, 16, 17, 33])
+def test_groups_of_sensitive_entries_of_a_sparse_step(nnz, group, tile):
+    """The same beside a layer without entries: at 0.03 % the kernel gathers half a group where eight entries or fewer are in it."""
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    (o, d), (o2, d2) = make_pair(440 + nnz, 70, 64, 128, group, nnz=nnz), make_pair(439, 70, 512, 256, group, nnz=0)
+    ref = [clone(o), clone(o2)]
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_set_tile_config(11)
+    eps = 0.1
+    szo.szo_zo_step([d.desc(dt), d2.desc(dt)], 7, 0, eps, 0.0, scal, szo.new_workspace(), 0)
+    r = ozo.zo_step(ref, 7, 0, eps, 0.0)
+    lp, lm, _ = scal.cpu().numpy()
+    ltol = 2e-3 / np.sqrt(70 * 576) if tile == "f16" else 5e-3          # as in test_step_matches_oracle
+    assert abs(lp - r["loss_plus"]) <= ltol * r["loss_plus"] and abs(lm - r["loss_minus"]) <= ltol * r["loss_minus"]
+    want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, o.group, o.sp_idx, o.sp_val, r["z"][0], -1, eps, "E")
+    assert rel_fro(d.y.cpu().numpy(), want) <= (5e-4 if tile == "f16" else 4e-3)
+
+
 def test_layers_that_share_their_output_buffer_run_one_after_the_other():
     """One buffer for the outputs of a stack holds the last layer's afterwards: concurrent workgroups would mix them."""
     (oa, ob), (da, db) = [list(t) for t in zip(*[make_pair(411 + i, 300, 320, 256, 128, 5e-3, nnz_base=8192 * i) for i in range(2)])]

@@ -21,3 +21,36 @@ def test_the_update_of_a_stack_keeps_eight_waves_per_simd(tmp_path):
     use = {name: (int(re.search(r"amdhsa_group_segment_fixed_size (\d+)", body).group(1)),
                   int(re.search(r"amdhsa_next_free_vgpr (\d+)", body).group(1))) for name, body in kernels}
     assert len([u for u in use.values() if u[0] == 0 and u[1] <= 32]) == 2, use      # table staged, table in the arguments
+
+
+def _blocks(text, kernel):
+    """Straight stretches of a kernel's instructions: between labels and branches."""
+    start = text.index("\n" + kernel + ":")
+    blocks, cur = [], []
+    for line in text[start:text.index(".section", start)].splitlines():
+        t = line.split(";")[0].strip()
+        if re.match(r"\.LBB\w+:", t) or t.startswith(("s_cbranch", "s_branch")):
+            blocks.append(cur)
+            cur = []
+        elif t and not t.startswith("."):
+            cur.append(t.split()[0])
+    return blocks + [cur]
+
+
+@pytest.mark.skipif(not HIPCC, reason="no hipcc")
+def test_further_groups_of_sensitive_entries_gather_beside_their_products(tmp_path):
+    """One-dense-pass kernel: the loop over a chunk's entries beyond the first sixteen is one stretch of sixteen gathers and
+    eight matrix instructions in every form (a branch between them cost dense masks 2 to 6 %), and the forms for denser masks
+    have none in the schedule's group either."""
+    out = str(tmp_path / "onepass.s")
+    subprocess.check_call([HIPCC, "--cuda-device-only", "-S"] + szo_build.COMMON + szo_build.DEVICE +
+                          [os.path.join(szo_build.CSRC, "szo_onepass.hip"), "-o", out], stderr=subprocess.DEVNULL)
+    text = open(out).read()
+    kernels = re.findall(r"\.amdhsa_kernel (\S*onepass_\S*kernel\S*)", text)
+    assert len(kernels) >= 11
+    whole_schedules = 0
+    for kernel in kernels:
+        count = [(sum(i.startswith("v_mfma") for i in b), sum(i.startswith("ds_read_u16") for i in b)) for b in _blocks(text, kernel)]
+        assert (8, 16) in count, (kernel, [c for c in count if c[0]])
+        whole_schedules += any(m > 8 and g == 16 for m, g in count)
+    assert 2 * whole_schedules >= len(kernels)
