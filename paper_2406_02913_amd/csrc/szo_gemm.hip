@@ -281,7 +281,10 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
 
     // Per-tile bookkeeping, done before the MFMA loop that stages the tile.  Tiles with at most 64
     // entries (the normal case) take the in-slot path: sc_cnt entries starting at window offset
-    // sc_e0, one per lane.  Larger tiles are left to scatter_range after the loop.
+    // sc_e0, one per lane.  Of larger tiles the 16-slot schedule takes the first 64 that way and leaves the rest to
+    // scatter_range after the loop; the 32-slot one leaves all of them to it.  A forward with 1 % of sensitive weights, half of them in
+    // 1 % of the rows, us with the whole tile / the rest of it behind the loop: 4096 x 4096 at 450 tokens 89 / 81, 1024 x 4096 at
+    // 700 80 / 71, 4096 x 11008 at 1200 261 / 249 (32 slots: a Llama block's step at 4096 tokens takes 0.7 % longer with the rest behind it).
     uint32_t sc_cnt = 0, sc_e0 = 0, big_lo = 0, big_hi = 0;
     auto prepare_scatter = [&](int kt) {
       sc_cnt = 0; big_lo = 0; big_hi = 0;
@@ -294,7 +297,13 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       const uint32_t hi = __builtin_amdgcn_readlane(tp_reg, kt & 63), lo = tile_lo;
       tile_lo = hi;
       if (hi <= lo) return;
-      if (hi - lo <= 64u) {
+      if (SLOTS == 16) {
+        const uint32_t first = min(hi, lo + 64u);
+        if (lo < win_lo || first > win_hi) refill(lo & ~3u);
+        sc_cnt = first - lo;
+        sc_e0 = lo - win_lo;
+        big_lo = first; big_hi = hi;
+      } else if (hi - lo <= 64u) {
         if (lo < win_lo || hi > win_hi) refill(lo & ~3u);
         sc_cnt = hi - lo;
         sc_e0 = lo - win_lo;

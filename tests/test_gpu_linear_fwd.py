@@ -72,6 +72,23 @@ def test_entries_of_a_tile(nnz, tile_cfg):
         assert rel_fro(y, want) <= tol
 
 
+# More than the schedule of 128-row tiles scatters by itself: the rest of a tile stands behind it, in this window of 256 entries or the next
+@pytest.mark.parametrize("nnz", [63, 66, 127, 128, 129, 191, 255, 256, 257, 320])
+def test_entries_beyond_the_schedule(nnz):
+    szo.szo_set_tile_config(1)
+    for dt, dtname, tol in DTYPES:
+        o, d = make_pair(61, 70, 128, 192, 32, nnz=nnz)         # two bands and three tiles of columns, their entries one after the other
+        z = ophilox.zbar(9, 2, 0, o.sp_idx.size)
+        y = _run(d, -1, 1e-3, 9, 2, dt)
+        want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, 32, o.sp_idx, o.sp_val, z, -1, 1e-3, "D", dtname)
+        assert rel_fro(y, want) <= tol
+        o, d = make_pair(62, 70, 64, 256, 32, nnz=4 * nnz)      # about that many in each of four tiles
+        z = ophilox.zbar(9, 2, 0, o.sp_idx.size)
+        y = _run(d, +1, 1e-3, 9, 2, dt)
+        want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, 32, o.sp_idx, o.sp_val, z, +1, 1e-3, "D", dtname)
+        assert rel_fro(y, want) <= tol
+
+
 def test_perturbation_difference_is_linear_in_z():
     # y(+) - y(-) = 2 eps x Z^T: checks the sign convention and that only masked entries move
     o, d = make_pair(7, 96, 256, 256, 32, 5e-3)
