@@ -685,11 +685,24 @@ static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, boo
 // 48 tokens (664 / 1328 / 1992 workgroups) 43.5 / 36.3, 55.1 / 57.1, 70.5 / 77.3, one OPT block at 64 tokens (2304) 83 / 93; with the
 // sensitive weights rounded as in the tile for both signs, where the registers of eight waves leave no room for a second
 // workgroup on a CU, a 5000 x 4160 layer at 48 / 77 tokens (237 / 395) 23.5 / 22.1, 30.8 / 35.3, a Llama block at 48 tokens 89 / 130.
-// `subs`: 16-row subtiles of a workgroup.
-static int split_waves(const FewPlan& p, bool one_sign, int64_t workgroups, int64_t longest_k, int subs) {
-  const int64_t blocks = (longest_k + 127) / 128, wide = p.dual() ? 2304 : p.dequant >= D_TILE_F16 && !one_sign ? 256 : 1024;
+// Sensitive entries are a chain of their own, a memory round trip per sixteen of them, which more waves shorten: sixteen waves
+// where each would still have about 80 of a band's, eight up to 2304 workgroups where a band of the longest K has many against
+// the number of workgroups.  us with 8 / 16 waves: a forward at one token and 1 %, 11008 x 4096 17.8 / 15.8, 16384 x 4096 with half the
+// entries in 1 % of the rows 42.2 / 35.4; below the line a step of 16384 x 8192 at 16 tokens and 0.1 % 28.0 / 29.0.  us per step with 4 / 8
+// (e = entries of a band over workgroups; "rows": half of them in 1 % of the rows): two OPT blocks at one token, 0.05 %, rows (e = 0.46)
+// 63 / 54, two Mistral blocks at 16 tokens, 0.1 %, rows (0.7) 92 / 74, three at one token, 0.3 %, rows (1.4) 152 / 129; below it three Llama
+// blocks at 4 tokens and 0.05 % (0.2) 76 / 80.  With v and eps z rounded together for both signs, bf16 tile: one Llama block at 16 tokens
+// and 0.5 % (5.3) 89 / 79, at 4 and 0.2 % (2.1) 51 / 52; two OPT blocks at 21, 0.2 %, rows (0.9) 141 / 197, at one token and 0.5 % (4.6)
+// 95 / 114, one at 32, 1 %, rows (9) 338 / 248.  Between those lines rows full of entries take up to 8 % longer with four than with
+// eight, evenly spread ones 20 to 40 % less.
+// `subs`: 16-row subtiles of a workgroup; `band_entries`: of a band of the longest K, on average.
+static int split_waves(const FewPlan& p, bool one_sign, int64_t workgroups, int64_t longest_k, int subs, double band_entries) {
+  const int64_t blocks = (longest_k + 127) / 128;
+  const bool both_rounded = p.dequant >= D_TILE_F16 && !one_sign;
+  const double many = both_rounded ? (workgroups <= 1024 ? 2.5 : 6.0) : 0.45;
+  const int64_t wide = p.dual() || band_entries > many * (double)workgroups ? 2304 : both_rounded ? 256 : 1024;
   if (workgroups > wide || blocks * subs < 16) return 4;
-  return workgroups <= 256 && blocks > 96 ? 16 : 8;
+  return workgroups <= 256 && (blocks > 96 || 0.25 * subs * band_entries >= 1300.0) ? 16 : 8;
 }
 
 template <int MODE, int R, bool DUAL>
@@ -717,6 +730,7 @@ static int stream_once_rule(int slices, int64_t launch_code_bytes) {
 struct LaunchTotals {                                       // over a launch's matrices
   int slices = 0, subs = 1;                                 // most slices; most 16-row subtiles of a split workgroup
   int64_t units = 0, k = 0, rows = 0, code_bytes = 0;       // workgroups per slice, longest K, most token rows, codes
+  double entries = 0.0, weights = 0.0;
   void add(const FewPlan& p, const szo_linear_desc* d) {
     slices = std::max(slices, p.slices(d));
     subs = std::max(subs, 4 >> p.part_shift);
@@ -724,6 +738,8 @@ struct LaunchTotals {                                       // over a launch's m
     k = std::max(k, d->K);
     rows = std::max(rows, d->M);
     code_bytes += ::szo::code_bytes(d);
+    entries += (double)d->nnz;
+    weights += (double)d->N * (double)d->K;
   }
 };
 // One launch of the matrices described by `a` (their table or the single one).
@@ -737,7 +753,7 @@ static int launch_plan(const FewPlan& p, const LaunchTotals& t, bool one_sign, S
   if (rc != SZO_OK) return rc;
   if (p.split()) {
     rc = split_launch(SplitLaunch{p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, one_sign, t.subs,
-                                  split_waves(p, one_sign, wgs, t.k, t.subs), wgs}, a, stream);
+                                  split_waves(p, one_sign, wgs, t.k, t.subs, 64.0 * (double)t.k * t.entries / t.weights), wgs}, a, stream);
     if (rc != SZO_OK) return rc;
   } else {
     const dim3 blocks((unsigned)wgs);

@@ -1,0 +1,88 @@
+"""The rules that choose a kernel and its launch, evaluated on the host by a probe that is compiled here from the library's own
+sources (no GPU): waves per workgroup of the split kernel, and who takes a step where several kernels could."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2406_02913_amd import build as szo_build
+
+HIPCC = szo_build.HIPCC if os.path.exists(szo_build.HIPCC) else shutil.which("hipcc")
+pytestmark = pytest.mark.skipif(not HIPCC, reason="no hipcc")
+
+PROBE = r"""
+#include "szo_smallm.hip"
+#include <cstdio>
+using namespace szo;
+static SplitLaunch g_last;
+namespace szo { int split_launch(const SplitLaunch& l, const SmallArgs&, hipStream_t) { g_last = l; return SZO_OK; } }
+// a line: layers, token rows, N, K, group, entries, bf16, table format, two sets, one sign, separate launches, asked for
+int main() {
+  long long n, M, N, K, group, nnz, bf16, lut, two, one, separate, asked;
+  while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld", &n, &M, &N, &K, &group, &nnz, &bf16, &lut, &two, &one, &separate, &asked) == 12) {
+    szo_linear_desc d{};
+    d.M = M; d.N = N; d.K = K; d.group = (int)group; d.nnz = nnz;
+    d.tile_dtype = bf16 ? SZO_TILE_BF16 : SZO_TILE_F16;
+    d.format = lut ? SZO_FORMAT_LUT : SZO_FORMAT_UNIFORM;
+    d.x_minus = two ? &d : nullptr;
+    std::vector<szo_linear_desc> descs((size_t)n, d);
+    LaunchShape shape;
+    for (const auto& e : descs) shape.add(&e);
+    const FewPlan p = few_plan(&d, shape, two != 0);
+    LaunchTotals t;
+    for (const auto& e : descs) t.add(p, &e);
+    SmallArgs a{};
+    g_last = SplitLaunch{};
+    if (p.split() && launch_plan(p, t, one != 0, a, nullptr) != SZO_OK) return 1;
+    const bool few = small_m_eligible(descs.data(), (int)n, false, separate != 0, one ? 1 : 2);
+    printf("%d %d %d %lld\n", few, g_last.waves, g_last.workgroups,
+           one ? 0ll : (long long)onepass_partials(descs.data(), (int)n, few, asked != 0, false, separate != 0));
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """ask(case, ...) -> [(few-token path, waves, workgroups, loss partials of the one-dense-pass kernel or 0), ...]"""
+    if not os.path.exists(szo_build.LIB):
+        szo_build.build()
+    where = tmp_path_factory.mktemp("rules")
+    src, exe = str(where / "probe.hip"), str(where / "probe")
+    with open(src, "w") as f:
+        f.write(PROBE)
+    subprocess.check_call([HIPCC, "--cuda-host-only"] + szo_build.COMMON + [src, "-o", exe, "-L" + os.path.dirname(szo_build.LIB), "-l:" + os.path.basename(szo_build.LIB),
+                           "-Wl,-rpath," + os.path.dirname(szo_build.LIB), "-Wl,--unresolved-symbols=ignore-all"], stderr=subprocess.DEVNULL)      # (the device code, which nothing here launches)
+
+    def run(*cases):
+        keys = ("layers", "M", "N", "K", "group", "nnz", "bf16", "lut", "two_sets", "one_sign", "separate", "asked_for")
+        lines = "\n".join(" ".join(str(int(c.get(k, 0))) for k in keys) for c in cases)
+        out = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split("\n")
+        return [tuple(int(v) for v in line.split()) for line in out[:len(cases)]]
+    return run
+
+
+def _layer(N, K, M, density, layers=1, group=128, **kw):
+    return dict(layers=layers, M=M, N=N, K=K, group=group, nnz=int(density * N * K + 0.5), **kw)
+
+
+@pytest.mark.parametrize("case,waves,workgroups", [
+    # sixteen waves: long K, or many entries per band
+    (_layer(11008, 4096, 1, 1e-2, one_sign=1), 16, 172), (_layer(11008, 4096, 1, 3e-3, one_sign=1), 8, 172),
+    (_layer(16384, 12416, 1, 1e-4, one_sign=1), 16, 256), (_layer(16384, 12288, 1, 1e-4, one_sign=1), 8, 256),
+    (_layer(4096, 4096, 16, 1e-2, one_sign=1), 8, 256),               # cut in four: each part works on its own quarter of the entries
+    # eight, and four beyond 1024 workgroups unless the mask is dense
+    (_layer(16384, 4096, 64, 1e-3), 8, 1024), (_layer(8192, 16384, 48, 1e-4, layers=3), 4, 1152), (_layer(8192, 16384, 48, 1e-3, layers=3), 8, 1152),
+    # both signs rounded with the weights: four beyond 256
+    (_layer(5000, 4160, 48, 1e-3, group=64, bf16=1), 8, 237), (_layer(5000, 4160, 64, 1e-3, group=64, bf16=1), 4, 316),
+    (_layer(5000, 4160, 64, 1e-2, group=64, bf16=1), 8, 316), (_layer(5000, 4160, 64, 1e-3, group=64, bf16=1, one_sign=1), 8, 316),
+    (_layer(16384, 4160, 80, 1e-2, group=64, bf16=1), 4, 1280),
+    (_layer(4096, 8192, 48, 3e-2, group=64, bf16=1, layers=12), 8, 2304), (_layer(4096, 8192, 48, 3e-2, group=64, bf16=1, layers=13), 4, 2496),
+    # two blocks of K: nothing to split
+    (_layer(5000, 256, 4, 1e-2), 4, 158),
+])
+def test_waves_of_the_split_kernel(ask, case, waves, workgroups):
+    (_, got, wgs, _), = ask(case)
+    assert (got, wgs) == (waves, workgroups)
