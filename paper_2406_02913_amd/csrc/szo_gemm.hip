@@ -1099,9 +1099,9 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
     if (2 * T <= kNoAllocMaxPartials || !few_all) break;
   }
   // ... or, where the tiled kernel would run, the one-dense-pass kernel under szo_zo_step's conditions, if its partials fit.
-  // (Not in place of the few-token path: launched layer by layer it does not fill the chip; one OPT block at 405 tokens
-  // 465 us with the few-token kernels, 479 with this one.)
-  int64_t one_T = few_token_enabled() && small_m_eligible(descs, n, false, true, 2) ? 0 : onepass_partials(descs, n, false, false, false, true);
+  // (Not in place of the few-token path, but for layers beyond 128 tokens that only its split kernel takes: launched layer by
+  // layer it does not fill the chip; one OPT block at 405 tokens 465 us with the few-token kernels, 479 with this one.)
+  int64_t one_T = onepass_partials(descs, n, few_token_enabled() && small_m_eligible(descs, n, false, true, 2), false, false, true);
   if (2 * one_T > kNoAllocMaxPartials) one_T = 0;
   if (one_T) T = one_T;
   if (2 * T > kNoAllocMaxPartials) return SZO_EUNSUPPORTED;

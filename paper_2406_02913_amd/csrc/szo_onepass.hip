@@ -643,6 +643,7 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    64): four Llama blocks with the bf16 tile at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393; there, and against
 //    the 128-row tiles that such layers run on otherwise, both paths are estimated from sizes and density (fitted with
 //    split_rounded_us): one OPT block at 128 tokens and 0.1 / 0.7 / 1 %, tiles -> this one 379 / 437 / 463 -> 253 / 473 / 568.
+//    Beyond 128 tokens, where that path takes a layer of up to 2304 workgroups, too: 11008 x 4160 with groups of 64 at 200 tokens 77 -> 60.
 //  * asked for at more tokens than the few-token path takes by itself, against its slices: from 160 workgroups on (110
 //    with smaller groups, whose slices are slower).  A 2048 x 12288 layer at 512 tokens (64 of them) 91 -> 154, a 4096 x 16384
 //    layer at 512 / 700 (128 / 176) 187 / 240 -> 210 / 214.
@@ -689,16 +690,25 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
   const double rho = entries / weights;
   if (store_y) return wgs >= 4 && rho <= 0.015;
   if (asked_for && stream && !few) return wgs >= (groups_of_128 ? 160 : 110);
+  const bool rounded_many = few && !stream && most_tokens > 128;         // the split kernel against this one, both estimated
+  if (separate && few && !rounded_many) return false;
   if (!(asked_for && !stream)) {
-    if (few && (wgs < 512 ? stream || most_tokens <= 64 || wgs < 256 : most_tokens <= (stream ? 32 : 16))) return false;
+    if (few && !rounded_many && (wgs < 512 ? stream || most_tokens <= 64 || wgs < 256 : most_tokens <= (stream ? 32 : 16))) return false;
     if (few && stream) return most_tokens > 64 || 205.0 * longest_k <= wg_k;
-    if (!few && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
+    if ((!few || rounded_many) && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
   }
-  if (!stream && most_tokens <= 128) {
-    const double k = longest_k / 1024.0;
-    const double us = 26.6 + 3.5 * k + std::max(9.3 * k * (1.0 + 176.0 * rho), 0.0221 * wg_k / 1024.0 * (1.0 + 42.0 * rho));
+  if (!stream && (few || most_tokens <= 128)) {
+    auto estimate = [&](double k, double work) {            // both in units of 1024 columns
+      return 26.6 + 3.5 * k + std::max(9.3 * k * (1.0 + 176.0 * rho), 0.0221 * work * (1.0 + 42.0 * rho));
+    };
+    double us = estimate(longest_k / 1024.0, wg_k / 1024.0);
+    if (rounded_many && separate) {
+      us = 0.0;
+      for (int i = 0; i < n; ++i)
+        if (descs[i].M > 0 && descs[i].N > 0) us += estimate((double)descs[i].K / 1024.0, (double)onepass_tiles(&descs[i]) * (double)descs[i].K / 1024.0);
+    }
     if (us >= small_m_rounded_us(descs, n, few, separate)) return false;
-    if (few) return true;
+    if (few && !rounded_many) return true;
   }
   // asked for in a step too small for a grouped tiled launch (384 tiles of 256 x 128): the tiles would run layer by layer and sign
   if (asked_for && tiles < 384) return wgs >= 32;

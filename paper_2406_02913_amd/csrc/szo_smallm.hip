@@ -550,7 +550,7 @@ struct LaunchShape {
   double band_k = 0.0, longest_k = 0.0;                     // K summed over those bands, longest K
   double slice_entries = 0.0, row_entries = 0.0;            // sensitive entries times slices, times token rows / 16
   double entries = 0.0, weights = 0.0, sum_k = 0.0;
-  int64_t matrices = 0, tiles128 = 0;                       // 128 x 128 output tiles
+  int64_t matrices = 0, tiles128 = 0, most_tokens = 0;      // 128 x 128 output tiles
   double tile_k = 0.0;                                      // K summed over those tiles
   void add(const szo_linear_desc* d) {
     if (d->M <= 0 || d->N <= 0) return;
@@ -566,6 +566,7 @@ struct LaunchShape {
     weights += (double)d->N * (double)d->K;
     sum_k += k;
     ++matrices;
+    most_tokens = std::max<int64_t>(most_tokens, d->M);
     tiles128 += tiles;
     tile_k += (double)tiles * k;
   }
@@ -782,11 +783,17 @@ constexpr int64_t kSplitOnlyTokens = 64;
 // evenly and half in 1 % of the rows: 20 of 3028 cases are more than 3 % slower than the tiles (20 % at most: a 300 x 320 layer at
 // one token), where token counts alone left 74 (65 %).  us per step at 1 %, split against tiles: a 16384 x 4096 layer at 64 / 128
 // tokens 140 / 266 against 191 / 186, three Llama blocks at 64 tokens 869 against 689, one OPT block at 128 tokens 437 against 463.
-static double split_rounded_us(const LaunchShape& l) {
-  return 13.5 + std::max(0.016 * (double)l.bands16 + 0.0036 * l.band_k + 0.02 * l.slice_entries, l.longest_k * (1.9 + 5.3 * l.percent()));
+// Beyond 128 tokens (single layers of 64..16384 rows x 256..16384 columns at 129..4000, 0.01..1 %) an entry costs more, a second set
+// of activations the larger part of a pass again, and tiles take longer for a column, two launches of them for a step.  us on the
+// split kernel against the others: 4059 x 6848 at 473 tokens and 0.3 % 154 against 141 on the one-dense-pass kernel; two sets of 4096 x 4160
+// at 200 and 1 % 204 against 185 in tiles, of 9902 x 4096 at 159 and 0.1 % 127 against 175, of 6111 x 384 at 135 25 against 41.
+static double split_rounded_us(const LaunchShape& l, bool two_sets) {
+  const bool many_tokens = l.most_tokens > 128, twice = many_tokens && two_sets;
+  return 13.5 + std::max((twice ? 0.021 : 0.016) * (double)l.bands16 + (twice ? 1.65 : 1.0) * (0.0036 * l.band_k + (many_tokens ? 0.025 : 0.02) * l.slice_entries),
+                         (twice ? 1.65 : 1.0) * l.longest_k * (1.9 + 5.3 * l.percent()));
 }
 static double tiled_us(const LaunchShape& l, int forwards) {
-  const double chain = 9.1 * (1.0 + 0.05 * l.percent()), share = 0.0123 * forwards * l.tile_k * (1.0 + 0.73 * l.percent());
+  const double chain = (l.most_tokens > 128 ? 11.5 : 9.1) * (1.0 + 0.05 * l.percent()), share = 0.0123 * forwards * l.tile_k * (1.0 + 0.73 * l.percent());
   const bool one_launch = l.matrices == 1 ? forwards == 1 : forwards * l.tiles128 >= 384;
   return 7.0 + 11.3 * (double)(forwards * l.matrices) + std::max(chain * (one_launch ? l.longest_k : forwards * l.sum_k), share);
 }
@@ -823,8 +830,12 @@ static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, 
 static double rounded_us(const szo_linear_desc* descs, int n, bool split, int forwards, bool separate) {
   if (!separate) {
     LaunchShape shape;
-    for (int i = 0; i < n; ++i) shape.add(&descs[i]);
-    return split ? split_rounded_us(shape) : tiled_us(shape, forwards);
+    bool two_sets = false;
+    for (int i = 0; i < n; ++i) {
+      shape.add(&descs[i]);
+      two_sets = two_sets || (forwards == 2 && descs[i].x_minus);
+    }
+    return split ? split_rounded_us(shape, two_sets) : tiled_us(shape, forwards);
   }
   double us = 0.0;
   for (int i = 0; i < n; ++i) us += rounded_us(&descs[i], 1, split, forwards, false);

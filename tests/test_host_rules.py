@@ -86,3 +86,35 @@ def _layer(N, K, M, density, layers=1, group=128, **kw):
 def test_waves_of_the_split_kernel(ask, case, waves, workgroups):
     (_, got, wgs, _), = ask(case)
     assert (got, wgs) == (waves, workgroups)
+
+
+@pytest.mark.parametrize("case,few,onepass", [
+    # only the split kernel can, up to 128 tokens as measured there; beyond, it or the one-dense-pass kernel or the tiles
+    (_layer(11008, 4160, 200, 1e-3, group=64), True, True), (_layer(11008, 4160, 200, 1e-3, group=64, separate=1), True, True),
+    (_layer(4059, 6848, 473, 3e-3, group=32), True, True), (_layer(5344, 3584, 208, 1e-4, group=32, bf16=1), True, False),
+    (_layer(3360, 4288, 535, 1e-3, group=64, bf16=1), True, False), (_layer(9196, 6592, 165, 1e-4, group=64, separate=1), True, False),
+    (_layer(1653, 896, 419, 1e-4, group=64, bf16=1), True, False), (_layer(1653, 896, 419, 1e-4, group=64, bf16=1, asked_for=1), True, False),
+    (_layer(4096, 4160, 128, 1e-3, group=64), True, False), (_layer(4096, 4160, 128, 1e-3, group=64, separate=1), True, False),
+    # ... with two sets of activations: it or the tiles
+    (_layer(4096, 4160, 200, 1e-2, group=32, bf16=1, two_sets=1), False, False), (_layer(5782, 3264, 394, 1e-4, group=64, two_sets=1), False, False),
+    (_layer(9902, 4096, 159, 1e-3, group=64, bf16=1, two_sets=1), True, False), (_layer(3638, 8128, 137, 1e-2, group=64, two_sets=1), True, False),
+])
+def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepass):
+    (got_few, _, _, partials), = ask(case)
+    assert (bool(got_few), partials > 0) == (few, onepass)
+
+
+@pytest.mark.parametrize("case,few", [
+    # layers of few rows: a step at any of these sizes, a single forward up to 1536 bands and slices or well inside the line
+    (_layer(258, 5248, 6437, 1e-3, one_sign=1), False), (_layer(258, 5248, 6437, 1e-3), True),
+    (_layer(285, 1152, 5600, 1e-3, one_sign=1), False), (_layer(300, 4096, 6000, 1e-3, lut=1, one_sign=1), False),
+    (_layer(1231, 15872, 1741, 1e-3, lut=1, one_sign=1), False), (_layer(1231, 15872, 1741, 1e-3, lut=1), True),
+    (_layer(300, 4096, 1000, 1e-3, one_sign=1), True), (_layer(635, 6400, 2409, 1e-4, one_sign=1), True),
+    (_layer(111, 9088, 7496, 3e-3, one_sign=1), True), (_layer(4096, 1024, 450, 1e-3, one_sign=1), True),
+    # the group of a table layer decides nothing
+    (_layer(1803, 2432, 990, 1e-3, lut=1), True), (_layer(1803, 2432, 990, 1e-3, lut=1, group=64), True),
+    (_layer(1803, 2432, 990, 1e-3, lut=1, group=32), True),
+])
+def test_who_takes_many_tokens_of_few_rows(ask, case, few):
+    (got, _, _, _), = ask(case)
+    assert bool(got) == few
