@@ -805,17 +805,23 @@ constexpr int64_t kSplitOnlyColumns = 1 << 23;
 // other kernels -> this path: a forward of a 300 x 4096 layer at 450 / 1000 / 4000 tokens 55 / 56 / 56 -> 11 / 17 / 46, 64 x 16384 at
 // 600 / 8000 tokens 203 / 208 -> 21 / 80, 1024 x 4096 at 600 / 2000 tokens 56 / 57 -> 26 / 48, 4096 x 1024 at 450 tokens 18.9 -> 15.4;
 // steps of the same 132 / 69 / 78 -> 18 / 25 / 50, 422 / 208 -> 28 / 88, 65 / 66 -> 35 / 57, 29.7 -> 23.8; beyond the line a step over 4096 x
-// 4096 at 600 tokens 67 -> 68, a forward 57 -> 59.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
+// 4096 at 600 tokens 67 -> 68, a forward 57 -> 59, of 258 x 5248 at 6437 69 -> 78.  Forwards with tables (256 x 256 tiles): 300 x 4096 at
+// 6000 tokens 87 -> 102, 445 x 9984 at 3681 232 -> 176, 1231 x 15872 at 1741 353 -> 398.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
 // forward of a 1024 x 1024 / 4096 x 4096 layer at 300 tokens 21 / 70 -> 9 / 45.
 // (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.  The tiles' times are those of the
 // 128 x 128 schedule that scattered behind its last matrix instruction; it takes 5 % less by now, and the line stays where both were measured.)
 static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (d->K < 1024) return false;
-  const FewEstimate e = few_estimate(launch, d->x_minus && forwards == 2, d->format == SZO_FORMAT_LUT, d->group != 128);
-  // (the estimates are of steps up to 448 tokens: with groups below 128 and dense masks a forward over more of them takes up to that much longer)
-  const double few = std::min(e.split * (d->group != 128 ? 1.35 : 1.0), e.stream + 3.0 + 0.0015 * (double)launch.bands16) *
-                     (1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0));
-  return few < (forwards == 2 ? 10.0 + 11.8 * launch.longest_k : 5.0 + 12.7 * launch.longest_k);
+  const bool lut = d->format == SZO_FORMAT_LUT, plain = !lut && d->group != 128, single = forwards == 1;      // (a table layer's group means nothing)
+  const FewEstimate e = few_estimate(launch, d->x_minus && !single, lut, plain);
+  // (the estimates are of steps up to 448 tokens: with groups below 128 and dense masks a forward over more of them takes up to that much longer.)
+  // A single forward has the others' time against it once, not twice: there the estimates have to hold beyond 448 tokens.  From six
+  // workgroups per CU on they fall short; with tables so does that of the stream kernel, which looks up whole strips again for every slice.
+  double few = std::min(e.split * (plain ? 1.35 : 1.0), e.stream + 3.0 + 0.0015 * (double)launch.bands16);
+  if (single && lut) few = e.split <= e.stream ? e.split : e.stream + (0.032 * (double)launch.strips16 * launch.longest_k - 0.0026 * launch.band_k);
+  else if (single && launch.bands16 > 1536) few *= 1.15;
+  few *= 1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0);
+  return few < (!single ? 10.0 + 11.8 * launch.longest_k : 5.0 + (lut ? 20.0 : 12.7) * launch.longest_k);
 }
 static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (!stream_ok(d))

@@ -107,13 +107,14 @@ def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepas
 @pytest.mark.parametrize("case,few", [
     # layers of few rows: a step at any of these sizes, a single forward up to 1536 bands and slices or well inside the line
     (_layer(258, 5248, 6437, 1e-3, one_sign=1), False), (_layer(258, 5248, 6437, 1e-3), True),
-    (_layer(285, 1152, 5600, 1e-3, one_sign=1), False), (_layer(300, 4096, 6000, 1e-3, lut=1, one_sign=1), False),
-    (_layer(1231, 15872, 1741, 1e-3, lut=1, one_sign=1), False), (_layer(1231, 15872, 1741, 1e-3, lut=1), True),
-    (_layer(300, 4096, 1000, 1e-3, one_sign=1), True), (_layer(635, 6400, 2409, 1e-4, one_sign=1), True),
-    (_layer(111, 9088, 7496, 3e-3, one_sign=1), True), (_layer(4096, 1024, 450, 1e-3, one_sign=1), True),
+    (_layer(285, 1152, 5600, 1e-3, one_sign=1), False), (_layer(300, 4096, 1000, 1e-3, one_sign=1), True),
+    (_layer(635, 6400, 2409, 1e-4, one_sign=1), True), (_layer(111, 9088, 7496, 3e-3, one_sign=1), True),
+    # with tables
+    (_layer(300, 4096, 6000, 1e-3, lut=1, one_sign=1), False), (_layer(300, 4096, 6000, 1e-3, lut=1), True),
+    (_layer(1231, 15872, 1741, 1e-3, lut=1, one_sign=1), False), (_layer(445, 9984, 3681, 1e-4, lut=1, one_sign=1), False), (_layer(799, 2304, 1037, 1e-4, lut=1, one_sign=1), True),
     # the group of a table layer decides nothing
-    (_layer(1803, 2432, 990, 1e-3, lut=1), True), (_layer(1803, 2432, 990, 1e-3, lut=1, group=64), True),
-    (_layer(1803, 2432, 990, 1e-3, lut=1, group=32), True),
+    (_layer(1803, 2432, 700, 1e-3, lut=1), True), (_layer(1803, 2432, 700, 1e-3, lut=1, group=64), True),
+    (_layer(1803, 2432, 700, 1e-3, lut=1, group=32), True),
 ])
 def test_who_takes_many_tokens_of_few_rows(ask, case, few):
     (got, _, _, _), = ask(case)
