@@ -643,7 +643,8 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    64): four Llama blocks with the bf16 tile at 17 / 64 / 100 tokens 264 / 500 / 713 -> 218 / 220 / 393; there, and against
 //    the 128-row tiles that such layers run on otherwise, both paths are estimated from sizes and density (fitted with
 //    split_rounded_us): one OPT block at 128 tokens and 0.1 / 0.7 / 1 %, tiles -> this one 379 / 437 / 463 -> 253 / 473 / 568.
-//    Beyond 128 tokens, where that path takes a layer of up to 2304 workgroups, too: 11008 x 4160 with groups of 64 at 200 tokens 77 -> 60.
+//    Beyond 128 tokens, where that path takes a layer of up to 2304 workgroups, too: 11008 x 4160 with groups of 64 at 200 tokens 77 -> 60,
+//    2080 x 448 at 905 30 -> 19, 4590 x 1024 with the bf16 tile at 491 42 -> 32, the other way 3360 x 4288 with it at 535 83 against 90.
 //  * asked for at more tokens than the few-token path takes by itself, against its slices: from 160 workgroups on (110
 //    with smaller groups, whose slices are slower).  A 2048 x 12288 layer at 512 tokens (64 of them) 91 -> 154, a 4096 x 16384
 //    layer at 512 / 700 (128 / 176) 187 / 240 -> 210 / 214.
@@ -670,7 +671,7 @@ void onepass_force(int how) { g_force_onepass = how; }
 static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_for, bool store_y, bool separate) {
   int64_t wgs = 0, tiles = 0, most_tokens = 0;
   double weights = 0.0, entries = 0.0, here = 0.0, tiled = 0.0, wg_k = 0.0, longest_k = 0.0;
-  bool stream = true, groups_of_128 = true;
+  bool stream = true, groups_of_128 = true, bf16 = false;
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc* d = &descs[i];
     if (d->M == 0 || d->N == 0) continue;
@@ -686,6 +687,7 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
     tiled += size * (double)((d->M + 255) / 256) * 4.0;
     stream = stream && d->K % 128 == 0 && d->tile_dtype == SZO_TILE_F16;
     groups_of_128 = groups_of_128 && d->group == 128;
+    bf16 = bf16 || d->tile_dtype == SZO_TILE_BF16;
   }
   const double rho = entries / weights;
   if (store_y) return wgs >= 4 && rho <= 0.015;
@@ -698,8 +700,10 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
     if ((!few || rounded_many) && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
   }
   if (!stream && (few || most_tokens <= 128)) {
-    auto estimate = [&](double k, double work) {            // both in units of 1024 columns
-      return 26.6 + 3.5 * k + std::max(9.3 * k * (1.0 + 176.0 * rho), 0.0221 * work * (1.0 + 42.0 * rho));
+    // both in units of 1024 columns; beyond 128 tokens fitted again, where the launch and the walk of the fp16 tile are shorter
+    const double fixed = rounded_many ? 17.0 : 26.6, walk = !rounded_many ? 9.3 : bf16 ? 12.0 : 8.0;
+    auto estimate = [&](double k, double work) {
+      return fixed + 3.5 * k + std::max(walk * k * (1.0 + 176.0 * rho), 0.0221 * work * (1.0 + 42.0 * rho));
     };
     double us = estimate(longest_k / 1024.0, wg_k / 1024.0);
     if (rounded_many && separate) {

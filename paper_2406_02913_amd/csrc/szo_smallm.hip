@@ -552,6 +552,7 @@ struct LaunchShape {
   double entries = 0.0, weights = 0.0, sum_k = 0.0;
   int64_t matrices = 0, tiles128 = 0, most_tokens = 0;      // 128 x 128 output tiles
   double tile_k = 0.0;                                      // K summed over those tiles
+  bool bf16 = false;                                        // tile type of a layer
   void add(const szo_linear_desc* d) {
     if (d->M <= 0 || d->N <= 0) return;
     const int64_t slices = (d->M + SM_ROWS - 1) / SM_ROWS, tiles = ((d->M + 127) / 128) * ((d->N + 127) / 128);
@@ -568,6 +569,7 @@ struct LaunchShape {
     ++matrices;
     most_tokens = std::max<int64_t>(most_tokens, d->M);
     tiles128 += tiles;
+    bf16 = bf16 || d->tile_dtype == SZO_TILE_BF16;
     tile_k += (double)tiles * k;
   }
   double percent() const { return weights > 0.0 ? 1e5 * entries / weights : 0.0; }      // sensitive weights, in percent
@@ -677,6 +679,27 @@ static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, boo
   return p;
 }
 
+// Codes of a matrix in bytes.
+static int64_t code_bytes(const szo_linear_desc* d) { return (int64_t)((d->N + 63) / 64 * 64) * (d->K / 2); }
+
+struct LaunchTotals {                                       // over a launch's matrices
+  int slices = 0, subs = 1;                                 // most slices; most 16-row subtiles of a split workgroup
+  int64_t units = 0, k = 0, rows = 0, code_bytes = 0;       // workgroups per slice, longest K, most token rows, codes
+  int64_t live = 0;                                         // workgroups that have rows, their K in all
+  double live_k = 0.0, entries = 0.0, weights = 0.0;
+  void add(const FewPlan& p, const szo_linear_desc* d) {
+    slices = std::max(slices, p.slices(d));
+    subs = std::max(subs, 4 >> p.part_shift);
+    units += p.units(d);
+    live += p.units(d) * p.slices(d);
+    live_k += (double)(p.units(d) * p.slices(d)) * (double)d->K;
+    k = std::max(k, d->K);
+    rows = std::max(rows, d->M);
+    code_bytes += ::szo::code_bytes(d);
+    entries += (double)d->nnz;
+    weights += (double)d->N * (double)d->K;
+  }
+};
 // Waves of a split workgroup.  Four, because the sum over the waves and the loss are spread over them; eight where
 // each of them still has two subtiles of a 128-column block to itself; 16 for the longest K while every workgroup has a CU to itself.
 // One forward at 16 tokens, us with 4 / 8 / 16 waves: 512 x 512 4.2 / 4.5 / 5.6 (bands in four parts, as all of these but the last two), 2048 x 1024
@@ -687,23 +710,27 @@ static FewPlan few_plan(const szo_linear_desc* d, const LaunchShape& launch, boo
 // sensitive weights rounded as in the tile for both signs, where the registers of eight waves leave no room for a second
 // workgroup on a CU, a 5000 x 4160 layer at 48 / 77 tokens (237 / 395) 23.5 / 22.1, 30.8 / 35.3, a Llama block at 48 tokens 89 / 130.
 // Sensitive entries are a chain of their own, a memory round trip per sixteen of them, which more waves shorten: sixteen waves
-// where each would still have about 80 of a band's, eight up to 2304 workgroups where a band of the longest K has many against
-// the number of workgroups.  us with 8 / 16 waves: a forward at one token and 1 %, 11008 x 4096 17.8 / 15.8, 16384 x 4096 with half the
-// entries in 1 % of the rows 42.2 / 35.4; below the line a step of 16384 x 8192 at 16 tokens and 0.1 % 28.0 / 29.0.  us per step with 4 / 8
-// (e = entries of a band over workgroups; "rows": half of them in 1 % of the rows): two OPT blocks at one token, 0.05 %, rows (e = 0.46)
-// 63 / 54, two Mistral blocks at 16 tokens, 0.1 %, rows (0.7) 92 / 74, three at one token, 0.3 %, rows (1.4) 152 / 129; below it three Llama
-// blocks at 4 tokens and 0.05 % (0.2) 76 / 80.  With v and eps z rounded together for both signs, bf16 tile: one Llama block at 16 tokens
-// and 0.5 % (5.3) 89 / 79, at 4 and 0.2 % (2.1) 51 / 52; two OPT blocks at 21, 0.2 %, rows (0.9) 141 / 197, at one token and 0.5 % (4.6)
-// 95 / 114, one at 32, 1 %, rows (9) 338 / 248.  Between those lines rows full of entries take up to 8 % longer with four than with
-// eight, evenly spread ones 20 to 40 % less.
-// `subs`: 16-row subtiles of a workgroup; `band_entries`: of a band of the longest K, on average.
-static int split_waves(const FewPlan& p, bool one_sign, int64_t workgroups, int64_t longest_k, int subs, double band_entries) {
-  const int64_t blocks = (longest_k + 127) / 128;
-  const bool both_rounded = p.dequant >= D_TILE_F16 && !one_sign;
-  const double many = both_rounded ? (workgroups <= 1024 ? 2.5 : 6.0) : 0.45;
+// where each would still have about 80 of a band's, in up to four slices; eight up to 2304 workgroups where a band of the longest K
+// has many against the number of workgroups.  us with 8 / 16 waves: a forward at one token and 1 %, 11008 x 4096 17.8 / 15.8, 16384 x
+// 4096 with half the entries in 1 % of the rows 42.2 / 35.4; below the line a step of 16384 x 8192 at 16 tokens and 0.1 % 28.0 / 29.0, with more slices
+// one of 70 x 5120 at 1722 and 0.7 % 36.1 / 39.3.  us per step with 4 / 8 (e = entries of a band over workgroups; "rows": half of them in
+// 1 % of the rows): two OPT blocks at one token, 0.05 %, rows (e = 0.46) 63 / 54, two Mistral blocks at 16 tokens, 0.1 %, rows (0.7)
+// 92 / 74, three at one token, 0.3 %, rows (1.4) 152 / 129; below it three Llama blocks at 4 tokens and 0.05 % (0.2) 76 / 80.  Evenly spread
+// entries gain nothing up to e = 2 or so (two OPT blocks at 32 tokens and 0.1 % 100 / 111), but nothing here tells the two apart.
+// Where the accumulators take more registers: tables (two Llama blocks at 2 tokens and 0.2 % (1) 86 / 107), and v and eps z rounded
+// together for both signs: one Llama block with the bf16 tile at 16 tokens and 0.5 % (5.3) 89 / 79, at 4 and 0.2 % (2.1) 51 / 52; where all
+// K are about the longest and its chain is hidden, as in slices of one layer, 5000 x 4160 at 160 tokens and 1 % (3.4) 115 / 130, 1770 x
+// 15680 at 228 and 1 %, rows (24) 253 / 294; more workgroups, two OPT blocks at 21, 0.2 %, rows (0.9) 141 / 197, at one
+// token and 0.5 % (4.6) 95 / 114, one at 32, 1 %, rows (9) 338 / 248.  Between those lines rows full of entries take up to 8 % longer
+// with four than with eight, evenly spread ones 20 to 40 % less.
+static int split_waves(const FewPlan& p, bool one_sign, int64_t workgroups, const LaunchTotals& t) {
+  const int64_t blocks = (t.k + 127) / 128;
+  const double band_entries = 64.0 * (double)t.k * t.entries / t.weights;      // of a band of the longest K, on average
+  const bool both_rounded = p.dequant >= D_TILE_F16 && !one_sign, one_k = 2.0 * (double)t.k * (double)t.live < 3.0 * t.live_k;
+  const double many = both_rounded && one_k ? 1e30 : !both_rounded && p.dequant != D_LUT ? 0.45 : workgroups <= 1024 ? 2.5 : 6.0;
   const int64_t wide = p.dual() || band_entries > many * (double)workgroups ? 2304 : both_rounded ? 256 : 1024;
-  if (workgroups > wide || blocks * subs < 16) return 4;
-  return workgroups <= 256 && (blocks > 96 || 0.25 * subs * band_entries >= 1300.0) ? 16 : 8;
+  if (workgroups > wide || blocks * t.subs < 16) return 4;
+  return workgroups <= 256 && (blocks > 96 || (t.slices <= 4 && 0.25 * t.subs * band_entries >= 1300.0)) ? 16 : 8;
 }
 
 template <int MODE, int R, bool DUAL>
@@ -718,31 +745,15 @@ static void launch_mode(int mode, dim3 blocks, const SmallArgs& a, hipStream_t s
   else if (mode == SM_LUT) launch_variant<SM_LUT, R, DUAL>(blocks, a, stream);
   else launch_variant<SM_PLAIN, R, DUAL>(blocks, a, stream);
 }
-// Codes of a matrix in bytes, and the rule for the non-temporal stream: one slice per strip and more codes in
+// The rule for the non-temporal stream of codes: one slice per strip and more codes in
 // the launch than the 256 MB last-level (memory-side) cache of the chip keeps from one step to the next.
 constexpr int64_t kLastLevelCacheBytes = 256ll << 20;
-static int64_t code_bytes(const szo_linear_desc* d) { return (int64_t)((d->N + 63) / 64 * 64) * (d->K / 2); }
 static bool g_force_stream_once = false;                    // testing hook: the stream for every one-slice launch
 void small_m_force_stream_once(bool on) { g_force_stream_once = on; }
 static int stream_once_rule(int slices, int64_t launch_code_bytes) {
   return slices == 1 && (g_force_stream_once || launch_code_bytes > kLastLevelCacheBytes);
 }
 
-struct LaunchTotals {                                       // over a launch's matrices
-  int slices = 0, subs = 1;                                 // most slices; most 16-row subtiles of a split workgroup
-  int64_t units = 0, k = 0, rows = 0, code_bytes = 0;       // workgroups per slice, longest K, most token rows, codes
-  double entries = 0.0, weights = 0.0;
-  void add(const FewPlan& p, const szo_linear_desc* d) {
-    slices = std::max(slices, p.slices(d));
-    subs = std::max(subs, 4 >> p.part_shift);
-    units += p.units(d);
-    k = std::max(k, d->K);
-    rows = std::max(rows, d->M);
-    code_bytes += ::szo::code_bytes(d);
-    entries += (double)d->nnz;
-    weights += (double)d->N * (double)d->K;
-  }
-};
 // One launch of the matrices described by `a` (their table or the single one).
 static int launch_plan(const FewPlan& p, const LaunchTotals& t, bool one_sign, SmallArgs& a, hipStream_t stream) {
   if (t.units * t.slices > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
@@ -754,7 +765,7 @@ static int launch_plan(const FewPlan& p, const LaunchTotals& t, bool one_sign, S
   if (rc != SZO_OK) return rc;
   if (p.split()) {
     rc = split_launch(SplitLaunch{p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, one_sign, t.subs,
-                                  split_waves(p, one_sign, wgs, t.k, t.subs, 64.0 * (double)t.k * t.entries / t.weights), wgs}, a, stream);
+                                  split_waves(p, one_sign, wgs, t), wgs}, a, stream);
     if (rc != SZO_OK) return rc;
   } else {
     const dim3 blocks((unsigned)wgs);
@@ -776,24 +787,26 @@ constexpr int kSmallMaxSlices = 15;
 // Uniform layers that only the split kernel takes (bf16 tile, K an odd multiple of 64), against 128x128 tiles.  Measured with
 // the bf16 tile, us per step: one Llama block at 16 / 64 / 128 tokens 62 / 134 / 302 against 371 / 375 / 379, sixteen blocks
 // 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where the tiles would leave the chip idle (2304 workgroups here).
-constexpr int64_t kSplitOnlyTokens = 64;
+constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTwoSets = 1024;
 // Inside these limits both are estimated: the split kernel by its bands and their entries or the chain of the longest K, the
 // tiles by the chain of the longest K or their share of the work, one launch after the other where they are too few for a
 // grouped one.  Fitted, in about us, to steps and single-layer losses with the bf16 tile over the same shapes, masks spread
 // evenly and half in 1 % of the rows: 20 of 3028 cases are more than 3 % slower than the tiles (20 % at most: a 300 x 320 layer at
 // one token), where token counts alone left 74 (65 %).  us per step at 1 %, split against tiles: a 16384 x 4096 layer at 64 / 128
 // tokens 140 / 266 against 191 / 186, three Llama blocks at 64 tokens 869 against 689, one OPT block at 128 tokens 437 against 463.
-// Beyond 128 tokens (single layers of 64..16384 rows x 256..16384 columns at 129..4000, 0.01..1 %) an entry costs more, a second set
-// of activations the larger part of a pass again, and tiles take longer for a column, two launches of them for a step.  us on the
-// split kernel against the others: 4059 x 6848 at 473 tokens and 0.3 % 154 against 141 on the one-dense-pass kernel; two sets of 4096 x 4160
-// at 200 and 1 % 204 against 185 in tiles, of 9902 x 4096 at 159 and 0.1 % 127 against 175, of 6111 x 384 at 135 25 against 41.
+// Beyond 128 tokens (single layers of 64..16384 rows x 256..16384 columns at 129..4000, 0.01..1 %) a band's time goes with its columns and
+// entries, those of a second set of activations on top, which is measured up to 1024 bands and slices (kSplitOnlyTwoSets), and a
+// tile's walk takes longer, more so with the bf16 tile and with two launches for a step.  us on the split kernel against the others:
+// 4059 x 6848 at 473 tokens and 0.3 % 154 against 141 on the one-dense-pass kernel, a forward of 810 x 9280 at 2238 185 against 133 in tiles;
+// two sets of 4096 x 4160 at 200 and 1 % 204 against 185, of 2354 x 704 at 953 72 against 51, of 3085 x 6464 at 187 66 against 188.
 static double split_rounded_us(const LaunchShape& l, bool two_sets) {
-  const bool many_tokens = l.most_tokens > 128, twice = many_tokens && two_sets;
-  return 13.5 + std::max((twice ? 0.021 : 0.016) * (double)l.bands16 + (twice ? 1.65 : 1.0) * (0.0036 * l.band_k + (many_tokens ? 0.025 : 0.02) * l.slice_entries),
-                         (twice ? 1.65 : 1.0) * l.longest_k * (1.9 + 5.3 * l.percent()));
+  const double chain = l.longest_k * (1.9 + 5.3 * l.percent());
+  if (l.most_tokens <= 128) return 13.5 + std::max(0.016 * (double)l.bands16 + 0.0036 * l.band_k + 0.02 * l.slice_entries, chain);
+  const double columns = 0.005 * (double)l.bands16 + 0.0062 * l.band_k;
+  return 13.5 + (two_sets ? std::max(1.65 * columns + 0.06 * l.slice_entries, 1.65 * chain) : std::max(columns + 0.03 * l.slice_entries, chain));
 }
 static double tiled_us(const LaunchShape& l, int forwards) {
-  const double chain = (l.most_tokens > 128 ? 11.5 : 9.1) * (1.0 + 0.05 * l.percent()), share = 0.0123 * forwards * l.tile_k * (1.0 + 0.73 * l.percent());
+  const double chain = (l.most_tokens <= 128 ? 9.1 : (forwards == 1 ? 11.5 : 12.5) + (l.bf16 ? 2.0 : 0.0)) * (1.0 + 0.05 * l.percent()), share = 0.0123 * forwards * l.tile_k * (1.0 + 0.73 * l.percent());
   const bool one_launch = l.matrices == 1 ? forwards == 1 : forwards * l.tiles128 >= 384;
   return 7.0 + 11.3 * (double)(forwards * l.matrices) + std::max(chain * (one_launch ? l.longest_k : forwards * l.sum_k), share);
 }
@@ -806,7 +819,7 @@ constexpr int64_t kSplitOnlyColumns = 1 << 23;
 // 600 / 8000 tokens 203 / 208 -> 21 / 80, 1024 x 4096 at 600 / 2000 tokens 56 / 57 -> 26 / 48, 4096 x 1024 at 450 tokens 18.9 -> 15.4;
 // steps of the same 132 / 69 / 78 -> 18 / 25 / 50, 422 / 208 -> 28 / 88, 65 / 66 -> 35 / 57, 29.7 -> 23.8; beyond the line a step over 4096 x
 // 4096 at 600 tokens 67 -> 68, a forward 57 -> 59, of 258 x 5248 at 6437 69 -> 78.  Forwards with tables (256 x 256 tiles): 300 x 4096 at
-// 6000 tokens 87 -> 102, 445 x 9984 at 3681 232 -> 176, 1231 x 15872 at 1741 353 -> 398.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
+// 6000 tokens 87 -> 102, 445 x 9984 at 3681 232 -> 176, 4096 x 4096 at 450 87 -> 78, 1231 x 15872 at 1741 353 -> 398.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
 // forward of a 1024 x 1024 / 4096 x 4096 layer at 300 tokens 21 / 70 -> 9 / 45.
 // (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.  The tiles' times are those of the
 // 128 x 128 schedule that scattered behind its last matrix instruction; it takes 5 % less by now, and the line stays where both were measured.)
@@ -815,18 +828,19 @@ static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launc
   const bool lut = d->format == SZO_FORMAT_LUT, plain = !lut && d->group != 128, single = forwards == 1;      // (a table layer's group means nothing)
   const FewEstimate e = few_estimate(launch, d->x_minus && !single, lut, plain);
   // (the estimates are of steps up to 448 tokens: with groups below 128 and dense masks a forward over more of them takes up to that much longer.)
-  // A single forward has the others' time against it once, not twice: there the estimates have to hold beyond 448 tokens.  From six
-  // workgroups per CU on they fall short; with tables so does that of the stream kernel, which looks up whole strips again for every slice.
-  double few = std::min(e.split * (plain ? 1.35 : 1.0), e.stream + 3.0 + 0.0015 * (double)launch.bands16);
-  if (single && lut) few = e.split <= e.stream ? e.split : e.stream + (0.032 * (double)launch.strips16 * launch.longest_k - 0.0026 * launch.band_k);
-  else if (single && launch.bands16 > 1536) few *= 1.15;
-  few *= 1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0);
+  // A single forward has the others' time against it once, not twice: there the estimate has to hold.  The stream kernel computes
+  // whole strips of 256 rows for every slice, with tables at the price of their look-ups (which the choice of the kernel leaves out).
+  const double strip_k = 4.0 * (double)launch.strips16 * launch.longest_k;
+  const double stream = e.stream + (single ? (lut ? 0.00675 : 0.0026) * strip_k - 0.0026 * launch.band_k : 0.0) + 3.0 + 0.0015 * (double)launch.bands16;
+  const double few = (single && lut ? (e.split <= e.stream ? e.split : stream) : std::min(e.split * (plain ? 1.35 : 1.0), stream)) *
+                     (1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0));
   return few < (!single ? 10.0 + 11.8 * launch.longest_k : 5.0 + (lut ? 20.0 : 12.7) * launch.longest_k);
 }
 static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (!stream_ok(d))
     return d->format == SZO_FORMAT_UNIFORM && d->K < kSplitOnlyColumns &&
-           (launch.bands16 <= 2304 || d->M <= kSplitOnlyTokens);
+           (launch.bands16 <= 2304 || d->M <= kSplitOnlyTokens) &&
+           (!(d->x_minus && forwards == 2) || d->M <= 128 || launch.bands16 <= kSplitOnlyTwoSets);
   if (outruns_the_chain(d, launch, forwards)) return true;
   // two activation sets: a pass holds 16 token rows of each, so it is worth less
   const int64_t slices = (d->M + (d->x_minus ? 15 : 31)) / (d->x_minus ? 16 : 32), tile_rows = (d->M + 255) / 256;

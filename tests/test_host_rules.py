@@ -17,16 +17,23 @@ PROBE = r"""
 using namespace szo;
 static SplitLaunch g_last;
 namespace szo { int split_launch(const SplitLaunch& l, const SmallArgs&, hipStream_t) { g_last = l; return SZO_OK; } }
-// a line: layers, token rows, N, K, group, entries, bf16, table format, two sets, one sign, separate launches, asked for
+// a line: layers, token rows, N, K, group, entries, bf16, table format, two sets, one sign, separate launches, asked for,
+// K of one more layer
 int main() {
-  long long n, M, N, K, group, nnz, bf16, lut, two, one, separate, asked;
-  while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld", &n, &M, &N, &K, &group, &nnz, &bf16, &lut, &two, &one, &separate, &asked) == 12) {
+  long long n, M, N, K, group, nnz, bf16, lut, two, one, separate, asked, tail;
+  while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld", &n, &M, &N, &K, &group, &nnz, &bf16, &lut, &two, &one, &separate, &asked, &tail) == 13) {
     szo_linear_desc d{};
     d.M = M; d.N = N; d.K = K; d.group = (int)group; d.nnz = nnz;
     d.tile_dtype = bf16 ? SZO_TILE_BF16 : SZO_TILE_F16;
     d.format = lut ? SZO_FORMAT_LUT : SZO_FORMAT_UNIFORM;
     d.x_minus = two ? &d : nullptr;
     std::vector<szo_linear_desc> descs((size_t)n, d);
+    if (tail > 0) {                                         // and one of 4096 rows with a K of its own
+      szo_linear_desc e = d;
+      e.N = 4096; e.K = tail; e.nnz = nnz * 4096 * tail / (N * K);
+      descs.push_back(e);
+      ++n;
+    }
     LaunchShape shape;
     for (const auto& e : descs) shape.add(&e);
     const FewPlan p = few_plan(&d, shape, two != 0);
@@ -57,7 +64,7 @@ def ask(tmp_path_factory):
                            "-Wl,-rpath," + os.path.dirname(szo_build.LIB), "-Wl,--unresolved-symbols=ignore-all"], stderr=subprocess.DEVNULL)      # (the device code, which nothing here launches)
 
     def run(*cases):
-        keys = ("layers", "M", "N", "K", "group", "nnz", "bf16", "lut", "two_sets", "one_sign", "separate", "asked_for")
+        keys = ("layers", "M", "N", "K", "group", "nnz", "bf16", "lut", "two_sets", "one_sign", "separate", "asked_for", "tail_k")
         lines = "\n".join(" ".join(str(int(c.get(k, 0))) for k in keys) for c in cases)
         out = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split("\n")
         return [tuple(int(v) for v in line.split()) for line in out[:len(cases)]]
@@ -75,11 +82,14 @@ def _layer(N, K, M, density, layers=1, group=128, **kw):
     (_layer(4096, 4096, 16, 1e-2, one_sign=1), 8, 256),               # cut in four: each part works on its own quarter of the entries
     # eight, and four beyond 1024 workgroups unless the mask is dense
     (_layer(16384, 4096, 64, 1e-3), 8, 1024), (_layer(8192, 16384, 48, 1e-4, layers=3), 4, 1152), (_layer(8192, 16384, 48, 1e-3, layers=3), 8, 1152),
-    # both signs rounded with the weights: four beyond 256
+    # both signs rounded with the weights: four beyond 256, eight for dense masks where one K is far longer than the others
     (_layer(5000, 4160, 48, 1e-3, group=64, bf16=1), 8, 237), (_layer(5000, 4160, 64, 1e-3, group=64, bf16=1), 4, 316),
-    (_layer(5000, 4160, 64, 1e-2, group=64, bf16=1), 8, 316), (_layer(5000, 4160, 64, 1e-3, group=64, bf16=1, one_sign=1), 8, 316),
-    (_layer(16384, 4160, 80, 1e-2, group=64, bf16=1), 4, 1280),
-    (_layer(4096, 8192, 48, 3e-2, group=64, bf16=1, layers=12), 8, 2304), (_layer(4096, 8192, 48, 3e-2, group=64, bf16=1, layers=13), 4, 2496),
+    (_layer(5000, 4160, 64, 1e-2, group=64, bf16=1), 4, 316), (_layer(5000, 4160, 64, 1e-3, group=64, bf16=1, one_sign=1), 8, 316),
+    (_layer(4096, 4096, 16, 1e-3, layers=6, bf16=1, tail_k=16384), 4, 448), (_layer(4096, 4096, 16, 2e-3, layers=6, bf16=1, tail_k=16384), 8, 448),
+    (_layer(4096, 4096, 48, 3e-3, layers=6, bf16=1, tail_k=16384), 4, 1344), (_layer(4096, 4096, 48, 1e-2, layers=6, bf16=1, tail_k=16384), 8, 1344),
+    (_layer(4096, 4096, 64, 2e-2, layers=8, bf16=1, tail_k=16384), 8, 2304), (_layer(4096, 4096, 64, 2e-2, layers=9, bf16=1, tail_k=16384), 4, 2560),
+    # many slices: eight; tables: four beyond 1024
+    (_layer(70, 5120, 1722, 7e-3, group=64), 8, 216), (_layer(8192, 16384, 48, 1e-3, layers=3, lut=1), 4, 1152),
     # two blocks of K: nothing to split
     (_layer(5000, 256, 4, 1e-2), 4, 158),
 ])
@@ -91,13 +101,16 @@ def test_waves_of_the_split_kernel(ask, case, waves, workgroups):
 @pytest.mark.parametrize("case,few,onepass", [
     # only the split kernel can, up to 128 tokens as measured there; beyond, it or the one-dense-pass kernel or the tiles
     (_layer(11008, 4160, 200, 1e-3, group=64), True, True), (_layer(11008, 4160, 200, 1e-3, group=64, separate=1), True, True),
-    (_layer(4059, 6848, 473, 3e-3, group=32), True, True), (_layer(5344, 3584, 208, 1e-4, group=32, bf16=1), True, False),
+    (_layer(4059, 6848, 473, 3e-3, group=32), True, True), (_layer(1363, 2816, 1114, 3e-3, group=64, bf16=1), True, False), (_layer(402, 2688, 3276, 1e-3, group=64, bf16=1), True, False),
+    (_layer(2080, 448, 905, 1e-3, group=32, separate=1), True, True), (_layer(4590, 1024, 491, 1e-3, group=32, bf16=1), True, True),
+    (_layer(810, 9280, 2238, 1e-3, group=64, one_sign=1), False, False), (_layer(544, 13952, 2544, 1e-3, group=32, bf16=1, one_sign=1), True, False), (_layer(5344, 3584, 208, 1e-4, group=32, bf16=1), True, False),
     (_layer(3360, 4288, 535, 1e-3, group=64, bf16=1), True, False), (_layer(9196, 6592, 165, 1e-4, group=64, separate=1), True, False),
     (_layer(1653, 896, 419, 1e-4, group=64, bf16=1), True, False), (_layer(1653, 896, 419, 1e-4, group=64, bf16=1, asked_for=1), True, False),
     (_layer(4096, 4160, 128, 1e-3, group=64), True, False), (_layer(4096, 4160, 128, 1e-3, group=64, separate=1), True, False),
     # ... with two sets of activations: it or the tiles
     (_layer(4096, 4160, 200, 1e-2, group=32, bf16=1, two_sets=1), False, False), (_layer(5782, 3264, 394, 1e-4, group=64, two_sets=1), False, False),
-    (_layer(9902, 4096, 159, 1e-3, group=64, bf16=1, two_sets=1), True, False), (_layer(3638, 8128, 137, 1e-2, group=64, two_sets=1), True, False),
+    (_layer(3085, 6464, 187, 1e-4, group=64, two_sets=1), True, False), (_layer(2354, 704, 953, 1e-4, group=32, bf16=1, two_sets=1), False, False),
+    (_layer(3638, 8128, 137, 1e-2, group=64, two_sets=1), True, False),
 ])
 def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepass):
     (got_few, _, _, partials), = ask(case)
@@ -111,7 +124,8 @@ def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepas
     (_layer(635, 6400, 2409, 1e-4, one_sign=1), True), (_layer(111, 9088, 7496, 3e-3, one_sign=1), True),
     # with tables
     (_layer(300, 4096, 6000, 1e-3, lut=1, one_sign=1), False), (_layer(300, 4096, 6000, 1e-3, lut=1), True),
-    (_layer(1231, 15872, 1741, 1e-3, lut=1, one_sign=1), False), (_layer(445, 9984, 3681, 1e-4, lut=1, one_sign=1), False), (_layer(799, 2304, 1037, 1e-4, lut=1, one_sign=1), True),
+    (_layer(1231, 15872, 1741, 1e-3, lut=1, one_sign=1), False), (_layer(445, 9984, 3681, 1e-4, lut=1, one_sign=1), True),
+    (_layer(4096, 4096, 450, 1e-3, lut=1, one_sign=1), True), (_layer(312, 12160, 4270, 1e-4, lut=1, one_sign=1), False), (_layer(799, 2304, 1037, 1e-4, lut=1, one_sign=1), True),
     # the group of a table layer decides nothing
     (_layer(1803, 2432, 700, 1e-3, lut=1), True), (_layer(1803, 2432, 700, 1e-3, lut=1, group=64), True),
     (_layer(1803, 2432, 700, 1e-3, lut=1, group=32), True),
