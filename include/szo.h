@@ -171,7 +171,8 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * the layers are of the uniform format with one tile type, fill the chip, and their masks are sparse (against the tiled kernel up to
  * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Otherwise, and beyond 2048
  * tokens in steps of more than 2048 output tiles of 256 x 128, each layer runs as two full products, as the single-layer
- * calls compute them; the results are the same up to the roundings described at SZO_TILE_F16.
+ * calls compute them; the results are the same up to the roundings described at SZO_TILE_F16.  The tiles are counted over
+ * the step as a whole: the same layers in several smaller steps may be computed the other way, to the same roundings.
  * With bit 0 clear y holds the -eps forward's outputs afterwards, and the loss is summed in fp64 from the
  * fp32 outputs; layers of the uniform format with one tile type, one set of activations, masks of up to 1.5 % and no
  * output buffer in common with another layer run as one launch there too.

@@ -429,7 +429,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     uint16_t* sc_addr_minus = nullptr;
     auto make_slice = [&](int dst, int load_kt) {
       return [&, dst, load_kt](int s) {
-        // the k-th (0 or 1) output word staged from slot `slot`: unit u, word w; false if none
+        // the k-th output word (of two, three with 16 slots) staged from slot `slot`: unit u, word w; false if none
         auto item = [](int slot, int k, int& u, int& w) -> bool {
           if (slot < 0 || slot >= SLOTS / 4 * 3) return false;
           const int ph = slot % 3;

@@ -51,12 +51,12 @@ int reduce_step(const double* partials, int count, float eps, double* scalars, h
 // single-forward calls (what the tiled kernel would have to do instead).  `separate`: one launch per layer; a step of such
 // launches takes no second activation set.
 bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool separate, int forwards);
-// Estimated us of a step's forwards, up to 128 tokens, where the stream kernel does not take every layer: on the few-token path
-// (`few`) or in the tiled kernel.
+// Estimated us of a step's forwards where the stream kernel does not take every layer: on the few-token path (`few`) or in the tiled
+// kernel.  Fitted up to 128 tokens and, for single layers, from 129 to 4000.
 double small_m_rounded_us(const szo_linear_desc* descs, int n, bool few, bool separate);
-int64_t small_m_partials(const szo_linear_desc* d, bool compact = false);   // loss partials per sign of a single-matrix launch, one per
-                                                            // band (split kernel) or strip (stream kernel; compact: always) and slice
-// ... and of the launch as it runs by itself, which may cut bands into parts; callers with little room ask for fewer.
+// Loss partials per sign of a single-matrix launch, one per workgroup: per strip and slice of the stream kernel, per band or part of
+// one and slice of the split kernel.  Callers with little room ask for fewer: as chosen by size (kBandsInParts), bands not cut, or
+// the stream kernel where it can.
 enum Partials { kBandsInParts, kWholeBands, kStreamKernel };
 int64_t small_m_launch_partials(const szo_linear_desc* d, Partials less);
 void small_m_force_split(int how);                          // testing hook: 1 = the split kernel always, -1 = only where nothing else can, 0 = choose

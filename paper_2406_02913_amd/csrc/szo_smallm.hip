@@ -880,7 +880,6 @@ static FewPlan plan_of_one(const szo_linear_desc* d, Partials less) {
   shape.add(d);
   return few_plan(d, shape, false, less);
 }
-int64_t small_m_partials(const szo_linear_desc* d, bool compact) { return small_m_launch_partials(d, compact ? kStreamKernel : kWholeBands); }
 int64_t small_m_launch_partials(const szo_linear_desc* d, Partials less) {
   const FewPlan p = plan_of_one(d, less);
   return p.units(d) * p.slices(d);
@@ -943,8 +942,8 @@ int small_m_launch_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, f
   if (rc != SZO_OK) return rc;
   const FewPlan p = plan_of_one(d, less);
   SmallArgs a{};
-  fill_mat(a.inl[0], d);
-  a.part_shifts = (uint32_t)p.part_shift;                                       // whole matrix: the kernel offsets rows by slice
+  fill_mat(a.inl[0], d);                                       // whole matrix: the kernel offsets rows by slice
+  a.part_shifts = (uint32_t)p.part_shift;
   a.table = nullptr; a.n_mats = 1;
   a.store_sign = store_sign; a.loss_mode = loss_mode ? 1 : 0;
   a.seed = seed; a.step = step; a.eps = eps;

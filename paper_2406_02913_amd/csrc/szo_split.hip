@@ -211,7 +211,7 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
 #pragma unroll
     for (int s = 0; s < SUBS; ++s) acc[i][s] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // ---- sensitive entries, while the first codes are on their way: 256 at a time into the wave's own part of LDS
+  // ---- sensitive entries, while the first codes are on their way: 128 at a time into the wave's own part of LDS
   //      (its later accumulator area), then 16 per matrix product ----
   {
     uint32_t* const wk = reinterpret_cast<uint32_t*>(red + wave * RED);            // column

@@ -239,12 +239,13 @@ def _layers(shapes, M, density, tile=szo.TILE_F16, group=128):
 def test_kernel_choice_follows_the_density_of_the_mask():
     """Host rules only, at sizes where both sides were measured: the split kernel (one partial per 64-row band and slice)
     against the stream kernel (one per 256-column strip), the split kernel against tiles, the one-dense-pass kernel against both."""
-    partials = _rule("_ZN3szo16small_m_partialsEPK15szo_linear_descb", ctypes.c_int64, ctypes.c_bool)
+    partials = _rule("_ZN3szo23small_m_launch_partialsEPK15szo_linear_descNS_8PartialsE", ctypes.c_int64, ctypes.c_int)
+    whole_bands = 1
     for (n, k, m), density, split in (((16384, 16384, 96), 1e-4, True), ((16384, 16384, 96), 1e-2, False), ((16384, 4096, 64), 1e-3, True),
                                       ((16384, 4096, 64), 1e-2, False), ((4096, 4096, 16), 1e-2, True), ((4096, 16384, 224), 1e-2, False)):
         d = _layers([(n, k)], m, density)
         slices = (m + 15) // 16
-        assert (partials(d, False) == n // 64 * slices) is split, (n, k, m, density)
+        assert (partials(d, whole_bands) == n // 64 * slices) is split, (n, k, m, density)
     eligible = _rule("_ZN3szo16small_m_eligibleEPK15szo_linear_descibbi", ctypes.c_bool, ctypes.c_int, ctypes.c_bool, ctypes.c_bool, ctypes.c_int)
     for m, density, want in ((64, 1e-2, True), (128, 1e-3, True), (128, 1e-2, False)):
         assert eligible(_layers([(16384, 4096)], m, density, szo.TILE_BF16, 64), 1, False, False, 2) is want, (m, density)
