@@ -190,3 +190,18 @@ def test_noalloc_falls_back_to_fewer_partials():
     szo.szo_zo_step_noalloc([one] * n, 1, 0, 1e-3, 0.0, scal)
     szo.szo_zo_step_noalloc([one], 1, 0, 1e-3, 0.0, ref)
     assert abs(scal[0].item() - n * ref[0].item()) <= 1e-6 * scal[0].item()
+
+
+@pytest.mark.parametrize("n", [256, 257])               # 64 bands in four parts each: 65 536 partials per sign, as many as fit, and one layer more
+def test_noalloc_falls_back_to_whole_bands(n):
+    szo.szo_set_tile_config(8)
+    o, d = make_pair(242, 13, 4096, 128, 128, 1e-3)
+    one = d.desc(with_y=False)
+    scal, ref = torch.zeros(3, dtype=torch.float64, device="cuda"), torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_zo_step_noalloc([one], 1, 0, 1e-3, 0.0, ref)
+    szo.szo_zo_step_noalloc([one] * n, 1, 0, 1e-3, 0.0, scal)
+    # the same outputs either way (one block of K, four waves), their squares added in fp64 in another order: 2^-53 x 65 536 terms
+    want = n * ref[:2].cpu().numpy()
+    assert np.all(np.abs(scal[:2].cpu().numpy() - want) <= 1e-11 * want)
+    want = olayer.mse_loss(olayer.linear_fwd(o.x_bits, o.codes, o.scales, 128, o.sp_idx, o.sp_val, ophilox.zbar(1, 0, 0, o.sp_idx.size), +1, 1e-3, "E"), o.target_bits)
+    assert abs(ref[0].item() - want) <= 1e-4 * want

@@ -133,3 +133,17 @@ def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepas
 def test_who_takes_many_tokens_of_few_rows(ask, case, few):
     (got, _, _, _), = ask(case)
     assert bool(got) == few
+
+
+@pytest.mark.parametrize("case,onepass", [
+    # either side of the lines on the mask's density beyond 512 tokens: 1.34 / 4 with the fp16 tile and K a multiple of 128, else 1.22 / 4
+    (_layer(2048, 512, 1024, 3.0e-3), True), (_layer(2048, 512, 1024, 3.3e-3), False),
+    (_layer(2368, 320, 1024, 1.9e-3, group=64, bf16=1), True), (_layer(2368, 320, 1024, 2.2e-3, group=64, bf16=1), False),
+    (_layer(2368, 320, 1024, 1.9e-3, group=64), True), (_layer(2368, 320, 1024, 2.2e-3, group=64), False),
+    # 2048 tokens; 2048 tiles of 256 x 128 beyond
+    (_layer(29184, 128, 2048, 1e-3), True), (_layer(29184, 128, 2049, 1e-3), False), (_layer(29056, 128, 2049, 1e-3), True),
+    (_layer(16384, 128, 2049, 1e-3), True), (_layer(16384, 128, 2049, 1e-3, layers=2), False),
+])
+def test_who_takes_one_dense_product_beyond_512_tokens(ask, case, onepass):
+    (few, _, _, partials), = ask(case)
+    assert not few and (partials > 0) == onepass
