@@ -617,12 +617,14 @@ static int launch_one(const szo_linear_desc* d, const FwdParams& p, hipStream_t 
 // 2033 / 2327 / 2535, at 300 tokens 182 / 181 / 186 / 204 / 226 -> 176 / 175 / 182 / 206 / 229, sixteen OPT blocks at 64 tokens 602 / 610 / 617 /
 // 690 / 760 -> 587 / 590 / 612 / 704 / 770; one 4096 x 4096 layer at 600 tokens (160 workgroups) 65.1 / 65.2 / 67.1 / 80.2 / 88.6 -> 64.6 /
 // 64.9 / 68.9 / 84.0 / 92.4, with groups of 64 63.5 / 62.8 / 65.1 / 77.2 / 84.4 -> 62.2 / 61.3 / 66.4 / 80.7 / 88.2; one Llama block with outputs
-// at one token (172) at 0.05 / 0.07 / 0.13 / 0.3 % 146 / 146 / 155 / 199 -> 147 / 149 / 163 / 210.  With the bf16 tile there is less to
-// gain at 0.1 % (eight OPT blocks at 64 tokens 363 -> 361) and masks with rows full of entries lose (two at 128 tokens, half the
-// entries in 1 % of the rows, 302 -> 310): the lower line there too.
+// at one token (172) at 0.05 / 0.07 / 0.13 / 0.3 % 146 / 146 / 155 / 199 -> 147 / 149 / 163 / 210.  Without the scale in fp32
+// there is less to gain at 0.1 % (eight OPT blocks with the bf16 tile at 64 tokens 363 -> 361, one Llama block with groups of 64 at 300 188 ->
+// 185) and masks with rows full of entries lose (half of them in 1 % of the rows: two OPT blocks with the bf16 tile at 128 tokens 302 -> 310,
+// one with groups of 64 and outputs at 300 273 -> 282; in fp32 two Llama blocks at 2048 2179 -> 2152): the lower line there too,
+// and where the longest K outlasts the launch's work spread over the chip (one OPT block with outputs at 300 tokens and 0.1 % 234 -> 239).
 constexpr double kSparseEntries = 0.0012, kSparseEntriesAlone = 0.00075;
-static bool sparse_launch(double entries, double weights, int64_t wgs, bool bf16) {
-  return entries <= (wgs >= 512 && !bf16 ? kSparseEntries : kSparseEntriesAlone) * weights;
+static bool sparse_launch(double entries, double weights, int64_t wgs, double wg_k, int64_t longest_k, bool group_scale) {
+  return entries <= (wgs >= 512 && 1.5 * wg_k >= 512.0 * (double)longest_k && group_scale ? kSparseEntries : kSparseEntriesAlone) * weights;
 }
 
 int64_t onepass_tiles(const szo_linear_desc* d) {
@@ -768,7 +770,8 @@ int onepass_one(const szo_linear_desc* d, uint64_t seed, uint64_t step, float ep
   const int rc = fill_tiled(p, d, seed, step, eps, plus, minus);
   if (rc != SZO_OK) return rc;
   if (onepass_tiles(d) > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
-  return sparse_launch((double)d->nnz, (double)d->N * (double)d->K, onepass_tiles(d), d->tile_dtype == SZO_TILE_BF16) ? launch_one<true>(d, p, stream) : launch_one<false>(d, p, stream);
+  return sparse_launch((double)d->nnz, (double)d->N * (double)d->K, onepass_tiles(d), (double)onepass_tiles(d) * (double)d->K, d->K,
+                       d->tile_dtype == SZO_TILE_F16 && d->group == 128) ? launch_one<true>(d, p, stream) : launch_one<false>(d, p, stream);
 }
 
 int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, bool few, bool asked_for,
@@ -785,11 +788,12 @@ int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_
   static thread_local std::vector<FwdParams> table;
   table.clear();
   int64_t first_block = 0, offset = 0;
-  double entries = 0.0, weights = 0.0;
+  double entries = 0.0, weights = 0.0, wg_k = 0.0;
   for (int i : order) {
     const szo_linear_desc* d = &descs[i];
     entries += (double)d->nnz;
     weights += (double)d->N * (double)d->K;
+    wg_k += (double)onepass_tiles(d) * (double)d->K;
     FwdParams p;
     const int rc = fill_tiled(p, d, seed, step, eps, partials + offset, partials + T + offset);
     if (rc != SZO_OK) return rc;
@@ -806,7 +810,7 @@ int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_
   const int e = (int)table.size(), with = (int)std::count_if(table.begin(), table.end(), [](const FwdParams& p) { return p.group_shift == 7; });
   const int groups = with == e ? kAllGroups128 : with == 0 ? kNoGroups128 : kSomeGroups128;
   const bool bf16 = descs[order[0]].tile_dtype == SZO_TILE_BF16;
-  if (sparse_launch(entries, weights, T, bf16))
+  if (sparse_launch(entries, weights, T, wg_k, descs[order[0]].K, !bf16 && groups == kAllGroups128))
     return store_y ? launch_table<true, true>(bf16, groups, t, e, first_block, stream) : launch_table<false, true>(bf16, groups, t, e, first_block, stream);
   return store_y ? launch_table<true, false>(bf16, groups, t, e, first_block, stream) : launch_table<false, false>(bf16, groups, t, e, first_block, stream);
 }
