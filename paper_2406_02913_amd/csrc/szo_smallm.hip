@@ -829,11 +829,13 @@ static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launc
   const FewEstimate e = few_estimate(launch, d->x_minus && !single, lut, plain);
   // (the estimates are of steps up to 448 tokens: with groups below 128 and dense masks a forward over more of them takes up to that much longer.)
   // A single forward has the others' time against it once, not twice: there the estimate has to hold.  The stream kernel computes
-  // whole strips of 256 rows for every slice, with tables at the price of their look-ups (which the choice of the kernel leaves out).
+  // whole strips of 256 rows for every slice, with tables at the price of their look-ups (which the choice of the kernel leaves out); the
+  // split kernel's time goes with columns and entries as in split_rounded_us below (692 x 15872 at 2253 tokens 201 in tiles, 236 there).
   const double strip_k = 4.0 * (double)launch.strips16 * launch.longest_k;
   const double stream = e.stream + (single ? (lut ? 0.00675 : 0.0026) * strip_k - 0.0026 * launch.band_k : 0.0) + 3.0 + 0.0015 * (double)launch.bands16;
-  const double few = (single && lut ? (e.split <= e.stream ? e.split : stream) : std::min(e.split * (plain ? 1.35 : 1.0), stream)) *
-                     (1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0));
+  const double split = e.split * (plain ? 1.35 : 1.0), dense = 1.0 + 0.8 * std::max(launch.percent() - 0.1, 0.0);
+  double few = dense * (!single ? std::min(split, stream) : e.split <= e.stream ? split : stream);
+  if (single && !lut && e.split <= e.stream) few = std::max(few, 0.005 * (double)launch.bands16 + 0.0062 * launch.band_k + 0.03 * launch.slice_entries);
   return few < (!single ? 10.0 + 11.8 * launch.longest_k : 5.0 + (lut ? 20.0 : 12.7) * launch.longest_k);
 }
 static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {

@@ -120,7 +120,8 @@ def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepas
 @pytest.mark.parametrize("case,few", [
     # layers of few rows: a step at any of these sizes, a single forward up to 1536 bands and slices or well inside the line
     (_layer(258, 5248, 6437, 1e-3, one_sign=1), False), (_layer(258, 5248, 6437, 1e-3), True),
-    (_layer(285, 1152, 5600, 1e-3, one_sign=1), False), (_layer(300, 4096, 1000, 1e-3, one_sign=1), True),
+    (_layer(692, 15872, 2253, 1e-3, one_sign=1), False), (_layer(692, 15872, 2253, 1e-3), True), (_layer(2478, 16000, 695, 1e-3, one_sign=1), False),
+    (_layer(423, 13184, 2884, 3e-4, one_sign=1), True), (_layer(285, 1152, 5600, 1e-3, one_sign=1), False), (_layer(300, 4096, 1000, 1e-3, one_sign=1), True),
     (_layer(635, 6400, 2409, 1e-4, one_sign=1), True), (_layer(111, 9088, 7496, 3e-3, one_sign=1), True),
     # with tables
     (_layer(300, 4096, 6000, 1e-3, lut=1, one_sign=1), False), (_layer(300, 4096, 6000, 1e-3, lut=1), True),
