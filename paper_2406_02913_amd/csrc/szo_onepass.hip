@@ -646,7 +646,8 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    the 128-row tiles that such layers run on otherwise, both paths are estimated from sizes and density (fitted with
 //    split_rounded_us): one OPT block at 128 tokens and 0.1 / 0.7 / 1 %, tiles -> this one 379 / 437 / 463 -> 253 / 473 / 568.
 //    Beyond 128 tokens, where that path takes a layer of up to 2304 workgroups, too: 11008 x 4160 with groups of 64 at 200 tokens 77 -> 60,
-//    2080 x 448 at 905 30 -> 19, 4590 x 1024 with the bf16 tile at 491 42 -> 32, the other way 3360 x 4288 with it at 535 83 against 90.
+//    2080 x 448 at 905 30 -> 19, 4590 x 1024 with the bf16 tile at 491 42 -> 32, the other way 3360 x 4288 with it at 535
+//    83 against 90, 710 x 4032 at 2009 60 against 80.
 //  * asked for at more tokens than the few-token path takes by itself, against its slices: from 160 workgroups on (110
 //    with smaller groups, whose slices are slower).  A 2048 x 12288 layer at 512 tokens (64 of them) 91 -> 154, a 4096 x 16384
 //    layer at 512 / 700 (128 / 176) 187 / 240 -> 210 / 214.
@@ -703,8 +704,8 @@ static bool worth_it(const szo_linear_desc* descs, int n, bool few, bool asked_f
     if ((!few || rounded_many) && wgs < (most_tokens <= 128 ? 256 : 32)) return false;
   }
   if (!stream && (few || most_tokens <= 128)) {
-    // both in units of 1024 columns; beyond 128 tokens fitted again, where the launch and the walk of the fp16 tile are shorter
-    const double fixed = rounded_many ? 17.0 : 26.6, walk = !rounded_many ? 9.3 : bf16 ? 12.0 : 8.0;
+    // both in units of 1024 columns; beyond 128 tokens fitted again: the launch is shorter there, the walk longer
+    const double fixed = rounded_many ? 17.0 : 26.6, walk = !rounded_many ? 9.3 : bf16 ? 13.0 : 10.0;
     auto estimate = [&](double k, double work) {
       return fixed + 3.5 * k + std::max(walk * k * (1.0 + 176.0 * rho), 0.0221 * work * (1.0 + 42.0 * rho));
     };

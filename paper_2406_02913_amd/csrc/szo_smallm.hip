@@ -787,7 +787,7 @@ constexpr int kSmallMaxSlices = 15;
 // Uniform layers that only the split kernel takes (bf16 tile, K an odd multiple of 64), against 128x128 tiles.  Measured with
 // the bf16 tile, us per step: one Llama block at 16 / 64 / 128 tokens 62 / 134 / 302 against 371 / 375 / 379, sixteen blocks
 // 788 / 2934 / 2477 against 3047 / 3106 / 3204.  From 65 tokens on only where the tiles would leave the chip idle (2304 workgroups here).
-constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTwoSets = 1024;
+constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTwoSets = 1536;
 // Inside these limits both are estimated: the split kernel by its bands and their entries or the chain of the longest K, the
 // tiles by the chain of the longest K or their share of the work, one launch after the other where they are too few for a
 // grouped one.  Fitted, in about us, to steps and single-layer losses with the bf16 tile over the same shapes, masks spread
@@ -795,10 +795,11 @@ constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTwoSets = 1024;
 // one token), where token counts alone left 74 (65 %).  us per step at 1 %, split against tiles: a 16384 x 4096 layer at 64 / 128
 // tokens 140 / 266 against 191 / 186, three Llama blocks at 64 tokens 869 against 689, one OPT block at 128 tokens 437 against 463.
 // Beyond 128 tokens (single layers of 64..16384 rows x 256..16384 columns at 129..4000, 0.01..1 %) a band's time goes with its columns and
-// entries, those of a second set of activations on top, which is measured up to 1024 bands and slices (kSplitOnlyTwoSets), and a
+// entries, those of a second set of activations on top, which is measured up to 1536 bands and slices (kSplitOnlyTwoSets), and a
 // tile's walk takes longer, more so with the bf16 tile and with two launches for a step.  us on the split kernel against the others:
 // 4059 x 6848 at 473 tokens and 0.3 % 154 against 141 on the one-dense-pass kernel, a forward of 810 x 9280 at 2238 185 against 133 in tiles;
-// two sets of 4096 x 4160 at 200 and 1 % 204 against 185, of 2354 x 704 at 953 72 against 51, of 3085 x 6464 at 187 66 against 188.
+// two sets of 4096 x 4160 at 200 and 1 % 204 against 185, of 2354 x 704 at 953 (2220 bands and slices) 72 against 51, of
+// 3552 x 12416 at 329 248 against 378.
 static double split_rounded_us(const LaunchShape& l, bool two_sets) {
   const double chain = l.longest_k * (1.9 + 5.3 * l.percent());
   if (l.most_tokens <= 128) return 13.5 + std::max(0.016 * (double)l.bands16 + 0.0036 * l.band_k + 0.02 * l.slice_entries, chain);

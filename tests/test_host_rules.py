@@ -110,6 +110,7 @@ def test_waves_of_the_split_kernel(ask, case, waves, workgroups):
     # ... with two sets of activations: it or the tiles
     (_layer(4096, 4160, 200, 1e-2, group=32, bf16=1, two_sets=1), False, False), (_layer(5782, 3264, 394, 1e-4, group=64, two_sets=1), False, False),
     (_layer(3085, 6464, 187, 1e-4, group=64, two_sets=1), True, False), (_layer(2354, 704, 953, 1e-4, group=32, bf16=1, two_sets=1), False, False),
+    (_layer(3552, 12416, 329, 1e-3, group=64, bf16=1, two_sets=1), True, False), (_layer(710, 4032, 2009, 1e-3, group=32), True, False),
     (_layer(3638, 8128, 137, 1e-2, group=64, two_sets=1), True, False),
 ])
 def test_who_takes_layers_that_the_stream_kernel_does_not(ask, case, few, onepass):
