@@ -47,15 +47,16 @@ def algorithmic_bytes_fwd(m, M, fused=True):
 
 
 def few_token_path(M, two_sets=False):
-    """Token counts that the library's few-token path takes by itself: at most 15 slices of 32 token rows (16 with two
-    activation sets), fewer than 7.5 of them per row of 256-row tiles."""
+    """Token counts that the library's few-token path takes by itself whatever the layers: at most 15 slices of 32 token rows (16
+    with two activation sets), fewer than 7.5 of them per row of 256-row tiles.  (It also takes layers of few rows at more tokens, by
+    estimates that are not restated here: none of the workloads below has such layers.)"""
     slices, tile_rows = (M + (15 if two_sets else 31)) // (16 if two_sets else 32), (M + 255) // 256
     return slices <= 15 and 2 * slices < 15 * tile_rows
 
 
 def one_product_kernel(mats, M, two_sets=False, asked_for=False):
     """Which kernel computes a fused step's dense product once for both signs, or None where two forwards run: the
-    library's rules for fp16-tile layers with K a multiple of 128, restated to label the measurement."""
+    library's rules for fp16-tile layers of these workloads' sizes with K a multiple of 128, restated to label the measurement."""
     few, uniform = few_token_path(M, two_sets), all(m.lut is None for m in mats)
     wgs = sum(-(-m.N // 256) * -(-M // 64) for m in mats)
     wg_k = sum(-(-m.N // 256) * -(-M // 64) * m.K for m in mats)
