@@ -722,7 +722,8 @@ struct LaunchTotals {                                       // over a launch's m
 // K are about the longest and its chain is hidden, as in slices of one layer, 5000 x 4160 at 160 tokens and 1 % (3.4) 115 / 130, 1770 x
 // 15680 at 228 and 1 %, rows (24) 253 / 294; more workgroups, two OPT blocks at 21, 0.2 %, rows (0.9) 141 / 197, at one
 // token and 0.5 % (4.6) 95 / 114, one at 32, 1 %, rows (9) 338 / 248.  Between those lines rows full of entries take up to 8 % longer
-// with four than with eight, evenly spread ones 20 to 40 % less.
+// with four than with eight, 11 % with tables, evenly spread ones 17 to 40 % less (two Llama blocks with tables at 4 tokens and 1 % (5.3),
+// rows 252 / 228, evenly spread 157 / 190).
 static int split_waves(const FewPlan& p, bool one_sign, int64_t workgroups, const LaunchTotals& t) {
   const int64_t blocks = (t.k + 127) / 128;
   const double band_entries = 64.0 * (double)t.k * t.entries / t.weights;      // of a band of the longest K, on average
