@@ -3,7 +3,7 @@
 //
 //   4-bit codes --dequantise--> 16-bit tile in LDS  <--scatter--  sp_val[j] + sign*eps*z_j
 //   activations (bf16) -------> 16-bit tile in LDS
-//   tiles --MFMA 32x32x16--> fp32 accumulators --> y (fp32) and/or sum (y - target)^2 (fp64)
+//   tiles --MFMA 16x16x32--> fp32 accumulators --> y (fp32) and/or sum (y - target)^2 (fp64)
 //
 // The dense fp weight never exists in memory and the perturbation costs no pass over HBM: it
 // is regenerated from (seed, step, entry index) for exactly the entries of the band a wave
@@ -41,12 +41,11 @@ namespace szo {
 
 // Workgroup = WAVES_M x WAVES_N waves; each wave computes (32*WMB) x (32*WNB) outputs.
 //
-// Schedule of one K step of one wave.  The wave issues SLOTS = 4*WMB*WNB MFMAs.  Its staging
+// Schedule of one K step of one wave.  The wave issues SLOTS = 4*WMB*WNB pairs of MFMAs.  Its staging
 // work for the NEXT tile (8 units per lane: 16-byte chunks of x, or 32-bit words of codes) is
 // cut into SLOTS slices of three to four VALU instructions, and one slice is issued behind
-// each MFMA, where it executes in the shadow of the matrix pipeline.  The LDS reads of the
-// next k-step's operands are issued the same way, one behind each of the first MFMAs of a
-// k-step, into a second set of operand registers.  A scheduling fence after every slot keeps
+// each pair of MFMAs, where it executes in the shadow of the matrix pipeline.  The LDS reads of
+// later operands stand between them (see run_tile).  A scheduling fence after every slot keeps
 // the compiler from regrouping the slots.  Global loads are in place: as soon as a unit's
 // registers have been consumed they are reloaded with the same unit of the tile after next,
 // which gives every load one full K step (about a microsecond) to arrive.
@@ -68,8 +67,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   static_assert(BN % 64 == 0 && X_WAVES > 0, "need whole bands and at least one activation wave");
   constexpr int X_ROWS_PER_PASS = 8 * X_WAVES;     // 8 lanes cover one 128-byte row of x
   static_assert(BM == 8 * X_ROWS_PER_PASS, "every activation lane stages 8 chunks per tile");
-  constexpr int MPK = WMB * WNB;                   // MFMAs per k-step
-  constexpr int SLOTS = 4 * MPK;                   // MFMAs per K step
+  constexpr int SLOTS = 4 * WMB * WNB;             // pairs of MFMAs per K step
   constexpr int SPU = SLOTS / 8;                   // slots per activation staging unit: 1, 2 or 4
   constexpr int WPS = 4 / SPU;                     // output words produced per slot
   // Weight waves finish their dense staging in the first three quarters of the slots (32 slots: 3 per unit; 16 slots: 3 per
@@ -78,7 +76,6 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // at 600 tokens 513 -> 486 us, a 3000 x 4096 layer at 560 tokens and 1 % 68 -> 63, a 4096 x 4096 composed step at 1000 128 -> 121).
   static_assert(SLOTS == 32 || SLOTS == 16, "two schedules exist");
   constexpr int SC_WINDOW = SLOTS == 32 ? 24 : 6, SC_READ = SLOTS == 32 ? 27 : 12, SC_STORE = SLOTS == 32 ? 30 : 15;
-  static_assert(WMB + WNB <= MPK, "operand reads of the next k-step must fit behind this one's MFMAs");
   typedef typename Frag<DT>::type frag_t;
 
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
@@ -108,38 +105,55 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     return __builtin_bit_cast(FwdParams, raw);
   };
 
-  float16_t acc[WMB][WNB];
+  // Blocks of 16 x 16 outputs.  At the sizes that fill the chip this kernel runs at the chip's power limit, and 16x16x32 takes
+  // less power per product than 32x32x16 (half the accumulator traffic): a bare loop with the kernel's operands, operand reads
+  // and four vector instructions per 32 768 FLOP reaches 1566 against 1411 TFLOP/s, and the step over four Llama blocks
+  // runs at 1.86 GHz instead of 1.69 for 5 % more cycles.  us, 32x32x16 -> 16x16x32: two Llama blocks at 4096 tokens 5358 -> 5120, with the bf16 tile 5528 -> 5212, with tables 5880 -> 5685; one Mistral block
+  // at 8192 and 1 % 6148 -> 5836; two of them with two sets of activations at 333 701 -> 661; a 4096 x 4096 composed step at 2000 176 ->
+  // 167.  Where a tile has a CU to itself nothing changes (six forwards of a Llama block at 600 tokens 490 -> 494).
+  // RING operands of x are held at a time, each re-read for a later row of blocks as soon as its own has been issued: three are
+  // what the registers of the 32-slot schedule allow, four hide more where one wave has a SIMD to itself (501 -> 494 above).
+  constexpr int NA = 2 * WMB, NB = 2 * WNB, RING = SLOTS == 32 ? 3 : 4;
+  float4_t acc[NA][NB];
 #pragma unroll
-  for (int i = 0; i < WMB; ++i)
+  for (int i = 0; i < NA; ++i)
 #pragma unroll
-    for (int j = 0; j < WNB; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
 
-  // Operand t of k-step ks in buffer buf: t < WNB is the B (weight) operand of MFMA column
-  // block t, otherwise the A (activation) operand of row block t - WNB.  B operands come first
-  // because the first MFMAs of a k-step need all of them but only the first A operand.
-  const int fragA_row = wm * 32 * WMB + (lane & 31), fragB_row = wn * 32 * WNB + (lane & 31);
-  auto read_operand = [&](int buf, int ks, int t) -> frag_t {
-    const int chunk = 2 * ks + (lane >> 5);
-    if (t < WNB) return *reinterpret_cast<const frag_t*>(ldsB + buf * BN * BK + chunk_off(fragB_row + 32 * t, chunk));
-    return *reinterpret_cast<const frag_t*>(ldsA + buf * BM * BK + chunk_off(fragA_row + 32 * (t - WNB), chunk));
+  // Lane l of an operand holds row l % 16 of its block, columns 8 (l / 16) .. of a 32-column step: a chunk of the staged row.
+  const int fragA_row = wm * 32 * WMB + (lane & 15), fragB_row = wn * 32 * WNB + (lane & 15);
+  auto read_a = [&](int buf, int ks, int i) -> frag_t {
+    return *reinterpret_cast<const frag_t*>(ldsA + buf * BM * BK + chunk_off(fragA_row, 4 * ks + (lane >> 4)) + 16 * i * BK);
+  };
+  auto read_b = [&](int buf, int ks, int j) -> frag_t {
+    return *reinterpret_cast<const frag_t*>(ldsB + buf * BN * BK + chunk_off(fragB_row, 4 * ks + (lane >> 4)) + 16 * j * BK);
   };
 
-  // All MFMAs of one K step on buffer buf, with slice(s) issued behind MFMA s.
+  // All MFMAs of one K step on buffer buf, with slice(s) issued behind every second one.
   auto run_tile = [&](int buf, auto&& slice) {
-    frag_t op[2][WMB + WNB];
+    frag_t a[RING], b[2][NB];
+    a[0] = read_a(buf, 0, 0);
 #pragma unroll
-    for (int t = 0; t < WMB + WNB; ++t) op[0][t] = read_operand(buf, 0, t);
+    for (int j = 0; j < NB; ++j) b[0][j] = read_b(buf, 0, j);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int i = 1; i < RING; ++i) a[i] = read_a(buf, 0, i);
 #pragma unroll
-      for (int t = 0; t < MPK; ++t) {
-        const int i = t / WNB, j = t % WNB;
-        acc[i][j] = Frag<DT>::mfma(op[ks & 1][WNB + i], op[ks & 1][j], acc[i][j]);
-        if (ks < 3 && t < WMB + WNB) op[(ks + 1) & 1][t] = read_operand(buf, ks + 1, t);
-        slice(ks * MPK + t);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          acc[i][j] = Frag<DT>::mfma16(a[(ks * NA + i) % RING], b[ks][j], acc[i][j]);
+          if (ks == 0 && i == NA / 2) b[1][j] = read_b(buf, 1, j);
+          if (j == NB - 1 && ks * NA + i + RING < 2 * NA) a[(ks * NA + i) % RING] = read_a(buf, (ks * NA + i + RING) / NA, (ks * NA + i + RING) % NA);
+          const int m = (ks * NA + i) * NB + j;
+          if (m & 1) {
+            slice(m >> 1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
     }
   };
@@ -605,10 +619,10 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   }
 
   // ---- epilogue: accumulator (i,j) register r holds
-  //      row  32*i + 8*(r/4) + 4*(lane/32) + r%4 ,  column 32*j + lane%32  of the wave tile ----
+  //      row  16*i + 4*(lane/16) + r ,  column 16*j + lane%16  of the wave tile ----
   // Fused loss: the bf16 target tile is first copied into the (now idle) LDS tile buffers with
   // coalesced 16-byte loads, then every lane picks its own elements from LDS.  Differences and
-  // squares are formed in fp32, summed over the 16 registers of one MFMA block in fp32, and
+  // squares are formed in fp32, summed over the 16 registers of four MFMA blocks in fp32, and
   // every such partial is added in fp64 (the loss difference of the two passes is ~1e-6 of the
   // loss, far below fp32 resolution of a long sum).
   constexpr int TROW = TN * 2 + 32;               // LDS row stride of the target tile in bytes
@@ -646,10 +660,10 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     }
   }
   double loss = 0.0;
-  // Element (i, j, r) of this lane: tile row ml0 + 32 i + 8 (r/4) + r%4, tile column nl0 + 32 j.
+  // Element (i, j, r) of this lane, r < 16: tile row ml0 + 32 i + 16 (r/8) + r%4, tile column nl0 + 32 j + 16 (r/4 % 2).
   // DUAL: the waves of the second half of a wave row hold the -eps forward of the same columns.
   const int wn_col = DUAL ? wn % (WAVES_N / 2) : wn;
-  const int ml0 = wm * 32 * WMB + 4 * (lane >> 5), nl0 = wn_col * 32 * WNB + (lane & 31);
+  const int ml0 = wm * 32 * WMB + 4 * (lane >> 4), nl0 = wn_col * 32 * WNB + (lane & 15);
   const uint8_t* const trow = reinterpret_cast<const uint8_t*>(lds) + ml0 * TROW + nl0 * 2;
   // FULL: whole tile inside the matrix (no bounds checks).  STAGED: targets come from LDS.
   // STORE: y is written.  The three are compile-time so that the common cases are straight code.
@@ -664,9 +678,9 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
         float part = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int dm = 32 * i + 8 * (r >> 2) + (r & 3), dn = 32 * j;
+          const int dm = 32 * i + 16 * (r >> 3) + (r & 3), dn = 32 * j + 16 * ((r >> 2) & 1);
           if (FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) {
-            const float v = acc[i][j][r];
+            const float v = acc[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
             const uint32_t off = ybase + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn;
             if (STORE) pe.y[off] = v;
             if (FUSE_LOSS) {
