@@ -418,3 +418,12 @@ def test_dual_sign_tiles_of_the_grouped_launch(dt, fmt):
         for i, (om, o) in enumerate(zip(ref, os_)):
             if o.sp_idx.size:
                 bound.check(i, results[0][1][i], om.sp_val, o.sp_val)
+
+
+def test_calls_without_a_stream_use_the_current_one():
+    """The raw handle that the binding asks torch for, on the default stream, inside a side stream's context and behind it."""
+    side = torch.cuda.Stream()
+    assert szo._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert szo._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+    assert szo._stream(None) == torch.cuda.default_stream().cuda_stream and szo._stream(7) == 7
