@@ -153,26 +153,27 @@ typedef const uint32_t __attribute__((address_space(4)))* small_words;
 __device__ __forceinline__ small_words small_table(const SmallArgs& a) {
   return a.table ? (small_words)a.table : (small_words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SmallArgs, inl) / 4;
 }
-__device__ __forceinline__ int find_index(const SmallArgs& a, int unit) {
+__device__ __forceinline__ int find_index(small_words tab, int n_mats, int unit) {
   constexpr int W = (int)(sizeof(SmallMat) / 4), FB = (int)(offsetof(SmallMat, first_block) / 4);
   static_assert(sizeof(SmallMat) % 4 == 0 && offsetof(SmallMat, first_block) % 4 == 0, "table entry is read as words");
-  const small_words tab = small_table(a);
-  int lo = 0, hi = a.n_mats - 1;
+  int lo = 0, hi = n_mats - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if ((int)tab[mid * W + FB] <= unit) lo = mid; else hi = mid - 1;
   }
   return lo;
 }
-__device__ __forceinline__ SmallMat read_matrix(const SmallArgs& a, int index) {
+__device__ __forceinline__ SmallMat read_matrix(small_words tab, int index) {
   constexpr int W = (int)(sizeof(SmallMat) / 4);
   struct Words { uint32_t w[W]; } raw;
-  const small_words tab = small_table(a);
 #pragma unroll
   for (int i = 0; i < W; ++i) raw.w[i] = tab[index * W + i];
   return __builtin_bit_cast(SmallMat, raw);
 }
-__device__ __forceinline__ SmallMat find_matrix(const SmallArgs& a, int unit) { return read_matrix(a, find_index(a, unit)); }
+__device__ __forceinline__ SmallMat find_matrix(const SmallArgs& a, int unit) {
+  const small_words tab = small_table(a);
+  return read_matrix(tab, find_index(tab, a.n_mats, unit));
+}
 
 // The tables of one row, 16 fp16 entries at p, as the four byte planes that sm_lut_word() reads.
 __device__ __forceinline__ void load_lut_planes(const uint16_t __attribute__((address_space(1)))* p, uint32_t (&T)[8]) {

@@ -116,7 +116,7 @@ constexpr int split_wave_floats(int nacc, int subs) {
 // SUBS: the workgroup's 16-row subtiles of the band.   XP: load instructions for 16 token rows of x, four rows each; with
 // XP = 1 rows 4..15 of the operands are whatever LDS held: they only reach output rows that do not exist.
 template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE, int SUBS, int XP>
-__device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, const int bid, const int slice) {
+__device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_words tab, int index, const int bid, const int slice) {
   static_assert(!BF16 || (MODE == SM_PLAIN && TILE_ROUND), "bf16 tile: plain dequantisation, rounded as in the tile");
   constexpr bool FAST = MODE == SM_FAST, LUT = MODE == SM_LUT;
   static_assert(!ONE || (TILE_ROUND && !DUAL), "instantiations");
@@ -129,7 +129,7 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
   extern __shared__ __attribute__((aligned(16))) float red[];                     // [waves][RED]
 
   asm volatile("" : "+s"(index));                           // (the bodies read the entry one by one: read before the choice, it overflows the scalar registers)
-  const SmallMat mt = read_matrix(a, index);
+  const SmallMat mt = read_matrix(tab, index);
   if (slice * SM_ROWS >= mt.M) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
@@ -190,14 +190,12 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
   };
   uint32_t e_lo = 0, e_hi = 0;                              // this wave's sensitive entries
   if (b0 < b1) {
+    const small_words bounds = (small_words)(uintptr_t)g_tile_ptr;       // scalar loads: a vector load is waited for behind the codes (the six calls 55.4 -> 54.1)
+    if (mt.nnz > 0) { e_lo = bounds[2 * b0]; e_hi = bounds[min(2 * b1, ktiles)]; }
 #pragma unroll
     for (int s = 0; s < SUBS; ++s) load_q(b0, s);
     load_x(b0);
     load_scales(b0);
-    if (mt.nnz > 0) {
-      e_lo = __builtin_amdgcn_readfirstlane(g_tile_ptr[2 * b0]);
-      e_hi = __builtin_amdgcn_readfirstlane(g_tile_ptr[min(2 * b1, ktiles)]);
-    }
   }
   uint32_t tb[LUT ? SUBS : 1][8];
   if (LUT) {
@@ -398,7 +396,7 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
     if constexpr (AGAIN) {
       int again = index;                                    // the entry is read again (laundered: not kept for this)
       asm volatile("" : "+s"(again));
-      const SmallMat ms = read_matrix(a, again);
+      const SmallMat ms = read_matrix(tab, again);
       source = WeightSource{(global_u8)ms.qweight, LUT ? nullptr : (global_u16)ms.scales, LUT ? (global_u16)ms.scales : nullptr,
                             (global_u32)ms.tile_ptr, (global_u32)ms.sp_idx, (global_f32)ms.sp_val, ms.K, ms.group_shift,
                             ms.nnz, ms.nnz_base, a.seed, a.step};
@@ -461,20 +459,28 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, int index, c
 }
 
 // ONE: the "+" forward alone is wanted (single forwards of TILE_ROUND layers); the partials and outputs of the other are not valid then.
+// What a wave needs before it can ask for its matrix's table entry comes as arguments of its own, ahead of the rest: they
+// are in scalar registers when the wave starts (kernarg preload, see build.py), so that the entry is the first memory round trip and
+// not the third, behind the arguments and the size of the grid.  us per pass over four sets of weights: a step over one small layer 11.30 -> 10.97,
+// six calls over an OPT block at one token 57.6 -> 55.4, a step over it at 16 tokens 44.0 -> 43.4.
+struct SplitArgs { const SmallMat* table; int n_mats; uint32_t part_shifts; int slices, few_rows, workgroups; SmallArgs a; };   // as the arguments lie in memory
 template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE>
-__global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>())) band_split_kernel(SmallArgs a) {
-  int bid = xcd_unit((int)blockIdx.x, (int)gridDim.x);
-  const int slice = bid % a.slices;
-  bid /= a.slices;
-  const int index = find_index(a, bid);
-  const uint32_t part_shift = (a.part_shifts >> (4 * (index & 7))) & 15u;
+__global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>()))
+band_split_kernel(const SmallMat* table, int n_mats, uint32_t part_shifts, int slices, int few_rows, int workgroups, SmallArgs a) {
+  int bid = xcd_unit((int)blockIdx.x, workgroups);
+  const small_words tab = table ? (small_words)table
+                                : (small_words)__builtin_amdgcn_kernarg_segment_ptr() + (offsetof(SplitArgs, a) + offsetof(SmallArgs, inl)) / 4;
+  const int slice = bid % slices;
+  bid /= slices;
+  const int index = find_index(tab, n_mats, bid);
+  const uint32_t part_shift = (part_shifts >> (4 * (index & 7))) & 15u;
   auto run = [&](auto rows_tag) {
     constexpr int XP = decltype(rows_tag)::value;
-    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 4, XP>(a, index, bid, slice);
-    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 2, XP>(a, index, bid, slice);
-    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 1, XP>(a, index, bid, slice);
+    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 4, XP>(a, tab, index, bid, slice);
+    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 2, XP>(a, tab, index, bid, slice);
+    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 1, XP>(a, tab, index, bid, slice);
   };
-  if (MODE == SM_FAST && !DUAL && a.few_rows) run(std::integral_constant<int, 1>{});
+  if (MODE == SM_FAST && !DUAL && few_rows) run(std::integral_constant<int, 1>{});
   else run(std::integral_constant<int, 4>{});
 }
 
@@ -487,7 +493,7 @@ static int launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) 
   const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND, ONE>;
   const int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, most_bytes);
   if (rc != SZO_OK) return rc;
-  kern<<<(unsigned)l.workgroups, 64 * waves, split_wave_floats(nacc, l.subs) * sizeof(float) * (size_t)waves, stream>>>(a);
+  kern<<<(unsigned)l.workgroups, 64 * waves, split_wave_floats(nacc, l.subs) * sizeof(float) * (size_t)waves, stream>>>(a.table, a.n_mats, a.part_shifts, a.slices, a.few_rows, l.workgroups, a);
   SZO_LAUNCH_CHECK();
   return SZO_OK;
 }
