@@ -98,39 +98,53 @@ __global__ void spsa_g_kernel(const double* lp, const double* lm, float eps, dou
   *g = (eps == 0.0f) ? 0.0 : (*lp - *lm) / (2.0 * (double)eps);
 }
 
-// Sum of v[0..count) by one workgroup of 1024 threads: thread t adds elements t, t+1024, ... in four
-// interleaved chains (four loads in flight: the loop is bound by memory latency), then the chains and the
-// 1024 thread sums are combined by a fixed tree.  Bit-reproducible.
-__device__ __forceinline__ double block_sum_1024(const double* __restrict__ v, int count, double* scratch) {
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+// Sums of v[0..count) and, with TWO, of v[count..2 count) by one workgroup of 1024 threads: thread t adds elements t, t+1024, ...
+// in four interleaved chains (four loads in flight: the loop is bound by memory latency), then the chains and the
+// 1024 thread sums are combined by a fixed tree.  Bit-reproducible.  Both sums side by side: one after the other they are two memory
+// round trips and two pairs of barriers.
+template <bool TWO>
+__device__ __forceinline__ void block_sums_1024(const double* __restrict__ v, int count, double (&scratch)[2][16], double (&total)[2]) {
+  double a[2][4] = {};
   int i = threadIdx.x;
   for (; i + 3 * 1024 < count; i += 4 * 1024) {
-    a0 += v[i]; a1 += v[i + 1024]; a2 += v[i + 2 * 1024]; a3 += v[i + 3 * 1024];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      a[0][c] += v[i + 1024 * c];
+      if (TWO) a[1][c] += v[count + i + 1024 * c];
+    }
   }
-  for (; i < count; i += 1024) a0 += v[i];
-  double a = (a0 + a1) + (a2 + a3);
-  a = wave_sum(a);
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = a;
+  for (; i < count; i += 1024) {
+    a[0][0] += v[i];
+    if (TWO) a[1][0] += v[count + i];
+  }
+#pragma unroll
+  for (int s = 0; s < (TWO ? 2 : 1); ++s) {
+    const double w = wave_sum((a[s][0] + a[s][1]) + (a[s][2] + a[s][3]));
+    if ((threadIdx.x & 63) == 0) scratch[s][threadIdx.x >> 6] = w;
+  }
   __syncthreads();
-  double t = 0.0;
-  for (int i = 0; i < 16; ++i) t += scratch[i];
-  __syncthreads();
-  return t;
+#pragma unroll
+  for (int s = 0; s < (TWO ? 2 : 1); ++s) {
+    total[s] = 0.0;
+    for (int k = 0; k < 16; ++k) total[s] += scratch[s][k];
+  }
 }
 
 __global__ void __launch_bounds__(1024) reduce_partials_kernel(const double* __restrict__ partials, int count,
                                                                double scale, double* loss_acc) {
-  __shared__ double scratch[16];
-  const double t = block_sum_1024(partials, count, scratch);
-  if (threadIdx.x == 0) *loss_acc += scale * t;
+  __shared__ double scratch[2][16];
+  double t[2];
+  block_sums_1024<false>(partials, count, scratch, t);
+  if (threadIdx.x == 0) *loss_acc += scale * t[0];
 }
 
 // The SPSA scalar of Definition 1 from the two passes' partial losses.
 __global__ void __launch_bounds__(1024) reduce_step_kernel(const double* __restrict__ partials, int count, float eps,
                                                            double* scalars) {
-  __shared__ double scratch[16];
-  const double lp = block_sum_1024(partials, count, scratch);
-  const double lm = block_sum_1024(partials + count, count, scratch);
+  __shared__ double scratch[2][16];
+  double t[2];
+  block_sums_1024<true>(partials, count, scratch, t);
+  const double lp = t[0], lm = t[1];
   if (threadIdx.x == 0) {
     scalars[0] = lp;
     scalars[1] = lm;

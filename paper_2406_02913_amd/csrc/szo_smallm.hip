@@ -461,21 +461,32 @@ struct UpdateArgs {
 };
 struct InlineUpdateArgs { UpdateArgs staged; SmallMat inl[kInlineMats]; };         // the table in the kernel arguments
 
-// What reduce_step_kernel adds up, in its order: 256 threads stand for its 1024.
-__device__ __forceinline__ double block_sum_as_1024(const double* __restrict__ v, int count, double (&scratch)[16]) {
+// What reduce_step_kernel adds up, in its order: 256 threads stand for its 1024.  Both signs side by side, as there.
+__device__ __forceinline__ void block_sums_as_1024(const double* __restrict__ v, int count, double (&scratch)[2][16], double (&total)[2]) {
+  double a[4][2][4] = {};
+#pragma unroll
   for (int k = 0; k < 4; ++k) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     int i = 256 * k + (int)threadIdx.x;
-    for (; i + 3 * 1024 < count; i += 4 * 1024) { a0 += v[i]; a1 += v[i + 1024]; a2 += v[i + 2 * 1024]; a3 += v[i + 3 * 1024]; }
-    for (; i < count; i += 1024) a0 += v[i];
-    const double a = wave_sum((a0 + a1) + (a2 + a3));
-    if ((threadIdx.x & 63) == 0) scratch[4 * k + (threadIdx.x >> 6)] = a;
+    for (; i + 3 * 1024 < count; i += 4 * 1024)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        for (int s = 0; s < 2; ++s) a[k][s][c] += v[s * count + i + 1024 * c];
+    for (; i < count; i += 1024)
+      for (int s = 0; s < 2; ++s) a[k][s][0] += v[s * count + i];
   }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const double w = wave_sum((a[k][s][0] + a[k][s][1]) + (a[k][s][2] + a[k][s][3]));
+      if ((threadIdx.x & 63) == 0) scratch[s][4 * k + (threadIdx.x >> 6)] = w;
+    }
   __syncthreads();
-  double t = 0.0;
-  for (int i = 0; i < 16; ++i) t += scratch[i];
-  __syncthreads();
-  return t;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    total[s] = 0.0;
+    for (int i = 0; i < 16; ++i) total[s] += scratch[s][i];
+  }
 }
 
 // With few partials every workgroup adds them up by itself (same order, same g everywhere) instead of waiting for a
@@ -494,17 +505,7 @@ __global__ void __launch_bounds__(256) sparse_update_table_kernel(Args args) {
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int64_t tw = (int64_t)blockIdx.x * 256 + 64 * wave;           // the wave's first thread
   if (!REDUCE && tw >= a.total_quads) return;
-  double g;
-  if constexpr (REDUCE) {
-    __shared__ double scratch[16];
-    const double lp = block_sum_as_1024(a.partials, a.partials_per_sign, scratch);
-    const double lm = block_sum_as_1024(a.partials + a.partials_per_sign, a.partials_per_sign, scratch);
-    g = (a.eps == 0.0f) ? 0.0 : (lp - lm) / (2.0 * (double)a.eps);
-    if (blockIdx.x == 0 && threadIdx.x == 0) { a.scalars[0] = lp; a.scalars[1] = lm; a.scalars[2] = g; }
-  } else {
-    g = a.scalars[2];
-  }
-  if (tw >= a.total_quads) return;
+  // z and the values first: what g waits for (the sums of the losses) is a chain of its own
   const uint64_t seed = a.seed, step = a.step;
   typedef const uint32_t __attribute__((address_space(4)))* words;
   const words tab = INLINE ? (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(InlineUpdateArgs, inl) / 4 : (words)a.table;
@@ -519,14 +520,27 @@ __global__ void __launch_bounds__(256) sparse_update_table_kernel(Args args) {
   for (int i = 0; i < W; ++i) raw.w[i] = tab[lo * W + i];
   const SmallMat mt = __builtin_bit_cast(SmallMat, raw);
   const int64_t tq = tw + (int64_t)(threadIdx.x & 63) - mt.first_quad, j0 = 4 * tq;
-  if (j0 >= (int64_t)mt.nnz) return;
-  const float c = (float)((double)a.lr * g);                          // lr * g, rounded once
-  float z[4];
-  zbar_quad((mt.nnz_base >> 2) + (uint64_t)tq, seed, step, z);
+  const bool mine = tw < a.total_quads && j0 < (int64_t)mt.nnz, whole = mine && j0 + 4 <= (int64_t)mt.nnz;
+  if (!REDUCE && !mine) return;
+  float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   float __attribute__((address_space(1)))* const v = (float __attribute__((address_space(1)))*)mt.sp_val + j0;
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  if (j0 + 4 <= (int64_t)mt.nnz) {
-    f32x4 w = *reinterpret_cast<f32x4 __attribute__((address_space(1)))*>(v);
+  f32x4 w = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (whole) w = *reinterpret_cast<f32x4 __attribute__((address_space(1)))*>(v);
+  if (mine) zbar_quad((mt.nnz_base >> 2) + (uint64_t)tq, seed, step, z);
+  double g;
+  if constexpr (REDUCE) {
+    __shared__ double scratch[2][16];
+    double loss[2];
+    block_sums_as_1024(a.partials, a.partials_per_sign, scratch, loss);
+    g = (a.eps == 0.0f) ? 0.0 : (loss[0] - loss[1]) / (2.0 * (double)a.eps);
+    if (blockIdx.x == 0 && threadIdx.x == 0) { a.scalars[0] = loss[0]; a.scalars[1] = loss[1]; a.scalars[2] = g; }
+    if (!mine) return;
+  } else {
+    g = a.scalars[2];
+  }
+  const float c = (float)((double)a.lr * g);                          // lr * g, rounded once
+  if (whole) {
     w[0] = fmaf(-c, z[0], w[0]); w[1] = fmaf(-c, z[1], w[1]); w[2] = fmaf(-c, z[2], w[2]); w[3] = fmaf(-c, z[3], w[3]);
     *reinterpret_cast<f32x4 __attribute__((address_space(1)))*>(v) = w;
   } else {
