@@ -36,6 +36,7 @@ typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
 constexpr int SP_WIN = 128;             // sensitive entries computed per refill of a wave's window, two per lane
+constexpr int SP_WIN_FLOATS = SP_WIN * 10 / 4;             // of a window: column, row, two 16-bit values
 constexpr int SP_MAX_WAVES = 16;
 constexpr int SP_XROW = 128 + 8;        // LDS row stride of a staged block of x, in 16-bit elements
 
@@ -123,6 +124,12 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_
   constexpr int SETS = DUAL ? 2 : 1;
   constexpr int NACC = split_sets<DUAL, TILE_ROUND, ONE>();
   constexpr int RED = split_wave_floats(NACC, SUBS);
+  // The entries stand behind the first block of the codes where one window holds them all: their bounds, values and columns of x are a
+  // chain of memory round trips that the block's dequantisation covers.  Single forwards of TILE_ROUND layers, us: a 5000 x 4160 layer with
+  // the bf16 tile at 77 tokens 20.8 -> 19.5, 4096 x 4096 at 128 20.1 -> 18.7.  Elsewhere before all codes: groups of 128 have less to
+  // dequantise (six forwards of an OPT block at one token 53.1 -> 53.9), and with both signs rounded the registers of the block and of the
+  // entries together cost a workgroup per CU (one Mistral block with the bf16 tile at 40 tokens 87 -> 99).
+  constexpr bool LATER = TILE_ROUND && ONE;
   constexpr int DENSE1 = TILE_ROUND ? 1 : 2;                // accumulator set of x2's dense product
   typedef SplitOps<BF16> Ops;
   typedef typename Ops::frag frag_t;
@@ -209,10 +216,72 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_
 #pragma unroll
     for (int s = 0; s < SUBS; ++s) acc[i][s] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // ---- sensitive entries, while the first codes are on their way: 128 at a time into the wave's own part of LDS
-  //      (its later accumulator area), then 16 per matrix product ----
-  {
-    uint32_t* const wk = reinterpret_cast<uint32_t*>(red + wave * RED);            // column
+  // ---- dense: this wave's blocks of 128 columns, codes and x one block ahead ----
+  uint16_t* const xs = reinterpret_cast<uint16_t*>(red + wave * RED);              // [16][SP_XROW], in place of the window
+  uint32_t magic_lo = 0x64006400u, magic_hi = 0x54005400u;
+  asm volatile("" : "+v"(magic_lo), "+v"(magic_hi));
+  const half8_t minus_offsets = {(_Float16)-1032.0f, (_Float16)-1032.0f, (_Float16)-72.0f, (_Float16)-72.0f,
+                                 (_Float16)-1032.0f, (_Float16)-1032.0f, (_Float16)-72.0f, (_Float16)-72.0f};
+  // MORE at compile time: as a run-time condition around the loads it made the compiler drain them in every iteration
+  auto dense_block = [&](int b, auto more_tag) {
+    constexpr bool MORE = decltype(more_tag)::value;
+    const bool empty = 128 * b + 8 * xr_piece >= K;         // the columns this lane has loaded lie past the end of K
+    frag_t af[SETS][4];
+#pragma unroll
+    for (int set = 0; set < SETS; ++set) {
+#pragma unroll
+      for (int i = 0; i < XP; ++i)
+        *reinterpret_cast<frag_t*>(xs + (4 * i + xr_row) * SP_XROW + 8 * xr_piece) =
+            Ops::activations(empty ? u32x4{0u, 0u, 0u, 0u} : xr[set][i]);
+      asm volatile("" ::: "memory");                        // written by the wave's other lanes; LDS keeps a wave's order
+#pragma unroll
+      for (int t = 0; t < 4; ++t) af[set][t] = *reinterpret_cast<const frag_t*>(xs + nn * SP_XROW + 32 * jj + 8 * t);
+      asm volatile("" ::: "memory");
+    }
+    if (MORE) load_x(b + 1);
+    const half4_t sh4 = __builtin_bit_cast(half4_t, SUBS == 4 ? sc : sc >> (16 * sub0));
+    if (MORE) load_scales(b + 1);
+    float4_t init[SETS];
+#pragma unroll
+    for (int set = 0; set < SETS; ++set) {
+      init[set] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (FAST) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) init[set] = Ops::dense(af[set][t], minus_offsets, init[set]);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < SUBS; ++s) {
+      const u32x4 qs = q[s];
+      if (MORE) load_q(b + 1, s);
+      float4_t tmp[SETS];
+#pragma unroll
+      for (int set = 0; set < SETS; ++set) tmp[set] = FAST ? init[set] : acc[set * DENSE1][s];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        frag_t w;
+        if constexpr (BF16) w = dequant_word_bf16(qs[t], sh4[s]);
+        else if constexpr (LUT) w = sm_lut_word(qs[t], tb[s]);
+        else w = sm_dequant_word<FAST>(qs[t], magic_lo, magic_hi, half2_t{sh4[s], sh4[s]});
+#pragma unroll
+        for (int set = 0; set < SETS; ++set) tmp[set] = Ops::dense(af[set][t], w, tmp[set]);
+      }
+#pragma unroll
+      for (int set = 0; set < SETS; ++set) {
+        if (FAST) {
+          const float sf = (float)sh4[s];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[set * DENSE1][s][r] = fmaf(tmp[set][r], sf, acc[set * DENSE1][s][r]);
+        } else {
+          acc[set * DENSE1][s] = tmp[set];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);                    // subtiles in program order: fewer registers in flight
+    }
+  };
+  // ---- sensitive entries: 128 at a time into LDS of the wave's own, then 16 per matrix product ----
+  auto sensitive_entries = [&]() {
+    uint32_t* const wk = reinterpret_cast<uint32_t*>(LATER ? red + waves * RED + wave * SP_WIN_FLOATS : red + wave * RED);      // column
     uint16_t* const wr = reinterpret_cast<uint16_t*>(wk + SP_WIN);                  // row of the band
     uint16_t* const wv = wr + SP_WIN;                                                // 16-bit v | v + eps z
     uint16_t* const wz = wv + SP_WIN;                                                // 16-bit z | v - eps z
@@ -307,72 +376,12 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_
       }
       asm volatile("" ::: "memory");                        // the next refill overwrites the window
     }
-  }
-
-  // ---- dense: this wave's blocks of 128 columns, codes and x one block ahead ----
-  uint16_t* const xs = reinterpret_cast<uint16_t*>(red + wave * RED);              // [16][SP_XROW], in place of the window
-  uint32_t magic_lo = 0x64006400u, magic_hi = 0x54005400u;
-  asm volatile("" : "+v"(magic_lo), "+v"(magic_hi));
-  const half8_t minus_offsets = {(_Float16)-1032.0f, (_Float16)-1032.0f, (_Float16)-72.0f, (_Float16)-72.0f,
-                                 (_Float16)-1032.0f, (_Float16)-1032.0f, (_Float16)-72.0f, (_Float16)-72.0f};
-  // MORE at compile time: as a run-time condition around the loads it made the compiler drain them in every iteration
-  auto dense_block = [&](int b, auto more_tag) {
-    constexpr bool MORE = decltype(more_tag)::value;
-    const bool empty = 128 * b + 8 * xr_piece >= K;         // the columns this lane has loaded lie past the end of K
-    frag_t af[SETS][4];
-#pragma unroll
-    for (int set = 0; set < SETS; ++set) {
-#pragma unroll
-      for (int i = 0; i < XP; ++i)
-        *reinterpret_cast<frag_t*>(xs + (4 * i + xr_row) * SP_XROW + 8 * xr_piece) =
-            Ops::activations(empty ? u32x4{0u, 0u, 0u, 0u} : xr[set][i]);
-      asm volatile("" ::: "memory");                        // written by the wave's other lanes; LDS keeps a wave's order
-#pragma unroll
-      for (int t = 0; t < 4; ++t) af[set][t] = *reinterpret_cast<const frag_t*>(xs + nn * SP_XROW + 32 * jj + 8 * t);
-      asm volatile("" ::: "memory");
-    }
-    if (MORE) load_x(b + 1);
-    const half4_t sh4 = __builtin_bit_cast(half4_t, SUBS == 4 ? sc : sc >> (16 * sub0));
-    if (MORE) load_scales(b + 1);
-    float4_t init[SETS];
-#pragma unroll
-    for (int set = 0; set < SETS; ++set) {
-      init[set] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-      if constexpr (FAST) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) init[set] = Ops::dense(af[set][t], minus_offsets, init[set]);
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < SUBS; ++s) {
-      const u32x4 qs = q[s];
-      if (MORE) load_q(b + 1, s);
-      float4_t tmp[SETS];
-#pragma unroll
-      for (int set = 0; set < SETS; ++set) tmp[set] = FAST ? init[set] : acc[set * DENSE1][s];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        frag_t w;
-        if constexpr (BF16) w = dequant_word_bf16(qs[t], sh4[s]);
-        else if constexpr (LUT) w = sm_lut_word(qs[t], tb[s]);
-        else w = sm_dequant_word<FAST>(qs[t], magic_lo, magic_hi, half2_t{sh4[s], sh4[s]});
-#pragma unroll
-        for (int set = 0; set < SETS; ++set) tmp[set] = Ops::dense(af[set][t], w, tmp[set]);
-      }
-#pragma unroll
-      for (int set = 0; set < SETS; ++set) {
-        if (FAST) {
-          const float sf = (float)sh4[s];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[set * DENSE1][s][r] = fmaf(tmp[set][r], sf, acc[set * DENSE1][s][r]);
-        } else {
-          acc[set * DENSE1][s] = tmp[set];
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);                    // subtiles in program order: fewer registers in flight
-    }
   };
-  for (int b = b0; b + 1 < b1; ++b) dense_block(b, std::true_type{});
+
+  int next = b0;
+  if (LATER && e_hi - e_lo <= (uint32_t)SP_WIN && next + 1 < b1) dense_block(next++, std::true_type{});
+  sensitive_entries();
+  for (; next + 1 < b1; ++next) dense_block(next, std::true_type{});
   if (b0 < b1) dense_block(b1 - 1, std::false_type{});
 
   // ---- sum over the waves, in wave order ----
@@ -487,13 +496,13 @@ band_split_kernel(const SmallMat* table, int n_mats, uint32_t part_shifts, int s
 template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE = false>
 static int launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) {
   constexpr int nacc = split_sets<DUAL, TILE_ROUND, ONE>(), most = split_max_waves<MODE, DUAL, TILE_ROUND>();
-  constexpr size_t most_bytes = split_wave_floats(nacc, 4) * sizeof(float) * most;
+  constexpr size_t window = (TILE_ROUND && ONE ? SP_WIN_FLOATS : 0) * sizeof(float), most_bytes = (split_wave_floats(nacc, 4) * sizeof(float) + window) * most;
   const int waves = l.waves < most ? l.waves : most;
   static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
   const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND, ONE>;
   const int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, most_bytes);
   if (rc != SZO_OK) return rc;
-  kern<<<(unsigned)l.workgroups, 64 * waves, split_wave_floats(nacc, l.subs) * sizeof(float) * (size_t)waves, stream>>>(a.table, a.n_mats, a.part_shifts, a.slices, a.few_rows, l.workgroups, a);
+  kern<<<(unsigned)l.workgroups, 64 * waves, (split_wave_floats(nacc, l.subs) * sizeof(float) + window) * (size_t)waves, stream>>>(a.table, a.n_mats, a.part_shifts, a.slices, a.few_rows, l.workgroups, a);
   SZO_LAUNCH_CHECK();
   return SZO_OK;
 }
