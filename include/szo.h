@@ -178,7 +178,7 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * output buffer in common with another layer run as one launch there too.
  * descs: host array, read before the call returns.  Everything is enqueued on `stream`.  The
  * descriptor tables of the grouped launches (forwards of a step; the update), except those of up to eight layers
- * on the few-token path and in the update, which are kernel arguments, travel through a ring of eight pinned host buffers per host thread (allocated on first use,
+ * on the few-token path and in the update and of up to sixteen in the other forwards, which are kernel arguments, travel through a ring of eight pinned host buffers per host thread (allocated on first use,
  * released when the thread ends); a call waits on the host only if a copy issued eight tables
  * earlier on this thread (four tiled steps) has not executed yet.  Because of those buffers NO
  * variant of this call can be captured into a HIP graph: it returns SZO_EUNSUPPORTED, with nothing

@@ -738,7 +738,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_kernel(FwdP
 
 // Grouped launch: every forward of a step (all matrices, both signs) in one grid, so that the only
 // partly filled round of workgroups is the last one of the step, not the last one of every matrix.
-// `table` holds one FwdParams per MATRIX, ordered by first_block; a workgroup finds its entry by
+// The table (see forward_table) holds one FwdParams per MATRIX, ordered by first_block; a workgroup finds its entry by
 // binary search and reads it through the constant address space (scalar loads into scalar registers).
 // An entry has 2 * grid_m * grid_n workgroups: neighbouring logical ids are the +eps and the -eps
 // forward of the same tile, and pairs walk the grid in strips of 2 row blocks, so the 32 workgroups
@@ -748,10 +748,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_kernel(FwdP
 // With DUAL an entry has grid_m * grid_n workgroups, each computing both forwards of a tile of half the
 // width (see linear_fwd_body); the 32 workgroups resident on an XCD are then 2 x 16 such tiles.
 template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kernel(const FwdParams* table, int n_entries) {
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kernel(const FwdParams* table, int n_entries, InlineForwards) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
   static_assert(sizeof(FwdParams) % 4 == 0 && offsetof(FwdParams, first_block) % 4 == 0, "table entry is read as words");
-  const auto* tab = (const uint32_t __attribute__((address_space(4)))*)table;
+  const table_words tab = forward_table(table);
   int lo = 0, hi = n_entries - 1;                           // last entry whose first_block <= blockIdx.x
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -936,7 +936,7 @@ static int update_all(const szo_linear_desc* descs, int n, uint64_t seed, uint64
 static double* partial_area(void* workspace) { return (double*)((char*)workspace + kWorkspaceHeader); }
 
 template <int DT, int FMT = SZO_FORMAT_UNIFORM, int TILE = 256, bool DUAL = false>
-static int launch_table(const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
+static int launch_table(const ForwardTableArgs& t, int64_t blocks, hipStream_t stream) {
   static_assert(TILE == 256 || TILE == 128, "two workgroup tiles exist");
   constexpr int BM = TILE, BN = TILE;
   constexpr int WAVES_N = TILE == 256 ? 4 : 2, WMB = TILE == 256 ? 4 : 2;      // 2x4 waves of 128x64, or 2x2 of 64x64
@@ -949,7 +949,7 @@ static int launch_table(const FwdParams* table_dev, int entries, int64_t blocks,
   if (rc != SZO_OK) return rc;
   rc = timing_begin(stream);
   if (rc != SZO_OK) return rc;
-  kern<<<(unsigned)blocks, 128 * WAVES_N, lds_bytes, stream>>>(table_dev, entries);
+  kern<<<(unsigned)blocks, 128 * WAVES_N, lds_bytes, stream>>>(t.table, t.n_entries, t.inl);
   SZO_LAUNCH_CHECK();
   return timing_end(stream);
 }
@@ -1038,24 +1038,25 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
     first_block += ((dual ? 1 : 2) * (int64_t)p.grid_m * p.grid_n + 7) & ~(int64_t)7;
     if (first_block > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
   }
-  int rc = stage_table(table.data(), sizeof(FwdParams) * table.size(), table_dev, stream);
+  static thread_local ForwardTableArgs t;
+  int rc = place_table(table.data(), table.size(), table_dev, stream, t);
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;
   if (descs[0].format == SZO_FORMAT_LUT)
-    return launch_table<SZO_TILE_F16, SZO_FORMAT_LUT>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
+    return launch_table<SZO_TILE_F16, SZO_FORMAT_LUT>(t, first_block, stream);
   if (tile == 128) {
     if (descs[0].tile_dtype == SZO_TILE_F16)
-      return launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 128>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
-    return launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 128>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
+      return launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 128>(t, first_block, stream);
+    return launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 128>(t, first_block, stream);
   }
   if (dual) {
     if (descs[0].tile_dtype == SZO_TILE_F16)
-      return launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, true>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
-    return launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, true>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
+      return launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, true>(t, first_block, stream);
+    return launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, true>(t, first_block, stream);
   }
   if (descs[0].tile_dtype == SZO_TILE_F16)
-    return launch_table<SZO_TILE_F16>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
-  return launch_table<SZO_TILE_BF16>((const FwdParams*)table_dev, (int)table.size(), first_block, stream);
+    return launch_table<SZO_TILE_F16>(t, first_block, stream);
+  return launch_table<SZO_TILE_BF16>(t, first_block, stream);
 }
 
 // Device address of `scratch` on the current device, looked up once per device.

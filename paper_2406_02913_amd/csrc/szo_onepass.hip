@@ -53,7 +53,6 @@ struct OnePassLds {                                         // byte offsets
 };
 static_assert(OnePassLds::BYTES <= 80 * 1024 && OP_BM * OP_TROW <= OnePassLds::RING, "two workgroups per CU; the target tile replaces x");
 
-typedef const uint32_t __attribute__((address_space(4)))* table_words;
 __device__ __forceinline__ FwdParams read_entry(table_words e) {
   struct Words { uint32_t w[sizeof(FwdParams) / 4]; } raw;
 #pragma unroll
@@ -551,11 +550,11 @@ __device__ __forceinline__ void onepass_body(const FwdParams& p, const int bid, 
 // that one alone.
 constexpr int kNoGroups128 = 0, kAllGroups128 = 1, kSomeGroups128 = 2;
 
-// Every layer of a step in one grid: `table` holds one entry per layer, ordered by first_block (a multiple of 8).
+// Every layer of a step in one grid: the table (see forward_table) holds one entry per layer, ordered by first_block (a multiple of 8).
 template <int DT, bool STORE_Y, int GROUPS, bool SPARSE>
-__global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const FwdParams* table, int n_entries) {
+__global__ void __launch_bounds__(64 * OP_WAVES, 2) onepass_table_kernel(const FwdParams* table, int n_entries, InlineForwards) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
-  const table_words tab = (table_words)table;
+  const table_words tab = forward_table(table);
   int first = 0, last = n_entries - 1;                      // last entry whose first_block <= blockIdx.x
   while (first < last) {
     const int mid = (first + last + 1) >> 1;
@@ -589,16 +588,16 @@ static int launch(Kernel kern, std::atomic<uint64_t>& lds_limit_set, int64_t blo
   return timing_end(stream);
 }
 template <int DT, bool STORE_Y, int GROUPS, bool SPARSE>
-static int launch_table(const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
+static int launch_table(const ForwardTableArgs& t, int64_t blocks, hipStream_t stream) {
   static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
-  return launch(onepass_table_kernel<DT, STORE_Y, GROUPS, SPARSE>, lds_limit_set, blocks, stream, table_dev, entries);
+  return launch(onepass_table_kernel<DT, STORE_Y, GROUPS, SPARSE>, lds_limit_set, blocks, stream, t.table, t.n_entries, t.inl);
 }
 template <bool STORE_Y, bool SPARSE>
-static int launch_table(bool bf16, int groups, const FwdParams* table_dev, int entries, int64_t blocks, hipStream_t stream) {
-  if (bf16) return launch_table<SZO_TILE_BF16, STORE_Y, kNoGroups128, SPARSE>(table_dev, entries, blocks, stream);
-  if (groups == kNoGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kNoGroups128, SPARSE>(table_dev, entries, blocks, stream);
-  if (groups == kAllGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kAllGroups128, SPARSE>(table_dev, entries, blocks, stream);
-  return launch_table<SZO_TILE_F16, STORE_Y, kSomeGroups128, false>(table_dev, entries, blocks, stream);
+static int launch_table(bool bf16, int groups, const ForwardTableArgs& t, int64_t blocks, hipStream_t stream) {
+  if (bf16) return launch_table<SZO_TILE_BF16, STORE_Y, kNoGroups128, SPARSE>(t, blocks, stream);
+  if (groups == kNoGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kNoGroups128, SPARSE>(t, blocks, stream);
+  if (groups == kAllGroups128) return launch_table<SZO_TILE_F16, STORE_Y, kAllGroups128, SPARSE>(t, blocks, stream);
+  return launch_table<SZO_TILE_F16, STORE_Y, kSomeGroups128, false>(t, blocks, stream);
 }
 template <int DT, int GROUPS, bool SPARSE>
 static int launch_one(const FwdParams& p, hipStream_t stream) {
@@ -804,16 +803,16 @@ int onepass_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_
     if (first_block > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
     offset += onepass_tiles(d);
   }
-  const int rc = stage_table(table.data(), sizeof(FwdParams) * table.size(), table_dev, stream);
+  static thread_local ForwardTableArgs t;
+  const int rc = place_table(table.data(), table.size(), table_dev, stream, t);
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;
-  const FwdParams* t = (const FwdParams*)table_dev;
   const int e = (int)table.size(), with = (int)std::count_if(table.begin(), table.end(), [](const FwdParams& p) { return p.group_shift == 7; });
   const int groups = with == e ? kAllGroups128 : with == 0 ? kNoGroups128 : kSomeGroups128;
   const bool bf16 = descs[order[0]].tile_dtype == SZO_TILE_BF16;
   if (sparse_launch(entries, weights, T, wg_k, descs[order[0]].K, !bf16 && groups == kAllGroups128))
-    return store_y ? launch_table<true, true>(bf16, groups, t, e, first_block, stream) : launch_table<false, true>(bf16, groups, t, e, first_block, stream);
-  return store_y ? launch_table<true, false>(bf16, groups, t, e, first_block, stream) : launch_table<false, false>(bf16, groups, t, e, first_block, stream);
+    return store_y ? launch_table<true, true>(bf16, groups, t, first_block, stream) : launch_table<false, true>(bf16, groups, t, first_block, stream);
+  return store_y ? launch_table<true, false>(bf16, groups, t, first_block, stream) : launch_table<false, false>(bf16, groups, t, first_block, stream);
 }
 
 }  // namespace szo
