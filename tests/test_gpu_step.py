@@ -427,3 +427,30 @@ def test_calls_without_a_stream_use_the_current_one():
     with torch.cuda.stream(side):
         assert szo._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
     assert szo._stream(None) == torch.cuda.default_stream().cuda_stream and szo._stream(7) == 7
+
+
+@pytest.mark.parametrize("config", [6, 11])                  # the tiled kernel's grouped launch, the one-dense-pass kernel
+@pytest.mark.parametrize("layers", [16, 17])                 # the last table in the kernel arguments, the first that is staged
+def test_tables_in_the_kernel_arguments_and_staged(layers, config):
+    """A step over many small layers against steps over each of them: the same outputs.  The one-dense-pass kernel adds their squares
+    one by one in fp64; the tiled one sixteen at a time in fp32, and which sixteen depends on the tile: 16 x 2^-24 at most."""
+    descs, keep, base = [], [], 0
+    for i in range(layers):
+        o, d = make_pair(601 + i, 70 + i, 130, 128 * (1 + i % 3), 128, 1e-2, nnz_base=base)
+        base += (o.sp_idx.size + 3) // 4 * 4
+        keep.append(d)
+        descs.append(d.desc(with_y=False))
+    ws, scal = szo.new_workspace(), torch.zeros(3, dtype=torch.float64, device="cuda")
+    want = np.zeros(2)
+    szo.szo_set_tile_config(config)
+    try:
+        for d in descs:
+            szo.szo_zo_step([d], 5, 1, 1e-3, 0.0, scal, ws, szo.STEP_FUSED_LOSS)
+            want += scal.cpu().numpy()[:2]
+        szo.szo_kernel_timing(True)
+        szo.szo_zo_step(descs, 5, 1, 1e-3, 0.0, scal, ws, szo.STEP_FUSED_LOSS)
+        _, launches = szo.szo_kernel_timing_read()
+    finally:
+        szo.szo_kernel_timing(False)
+        szo.szo_set_tile_config(0)
+    assert launches == 1 and np.allclose(scal.cpu().numpy()[:2], want, rtol=1e-12 if config == 11 else 16 * 2.0 ** -24, atol=0.0)
