@@ -39,6 +39,9 @@ static __device__ __align__(256) double scratch[kNoAllocMaxPartials];
 
 namespace szo {
 
+// LDS of a tile: two stages of both operands, the weight waves' windows and write sinks.
+constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int)sizeof(uint16_t) + (bn / 64) * (kWindow * 6 + 128); }
+
 // Workgroup = WAVES_M x WAVES_N waves; each wave computes (32*WMB) x (32*WNB) outputs.
 //
 // Schedule of one K step of one wave.  The wave issues SLOTS = 4*WMB*WNB pairs of MFMAs.  Its staging
@@ -55,7 +58,12 @@ namespace szo {
 // and written twice, the two copies differ only at the sensitive entries.  Waves of the first half of a
 // wave row compute the +eps forward, the others the -eps forward; every MFMA of both forwards is
 // executed, only the staging of the weights is shared.  The MFMA loop is the same as without DUAL.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false>
+//
+// KS = 2 (a launch of few 128 x 128 tiles): eight waves, of which the second four compute the second half of the K steps in
+// buffers of their own.  Such a launch is bound by a weight wave's chain, ~220 instructions per K step at one wave on its SIMD
+// (which issues one every ~6 cycles); with two waves per SIMD half as many steps stand one behind the other.  Either half keeps
+// the sums of half of the tile's rows.
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1>
 __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm, const int bn,
                                                 const uint32_t __attribute__((address_space(4)))* entry = nullptr) {
   constexpr int NWAVES = WAVES_M * WAVES_N;
@@ -78,18 +86,22 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   constexpr int SC_WINDOW = SLOTS == 32 ? 24 : 6, SC_READ = SLOTS == 32 ? 27 : 12, SC_STORE = SLOTS == 32 ? 30 : 15;
   typedef typename Frag<DT>::type frag_t;
 
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  static_assert(KS == 1 || (KS == 2 && SLOTS == 16 && !DUAL && FMT == SZO_FORMAT_UNIFORM), "K in two parts: the small tile");
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int any_wave = __builtin_amdgcn_readfirstlane(tid >> 6), kpart = KS == 1 ? 0 : any_wave / NWAVES;
+  // (the second part's weight waves share their SIMDs with the first part's activation waves)
+  const int wave = KS == 1 ? any_wave : (any_wave % NWAVES) ^ (kpart ? NWAVES / 2 : 0);
+  uint16_t* const lds = smem + kpart * (tiled_lds_bytes(BM, BN) / 2);
   uint16_t* const ldsA = lds;                                   // [2][BM*BK]
   uint16_t* const ldsB = lds + 2 * BM * BK;                     // [2][BN*BK]
   float* const winVal = reinterpret_cast<float*>(lds + 2 * (BM + BN) * BK);        // [W_WAVES][kWindow]
   uint16_t* const winPos = reinterpret_cast<uint16_t*>(winVal + W_WAVES * kWindow);  // [W_WAVES][kWindow]
   uint16_t* const sink16 = winPos + W_WAVES * kWindow;                              // [W_WAVES][64] write sink of idle lanes
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int m0 = bm * BM, n0 = bn * TN;
-  const int nk = p.ktiles;
+  const int nk = p.ktiles / KS, k0 = kpart * nk;            // this part's K steps: k0 .. k0 + nk - 1 (whole parts, checked on the host)
   // Fields that are only needed now and then (a window refill every ~64 K steps, the loss epilogue) are read
   // again from the table entry where they are used instead of occupying scalar registers for the whole
   // tile; the pointer is laundered so that the loads stay where they are written.  Only with dual-sign
@@ -178,7 +190,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     const int wr = wave * 64 + lane;                             // tile row
     const int band = n0 / 64 + wave;                             // band of the sparse layout
     const bool band_ok = band < p.bands;
-    const uint32_t tp_base = (uint32_t)band * (uint32_t)nk;
+    const uint32_t tp_base = (uint32_t)band * (uint32_t)p.ktiles + (uint32_t)k0;
     uint32_t tile_lo = 0, band_end = 0;                          // entry range bookkeeping (uniform)
     uint32_t tp_reg = 0;                                         // lane l: tile_ptr[tp_base + 64*c + 1 + l]
     uint32_t t_lo = 0, t_end = 0;
@@ -208,7 +220,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int r = lane;                                        // row inside the band
-        qrow[i] = p.qweight + (bsafe * (size_t)nk * 64 + (size_t)r) * 32 + 16 * i;
+        qrow[i] = p.qweight + ((bsafe * (size_t)p.ktiles + (size_t)k0) * 64 + (size_t)r) * 32 + 16 * i;
         srow[i] = p.scales + bsafe * (size_t)(p.K >> p.group_shift) * 64 + (size_t)((r & 15) * 4 + (r >> 4));
       }
     }
@@ -221,7 +233,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
       qreg[i] = *reinterpret_cast<global_u32x4>(qrow[i] + (size_t)min(kt, nk - 1) * (64 * BK / 2));
     };
     auto load_s = [&](int kt, int i) {
-      sreg[i] = srow[i][(size_t)((min(kt, nk - 1) * BK + 32 * i) >> p.group_shift) * 64];
+      sreg[i] = srow[i][(size_t)(((k0 + min(kt, nk - 1)) * BK + 32 * i) >> p.group_shift) * 64];
     };
     auto load_w = [&](int kt, int i) { load_q(kt, i); load_s(kt, i); };
 
@@ -579,12 +591,12 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     }  // uniform format
   } else {
     // =============================== activation wave ===========================================
-    const int xt = tid - 64 * W_WAVES;
+    const int xt = 64 * wave + lane - 64 * W_WAVES;
     const int xc = xt & 7, xr = xt >> 3;                       // chunk, row (plus X_ROWS_PER_PASS*u)
     global_u16 xrow[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      xrow[u] = p.x + (size_t)min(m0 + xr + X_ROWS_PER_PASS * u, p.M - 1) * p.K + xc * 8;
+      xrow[u] = p.x + (size_t)min(m0 + xr + X_ROWS_PER_PASS * u, p.M - 1) * p.K + k0 * BK + xc * 8;
     u32x4 xreg[8];
     auto load_x = [&](int kt, int u) {
       xreg[u] = *reinterpret_cast<global_u32x4>(xrow[u] + min(kt, nk - 1) * BK);
@@ -647,6 +659,28 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // squares are formed in fp32, summed over the 16 registers of four MFMA blocks in fp32, and
   // every such partial is added in fp64 (the loss difference of the two passes is ~1e-6 of the
   // loss, far below fp32 resolution of a long sum).
+  // K in two parts: either part keeps half of the row blocks and gets the other's sums of them through the second part's tile
+  // buffers (idle by now).  The first part's sum is added to the second's.
+  constexpr int KB = NA / KS;                     // row blocks of a wave in the epilogue
+  float4_t out[KB][NB];
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) out[i][j] = acc[i][j];
+  } else {
+    float4_t* const given = reinterpret_cast<float4_t*>(smem + tiled_lds_bytes(BM, BN) / 2) + (size_t)wave * (NA * NB * 64) + lane;
+    __syncthreads();                              // every wave is done with the tile buffers
+#pragma unroll
+    for (int i = 0; i < KB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) given[(kpart * KB * NB + i * NB + j) * 64] = kpart ? acc[i][j] : acc[i + KB][j];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) out[i][j] = (kpart ? acc[i + KB][j] : acc[i][j]) + given[((1 - kpart) * KB * NB + i * NB + j) * 64];
+  }
   constexpr int TROW = TN * 2 + 32;               // LDS row stride of the target tile in bytes
   const FwdParams pe = cold();
   bool staged = false;
@@ -654,8 +688,8 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     staged = ((pe.N & 7) == 0) && ((reinterpret_cast<uintptr_t>(pe.target) & 15) == 0);
     if (staged) {
       constexpr int CPR = TN / 8;                 // 16-byte chunks per tile row
-      constexpr int ROWS_PER_PASS = 64 * NWAVES / CPR;
-      uint8_t* const T = reinterpret_cast<uint8_t*>(lds);
+      constexpr int ROWS_PER_PASS = 64 * NWAVES * KS / CPR;
+      uint8_t* const T = reinterpret_cast<uint8_t*>(smem);
       const int c = tid % CPR, r0 = tid / CPR;
       __syncthreads();                            // every wave is done with the tile buffers
       // The loads of a batch are issued before the first one is used: guarded loads in a loop would each
@@ -685,8 +719,8 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // Element (i, j, r) of this lane, r < 16: tile row ml0 + 32 i + 16 (r/8) + r%4, tile column nl0 + 32 j + 16 (r/4 % 2).
   // DUAL: the waves of the second half of a wave row hold the -eps forward of the same columns.
   const int wn_col = DUAL ? wn % (WAVES_N / 2) : wn;
-  const int ml0 = wm * 32 * WMB + 4 * (lane >> 4), nl0 = wn_col * 32 * WNB + (lane & 15);
-  const uint8_t* const trow = reinterpret_cast<const uint8_t*>(lds) + ml0 * TROW + nl0 * 2;
+  const int ml0 = wm * 32 * WMB + 16 * KB * kpart + 4 * (lane >> 4), nl0 = wn_col * 32 * WNB + (lane & 15);
+  const uint8_t* const trow = reinterpret_cast<const uint8_t*>(smem) + ml0 * TROW + nl0 * 2;
   // FULL: whole tile inside the matrix (no bounds checks).  STAGED: targets come from LDS.
   // STORE: y is written.  The three are compile-time so that the common cases are straight code.
   auto finish = [&](auto full_tag, auto staged_tag, auto store_tag) {
@@ -694,7 +728,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
                    STORE = decltype(store_tag)::value;
     const uint32_t ybase = (uint32_t)(m0 + ml0) * (uint32_t)pe.N + (uint32_t)(n0 + nl0);   // M*N < 2^32 checked on the host
 #pragma unroll
-    for (int i = 0; i < WMB; ++i) {
+    for (int i = 0; i < WMB / KS; ++i) {
 #pragma unroll
       for (int j = 0; j < WNB; ++j) {
         float part = 0.0f;
@@ -702,7 +736,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
         for (int r = 0; r < 16; ++r) {
           const int dm = 32 * i + 16 * (r >> 3) + (r & 3), dn = 32 * j + 16 * ((r >> 2) & 1);
           if (FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) {
-            const float v = acc[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
+            const float v = out[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
             const uint32_t off = ybase + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn;
             if (STORE) pe.y[off] = v;
             if (FUSE_LOSS) {
@@ -734,14 +768,14 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   if (FUSE_LOSS) {
     // One scaled partial per workgroup, plain store: a later kernel on the same stream adds them
     // up in index order, so the kernel boundary is the only synchronisation needed.
-    __shared__ double wave_part[NWAVES];
+    __shared__ double wave_part[NWAVES * KS];
     const double w = wave_sum(loss);
-    if (lane == 0) wave_part[wave] = w;
+    if (lane == 0) wave_part[any_wave] = w;
     __syncthreads();
     if (tid == 0) {
       double b = 0.0, b_minus = 0.0;
 #pragma unroll
-      for (int i = 0; i < NWAVES; ++i) {
+      for (int i = 0; i < NWAVES * KS; ++i) {
         if (DUAL && (i % WAVES_N) >= WAVES_N / 2) b_minus += wave_part[i];
         else b += wave_part[i];
       }
@@ -751,11 +785,11 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   }
 }
 
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_kernel(FwdParams p) {
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, int KS>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KS) linear_fwd_kernel(FwdParams p) {
   int bm, bn;
   tile_of_logical(logical_block((int)blockIdx.x, p.grid_m * p.grid_n), p.grid_m, p.grid_n, 4, bm, bn);
-  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT>(p, bm, bn);
+  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, false, KS>(p, bm, bn);
 }
 
 // Grouped launch: every forward of a step (all matrices, both signs) in one grid, so that the only
@@ -843,23 +877,23 @@ static int validate_desc(const szo_linear_desc* d, int sign, bool need_y, bool n
   return SZO_OK;
 }
 
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE, int FMT = SZO_FORMAT_UNIFORM>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE, int FMT = SZO_FORMAT_UNIFORM, int KS = 1>
 static int launch(FwdParams& p, hipStream_t stream) {
   constexpr int BM = 32 * WMB * WAVES_M, BN = 32 * WNB * WAVES_N;
   p.grid_m = (p.M + BM - 1) / BM;
   p.grid_n = (p.N + BN - 1) / BN;
   const int64_t blocks = (int64_t)p.grid_m * p.grid_n;
   if (blocks > 0x7FFFFFFF) return SZO_EUNSUPPORTED;
-  constexpr size_t main_bytes = 2 * (size_t)(BM + BN) * BK * sizeof(uint16_t) + (size_t)(BN / 64) * (kWindow * 6 + 128);
+  constexpr size_t main_bytes = KS * (size_t)tiled_lds_bytes(BM, BN);
   constexpr size_t target_bytes = FUSE ? (size_t)BM * (BN * 2 + 32) : 0;      // staged target tile of the fused loss
   constexpr size_t lds_bytes = main_bytes > target_bytes ? main_bytes : target_bytes;
-  auto kern = linear_fwd_kernel<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE, FMT>;
+  auto kern = linear_fwd_kernel<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE, FMT, KS>;
   static std::atomic<uint64_t> lds_limit_set{0};     // per instantiation
   int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, lds_bytes);
   if (rc != SZO_OK) return rc;
   rc = timing_begin(stream);
   if (rc != SZO_OK) return rc;
-  kern<<<(unsigned)blocks, 64 * WAVES_M * WAVES_N, lds_bytes, stream>>>(p);
+  kern<<<(unsigned)blocks, 64 * WAVES_M * WAVES_N * KS, lds_bytes, stream>>>(p);
   SZO_LAUNCH_CHECK();
   return timing_end(stream);
 }
@@ -883,6 +917,13 @@ template <int DT, bool FUSE>
 static int dispatch_tile(FwdParams& p, hipStream_t stream) {
   int blocks;
   if (plan_tiles(p.M, p.N, SZO_FORMAT_UNIFORM, &blocks) == 2) return launch<2, 4, 4, 2, DT, FUSE>(p, stream);
+  // K in two parts while every tile has a CU to itself: a workgroup of two parts takes a CU's LDS, where two whole tiles would share
+  // it, so from 257 tiles on the parts only take turns.  Both parts walk the same number of K steps, at least two.
+  // us of one forward with 0.1 % sensitive, one part -> two: 4096 x 4096 at 460 / 1000 tokens (128 / 256 tiles) 42.3 / 52.9 -> 35.3 / 41.7
+  // (the first against the few-token path), with 1 % in half of the rows at 450 87.8 -> 53.4, 1024 x 8192 at 3000 99.5 -> 68.8,
+  // 1024 x 512 at 2000 11.5 -> 9.9, 2000 x 256 at 700 8.5 -> 7.7, the seven layers of a Llama block at 600 506 -> 388.
+  if ((g_tile_config == 0 || g_tile_config >= 4) && p.ktiles % 2 == 0 && p.ktiles >= 4 && blocks <= 256)
+    return launch<2, 2, 2, 2, DT, FUSE, SZO_FORMAT_UNIFORM, 2>(p, stream);
   return launch<2, 2, 2, 2, DT, FUSE>(p, stream);
 }
 

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from oracle import layer as olayer, philox as ophilox
+from oracle.quant import bf16_bits_to_f64
 from paper_2406_02913_amd import szo
 from helpers import make_pair, rel_fro
 
@@ -87,6 +88,32 @@ def test_entries_beyond_the_schedule(nnz):
         y = _run(d, +1, 1e-3, 9, 2, dt)
         want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, 32, o.sp_idx, o.sp_val, z, +1, 1e-3, "D", dtname)
         assert rel_fro(y, want) <= tol
+
+
+# 128 x 128 tiles with K in two parts: the shortest K and one above it, both tile types, ragged and half-empty tiles, tiles with more
+# entries than their schedule; 192 columns (an odd number of K steps) and 128 (one step for each part) stay whole
+@pytest.mark.parametrize("M,N,K,G,dens,dt,dtname", [
+    (500, 300, 256, 32, 1e-2, szo.TILE_F16, "f16"), (513, 130, 384, 128, 0.0, szo.TILE_F16, "f16"), (600, 60, 512, 64, 0.2, szo.TILE_F16, "f16"),
+    (2100, 1000, 256, 64, 2e-3, szo.TILE_BF16, "bf16"), (513, 200, 128, 32, 1e-2, szo.TILE_F16, "f16"),
+    (2100, 1000, 192, 32, 1e-2, szo.TILE_F16, "f16")])
+def test_tiles_with_k_in_two_parts(M, N, K, G, dens, dt, dtname):
+    o, d = make_pair(63, M, N, K, G, dens, nnz_base=4)
+    z = ophilox.zbar(9, 2, 4, o.sp_idx.size)
+    ws, loss = szo.new_workspace(), torch.zeros(1, dtype=torch.float64, device="cuda")
+    for sign in (+1, -1):
+        y = _run(d, sign, 1e-3, 9, 2, dt)
+        want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, G, o.sp_idx, o.sp_val, z, sign, 1e-3, "D", dtname)
+        assert rel_fro(y, want) <= 2e-5                            # the bar of the shapes above: K exact products summed in fp32
+        szo.szo_set_tile_config(1)                                 # the same tiles, K whole: other sums exactly where K is cut
+        assert np.array_equal(y, _run(d, sign, 1e-3, 9, 2, dt)) == (K % 128 != 0 or K < 256)
+        szo.szo_set_tile_config(0)
+        loss.zero_()
+        d.y.fill_(float("nan"))
+        szo.szo_linear_fwd_mse(d.desc(dt), 9, 2, sign, 1e-3, 1.0 / (M * N), loss, ws)
+        assert np.array_equal(d.y.cpu().numpy(), y)
+        # the loss of these very outputs: squares and the sums of sixteen of them in fp32 (16 x 2^-24), the rest in fp64
+        err = y.astype(np.float64) - bf16_bits_to_f64(o.target_bits)
+        assert abs(loss.item() / (np.sum(err * err) / (M * N)) - 1.0) <= 18 * 2.0 ** -24
 
 
 def test_perturbation_difference_is_linear_in_z():
