@@ -137,6 +137,20 @@ def test_who_takes_many_tokens_of_few_rows(ask, case, few):
     assert bool(got) == few
 
 
+@pytest.mark.parametrize("case,few", [
+    # single forwards against 128 x 128 tiles with K in two parts, either side of the line: groups, tokens, density, tiles (256 at most), columns
+    (_layer(4096, 4096, 256, 1e-3, group=32, one_sign=1), True), (_layer(4096, 4096, 440, 1e-3, group=32, one_sign=1), False),
+    (_layer(4096, 4096, 440, 1e-3, one_sign=1), True), (_layer(4096, 4096, 440, 1e-3, group=32, lut=1, one_sign=1), True), (_layer(4096, 4096, 440, 1e-3, group=32), True),
+    (_layer(4096, 4096, 64, 1e-2, group=64, one_sign=1), True), (_layer(4096, 4096, 128, 1e-2, group=64, one_sign=1), False), (_layer(4096, 4096, 128, 1e-2, group=64, one_sign=1, bf16=1), True),
+    (_layer(11008, 4096, 64, 1e-3, group=32, one_sign=1), True), (_layer(11008, 4096, 128, 1e-3, group=32, one_sign=1), False),
+    (_layer(16384, 4096, 200, 1e-3, group=64, one_sign=1), False), (_layer(16512, 4096, 200, 1e-3, group=64, one_sign=1), True),
+    (_layer(9359, 512, 69, 1e-3, group=64, one_sign=1), True), (_layer(13245, 256, 43, 1e-2, group=32, one_sign=1), False), (_layer(13245, 128, 43, 1e-2, group=32, one_sign=1), True),
+])
+def test_who_takes_a_single_forward_of_few_tiles(ask, case, few):
+    (got, _, _, _), = ask(case)
+    assert bool(got) == few
+
+
 @pytest.mark.parametrize("case,onepass", [
     # either side of the lines on the mask's density beyond 512 tokens: 1.34 / 4 with the fp16 tile and K a multiple of 128, else 1.22 / 4
     (_layer(2048, 512, 1024, 3.0e-3), True), (_layer(2048, 512, 1024, 3.3e-3), False),
