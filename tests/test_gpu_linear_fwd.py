@@ -95,6 +95,7 @@ def test_entries_beyond_the_schedule(nnz):
 @pytest.mark.parametrize("M,N,K,G,dens,dt,dtname", [
     (500, 300, 256, 32, 1e-2, szo.TILE_F16, "f16"), (513, 130, 384, 128, 0.0, szo.TILE_F16, "f16"), (600, 60, 512, 64, 0.2, szo.TILE_F16, "f16"),
     (2100, 1000, 256, 64, 2e-3, szo.TILE_BF16, "bf16"), (513, 200, 128, 32, 1e-2, szo.TILE_F16, "f16"),
+    (500, 70, 8448, 64, 0.2, szo.TILE_F16, "f16"),                 # 66 tiles of columns per part (tile bounds are loaded 64 at a time)
     (2100, 1000, 192, 32, 1e-2, szo.TILE_F16, "f16")])
 def test_tiles_with_k_in_two_parts(M, N, K, G, dens, dt, dtname):
     o, d = make_pair(63, M, N, K, G, dens, nnz_base=4)
