@@ -65,7 +65,7 @@ extern "C" {
  *   SZO_TILE_BF16 stages the activations unchanged (full bf16 range); the sensitive values are then
  *   rounded to 8 significant bits, which costs about 1-2 % of sigma_g on the SPSA scalar.
  * The kernels round to this type in two ways, and which of them runs a call depends on its sizes, the format, the
- * density of the mask and the entry point:
+ * density of the mask, the entry point and, for single forwards, on whether there is a perturbation:
  *   - as ONE weight tile: dq is rounded, then dq + (v + eps z) and dq + (v - eps z) are (tiled kernel; the
  *     few-token kernels for layers with the bf16 tile or K an odd multiple of 64);
  *   - v and z one by one, eps applied in fp32 (the other few-token launches, the one-dense-pass kernel), which

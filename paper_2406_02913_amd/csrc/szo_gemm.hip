@@ -1228,7 +1228,7 @@ int szo_linear_fwd(const szo_linear_desc* desc, uint64_t seed, uint64_t step, in
   const int rc = validate_desc(desc, sign, true, false);
   if (rc != SZO_OK) return rc;
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
-  if (few_token_enabled() && small_m_eligible(desc, 1, false, false, 1))
+  if (few_token_enabled() && small_m_takes_forward(desc, sign != 0 && eps != 0.0f))
     return small_m_launch_one(desc, seed, step, sign == 0 ? 0.0f : eps, sign == 0 ? 1 : sign, false, false, nullptr, nullptr,
                               kBandsInParts, (hipStream_t)stream);
   return run_forward(desc, seed, step, sign, eps, nullptr, 0.0, (hipStream_t)stream);
@@ -1242,7 +1242,7 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   if (desc->M == 0 || desc->N == 0) return SZO_OK;
   // the few-token kernels compute both signs at once: make the requested one the "+" forward.  Their scale is that of a
   // step's loss, and both signs' partials have to fit.
-  const bool few = few_token_enabled() && small_m_eligible(desc, 1, false, false, 1) && scale == 1.0 / ((double)desc->M * (double)desc->N);
+  const bool few = few_token_enabled() && small_m_takes_forward(desc, sign != 0 && eps != 0.0f) && scale == 1.0 / ((double)desc->M * (double)desc->N);
   const int64_t nb = few ? small_m_launch_partials(desc, kBandsInParts) : 0;
   if (few && 2 * nb <= kMaxLossPartials) {
     rc = small_m_launch_one(desc, seed, step, (float)sign * eps, desc->y ? 1 : 0, true, false, partial_area(workspace),

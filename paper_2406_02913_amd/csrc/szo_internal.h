@@ -51,6 +51,8 @@ int reduce_step(const double* partials, int count, float eps, double* scalars, h
 // single-forward calls (what the tiled kernel would have to do instead).  `separate`: one launch per layer; a step of such
 // launches takes no second activation set.
 bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count, bool separate, int forwards);
+// Whether it takes a single forward (szo_linear_fwd, szo_linear_fwd_mse); `perturbed`: of sign +1 or -1 with eps != 0.
+bool small_m_takes_forward(const szo_linear_desc* d, bool perturbed);
 // Estimated us of a step's forwards where the stream kernel does not take every layer: on the few-token path (`few`) or in the tiled
 // kernel.  Fitted up to 128 tokens and, for single layers, from 129 to 4000.
 double small_m_rounded_us(const szo_linear_desc* descs, int n, bool few, bool separate);

@@ -854,28 +854,32 @@ static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launc
   if (single && !lut && e.split <= e.stream) few = std::max(few, 0.005 * (double)launch.bands16 + 0.0062 * launch.band_k + 0.03 * launch.slice_entries);
   return few < (!single ? 10.0 + 11.8 * launch.longest_k : 5.0 + (lut ? 20.0 : 12.7) * launch.longest_k);
 }
-// A single forward of a layer with groups below 128 against 128 x 128 tiles that compute K in two parts (launches of up to 256 tiles): both
-// round the weights to the tile type.  (With groups of 128 and with tables the few-token kernels do not, and keep the call.)  The tiles take the
-// chain of half of K whatever the number of tokens, 8 % more per 64 tiles beyond 128 and 10 % more at 1 %.  The few-token estimates are as above, the
-// split kernel's at its lower side (0.8..1.2 of it, with dense masks a third more), so that a call moves where the tiles are faster by
-// more than the estimate's spread.  us with 0.1 % / 1 % sensitive, few-token kernels -> tiles: 4096 x 4096 at 256 tokens 33 (34), at 440
-// 52 -> 35; 11008 x 4096 at 64 tokens 26 (30), at 128 43 -> 35; 10241 x 2944 at 269 56 -> 29; 5831 x 3200 at 196 33 -> 28; 3284 x 512 at 354
-// 11.8 -> 9.6; 6140 x 10752 at 189 - / 297 -> 96, 2034 x 1152 at 317 - / 30 -> 14, 13245 x 256 at 43 - / 9.4 -> 6.9; 9359 x 512 at 69 9.0 (9.3).
-// (In brackets: the tiles where the few-token kernels stay.)
-static bool two_part_tiles_win(const szo_linear_desc* d, const LaunchShape& launch) {
-  if (d->format != SZO_FORMAT_UNIFORM || d->group == 128 || d->K % 128 != 0 || d->K < 256 || launch.tiles128 > 256) return false;
+// An unperturbed single forward of a layer with groups below 128 against 128 x 128 tiles that compute K in two parts (launches of up
+// to 256 tiles).  Without a perturbation the tiles round what these few-token launches round, the dequantised weights and v, and either error is the
+// same.  Perturbed forwards stay: the few-token kernels round v and z one by one, the tiles v + eps z, which leaves 14 times the
+// error in y(+) - y(-) (2.1e-4 -> 2.9e-3 of it with v ~ 0.02, eps = 1e-3).  Groups of 128 and tables stay: there the few-token kernels
+// do not round the dequantised weights at all.
+// The tiles take the chain of half of K whatever the number of tokens, 8 % more per 64 tiles beyond 128 and 10 % more at 1 %.
+// The few-token estimates are as above, the split kernel's at its lower side (0.8..1.2 of it, with dense masks a third more), so that a
+// call moves where the tiles are faster by more than the estimate's spread.  us with 0.1 % / 1 % sensitive, few-token kernels -> tiles
+// (in brackets: the tiles where the few-token kernels stay): 4096 x 4096 at 256 tokens 33 (34), at 440 52 -> 35; 11008 x 4096 at 64
+// tokens 26 (30), at 128 43 -> 35; 10241 x 2944 at 269 56 -> 29; 5831 x 3200 at 196 33 -> 28; 3284 x 512 at 354 11.8 -> 9.6; 9359 x
+// 512 at 69 9.0 (9.3); 6140 x 10752 at 189 - / 297 -> 96, 2034 x 1152 at 317 - / 30 -> 14, 13245 x 256 at 43 - / 9.4 -> 6.9.
+static bool two_part_tiles_win(const szo_linear_desc* d) {
+  LaunchShape launch;
+  launch.add(d);
+  if (d->format != SZO_FORMAT_UNIFORM || d->group == 128 || !stream_ok(d) || launch.tiles128 > 256) return false;
   if (g_force_split || g_force_rblocks || g_force_stream_once) return false;                 // testing hooks that name a few-token kernel
   const FewEstimate e = few_estimate(launch, false, false, true);
   const double few = (e.split <= e.stream ? 0.85 * e.split : e.stream + 2.0) * (1.0 + 0.35 * std::max(launch.percent() - 0.1, 0.0));
   const double wide = 1.0 + 0.17 * std::max((double)(launch.tiles128 - 128), 0.0) / 128.0;
-  return (6.0 + 7.2 * launch.longest_k) * wide * (1.0 + 0.1 * launch.percent()) < few;
+  return d->K >= 256 && (6.0 + 7.2 * launch.longest_k) * wide * (1.0 + 0.1 * launch.percent()) < few;
 }
 static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (!stream_ok(d))
     return d->format == SZO_FORMAT_UNIFORM && d->K < kSplitOnlyColumns &&
            (launch.bands16 <= 2304 || d->M <= kSplitOnlyTokens) &&
            (!(d->x_minus && forwards == 2) || d->M <= 128 || launch.bands16 <= kSplitOnlyTwoSets);
-  if (forwards == 1 && two_part_tiles_win(d, launch)) return false;
   if (outruns_the_chain(d, launch, forwards)) return true;
   // two activation sets: a pass holds 16 token rows of each, so it is worth less
   const int64_t slices = (d->M + (d->x_minus ? 15 : 31)) / (d->x_minus ? 16 : 32), tile_rows = (d->M + 255) / 256;
@@ -909,6 +913,9 @@ bool small_m_eligible(const szo_linear_desc* descs, int n, bool any_token_count,
     all_stream = all_stream && stream_ok(d);
   }
   return n > 0 && (all_stream || rounded_us(descs, n, true, forwards, separate) <= rounded_us(descs, n, false, forwards, separate));
+}
+bool small_m_takes_forward(const szo_linear_desc* d, bool perturbed) {
+  return small_m_eligible(d, 1, false, false, 1) && (perturbed || !two_part_tiles_win(d));
 }
 static FewPlan plan_of_one(const szo_linear_desc* d, Partials less) {
   LaunchShape shape;

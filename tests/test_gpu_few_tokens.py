@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from oracle import layer as olayer, philox as ophilox, zo as ozo
+from oracle.quant import bf16_bits_to_f64
 from paper_2406_02913_amd import szo
 from helpers import make_pair, clone, rel_fro, sigma_g, UpdateBound
 
@@ -234,3 +235,38 @@ def test_step_with_up_to_64_tokens_runs_as_slices(cfg):
     assert launches == (6 if cfg == 0 else 9)
     for i, (om, dd, o) in enumerate(zip(ref, ds_, os_)):
         bound.check(i, dd.sp_val.cpu().numpy(), om.sp_val, o.sp_val)
+
+
+@pytest.mark.parametrize("M,N,K,G,dens", [(317, 2034, 1152, 64, 1e-2), (354, 3284, 512, 32, 1e-3)])
+def test_single_forwards_that_tiles_would_take_unperturbed_keep_the_perturbation(M, N, K, G, dens):
+    """Single forwards with small groups, at sizes where an unperturbed one runs in tiles.  Tiles round v + eps z and v - eps z to fp16 as
+    they stand: with v ~ 0.02 and eps = 1e-3 that leaves an error of 2.9e-3 on the difference.  The few-token kernels round v and
+    z one by one: 2^-11 at most on an entry, 2.1e-4 in the norm, and the roundings of v are the same without the perturbation."""
+    eps, steps = 1e-3, 6
+    o, d = make_pair(64, M, N, K, G, dens, nnz_base=4)
+    x, t = bf16_bits_to_f64(o.x_bits), bf16_bits_to_f64(o.target_bits)
+    ws, loss, Z = szo.new_workspace(), torch.zeros(2, dtype=torch.float64, device="cuda"), np.zeros((N, K))
+    y0 = olayer.linear_fwd(o.x_bits, o.codes, o.scales, G, o.sp_idx, o.sp_val)
+
+    def forward(sign, step):
+        d.y.fill_(float("nan"))
+        szo.szo_linear_fwd(d.desc(), 9, step, sign, eps)
+        return d.y.cpu().numpy().astype(np.float64)
+    at_rest, off_g = forward(0, 0), []
+    assert rel_fro(at_rest, y0) <= 1e-3
+    for step in range(steps):
+        Z.reshape(-1)[o.sp_idx.astype(np.int64)] = ophilox.zbar(9, step, 4, o.sp_idx.size)
+        moved = float(np.float32(eps)) * (x @ Z.T)
+        loss.zero_()
+        for i, sign in enumerate((+1, -1)):
+            szo.szo_linear_fwd_mse(d.desc(with_y=False), 9, step, sign, eps, 1.0 / (M * N), loss[i:i + 1], ws)
+        g, want = (loss[0] - loss[1]).item() / (2 * eps), 2.0 * np.sum((y0 - t) * moved) / (M * N * eps)
+        off_g.append((g - want) / sigma_g([o]))
+        if step < 2:
+            plus, minus = forward(+1, step), forward(-1, step)
+            assert rel_fro(plus - minus, 2 * moved) <= 3e-4
+            # against the unperturbed forward the sums over K stand in two orders: sqrt(K) 2^-24 of y at most, here 4e-7, of which
+            # the perturbation is eps sqrt(dens) / 0.02 = 1.6e-3 and more
+            assert rel_fro(plus - at_rest, moved) <= 6e-4
+    # g: 2.1e-4 of its scale from z, as much from the rounded weights in y - t; 2.9e-3 where v and z are rounded together
+    assert float(np.sqrt(np.mean(np.square(off_g)))) <= 1e-3
