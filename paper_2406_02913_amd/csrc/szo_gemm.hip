@@ -917,13 +917,7 @@ template <int DT, bool FUSE>
 static int dispatch_tile(FwdParams& p, hipStream_t stream) {
   int blocks;
   if (plan_tiles(p.M, p.N, SZO_FORMAT_UNIFORM, &blocks) == 2) return launch<2, 4, 4, 2, DT, FUSE>(p, stream);
-  // K in two parts while every tile has a CU to itself: a workgroup of two parts takes a CU's LDS, where two whole tiles would share
-  // it, so from 257 tiles on the parts only take turns.  Both parts walk the same number of K steps,
-  // at least two, three where the tiles nearly fill the chip (2077 x 256 at 1763 tokens, 238 tiles: 10.1 whole, 10.4 in parts; 384 columns 11.5 -> 11.2).
-  // us of one forward with 0.1 % sensitive, one part -> two: 4096 x 4096 at 460 / 1000 tokens (128 / 256 tiles) 42.3 / 52.9 -> 35.3 / 41.7
-  // (the first against the few-token path), with 1 % in half of the rows at 450 87.8 -> 53.4, 1024 x 8192 at 3000 99.5 -> 68.8,
-  // 1024 x 512 at 2000 11.5 -> 9.9, 2000 x 256 at 700 8.5 -> 7.7, the seven layers of a Llama block at 600 506 -> 388.
-  if ((g_tile_config == 0 || g_tile_config >= 4) && p.ktiles % 2 == 0 && p.ktiles >= (blocks <= 192 ? 4 : 6) && blocks <= 256)
+  if ((g_tile_config == 0 || g_tile_config >= 4) && tiles_halve_k(blocks, p.K))
     return launch<2, 2, 2, 2, DT, FUSE, SZO_FORMAT_UNIFORM, 2>(p, stream);
   return launch<2, 2, 2, 2, DT, FUSE>(p, stream);
 }

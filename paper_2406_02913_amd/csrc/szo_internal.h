@@ -45,6 +45,19 @@ int reduce_partials(const double* partials, int count, double scale, double* los
 // scalars[0] = sum partials[0..count), scalars[1] = sum partials[count..2*count), scalars[2] = SPSA g.
 int reduce_step(const double* partials, int count, float eps, double* scalars, hipStream_t stream);
 
+// Whether a launch of 128 x 128 tiles, one forward, computes K in two parts side by side (szo_gemm.hip).  While every tile has a CU to itself: a
+// workgroup of two parts takes a CU's LDS, where two whole tiles would share it, so from 257 tiles on the parts only take turns.  Both
+// parts walk the same number of K steps of 64 columns, at least two; three where the tiles nearly fill the chip, where two gain and lose.
+// us of one forward with 0.1 % sensitive, one part -> two: 4096 x 4096 at 460 / 1000 tokens (128 / 256 tiles) 42.3 / 52.9 -> 35.3 / 41.7
+// (the first against the few-token path), with 1 % in half of the rows at 450 87.8 -> 53.4, 1024 x 8192 at 3000 99.5 -> 68.8,
+// 1024 x 512 at 2000 11.5 -> 9.9, 2000 x 256 at 700 8.5 -> 7.7, the seven layers of a Llama block at 600 506 -> 388.  256 columns: 1536
+// rows at 1500 / 1900 tokens (144 / 180 tiles) 8.8 / 9.2 -> 8.2 / 8.6; beyond the line 2077 at 1763 (238) 10.2 -> 10.3, 2048 at 2048 (256)
+// 9.3 -> 9.5, 1500 at 1900 9.2 -> 9.1, 3200 at 1000 9.2 -> 8.8, 6400 at 500 9.5 -> 8.8; 2077 x 384 at 1763 11.5 -> 11.2.
+constexpr int64_t kTwoPartTiles = 256, kTwoPartColumns = 256;       // most tiles, fewest columns
+inline bool tiles_halve_k(int64_t tiles, int64_t K) {
+  return tiles <= kTwoPartTiles && K % 128 == 0 && K >= (tiles <= 192 ? kTwoPartColumns : 384);
+}
+
 // Few-token path (szo_smallm.hip, szo_split.hip).
 // Whether every layer of a launch is taken: few enough tokens to run as slices of 16 or more token rows, or, with
 // any_token_count, a shape that the stream kernel takes whatever its number of tokens.  `forwards`: 2 for a step, 1 for the

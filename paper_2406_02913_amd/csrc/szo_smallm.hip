@@ -854,8 +854,8 @@ static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launc
   if (single && !lut && e.split <= e.stream) few = std::max(few, 0.005 * (double)launch.bands16 + 0.0062 * launch.band_k + 0.03 * launch.slice_entries);
   return few < (!single ? 10.0 + 11.8 * launch.longest_k : 5.0 + (lut ? 20.0 : 12.7) * launch.longest_k);
 }
-// An unperturbed single forward of a layer with groups below 128 against 128 x 128 tiles that compute K in two parts (launches of up
-// to 256 tiles).  Without a perturbation the tiles round what these few-token launches round, the dequantised weights and v, and either error is the
+// An unperturbed single forward of a layer with groups below 128 against 128 x 128 tiles that compute K in two parts
+// (tiles_halve_k).  Without a perturbation the tiles round what these few-token launches round, the dequantised weights and v, and either error is the
 // same.  Perturbed forwards stay: the few-token kernels round v and z one by one, the tiles v + eps z, which leaves 14 times the
 // error in y(+) - y(-) (2.1e-4 -> 2.9e-3 of it with v ~ 0.02, eps = 1e-3).  Groups of 128 and tables stay: there the few-token kernels
 // do not round the dequantised weights at all.
@@ -865,15 +865,17 @@ static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launc
 // (in brackets: the tiles where the few-token kernels stay): 4096 x 4096 at 256 tokens 33 (34), at 440 52 -> 35; 11008 x 4096 at 64
 // tokens 26 (30), at 128 43 -> 35; 10241 x 2944 at 269 56 -> 29; 5831 x 3200 at 196 33 -> 28; 3284 x 512 at 354 11.8 -> 9.6; 9359 x
 // 512 at 69 9.0 (9.3); 6140 x 10752 at 189 - / 297 -> 96, 2034 x 1152 at 317 - / 30 -> 14, 13245 x 256 at 43 - / 9.4 -> 6.9.
+// (256 columns in 193 to 256 tiles are computed whole, see tiles_halve_k.  The estimate, 9.4 at 1 %, holds for them too: 25000 rows at 43 / 100 /
+// 128 tokens 11.6 / 15.4 / 18.0 -> 8.1 / 9.0 / 9.2, half the entries in 1 % of the rows 19.7 -> 10.4; 6300 at 440 15.5 -> 9.2.)
 static bool two_part_tiles_win(const szo_linear_desc* d) {
   LaunchShape launch;
   launch.add(d);
-  if (d->format != SZO_FORMAT_UNIFORM || d->group == 128 || !stream_ok(d) || launch.tiles128 > 256) return false;
+  if (d->format != SZO_FORMAT_UNIFORM || d->group == 128 || !stream_ok(d) || launch.tiles128 > kTwoPartTiles || d->K < kTwoPartColumns) return false;
   if (g_force_split || g_force_rblocks || g_force_stream_once) return false;                 // testing hooks that name a few-token kernel
   const FewEstimate e = few_estimate(launch, false, false, true);
   const double few = (e.split <= e.stream ? 0.85 * e.split : e.stream + 2.0) * (1.0 + 0.35 * std::max(launch.percent() - 0.1, 0.0));
   const double wide = 1.0 + 0.17 * std::max((double)(launch.tiles128 - 128), 0.0) / 128.0;
-  return d->K >= 256 && (6.0 + 7.2 * launch.longest_k) * wide * (1.0 + 0.1 * launch.percent()) < few;
+  return (6.0 + 7.2 * launch.longest_k) * wide * (1.0 + 0.1 * launch.percent()) < few;
 }
 static bool layer_eligible(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (!stream_ok(d))

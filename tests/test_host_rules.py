@@ -19,7 +19,10 @@ static SplitLaunch g_last;
 namespace szo { int split_launch(const SplitLaunch& l, const SmallArgs&, hipStream_t) { g_last = l; return SZO_OK; } }
 // a line: layers, token rows, N, K, group, entries, bf16, table format, two sets, one sign (2: unperturbed), separate launches, asked for,
 // K of one more layer
-int main() {
+// with the argument "parts": tiles, columns -> whether K is computed in two parts
+int main(int argc, char**) {
+  long long tiles, columns;
+  while (argc > 1 && scanf("%lld %lld", &tiles, &columns) == 2) printf("%d\n", tiles_halve_k(tiles, columns));
   long long n, M, N, K, group, nnz, bf16, lut, two, one, separate, asked, tail;
   while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld", &n, &M, &N, &K, &group, &nnz, &bf16, &lut, &two, &one, &separate, &asked, &tail) == 13) {
     szo_linear_desc d{};
@@ -68,6 +71,7 @@ def ask(tmp_path_factory):
         lines = "\n".join(" ".join(str(int(c.get(k, 0))) for k in keys) for c in cases)
         out = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split("\n")
         return [tuple(int(v) for v in line.split()) for line in out[:len(cases)]]
+    run.exe = exe
     return run
 
 
@@ -146,6 +150,9 @@ def test_who_takes_many_tokens_of_few_rows(ask, case, few):
     (_layer(16384, 4096, 200, 1e-3, group=64, one_sign=2), False), (_layer(16512, 4096, 200, 1e-3, group=64, one_sign=2), True),
     (_layer(9359, 512, 69, 1e-3, group=64, one_sign=2), True), (_layer(13245, 256, 43, 1e-2, group=32, one_sign=2), False), (_layer(13245, 128, 43, 1e-2, group=32, one_sign=2), True),
     (_layer(2034, 1152, 317, 1e-2, group=64, one_sign=2), False), (_layer(3284, 512, 354, 1e-3, group=32, one_sign=2), False),
+    # 256 columns: cut up to 192 tiles, whole beyond, few-token kernels beyond 256
+    (_layer(24500, 256, 43, 1e-2, group=64, one_sign=2), False), (_layer(25000, 256, 43, 1e-2, group=64, one_sign=2), False), (_layer(25000, 256, 100, 5e-3, group=64, one_sign=2), True),
+    (_layer(32768, 256, 100, 1e-2, group=64, one_sign=2), False), (_layer(32769, 256, 100, 1e-2, group=64, one_sign=2), True),
     # perturbed forwards stay where v and z are rounded one by one
     (_layer(3284, 512, 354, 1e-3, group=32, one_sign=1), True),
     (_layer(4096, 4096, 440, 1e-3, group=32, one_sign=1), True), (_layer(4096, 4096, 128, 1e-2, group=64, one_sign=1), True), (_layer(11008, 4096, 128, 1e-3, group=32, one_sign=1), True),
@@ -154,6 +161,12 @@ def test_who_takes_many_tokens_of_few_rows(ask, case, few):
 def test_who_takes_a_single_forward_of_few_tiles(ask, case, few):
     (got, _, _, _), = ask(case)
     assert bool(got) == few
+
+
+def test_where_tiles_compute_k_in_two_parts(ask):
+    cases = {(192, 256): 1, (193, 256): 0, (193, 384): 1, (256, 384): 1, (257, 384): 0, (1, 128): 0, (1, 192): 0, (1, 320): 0, (1, 256): 1, (1, 448): 0, (256, 16384): 1, (257, 16384): 0}
+    out = subprocess.run([ask.exe, "parts"], input="\n".join("%d %d" % c for c in cases), capture_output=True, text=True, check=True).stdout
+    assert [int(v) for v in out.split()] == list(cases.values())
 
 
 @pytest.mark.parametrize("case,onepass", [
