@@ -44,7 +44,7 @@ constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int
 
 // Workgroup = WAVES_M x WAVES_N waves; each wave computes (32*WMB) x (32*WNB) outputs.
 //
-// Schedule of one K step of one wave.  The wave issues SLOTS = 4*WMB*WNB pairs of MFMAs.  Its staging
+// Schedule of one K step of one wave.  The wave issues SLOTS = 4*WMB*WNB pairs of 16x16x32 MFMAs (or as many 32x32x16).  Its staging
 // work for the NEXT tile (8 units per lane: 16-byte chunks of x, or 32-bit words of codes) is
 // cut into SLOTS slices of three to four VALU instructions, and one slice is issued behind
 // each pair of MFMAs, where it executes in the shadow of the matrix pipeline.  The LDS reads of
@@ -63,7 +63,9 @@ constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int
 // buffers of their own.  Such a launch is bound by a weight wave's chain, ~220 instructions per K step at one wave on its SIMD
 // (which issues one every ~6 cycles); with two waves per SIMD half as many steps stand one behind the other.  Either half keeps
 // the sums of half of the tile's rows.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1>
+//
+// BLK: the matrix instruction, 16x16x32 or 32x32x16 (see below).  GROUPED: a grouped launch, which never writes y.
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1, int BLK = 16, bool GROUPED = false>
 __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm, const int bn,
                                                 const uint32_t __attribute__((address_space(4)))* entry = nullptr) {
   constexpr int NWAVES = WAVES_M * WAVES_N;
@@ -75,7 +77,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   static_assert(BN % 64 == 0 && X_WAVES > 0, "need whole bands and at least one activation wave");
   constexpr int X_ROWS_PER_PASS = 8 * X_WAVES;     // 8 lanes cover one 128-byte row of x
   static_assert(BM == 8 * X_ROWS_PER_PASS, "every activation lane stages 8 chunks per tile");
-  constexpr int SLOTS = 4 * WMB * WNB;             // pairs of MFMAs per K step
+  constexpr int SLOTS = 4 * WMB * WNB;             // pairs of 16x16x32 MFMAs per K step
   constexpr int SPU = SLOTS / 8;                   // slots per activation staging unit: 1, 2 or 4
   constexpr int WPS = 4 / SPU;                     // output words produced per slot
   // Weight waves finish their dense staging in the first three quarters of the slots (32 slots: 3 per unit; 16 slots: 3 per
@@ -120,49 +122,56 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // Blocks of 16 x 16 outputs.  At the sizes that fill the chip this kernel runs at the chip's power limit, and 16x16x32 takes
   // less power per product than 32x32x16 (half the accumulator traffic): a bare loop with the kernel's operands, operand reads
   // and four vector instructions per 32 768 FLOP reaches 1566 against 1411 TFLOP/s, and the step over four Llama blocks
-  // runs at 1.86 GHz instead of 1.69 for 5 % more cycles.  us, 32x32x16 -> 16x16x32: two Llama blocks at 4096 tokens 5358 -> 5120, with the bf16 tile 5528 -> 5212, with tables 5880 -> 5685; one Mistral block
-  // at 8192 and 1 % 6148 -> 5836; two of them with two sets of activations at 333 701 -> 661; a 4096 x 4096 composed step at 2000 176 ->
-  // 167.  Where a tile has a CU to itself nothing changes (six forwards of a Llama block at 600 tokens 490 -> 494).
+  // runs at 1.86 GHz instead of 1.69 for 5 % more cycles.  us, 32x32x16 -> 16x16x32: two Llama blocks at 4096 tokens 5358 -> 5120, with
+  // the bf16 tile 5528 -> 5212, with tables 5880 -> 5685; one Mistral block at 8192 and 1 % 6148 -> 5836; two of them with two sets of
+  // activations at 333 701 -> 661; a 4096 x 4096 composed step at 2000 176 -> 167.
+  // Blocks of 32 x 32: half as many instructions, for launches of 128 x 128 tiles that are bound by a weight wave's
+  // instructions and not by power (see wide_blocks).
   // RING operands of x are held at a time, each re-read for a later row of blocks as soon as its own has been issued: three are
-  // what the registers of the 32-slot schedule allow, four hide more where one wave has a SIMD to itself (501 -> 494 above).
-  constexpr int NA = 2 * WMB, NB = 2 * WNB, RING = SLOTS == 32 ? 3 : 4;
-  float4_t acc[NA][NB];
+  // what the registers of the 32-slot schedule allow, four hide more where one wave has a SIMD to itself (six forwards of a Llama block
+  // at 600 tokens 501 -> 494).
+  static_assert(BLK == 16 || (BLK == 32 && SLOTS == 16 && KS == 1 && !DUAL), "32 x 32: whole small tiles");
+  constexpr int NA = 32 * WMB / BLK, NB = 32 * WNB / BLK, KSTEPS = BLK / 8, LANE_SHIFT = BLK == 16 ? 4 : 5, RING = SLOTS == 32 ? 3 : 4;
+  typedef typename std::conditional<BLK == 16, float4_t, float16_t>::type acc_t;
+  acc_t acc[NA][NB];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+      for (int r = 0; r < BLK * BLK / 64; ++r) acc[i][j][r] = 0.0f;
 
-  // Lane l of an operand holds row l % 16 of its block, columns 8 (l / 16) .. of a 32-column step: a chunk of the staged row.
-  const int fragA_row = wm * 32 * WMB + (lane & 15), fragB_row = wn * 32 * WNB + (lane & 15);
+  // Lane l of an operand holds row l % BLK of its block, columns 8 (l / BLK) .. of a step: a chunk of the staged row.
+  const int fragA_row = wm * 32 * WMB + (lane & (BLK - 1)), fragB_row = wn * 32 * WNB + (lane & (BLK - 1));
   auto read_a = [&](int buf, int ks, int i) -> frag_t {
-    return *reinterpret_cast<const frag_t*>(ldsA + buf * BM * BK + chunk_off(fragA_row, 4 * ks + (lane >> 4)) + 16 * i * BK);
+    return *reinterpret_cast<const frag_t*>(ldsA + buf * BM * BK + chunk_off(fragA_row, 64 / BLK * ks + (lane >> LANE_SHIFT)) + BLK * i * BK);
   };
   auto read_b = [&](int buf, int ks, int j) -> frag_t {
-    return *reinterpret_cast<const frag_t*>(ldsB + buf * BN * BK + chunk_off(fragB_row, 4 * ks + (lane >> 4)) + 16 * j * BK);
+    return *reinterpret_cast<const frag_t*>(ldsB + buf * BN * BK + chunk_off(fragB_row, 64 / BLK * ks + (lane >> LANE_SHIFT)) + BLK * j * BK);
   };
 
-  // All MFMAs of one K step on buffer buf, with slice(s) issued behind every second one.
+  // All MFMAs of one K step on buffer buf, with slice(s) issued behind every second one (32 x 32: behind each).
   auto run_tile = [&](int buf, auto&& slice) {
+    constexpr int PER_SLOT = BLK == 16 ? 2 : 1;
     frag_t a[RING], b[2][NB];
     a[0] = read_a(buf, 0, 0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) b[0][j] = read_b(buf, 0, j);
 #pragma unroll
-    for (int i = 1; i < RING; ++i) a[i] = read_a(buf, 0, i);
+    for (int i = 1; i < RING; ++i) a[i] = read_a(buf, i / NA, i % NA);
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int ks = 0; ks < KSTEPS; ++ks) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          acc[i][j] = Frag<DT>::mfma16(a[(ks * NA + i) % RING], b[ks][j], acc[i][j]);
-          if (ks == 0 && i == NA / 2) b[1][j] = read_b(buf, 1, j);
-          if (j == NB - 1 && ks * NA + i + RING < 2 * NA) a[(ks * NA + i) % RING] = read_a(buf, (ks * NA + i + RING) / NA, (ks * NA + i + RING) % NA);
-          const int m = (ks * NA + i) * NB + j;
-          if (m & 1) {
-            slice(m >> 1);
+          const int at = ks * NA + i, m = at * NB + j;
+          if constexpr (BLK == 16) acc[i][j] = Frag<DT>::mfma16(a[at % RING], b[ks & 1][j], acc[i][j]);
+          else acc[i][j] = Frag<DT>::mfma(a[at % RING], b[ks & 1][j], acc[i][j]);
+          if (ks + 1 < KSTEPS && i == (BLK == 16 ? NA / 2 : 0)) b[(ks + 1) & 1][j] = read_b(buf, ks + 1, j);
+          if (j == NB - 1 && at + RING < KSTEPS * NA) a[at % RING] = read_a(buf, (at + RING) / NA, (at + RING) % NA);
+          if (m % PER_SLOT == PER_SLOT - 1) {
+            slice(m / PER_SLOT);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -652,34 +661,44 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     }
   }
 
-  // ---- epilogue: accumulator (i,j) register r holds
-  //      row  16*i + 4*(lane/16) + r ,  column 16*j + lane%16  of the wave tile ----
+  // ---- epilogue: in quads, of four rows in one column for each lane.  Register r of quad (i,j) of a wave tile holds
+  //      row  16*i + 4*(lane/16) + r ,  column 16*j + lane%16  (blocks of 32 x 32: row 32*(i/2) + 8*(2*(i%2) + j%2) + 4*(lane/32) + r,
+  //      column 32*(j/2) + lane%32) ----
   // Fused loss: the bf16 target tile is first copied into the (now idle) LDS tile buffers with
   // coalesced 16-byte loads, then every lane picks its own elements from LDS.  Differences and
-  // squares are formed in fp32, summed over the 16 registers of four MFMA blocks in fp32, and
+  // squares are formed in fp32, summed over the 16 registers of four quads in fp32, and
   // every such partial is added in fp64 (the loss difference of the two passes is ~1e-6 of the
   // loss, far below fp32 resolution of a long sum).
   // K in two parts: either part keeps half of the row blocks and gets the other's sums of them through the second part's tile
   // buffers (idle by now).  The first part's sum is added to the second's.
-  constexpr int KB = NA / KS;                     // row blocks of a wave in the epilogue
-  float4_t out[KB][NB];
+  constexpr int QM = 2 * WMB, QN = 2 * WNB, KB = QM / KS;       // quads of a wave; KB: its rows of them in the epilogue
+  auto quad = [&](int i, int j) {
+    if constexpr (BLK == 16) {
+      return acc[i][j];
+    } else {
+      const float16_t b = acc[i / 2][j / 2];
+      const int r = 8 * (i % 2) + 4 * (j % 2);
+      return float4_t{b[r], b[r + 1], b[r + 2], b[r + 3]};
+    }
+  };
+  float4_t out[KB][QN];
   if constexpr (KS == 1) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+    for (int i = 0; i < KB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) out[i][j] = acc[i][j];
+      for (int j = 0; j < QN; ++j) out[i][j] = quad(i, j);
   } else {
-    float4_t* const given = reinterpret_cast<float4_t*>(smem + tiled_lds_bytes(BM, BN) / 2) + (size_t)wave * (NA * NB * 64) + lane;
+    float4_t* const given = reinterpret_cast<float4_t*>(smem + tiled_lds_bytes(BM, BN) / 2) + (size_t)wave * (QM * QN * 64) + lane;
     __syncthreads();                              // every wave is done with the tile buffers
 #pragma unroll
     for (int i = 0; i < KB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) given[(kpart * KB * NB + i * NB + j) * 64] = kpart ? acc[i][j] : acc[i + KB][j];
+      for (int j = 0; j < QN; ++j) given[(kpart * KB * QN + i * QN + j) * 64] = kpart ? quad(i, j) : quad(i + KB, j);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < KB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) out[i][j] = (kpart ? acc[i + KB][j] : acc[i][j]) + given[((1 - kpart) * KB * NB + i * NB + j) * 64];
+      for (int j = 0; j < QN; ++j) out[i][j] = (kpart ? quad(i + KB, j) : quad(i, j)) + given[((1 - kpart) * KB * QN + i * QN + j) * 64];
   }
   constexpr int TROW = TN * 2 + 32;               // LDS row stride of the target tile in bytes
   const FwdParams pe = cold();
@@ -716,10 +735,13 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     }
   }
   double loss = 0.0;
-  // Element (i, j, r) of this lane, r < 16: tile row ml0 + 32 i + 16 (r/8) + r%4, tile column nl0 + 32 j + 16 (r/4 % 2).
+  // Element (i, j, r) of this lane, r < 16: register r%4 of quad (2 i + r/8, 2 j + r/4 % 2), tile row ml0 + row_of(i, r), tile column
+  // nl0 + column_of(j, r).
   // DUAL: the waves of the second half of a wave row hold the -eps forward of the same columns.
   const int wn_col = DUAL ? wn % (WAVES_N / 2) : wn;
-  const int ml0 = wm * 32 * WMB + 16 * KB * kpart + 4 * (lane >> 4), nl0 = wn_col * 32 * WNB + (lane & 15);
+  const int ml0 = wm * 32 * WMB + 16 * KB * kpart + 4 * (lane >> LANE_SHIFT), nl0 = wn_col * 32 * WNB + (lane & (BLK - 1));
+  auto row_of = [](int i, int r) { return 32 * i + (BLK == 16 ? 16 * (r >> 3) : 8 * (r >> 2)) + (r & 3); };
+  auto column_of = [](int j, int r) { return 32 * j + (BLK == 16 ? 16 * ((r >> 2) & 1) : 0); };
   const uint8_t* const trow = reinterpret_cast<const uint8_t*>(smem) + ml0 * TROW + nl0 * 2;
   // FULL: whole tile inside the matrix (no bounds checks).  STAGED: targets come from LDS.
   // STORE: y is written.  The three are compile-time so that the common cases are straight code.
@@ -734,7 +756,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
         float part = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int dm = 32 * i + 16 * (r >> 3) + (r & 3), dn = 32 * j + 16 * ((r >> 2) & 1);
+          const int dm = row_of(i, r), dn = column_of(j, r);
           if (FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) {
             const float v = out[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
             const uint32_t off = ybase + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn;
@@ -756,8 +778,12 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     using T = std::true_type;
     using F = std::false_type;
     const bool full = m0 + BM <= pe.M && n0 + TN <= pe.N;
-    if (FUSE_LOSS) {
-      if (full && staged && !pe.y) finish(T{}, T{}, F{});            // the step's path
+    if constexpr (GROUPED) {
+      if (full && staged) finish(T{}, T{}, F{});
+      else if (staged) finish(F{}, T{}, F{});
+      else finish(F{}, F{}, F{});
+    } else if (FUSE_LOSS) {
+      if (full && staged && !pe.y) finish(T{}, T{}, F{});          // the step's path
       else if (staged) { if (pe.y) finish(F{}, T{}, T{}); else finish(F{}, T{}, F{}); }
       else { if (pe.y) finish(F{}, F{}, T{}); else finish(F{}, F{}, F{}); }
     } else {
@@ -785,11 +811,11 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   }
 }
 
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, int KS>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, int KS, int BLK>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KS) linear_fwd_kernel(FwdParams p) {
   int bm, bn;
   tile_of_logical(logical_block((int)blockIdx.x, p.grid_m * p.grid_n), p.grid_m, p.grid_n, 4, bm, bn);
-  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, false, KS>(p, bm, bn);
+  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, false, KS, BLK>(p, bm, bn);
 }
 
 // Grouped launch: every forward of a step (all matrices, both signs) in one grid, so that the only
@@ -803,7 +829,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KS) linear_fwd_kernel
 // again later.  Workgroups between an entry's last tile and the next multiple of 8 have nothing to do.
 // With DUAL an entry has grid_m * grid_n workgroups, each computing both forwards of a tile of half the
 // width (see linear_fwd_body); the 32 workgroups resident on an XCD are then 2 x 16 such tiles.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int BLK = 16>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kernel(const FwdParams* table, int n_entries, InlineForwards) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
   static_assert(sizeof(FwdParams) % 4 == 0 && offsetof(FwdParams, first_block) % 4 == 0, "table entry is read as words");
@@ -831,12 +857,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kerne
       p.signed_eps = -p.signed_eps;
     }
   }
-  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, DUAL>(p, bm, bn, tab + lo * W);
+  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, DUAL, 1, BLK, true>(p, bm, bn, tab + lo * W);
 }
 
 // ---- host side -----------------------------------------------------------------------------
 
-static int g_tile_config = 0;      // 0 = choose by shape, 1 = 128x128 (4 waves), 2 = 256x256 (8 waves), 3 = 2 + always group the step,
+static int g_tile_config = 0;      // 0 = choose by shape, 1 = 128x128 (4 waves, K whole, the blocks of the grouped launch), 2 = 256x256 (8 waves), 3 = 2 + always group the step,
                                    // 4, 5 = as 0 with the few-token path's 32- / 48-row passes forced (see small_m_force_rblocks),
                                    // 6 = as 0 + always group the step, 7 = as 0 + non-temporal code stream in every one-slice launch,
                                    // 8, 9 = as 0 with the few-token path's split kernel always / never chosen, 10 = 9 and 7,
@@ -877,7 +903,7 @@ static int validate_desc(const szo_linear_desc* d, int sign, bool need_y, bool n
   return SZO_OK;
 }
 
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE, int FMT = SZO_FORMAT_UNIFORM, int KS = 1>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE, int FMT = SZO_FORMAT_UNIFORM, int KS = 1, int BLK = 16>
 static int launch(FwdParams& p, hipStream_t stream) {
   constexpr int BM = 32 * WMB * WAVES_M, BN = 32 * WNB * WAVES_N;
   p.grid_m = (p.M + BM - 1) / BM;
@@ -887,7 +913,7 @@ static int launch(FwdParams& p, hipStream_t stream) {
   constexpr size_t main_bytes = KS * (size_t)tiled_lds_bytes(BM, BN);
   constexpr size_t target_bytes = FUSE ? (size_t)BM * (BN * 2 + 32) : 0;      // staged target tile of the fused loss
   constexpr size_t lds_bytes = main_bytes > target_bytes ? main_bytes : target_bytes;
-  auto kern = linear_fwd_kernel<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE, FMT, KS>;
+  auto kern = linear_fwd_kernel<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE, FMT, KS, BLK>;
   static std::atomic<uint64_t> lds_limit_set{0};     // per instantiation
   int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, lds_bytes);
   if (rc != SZO_OK) return rc;
@@ -913,13 +939,25 @@ static int plan_tiles(int M, int N, int format, int* blocks_out) {
   return cfg;
 }
 
+// 128 x 128 tiles, K whole: blocks of 32 x 32, half as many matrix instructions, where a weight wave's instructions bound the launch, of
+// 16 x 16 where power does.  With the bf16 tile, whose dequantisation is longest, always.  With the fp16 tile while few CUs have more than one
+// tile, and a little further with denser masks.  us, 16x16x32 -> 32x32x16: bf16 forwards of 8192 x 8192 at 700 tokens 181.5 -> 173.9, 4096 x 4096 at
+// 1280 / 2000 93.4 / 94.9 -> 88.7 / 93.4, a step over 8192 x 4096 at 700 and 0.8 % 218 -> 210; fp16 forwards of 4096 x 4096 at 1100 / 1280 (288 / 320
+// tiles) 69.0 / 68.7 -> 66.7 / 67.0, 4096 x 11008 at 1200 174.9 -> 168.0, 4096 x 4160 at 500 (128 tiles) 51.9 -> 50.4; beyond the line 4096 x 4096 at
+// 1400 (352) 69.4 -> 70.4 and 69.8 -> 68.9 on two boxes, at 1500 / 2000 (384 / 512) 70.2 / 77.7 -> 70.7 / 81.2; with 0.3 / 0.5 / 1 % at 1500 72.0 /
+// 73.0 / 77.3 -> 71.4 / 72.2 / 75.6, a step over 8192 x 8192 at 700 and 0.5 % 301 -> 290.
+static bool wide_blocks(int tiles, const FwdParams& p) {
+  return tiles <= 320 || (tiles <= 384 && 250ll * p.nnz >= (int64_t)p.N * p.K);
+}
+
 template <int DT, bool FUSE>
 static int dispatch_tile(FwdParams& p, hipStream_t stream) {
   int blocks;
   if (plan_tiles(p.M, p.N, SZO_FORMAT_UNIFORM, &blocks) == 2) return launch<2, 4, 4, 2, DT, FUSE>(p, stream);
-  if ((g_tile_config == 0 || g_tile_config >= 4) && tiles_halve_k(blocks, p.K))
-    return launch<2, 2, 2, 2, DT, FUSE, SZO_FORMAT_UNIFORM, 2>(p, stream);
-  return launch<2, 2, 2, 2, DT, FUSE>(p, stream);
+  const bool chosen = g_tile_config == 0 || g_tile_config >= 4;
+  if (chosen && tiles_halve_k(blocks, p.K)) return launch<2, 2, 2, 2, DT, FUSE, SZO_FORMAT_UNIFORM, 2>(p, stream);
+  if (DT == SZO_TILE_BF16 || (chosen && wide_blocks(blocks, p))) return launch<2, 2, 2, 2, DT, FUSE, SZO_FORMAT_UNIFORM, 1, 32>(p, stream);
+  return launch<2, 2, 2, 2, SZO_TILE_F16, FUSE>(p, stream);
 }
 
 // Enqueues one forward.  With `partials` set the loss is fused: workgroup b stores
@@ -1001,7 +1039,8 @@ static int launch_table(const ForwardTableArgs& t, int64_t blocks, hipStream_t s
   constexpr size_t main_bytes = 2 * (size_t)(BM + BN) * BK * sizeof(uint16_t) + (size_t)(BN / 64) * (kWindow * 6 + 128);
   constexpr size_t target_bytes = (size_t)BM * (BN * 2 + 32);
   constexpr size_t lds_bytes = main_bytes > target_bytes ? main_bytes : target_bytes;
-  auto kern = linear_fwd_table_kernel<2, WAVES_N, WMB, 2, DT, true, FMT, DUAL>;
+  constexpr int BLK = TILE == 128 && DT == SZO_TILE_BF16 ? 32 : 16;            // as in dispatch_tile
+  auto kern = linear_fwd_table_kernel<2, WAVES_N, WMB, 2, DT, true, FMT, DUAL, BLK>;
   static std::atomic<uint64_t> lds_limit_set{0};
   int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, lds_bytes);
   if (rc != SZO_OK) return rc;

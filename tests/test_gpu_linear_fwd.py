@@ -117,6 +117,29 @@ def test_tiles_with_k_in_two_parts(M, N, K, G, dens, dt, dtname):
         assert abs(loss.item() / (np.sum(err * err) / (M * N)) - 1.0) <= 18 * 2.0 ** -24
 
 
+# 128 x 128 tiles with K whole, the library choosing: blocks of 32 x 32 (fp16: up to 320 tiles, 384 with denser masks; bf16), blocks of 16 x
+# 16 beyond; ragged tiles, half-empty ones, tiles with more entries than their schedule; targets staged (rows of 16 bytes) and not
+@pytest.mark.parametrize("M,N,K,G,dens,dt,dtname", [
+    (2100, 2400, 192, 64, 2e-3, szo.TILE_F16, "f16"), (2100, 2608, 192, 32, 2e-3, szo.TILE_F16, "f16"), (2100, 2608, 192, 32, 1e-2, szo.TILE_F16, "f16"),
+    (2100, 2608, 192, 32, 2e-3, szo.TILE_BF16, "bf16"), (500, 300, 448, 64, 0.2, szo.TILE_F16, "f16"), (513, 130, 64, 32, 0.2, szo.TILE_BF16, "bf16"),
+    (1100, 70, 4160, 64, 0.1, szo.TILE_F16, "f16")])
+def test_whole_small_tiles(M, N, K, G, dens, dt, dtname):
+    o, d = make_pair(65, M, N, K, G, dens, nnz_base=4)
+    z = ophilox.zbar(9, 2, 4, o.sp_idx.size)
+    ws, loss = szo.new_workspace(), torch.zeros(2, dtype=torch.float64, device="cuda")
+    for sign in (+1, -1):
+        y = _run(d, sign, 1e-3, 9, 2, dt)
+        want = olayer.linear_fwd(o.x_bits, o.codes, o.scales, G, o.sp_idx, o.sp_val, z, sign, 1e-3, "D", dtname)
+        assert rel_fro(y, want) <= 2e-5
+        loss.zero_()
+        d.y.fill_(float("nan"))
+        szo.szo_linear_fwd_mse(d.desc(dt), 9, 2, sign, 1e-3, 1.0 / (M * N), loss[:1], ws)
+        szo.szo_linear_fwd_mse(d.desc(dt, with_y=False), 9, 2, sign, 1e-3, 1.0 / (M * N), loss[1:], ws)
+        assert np.array_equal(d.y.cpu().numpy(), y) and loss[0].item() == loss[1].item()
+        err = y.astype(np.float64) - bf16_bits_to_f64(o.target_bits)     # squares and the sums of sixteen of them in fp32, the rest in fp64
+        assert abs(loss[0].item() / (np.sum(err * err) / (M * N)) - 1.0) <= 18 * 2.0 ** -24
+
+
 def test_perturbation_difference_is_linear_in_z():
     # y(+) - y(-) = 2 eps x Z^T: checks the sign convention and that only masked entries move
     o, d = make_pair(7, 96, 256, 256, 32, 5e-3)
