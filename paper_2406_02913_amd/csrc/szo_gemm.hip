@@ -739,16 +739,41 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // nl0 + column_of(j, r).
   // DUAL: the waves of the second half of a wave row hold the -eps forward of the same columns.
   const int wn_col = DUAL ? wn % (WAVES_N / 2) : wn;
-  const int ml0 = wm * 32 * WMB + 16 * KB * kpart + 4 * (lane >> LANE_SHIFT), nl0 = wn_col * 32 * WNB + (lane & (BLK - 1));
+  const int mw = wm * 32 * WMB + 16 * KB * kpart, nw = wn_col * 32 * WNB, ml0 = mw + 4 * (lane >> LANE_SHIFT), nl0 = nw + (lane & (BLK - 1));
   auto row_of = [](int i, int r) { return 32 * i + (BLK == 16 ? 16 * (r >> 3) : 8 * (r >> 2)) + (r & 3); };
   auto column_of = [](int j, int r) { return 32 * j + (BLK == 16 ? 16 * ((r >> 2) & 1) : 0); };
   const uint8_t* const trow = reinterpret_cast<const uint8_t*>(smem) + ml0 * TROW + nl0 * 2;
+  // A quad's rows of y are pieces of 16 elements.  Where rows begin at odd multiples of four or eight bytes a piece shares its first and
+  // last sector of memory with its neighbours, and two quads side by side trade rows first, so that an instruction writes two rows of 32
+  // elements and not four of 16.  us of a forward, four rows -> two: 2077 x 256 at 1763 tokens 10.2 -> 9.7, 4097 x 256 at 4000 29.5 -> 28.3,
+  // 16381 x 640 at 4000 111 -> 105, 11009 x 1024 at 8000 233 -> 219.  With rows at multiples of 16 bytes the trade costs: 4100 x 256 at 4000
+  // 28.3 -> 28.6, 4104 x 256 28.6 -> 29.3, 4096 x 1024 at 1280 22.4 -> 22.8.
+  enum { NO_Y, QUAD_ROWS, TRADED_ROWS };
+  const bool trade = BLK == 16 && ((pe.N & 3) != 0 || (reinterpret_cast<uintptr_t>(pe.y) & 15) != 0);
   // FULL: whole tile inside the matrix (no bounds checks).  STAGED: targets come from LDS.
-  // STORE: y is written.  The three are compile-time so that the common cases are straight code.
+  // STORE: how y is written.  The three are compile-time so that the common cases are straight code.
   auto finish = [&](auto full_tag, auto staged_tag, auto store_tag) {
-    constexpr bool FULL = decltype(full_tag)::value, STAGED = decltype(staged_tag)::value,
-                   STORE = decltype(store_tag)::value;
+    constexpr bool FULL = decltype(full_tag)::value, STAGED = decltype(staged_tag)::value;
+    constexpr int STORE = decltype(store_tag)::value;
     const uint32_t ybase = (uint32_t)(m0 + ml0) * (uint32_t)pe.N + (uint32_t)(n0 + nl0);   // M*N < 2^32 checked on the host
+    if constexpr (STORE == TRADED_ROWS) {
+      // register h of a traded pair: row 16*i + 8*(lane/32) + 4*h + r, column 32*j + lane%32
+      const int mt = m0 + mw + 8 * (lane >> 5), nt = n0 + nw + (lane & 31);
+      const uint32_t tbase = (uint32_t)mt * (uint32_t)pe.N + (uint32_t)nt;
+#pragma unroll
+      for (int i = 0; i < KB; ++i)
+#pragma unroll
+        for (int j = 0; j < WNB; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(out[i][2 * j][r]), __float_as_uint(out[i][2 * j + 1][r]), false, false);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const int dm = 16 * i + 4 * h + r, dn = 32 * j;
+              if (FULL || (mt + dm < pe.M && nt + dn < pe.N)) pe.y[tbase + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn] = __uint_as_float(rows[h]);
+            }
+          }
+    }
 #pragma unroll
     for (int i = 0; i < WMB / KS; ++i) {
 #pragma unroll
@@ -760,7 +785,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
           if (FULL || (m0 + ml0 + dm < pe.M && n0 + nl0 + dn < pe.N)) {
             const float v = out[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
             const uint32_t off = ybase + (uint32_t)dm * (uint32_t)pe.N + (uint32_t)dn;
-            if (STORE) pe.y[off] = v;
+            if (STORE == QUAD_ROWS) pe.y[off] = v;
             if (FUSE_LOSS) {
               uint32_t tb;
               if (STAGED) tb = *reinterpret_cast<const uint16_t*>(trow + dm * TROW + dn * 2);
@@ -778,17 +803,24 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     using T = std::true_type;
     using F = std::false_type;
     const bool full = m0 + BM <= pe.M && n0 + TN <= pe.N;
+    auto with_y = [&](auto full_tag, auto staged_tag) {
+      if constexpr (BLK == 16) {
+        if (trade) return finish(full_tag, staged_tag, std::integral_constant<int, TRADED_ROWS>{});
+      }
+      finish(full_tag, staged_tag, std::integral_constant<int, QUAD_ROWS>{});
+    };
+    using NoY = std::integral_constant<int, NO_Y>;
     if constexpr (GROUPED) {
-      if (full && staged) finish(T{}, T{}, F{});
-      else if (staged) finish(F{}, T{}, F{});
-      else finish(F{}, F{}, F{});
+      if (full && staged) finish(T{}, T{}, NoY{});
+      else if (staged) finish(F{}, T{}, NoY{});
+      else finish(F{}, F{}, NoY{});
     } else if (FUSE_LOSS) {
-      if (full && staged && !pe.y) finish(T{}, T{}, F{});          // the step's path
-      else if (staged) { if (pe.y) finish(F{}, T{}, T{}); else finish(F{}, T{}, F{}); }
-      else { if (pe.y) finish(F{}, F{}, T{}); else finish(F{}, F{}, F{}); }
+      if (full && staged && !pe.y) finish(T{}, T{}, NoY{});          // the step's path
+      else if (staged) { if (pe.y) with_y(F{}, T{}); else finish(F{}, T{}, NoY{}); }
+      else { if (pe.y) with_y(F{}, F{}); else finish(F{}, F{}, NoY{}); }
     } else {
-      if (full) finish(T{}, F{}, T{});
-      else finish(F{}, F{}, T{});
+      if (full) with_y(T{}, F{});
+      else with_y(F{}, F{});
     }
   }
   if (FUSE_LOSS) {
@@ -941,13 +973,15 @@ static int plan_tiles(int M, int N, int format, int* blocks_out) {
 
 // 128 x 128 tiles, K whole: blocks of 32 x 32, half as many matrix instructions, where a weight wave's instructions bound the launch, of
 // 16 x 16 where power does.  With the bf16 tile, whose dequantisation is longest, always.  With the fp16 tile while few CUs have more than one
-// tile, and a little further with denser masks.  us, 16x16x32 -> 32x32x16: bf16 forwards of 8192 x 8192 at 700 tokens 181.5 -> 173.9, 4096 x 4096 at
-// 1280 / 2000 93.4 / 94.9 -> 88.7 / 93.4, a step over 8192 x 4096 at 700 and 0.8 % 218 -> 210; fp16 forwards of 4096 x 4096 at 1100 / 1280 (288 / 320
-// tiles) 69.0 / 68.7 -> 66.7 / 67.0, 4096 x 11008 at 1200 174.9 -> 168.0, 4096 x 4160 at 500 (128 tiles) 51.9 -> 50.4; beyond the line 4096 x 4096 at
-// 1400 (352) 69.4 -> 70.4 and 69.8 -> 68.9 on two boxes, at 1500 / 2000 (384 / 512) 70.2 / 77.7 -> 70.7 / 81.2; with 0.3 / 0.5 / 1 % at 1500 72.0 /
-// 73.0 / 77.3 -> 71.4 / 72.2 / 75.6, a step over 8192 x 8192 at 700 and 0.5 % 301 -> 290.
+// tile, a little further with denser masks, and for short K with unaligned rows of y, which blocks of 32 x 32 store in two rows of 32
+// by themselves.  us, 16x16x32 -> 32x32x16: bf16 forwards of 8192 x 8192 at 700 tokens 181.5 -> 173.9, 4096 x 4096 at 1280 / 2000 93.4 / 94.9 ->
+// 88.7 / 93.4, a step over 8192 x 4096 at 700 and 0.8 % 218 -> 210; fp16 forwards of 4096 x 4096 at 1100 / 1280 (288 / 320 tiles) 69.0 / 68.7 -> 66.7 /
+// 67.0, 4096 x 11008 at 1200 174.9 -> 168.0, 4096 x 4160 at 500 (128 tiles) 51.9 -> 50.4; beyond the line 4096 x 4096 at 1400 (352) 69.4 -> 70.4 and
+// 69.8 -> 68.9 on two boxes, at 1500 / 2000 (384 / 512) 70.2 / 77.7 -> 70.7 / 81.2; with 0.3 / 0.5 / 1 % at 1500 72.0 / 73.0 / 77.3 -> 71.4 / 72.2 / 75.6, a
+// step over 8192 x 8192 at 700 and 0.5 % 301 -> 290; 5003 x 256 / 1024 at 1100 (360) 11.6 / 23.1 -> 11.4 / 22.6, 3333 x 256 / 1024 / 2048 at 2000 (432)
+// 12.1 / 23.9 / 39.6 -> 11.8 / 24.0 / 40.3.
 static bool wide_blocks(int tiles, const FwdParams& p) {
-  return tiles <= 320 || (tiles <= 384 && 250ll * p.nnz >= (int64_t)p.N * p.K);
+  return tiles <= 320 || (tiles <= 384 && 250ll * p.nnz >= (int64_t)p.N * p.K) || ((p.N & 3) != 0 && p.K <= 1024);
 }
 
 template <int DT, bool FUSE>

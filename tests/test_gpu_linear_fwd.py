@@ -140,6 +140,31 @@ def test_whole_small_tiles(M, N, K, G, dens, dt, dtname):
         assert abs(loss[0].item() / (np.sum(err * err) / (M * N)) - 1.0) <= 18 * 2.0 ** -24
 
 
+# Rows of y at any multiple of four bytes: quads side by side trade rows where they do not begin at multiples of 16.  K in two parts, whole
+# with blocks of 16 x 16 and of 32 x 32, 256 x 256 tiles, tables; full and ragged tiles; targets staged (rows of 16 bytes) and not
+@pytest.mark.parametrize("cfg,M,N,K,fmt", [(0, 513, 130, 384, "uniform"), (0, 384, 256, 256, "uniform"), (0, 2100, 2608, 192, "uniform"), (0, 2100, 2609, 192, "uniform"),
+                                           (0, 2100, 2609, 1088, "uniform"), (2, 300, 520, 128, "uniform"), (2, 512, 513, 128, "uniform"), (2, 300, 520, 128, "lut")])
+def test_outputs_at_any_alignment(cfg, M, N, K, fmt):
+    szo.szo_set_tile_config(cfg)
+    o, d = make_pair(66, M, N, K, 64, 2e-3, nnz_base=4, fmt=fmt)
+    y = torch.from_numpy(_run(d, +1, 1e-3, 9, 2, szo.TILE_F16))
+    z = ophilox.zbar(9, 2, 4, o.sp_idx.size)
+    assert rel_fro(y, olayer.linear_fwd(o.x_bits, o.codes, o.scales, 64, o.sp_idx, o.sp_val, z, +1, 1e-3, "D", "f16", lut=o.lut)) <= 2e-5
+    ws, loss = szo.new_workspace(), torch.zeros(1, dtype=torch.float64, device="cuda")
+    szo.szo_linear_fwd_mse(d.desc(with_y=False), 9, 2, +1, 1e-3, 1.0 / (M * N), loss, ws)
+    want = loss.item()
+    for first in (256, 257, 258, 259, 260):
+        guarded = torch.full((M * N + 512,), 7.5, device="cuda")
+        d.y = guarded[first:first + M * N].view(M, N)
+        szo.szo_linear_fwd(d.desc(), 9, 2, +1, 1e-3)
+        assert torch.equal(d.y.cpu(), y)
+        d.y.fill_(float("nan"))
+        loss.zero_()
+        szo.szo_linear_fwd_mse(d.desc(), 9, 2, +1, 1e-3, 1.0 / (M * N), loss, ws)
+        assert torch.equal(d.y.cpu(), y) and loss.item() == want
+        assert bool((guarded[:first] == 7.5).all()) and bool((guarded[first + M * N:] == 7.5).all())
+
+
 def test_perturbation_difference_is_linear_in_z():
     # y(+) - y(-) = 2 eps x Z^T: checks the sign convention and that only masked entries move
     o, d = make_pair(7, 96, 256, 256, 32, 5e-3)
