@@ -125,12 +125,12 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // runs at 1.86 GHz instead of 1.69 for 5 % more cycles.  us, 32x32x16 -> 16x16x32: two Llama blocks at 4096 tokens 5358 -> 5120, with
   // the bf16 tile 5528 -> 5212, with tables 5880 -> 5685; one Mistral block at 8192 and 1 % 6148 -> 5836; two of them with two sets of
   // activations at 333 701 -> 661; a 4096 x 4096 composed step at 2000 176 -> 167.
-  // Blocks of 32 x 32: half as many instructions, for launches of 128 x 128 tiles that are bound by a weight wave's
-  // instructions and not by power (see wide_blocks).
+  // Blocks of 32 x 32: half as many instructions, for launches that are bound by a weight wave's instructions and not by power
+  // (see wide_blocks, kFewTableTiles).
   // RING operands of x are held at a time, each re-read for a later row of blocks as soon as its own has been issued: three are
   // what the registers of the 32-slot schedule allow, four hide more where one wave has a SIMD to itself (six forwards of a Llama block
   // at 600 tokens 501 -> 494).
-  static_assert(BLK == 16 || (BLK == 32 && SLOTS == 16 && KS == 1 && !DUAL), "32 x 32: whole small tiles");
+  static_assert(BLK == 16 || (BLK == 32 && KS == 1 && !DUAL && (SLOTS == 16 || FMT == SZO_FORMAT_LUT)), "32 x 32: whole small tiles and tables");
   constexpr int NA = 32 * WMB / BLK, NB = 32 * WNB / BLK, KSTEPS = BLK / 8, LANE_SHIFT = BLK == 16 ? 4 : 5, RING = SLOTS == 32 ? 3 : 4;
   typedef typename std::conditional<BLK == 16, float4_t, float16_t>::type acc_t;
   acc_t acc[NA][NB];
@@ -984,6 +984,12 @@ static bool wide_blocks(int tiles, const FwdParams& p) {
   return tiles <= 320 || (tiles <= 384 && 250ll * p.nnz >= (int64_t)p.N * p.K) || ((p.N & 3) != 0 && p.K <= 1024);
 }
 
+// Tables (256 x 256 tiles): up to this many a K step is bound by the look-ups and blocks of 32 x 32 are faster, with more of the chip at work
+// power decides.  us of a forward of 4096 x 4096, 32x32x16 / 16x16x32, at 1024 / 2048 / 2560 / 2816 / 3072 / 4096 tokens (64 / 128 / 160 / 176 / 192 /
+// 256 tiles) 85.9 / 96.0, 88.3 / 97.1, 95.9 / 98.6, 101.1 / 101.0, 106.4 / 105.0, 131.1 / 125.6; beyond a round at 5120 / 8192 209 / 211, 257 / 250; 1024
+// columns at 2304 / 3072 30.5 / 31.7, 34.9 / 34.4; a step over a Llama block with outputs at 600 1583 / 1766.
+constexpr int kFewTableTiles = 168;
+
 template <int DT, bool FUSE>
 static int dispatch_tile(FwdParams& p, hipStream_t stream) {
   int blocks;
@@ -1037,9 +1043,15 @@ static int run_forward(const szo_linear_desc* d, uint64_t seed, uint64_t step, i
   const int frc = fill_params(p, d, seed, step, sign, eps, partials, scale);
   if (frc != SZO_OK) return frc;
   if (step_minus && d->x_minus) p.x = (global_u16)d->x_minus;
-  if (d->format == SZO_FORMAT_LUT)
+  if (d->format == SZO_FORMAT_LUT) {
+    int blocks;
+    plan_tiles(p.M, p.N, SZO_FORMAT_LUT, &blocks);
+    if ((g_tile_config == 0 || g_tile_config >= 4) && blocks <= kFewTableTiles)
+      return fuse ? launch<2, 4, 4, 2, SZO_TILE_F16, true, SZO_FORMAT_LUT, 1, 32>(p, stream)
+                  : launch<2, 4, 4, 2, SZO_TILE_F16, false, SZO_FORMAT_LUT, 1, 32>(p, stream);
     return fuse ? launch<2, 4, 4, 2, SZO_TILE_F16, true, SZO_FORMAT_LUT>(p, stream)
                 : launch<2, 4, 4, 2, SZO_TILE_F16, false, SZO_FORMAT_LUT>(p, stream);
+  }
   if (d->tile_dtype == SZO_TILE_F16)
     return fuse ? dispatch_tile<SZO_TILE_F16, true>(p, stream) : dispatch_tile<SZO_TILE_F16, false>(p, stream);
   return fuse ? dispatch_tile<SZO_TILE_BF16, true>(p, stream) : dispatch_tile<SZO_TILE_BF16, false>(p, stream);

@@ -141,9 +141,9 @@ def test_whole_small_tiles(M, N, K, G, dens, dt, dtname):
 
 
 # Rows of y at any multiple of four bytes: quads side by side trade rows where they do not begin at multiples of 16.  K in two parts, whole
-# with blocks of 16 x 16 and of 32 x 32, 256 x 256 tiles, tables; full and ragged tiles; targets staged (rows of 16 bytes) and not
+# with blocks of 16 x 16 and of 32 x 32, 256 x 256 tiles, tables with either block; full and ragged tiles; targets staged (rows of 16 bytes) and not
 @pytest.mark.parametrize("cfg,M,N,K,fmt", [(0, 513, 130, 384, "uniform"), (0, 384, 256, 256, "uniform"), (0, 2100, 2608, 192, "uniform"), (0, 2100, 2609, 192, "uniform"),
-                                           (0, 2100, 2609, 1088, "uniform"), (2, 300, 520, 128, "uniform"), (2, 512, 513, 128, "uniform"), (2, 300, 520, 128, "lut")])
+                                           (0, 2100, 2609, 1088, "uniform"), (0, 700, 513, 192, "lut"), (0, 3500, 3072, 64, "lut"), (2, 300, 520, 128, "uniform"), (2, 512, 513, 128, "uniform"), (2, 300, 520, 128, "lut")])
 def test_outputs_at_any_alignment(cfg, M, N, K, fmt):
     szo.szo_set_tile_config(cfg)
     o, d = make_pair(66, M, N, K, 64, 2e-3, nnz_base=4, fmt=fmt)
