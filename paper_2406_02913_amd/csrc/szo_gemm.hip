@@ -128,10 +128,10 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // Blocks of 32 x 32: half as many instructions, for launches that are bound by a weight wave's instructions and not by power
   // (see wide_blocks, kFewTableTiles).
   // RING operands of x are held at a time, each re-read for a later row of blocks as soon as its own has been issued: three are
-  // what the registers of the 32-slot schedule allow, four hide more where one wave has a SIMD to itself (six forwards of a Llama block
-  // at 600 tokens 501 -> 494).
+  // what the registers of the 32-slot schedule allow with 16 x 16, four hide more where one wave has a SIMD to itself (six forwards of a Llama
+  // block at 600 tokens 501 -> 494; 32 x 32 with tables in half-empty tiles, 5087 x 6208 at 14 tokens 104.3 -> 103.6).
   static_assert(BLK == 16 || (BLK == 32 && KS == 1 && !DUAL && (SLOTS == 16 || FMT == SZO_FORMAT_LUT)), "32 x 32: whole small tiles and tables");
-  constexpr int NA = 32 * WMB / BLK, NB = 32 * WNB / BLK, KSTEPS = BLK / 8, LANE_SHIFT = BLK == 16 ? 4 : 5, RING = SLOTS == 32 ? 3 : 4;
+  constexpr int NA = 32 * WMB / BLK, NB = 32 * WNB / BLK, KSTEPS = BLK / 8, LANE_SHIFT = BLK == 16 ? 4 : 5, RING = SLOTS == 32 && BLK == 16 ? 3 : 4;
   typedef typename std::conditional<BLK == 16, float4_t, float16_t>::type acc_t;
   acc_t acc[NA][NB];
 #pragma unroll
@@ -986,7 +986,7 @@ static bool wide_blocks(int tiles, const FwdParams& p) {
 
 // Tables (256 x 256 tiles): up to this many a K step is bound by the look-ups and blocks of 32 x 32 are faster, with more of the chip at work
 // power decides.  us of a forward of 4096 x 4096, 32x32x16 / 16x16x32, at 1024 / 2048 / 2560 / 2816 / 3072 / 4096 tokens (64 / 128 / 160 / 176 / 192 /
-// 256 tiles) 85.9 / 96.0, 88.3 / 97.1, 95.9 / 98.6, 101.1 / 101.0, 106.4 / 105.0, 131.1 / 125.6; beyond a round at 5120 / 8192 209 / 211, 257 / 250; 1024
+// 256 tiles) 86 / 96, 88 / 97, 96 / 99, 101.1 / 101.0, 106 / 105, 131 / 126; beyond a round at 5120 / 8192 209 / 211, 257 / 250; 1024
 // columns at 2304 / 3072 30.5 / 31.7, 34.9 / 34.4; a step over a Llama block with outputs at 600 1583 / 1766.
 constexpr int kFewTableTiles = 168;
 
