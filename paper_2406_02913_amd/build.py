@@ -14,7 +14,8 @@ HOST_SOURCES = ["szo_host.cpp"]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 # packed fp32 VALU forms are switched off (see the hardware notes this project follows)
-# the first 16 words of a kernel's arguments are in scalar registers when a wave starts, instead of a memory round trip away
+# A kernel's leading scalar and pointer arguments are in scalar registers when a wave starts, instead of a memory round trip away: up to
+# 14 words (a wave has 16 such registers, two hold the address of the arguments), none from the first struct passed by value on.
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 

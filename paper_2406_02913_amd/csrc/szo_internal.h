@@ -117,8 +117,8 @@ bool stream_is_capturing(hipStream_t stream);
 int zero_words(void* p, int n, hipStream_t stream);
 
 // Wave-wide sum in a fixed order (64 lanes): halves, then rows of 16, 8, 4, 2, 1 lanes added to each other; result valid in every
-// lane.  By lane swaps and row rotations, which stay in registers: the same sums by shuffles are twelve round trips through LDS one
-// after the other, 0.3 us at the end of kernels that take five.  (A row rotated by 4, 2 or 1 pairs the lanes that an exclusive or
+// lane.  By lane swaps and row rotations, which stay in registers: the same sums by shuffles are six round trips through LDS, of two
+// permutations each, one after the other: 0.3 us at the end of kernels that take five.  (A row rotated by 4, 2 or 1 pairs the lanes that an exclusive or
 // would: after each step the sums repeat with that period.)
 template <int ROTATE>
 __device__ __forceinline__ double add_row_rotated(double v) {

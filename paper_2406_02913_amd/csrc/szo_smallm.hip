@@ -815,6 +815,8 @@ constexpr int64_t kSplitOnlyTokens = 64, kSplitOnlyTwoSets = 1536;
 // 4059 x 6848 at 473 tokens and 0.3 % 154 against 141 on the one-dense-pass kernel, a forward of 810 x 9280 at 2238 185 against 133 in tiles;
 // two sets of 4096 x 4160 at 200 and 1 % 204 against 185, of 2354 x 704 at 953 (2220 bands and slices) 72 against 51, of
 // 3552 x 12416 at 329 248 against 378.
+// (All of these are tiles with K whole.  With K in two parts, which the estimates leave out, a few sizes near the line are 5..20 % faster
+// in tiles: 4096 x 4096 at 128 tokens and 1 % with the bf16 tile.)
 static double split_rounded_us(const LaunchShape& l, bool two_sets) {
   const double chain = l.longest_k * (1.9 + 5.3 * l.percent());
   if (l.most_tokens <= 128) return 13.5 + std::max(0.016 * (double)l.bands16 + 0.0036 * l.band_k + 0.02 * l.slice_entries, chain);
@@ -837,8 +839,10 @@ constexpr int64_t kSplitOnlyColumns = 1 << 23;
 // 4096 at 600 tokens 67 -> 68, a forward 57 -> 59, of 258 x 5248 at 6437 69 -> 78.  Forwards with tables (256 x 256 tiles): 300 x 4096 at
 // 6000 tokens 87 -> 102, 445 x 9984 at 3681 232 -> 176, 4096 x 4096 at 450 87 -> 78, 1231 x 15872 at 1741 353 -> 398.  The bf16 tile (and K an odd multiple of 64) compares its own estimates below: a
 // forward of a 1024 x 1024 / 4096 x 4096 layer at 300 tokens 21 / 70 -> 9 / 45.
-// (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.  The tiles' times are those of the
-// 128 x 128 schedule that scattered behind its last matrix instruction; it takes 5 % less by now, and the line stays where both were measured.)
+// (Below 1024 columns the chain is a few launches' time and either path's launches weigh more.  The tiles' times are of tiles that walk K as a
+// whole, with a schedule that scattered behind its last matrix instruction; with K in two parts they take up to 40 % less.  The line stays
+// for what moves with it beside the time: the tiles round v + eps z, and with groups of 128 the dequantised weights, which the few-token
+// kernels do not.  Unperturbed forwards with small groups, where nothing of that differs, have a line of their own, two_part_tiles_win.)
 static bool outruns_the_chain(const szo_linear_desc* d, const LaunchShape& launch, int forwards) {
   if (d->K < 1024) return false;
   const bool lut = d->format == SZO_FORMAT_LUT, plain = !lut && d->group != 128, single = forwards == 1;      // (a table layer's group means nothing)

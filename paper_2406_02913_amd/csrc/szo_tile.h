@@ -71,6 +71,7 @@ struct FwdParams {
 // The table of a grouped launch: staged in device memory, or, up to kInlineForwards entries, in the kernel's arguments, where it
 // costs no copy kernel in front of the launch.  us per step, staged -> in the arguments: 4096 x 4096 at 200 tokens 37.8 -> 34.6, 2048 x 1024 at
 // 500 19.0 -> 16.9, with outputs at 100 67.5 -> 60.5, one Llama block at 256 172 -> 166, one Mistral block with two sets at 333 358 -> 345.
+// (A staged launch passes the arguments' table too, unread: whatever the thread's last table was.)
 constexpr int kInlineForwards = 16;
 struct InlineForwards { FwdParams e[kInlineForwards]; };
 struct ForwardTableArgs { const FwdParams* table; int n_entries; InlineForwards inl; };          // as the arguments lie in memory

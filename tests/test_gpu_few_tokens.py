@@ -253,7 +253,8 @@ def test_single_forwards_that_tiles_would_take_unperturbed_keep_the_perturbation
         szo.szo_linear_fwd(d.desc(), 9, step, sign, eps)
         return d.y.cpu().numpy().astype(np.float64)
     at_rest, off_g = forward(0, 0), []
-    assert rel_fro(at_rest, y0) <= 1e-3
+    # both kernels round the dequantised weights and v to fp16, and the sensitive weights have none of the former: the same weights
+    assert rel_fro(at_rest, olayer.linear_fwd(o.x_bits, o.codes, o.scales, G, o.sp_idx, o.sp_val, mode="D")) <= 2e-5
     for step in range(steps):
         Z.reshape(-1)[o.sp_idx.astype(np.int64)] = ophilox.zbar(9, step, 4, o.sp_idx.size)
         moved = float(np.float32(eps)) * (x @ Z.T)
