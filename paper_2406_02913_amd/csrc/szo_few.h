@@ -202,6 +202,7 @@ struct SplitLaunch {
   bool one;                 // only the "+" forward is wanted (used by tile_round)
   int subs;                 // most subtiles of a workgroup: 4 >> the smallest part shift of the launch
   int waves, workgroups;
+  int64_t longest_k;
 };
 int split_launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream);
 

@@ -780,7 +780,7 @@ static int launch_plan(const FewPlan& p, const LaunchTotals& t, bool one_sign, S
   if (rc != SZO_OK) return rc;
   if (p.split()) {
     rc = split_launch(SplitLaunch{p.mode(), p.dual(), p.dequant == D_TILE_BF16, p.dequant >= D_TILE_F16, one_sign, t.subs,
-                                  split_waves(p, one_sign, wgs, t), wgs}, a, stream);
+                                  split_waves(p, one_sign, wgs, t), wgs, t.k}, a, stream);
     if (rc != SZO_OK) return rc;
   } else {
     const dim3 blocks((unsigned)wgs);

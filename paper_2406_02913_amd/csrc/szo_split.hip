@@ -116,7 +116,7 @@ constexpr int split_wave_floats(int nacc, int subs) {
 }
 // SUBS: the workgroup's 16-row subtiles of the band.   XP: load instructions for 16 token rows of x, four rows each; with
 // XP = 1 rows 4..15 of the operands are whatever LDS held: they only reach output rows that do not exist.
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE, int SUBS, int XP>
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE, bool BEHIND, int SUBS, int XP>
 __device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_words tab, int index, const int bid, const int slice) {
   static_assert(!BF16 || (MODE == SM_PLAIN && TILE_ROUND), "bf16 tile: plain dequantisation, rounded as in the tile");
   constexpr bool FAST = MODE == SM_FAST, LUT = MODE == SM_LUT;
@@ -201,14 +201,12 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_
     auto load_bounds = [&]() {
       if (mt.nnz > 0) { e_lo = bounds[2 * b0]; e_hi = bounds[min(2 * b1, ktiles)]; }
     };
-    // With two sets of activations behind the block's loads: in front of them the compiler gives the bf16 form 21 registers less and orders its
-    // products one behind the other (steps over four Llama blocks at 3 / 16 / 40 tokens 134 / 214 / 421 -> 130 / 208 / 412; fp16 as before).
-    if (!DUAL) load_bounds();
+    if (!BEHIND) load_bounds();
 #pragma unroll
     for (int s = 0; s < SUBS; ++s) load_q(b0, s);
     load_x(b0);
     load_scales(b0);
-    if (DUAL) load_bounds();
+    if (BEHIND) load_bounds();
   }
   uint32_t tb[LUT ? SUBS : 1][8];
   if (LUT) {
@@ -478,8 +476,9 @@ __device__ __forceinline__ void band_split_body(const SmallArgs& a, const small_
 // are in scalar registers when the wave starts (kernarg preload, see build.py), so that the entry is the first memory round trip and
 // not the third, behind the arguments and the size of the grid.  us per pass over four sets of weights: a step over one small layer 11.30 -> 10.97,
 // six calls over an OPT block at one token 57.6 -> 55.4, a step over it at 16 tokens 44.0 -> 43.4.
+// BEHIND: a wave asks for its tile bounds behind its first block's loads (see launch_mode).
 struct SplitArgs { const SmallMat* table; int n_mats; uint32_t part_shifts; int slices, few_rows, workgroups; SmallArgs a; };   // as the arguments lie in memory
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE>
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE, bool BEHIND>
 __global__ void __launch_bounds__((64 * split_max_waves<MODE, DUAL, TILE_ROUND>()))
 band_split_kernel(const SmallMat* table, int n_mats, uint32_t part_shifts, int slices, int few_rows, int workgroups, SmallArgs a) {
   int bid = xcd_unit((int)blockIdx.x, workgroups);
@@ -491,21 +490,21 @@ band_split_kernel(const SmallMat* table, int n_mats, uint32_t part_shifts, int s
   const uint32_t part_shift = (part_shifts >> (4 * (index & 7))) & 15u;
   auto run = [&](auto rows_tag) {
     constexpr int XP = decltype(rows_tag)::value;
-    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 4, XP>(a, tab, index, bid, slice);
-    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 2, XP>(a, tab, index, bid, slice);
-    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, 1, XP>(a, tab, index, bid, slice);
+    if (part_shift == 0) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, BEHIND, 4, XP>(a, tab, index, bid, slice);
+    else if (part_shift == 1) band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, BEHIND, 2, XP>(a, tab, index, bid, slice);
+    else band_split_body<MODE, BF16, DUAL, TILE_ROUND, ONE, BEHIND, 1, XP>(a, tab, index, bid, slice);
   };
   if (MODE == SM_FAST && !DUAL && few_rows) run(std::integral_constant<int, 1>{});
   else run(std::integral_constant<int, 4>{});
 }
 
-template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE = false>
+template <int MODE, bool BF16, bool DUAL, bool TILE_ROUND, bool ONE = false, bool BEHIND = false>
 static int launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) {
   constexpr int nacc = split_sets<DUAL, TILE_ROUND, ONE>(), most = split_max_waves<MODE, DUAL, TILE_ROUND>();
   constexpr size_t window = (TILE_ROUND && ONE ? SP_WIN_FLOATS : 0) * sizeof(float), most_bytes = (split_wave_floats(nacc, 4) * sizeof(float) + window) * most;
   const int waves = l.waves < most ? l.waves : most;
   static std::atomic<uint64_t> lds_limit_set{0};             // per instantiation
-  const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND, ONE>;
+  const auto kern = band_split_kernel<MODE, BF16, DUAL, TILE_ROUND, ONE, BEHIND>;
   const int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, most_bytes);
   if (rc != SZO_OK) return rc;
   kern<<<(unsigned)l.workgroups, 64 * waves, (split_wave_floats(nacc, l.subs) * sizeof(float) + window) * (size_t)waves, stream>>>(a.table, a.n_mats, a.part_shifts, a.slices, a.few_rows, l.workgroups, a);
@@ -513,11 +512,20 @@ static int launch(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) 
   return SZO_OK;
 }
 
+// The bf16 form for two sets of activations: with the bounds in front of the loads the compiler gives it 21 registers less and orders its
+// products one behind the other, which large launches lose by; small ones and short K lose by the later bounds.  us per step, in front / behind:
+// four Llama blocks at 3 / 16 / 40 tokens 138 / 215 / 424, 133 / 208 / 416, one at 16 (664 workgroups) 64.0 / 62.8, 8192 x 4096 at 64 (512) 40.7 / 39.5,
+// 4096 x 8192 at 120 (512) 67.1 / 65.4; on the other side 8192 x 1024 at 110 (896) 33.3 / 34.2, 4096 x 1024 / 4096 at 64 (256) 13.2 / 13.4, 22.8 / 22.7,
+// 8192 x 8192 at 2 (256) 19.6 / 20.0.  The other forms are the same either way, or gain 1 to 3 % in front.
+static bool bounds_behind(const SplitLaunch& l) { return l.workgroups >= 512 && l.longest_k >= 2048; }
 template <bool DUAL>
 static int launch_mode(const SplitLaunch& l, const SmallArgs& a, hipStream_t stream) {
   if constexpr (!DUAL) {
     if (l.bf16 && l.one) return launch<SM_PLAIN, true, false, true, true>(l, a, stream);
     if (l.tile_round && l.one) return launch<SM_PLAIN, false, false, true, true>(l, a, stream);
+  }
+  if constexpr (DUAL) {
+    if (l.bf16 && bounds_behind(l)) return launch<SM_PLAIN, true, true, true, false, true>(l, a, stream);
   }
   if (l.bf16) return launch<SM_PLAIN, true, DUAL, true>(l, a, stream);
   if (l.tile_round) return launch<SM_PLAIN, false, DUAL, true>(l, a, stream);
