@@ -977,7 +977,7 @@ static int plan_tiles(int M, int N, int format, int* blocks_out) {
 // by themselves.  us, 16x16x32 -> 32x32x16: bf16 forwards of 8192 x 8192 at 700 tokens 181.5 -> 173.9, 4096 x 4096 at 1280 / 2000 93.4 / 94.9 ->
 // 88.7 / 93.4, a step over 8192 x 4096 at 700 and 0.8 % 218 -> 210; fp16 forwards of 4096 x 4096 at 1100 / 1280 (288 / 320 tiles) 69.0 / 68.7 -> 66.7 /
 // 67.0, 4096 x 11008 at 1200 174.9 -> 168.0, 4096 x 4160 at 500 (128 tiles) 51.9 -> 50.4; beyond the line 4096 x 4096 at 1400 (352) 69.4 -> 70.4 and
-// 69.8 -> 68.9 on two boxes, at 1500 / 2000 (384 / 512) 70.2 / 77.7 -> 70.7 / 81.2; with 0.3 / 0.5 / 1 % at 1500 72.0 / 73.0 / 77.3 -> 71.4 / 72.2 / 75.6, a
+// 69.8 -> 68.9 on two machines, at 1500 / 2000 (384 / 512) 70.2 / 77.7 -> 70.7 / 81.2; with 0.3 / 0.5 / 1 % at 1500 72.0 / 73.0 / 77.3 -> 71.4 / 72.2 / 75.6, a
 // step over 8192 x 8192 at 700 and 0.5 % 301 -> 290; 5003 x 256 / 1024 at 1100 (360) 11.6 / 23.1 -> 11.4 / 22.6, 3333 x 256 / 1024 / 2048 at 2000 (432)
 // 12.1 / 23.9 / 39.6 -> 11.8 / 24.0 / 40.3.
 static bool wide_blocks(int tiles, const FwdParams& p) {
@@ -1170,7 +1170,7 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
   // time.  In the caller's order it ended with the last block's longest layer: two Mistral blocks with two sets of activations at
   // 333 tokens (1344 tiles, the last 64 of them 3.4 times as long as the others) 889 -> 812 us per step.  From 32 rounds of
   // workgroups on there is nothing to gain (a Mistral block at 8192 tokens, 42 rounds, 6251 -> 6295): the caller's order.
-  // Half-empty tiles are ordered by half their K: those blocks 733 -> 688 on another box, one OPT / Mistral block at 600 tokens
+  // Half-empty tiles are ordered by half their K: those blocks 733 -> 688 on another machine, one OPT / Mistral block at 600 tokens
   // 575 / 619 -> 517 / 541, two Llama blocks at 850 1479 -> 1448.
   if (ordered) {
     auto walk = [&](const FwdParams& p) { return (int64_t)p.K * (split && p.grid_m * tile - p.M >= tile / 2 ? 1 : 2); };

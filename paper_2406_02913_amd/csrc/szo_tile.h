@@ -23,7 +23,7 @@ constexpr int kWindow = 256;           // sensitive entries computed per refill 
 
 // Device pointers of a descriptor.  In device code they say that they are global memory: a pointer that comes out of a
 // table in memory is generic to the compiler, and a generic (flat) load counts on the LDS counter as well, so that every
-// wait for an LDS operand also waits for whatever load was issued before it.  Measured on the grouped launches, same box:
+// wait for an LDS operand also waits for whatever load was issued before it.  Measured on the grouped launches, same machine:
 // one Llama block at 4096 tokens 2914 -> 2849 us, eight of them 22.65 -> 22.20 ms, two Mistral blocks at 333 tokens with
 // two activation sets 980 -> 935 us.
 #ifdef __HIP_DEVICE_COMPILE__
