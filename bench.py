@@ -29,10 +29,12 @@ PEAK_HBM_GBS = 8000.0                # MI355X HBM3E
 # HBM bytes per launch of the dominant kernel, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
 # script scaled by a plain copy of known size (profiles/*.md give the commands and the raw readings).
 # Only valid for the unmodified workloads; anything else reports null.
-MEASURED_TRAFFIC_BYTES = {"c3": 7.96e10, "c3m16": 3.613e9,
+MEASURED_TRAFFIC_BYTES = {"c3m16": 3.613e9,
                           # the extra legs of the default run (one Mistral block by density, 32 OPT blocks by token count)
                           "c4:0.0001": 4.290e9, "c4:0.001": 4.318e9, "c4:0.01": 5.305e9,
                           "c5:1": 3.447e9, "c5:16": 3.586e9, "c5:64": 4.237e9}
+
+SHARED_PRODUCT_KERNEL = "linear_fwd_table_kernel (one dense product), transpose_kernel"      # timed as one launch
 
 
 def log(*a):
@@ -74,6 +76,15 @@ def one_product_kernel(mats, M, two_sets=False, asked_for=False):
     if few or asked_for:
         # a few blocks: K split over the waves of a workgroup
         return "band_split_kernel" if M <= 64 and wgs * -(-M // 16) <= 600 else "small_m_kernel"
+    if uniform and not two_sets:        # the tiled kernel with one dense product
+        tiles = gain = entries = 0.0
+        for m in mats:
+            rows, columns = -(-M // 256), -(-m.N // 256)
+            tiles += rows * columns
+            gain += rows * (columns * (1.14 * m.K - 256) - 2.3 * m.K)
+            entries += rows * columns * m.nnz / m.N
+        if tiles > 8192 and gain > 160 * entries:
+            return SHARED_PRODUCT_KERNEL
     return None
 
 
@@ -386,6 +397,8 @@ def main():
             one_product = "band_split_kernel" if args.tile_config == 8 else "small_m_kernel"
         elif args.tile_config == 11:
             one_product = "onepass_table_kernel"
+        elif args.tile_config == 12:
+            one_product = SHARED_PRODUCT_KERNEL
     traffic = MEASURED_TRAFFIC_BYTES.get(args.workload) if (
         args.layers is None and args.m is None and args.density is None and flags and dt == szo.TILE_F16
         and args.tile_config == 0 and args.format == "uniform" and not args.two_activation_sets

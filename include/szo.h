@@ -169,7 +169,10 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * tokens, or launches of so few workgroups that any tile would outlast them, stream the weights once per 16 to 48 token rows; the
  * others run on the matrix cores in tiles of 64 token rows, if
  * the layers are of the uniform format with one tile type, fill the chip, and their masks are sparse (against the tiled kernel up to
- * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Otherwise, and beyond 2048
+ * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Steps of more than 8192 output tiles of 256 x 256 that those rules leave (several blocks beyond 2048
+ * tokens) compute the dense product of such layers in tiles of that size, with weights rounded once to the tile's type, and the sensitive products behind
+ * it, with masks of up to about 0.6 % (less with few rows of W or a short K): a copy of the activations in the workspace, 64 tokens of
+ * a column side by side, serves them, and the step goes in launches of as many layers as it has room for (1 GiB).  Otherwise, and beyond 2048
  * tokens in steps of more than 2048 output tiles of 256 x 128, each layer runs as two full products, as the single-layer
  * calls compute them; the results are the same up to the roundings described at SZO_TILE_F16.  The tiles are counted over
  * the step as a whole: the same layers in several smaller steps may be computed the other way, to the same roundings.
@@ -189,9 +192,8 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
 /* Bit 1 (with bit 0): one dense product per layer in larger steps, with denser masks and in steps of few workgroups too: half the
  * dense work, same results up to the roundings above.  A step keeps two products all the same where its layers have a
  * second set of activations or where it loses by it (bf16 tile or K an odd multiple of 64 with masks of about 1 % and
- * more, where the sparse products cost what the second dense product does).  Not the default for large steps because
- * it does not carry over to a caller whose two forwards see different activations (every layer of a real model but the
- * first), who calls szo_linear_fwd per sign instead. */
+ * more, where the sparse products cost what the second dense product does).  Not the default for large steps, which take one
+ * dense product in larger tiles where that pays: with the fp16 tile and groups of 128 this one applies the group scales in fp32. */
 #define SZO_STEP_ONE_DENSE_PASS 2
 int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
                 float eps, float lr, double* scalars, void* workspace, int flags, void* stream);
@@ -219,7 +221,8 @@ int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, u
 int szo_zo_step_noalloc(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
                         float eps, float lr, double* scalars /* device double[3] */, void* stream);
 
-/* Bytes of device workspace the loss-accumulating calls need (a constant). */
+/* Bytes of device workspace the loss-accumulating calls need (a constant: 16 MiB for loss partials, tables, and 1 GiB for
+ * copies of activations, of which only large steps write what they need). */
 size_t szo_workspace_bytes(void);
 
 /* Puts a freshly allocated workspace into its idle state (zeroes its header).  Needed once per
@@ -321,7 +324,8 @@ int szo_debug_zbar(uint64_t nnz_base, int64_t nnz, uint64_t seed, uint64_t step,
  * of token rows per strip (by default only when the launch streams more codes than the last-level cache
  * holds), 8 / 9 = as 0 and the few-token path takes its kernel for small launches (K split over the waves of
  * a workgroup) always / never, 10 = 9 and 7, 11 = szo_zo_step takes the kernel that computes one dense
- * product per layer in tiles of 64 token rows wherever it can (chosen by size with 0, never with 1 to 10).
+ * product per layer in tiles of 64 token rows wherever it can (chosen by size with 0, never with 1 to 10), 12 = the one that does so in
+ * tiles of 256 x 256 wherever it can (likewise; never with 11).
  * Process-wide, not thread-safe.  Results depend on it by the roundings described at SZO_TILE_F16 and by fp32
  * summation order. */
 int szo_set_tile_config(int config);

@@ -26,6 +26,7 @@
 #include <vector>
 #include "szo_internal.h"
 #include "szo_rng.h"
+#include "szo_shared.h"
 #include "szo_tile.h"
 #include <mutex>
 #include <type_traits>
@@ -58,6 +59,8 @@ constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int
 // and written twice, the two copies differ only at the sensitive entries.  Waves of the first half of a
 // wave row compute the +eps forward, the others the -eps forward; every MFMA of both forwards is
 // executed, only the staging of the weights is shared.  The MFMA loop is the same as without DUAL.
+// SHARED (likewise, sparse masks): D of 256 x 256 outputs, without the perturbation, and behind it the sensitive products that both
+// forwards add to it (szo_shared.h).
 //
 // KS = 2 (a launch of few 128 x 128 tiles): eight waves, of which the second four compute the second half of the K steps in
 // buffers of their own.  Such a launch is bound by a weight wave's chain, ~220 instructions per K step at one wave on its SIMD
@@ -65,7 +68,7 @@ constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int
 // the sums of half of the tile's rows.
 //
 // BLK: the matrix instruction, 16x16x32 or 32x32x16 (see below).  GROUPED: a grouped launch, which never writes y.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1, int BLK = 16, bool GROUPED = false>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1, int BLK = 16, bool GROUPED = false, bool SHARED = false>
 __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm, const int bn,
                                                 const uint32_t __attribute__((address_space(4)))* entry = nullptr) {
   constexpr int NWAVES = WAVES_M * WAVES_N;
@@ -109,7 +112,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
   // tile; the pointer is laundered so that the loads stay where they are written.  Only with dual-sign
   // tiles: otherwise the grouped launch has changed `p` for the -eps forward.
   auto cold = [&]() -> FwdParams {
-    if (!DUAL || entry == nullptr) return p;
+    if (!(DUAL || SHARED) || entry == nullptr) return p;
     constexpr int W = (int)(sizeof(FwdParams) / 4);
     const uint32_t __attribute__((address_space(4)))* e = entry;
     asm volatile("" : "+s"(e));
@@ -270,7 +273,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
           }
         }
         float val_minus[4] = {val[0], val[1], val[2], val[3]};
-        if (pr.signed_eps != 0.0f) {
+        if (!SHARED && pr.signed_eps != 0.0f) {
           float z[4];
           zbar_quad((pr.nnz_base + j) >> 2, pr.seed, pr.step, z);
 #pragma unroll
@@ -602,13 +605,18 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     // =============================== activation wave ===========================================
     const int xt = 64 * wave + lane - 64 * W_WAVES;
     const int xc = xt & 7, xr = xt >> 3;                       // chunk, row (plus X_ROWS_PER_PASS*u)
+    u32x4 xreg[8];
+    // SHARED: a buffer of the tile's rows and one offset instead of eight pointers, whose registers its epilogue has no room for.  Rows past M
+    // are out of its bounds and read as zero; what is loaded past the end of a row is not used.
     global_u16 xrow[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       xrow[u] = p.x + (size_t)min(m0 + xr + X_ROWS_PER_PASS * u, p.M - 1) * p.K + k0 * BK + xc * 8;
-    u32x4 xreg[8];
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(p.x + (size_t)m0 * p.K), 0, min(p.M - m0, BM) * 2 * p.K, 0x00027000);
+    const int xoff = xr * 2 * p.K + 16 * xc;
     auto load_x = [&](int kt, int u) {
-      xreg[u] = *reinterpret_cast<global_u32x4>(xrow[u] + min(kt, nk - 1) * BK);
+      if (SHARED) xreg[u] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, xoff + (X_ROWS_PER_PASS * u * 2 * p.K + kt * (2 * BK)), 0, 0);
+      else xreg[u] = *reinterpret_cast<global_u32x4>(xrow[u] + min(kt, nk - 1) * BK);
     };
     u32x4 outw;
     auto make_slice = [&](int dst, int load_kt) {
@@ -661,6 +669,11 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
     }
   }
 
+  if constexpr (SHARED) {
+    static_assert(!DUAL && KS == 1 && BLK == 16 && BM == 256 && BN == 256 && FUSE_LOSS, "256 x 256 outputs, one launch for both signs");
+    shared_tail<DT>(acc, cold, bm, bn, reinterpret_cast<uint8_t*>(smem));
+    return;
+  }
   // ---- epilogue: in quads, of four rows in one column for each lane.  Register r of quad (i,j) of a wave tile holds
   //      row  16*i + 4*(lane/16) + r ,  column 16*j + lane%16  (blocks of 32 x 32: row 32*(i/2) + 8*(2*(i%2) + j%2) + 4*(lane/32) + r,
   //      column 32*(j/2) + lane%32) ----
@@ -861,7 +874,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KS) linear_fwd_kernel
 // again later.  Workgroups between an entry's last tile and the next multiple of 8 have nothing to do.
 // With DUAL an entry has grid_m * grid_n workgroups, each computing both forwards of a tile of half the
 // width (see linear_fwd_body); the 32 workgroups resident on an XCD are then 2 x 16 such tiles.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int BLK = 16>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int BLK = 16, bool SHARED = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kernel(const FwdParams* table, int n_entries, InlineForwards) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
   static_assert(sizeof(FwdParams) % 4 == 0 && offsetof(FwdParams, first_block) % 4 == 0, "table entry is read as words");
@@ -875,11 +888,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kerne
 #pragma unroll
   for (int i = 0; i < W; ++i) raw.w[i] = tab[lo * W + i];
   FwdParams p = __builtin_bit_cast(FwdParams, raw);
-  const int bid = (int)blockIdx.x - p.first_block, count = (DUAL ? 1 : 2) * p.grid_m * p.grid_n;
+  const int bid = (int)blockIdx.x - p.first_block, count = (DUAL || SHARED ? 1 : 2) * p.grid_m * p.grid_n;
   if (bid >= count) return;
   const int L = logical_block(bid, count);
   int bm, bn;
-  if (DUAL) {
+  if (DUAL || SHARED) {
     tile_of_logical(L, p.grid_m, p.grid_n, 2, bm, bn);
   } else {
     tile_of_logical(L >> 1, p.grid_m, p.grid_n, 2, bm, bn);
@@ -889,7 +902,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kerne
       p.signed_eps = -p.signed_eps;
     }
   }
-  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, DUAL, 1, BLK, true>(p, bm, bn, tab + lo * W);
+  linear_fwd_body<WAVES_M, WAVES_N, WMB, WNB, DT, FUSE_LOSS, FMT, DUAL, 1, BLK, true, SHARED>(p, bm, bn, tab + lo * W);
 }
 
 // ---- host side -----------------------------------------------------------------------------
@@ -898,7 +911,8 @@ static int g_tile_config = 0;      // 0 = choose by shape, 1 = 128x128 (4 waves,
                                    // 4, 5 = as 0 with the few-token path's 32- / 48-row passes forced (see small_m_force_rblocks),
                                    // 6 = as 0 + always group the step, 7 = as 0 + non-temporal code stream in every one-slice launch,
                                    // 8, 9 = as 0 with the few-token path's split kernel always / never chosen, 10 = 9 and 7,
-                                   // 11 = the one-dense-pass kernel wherever it can run (chosen by shape with 0, never with the others)
+                                   // 11 = the one-dense-pass kernel wherever it can run (chosen by shape with 0, never with the others),
+                                   // 12 = the tiled kernel with one dense product wherever it can run (likewise)
 static bool few_token_enabled() { return g_tile_config == 0 || g_tile_config >= 4; }
 
 static int ilog2_exact(int v) {
@@ -1076,25 +1090,27 @@ static int update_all(const szo_linear_desc* descs, int n, uint64_t seed, uint64
 }
 
 static double* partial_area(void* workspace) { return (double*)((char*)workspace + kWorkspaceHeader); }
+static void* copy_area(void* workspace) { return (void*)(((uintptr_t)workspace + kWorkspaceCopyOffset + 127) & ~(uintptr_t)127); }
 
-template <int DT, int FMT = SZO_FORMAT_UNIFORM, int TILE = 256, bool DUAL = false>
+template <int DT, int FMT = SZO_FORMAT_UNIFORM, int TILE = 256, bool DUAL = false, bool SHARED = false>
 static int launch_table(const ForwardTableArgs& t, int64_t blocks, hipStream_t stream) {
   static_assert(TILE == 256 || TILE == 128, "two workgroup tiles exist");
   constexpr int BM = TILE, BN = TILE;
   constexpr int WAVES_N = TILE == 256 ? 4 : 2, WMB = TILE == 256 ? 4 : 2;      // 2x4 waves of 128x64, or 2x2 of 64x64
   constexpr size_t main_bytes = 2 * (size_t)(BM + BN) * BK * sizeof(uint16_t) + (size_t)(BN / 64) * (kWindow * 6 + 128);
   constexpr size_t target_bytes = (size_t)BM * (BN * 2 + 32);
-  constexpr size_t lds_bytes = main_bytes > target_bytes ? main_bytes : target_bytes;
+  constexpr size_t lds_bytes = SHARED ? (size_t)SharedLds::BYTES : main_bytes > target_bytes ? main_bytes : target_bytes;
+  static_assert(lds_bytes >= main_bytes, "the sensitive product's buffers replace the operands");
   constexpr int BLK = TILE == 128 && DT == SZO_TILE_BF16 ? 32 : 16;            // as in dispatch_tile
-  auto kern = linear_fwd_table_kernel<2, WAVES_N, WMB, 2, DT, true, FMT, DUAL, BLK>;
+  auto kern = linear_fwd_table_kernel<2, WAVES_N, WMB, 2, DT, true, FMT, DUAL, BLK, SHARED>;
   static std::atomic<uint64_t> lds_limit_set{0};
   int rc = set_lds_limit_once(lds_limit_set, (const void*)kern, lds_bytes);
   if (rc != SZO_OK) return rc;
-  rc = timing_begin(stream);
+  if (!SHARED) rc = timing_begin(stream);                   // SHARED: its caller times the copies too
   if (rc != SZO_OK) return rc;
   kern<<<(unsigned)blocks, 128 * WAVES_N, lds_bytes, stream>>>(t.table, t.n_entries, t.inl);
   SZO_LAUNCH_CHECK();
-  return timing_end(stream);
+  return SHARED ? SZO_OK : timing_end(stream);
 }
 
 // Both forwards of every matrix of a step as ONE launch with the loss fused: 256x256 tiles, or 128x128
@@ -1202,6 +1218,111 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
   return launch_table<SZO_TILE_BF16>(t, first_block, stream);
 }
 
+// Whether the dense product once for both signs, with the sensitive products behind it, is faster than two products (dual-sign tiles): what
+// the second product takes against copying the activations and the sensitive products, in units of one column of K in one tile.  Fitted
+// to four to eight layers of 4096 x K at 4096 tokens, us per step, two products -> one: K = 256 / 1024 / 4096 at 0.1 % 212 / 497 / 843 -> 212 / 390 / 570,
+// at 0.4 % 212 / 508 / 872 -> 219 / 433 / 726, at 1 % 211 / 517 / 910 -> 238 / 610 / 1009.  The line is drawn for masks with rows full of
+// entries, whose bands take longer (a Llama block with half of them in 1 % of the rows, 0.4 % / 1 %: 2668 / 2956 -> 2498 / 4204).
+// Only in steps of more than 32 rounds of workgroups, several blocks: the losses of smaller ones are promised to be the single-layer calls'
+// up to the order of the partial sums, so that a block can be checked against those calls, which a weight rounded together with its
+// perturbation makes true and D +- eps Z does not (1e-9 of the loss apart).  It is no limit of the kernel: one Llama block at 4096 tokens 2630 -> 1750.
+static bool shared_pays(const szo_linear_desc* descs, int n) {
+  double tiles = 0.0, entries = 0.0, gain = 0.0;            // tiles: of 256 x 256 outputs, one workgroup each
+  for (int i = 0; i < n; ++i) {
+    const szo_linear_desc& d = descs[i];
+    if (d.M == 0 || d.N == 0) continue;
+    const double rows = (double)((d.M + 255) / 256), columns = (double)((d.N + 255) / 256), K = (double)d.K;
+    tiles += rows * columns;
+    gain += rows * (columns * (1.14 * K - 256.0) - 2.3 * K);
+    entries += rows * columns * (double)d.nnz / (double)d.N;
+  }
+  return tiles > 8192.0 && gain > 160.0 * entries;
+}
+
+// Both forwards of every matrix with the dense product computed once (szo_shared.h), the loss fused: launches of 256 x 256 tiles, each over as many
+// layers as the workspace has room for the activations of, in the order that its sensitive products read them.
+// SZO_EUNSUPPORTED, with nothing enqueued, when the stack does not qualify.
+static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, void* table_dev, void* copies,
+                           double* partials, int64_t* partials_per_sign, hipStream_t stream) {
+  constexpr int tile = 256;
+  int64_t T = 0;
+  auto copy_bytes = [](const szo_linear_desc& d) { return (size_t)((d.M + 63) / 64) * (size_t)d.K * 128; };
+  for (int i = 0; i < n; ++i) {                             // reject everything before anything is enqueued
+    const szo_linear_desc& d = descs[i];
+    if (d.tile_dtype != descs[0].tile_dtype || d.format != SZO_FORMAT_UNIFORM) return SZO_EUNSUPPORTED;
+    if (d.M == 0 || d.N == 0) continue;
+    if (d.x_minus || d.K >= (1 << 22) || copy_bytes(d) > kCopyAreaBytes) return SZO_EUNSUPPORTED;
+    T += ((d.M + tile - 1) / tile) * ((d.N + tile - 1) / tile);
+  }
+  if (T == 0 || 2 * T > kMaxLossPartials || sizeof(FwdParams) * (size_t)n > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;
+  const bool f16 = descs[0].tile_dtype == SZO_TILE_F16;
+  static thread_local std::vector<FwdParams> table;
+  int64_t offset = 0;
+  int rc = timing_begin(stream);
+  for (int i = 0; rc == SZO_OK && i < n;) {
+    table.clear();
+    TransposeArgs args;
+    args.n = 0;
+    args.blocks = 0;
+    size_t used = 0;
+    auto transpose = [&]() {
+      if (args.n == 0) return SZO_OK;
+      const unsigned grid = (args.blocks + 3u) / 4u;
+      if (f16) transpose_kernel<SZO_TILE_F16><<<grid, 256, 0, stream>>>(args);
+      else transpose_kernel<SZO_TILE_BF16><<<grid, 256, 0, stream>>>(args);
+      SZO_LAUNCH_CHECK();
+      args.n = 0;
+      args.blocks = 0;
+      return SZO_OK;
+    };
+    int64_t tiles = 0;
+    for (; rc == SZO_OK && i < n; ++i) {
+      const szo_linear_desc& d = descs[i];
+      if (d.M == 0 || d.N == 0) continue;
+      global_u16 copy = nullptr;
+      for (const FwdParams& e : table)                      // several matrices may be applied to the same activations
+        if (e.x == (global_u16)d.x && e.M == d.M && e.K == d.K) copy = e.x_minus;
+      if (!copy) {
+        if (used + copy_bytes(d) > kCopyAreaBytes) break;
+        uint16_t* const out = (uint16_t*)((char*)copies + used);
+        used += copy_bytes(d);
+        copy = (global_u16)out;
+        args.item[args.n++] = TransposeItem{(const uint16_t*)d.x, out, (int)d.M, (int)d.K, args.blocks};
+        args.blocks += (uint32_t)((d.M + 63) / 64) * (uint32_t)(d.K / 64);
+        if (args.n == (int)(sizeof(args.item) / sizeof(args.item[0]))) rc = transpose();
+        if (rc != SZO_OK) break;
+      }
+      FwdParams p;
+      rc = fill_params(p, &d, seed, step, +1, eps, partials + offset, 1.0 / ((double)d.M * (double)d.N));
+      p.x_minus = copy;
+      p.partials_minus = (global_f64_out)(partials + T + offset);
+      p.grid_m = (int)((d.M + tile - 1) / tile);
+      p.grid_n = (int)((d.N + tile - 1) / tile);
+      p.y = nullptr;
+      offset += (int64_t)p.grid_m * p.grid_n;
+      tiles += (int64_t)p.grid_m * p.grid_n;
+      table.push_back(p);
+    }
+    if (rc == SZO_OK) rc = transpose();
+    if (rc != SZO_OK) return rc;
+    // Longest K first, as above: the launch ends with its shortest tiles.
+    if (tiles <= 8192) std::stable_sort(table.begin(), table.end(), [](const FwdParams& a, const FwdParams& b) { return a.K > b.K; });
+    int64_t first_block = 0;
+    for (FwdParams& p : table) {
+      p.first_block = (int)first_block;
+      first_block += ((int64_t)p.grid_m * p.grid_n + 7) & ~(int64_t)7;      // fits: fewer than 2^20 tiles and 4096 entries
+    }
+    static thread_local ForwardTableArgs t;
+    rc = place_table(table.data(), table.size(), table_dev, stream, t);
+    if (rc != SZO_OK) return rc;
+    rc = f16 ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, true>(t, first_block, stream)
+             : launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, true>(t, first_block, stream);
+  }
+  if (rc != SZO_OK) return rc;
+  *partials_per_sign = T;
+  return timing_end(stream);
+}
+
 // Device address of `scratch` on the current device, looked up once per device.
 static int noalloc_partials(double** out) {
   constexpr int kMaxDevices = 64;
@@ -1294,7 +1415,7 @@ int szo_zo_step_noalloc(const szo_linear_desc* descs, int n, uint64_t seed, uint
 }
 
 int szo_set_tile_config(int config) {
-  if (config < 0 || config > 11) return SZO_EINVAL;
+  if (config < 0 || config > 12) return SZO_EINVAL;
   g_tile_config = config;
   small_m_force_rblocks(config == 4 ? 2 : config == 5 ? 3 : 0);
   small_m_force_stream_once(config == 7 || config == 10);
@@ -1361,7 +1482,7 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   void* const table_dev = (char*)workspace + kWorkspaceTableOffset;
   // Few-token stacks: one pass over the weights serves both forwards of the step.  SZO_STEP_ONE_DENSE_PASS: also at token counts
   // that the rule leaves to the tiled kernel.
-  const bool can_few = fuse && few_token_enabled() && n <= kMaxStepMatrices, asked_for = (flags & SZO_STEP_ONE_DENSE_PASS) != 0;
+  const bool can_few = fuse && few_token_enabled() && g_tile_config != 12 && n <= kMaxStepMatrices, asked_for = (flags & SZO_STEP_ONE_DENSE_PASS) != 0;
   const bool few_rule = can_few && small_m_eligible(descs, n, false, false, 2);
   const bool few = few_rule || (can_few && asked_for && small_m_eligible(descs, n, true, false, 2));
   // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip).
@@ -1377,8 +1498,9 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   }
   if (fuse) {
     int64_t T = 0;
-    rc = grouped_forwards(descs, n, seed, step, eps, (char*)workspace + kWorkspaceTableOffset, partial_area(workspace),
-                          &T, s);
+    const bool shared = g_tile_config == 12 || (g_tile_config == 0 && shared_pays(descs, n));
+    rc = shared ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
+    if (rc == SZO_EUNSUPPORTED) rc = grouped_forwards(descs, n, seed, step, eps, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK)
       return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
     if (rc != SZO_EUNSUPPORTED) return rc;

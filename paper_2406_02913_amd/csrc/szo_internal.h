@@ -38,7 +38,10 @@ constexpr size_t kWorkspaceHeader = 64;
 constexpr int kMaxStepMatrices = 4096;            // descriptor table of the few-token step
 constexpr size_t kTableBytesPerMatrix = 144;
 constexpr size_t kWorkspaceTableOffset = kWorkspaceHeader + sizeof(double) * (size_t)kMaxLossPartials;
-constexpr size_t kWorkspaceBytes = kWorkspaceTableOffset + kTableBytesPerMatrix * (size_t)kMaxStepMatrices;
+// Copies of activations, column by column, for the sensitive products of large steps: a step goes in launches of as many layers as fit.
+constexpr size_t kWorkspaceCopyOffset = kWorkspaceTableOffset + kTableBytesPerMatrix * (size_t)kMaxStepMatrices;
+constexpr size_t kCopyAreaBytes = (size_t)1 << 30;
+constexpr size_t kWorkspaceBytes = kWorkspaceCopyOffset + kCopyAreaBytes + 128;
 
 // loss_acc[0] += scale * sum of partials[0..count) in a fixed order (one workgroup).
 int reduce_partials(const double* partials, int count, double scale, double* loss_acc, hipStream_t stream);

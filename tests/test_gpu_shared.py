@@ -1,0 +1,150 @@
+"""GPU parity of the tiled kernel that computes one dense product for both forwards and the sensitive products behind it (forced by
+tile configuration 12, or chosen): ragged tiles, bands with no entries, with one more than a group of thirty-two and with more than
+are held at once, targets that are not staged, both tile types, infinite activations, and steps that take more than one launch."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import zo as ozo
+from paper_2406_02913_amd import szo
+from helpers import UpdateBound, clone, make_pair, sigma_g
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _auto_tile_config():
+    yield
+    szo.szo_set_tile_config(0)
+
+
+def _step(descs, config, lr=0.0, eps=1e-3, seed=9, step=0):
+    scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+    szo.szo_set_tile_config(config)
+    szo.szo_kernel_timing(True)
+    szo.szo_zo_step(descs, seed, step, eps, lr, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+    _, launches = szo.szo_kernel_timing_read()
+    szo.szo_kernel_timing(False)
+    assert launches == 1
+    return scal.cpu().numpy().copy()
+
+
+LAYERS = {            # (seed, M, N, K, group, density, mask)
+    "one_token_one_row": [(801, 1, 1, 64, 32, 5e-2, "uniform")],
+    "tile_exactly": [(802, 256, 256, 128, 128, 1e-2, "uniform")],
+    "one_more_each": [(803, 257, 257, 1088, 64, 1e-3, "uniform")],        # targets not staged
+    "half_a_tile": [(804, 129, 200, 320, 32, 2e-2, "uniform")],
+    "dense_mask": [(805, 70, 128, 2048, 128, 0.1, "uniform")],            # 13 000 entries per band: the window is refilled
+    "hot_rows": [(806, 300, 648, 1024, 128, 1e-2, "heavy_tail")],
+    "several": [(807, 200, 320, 512, 128, 2e-3, "uniform"), (808, 5, 64, 320, 64, 0.0, "uniform"),
+                (809, 330, 513, 384, 128, 2e-2, "uniform")],
+}
+
+
+@pytest.mark.parametrize("tile", ["f16", "bf16"])
+@pytest.mark.parametrize("name", sorted(LAYERS))
+def test_step_matches_oracle(name, tile):
+    dt = szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16
+    os_, ds_, base = [], [], 0
+    for sd, M, N, K, G, dens, kind in LAYERS[name]:
+        o, d = make_pair(sd, M, N, K, G, dens, kind=kind, nnz_base=base)
+        base += (o.sp_idx.size + 3) // 4 * 4
+        os_.append(o)
+        ds_.append(d)
+    ref = [clone(o) for o in os_]
+    sg, eps, lr = sigma_g(os_), 1e-3, 1e-3
+    bound = UpdateBound(sg, lr)
+    # as for the dual-sign tiles: an independent rounding error of ~1e-4 per output, averaged over the outputs
+    cells = sum(o.x_bits.shape[0] * o.codes.shape[0] for o in os_)
+    ltol, gtol = (max(1e-5, 2e-3 / np.sqrt(cells)), 1e-2) if tile == "f16" else (5e-3, 1e-1)
+    for step in range(2):
+        lp, lm, g = _step([d.desc(dt, with_y=False) for d in ds_], 12, lr, eps, 19, step)
+        r = ozo.zo_step(ref, 19, step, eps, lr)
+        size = max(r["loss_plus"], 1.0)
+        assert abs(lp - r["loss_plus"]) <= ltol * size and abs(lm - r["loss_minus"]) <= ltol * size, (lp, lm, r)
+        assert abs(g - r["g"]) <= gtol * max(abs(r["g"]), sg), (g, r["g"], sg)
+        bound.add(r, extra_dg=(gtol - 1e-2) * max(abs(r["g"]), sg))
+    for i, (o, d, om) in enumerate(zip(os_, ds_, ref)):
+        if o.sp_idx.size:
+            bound.check(i, d.sp_val.cpu().numpy(), om.sp_val, o.sp_val)
+
+
+# entries of one band: none, around a group, around what is held at once (480), and the second half of the rows after refills
+@pytest.mark.parametrize("nnz", [1, 31, 32, 33, 479, 480, 481, 1000])
+def test_groups_of_sensitive_entries(nnz):
+    o, d = make_pair(840 + nnz, 130, 64, 128, 128, nnz=nnz)
+    eps = 0.1                                                # z weighs as much as the values: one entry is 1 % of the outputs
+    lp, lm, g = _step([d.desc(with_y=False)], 12, eps=eps)
+    r = ozo.zo_step([clone(o)], 9, 0, eps, 0.0)
+    ltol = 2e-3 / np.sqrt(130 * 64)                          # as above
+    assert abs(lp - r["loss_plus"]) <= ltol * r["loss_plus"] and abs(lm - r["loss_minus"]) <= ltol * r["loss_minus"]
+    assert abs(g - r["g"]) <= 1e-2 * max(abs(r["g"]), sigma_g([o]))
+
+
+@pytest.mark.parametrize("what", ["infinite", "overflow"])
+def test_losses_are_infinite_where_every_output_has_a_value(what):
+    """As on the tiled kernel that adds the sensitive weights to the weight tile first (configuration 1)."""
+    o, d = make_pair(860, 70, 5, 320, 64, 2e-2)
+    column = int(np.flatnonzero((o.codes != 8).all(axis=0))[0])
+    if what == "infinite":
+        d.x[11, column] = float("inf")
+    else:
+        d.x[11].fill_(0)
+        d.x[11, column] = 3e38
+        d.scales.fill_(100.0)
+    values = d.sp_val.clone()
+    for eps in (1e-3, 0.0):
+        for config in (1, 12):
+            d.sp_val.copy_(values)
+            scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+            szo.szo_set_tile_config(config)
+            szo.szo_zo_step([d.desc(szo.TILE_BF16, with_y=False)], 3, 1, eps, 0.0, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
+            assert np.isposinf(scal.cpu().numpy()[:2]).all(), (config, eps, scal)
+
+
+def test_a_nan_spoils_the_losses():
+    _, d = make_pair(861, 300, 70, 320, 64, 2e-2)
+    d.x[270, 5] = float("nan")
+    assert np.isnan(_step([d.desc(with_y=False)], 12)[:2]).all()
+
+
+def _stack(seed, n, M, N, K, density, same_x):
+    """n descriptors of one layer, each with activations of its own (or one set for all)."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    _, d = make_pair(seed, 64, N, K, 128, density)
+    keep, descs = [d], []
+    for i in range(n):
+        if i == 0 or not same_x:
+            keep.append(torch.randn((M, K), generator=gen, device="cuda", dtype=torch.bfloat16))
+        desc = d.desc(with_y=False)
+        desc.M, desc.x = M, keep[-1].data_ptr()
+        descs.append(desc)
+    target = torch.randn((M, N), generator=gen, device="cuda", dtype=torch.bfloat16)
+    for desc in descs:
+        desc.target = target.data_ptr()
+    return descs, keep + [target]
+
+
+@pytest.mark.parametrize("same_x", [False, True])
+def test_a_step_of_several_launches_is_the_sum_of_its_layers(same_x):
+    """Five layers whose activations, 256 MiB each, do not all fit the workspace at once (or are one and the same)."""
+    descs, keep = _stack(871, 5, 8192, 64, 16384, 1e-4, same_x)
+    alone = [_step([d], 12) for d in descs]
+    s = _step(descs, 12)
+    total = np.sum(alone, axis=0)
+    assert np.allclose(s[:2], total[:2], rtol=1e-12, atol=0.0)               # the order of the partials
+    assert abs(s[2] - total[2]) <= 1e-12 * s[0] / 1e-3                       # ... over 2 eps
+    one_pass = _step(descs, 11)
+    assert np.allclose(s[:2], one_pass[:2], rtol=1e-5, atol=0.0)             # the scale rounded once per weight or not at all
+
+
+@pytest.mark.parametrize("density,config", [(1e-3, 12), (1e-2, 6)])
+def test_chosen_for_large_steps_with_sparse_masks(density, config):
+    """One layer short of 8192 tiles of 256 x 256 the products of the single-layer calls, beyond them the dense product once or, with denser
+    masks, still twice."""
+    descs, keep = _stack(881, 57, 2304, 4096, 1024, density, True)
+    assert np.array_equal(_step(descs[:56], 0), _step(descs[:56], 6))        # 8064 tiles
+    chosen = _step(descs, 0)
+    assert np.array_equal(chosen, _step(descs, 0)) and np.array_equal(chosen, _step(descs, config))
+    other = _step(descs, 18 - config)
+    assert not np.array_equal(chosen, other) and np.allclose(chosen[:2], other[:2], rtol=1e-5, atol=0.0)
