@@ -9,8 +9,9 @@
 // through registers and are turned into the matrix operand by the transposing LDS read.  Every wave has buffers of its own and none
 // waits for another.
 //
-// Two Llama blocks at 4096 tokens, 0.1 %, us: two full products in dual-sign tiles 5130, this 3350, of which the dense product and the
-// losses are 2730 and the copies 203 (576 MB read and written at 5.7 TB/s).  The same with x streamed through LDS again, 2 MB per
+// Two Llama blocks at 4096 tokens, 0.1 %, us: two full products in dual-sign tiles 5130, this 3290, of which the dense product and the
+// losses are 2730 and the copies 203 (576 MB read and written at 5.7 TB/s).  A group takes its entries from LDS while the one before is
+// multiplied, and the one-hot operand is read in two halves, which leaves the main loop all of its registers: 3350 without.  The same with x streamed through LDS again, 2 MB per
 // tile, and its columns gathered there 3960; with Z carried through the main loop of 256 x 128 tiles 4220.
 //
 // A buffer holds 32 "rows" (columns of x, or rows of targets) of 128 bytes; their 16-byte piece c stands in slot c ^ swizzle(row), so that the eight
@@ -105,7 +106,7 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
   auto buffer = [](uint64_t base, uint32_t bytes) { return rsrc_t{(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, bytes, 0x00027000u}; };
   auto load_rows = [&](rsrc_t rsrc, const uint32_t (&at)[4], uint32_t buf) {
     const uint32_t lds = (uint32_t)(uintptr_t)mine_lds + buf;
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 4\n\t"      // the buffer has been read
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 4\n\t"
                  "buffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %2, %5, 0 offen lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %3, %5, 0 offen lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
@@ -129,17 +130,19 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
 #pragma unroll 1
     for (uint32_t part = 0; part < 2; ++part) {
       const uint32_t o = 256u * part + 4u * (uint32_t)lane, j = s + o;
-      float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (eps != 0.0f) zbar_quad((p.nnz_base + j) >> 2, p.seed, p.step, z);
-      u32x4 column, word;
+      u32x4 column = {0u, 0u, 0u, 0u}, word = {0u, 0u, 0u, 0u};
+      if (s + 256u * part < hi) {
+        float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (eps != 0.0f) zbar_quad((p.nnz_base + j) >> 2, p.seed, p.step, z);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t idx = p.sp_idx[min(j + e, p.nnz - 1u)];        // clamped; entries past the end are never consumed
-        const uint32_t row = fast_div(idx, p.div_mul, p.div_shift);
-        uint16_t zb;
-        Frag<DT>::store(&zb, z[e]);
-        column[e] = (idx - row * (uint32_t)K) << 7;
-        word[e] = ((uint32_t)zb << 16) | (((row - (uint32_t)(band * 64)) & 63u) << 6);
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t idx = p.sp_idx[min(j + e, p.nnz - 1u)];      // clamped; entries past the end are never consumed
+          const uint32_t row = fast_div(idx, p.div_mul, p.div_shift);
+          uint16_t zb;
+          Frag<DT>::store(&zb, z[e]);
+          column[e] = (idx - row * (uint32_t)K) << 7;
+          word[e] = ((uint32_t)zb << 16) | (((row - (uint32_t)(band * 64)) & 63u) << 6);
+        }
       }
       if (o < (uint32_t)SH_WIN) {
         *reinterpret_cast<u32x4*>(win + o) = column;
@@ -154,34 +157,52 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
   // ---- what goes through the three buffers, in order: for each half of the wave's rows its groups of entries, then its targets in two
   //      parts.  Three are under way at any time ----
   int next_half = 0, next_item = 0, ahead = 0;              // ahead: loads under way
-  uint32_t next_buf = 0, word[3] = {1u, 1u, 1u};            // the slots' entries of the groups under way; odd: none
+  uint32_t next_buf = 0, word[4] = {1u, 1u, 1u, 1u};        // the slots' entries of the groups under way and of the next; odd: none
+  uint32_t column[4];                                       // of the next group: where this lane's pieces stand in a block of x
+  uint8_t* hot_at = sink;                                   // where this lane's last entry stands
+  auto look_ahead = [&]() {                                 // reads the next group's entries; anything if it is no group
+    const bool group = next_half < 2 && next_item < groups;
+    const uint32_t g0 = begin + 32u * (uint32_t)next_item;
+    if (group && (g0 < win_lo || g0 + 32u > win_hi)) fill(g0);
+    const uint32_t* const at = win + (group ? g0 - win_lo : 0u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) column[i] = at[8 * i + (lane >> 3)];
+    const uint32_t j = g0 + (uint32_t)lane, w = at[SH_WIN + (lane & 31)];
+    word[3] = group && lane < 32 && j >= lo && j < hi ? w : 1u;
+  };
   auto issue = [&](bool targets) {
     word[0] = word[1];
     word[1] = word[2];
-    if (next_half == 2) return;
-    const int block = 4 * bm + 2 * wm + next_half;
-    uint32_t at[4];
-    rsrc_t rsrc;
-    if (next_item < groups) {
-      const uint32_t g0 = begin + 32u * (uint32_t)next_item;
-      if (g0 < win_lo || g0 + 32u > win_hi) fill(g0);
-      const uint32_t* const columns = win + (g0 - win_lo);
+    word[2] = word[3];
+    __builtin_amdgcn_s_waitcnt(0xC07F);                     // lgkmcnt(0): the buffer has been read
+    if (next_half < 2) {
+      uint32_t at[4];
+      rsrc_t rsrc;
+      if (next_item < groups) {
+        const int block = 4 * bm + 2 * wm + next_half;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) at[i] = columns[8 * i + (lane >> 3)] + (piece ^ (64u * (uint32_t)(i & 1)));
-      const uint32_t j = g0 + (uint32_t)lane, w = columns[SH_WIN + (lane & 31)];
-      word[2] = lane < 32 && j >= lo && j < hi ? w : 1u;
-      rsrc = buffer((uint64_t)(uintptr_t)p.x_minus + (uint64_t)block * block_bytes, block < row_blocks ? block_bytes : 0u);
-    } else {
-      const int part = next_item - groups;
-      const uint32_t row = (uint32_t)(128 * wm + 64 * next_half + 32 * part + (lane >> 3)), pitch = 2u * (uint32_t)p.N;
+        for (int i = 0; i < 4; ++i) at[i] = column[i] + (piece ^ (64u * (uint32_t)(i & 1)));
+        rsrc = buffer((uint64_t)(uintptr_t)p.x_minus + (uint64_t)block * block_bytes, block < row_blocks ? block_bytes : 0u);
+      } else {
+        const int part = next_item - groups;
+        const uint32_t row = (uint32_t)(128 * wm + 64 * next_half + 32 * part + (lane >> 3)), pitch = 2u * (uint32_t)p.N;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) at[i] = (row + 8u * (uint32_t)i) * pitch + 2u * (uint32_t)(n0 + 64 * wn) + (piece ^ (64u * (uint32_t)(i & 1)));
-      rsrc = buffer((uint64_t)(uintptr_t)(p.target + (size_t)m0 * p.N), staged && targets ? (uint32_t)min(p.M - m0, 256) * pitch : 0u);
+        for (int i = 0; i < 4; ++i) at[i] = (row + 8u * (uint32_t)i) * pitch + 2u * (uint32_t)(n0 + 64 * wn) + (piece ^ (64u * (uint32_t)(i & 1)));
+        rsrc = buffer((uint64_t)(uintptr_t)(p.target + (size_t)m0 * p.N), staged && targets ? (uint32_t)min(p.M - m0, 256) * pitch : 0u);
+      }
+      load_rows(rsrc, at, next_buf);
+      ++ahead;
+      next_buf = next_buf == 2 * SH_BUF ? 0u : next_buf + SH_BUF;
+      if (++next_item == groups + 2) { next_item = 0; ++next_half; }
     }
-    load_rows(rsrc, at, next_buf);
-    ++ahead;
-    next_buf = next_buf == 2 * SH_BUF ? 0u : next_buf + SH_BUF;
-    if (++next_item == groups + 2) { next_item = 0; ++next_half; }
+  };
+  // For the groups after this: the one-hot operand of the next that is multiplied, the entries of the next that is fetched.
+  auto prepare = [&]() {
+    asm volatile("" ::: "memory");                          // (other types than what is read before and behind: order)
+    *reinterpret_cast<uint16_t*>(hot_at) = 0;
+    hot_at = (word[0] & 1u) ? sink : hot + (word[0] & 0xFC0u) + 2 * lane;
+    *reinterpret_cast<uint16_t*>(hot_at) = (uint16_t)(word[0] >> 16);
+    look_ahead();
   };
   uint32_t buf = 0;                                         // of the oldest load under way
   auto arrived = [&]() {
@@ -195,30 +216,32 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
   };
 
   float4_t accz[4][4];
-  uint8_t* hot_at = sink;                                   // where this lane's last entry stands
   const uint32_t from = (uint32_t)(8 * kg + (n >> 2)) * 128u + 16u * (uint32_t)((n >> 1) & 1) + 8u * (uint32_t)(n & 1);
   const uint32_t swizzle = 32u * (uint32_t)((n >> 3) | ((kg & 1) << 1));
   auto multiply = [&](bool targets) {
     arrived();
-    *reinterpret_cast<uint16_t*>(hot_at) = 0;
-    hot_at = (word[0] & 1u) ? sink : hot + (word[0] & 0xFC0u) + 2 * lane;
-    *reinterpret_cast<uint16_t*>(hot_at) = (uint16_t)(word[0] >> 16);
-    asm volatile("" ::: "memory");                          // (other types: the compiler may take the reads below for independent)
-    u32x4 a[4], b[4];
+    u32x4 a[4], b[2];
+    auto read_b = [&](int j) { return *reinterpret_cast<const u32x4*>(hot + (16 * j + n) * 64 + 16 * kg); };
+    auto product = [&](int j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) accz[i][j] = Frag<DT>::mfma16(__builtin_bit_cast(operand_t, a[i]), __builtin_bit_cast(operand_t, b[j & 1]), accz[i][j]);
+    };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const lds_bytes_t at = mine_lds + buf + from + ((32u * (uint32_t)i) ^ swizzle);
       const uint64_t first = read_transposed(at), second = read_transposed(at + 4 * 128);
       a[i] = u32x4{(uint32_t)first, (uint32_t)(first >> 32), (uint32_t)second, (uint32_t)(second >> 32)};
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) b[j] = *reinterpret_cast<const u32x4*>(hot + (16 * j + n) * 64 + 16 * kg);
+    b[0] = read_b(0);
     consumed(targets);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        accz[i][j] = Frag<DT>::mfma16(__builtin_bit_cast(operand_t, a[i]), __builtin_bit_cast(operand_t, b[j]), accz[i][j]);
+    b[1] = read_b(1);
+    product(0);
+    b[0] = read_b(2);
+    product(1);
+    b[1] = read_b(3);
+    product(2);
+    prepare();
+    product(3);
   };
 
   // With d = D - t the losses are sum d^2 +- 2 eps sum d Z + eps^2 sum Z^2; sixteen terms at a time in fp32, those sums in fp64.  The
@@ -230,18 +253,20 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
     constexpr int PART = decltype(part_tag)::value;         // 32 rows
     const int ml = 128 * wm + 64 * half + 4 * kg, nl = 64 * wn + n;
     const uint32_t base = (uint32_t)(m0 + ml) * (uint32_t)p.N + (uint32_t)(n0 + nl);         // M * N < 2^32 checked on the host
-    const uint32_t t0 = (uint32_t)(4 * kg) * 128u + ((uint32_t)((n >> 3) ^ (4 * (kg >> 1))) << 4) + 2u * (uint32_t)(n & 7);
+    const lds_bytes_t t0 = mine_lds + buf + (uint32_t)(4 * kg + (n >> 2)) * 128u + 16u * (uint32_t)((n >> 1) & 1) + 8u * (uint32_t)(n & 1);
+    const uint32_t t_swizzle = 32u * (uint32_t)((n >> 3) | ((kg >> 1) << 1));
 #pragma unroll
     for (int i = 2 * PART; i < 2 * PART + 2; ++i) {
       float dd = 0.0f, dz = 0.0f, zz = 0.0f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 4; ++j) {
+        const uint64_t four = STAGED ? read_transposed(t0 + 16 * (i & 1) * 128 + ((32u * (uint32_t)j) ^ t_swizzle)) : 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int dm = 16 * i + r, dn = 16 * j;
           if ((FULL || (m0 + ml + dm < p.M && n0 + nl + dn < p.N)) && !(AGAIN && special[ml + dm])) {
             uint32_t tb;
-            if (STAGED) tb = *reinterpret_cast<const uint16_t*>(mine + buf + (t0 ^ (uint32_t)((j << 5) ^ ((r >> 1) << 5))) + (16 * (i & 1) + r) * 128);
+            if (STAGED) tb = (uint32_t)(four >> (16 * r)) & 0xFFFFu;
             else tb = p.target[base + (uint32_t)dm * (uint32_t)p.N + (uint32_t)dn];
             const float t = __uint_as_float(tb << 16), df = half ? acc[4 + i][j][r] : acc[i][j][r], zf = accz[i][j][r];
             if (AGAIN) {
@@ -257,6 +282,7 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
             }
           }
         }
+      }
       sum_dd += (double)dd;
       sum_dz += (double)dz;
       sum_zz += (double)zz;
@@ -282,18 +308,20 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
       else if (staged) finish(half, which, F{}, T{}, F{});
       else finish(half, which, F{}, F{}, F{});
       consumed(!AGAIN);
+      prepare();
     };
     part(std::integral_constant<int, 0>{});
     part(std::integral_constant<int, 1>{});
   };
   auto begin_loads = [&](bool targets) {
     next_half = 0;
-    for (int i = 0; i < 3; ++i) issue(targets);
+    look_ahead();
+    for (int i = 0; i < 3; ++i) { issue(targets); prepare(); }
   };
   __syncthreads();                                          // every wave is done with the main loop's buffers
-  begin_loads(true);
 #pragma unroll
   for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(hot + 1024 * i + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
+  begin_loads(true);
   one_half(std::integral_constant<int, 0>{}, F{});
   one_half(std::integral_constant<int, 1>{}, F{});
   {
