@@ -77,13 +77,13 @@ def one_product_kernel(mats, M, two_sets=False, asked_for=False):
         # a few blocks: K split over the waves of a workgroup
         return "band_split_kernel" if M <= 64 and wgs * -(-M // 16) <= 600 else "small_m_kernel"
     if uniform and not two_sets:        # the tiled kernel with one dense product
-        tiles = gain = entries = 0.0
+        tiles = second = here = 0.0
         for m in mats:
             rows, columns = -(-M // 256), -(-m.N // 256)
             tiles += rows * columns
-            gain += rows * (columns * (1.14 * m.K - 256) - 2.3 * m.K)
-            entries += rows * columns * m.nnz / m.N
-        if tiles > 8192 and gain > 160 * entries:
+            second += rows * columns * 1.14 * m.K
+            here += rows * (columns * (256 + 160 * m.nnz / m.N) + 2.3 * m.K)
+        if tiles > 4096 and here < second:
             return SHARED_PRODUCT_KERNEL
     return None
 

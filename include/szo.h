@@ -169,8 +169,8 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * tokens, or launches of so few workgroups that any tile would outlast them, stream the weights once per 16 to 48 token rows; the
  * others run on the matrix cores in tiles of 64 token rows, if
  * the layers are of the uniform format with one tile type, fill the chip, and their masks are sparse (against the tiled kernel up to
- * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Steps of more than 8192 output tiles of 256 x 256 that those rules leave (several blocks beyond 2048
- * tokens) compute the dense product of such layers in tiles of that size, with weights rounded once to the tile's type, and the sensitive products behind
+ * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Steps of more than 4096 output tiles of 256 x 256 that those rules leave (a block at 8192
+ * tokens, several at 4096), and larger ones of 512 tiles and tokens on with the bf16 tile or groups other than 128, compute the dense product of such layers in tiles of that size, with weights rounded once to the tile's type, and the sensitive products behind
  * it, with masks of up to about 0.6 % (less with few rows of W or a short K): a copy of the activations in the workspace, 64 tokens of
  * a column side by side, serves them, and the step goes in launches of as many layers as it has room for (1 GiB).  Otherwise, and beyond 2048
  * tokens in steps of more than 2048 output tiles of 256 x 128, each layer runs as two full products, as the single-layer

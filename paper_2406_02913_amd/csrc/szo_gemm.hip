@@ -1223,20 +1223,27 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
 // to four to eight layers of 4096 x K at 4096 tokens, us per step, two products -> one: K = 256 / 1024 / 4096 at 0.1 % 212 / 497 / 843 -> 212 / 390 / 570,
 // at 0.4 % 212 / 508 / 872 -> 219 / 433 / 726, at 1 % 211 / 517 / 910 -> 238 / 610 / 1009.  The line is drawn for masks with rows full of
 // entries, whose bands take longer (a Llama block with half of them in 1 % of the rows, 0.4 % / 1 %: 2668 / 2956 -> 2498 / 4204).
-// Only in steps of more than 32 rounds of workgroups, several blocks: the losses of smaller ones are promised to be the single-layer calls'
+// Only in steps of more than 16 rounds of workgroups: the losses of smaller ones are promised to be the single-layer calls'
 // up to the order of the partial sums, so that a block can be checked against those calls, which a weight rounded together with its
-// perturbation makes true and D +- eps Z does not (1e-9 of the loss apart).  It is no limit of the kernel: one Llama block at 4096 tokens 2630 -> 1750.
-static bool shared_pays(const szo_linear_desc* descs, int n) {
-  double tiles = 0.0, entries = 0.0, gain = 0.0;            // tiles: of 256 x 256 outputs, one workgroup each
+// perturbation makes true and D +- eps Z does not (1e-9 of the loss apart).  It is no limit of the kernel: one Llama block at 4096 tokens, the
+// largest below the line that is checked like that, 2630 -> 1750.  Beyond it a Mistral block at 8192 tokens and 0.1 % / 0.4 % 5507 / 5612 -> 3535 / 4486.
+// `instead_of_onepass`: of a step that the kernel with tiles of 64 token rows would take, where that one rounds weights to the tile's type
+// too (bf16 tile, groups other than 128).  From 512 tiles and tokens on, with a third of the second product to spare: bf16 tile, 0.1 %,
+// there -> here: one Llama block at 768 / 1000 / 2048 tokens 473 / 601 / 1184 -> 384 / 467 / 864, four OPT blocks at 520 / 1300 1374 / 3113 ->
+// 1180 / 2351, 0.3 % at 2048 tokens 1407 -> 1030; groups of 64 likewise 435 / 545 / 1063 -> 375 / 460 / 843, 1225 / 2783 -> 1156 / 2284, 1289 -> 1000.
+// Fewer tiles: one OPT block at 768 tokens (432) 410 -> 446, a layer of 4096 x 4096 at 2048 (128) 96 -> 117.
+static bool shared_pays(const szo_linear_desc* descs, int n, bool instead_of_onepass) {
+  double tiles = 0.0, second = 0.0, here = 0.0;             // tiles: of 256 x 256 outputs, one workgroup each
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc& d = descs[i];
     if (d.M == 0 || d.N == 0) continue;
+    if (instead_of_onepass && (d.M <= 512 || (d.tile_dtype == SZO_TILE_F16 && d.group == 128))) return false;
     const double rows = (double)((d.M + 255) / 256), columns = (double)((d.N + 255) / 256), K = (double)d.K;
     tiles += rows * columns;
-    gain += rows * (columns * (1.14 * K - 256.0) - 2.3 * K);
-    entries += rows * columns * (double)d.nnz / (double)d.N;
+    second += rows * columns * 1.14 * K;
+    here += rows * (columns * (256.0 + 160.0 * (double)d.nnz / (double)d.N) + 2.3 * K);
   }
-  return tiles > 8192.0 && gain > 160.0 * entries;
+  return instead_of_onepass ? tiles >= 512.0 && here < 0.65 * second : tiles > 4096.0 && here < second;
 }
 
 // Both forwards of every matrix with the dense product computed once (szo_shared.h), the loss fused: launches of 256 x 256 tiles, each over as many
@@ -1485,10 +1492,14 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   const bool can_few = fuse && few_token_enabled() && g_tile_config != 12 && n <= kMaxStepMatrices, asked_for = (flags & SZO_STEP_ONE_DENSE_PASS) != 0;
   const bool few_rule = can_few && small_m_eligible(descs, n, false, false, 2);
   const bool few = few_rule || (can_few && asked_for && small_m_eligible(descs, n, true, false, 2));
-  // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip).
+  // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip; in large launches with rounded weights
+  // the tiled kernel).
   {
     int64_t T = 0;
-    rc = onepass_forwards(descs, n, seed, step, eps, few_rule, asked_for, !fuse, table_dev, partial_area(workspace), &T, s);
+    const bool in_tiles = g_tile_config == 0 && fuse && shared_pays(descs, n, true) && onepass_partials(descs, n, few_rule, asked_for, false, false) > 0;
+    rc = in_tiles ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
+    if (rc == SZO_EUNSUPPORTED)
+      rc = onepass_forwards(descs, n, seed, step, eps, few_rule, asked_for, !fuse, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK) return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
     if (rc != SZO_EUNSUPPORTED) return rc;      // otherwise nothing was enqueued
   }
@@ -1498,7 +1509,7 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   }
   if (fuse) {
     int64_t T = 0;
-    const bool shared = g_tile_config == 12 || (g_tile_config == 0 && shared_pays(descs, n));
+    const bool shared = g_tile_config == 12 || (g_tile_config == 0 && shared_pays(descs, n, false));
     rc = shared ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
     if (rc == SZO_EUNSUPPORTED) rc = grouped_forwards(descs, n, seed, step, eps, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK)

@@ -108,15 +108,15 @@ def test_a_nan_spoils_the_losses():
     assert np.isnan(_step([d.desc(with_y=False)], 12)[:2]).all()
 
 
-def _stack(seed, n, M, N, K, density, same_x):
+def _stack(seed, n, M, N, K, density, same_x, group=128, tile=szo.TILE_F16):
     """n descriptors of one layer, each with activations of its own (or one set for all)."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
-    _, d = make_pair(seed, 64, N, K, 128, density)
+    _, d = make_pair(seed, 64, N, K, group, density)
     keep, descs = [d], []
     for i in range(n):
         if i == 0 or not same_x:
             keep.append(torch.randn((M, K), generator=gen, device="cuda", dtype=torch.bfloat16))
-        desc = d.desc(with_y=False)
+        desc = d.desc(tile, with_y=False)
         desc.M, desc.x = M, keep[-1].data_ptr()
         descs.append(desc)
     target = torch.randn((M, N), generator=gen, device="cuda", dtype=torch.bfloat16)
@@ -140,11 +140,26 @@ def test_a_step_of_several_launches_is_the_sum_of_its_layers(same_x):
 
 @pytest.mark.parametrize("density,config", [(1e-3, 12), (1e-2, 6)])
 def test_chosen_for_large_steps_with_sparse_masks(density, config):
-    """One layer short of 8192 tiles of 256 x 256 the products of the single-layer calls, beyond them the dense product once or, with denser
+    """One layer short of 4096 tiles of 256 x 256 the products of the single-layer calls, beyond them the dense product once or, with denser
     masks, still twice."""
-    descs, keep = _stack(881, 57, 2304, 4096, 1024, density, True)
-    assert np.array_equal(_step(descs[:56], 0), _step(descs[:56], 6))        # 8064 tiles
+    descs, keep = _stack(881, 29, 2304, 4096, 1024, density, True)
+    assert np.array_equal(_step(descs[:28], 0), _step(descs[:28], 6))        # 4032 tiles
     chosen = _step(descs, 0)
     assert np.array_equal(chosen, _step(descs, 0)) and np.array_equal(chosen, _step(descs, config))
     other = _step(descs, 18 - config)
     assert not np.array_equal(chosen, other) and np.allclose(chosen[:2], other[:2], rtol=1e-5, atol=0.0)
+
+
+@pytest.mark.parametrize("group,tile", [(128, "f16"), (64, "f16"), (128, "bf16")])
+def test_chosen_from_512_tiles_on_where_both_kernels_round_the_weights(group, tile):
+    """The kernel with tiles of 64 token rows has groups of 128 with the fp16 tile, which it does not round, and fewer tiles; asked for
+    or not."""
+    descs, keep = _stack(891, 11, 768, 4096, 1024, 1e-3, True, group, szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16)
+    for n, config in ((10, 11), (11, 11 if (group, tile) == (128, "f16") else 12)):        # 480 and 528 tiles
+        chosen, other = _step(descs[:n], 0), _step(descs[:n], 23 - config)
+        assert np.array_equal(chosen, _step(descs[:n], config)) and not np.array_equal(chosen, other)
+        assert np.allclose(chosen[:2], other[:2], rtol=1e-5, atol=0.0)
+        asked = torch.zeros(3, dtype=torch.float64, device="cuda")
+        szo.szo_set_tile_config(0)
+        szo.szo_zo_step(descs[:n], 9, 0, 1e-3, 0.0, asked, szo.new_workspace(), szo.STEP_FUSED_LOSS | szo.STEP_ONE_DENSE_PASS)
+        assert np.array_equal(chosen, asked.cpu().numpy())
