@@ -29,9 +29,9 @@ PEAK_HBM_GBS = 8000.0                # MI355X HBM3E
 # HBM bytes per launch of the dominant kernel, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
 # script scaled by a plain copy of known size (profiles/*.md give the commands and the raw readings).
 # Only valid for the unmodified workloads; anything else reports null.
-MEASURED_TRAFFIC_BYTES = {"c3m16": 3.613e9,
+MEASURED_TRAFFIC_BYTES = {"c3": 1.756e11, "c3m16": 3.613e9,
                           # the extra legs of the default run (one Mistral block by density, 32 OPT blocks by token count)
-                          "c4:0.0001": 4.290e9, "c4:0.001": 4.318e9, "c4:0.01": 5.305e9,
+                          "c4:0.001": 6.35e9, "c4:0.01": 5.305e9,
                           "c5:1": 3.447e9, "c5:16": 3.586e9, "c5:64": 4.237e9}
 
 SHARED_PRODUCT_KERNEL = "linear_fwd_table_kernel (one dense product), transpose_kernel"      # timed as one launch

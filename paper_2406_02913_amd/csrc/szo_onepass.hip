@@ -666,9 +666,10 @@ void onepass_force(int how) { g_force_onepass = how; }
 //    rows of tiles, the last round and the launches per layer weigh as much as the second product.  One Llama block at 520 /
 //    1000 / 2048 tokens 582 / 809 / 1416 -> 326 / 548 / 1064; single layers at 600 / 2048 / 8192 tokens: 4096 x 4096 122 / 175 / 462 -> 67 / 101 /
 //    352, 1024 x 1024 45 / 41 / 58 -> 19 / 24 / 40, 1024 x 16384 433 / 427 / 672 -> 98 / 180 / 359.  Larger steps keep two
-//    products unless asked, up to several blocks: their losses are the single-layer calls' up to the order of the partial sums (a Mistral
-//    block at 8192 tokens 5865 -> 4568 on request).  The largest are the tiled kernel's with one dense product (four Llama blocks
-//    at 4096 tokens here / there 8100 / 6700).  Tiles are counted over the step, so the same layers in smaller
+//    products unless asked, up to 4096 tiles of 256 x 256: their losses are the single-layer calls' up to the order of the partial sums.
+//    Beyond that they are the tiled kernel's with one dense product (four Llama blocks at 4096 tokens here / there 8100 / 6570, a Mistral
+//    block at 8192 4358 / 3420), which also takes steps of this kernel from 512 of those tiles on where this one rounds
+//    the weights as well (shared_pays in szo_gemm.hip).  Tiles are counted over the step, so the same layers in smaller
 //    steps may fall on the other side of the line, where losses and g differ by the roundings that szo.h describes.
 //  * with the outputs written (flags = 0) the other path is two tiled launches and two passes over y per layer: one Llama
 //    block at 1 / 256 / 1024 tokens 1044 / 1063 / 1508 -> 150 / 189 / 621; rho = 0.01, 1024 tokens: 1836 -> 1128.
