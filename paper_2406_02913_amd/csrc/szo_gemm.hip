@@ -1258,7 +1258,7 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
     const szo_linear_desc& d = descs[i];
     if (d.tile_dtype != descs[0].tile_dtype || d.format != SZO_FORMAT_UNIFORM) return SZO_EUNSUPPORTED;
     if (d.M == 0 || d.N == 0) continue;
-    if (d.x_minus || d.K >= (1 << 22) || copy_bytes(d) > kCopyAreaBytes) return SZO_EUNSUPPORTED;
+    if (d.x_minus || d.K >= (1 << 21) || copy_bytes(d) > kCopyAreaBytes) return SZO_EUNSUPPORTED;      // offsets within a tile's rows of x: 31 bits
     T += ((d.M + tile - 1) / tile) * ((d.N + tile - 1) / tile);
   }
   if (T == 0 || 2 * T > kMaxLossPartials || sizeof(FwdParams) * (size_t)n > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;

@@ -114,7 +114,7 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
                  "s"(lds), "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "s"(rsrc) : "memory", "scc");
   };
   const uint32_t piece = 16u * (uint32_t)((lane & 7) ^ (2 * ((lane >> 4) & 1)));       // row 8 i + lane / 8: ^ 64 for odd i
-  const uint32_t block_bytes = 128u * (uint32_t)K;          // K < 2^22
+  const uint32_t block_bytes = 128u * (uint32_t)K;          // K < 2^21
   const int row_blocks = (p.M + 63) / 64;
   const bool staged = ((p.N & 7) == 0) && ((reinterpret_cast<uintptr_t>(p.target) & 15) == 0) && p.N < (1 << 22);
 
