@@ -106,12 +106,17 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
   auto buffer = [](uint64_t base, uint32_t bytes) { return rsrc_t{(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, bytes, 0x00027000u}; };
   auto load_rows = [&](rsrc_t rsrc, const uint32_t (&at)[4], uint32_t buf) {
     const uint32_t lds = (uint32_t)(uintptr_t)mine_lds + buf;
+    // m0 is no register that values are allocated to, which the compiler warns of; named all the same, so that none of its own
+    // settings of m0 is taken to live on behind these
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 4\n\t"
                  "buffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %2, %5, 0 offen lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %3, %5, 0 offen lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %4, %5, 0 offen lds" ::
-                 "s"(lds), "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "s"(rsrc) : "memory", "scc");
+                 "s"(lds), "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "s"(rsrc) : "memory", "scc", "m0");
+#pragma clang diagnostic pop
   };
   const uint32_t piece = 16u * (uint32_t)((lane & 7) ^ (2 * ((lane >> 4) & 1)));       // row 8 i + lane / 8: ^ 64 for odd i
   const uint32_t block_bytes = 128u * (uint32_t)K;          // K < 2^21

@@ -102,3 +102,44 @@ def test_no_matrix_instruction_reads_an_inline_assembly_result(tmp_path):
         assert not hits, (src, hits[:3])
     # the kernels this is about are really in there, matrix instructions included
     assert sum(t.count("v_mfma_f32_32x32x16") for t in texts) > 100 and sum(t.count("v_mfma_f32_16x16x32") for t in texts) > 100
+
+
+def asm_statements(source):
+    """[(instructions, clobbers)] of a source file's inline assembly; comments are left out."""
+    source = re.sub(r"//[^\n]*", "", source)
+    out = []
+    for m in re.finditer(r"\basm\s*(?:volatile\s*)?\(", source):
+        depth, i, quoted, parts, start = 1, m.end(), False, [], m.end()
+        while depth:
+            c = source[i]
+            if c == '"' and source[i - 1] != "\\":
+                quoted = not quoted
+            elif not quoted:
+                depth += (c in "([{") - (c in ")]}")
+                if c == ":" and depth == 1:
+                    parts.append(source[start:i])
+                    start = i + 1
+            i += 1
+        parts.append(source[start:i - 1])
+        text = lambda p: "".join(re.findall(r'"([^"]*)"', p)).replace("\\n", "\n").replace("\\t", "")
+        out.append((text(parts[0]).split("\n"), re.findall(r'"([^"]*)"', parts[3]) if len(parts) > 3 else []))
+    return out
+
+
+def undeclared_m0(source):
+    """Inline assembly that writes m0 without saying so: the compiler may keep a value of its own there."""
+    return [code for code, clobbers in asm_statements(source)
+            if any(re.match(r"\s*s_\w+\s+m0\b", line) for line in code) and "m0" not in clobbers]
+
+
+def test_inline_assembly_that_writes_m0_says_so():
+    planted = 'asm volatile("s_mov_b32 m0, %0\\n\\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(a), "v"(b), "s"(c) : "memory", "scc");'
+    assert len(undeclared_m0(planted)) == 1
+    assert undeclared_m0(planted.replace('"scc"', '"scc", "m0"')) == [] and undeclared_m0(planted.replace("s_mov_b32 m0", "s_mov_b32 s0")) == []
+    seen = 0
+    for name in sorted(os.listdir(szo_build.CSRC)):
+        if name.endswith((".h", ".hip")):
+            source = open(os.path.join(szo_build.CSRC, name)).read()
+            seen += len(asm_statements(source))
+            assert not undeclared_m0(source), name
+    assert seen > 5
