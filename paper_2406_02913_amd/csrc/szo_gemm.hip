@@ -41,6 +41,7 @@ static __device__ __align__(256) double scratch[kNoAllocMaxPartials];
 namespace szo {
 
 // LDS of a tile: two stages of both operands, the weight waves' windows and write sinks.
+enum { kNotShared, kShared, kSharedFp64Sums };              // SHARED below
 constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int)sizeof(uint16_t) + (bn / 64) * (kWindow * 6 + 128); }
 
 // Workgroup = WAVES_M x WAVES_N waves; each wave computes (32*WMB) x (32*WNB) outputs.
@@ -60,7 +61,7 @@ constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int
 // wave row compute the +eps forward, the others the -eps forward; every MFMA of both forwards is
 // executed, only the staging of the weights is shared.  The MFMA loop is the same as without DUAL.
 // SHARED (likewise, sparse masks): D of 256 x 256 outputs, without the perturbation, and behind it the sensitive products that both
-// forwards add to it (szo_shared.h).
+// forwards add to it (szo_shared.h), the losses summed sixteen at a time in fp32 or one by one in fp64.
 //
 // KS = 2 (a launch of few 128 x 128 tiles): eight waves, of which the second four compute the second half of the K steps in
 // buffers of their own.  Such a launch is bound by a weight wave's chain, ~220 instructions per K step at one wave on its SIMD
@@ -68,7 +69,7 @@ constexpr int tiled_lds_bytes(int bm, int bn) { return 2 * (bm + bn) * BK * (int
 // the sums of half of the tile's rows.
 //
 // BLK: the matrix instruction, 16x16x32 or 32x32x16 (see below).  GROUPED: a grouped launch, which never writes y.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1, int BLK = 16, bool GROUPED = false, bool SHARED = false>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int KS = 1, int BLK = 16, bool GROUPED = false, int SHARED = kNotShared>
 __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm, const int bn,
                                                 const uint32_t __attribute__((address_space(4)))* entry = nullptr) {
   constexpr int NWAVES = WAVES_M * WAVES_N;
@@ -671,7 +672,7 @@ __device__ __forceinline__ void linear_fwd_body(const FwdParams& p, const int bm
 
   if constexpr (SHARED) {
     static_assert(!DUAL && KS == 1 && BLK == 16 && BM == 256 && BN == 256 && FUSE_LOSS, "256 x 256 outputs, one launch for both signs");
-    shared_tail<DT>(acc, cold, bm, bn, reinterpret_cast<uint8_t*>(smem));
+    shared_tail<DT, SHARED == kSharedFp64Sums>(acc, cold, bm, bn, reinterpret_cast<uint8_t*>(smem));
     return;
   }
   // ---- epilogue: in quads, of four rows in one column for each lane.  Register r of quad (i,j) of a wave tile holds
@@ -874,7 +875,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KS) linear_fwd_kernel
 // again later.  Workgroups between an entry's last tile and the next multiple of 8 have nothing to do.
 // With DUAL an entry has grid_m * grid_n workgroups, each computing both forwards of a tile of half the
 // width (see linear_fwd_body); the 32 workgroups resident on an XCD are then 2 x 16 such tiles.
-template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int BLK = 16, bool SHARED = false>
+template <int WAVES_M, int WAVES_N, int WMB, int WNB, int DT, bool FUSE_LOSS, int FMT, bool DUAL = false, int BLK = 16, int SHARED = kNotShared>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_fwd_table_kernel(const FwdParams* table, int n_entries, InlineForwards) {
   constexpr int W = (int)(sizeof(FwdParams) / 4), FB = (int)(offsetof(FwdParams, first_block) / 4);
   static_assert(sizeof(FwdParams) % 4 == 0 && offsetof(FwdParams, first_block) % 4 == 0, "table entry is read as words");
@@ -1092,7 +1093,7 @@ static int update_all(const szo_linear_desc* descs, int n, uint64_t seed, uint64
 static double* partial_area(void* workspace) { return (double*)((char*)workspace + kWorkspaceHeader); }
 static void* copy_area(void* workspace) { return (void*)(((uintptr_t)workspace + kWorkspaceCopyOffset + 127) & ~(uintptr_t)127); }
 
-template <int DT, int FMT = SZO_FORMAT_UNIFORM, int TILE = 256, bool DUAL = false, bool SHARED = false>
+template <int DT, int FMT = SZO_FORMAT_UNIFORM, int TILE = 256, bool DUAL = false, int SHARED = kNotShared>
 static int launch_table(const ForwardTableArgs& t, int64_t blocks, hipStream_t stream) {
   static_assert(TILE == 256 || TILE == 128, "two workgroup tiles exist");
   constexpr int BM = TILE, BN = TILE;
@@ -1218,6 +1219,9 @@ static int grouped_forwards(const szo_linear_desc* descs, int n, uint64_t seed, 
   return launch_table<SZO_TILE_BF16>(t, first_block, stream);
 }
 
+// Whether the one-dense-pass kernel rounds a layer's weights to the tile's type too (the others' scales it applies in fp32).
+static bool onepass_rounds(const szo_linear_desc& d) { return d.tile_dtype == SZO_TILE_BF16 || d.group != 128; }
+
 // Whether the dense product once for both signs, with the sensitive products behind it, is faster than two products (dual-sign tiles): what
 // the second product takes against copying the activations and the sensitive products, in units of one column of K in one tile.  Fitted
 // to four to eight layers of 4096 x K at 4096 tokens, us per step, two products -> one: K = 256 / 1024 / 4096 at 0.1 % 212 / 497 / 843 -> 212 / 390 / 570,
@@ -1237,7 +1241,7 @@ static bool shared_pays(const szo_linear_desc* descs, int n, bool instead_of_one
   for (int i = 0; i < n; ++i) {
     const szo_linear_desc& d = descs[i];
     if (d.M == 0 || d.N == 0) continue;
-    if (instead_of_onepass && (d.M <= 512 || (d.tile_dtype == SZO_TILE_F16 && d.group == 128))) return false;
+    if (instead_of_onepass && (d.M <= 512 || !onepass_rounds(d))) return false;
     const double rows = (double)((d.M + 255) / 256), columns = (double)((d.N + 255) / 256), K = (double)d.K;
     tiles += rows * columns;
     second += rows * columns * 1.14 * K;
@@ -1263,6 +1267,9 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
   }
   if (T == 0 || 2 * T > kMaxLossPartials || sizeof(FwdParams) * (size_t)n > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;
   const bool f16 = descs[0].tile_dtype == SZO_TILE_F16;
+  // Steps that the one-dense-pass kernel would take have its sums, one by one in fp64: the layers that tell them apart.
+  bool fp64_sums = true;
+  for (int i = 0; i < n; ++i) fp64_sums = fp64_sums && (descs[i].M == 0 || descs[i].N == 0 || onepass_rounds(descs[i]));
   static thread_local std::vector<FwdParams> table;
   int64_t offset = 0;
   int rc = timing_begin(stream);
@@ -1322,8 +1329,9 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
     static thread_local ForwardTableArgs t;
     rc = place_table(table.data(), table.size(), table_dev, stream, t);
     if (rc != SZO_OK) return rc;
-    rc = f16 ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, true>(t, first_block, stream)
-             : launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, true>(t, first_block, stream);
+    rc = !f16      ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, first_block, stream)
+         : fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, first_block, stream)
+                     : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, first_block, stream);
   }
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;

@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) transpose_kernel(TransposeArgs t) {
     }
 }
 
-template <int DT, typename ReadEntry>
+template <int DT, bool FP64_SUMS, typename ReadEntry>
 __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEntry& cold, const int bm, const int bn, uint8_t* const smem) {
   typedef typename Frag<DT>::type operand_t;
   const FwdParams p = cold();
@@ -249,8 +249,10 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
     product(3);
   };
 
-  // With d = D - t the losses are sum d^2 +- 2 eps sum d Z + eps^2 sum Z^2; sixteen terms at a time in fp32, those sums in fp64.  The
-  // difference of the losses, which g is made of, is summed as such.
+  // With d = D - t the losses are sum d^2 +- 2 eps sum d Z + eps^2 sum Z^2; the difference of the losses, which g is made of, is summed as
+  // such.  FP64_SUMS: squares and products, exact there, are added one by one in fp64, as in the one-dense-pass kernel; otherwise
+  // sixteen at a time in fp32 and those sums in fp64, as in the dual-sign tiles: 1.7 us less of 151 per tile at K = 4096 (32 Llama blocks
+  // at 4096 tokens 59.7 -> 59.1 ms), a few 1e-9 of the losses.
   double loss_plus = 0.0, loss_minus = 0.0, sum_dd = 0.0, sum_dz = 0.0, sum_zz = 0.0;
   uint8_t* const special = smem + SharedLds::SPECIAL;       // AGAIN: token rows that are left out
   auto finish = [&](int half, auto part_tag, auto full_tag, auto staged_tag, auto again_tag) {
@@ -279,6 +281,11 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
               const double dp = (double)(df + ez) - (double)t, dmn = (double)(df - ez) - (double)t;
               loss_plus = fma(dp, dp, loss_plus);
               loss_minus = fma(dmn, dmn, loss_minus);
+            } else if (FP64_SUMS) {
+              const double d = (double)(df - t), z = (double)zf;
+              sum_dd = fma(d, d, sum_dd);
+              sum_dz = fma(d, z, sum_dz);
+              sum_zz = fma(z, z, sum_zz);
             } else {
               const float d = df - t;
               dd = fmaf(d, d, dd);
@@ -288,9 +295,11 @@ __device__ __forceinline__ void shared_tail(float4_t (&acc)[8][4], const ReadEnt
           }
         }
       }
-      sum_dd += (double)dd;
-      sum_dz += (double)dz;
-      sum_zz += (double)zz;
+      if (!AGAIN && !FP64_SUMS) {
+        sum_dd += (double)dd;
+        sum_dz += (double)dz;
+        sum_zz += (double)zz;
+      }
     }
   };
   using T = std::true_type;

@@ -163,3 +163,33 @@ def test_chosen_from_512_tiles_on_where_both_kernels_round_the_weights(group, ti
         szo.szo_set_tile_config(0)
         szo.szo_zo_step(descs[:n], 9, 0, 1e-3, 0.0, asked, szo.new_workspace(), szo.STEP_FUSED_LOSS | szo.STEP_ONE_DENSE_PASS)
         assert np.array_equal(chosen, asked.cpu().numpy())
+
+
+@pytest.mark.parametrize("tile", ["f16", "bf16"])
+@pytest.mark.parametrize("M,N", [(256, 512), (300, 520), (70, 257)])        # whole tiles, ragged ones, targets that are not staged
+def test_losses_are_added_in_fp64(M, N, tile):
+    """Zero weights and one sensitive entry of value zero in every row of W: with x in eighths the outputs +- eps x z are exact in fp32, and
+    so are their squares in fp64.  What is left is the order of those sums, 2^-53 of the loss per term and far less in the mean (1e-13 is a
+    fifth of all M N of the smallest roundings one way); sixteen terms at a time in fp32, as where the weights are rounded by this kernel
+    alone (fp16 tile, groups of 128), leave up to 4e-9."""
+    dt, as16 = (szo.TILE_BF16, torch.bfloat16) if tile == "bf16" else (szo.TILE_F16, torch.float16)
+    K, group, eps, seed, step = 128, 64, 0.5, 7, 3
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    column = torch.randint(K, (N,), generator=gen, device="cuda")
+    tile_ptr, sp_idx, _ = szo.szo_tcsr_build(N, K, (torch.arange(N, device="cuda") * K + column).cpu().numpy().astype(np.uint32))
+    q, scales = np.full((N, K // 2), 0x88, dtype=np.uint8), np.full((N, K // group), 0.01, dtype=np.float16)
+    q, scales = szo.szo_layout_weights(q, scales, group)
+    dev = lambda a, t: torch.from_numpy(a.view(t)).cuda()
+    idx, ptr, qd, sd = dev(sp_idx, np.int32), dev(tile_ptr, np.int32), dev(q, np.uint8), dev(scales, np.float16)
+    x = (torch.randint(-64, 65, (M, K), generator=gen, device="cuda") / 8.0).bfloat16()
+    target, values = torch.randn((M, N), generator=gen, device="cuda").bfloat16(), torch.zeros(N, device="cuda")
+    desc = szo.make_desc(M, N, K, group, N, 0, x, qd, sd, ptr, idx, values, None, target, dt)
+    lp, lm, _ = _step([desc], 12, eps=eps, seed=seed, step=step)
+    z = torch.empty(N, device="cuda")
+    szo.szo_debug_zbar(0, N, seed, step, None, z)
+    flat = idx.long()
+    Z = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    Z[:, flat // K] = x.double()[:, flat % K] * z.to(as16).double()
+    for got, sign in ((lp, 1.0), (lm, -1.0)):
+        want = float(((sign * eps * Z - target.double()) ** 2).mean())
+        assert abs(got - want) <= 1e-13 * want, (got, want)
