@@ -23,6 +23,7 @@
 // its tile from the window into the weight tile.
 #include <algorithm>
 #include <cstddef>
+#include <unordered_map>
 #include <vector>
 #include "szo_internal.h"
 #include "szo_rng.h"
@@ -1270,45 +1271,38 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
   // Steps that the one-dense-pass kernel would take have its sums, one by one in fp64: the layers that tell them apart.
   bool fp64_sums = true;
   for (int i = 0; i < n; ++i) fp64_sums = fp64_sums && (descs[i].M == 0 || descs[i].N == 0 || onepass_rounds(descs[i]));
+  // One table for the whole step, staged once: the host runs as many steps ahead as with one launch.
+  struct Launch { size_t first, items; int64_t blocks; };   // its first entry, the end of its copies, its workgroups
   static thread_local std::vector<FwdParams> table;
+  static thread_local std::vector<TransposeItem> items;
+  static thread_local std::vector<Launch> launches;
+  static thread_local std::unordered_map<const void*, size_t> copy_of;      // the launch's latest copy of these activations
+  table.clear();
+  items.clear();
+  launches.clear();
   int64_t offset = 0;
-  int rc = timing_begin(stream);
-  for (int i = 0; rc == SZO_OK && i < n;) {
-    table.clear();
-    TransposeArgs args;
-    args.n = 0;
-    args.blocks = 0;
+  bool staged = false;
+  for (int i = 0; i < n;) {
+    Launch l = {table.size(), 0, 0};
+    copy_of.clear();
     size_t used = 0;
-    auto transpose = [&]() {
-      if (args.n == 0) return SZO_OK;
-      const unsigned grid = (args.blocks + 3u) / 4u;
-      if (f16) transpose_kernel<SZO_TILE_F16><<<grid, 256, 0, stream>>>(args);
-      else transpose_kernel<SZO_TILE_BF16><<<grid, 256, 0, stream>>>(args);
-      SZO_LAUNCH_CHECK();
-      args.n = 0;
-      args.blocks = 0;
-      return SZO_OK;
-    };
     int64_t tiles = 0;
-    for (; rc == SZO_OK && i < n; ++i) {
+    for (; i < n; ++i) {
       const szo_linear_desc& d = descs[i];
       if (d.M == 0 || d.N == 0) continue;
-      global_u16 copy = nullptr;
-      for (const FwdParams& e : table)                      // several matrices may be applied to the same activations
-        if (e.x == (global_u16)d.x && e.M == d.M && e.K == d.K) copy = e.x_minus;
-      if (!copy) {
+      const auto known = copy_of.find(d.x);                 // several matrices may be applied to the same activations
+      size_t copy = known == copy_of.end() ? items.size() : known->second;
+      if (copy < items.size() && (items[copy].M != (int)d.M || items[copy].K != (int)d.K)) copy = items.size();
+      if (copy == items.size()) {
         if (used + copy_bytes(d) > kCopyAreaBytes) break;
-        uint16_t* const out = (uint16_t*)((char*)copies + used);
+        items.push_back(TransposeItem{(const uint16_t*)d.x, (uint16_t*)((char*)copies + used), (int)d.M, (int)d.K, 0});
         used += copy_bytes(d);
-        copy = (global_u16)out;
-        args.item[args.n++] = TransposeItem{(const uint16_t*)d.x, out, (int)d.M, (int)d.K, args.blocks};
-        args.blocks += (uint32_t)((d.M + 63) / 64) * (uint32_t)(d.K / 64);
-        if (args.n == (int)(sizeof(args.item) / sizeof(args.item[0]))) rc = transpose();
-        if (rc != SZO_OK) break;
+        copy_of[d.x] = copy;
       }
       FwdParams p;
-      rc = fill_params(p, &d, seed, step, +1, eps, partials + offset, 1.0 / ((double)d.M * (double)d.N));
-      p.x_minus = copy;
+      const int rc = fill_params(p, &d, seed, step, +1, eps, partials + offset, 1.0 / ((double)d.M * (double)d.N));
+      if (rc != SZO_OK) return rc;
+      p.x_minus = (global_u16)items[copy].out;
       p.partials_minus = (global_f64_out)(partials + T + offset);
       p.grid_m = (int)((d.M + tile - 1) / tile);
       p.grid_n = (int)((d.N + tile - 1) / tile);
@@ -1317,21 +1311,41 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
       tiles += (int64_t)p.grid_m * p.grid_n;
       table.push_back(p);
     }
-    if (rc == SZO_OK) rc = transpose();
-    if (rc != SZO_OK) return rc;
+    if (table.size() == l.first) break;                     // nothing but layers without tokens or outputs
     // Longest K first, as above: the launch ends with its shortest tiles.
-    if (tiles <= 8192) std::stable_sort(table.begin(), table.end(), [](const FwdParams& a, const FwdParams& b) { return a.K > b.K; });
-    int64_t first_block = 0;
-    for (FwdParams& p : table) {
-      p.first_block = (int)first_block;
-      first_block += ((int64_t)p.grid_m * p.grid_n + 7) & ~(int64_t)7;      // fits: fewer than 2^20 tiles and 4096 entries
+    if (tiles <= 8192) std::stable_sort(table.begin() + (ptrdiff_t)l.first, table.end(), [](const FwdParams& a, const FwdParams& b) { return a.K > b.K; });
+    for (size_t e = l.first; e < table.size(); ++e) {
+      table[e].first_block = (int)l.blocks;
+      l.blocks += ((int64_t)table[e].grid_m * table[e].grid_n + 7) & ~(int64_t)7;      // fits: fewer than 2^20 tiles and 4096 entries
+    }
+    l.items = items.size();
+    launches.push_back(l);
+    staged = staged || table.size() - l.first > (size_t)kInlineForwards;
+  }
+  int rc = timing_begin(stream);
+  if (rc == SZO_OK && staged) rc = stage_table(table.data(), sizeof(FwdParams) * table.size(), table_dev, stream);
+  size_t item = 0;
+  for (size_t i = 0; rc == SZO_OK && i < launches.size(); ++i) {
+    const Launch& l = launches[i];
+    while (item < l.items) {
+      TransposeArgs args;
+      args.blocks = 0;
+      for (args.n = 0; item < l.items && args.n < (int)(sizeof(args.item) / sizeof(args.item[0])); ++item) {
+        TransposeItem& it = args.item[args.n++] = items[item];
+        it.first = args.blocks;
+        args.blocks += (uint32_t)((it.M + 63) / 64) * (uint32_t)(it.K / 64);
+      }
+      const unsigned grid = (args.blocks + 3u) / 4u;
+      if (f16) transpose_kernel<SZO_TILE_F16><<<grid, 256, 0, stream>>>(args);
+      else transpose_kernel<SZO_TILE_BF16><<<grid, 256, 0, stream>>>(args);
+      SZO_LAUNCH_CHECK();
     }
     static thread_local ForwardTableArgs t;
-    rc = place_table(table.data(), table.size(), table_dev, stream, t);
-    if (rc != SZO_OK) return rc;
-    rc = !f16      ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, first_block, stream)
-         : fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, first_block, stream)
-                     : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, first_block, stream);
+    const size_t end = i + 1 < launches.size() ? launches[i + 1].first : table.size();
+    use_table(table.data() + l.first, end - l.first, (const FwdParams*)table_dev + l.first, t);
+    rc = !f16      ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, l.blocks, stream)
+         : fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, l.blocks, stream)
+                     : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, l.blocks, stream);
   }
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;

@@ -213,16 +213,16 @@ __device__ __forceinline__ void tile_of_logical(int L, int grid_m, int grid_n, i
   bn = rem / gsize;
 }
 
-// Host: where a grouped launch finds its `entries` entries: in `inl`, or staged at table_dev.
-inline int place_table(const FwdParams* entries, size_t count, void* table_dev, hipStream_t stream, ForwardTableArgs& args) {
+// Host: where a grouped launch finds its `count` entries: in `inl`, or at table_dev if there are more; whether they are there.
+inline bool use_table(const FwdParams* entries, size_t count, const FwdParams* table_dev, ForwardTableArgs& args) {
   args.n_entries = (int)count;
-  if (count <= (size_t)kInlineForwards) {
-    args.table = nullptr;
-    memcpy((void*)args.inl.e, entries, count * sizeof(FwdParams));
-    return SZO_OK;
-  }
-  args.table = (const FwdParams*)table_dev;
-  return stage_table(entries, sizeof(FwdParams) * count, table_dev, stream);
+  args.table = count <= (size_t)kInlineForwards ? nullptr : table_dev;
+  if (!args.table) memcpy((void*)args.inl.e, entries, count * sizeof(FwdParams));
+  return args.table != nullptr;
+}
+// ... staged at table_dev in that case.
+inline int place_table(const FwdParams* entries, size_t count, void* table_dev, hipStream_t stream, ForwardTableArgs& args) {
+  return use_table(entries, count, (const FwdParams*)table_dev, args) ? stage_table(entries, sizeof(FwdParams) * count, table_dev, stream) : SZO_OK;
 }
 
 // Host: fills the per-layer part of `p` (szo_gemm.hip).

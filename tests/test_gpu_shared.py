@@ -193,3 +193,42 @@ def test_losses_are_added_in_fp64(M, N, tile):
     for got, sign in ((lp, 1.0), (lm, -1.0)):
         want = float(((sign * eps * Z - target.double()) ** 2).mean())
         assert abs(got - want) <= 1e-13 * want, (got, want)
+
+
+def _many_launches():
+    """153 layers with activations of their own, 63 MB each as a copy (views of one tensor, a row apart), 17 of which fit the workspace:
+    nine launches of more layers than travel in the kernel arguments."""
+    n, M, K = 153, 16384, 1920
+    gen = torch.Generator(device="cuda").manual_seed(907)
+    _, d = make_pair(907, 64, 64, K, 128, 1e-3)
+    x = torch.randn((M + n, K), generator=gen, device="cuda", dtype=torch.bfloat16)
+    target = torch.randn((M, 64), generator=gen, device="cuda", dtype=torch.bfloat16)
+    descs = []
+    for i in range(n):
+        desc = d.desc(with_y=False)
+        desc.M, desc.x, desc.target = M, x[i:].data_ptr(), target.data_ptr()
+        descs.append(desc)
+    return szo.desc_array(descs), (d, x, target)
+
+
+def test_the_host_runs_four_steps_ahead_of_the_gpu():
+    """A step stages two tables, however many launches its layers take, and the eighth before is the first that a call waits for: four
+    steps return while work before them on the stream is still running."""
+    descs, keep = _many_launches()
+    scal, ws = torch.zeros(3, dtype=torch.float64, device="cuda"), szo.new_workspace()
+    szo.szo_set_tile_config(12)
+    step = lambda: szo.szo_zo_step(descs, 9, 0, 1e-3, 0.0, scal, ws, szo.STEP_FUSED_LOSS)
+    for _ in range(8):                                       # every pinned buffer has its size
+        step()
+    want = scal.cpu().numpy().copy()
+    a = torch.randn((8192, 8192), device="cuda", dtype=torch.bfloat16)
+    b = a @ a
+    torch.cuda.synchronize()
+    for _ in range(400):                                     # some 0.3 s
+        torch.matmul(a, a, out=b)
+    before = torch.cuda.Event()
+    before.record()
+    for _ in range(4):
+        step()
+    assert not before.query()
+    assert np.array_equal(scal.cpu().numpy(), want)
