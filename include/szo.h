@@ -135,7 +135,7 @@ int szo_linear_fwd(const szo_linear_desc* desc /* host */, uint64_t seed, uint64
 /* Stand-in loss of the workloads: loss_acc += scale * sum_i (y[i] - target[i])^2, i < count
  * (Definition 1 only needs a scalar f).  Accumulates in fp64 in a fixed order: results are
  * bit-reproducible run to run.  y: device fp32; target: device bf16; loss_acc: device
- * double; workspace: device, at least szo_workspace_bytes() bytes, 8-byte aligned, not shared
+ * double; workspace: device, at least szo_step_workspace_bytes(NULL, 0, 0) bytes, 8-byte aligned, not shared
  * with a call running concurrently on another stream.  count == 0 adds nothing. */
 int szo_mse_loss(const float* y, const void* target, int64_t count, double scale,
                  double* loss_acc, void* workspace, void* stream);
@@ -195,6 +195,9 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
  * more, where the sparse products cost what the second dense product does).  Not the default for large steps, which take one
  * dense product in larger tiles where that pays: with the fp16 tile and groups of 128 this one applies the group scales in fp32. */
 #define SZO_STEP_ONE_DENSE_PASS 2
+/* Bit 2: the workspace ends before the copies of activations (szo_step_workspace_bytes with n == 0): large steps that would
+ * make them take tiles of 64 token rows or two full products instead, to the same roundings. */
+#define SZO_STEP_SMALL_WORKSPACE 4
 int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
                 float eps, float lr, double* scalars, void* workspace, int flags, void* stream);
 
@@ -221,9 +224,15 @@ int szo_zo_step(const szo_linear_desc* descs /* host */, int n, uint64_t seed, u
 int szo_zo_step_noalloc(const szo_linear_desc* descs /* host */, int n, uint64_t seed, uint64_t step,
                         float eps, float lr, double* scalars /* device double[3] */, void* stream);
 
-/* Bytes of device workspace the loss-accumulating calls need (a constant: 16 MiB for loss partials, tables, and 1 GiB for
- * copies of activations, of which only large steps write what they need). */
+/* Bytes of device workspace that are enough for every loss-accumulating call (a constant: 16 MiB for loss partials, tables,
+ * and 1 GiB for copies of activations, of which only large steps write what they need). */
 size_t szo_workspace_bytes(void);
+
+/* Bytes that are enough for szo_zo_step with these layers and flags: the part without copies (16.6 MiB) unless the step may
+ * take the kernel that makes them.  n == 0: that part, enough for szo_mse_loss, szo_linear_fwd_mse and steps with
+ * SZO_STEP_SMALL_WORKSPACE.  descs is what the step gets, pointers included (layers with the same x share a copy); for
+ * layers that szo_zo_step refuses the answer is szo_workspace_bytes(). */
+size_t szo_step_workspace_bytes(const szo_linear_desc* descs /* host */, int n, int flags);
 
 /* Puts a freshly allocated workspace into its idle state (zeroes its header).  Needed once per
  * workspace; every loss-accumulating call leaves the workspace idle again when it completes. */

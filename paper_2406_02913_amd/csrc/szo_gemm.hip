@@ -1251,87 +1251,112 @@ static bool shared_pays(const szo_linear_desc* descs, int n, bool instead_of_one
   return instead_of_onepass ? tiles >= 512.0 && here < 0.65 * second : tiles > 4096.0 && here < second;
 }
 
-// Both forwards of every matrix with the dense product computed once (szo_shared.h), the loss fused: launches of 256 x 256 tiles, each over as many
-// layers as the workspace has room for the activations of, in the order that its sensitive products read them.
+// The launches of a step with one dense product: each of as many layers as the copy area has room for the activations of.
+struct SharedPlan {
+  struct Launch { size_t first, items; };                   // its first layer, the end of its copies
+  std::vector<Launch> launches;
+  std::vector<int> layers;                                  // those with tokens and outputs
+  std::vector<size_t> copy;                                 // which copy each of them reads
+  std::vector<TransposeItem> items;                         // the copies; x -> out, here an offset
+  std::unordered_map<const void*, size_t> copy_of;          // the launch's latest copy of these activations
+  int64_t tiles;                                            // of 256 x 256 outputs
+  size_t bytes;                                             // of the copy area that is written
+  bool make(const szo_linear_desc* descs, int n) {          // false if the layers do not qualify
+    launches.clear();
+    layers.clear();
+    copy.clear();
+    items.clear();
+    copy_of.clear();
+    tiles = 0;
+    bytes = 0;
+    size_t used = 0;
+    for (int i = 0; i < n; ++i) {
+      const szo_linear_desc& d = descs[i];
+      if (d.tile_dtype != descs[0].tile_dtype || d.format != SZO_FORMAT_UNIFORM) return false;
+      if (d.M == 0 || d.N == 0) continue;
+      const size_t need = (size_t)((d.M + 63) / 64) * (size_t)d.K * 128;
+      if (d.x_minus || d.K >= (1 << 21) || need > kCopyAreaBytes) return false;      // offsets within a tile's rows of x: 31 bits
+      const auto known = copy_of.find(d.x);                 // several matrices may be applied to the same activations
+      size_t c = known == copy_of.end() ? items.size() : known->second;
+      if (c < items.size() && (items[c].M != (int)d.M || items[c].K != (int)d.K)) c = items.size();
+      if (c == items.size() && used + need > kCopyAreaBytes) {
+        copy_of.clear();
+        used = 0;
+      }
+      if (used == 0) launches.push_back(Launch{layers.size(), 0});
+      if (c == items.size()) {
+        items.push_back(TransposeItem{(const uint16_t*)d.x, (uint16_t*)(uintptr_t)used, (int)d.M, (int)d.K, 0});
+        used += need;
+        bytes = std::max(bytes, used);
+        copy_of[d.x] = c;
+      }
+      layers.push_back(i);
+      copy.push_back(c);
+      launches.back().items = items.size();
+      tiles += ((d.M + 255) / 256) * ((d.N + 255) / 256);
+    }
+    return tiles > 0 && 2 * tiles <= kMaxLossPartials && sizeof(FwdParams) * layers.size() <= kTableBytesPerMatrix * (size_t)kMaxStepMatrices;
+  }
+};
+
+// Both forwards of every matrix with the dense product computed once (szo_shared.h), the loss fused: launches of 256 x 256 tiles, each behind
+// the copies of its layers' activations in the order that its sensitive products read them.
 // SZO_EUNSUPPORTED, with nothing enqueued, when the stack does not qualify.
 static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, void* table_dev, void* copies,
                            double* partials, int64_t* partials_per_sign, hipStream_t stream) {
   constexpr int tile = 256;
-  int64_t T = 0;
-  auto copy_bytes = [](const szo_linear_desc& d) { return (size_t)((d.M + 63) / 64) * (size_t)d.K * 128; };
-  for (int i = 0; i < n; ++i) {                             // reject everything before anything is enqueued
-    const szo_linear_desc& d = descs[i];
-    if (d.tile_dtype != descs[0].tile_dtype || d.format != SZO_FORMAT_UNIFORM) return SZO_EUNSUPPORTED;
-    if (d.M == 0 || d.N == 0) continue;
-    if (d.x_minus || d.K >= (1 << 21) || copy_bytes(d) > kCopyAreaBytes) return SZO_EUNSUPPORTED;      // offsets within a tile's rows of x: 31 bits
-    T += ((d.M + tile - 1) / tile) * ((d.N + tile - 1) / tile);
-  }
-  if (T == 0 || 2 * T > kMaxLossPartials || sizeof(FwdParams) * (size_t)n > kTableBytesPerMatrix * (size_t)kMaxStepMatrices) return SZO_EUNSUPPORTED;
+  static thread_local SharedPlan plan;
+  if (!plan.make(descs, n)) return SZO_EUNSUPPORTED;        // reject everything before anything is enqueued
+  const int64_t T = plan.tiles;
   const bool f16 = descs[0].tile_dtype == SZO_TILE_F16;
   // Steps that the one-dense-pass kernel would take have its sums, one by one in fp64: the layers that tell them apart.
   bool fp64_sums = true;
-  for (int i = 0; i < n; ++i) fp64_sums = fp64_sums && (descs[i].M == 0 || descs[i].N == 0 || onepass_rounds(descs[i]));
+  for (int i : plan.layers) fp64_sums = fp64_sums && onepass_rounds(descs[i]);
   // One table for the whole step, staged once: the host runs as many steps ahead as with one launch.
-  struct Launch { size_t first, items; int64_t blocks; };   // its first entry, the end of its copies, its workgroups
   static thread_local std::vector<FwdParams> table;
-  static thread_local std::vector<TransposeItem> items;
-  static thread_local std::vector<Launch> launches;
-  static thread_local std::unordered_map<const void*, size_t> copy_of;      // the launch's latest copy of these activations
+  static thread_local std::vector<int64_t> blocks;          // workgroups of each launch
   table.clear();
-  items.clear();
-  launches.clear();
+  blocks.clear();
+  for (TransposeItem& it : plan.items) it.out = (uint16_t*)((char*)copies + (uintptr_t)it.out);
   int64_t offset = 0;
   bool staged = false;
-  for (int i = 0; i < n;) {
-    Launch l = {table.size(), 0, 0};
-    copy_of.clear();
-    size_t used = 0;
-    int64_t tiles = 0;
-    for (; i < n; ++i) {
-      const szo_linear_desc& d = descs[i];
-      if (d.M == 0 || d.N == 0) continue;
-      const auto known = copy_of.find(d.x);                 // several matrices may be applied to the same activations
-      size_t copy = known == copy_of.end() ? items.size() : known->second;
-      if (copy < items.size() && (items[copy].M != (int)d.M || items[copy].K != (int)d.K)) copy = items.size();
-      if (copy == items.size()) {
-        if (used + copy_bytes(d) > kCopyAreaBytes) break;
-        items.push_back(TransposeItem{(const uint16_t*)d.x, (uint16_t*)((char*)copies + used), (int)d.M, (int)d.K, 0});
-        used += copy_bytes(d);
-        copy_of[d.x] = copy;
-      }
+  auto end_of = [&](size_t launch) { return launch + 1 < plan.launches.size() ? plan.launches[launch + 1].first : plan.layers.size(); };
+  for (size_t l = 0; l < plan.launches.size(); ++l) {
+    const size_t first = plan.launches[l].first, end = end_of(l);
+    const int64_t before = offset;
+    for (size_t e = first; e < end; ++e) {
+      const szo_linear_desc& d = descs[plan.layers[e]];
       FwdParams p;
       const int rc = fill_params(p, &d, seed, step, +1, eps, partials + offset, 1.0 / ((double)d.M * (double)d.N));
       if (rc != SZO_OK) return rc;
-      p.x_minus = (global_u16)items[copy].out;
+      p.x_minus = (global_u16)plan.items[plan.copy[e]].out;
       p.partials_minus = (global_f64_out)(partials + T + offset);
       p.grid_m = (int)((d.M + tile - 1) / tile);
       p.grid_n = (int)((d.N + tile - 1) / tile);
       p.y = nullptr;
       offset += (int64_t)p.grid_m * p.grid_n;
-      tiles += (int64_t)p.grid_m * p.grid_n;
       table.push_back(p);
     }
-    if (table.size() == l.first) break;                     // nothing but layers without tokens or outputs
     // Longest K first, as above: the launch ends with its shortest tiles.
-    if (tiles <= 8192) std::stable_sort(table.begin() + (ptrdiff_t)l.first, table.end(), [](const FwdParams& a, const FwdParams& b) { return a.K > b.K; });
-    for (size_t e = l.first; e < table.size(); ++e) {
-      table[e].first_block = (int)l.blocks;
-      l.blocks += ((int64_t)table[e].grid_m * table[e].grid_n + 7) & ~(int64_t)7;      // fits: fewer than 2^20 tiles and 4096 entries
+    if (offset - before <= 8192) std::stable_sort(table.begin() + (ptrdiff_t)first, table.end(), [](const FwdParams& a, const FwdParams& b) { return a.K > b.K; });
+    int64_t first_block = 0;
+    for (size_t e = first; e < end; ++e) {
+      table[e].first_block = (int)first_block;
+      first_block += ((int64_t)table[e].grid_m * table[e].grid_n + 7) & ~(int64_t)7;      // fits: fewer than 2^20 tiles and 4096 entries
     }
-    l.items = items.size();
-    launches.push_back(l);
-    staged = staged || table.size() - l.first > (size_t)kInlineForwards;
+    blocks.push_back(first_block);
+    staged = staged || end - first > (size_t)kInlineForwards;
   }
   int rc = timing_begin(stream);
   if (rc == SZO_OK && staged) rc = stage_table(table.data(), sizeof(FwdParams) * table.size(), table_dev, stream);
   size_t item = 0;
-  for (size_t i = 0; rc == SZO_OK && i < launches.size(); ++i) {
-    const Launch& l = launches[i];
-    while (item < l.items) {
+  for (size_t l = 0; rc == SZO_OK && l < plan.launches.size(); ++l) {
+    const size_t first = plan.launches[l].first, items = plan.launches[l].items;
+    while (item < items) {
       TransposeArgs args;
       args.blocks = 0;
-      for (args.n = 0; item < l.items && args.n < (int)(sizeof(args.item) / sizeof(args.item[0])); ++item) {
-        TransposeItem& it = args.item[args.n++] = items[item];
+      for (args.n = 0; item < items && args.n < (int)(sizeof(args.item) / sizeof(args.item[0])); ++item) {
+        TransposeItem& it = args.item[args.n++] = plan.items[item];
         it.first = args.blocks;
         args.blocks += (uint32_t)((it.M + 63) / 64) * (uint32_t)(it.K / 64);
       }
@@ -1341,15 +1366,31 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
       SZO_LAUNCH_CHECK();
     }
     static thread_local ForwardTableArgs t;
-    const size_t end = i + 1 < launches.size() ? launches[i + 1].first : table.size();
-    use_table(table.data() + l.first, end - l.first, (const FwdParams*)table_dev + l.first, t);
-    rc = !f16      ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, l.blocks, stream)
-         : fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, l.blocks, stream)
-                     : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, l.blocks, stream);
+    use_table(table.data() + first, end_of(l) - first, (const FwdParams*)table_dev + first, t);
+    rc = !f16      ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, blocks[l], stream)
+         : fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, blocks[l], stream)
+                     : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, blocks[l], stream);
   }
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;
   return timing_end(stream);
+}
+
+// Which of the ways a step may go.  A later one is taken where those before it find that they cannot: the dense product once in large tiles
+// instead of in tiles of 64 token rows; those; the few-token path (up to 2^20 workgroups); once in large tiles instead of twice; twice.
+struct StepRoute { bool asked_for, few_rule, few, instead_of_onepass, instead_of_two; };
+static StepRoute step_route(const szo_linear_desc* descs, int n, int flags) {
+  const bool fuse = (flags & SZO_STEP_FUSED_LOSS) != 0, copies = fuse && !(flags & SZO_STEP_SMALL_WORKSPACE);
+  // Few-token stacks: one pass over the weights serves both forwards of the step.  SZO_STEP_ONE_DENSE_PASS: also at token counts
+  // that the rule leaves to the tiled kernel.
+  const bool can_few = fuse && few_token_enabled() && g_tile_config != 12 && n <= kMaxStepMatrices;
+  StepRoute r;
+  r.asked_for = (flags & SZO_STEP_ONE_DENSE_PASS) != 0;
+  r.few_rule = can_few && small_m_eligible(descs, n, false, false, 2);
+  r.few = r.few_rule || (can_few && r.asked_for && small_m_eligible(descs, n, true, false, 2));
+  r.instead_of_onepass = copies && g_tile_config == 0 && shared_pays(descs, n, true) && onepass_partials(descs, n, r.few_rule, r.asked_for, false, false) > 0;
+  r.instead_of_two = copies && !r.few && (g_tile_config == 12 || (g_tile_config == 0 && shared_pays(descs, n, false)));
+  return r;
 }
 
 // Device address of `scratch` on the current device, looked up once per device.
@@ -1487,6 +1528,17 @@ int szo_linear_fwd_mse(const szo_linear_desc* desc, uint64_t seed, uint64_t step
   return reduce_partials(partial_area(workspace), blocks, 1.0, loss_acc, (hipStream_t)stream);
 }
 
+size_t szo_step_workspace_bytes(const szo_linear_desc* descs, int n, int flags) {
+  if (n <= 0) return kSmallWorkspaceBytes;
+  if (!descs) return kWorkspaceBytes;
+  for (int i = 0; i < n; ++i)                               // copies are counted by their x: only of a step that would run
+    if (validate_desc(&descs[i], 1, !(flags & SZO_STEP_FUSED_LOSS), true) != SZO_OK) return kWorkspaceBytes;
+  const StepRoute route = step_route(descs, n, flags);
+  static thread_local SharedPlan plan;
+  if (!(route.instead_of_onepass || route.instead_of_two) || !plan.make(descs, n)) return kSmallWorkspaceBytes;
+  return kWorkspaceBytes - kCopyAreaBytes + plan.bytes;
+}
+
 int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, float lr,
                 double* scalars, void* workspace, int flags, void* stream) {
   if (n < 0 || (n > 0 && !descs) || !scalars || !workspace || ((uintptr_t)workspace & 7)) return SZO_EINVAL;
@@ -1509,30 +1561,24 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   }
   int rc;
   void* const table_dev = (char*)workspace + kWorkspaceTableOffset;
-  // Few-token stacks: one pass over the weights serves both forwards of the step.  SZO_STEP_ONE_DENSE_PASS: also at token counts
-  // that the rule leaves to the tiled kernel.
-  const bool can_few = fuse && few_token_enabled() && g_tile_config != 12 && n <= kMaxStepMatrices, asked_for = (flags & SZO_STEP_ONE_DENSE_PASS) != 0;
-  const bool few_rule = can_few && small_m_eligible(descs, n, false, false, 2);
-  const bool few = few_rule || (can_few && asked_for && small_m_eligible(descs, n, true, false, 2));
+  const StepRoute route = step_route(descs, n, flags);
   // Many tokens, one set of activations: the dense product once for both forwards (szo_onepass.hip; in large launches with rounded weights
   // the tiled kernel).
   {
     int64_t T = 0;
-    const bool in_tiles = g_tile_config == 0 && fuse && shared_pays(descs, n, true) && onepass_partials(descs, n, few_rule, asked_for, false, false) > 0;
-    rc = in_tiles ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
+    rc = route.instead_of_onepass ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
     if (rc == SZO_EUNSUPPORTED)
-      rc = onepass_forwards(descs, n, seed, step, eps, few_rule, asked_for, !fuse, table_dev, partial_area(workspace), &T, s);
+      rc = onepass_forwards(descs, n, seed, step, eps, route.few_rule, route.asked_for, !fuse, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK) return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
     if (rc != SZO_EUNSUPPORTED) return rc;      // otherwise nothing was enqueued
   }
-  if (few) {
+  if (route.few) {
     rc = small_m_step(descs, n, seed, step, eps, lr, table_dev, partial_area(workspace), 0, scalars, true, s);
     if (rc != SZO_EUNSUPPORTED) return rc;      // too many slices for the table: nothing was enqueued, take the tiled path
   }
   if (fuse) {
     int64_t T = 0;
-    const bool shared = g_tile_config == 12 || (g_tile_config == 0 && shared_pays(descs, n, false));
-    rc = shared ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
+    rc = route.instead_of_two ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
     if (rc == SZO_EUNSUPPORTED) rc = grouped_forwards(descs, n, seed, step, eps, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK)
       return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);

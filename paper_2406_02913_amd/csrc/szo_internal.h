@@ -40,6 +40,8 @@ constexpr size_t kTableBytesPerMatrix = 144;
 constexpr size_t kWorkspaceTableOffset = kWorkspaceHeader + sizeof(double) * (size_t)kMaxLossPartials;
 // Copies of activations, column by column, for the sensitive products of large steps: a step goes in launches of as many layers as fit.
 constexpr size_t kWorkspaceCopyOffset = kWorkspaceTableOffset + kTableBytesPerMatrix * (size_t)kMaxStepMatrices;
+// Steps that write none are content with the part before it.
+constexpr size_t kSmallWorkspaceBytes = kWorkspaceCopyOffset;
 constexpr size_t kCopyAreaBytes = (size_t)1 << 30;
 constexpr size_t kWorkspaceBytes = kWorkspaceCopyOffset + kCopyAreaBytes + 128;
 

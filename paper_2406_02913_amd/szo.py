@@ -19,6 +19,7 @@ TILE_F16, TILE_BF16 = 0, 1
 TILE_ROWS, TILE_COLS = 64, 64
 STEP_FUSED_LOSS = 1
 STEP_ONE_DENSE_PASS = 2
+STEP_SMALL_WORKSPACE = 4
 FORMAT_UNIFORM, FORMAT_LUT = 0, 1
 
 if not os.path.exists(LIB_PATH):
@@ -52,6 +53,7 @@ _SIGS = {
     "szo_zo_step_noalloc": (C.c_int, [_P(LinearDesc), C.c_int, C.c_uint64, C.c_uint64, C.c_float, C.c_float,
                                        C.c_void_p, C.c_void_p]),
     "szo_workspace_bytes": (C.c_size_t, []),
+    "szo_step_workspace_bytes": (C.c_size_t, [_P(LinearDesc), C.c_int, C.c_int]),
     "szo_workspace_init": (C.c_int, [C.c_void_p, C.c_void_p]),
     "szo_num_tiles": (C.c_int64, [C.c_int64, C.c_int64]),
     "szo_mask_generate": (C.c_int, [C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_uint64, C.c_void_p]),
@@ -177,13 +179,21 @@ def szo_workspace_bytes():
     return int(lib.szo_workspace_bytes())
 
 
+def szo_step_workspace_bytes(descs=(), flags=STEP_FUSED_LOSS):
+    """Without layers: what steps with STEP_SMALL_WORKSPACE and the loss calls need."""
+    if isinstance(descs, (list, tuple)):
+        descs = desc_array(descs)
+    return int(lib.szo_step_workspace_bytes(descs, len(descs), flags))
+
+
 def szo_workspace_init(workspace, stream=None):
     _check("szo_workspace_init", lib.szo_workspace_init(_dev(workspace), _stream(stream)))
 
 
-def new_workspace(device="cuda"):
+def new_workspace(device="cuda", nbytes=None):
+    """For any call, or of the size that szo_step_workspace_bytes() gives for some."""
     import torch
-    ws = torch.empty(szo_workspace_bytes(), dtype=torch.uint8, device=device)
+    ws = torch.empty(szo_workspace_bytes() if nbytes is None else nbytes, dtype=torch.uint8, device=device)
     szo_workspace_init(ws)
     return ws
 

@@ -232,3 +232,20 @@ def test_the_host_runs_four_steps_ahead_of_the_gpu():
         step()
     assert not before.query()
     assert np.array_equal(scal.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("tile,instead", [("f16", 6), ("bf16", 11)])
+def test_a_step_may_go_without_the_copies(tile, instead):
+    """Told that the workspace ends before them, a large step takes the kernel that it took before there were copies, and leaves what is behind
+    alone; with the bytes that the query gives it makes them and no more."""
+    descs, keep = _stack(911, 29 if tile == "f16" else 11, 2304 if tile == "f16" else 768, 4096, 1024, 1e-3, False, 128, szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16)
+    wanted = _step(descs, 12), _step(descs, instead)
+    szo.szo_set_tile_config(0)
+    sizes = szo.szo_step_workspace_bytes(descs), szo.szo_step_workspace_bytes(descs, szo.STEP_FUSED_LOSS | szo.STEP_SMALL_WORKSPACE)
+    assert sizes[1] == szo.szo_step_workspace_bytes() < 17 << 20 and sizes[0] > sizes[1]
+    for flags, nbytes, want in zip((0, szo.STEP_SMALL_WORKSPACE), sizes, wanted):
+        memory = torch.full((szo.szo_workspace_bytes(),), 0xA5, dtype=torch.uint8, device="cuda")
+        szo.szo_workspace_init(memory)
+        scal = torch.zeros(3, dtype=torch.float64, device="cuda")
+        szo.szo_zo_step(descs, 9, 0, 1e-3, 0.0, scal, memory, szo.STEP_FUSED_LOSS | flags)
+        assert np.array_equal(scal.cpu().numpy(), want) and bool((memory[nbytes:] == 0xA5).all())

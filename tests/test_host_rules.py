@@ -181,3 +181,40 @@ def test_where_tiles_compute_k_in_two_parts(ask):
 def test_who_takes_one_dense_product_beyond_512_tokens(ask, case, onepass):
     (few, _, _, partials), = ask(case)
     assert not few and (partials > 0) == onepass
+
+
+def _descs(layers, x_of=lambda i: i, **changes):
+    """Descriptors that validate; their addresses are never followed."""
+    from paper_2406_02913_amd import szo
+    at = 1 << 20
+    out = []
+    for i, (M, N, K, density) in enumerate(layers):
+        d = szo.LinearDesc(M, N, K, 128, szo.TILE_F16, int(density * N * K), 0, at + (x_of(i) << 30), at, at, at, at, at, None, at, None, 0, 0, None)
+        for name, value in changes.items():
+            setattr(d, name, value)
+        out.append(d)
+    return out
+
+
+def test_the_workspace_holds_copies_only_for_steps_that_make_them():
+    from paper_2406_02913_amd import szo, synth
+    at = 1 << 20
+    small, whole = szo.szo_step_workspace_bytes(), szo.szo_workspace_bytes()
+    assert 64 + 8 * (1 << 21) <= small <= 17 << 20 and small + (1 << 30) <= whole
+    block = lambda M, n, density=1e-3: [(M, N, K, density) for _ in range(n) for _, N, K in synth.LLAMA2_7B_BLOCK]
+    of = lambda layers, flags=szo.STEP_FUSED_LOSS, **kw: szo.szo_step_workspace_bytes(_descs(layers, **kw), flags)
+    copy = lambda M, K: -(-M // 64) * 64 * K * 2
+    # the largest steps: the copies of a launch's layers, each x once
+    assert 0.9 * (1 << 30) < of(block(4096, 32)) - small <= whole - small
+    assert of(block(4096, 2)) == small + 128 + 2 * sum(copy(4096, K) for _, _, K in synth.LLAMA2_7B_BLOCK)
+    assert of(block(4096, 2), x_of=lambda i: i % 7 // 6) == small + 128 + copy(4096, 4096) + copy(4096, 11008)
+    assert of(block(1000, 1), tile_dtype=szo.TILE_BF16) > small
+    # steps that other kernels take, and layers that this one does not
+    assert of(block(4096, 1)) == of(block(16, 32)) == of(block(1000, 1)) == of(block(4096, 32, 1e-2)) == of([(64, 256, 256, 1e-3)]) == small
+    assert of(block(4096, 32), x_minus=at) == of(block(4096, 32), format=szo.FORMAT_LUT, lut=at) == small
+    assert of(block(65536, 1)) == small                      # one copy alone is larger than what there is
+    assert of(block(4096, 32), flags=0, y=at) == small
+    # ... and those that are told
+    assert of(block(4096, 32), szo.STEP_FUSED_LOSS | szo.STEP_SMALL_WORKSPACE) == small
+    # what is refused writes nothing; said before its addresses are known the answer is no promise
+    assert of(block(4096, 1), x=None) == whole
