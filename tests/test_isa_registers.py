@@ -54,3 +54,25 @@ def test_further_groups_of_sensitive_entries_gather_beside_their_products(tmp_pa
         assert (8, 16) in count, (kernel, [c for c in count if c[0]])
         whole_schedules += any(m > 8 and g == 16 for m, g in count)
     assert 2 * whole_schedules >= len(kernels)
+
+
+@pytest.mark.skipif(not HIPCC, reason="no hipcc")
+def test_the_tiled_kernels_keep_their_main_loops_in_registers(tmp_path):
+    """A register spilled in the main loop costs 8 to 15 % of a step.  The tiles with one dense product spill some words behind it, none
+    before the end of its last products (stretches of 64 and more matrix instructions) and none among the sensitive products; the
+    other grouped forms spill none at all."""
+    out = str(tmp_path / "gemm.s")
+    subprocess.check_call([HIPCC, "--cuda-device-only", "-S"] + szo_build.COMMON + szo_build.DEVICE +
+                          [os.path.join(szo_build.CSRC, "szo_gemm.hip"), "-o", out], stderr=subprocess.DEVNULL)
+    text = open(out).read()
+    scratch = {name: int(size) for name, size in re.findall(r"\.name:\s+(\S*linear_fwd_table_kernel\S*)\s+\.private_segment_fixed_size: (\d+)", text)}
+    shared = [name for name in scratch if re.search(r"Li16ELi[12]EEEv", name)]
+    assert len(shared) == 3 and len(scratch) > 3
+    assert all(size == 0 for name, size in scratch.items() if name not in shared), scratch
+    for name in shared:
+        blocks = _blocks(text, name)
+        count = [(sum(i.startswith("v_mfma") for i in b), sum(i.startswith("scratch_") for i in b)) for b in blocks]
+        main = [i for i, (products, _) in enumerate(count) if products >= 64]
+        assert len(main) >= 2 and not any(spills for _, spills in count[:main[-1] + 1]), name
+        assert any(0 < products < 64 for products, _ in count[main[-1] + 1:]) and not any(products and spills for products, spills in count), name
+        assert scratch[name] <= 96, (name, scratch[name])
