@@ -1,6 +1,8 @@
 """Whole ZO steps at the headline sizes against the oracle: one Llama-2-7B decoder block at 4096 tokens
 and one Mistral-7B block at 8192 tokens, through szo_zo_step exactly as bench.py calls it (library's
-choice of tiles, loss fused, one grouped forward launch, one grouped update).  At these sizes
+choice of kernel, loss fused, one grouped forward launch, one grouped update).  The Llama block and the densest mask take two full
+products per layer, the Mistral block at 0.1 % the dense product once and the sensitive ones behind it, as the benchmark's full stack of
+Llama blocks does.  At these sizes
 L+ - L- is about 1e-6 of L (Definition 1 divides that difference by 2 eps), so this is where an fp32 loss
 sum, a 16-bit y or a dropped entry would show in g.  Every setup array is first compared bit for bit
 with the oracle's (make_pair)."""
@@ -39,7 +41,7 @@ def _block_step(workload, names, density, seed, step, lr, data_seed=0):
     szo.szo_zo_step([d.desc(with_y=False) for _, d in pairs], seed, step, eps, lr, scal, ws, szo.STEP_FUSED_LOSS)
     _, launches = szo.szo_kernel_timing_read()
     szo.szo_kernel_timing(False)
-    assert launches == 1                                        # the grouped launch, as in the benchmark
+    assert launches == 1                                        # the grouped launch
     Lp, Lm, g = scal.cpu().numpy()
     os_ = [o for o, _ in pairs]
     ref = [clone(o) for o in os_]

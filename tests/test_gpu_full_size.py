@@ -138,9 +138,9 @@ def test_opt_ffn_projections_decode_token_counts(M, cfg):
         bound.check(i, dd.sp_val.cpu().numpy(), om.sp_val, o.sp_val)
 
 
-def test_llama_block_step_in_the_benchmarks_launch_configuration():
-    """One whole Llama-2-7B block at 4096 tokens through szo_zo_step exactly as bench.py runs it (library's
-    choice of tiles: all 14 forwards in one table-driven launch, loss fused, grouped update).  Its losses
+def test_llama_block_step_as_one_grouped_launch():
+    """One whole Llama-2-7B block at 4096 tokens through szo_zo_step (library's choice of tiles: all 14 forwards in one table-driven
+    launch, loss fused, grouped update; the full stack computes the dense product once instead, see test_gpu_shared.py).  Its losses
     must equal the per-matrix fused-loss calls (same kernel body, checked against the oracle above) up to
     the order in which the fp64 partials are added, g must follow from them, and every sensitive value
     must move by exactly -lr g z with the oracle's z."""
@@ -166,7 +166,7 @@ def test_llama_block_step_in_the_benchmarks_launch_configuration():
     szo.szo_zo_step([d.desc(with_y=False) for _, d in pairs], seed, step, eps, lr, scal, ws, szo.STEP_FUSED_LOSS)
     _, launches = szo.szo_kernel_timing_read()
     szo.szo_kernel_timing(False)
-    assert launches == 1                                        # the grouped launch, as in the benchmark
+    assert launches == 1                                        # the grouped launch
     Lp, Lm, g = scal.cpu().numpy()
     assert abs(Lp - lp.item()) <= 1e-12 * Lp and abs(Lm - lm.item()) <= 1e-12 * Lm
     assert g == (Lp - Lm) / (2.0 * float(np.float32(eps)))

@@ -25,7 +25,7 @@ def _step(descs, config, lr=0.0, eps=1e-3, seed=9, step=0):
     szo.szo_zo_step(descs, seed, step, eps, lr, scal, szo.new_workspace(), szo.STEP_FUSED_LOSS)
     _, launches = szo.szo_kernel_timing_read()
     szo.szo_kernel_timing(False)
-    assert launches == 1
+    assert launches == 1                                     # one pair of events, around all launches of a step
     return scal.cpu().numpy().copy()
 
 
@@ -125,6 +125,23 @@ def _stack(seed, n, M, N, K, density, same_x, group=128, tile=szo.TILE_F16):
     return descs, keep + [target]
 
 
+def _gradient(d, desc, x, target):
+    """Of the layer's loss with respect to its sensitive values, in fp32 from the unperturbed outputs: g = gradient . z."""
+    y = torch.empty(target.shape, dtype=torch.float32, device="cuda")
+    plain = type(desc).from_buffer_copy(desc)
+    plain.y = y.data_ptr()
+    szo.szo_linear_fwd(plain, 0, 0, 0, 0.0)
+    r = (y - target.float()) * (2.0 / y.numel())
+    return (r.T @ x.float()).reshape(-1)[d.sp_idx.long()].double()
+
+
+def _sigma_of_stack(descs, keep):
+    """As helpers.sigma_g, of layers with the same z (_stack)."""
+    xs = {x.data_ptr(): x for x in keep[1:-1]}
+    total = sum(_gradient(keep[0], desc, xs[desc.x], keep[-1]) for desc in descs)
+    return float(total.norm())
+
+
 @pytest.mark.parametrize("same_x", [False, True])
 def test_a_step_of_several_launches_is_the_sum_of_its_layers(same_x):
     """Five layers whose activations, 256 MiB each, do not all fit the workspace at once (or are one and the same)."""
@@ -136,6 +153,7 @@ def test_a_step_of_several_launches_is_the_sum_of_its_layers(same_x):
     assert abs(s[2] - total[2]) <= 1e-12 * s[0] / 1e-3                       # ... over 2 eps
     one_pass = _step(descs, 11)
     assert np.allclose(s[:2], one_pass[:2], rtol=1e-5, atol=0.0)             # the scale rounded once per weight or not at all
+    assert abs(s[2] - one_pass[2]) <= 1e-2 * max(abs(one_pass[2]), _sigma_of_stack(descs, keep))
 
 
 @pytest.mark.parametrize("density,config", [(1e-3, 12), (1e-2, 6)])
@@ -148,6 +166,8 @@ def test_chosen_for_large_steps_with_sparse_masks(density, config):
     assert np.array_equal(chosen, _step(descs, 0)) and np.array_equal(chosen, _step(descs, config))
     other = _step(descs, 18 - config)
     assert not np.array_equal(chosen, other) and np.allclose(chosen[:2], other[:2], rtol=1e-5, atol=0.0)
+    # the sensitive products, which are 1e-6 of the losses
+    assert abs(chosen[2] - other[2]) <= 1e-2 * max(abs(other[2]), _sigma_of_stack(descs, keep))
 
 
 @pytest.mark.parametrize("group,tile", [(128, "f16"), (64, "f16"), (128, "bf16")])
@@ -159,6 +179,7 @@ def test_chosen_from_512_tiles_on_where_both_kernels_round_the_weights(group, ti
         chosen, other = _step(descs[:n], 0), _step(descs[:n], 23 - config)
         assert np.array_equal(chosen, _step(descs[:n], config)) and not np.array_equal(chosen, other)
         assert np.allclose(chosen[:2], other[:2], rtol=1e-5, atol=0.0)
+        assert abs(chosen[2] - other[2]) <= 1e-2 * max(abs(other[2]), _sigma_of_stack(descs[:n], keep))
         asked = torch.zeros(3, dtype=torch.float64, device="cuda")
         szo.szo_set_tile_config(0)
         szo.szo_zo_step(descs[:n], 9, 0, 1e-3, 0.0, asked, szo.new_workspace(), szo.STEP_FUSED_LOSS | szo.STEP_ONE_DENSE_PASS)
@@ -195,20 +216,35 @@ def test_losses_are_added_in_fp64(M, N, tile):
         assert abs(got - want) <= 1e-13 * want, (got, want)
 
 
-def _many_launches():
-    """153 layers with activations of their own, 63 MB each as a copy (views of one tensor, a row apart), 17 of which fit the workspace:
-    nine launches of more layers than travel in the kernel arguments."""
-    n, M, K = 153, 16384, 1920
+def _many_launches(n=153, columns=(1920,), M=16384):
+    """Layers with activations of their own (views of one tensor, a row apart), 63 MB each as a copy for 1920 columns: 17 of those fit the
+    workspace, more than travel in the kernel arguments.  153 make nine launches.  -> descriptors, [(d, desc, x, target)] of each"""
     gen = torch.Generator(device="cuda").manual_seed(907)
-    _, d = make_pair(907, 64, 64, K, 128, 1e-3)
-    x = torch.randn((M + n, K), generator=gen, device="cuda", dtype=torch.bfloat16)
-    target = torch.randn((M, 64), generator=gen, device="cuda", dtype=torch.bfloat16)
-    descs = []
+    rows = lambda K: torch.randn((M + n, K), generator=gen, device="cuda", dtype=torch.bfloat16)
+    kinds = [(make_pair(907 + K, 64, 64, K, 128, 1e-3)[1], rows(K)) for K in columns]
+    targets = rows(64)
+    layers = []
     for i in range(n):
+        d, xs = kinds[i % len(kinds)]
+        x, target = xs[i:i + M], targets[i:i + M]
         desc = d.desc(with_y=False)
-        desc.M, desc.x, desc.target = M, x[i:].data_ptr(), target.data_ptr()
-        descs.append(desc)
-    return szo.desc_array(descs), (d, x, target)
+        desc.M, desc.x, desc.target, desc.nnz_base = M, x.data_ptr(), target.data_ptr(), 65536 * i
+        layers.append((d, desc, x, target))
+    return szo.desc_array([l[1] for l in layers]), layers
+
+
+def test_several_launches_of_many_layers():
+    """Forty layers with three K in two launches of more entries than the arguments hold and more copies than one copy launch takes: every
+    layer is multiplied with its own activations, targets and z."""
+    descs, layers = _many_launches(40, (1920, 128, 1408))
+    copies = szo.szo_workspace_bytes() - szo.szo_step_workspace_bytes()
+    assert copies < sum(M * K * 2 for _, desc, _, _ in layers for M, K in [(desc.M, desc.K)]) < 2 * copies
+    s = _step(descs, 12)
+    total = np.sum([_step([desc], 12) for _, desc, _, _ in layers], axis=0)
+    assert np.allclose(s[:2], total[:2], rtol=1e-12, atol=0.0) and abs(s[2] - total[2]) <= 1e-12 * s[0] / 1e-3      # the order of the partials
+    two = _step(descs, 6)
+    sigma = float(torch.cat([_gradient(*l) for l in layers]).norm())        # every layer has z of its own
+    assert np.allclose(s[:2], two[:2], rtol=1e-5, atol=0.0) and abs(s[2] - two[2]) <= 1e-2 * max(abs(two[2]), sigma)
 
 
 def test_the_host_runs_four_steps_ahead_of_the_gpu():
