@@ -56,9 +56,16 @@ def few_token_path(M, two_sets=False):
     return slices <= 15 and 2 * slices < 15 * tile_rows
 
 
-def one_product_kernel(mats, M, two_sets=False, asked_for=False):
-    """Which kernel computes a fused step's dense product once for both signs, or None where two forwards run: the
-    library's rules for fp16-tile layers of these workloads' sizes with K a multiple of 128, restated to label the measurement."""
+def makes_copies(szo, descs, flags):
+    """Whether the step takes the tiled kernel with one dense product, the only one that needs room for copies of activations."""
+    return szo.szo_step_workspace_bytes(descs, flags) > szo.szo_step_workspace_bytes()
+
+
+def one_product_kernel(mats, M, copies, two_sets=False, asked_for=False):
+    """Which kernel computes a fused step's dense product once for both signs, or None where two forwards run: the one that makes copies,
+    or the library's rules for fp16-tile layers of these workloads' sizes with K a multiple of 128, restated to label the measurement."""
+    if copies:
+        return SHARED_PRODUCT_KERNEL
     few, uniform = few_token_path(M, two_sets), all(m.lut is None for m in mats)
     wgs = sum(-(-m.N // 256) * -(-M // 64) for m in mats)
     wg_k = sum(-(-m.N // 256) * -(-M // 64) * m.K for m in mats)
@@ -76,15 +83,6 @@ def one_product_kernel(mats, M, two_sets=False, asked_for=False):
     if few or asked_for:
         # a few blocks: K split over the waves of a workgroup
         return "band_split_kernel" if M <= 64 and wgs * -(-M // 16) <= 600 else "small_m_kernel"
-    if uniform and not two_sets:        # the tiled kernel with one dense product
-        tiles = second = here = 0.0
-        for m in mats:
-            rows, columns = -(-M // 256), -(-m.N // 256)
-            tiles += rows * columns
-            second += rows * columns * 1.14 * m.K
-            here += rows * (columns * (256 + 160 * m.nnz / m.N) + 2.3 * m.K)
-        if tiles > 4096 and here < second:
-            return SHARED_PRODUCT_KERNEL
     return None
 
 
@@ -177,7 +175,7 @@ def extra_workload(szo, torch, stack, name, seed, data_seed, dt, variants, steps
         t = time_steps(szo, torch, descs, seed, cfg["eps"], cfg["lr"], szo.STEP_FUSED_LOSS,
                        steps or (200 if few else 20), warmup if warmup is not None else (30 if few else 5))
         traffic = MEASURED_TRAFFIC_BYTES.get(f"{name}:{v['density']:g}" if "density" in v else f"{name}:{M}") if dt == szo.TILE_F16 else None
-        roof, upd, step_flops = rooflines(mats, M, t, one_product_kernel(mats, M), True, traffic)
+        roof, upd, step_flops = rooflines(mats, M, t, one_product_kernel(mats, M, makes_copies(szo, descs, szo.STEP_FUSED_LOSS)), True, traffic)
         row = {"M": M, "density": v.get("density", cfg["density"]), "matrices": len(mats),
                "ms_per_step": round(t["ms_per_step"], 4), "steps": t["steps"], "warmup": t["warmup"],
                "step_tflops": round(step_flops / (t["ms_per_step"] * 1e-3) / 1e12, 2),
@@ -193,8 +191,9 @@ def extra_workload(szo, torch, stack, name, seed, data_seed, dt, variants, steps
 def cpu_baseline_and_parity(szo, torch, mats, pristine, cfg, args, total_flops_per_step, dt):
     """The oracle, as it stands, on a bounded sample of the same workload (whole matrices in stack order,
     one full ZO step each, until the time budget is used), and the GPU path on the same sample (the same
-    matrices with their initial sparse values, one single-matrix fused step each through the C ABI):
-    the per-matrix losses and SPSA scalars of both sides, and the outputs of the first matrix, compared."""
+    matrices with their initial sparse values, through the C ABI): one single-matrix fused step each, whose losses and SPSA
+    scalars are compared with the oracle's matrix by matrix; the whole sample in one step, as the stack is timed (three Llama
+    blocks at 4096 tokens take the full stack's kernel, a single matrix does not); and the outputs of the first matrix."""
     import numpy as np
     sys.path.insert(0, os.path.join(ROOT, "tests"))
     from helpers import make_oracle_matrix, rel_fro
@@ -246,13 +245,21 @@ def cpu_baseline_and_parity(szo, torch, mats, pristine, cfg, args, total_flops_p
         mats[idx].sp_val.copy_(pristine[idx])
         szo.szo_zo_step([mats[idx].desc(dt, with_y=False)], args.seed, 0, cfg["eps"], 0.0, scal, ws, szo.STEP_FUSED_LOSS)
         got.append(scal.cpu().tolist())
-    ref, got = np.array(ref), np.array(got)
+    descs = szo.desc_array([m.desc(dt, with_y=False) for m in mats[:len(ref)]])
+    stack_kernel = SHARED_PRODUCT_KERNEL if makes_copies(szo, descs, szo.STEP_FUSED_LOSS) else None
+    szo.szo_zo_step(descs, args.seed, 0, cfg["eps"], 0.0, scal, ws, szo.STEP_FUSED_LOSS)
+    stack, ref, got = np.array(scal.cpu().tolist()), np.array(ref), np.array(got)
+    total = ref.sum(axis=0)
     parity = {"y_rel": y_rel,
               "loss_rel": float(np.max(np.abs(got[:, :2] - ref[:, :2]) / ref[:, :2])),
               "g_rel": float(np.linalg.norm(got[:, 2] - ref[:, 2]) / max(np.linalg.norm(ref[:, 2]), 1e-300)),
               "sample": f"the baseline's {len(ref)} matrices: y of one +eps forward of {used[0]} (relative Frobenius error), "
                         "per-matrix L+ and L- (largest relative error), per-matrix SPSA scalars g_i = (L+ - L-) / (2 eps) "
                         "(||g_gpu - g_oracle|| / ||g_oracle|| over the sample)",
+              "one_step": {"loss_rel": float(np.max(np.abs(stack[:2] - total[:2]) / total[:2])),
+                           "g_rel": float(abs(stack[2] - total[2]) / max(np.linalg.norm(ref[:, 2]), 1e-300)),
+                           "kernel": stack_kernel or one_product_kernel(mats[:len(ref)], M, False) or "two products",
+                           "sample": "the same matrices in one step: L+ and L- (relative error), g (|g_gpu - sum g_i| / ||g_i||)"},
               "tolerance": {"y_rel": 5e-3, "g_rel": 1e-2}}
     return base, parity
 
@@ -305,11 +312,12 @@ def main():
                     help="SZO_STEP_ONE_DENSE_PASS at any token count (the dense "
                          "product of a slice is computed once and serves both signs; valid because both forwards of a "
                          "layer see the same x in this benchmark).  Not the default: see include/szo.h")
-    ap.add_argument("--tile-config", type=int, default=0, choices=range(12),
+    ap.add_argument("--tile-config", type=int, default=0, choices=range(13),
                     help="0: the library chooses (few-token path for small token counts); 1 / 2: force the tiled kernel with "
                          "128x128 / 256x256 workgroup tiles; 3: as 2, and always one grouped launch per step; 4: as 0 "
                          "with 32 token rows per pass of the few-token path wherever there are more than 16; 8 / 9 / 11: the few-token "
-                         "path's split / stream kernel, the one-dense-pass kernel (all of them in include/szo.h; for comparisons)")
+                         "path's split / stream kernel, the one-dense-pass kernel; 12: the tiled kernel with one dense product "
+                         "(all of them in include/szo.h; for comparisons)")
     ap.add_argument("--seed", type=int, default=2024)
     ap.add_argument("--data-seed", type=int, default=0)
     ap.add_argument("--cpu-seconds", type=float, default=12.0, help="budget of the oracle baseline leg (0 = skip)")
@@ -390,15 +398,16 @@ def main():
     log(f"[bench] {ms_per_step:.3f} ms/step (events), {t['wall_ms_per_step']:.3f} ms/step (wall); "
         f"last step L+={lp:.6f} L-={lm:.6f} g={g:.4e}")
     one_product = None                   # with another tile type, K or configuration the label stays with the tiled kernel
-    if all(m.K % 128 == 0 for m in mats) and dt == szo.TILE_F16 and flags:
+    copies = makes_copies(szo, descs, flags)
+    if copies:
+        one_product = SHARED_PRODUCT_KERNEL
+    elif all(m.K % 128 == 0 for m in mats) and dt == szo.TILE_F16 and flags:
         if args.tile_config == 0:
-            one_product = one_product_kernel(mats, M, args.two_activation_sets, args.one_dense_pass)
+            one_product = one_product_kernel(mats, M, copies, args.two_activation_sets, args.one_dense_pass)
         elif args.tile_config in (4, 5, 7, 8, 9, 10) and (few_token_path(M, args.two_activation_sets) or args.one_dense_pass):
             one_product = "band_split_kernel" if args.tile_config == 8 else "small_m_kernel"
         elif args.tile_config == 11:
             one_product = "onepass_table_kernel"
-        elif args.tile_config == 12:
-            one_product = SHARED_PRODUCT_KERNEL
     traffic = MEASURED_TRAFFIC_BYTES.get(args.workload) if (
         args.layers is None and args.m is None and args.density is None and flags and dt == szo.TILE_F16
         and args.tile_config == 0 and args.format == "uniform" and not args.two_activation_sets
@@ -414,7 +423,7 @@ def main():
         try:
             d16 = descs_for(szo, mats, 16, dt, with_y=False)
             t16 = time_steps(szo, torch, d16, args.seed, eps, lr, flags, 200, 30, first_step=1000)
-            r16, u16, _ = rooflines(mats, 16, t16, one_product_kernel(mats, 16), True, MEASURED_TRAFFIC_BYTES.get("c3m16"))
+            r16, u16, _ = rooflines(mats, 16, t16, one_product_kernel(mats, 16, makes_copies(szo, d16, flags)), True, MEASURED_TRAFFIC_BYTES.get("c3m16"))
             extras["few_token"] = {"workload": f"the same {len(mats)} matrices at M=16 tokens (the first 16 rows of every x and target)",
                                    "ms_per_step": round(t16["ms_per_step"], 4), "value": round(1e3 / t16["ms_per_step"], 2),
                                    "unit": "ZO steps/s", "steps": 200, "warmup": 30, "roofline": r16, "sparse_update": u16}
@@ -429,7 +438,8 @@ def main():
         try:
             base, parity = cpu_baseline_and_parity(szo, torch, mats, pristine, cfg, args, step_flops, dt)
             log(f"[bench] oracle baseline: {base['value']:.3e} steps/s on {base['cores']} threads; parity {parity['y_rel']:.2e} (y), "
-                f"{parity['loss_rel']:.2e} (losses), {parity['g_rel']:.2e} (g)")
+                f"{parity['loss_rel']:.2e} (losses), {parity['g_rel']:.2e} (g); in one step {parity['one_step']['loss_rel']:.2e}, "
+                f"{parity['one_step']['g_rel']:.2e}")
         except Exception as e:      # noqa: BLE001
             base = {"error": f"{type(e).__name__}: {e}"}
             log(f"[bench] oracle baseline leg failed: {e}")
@@ -467,6 +477,7 @@ def main():
                    "activations": "x for +eps, x_minus for -eps" if args.two_activation_sets else "one x for both signs",
                    "tile": args.tile, "format": args.format, "accumulate": "f32", "loss_accumulate": "f64"},
         "step_tflops": round(step_flops / (ms_per_step * 1e-3) / 1e12, 2),
+        "step_flops_count": "the dense products of both forwards, executed or shared; roofline counts those that are executed",
         "step_frac_of_mfma_peak": round(step_flops / (ms_per_step * 1e-3) / 1e12 / PEAK_MFMA_16BIT_TFLOPS, 4),
         "roofline": roof,
         "sparse_update": upd,

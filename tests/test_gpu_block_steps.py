@@ -1,7 +1,7 @@
 """Whole ZO steps at the headline sizes against the oracle: one Llama-2-7B decoder block at 4096 tokens
 and one Mistral-7B block at 8192 tokens, through szo_zo_step exactly as bench.py calls it (library's
-choice of kernel, loss fused, one grouped forward launch, one grouped update).  The Llama block and the densest mask take two full
-products per layer, the Mistral block at 0.1 % the dense product once and the sensitive ones behind it, as the benchmark's full stack of
+choice of kernel, loss fused, one grouped forward launch, one grouped update).  The Llama block and the steps of four matrices take two
+full products per layer, the whole Mistral block the dense product once and the sensitive ones behind it, as the benchmark's full stack of
 Llama blocks does.  At these sizes
 L+ - L- is about 1e-6 of L (Definition 1 divides that difference by 2 eps), so this is where an fp32 loss
 sum, a 16-bit y or a dropped entry would show in g.  Every setup array is first compared bit for bit
