@@ -64,12 +64,14 @@ extern "C" {
  *   measures them with szo_activation_absmax() and takes what szo_choose_tile_dtype() returns.
  *   SZO_TILE_BF16 stages the activations unchanged (full bf16 range); the sensitive values are then
  *   rounded to 8 significant bits, which costs about 1-2 % of sigma_g on the SPSA scalar.
- * The kernels round to this type in two ways, and which of them runs a call depends on its sizes, the format, the
+ * The kernels round to this type in three ways, and which of them runs a call depends on its sizes, the format, the
  * density of the mask, the entry point and, for single forwards, on whether there is a perturbation:
  *   - as ONE weight tile: dq is rounded, then dq + (v + eps z) and dq + (v - eps z) are (tiled kernel; the
  *     few-token kernels for layers with the bf16 tile or K an odd multiple of 64);
  *   - v and z one by one, eps applied in fp32 (the other few-token launches, the one-dense-pass kernel), which
- *     leaves less error in g; dq itself is not rounded there with the fp16 tile and groups of 128.
+ *     leaves less error in g; dq itself is not rounded there with the fp16 tile and groups of 128;
+ *   - dq, then dq + v as one weight, and z by itself, eps applied in fp32 (the tiled kernel with one dense product,
+ *     in large steps): the error in g of the second way (where codes under sensitive entries are not 8, up to 1.4 times).
  * Results of the same layer on two kernels therefore agree to these roundings, not to fp32 summation order: outputs
  * to about 2^-11 (fp16 tile) or 2^-8 (bf16) relative, g to 1-2 % of sigma_g with the bf16 tile. */
 #define SZO_TILE_F16   0
@@ -162,28 +164,35 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
 /* One whole step over `n` layers: for every layer a +eps forward and a -eps forward, each
  * followed by its loss with scale 1/(M*N); then g; then the update of every layer.
  * scalars: device double[3], overwritten with (L+, L-, g).  flags: bit 0 set = use the
- * loss-fusing forward and never write y (desc->y may then be NULL); large steps then run all
- * forwards (every layer, both signs) as one launch driven by a descriptor table that is staged in
- * the workspace.  Both forwards of a layer with one set of activations see the same x, so y(+-) = x (dq + v)^T +- eps x z^T: such
- * steps compute the dense product once for both signs where that is the faster way, and add the sparse products.  Few
- * tokens, or launches of so few workgroups that any tile would outlast them, stream the weights once per 16 to 48 token rows; the
- * others run on the matrix cores in tiles of 64 token rows, if
- * the layers are of the uniform format with one tile type, fill the chip, and their masks are sparse (against the tiled kernel up to
- * about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 % with the bf16 tile or K an odd multiple of 64).  Steps of more than 4096 output tiles of 256 x 256 that those rules leave (a block at 8192
- * tokens, several at 4096), and larger ones of 512 tiles and tokens on with the bf16 tile or groups other than 128, compute the dense product of such layers in tiles of that size, with weights rounded once to the tile's type, and the sensitive products behind
- * it, with masks of up to about 0.6 % (less with few rows of W or a short K): a copy of the activations in the workspace, 64 tokens of
- * a column side by side, serves them, and the step goes in launches of as many layers as it has room for (1 GiB).  Otherwise, and beyond 2048
- * tokens in steps of more than 2048 output tiles of 256 x 128, each layer runs as two full products, as the single-layer
- * calls compute them; the results are the same up to the roundings described at SZO_TILE_F16.  The tiles are counted over
+ * loss-fusing forward and never write y (desc->y may then be NULL); large steps then run the
+ * forwards of all layers in one launch, or a few, driven by a descriptor table that is staged in
+ * the workspace.  Both forwards of a layer with one set of activations see the same x, so
+ * y(+-) = x (dq + v)^T +- eps x z^T: such steps compute the dense product once for both signs where
+ * that is the faster way, and add the sparse products:
+ *   - few tokens, or launches of so few workgroups that any tile would outlast them: the weights are
+ *     streamed once per 16 to 48 token rows;
+ *   - others, up to 2048 tokens or 2048 output tiles of 256 x 128: on the matrix cores in tiles of 64
+ *     token rows, if the layers are of the uniform format with one tile type, fill the chip, and their
+ *     masks are sparse (against the tiled kernel up to about 0.4 %, beyond 512 tokens 0.3 %, there 0.2 %
+ *     with the bf16 tile or K an odd multiple of 64);
+ *   - of those, with the bf16 tile or groups other than 128, steps of more than 512 tokens and at least
+ *     512 output tiles of 256 x 256 (masks up to about 0.3 %), and of the steps that are left those of
+ *     more than 4096 such tiles (a block at 8192 tokens, several at 4096; masks up to about 0.6 %): in
+ *     tiles of that size, dq + v rounded once to the tile's type, the sensitive products behind them.
+ *     They read a copy of the activations in the workspace, 64 tokens of a column side by side, and the
+ *     step goes in launches of as many layers as there is room for (1 GiB).
+ * Otherwise each layer runs as two full products, as the single-layer calls compute them; the results
+ * are the same up to the roundings described at SZO_TILE_F16.  The tiles are counted over
  * the step as a whole: the same layers in several smaller steps may be computed the other way, to the same roundings.
  * With bit 0 clear y holds the -eps forward's outputs afterwards, and the loss is summed in fp64 from the
  * fp32 outputs; layers of the uniform format with one tile type, one set of activations, masks of up to 1.5 % and no
  * output buffer in common with another layer run as one launch there too.
  * descs: host array, read before the call returns.  Everything is enqueued on `stream`.  The
- * descriptor tables of the grouped launches (forwards of a step; the update), except those of up to eight layers
- * on the few-token path and in the update and of up to sixteen in the other forwards, which are kernel arguments, travel through a ring of eight pinned host buffers per host thread (allocated on first use,
- * released when the thread ends); a call waits on the host only if a copy issued eight tables
- * earlier on this thread (four tiled steps) has not executed yet.  Because of those buffers NO
+ * descriptor tables of a step's forwards and of its update (two at most), except those of up to eight
+ * layers on the few-token path and in the update and of launches of up to sixteen in the other forwards,
+ * which are kernel arguments, travel through a ring of eight pinned host buffers per host thread
+ * (allocated on first use, released when the thread ends); a call waits on the host only if a copy
+ * issued eight tables earlier on this thread (four tiled steps) has not executed yet.  Because of those buffers NO
  * variant of this call can be captured into a HIP graph: it returns SZO_EUNSUPPORTED, with nothing
  * enqueued, while `stream` is capturing.  The single-layer calls above are plain launches and can
  * be captured.  The workspace must not be shared with a call running concurrently on another
@@ -192,8 +201,9 @@ int szo_sparse_update(float* sp_val, const uint32_t* sp_idx, int64_t nnz, uint64
 /* Bit 1 (with bit 0): one dense product per layer in larger steps, with denser masks and in steps of few workgroups too: half the
  * dense work, same results up to the roundings above.  A step keeps two products all the same where its layers have a
  * second set of activations or where it loses by it (bf16 tile or K an odd multiple of 64 with masks of about 1 % and
- * more, where the sparse products cost what the second dense product does).  Not the default for large steps, which take one
- * dense product in larger tiles where that pays: with the fp16 tile and groups of 128 this one applies the group scales in fp32. */
+ * more, where the sparse products cost what the second dense product does).  Not the default for large steps, which
+ * take one dense product in larger tiles where that pays: with the fp16 tile and groups of 128 this one
+ * applies the group scales in fp32, and is slower in steps of that size. */
 #define SZO_STEP_ONE_DENSE_PASS 2
 /* Bit 2: the workspace ends before the copies of activations (szo_step_workspace_bytes with n == 0): large steps that would
  * make them take tiles of 64 token rows or two full products instead, to the same roundings. */
@@ -300,7 +310,8 @@ int szo_choose_tile_dtype(float x_absmax);
 
 /* Timing of the forward kernels (tiled, few-token and one-dense-pass) for benchmarks.
  * szo_kernel_timing(1) makes every later forward-kernel launch record a pair of events around
- * itself on the stream it is launched on; szo_kernel_timing(0) stops that.  Either call drops
+ * itself on the stream it is launched on (a step with one dense product in large tiles one pair around its
+ * copies and launches); szo_kernel_timing(0) stops that.  Either call drops
  * what was recorded.  szo_kernel_timing_read() waits for the recorded launches, returns the sum
  * of their durations in milliseconds and their number, and starts a new collection.  Process-
  * wide state, for one measuring thread; events are created on demand and kept. */
@@ -333,8 +344,8 @@ int szo_debug_zbar(uint64_t nnz_base, int64_t nnz, uint64_t seed, uint64_t step,
  * of token rows per strip (by default only when the launch streams more codes than the last-level cache
  * holds), 8 / 9 = as 0 and the few-token path takes its kernel for small launches (K split over the waves of
  * a workgroup) always / never, 10 = 9 and 7, 11 = szo_zo_step takes the kernel that computes one dense
- * product per layer in tiles of 64 token rows wherever it can (chosen by size with 0, never with 1 to 10), 12 = the one that does so in
- * tiles of 256 x 256 wherever it can (likewise; never with 11).
+ * product per layer in tiles of 64 token rows wherever it can (chosen by size with 0, never with 1 to 10),
+ * 12 = the one that does so in tiles of 256 x 256 wherever it can (likewise; never with 11).
  * Process-wide, not thread-safe.  Results depend on it by the roundings described at SZO_TILE_F16 and by fp32
  * summation order. */
 int szo_set_tile_config(int config);

@@ -1228,14 +1228,15 @@ static bool onepass_rounds(const szo_linear_desc& d) { return d.tile_dtype == SZ
 // to four to eight layers of 4096 x K at 4096 tokens, us per step, two products -> one: K = 256 / 1024 / 4096 at 0.1 % 212 / 497 / 843 -> 212 / 390 / 570,
 // at 0.4 % 212 / 508 / 872 -> 219 / 433 / 726, at 1 % 211 / 517 / 910 -> 238 / 610 / 1009.  The line is drawn for masks with rows full of
 // entries, whose bands take longer (a Llama block with half of them in 1 % of the rows, 0.4 % / 1 %: 2668 / 2956 -> 2498 / 4204).
-// Only in steps of more than 16 rounds of workgroups: the losses of smaller ones are promised to be the single-layer calls'
-// up to the order of the partial sums, so that a block can be checked against those calls, which a weight rounded together with its
-// perturbation makes true and D +- eps Z does not (1e-9 of the loss apart).  It is no limit of the kernel: one Llama block at 4096 tokens, the
-// largest below the line that is checked like that, 2630 -> 1750.  Beyond it a Mistral block at 8192 tokens and 0.1 % / 0.4 % 5507 / 5612 -> 3535 / 4486.
-// `instead_of_onepass`: of a step that the kernel with tiles of 64 token rows would take, where that one rounds weights to the tile's type
+// Only in steps of more than 4096 tiles, 16 rounds of workgroups.  That line is not where the two cost the same: one Llama block at 4096
+// tokens (2656 tiles) would take 1750 us instead of 2630.  Up to it a step keeps the single-layer calls' roundings, to whose losses a block's
+// are compared at 1e-12 (tests/test_gpu_full_size.py), which a weight rounded together with its perturbation makes true and D +- eps Z does not
+// (1e-9 of the loss apart).  Beyond it, two products -> here: a Mistral block at 8192 tokens and 0.01 / 0.1 / 0.4 / 0.55 % 5572 / 5623 / 5820 /
+// 5866 -> 3305 / 3612 / 4545 / 4945, two Llama blocks at 4096 and 0.1 / 0.4 % 5391 / 5506 -> 3425 / 4246.
+// `instead_of_onepass`: of a step that the kernel with tiles of 64 token rows takes otherwise, where that one rounds weights to the tile's type
 // too (bf16 tile, groups other than 128).  From 512 tiles and tokens on, with a third of the second product to spare: bf16 tile, 0.1 %,
-// there -> here: one Llama block at 768 / 1000 / 2048 tokens 473 / 601 / 1184 -> 384 / 467 / 864, four OPT blocks at 520 / 1300 1374 / 3113 ->
-// 1180 / 2351, 0.3 % at 2048 tokens 1407 -> 1030; groups of 64 likewise 435 / 545 / 1063 -> 375 / 460 / 843, 1225 / 2783 -> 1156 / 2284, 1289 -> 1000.
+// there -> here: one Llama block at 1000 / 2048 tokens 626 / 1208 -> 471 / 878, four OPT blocks at 520 / 1300 1416 / 3201 -> 1208 / 2428; groups
+// of 64 likewise 561 / 1082 -> 463 / 869, 1264 / 2850 -> 1201 / 2462, one Llama block with 0.3 % at 2048 1302 -> 1034.
 // Fewer tiles: one OPT block at 768 tokens (432) 410 -> 446, a layer of 4096 x 4096 at 2048 (128) 96 -> 117.
 static bool shared_pays(const szo_linear_desc* descs, int n, bool instead_of_onepass) {
   double tiles = 0.0, second = 0.0, here = 0.0;             // tiles: of 256 x 256 outputs, one workgroup each
