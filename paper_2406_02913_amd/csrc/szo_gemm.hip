@@ -1303,15 +1303,16 @@ struct SharedPlan {
 // Both forwards of every matrix with the dense product computed once (szo_shared.h), the loss fused: launches of 256 x 256 tiles, each behind
 // the copies of its layers' activations in the order that its sensitive products read them.
 // SZO_EUNSUPPORTED, with nothing enqueued, when the stack does not qualify.
-static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t step, float eps, void* table_dev, void* copies,
-                           double* partials, int64_t* partials_per_sign, hipStream_t stream) {
+static int shared_forwards(const szo_linear_desc* descs, int n, bool instead_of_onepass, uint64_t seed, uint64_t step, float eps, void* table_dev,
+                           void* copies, double* partials, int64_t* partials_per_sign, hipStream_t stream) {
   constexpr int tile = 256;
   static thread_local SharedPlan plan;
   if (!plan.make(descs, n)) return SZO_EUNSUPPORTED;        // reject everything before anything is enqueued
   const int64_t T = plan.tiles;
   const bool f16 = descs[0].tile_dtype == SZO_TILE_F16;
-  // Steps that the one-dense-pass kernel would take have its sums, one by one in fp64: the layers that tell them apart.
-  bool fp64_sums = true;
+  // Steps that the one-dense-pass kernel would take have its sums, one by one in fp64; the others those of two products (a step of 9.1 ms
+  // with rounded weights 1.3 % less).  Forced: by what tells the layers apart.
+  bool fp64_sums = instead_of_onepass || g_tile_config == 12;
   for (int i : plan.layers) fp64_sums = fp64_sums && onepass_rounds(descs[i]);
   // One table for the whole step, staged once: the host runs as many steps ahead as with one launch.
   static thread_local std::vector<FwdParams> table;
@@ -1368,9 +1369,10 @@ static int shared_forwards(const szo_linear_desc* descs, int n, uint64_t seed, u
     }
     static thread_local ForwardTableArgs t;
     use_table(table.data() + first, end_of(l) - first, (const FwdParams*)table_dev + first, t);
-    rc = !f16      ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, blocks[l], stream)
-         : fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, blocks[l], stream)
-                     : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, blocks[l], stream);
+    rc = f16 ? (fp64_sums ? launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, blocks[l], stream)
+                          : launch_table<SZO_TILE_F16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, blocks[l], stream))
+             : (fp64_sums ? launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kSharedFp64Sums>(t, blocks[l], stream)
+                          : launch_table<SZO_TILE_BF16, SZO_FORMAT_UNIFORM, 256, false, kShared>(t, blocks[l], stream));
   }
   if (rc != SZO_OK) return rc;
   *partials_per_sign = T;
@@ -1567,7 +1569,7 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   // the tiled kernel).
   {
     int64_t T = 0;
-    rc = route.instead_of_onepass ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
+    rc = route.instead_of_onepass ? shared_forwards(descs, n, true, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
     if (rc == SZO_EUNSUPPORTED)
       rc = onepass_forwards(descs, n, seed, step, eps, route.few_rule, route.asked_for, !fuse, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK) return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);
@@ -1579,7 +1581,7 @@ int szo_zo_step(const szo_linear_desc* descs, int n, uint64_t seed, uint64_t ste
   }
   if (fuse) {
     int64_t T = 0;
-    rc = route.instead_of_two ? shared_forwards(descs, n, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
+    rc = route.instead_of_two ? shared_forwards(descs, n, false, seed, step, eps, table_dev, copy_area(workspace), partial_area(workspace), &T, s) : SZO_EUNSUPPORTED;
     if (rc == SZO_EUNSUPPORTED) rc = grouped_forwards(descs, n, seed, step, eps, table_dev, partial_area(workspace), &T, s);
     if (rc == SZO_OK)
       return update_all(descs, n, seed, step, eps, lr, scalars, partial_area(workspace), T, table_dev, s);

@@ -186,6 +186,19 @@ def test_chosen_from_512_tiles_on_where_both_kernels_round_the_weights(group, ti
         assert np.array_equal(chosen, asked.cpu().numpy())
 
 
+@pytest.mark.parametrize("group,tile", [(128, "bf16"), (64, "f16")])
+def test_steps_beyond_4096_tiles_keep_the_sums_of_two_products(group, tile):
+    """... sixteen at a time in fp32 whatever the layers; forced on such layers, the kernel adds them one by one in fp64."""
+    descs, keep = _stack(885, 29, 2304, 4096, 1024, 1e-3, True, group, szo.TILE_BF16 if tile == "bf16" else szo.TILE_F16)
+    chosen, forced, two = _step(descs, 0), _step(descs, 12), _step(descs, 6)
+    assert not np.array_equal(chosen, forced) and np.allclose(chosen[:2], forced[:2], rtol=1e-8, atol=0.0)
+    # 4e-9 of both losses at most, their difference is summed as such; against two products as test_step_matches_oracle
+    sigma = _sigma_of_stack(descs, keep)
+    assert abs(chosen[2] - forced[2]) <= 1e-3 * sigma
+    assert np.allclose(chosen[:2], two[:2], rtol=1e-5 if tile == "f16" else 1e-3, atol=0.0)
+    assert abs(chosen[2] - two[2]) <= (1e-2 if tile == "f16" else 1e-1) * max(abs(two[2]), sigma)
+
+
 @pytest.mark.parametrize("tile", ["f16", "bf16"])
 @pytest.mark.parametrize("M,N", [(256, 512), (300, 520), (70, 257)])        # whole tiles, ragged ones, targets that are not staged
 def test_losses_are_added_in_fp64(M, N, tile):

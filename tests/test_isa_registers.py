@@ -67,7 +67,7 @@ def test_the_tiled_kernels_keep_their_main_loops_in_registers(tmp_path):
     text = open(out).read()
     scratch = {name: int(size) for name, size in re.findall(r"\.name:\s+(\S*linear_fwd_table_kernel\S*)\s+\.private_segment_fixed_size: (\d+)", text)}
     shared = [name for name in scratch if re.search(r"Li16ELi[12]EEEv", name)]
-    assert len(shared) == 3 and len(scratch) > 3
+    assert len(shared) == 4 and len(scratch) > 3
     assert all(size == 0 for name, size in scratch.items() if name not in shared), scratch
     for name in shared:
         blocks = _blocks(text, name)
